@@ -120,11 +120,12 @@ def _check(status: int, where: str):
 
 
 def _ptr(t: Optional[torch.Tensor]):
+    # plain integers: the argtypes of every entry point turn them into pointers
     if t is None:
         return None
-    if not t.is_cuda or not t.is_contiguous():
+    if not (t.is_cuda and t.is_contiguous()):
         raise ValueError("device entry points take contiguous tensors on the GPU")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _dt(t: torch.Tensor) -> int:
@@ -135,9 +136,11 @@ def _dt(t: torch.Tensor) -> int:
     raise ValueError(f"unsupported element type {t.dtype}")
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream(stream):
+    if stream is not None:
+        return stream.cuda_stream
+    # the raw handle, without a Stream object around it: a merge-layer call of a short sequence takes tens of microseconds
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 # ---- host-only helpers ------------------------------------------------------------------------
