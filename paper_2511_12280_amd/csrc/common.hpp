@@ -49,6 +49,43 @@ __device__ __forceinline__ float wave_sum(float v) {
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, WAVE));
+// Dot product of two rows of n elements (16-byte aligned, n a multiple of the elements per 16 bytes), chunks c0, c0 + step, ...:
+// 16-byte loads, eight chunks requested before the first is used, float32 accumulation in that order.  For the
+// generic kernels, whose time is load latency: one scalar load per multiply made them 10-50 times slower.
+template <typename T>
+__device__ __forceinline__ float chunk_dot(const uint4& a, const uint4& b, float acc) {
+    const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if constexpr (sizeof(T) == 2) {
+            acc = __builtin_fmaf(bf16_lo(aw[e]), bf16_lo(bw[e]), acc);
+            acc = __builtin_fmaf(bf16_hi(aw[e]), bf16_hi(bw[e]), acc);
+        } else {
+            acc = __builtin_fmaf(__uint_as_float(aw[e]), __uint_as_float(bw[e]), acc);
+        }
+    }
+    return acc;
+}
+template <typename T>
+__device__ __forceinline__ float row_dot(const T* __restrict__ a, const T* __restrict__ b, int n, int c0 = 0, int step = 1) {
+    const uint4* pa = reinterpret_cast<const uint4*>(a);
+    const uint4* pb = reinterpret_cast<const uint4*>(b);
+    const int nch = n / (int)(16 / sizeof(T));
+    float acc = 0.f;
+    for (int c = c0; c < nch; c += 8 * step) {
+        uint4 x[8], y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const bool ok = c + u * step < nch;
+            x[u] = ok ? pa[c + u * step] : make_uint4(0, 0, 0, 0);
+            y[u] = ok ? pb[c + u * step] : make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc = chunk_dot<T>(x[u], y[u], acc);
+    }
+    return acc;
+}
+
     return v;
 }
 __device__ __forceinline__ int wave_sum_i(int v) {

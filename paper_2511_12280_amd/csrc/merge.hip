@@ -404,7 +404,10 @@ __global__ __launch_bounds__(256) void cos_reduce_argmax(
     }
 }
 
-// ---- cosine + argmax, generic: one workgroup per pruned row, waves stride over the kept slots ---
+// ---- cosine + argmax, generic: one workgroup per pruned row ---
+// 16 groups of 16 lanes, each takes every 16th kept slot: 16-byte loads and a reduction inside a data-parallel row of
+// 16 lanes (a whole wave per slot with scalar loads and a 64-lane reduction: 10 us at 108 x 36 rows of 256 floats, launch
+// included; this 6 us).
 template <typename T>
 __global__ __launch_bounds__(256) void cos_argmax_generic(
     const T* __restrict__ f, int d, const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_start,
@@ -414,27 +417,24 @@ __global__ __launch_bounds__(256) void cos_argmax_generic(
     const int p = blockIdx.x, b = blockIdx.y;
     const SampleGeom s = sample_geom(b, seq_off, vis_start, vis_count, kept_off, max_V, max_keep);
     if (p >= s.M) return;
-    __shared__ float2 red[4];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    __shared__ float2 red[16];
+    const int grp = threadIdx.x >> 4, l16 = threadIdx.x & 15;
     const int m = min(max(pruned[(size_t)b * max_V + p], 0), s.V - 1);
     const int32_t* kp = kept_idx + kept_off[b];
     const float* rn = rnorm + (size_t)b * max_V;
     const T* xm = f + (size_t)(s.tok0 + s.vs + m) * d;
     float bv = -INFINITY; int bi = 0x7FFFFFFF;
-    for (int r = wave; r < s.k; r += 4) {
+    for (int r = grp; r < s.k; r += 16) {
         const int j = min(max(kp[r], 0), s.V - 1);
-        const T* xk = f + (size_t)(s.tok0 + s.vs + j) * d;
-        float dot = 0.f;
-        for (int cidx = lane; cidx < d; cidx += 64) dot += Elem<T>::load(xm + cidx) * Elem<T>::load(xk + cidx);
-        dot = wave_sum(dot);
+        const float dot = row16_sum(row_dot<T>(xm, f + (size_t)(s.tok0 + s.vs + j) * d, d, l16, 16));
         const float v = dot * rn[rn_by_token ? j : r];        // the pruned row's own norm scales all its candidates alike
         if (v > bv) { bv = v; bi = r; }
     }
-    if (lane == 0) red[wave] = make_float2(bv, __int_as_float(bi));
+    if (l16 == 0) red[grp] = make_float2(bv, __int_as_float(bi));
     __syncthreads();
     if (threadIdx.x == 0) {
         float2 a = red[0];
-        for (int w = 1; w < 4; ++w) {
+        for (int w = 1; w < 16; ++w) {
             const float2 c2 = red[w];
             if (c2.x > a.x || (c2.x == a.x && __float_as_int(c2.y) < __float_as_int(a.y))) a = c2;
         }
@@ -443,7 +443,8 @@ __global__ __launch_bounds__(256) void cos_argmax_generic(
 }
 
 // ---- scatter-average + compaction ----------------------------------------------------------
-// One workgroup per output row.  A merged row first finds its members: the four waves scan the
+// One workgroup per output row (a launch sized for fewer rows than a sample has takes the rest in further turns).  A merged
+// row first finds its members: the four waves scan the
 // table of the sample (a quarter each, coalesced; the low word of an entry names the slot, and the kept
 // token's own entry makes it a member like the others), keep the matches in ascending token
 // order (ballot + popcount, no atomics) and the four pieces are joined into one list in LDS; the
