@@ -50,7 +50,7 @@ __host__ inline ImpWs imp_ws_layout(int B, int max_N, int max_V, int H, int max_
     w.c_off = o;    o += align_up((size_t)B * H * max_D * sizeof(float), 256);   // generic path
     w.NKB = w.NCH * (w.KC / 16);
     w.logit_off = o;                                                              // kept logits (small decider sets)
-    if (max_D <= IMP_KEEP_MAXD_WS) o += align_up((size_t)B * w.NKB * H * w.DPAD * 16 * sizeof(float), 256);
+    if (max_D <= IMP_KEEP_MAXD_WS) o += align_up((size_t)B * w.NKB * H * max_D * 16 * sizeof(float), 256);
     w.total = o;
     return w;
 }
@@ -139,9 +139,11 @@ __global__ __launch_bounds__(256) void imp_stats_bf16(
                 if constexpr (KEEP) {
                     // [key block][head][decider][key in block]: the 16 lanes of a decider row write 64 contiguous bytes
                     const int kb = (key_base >> 4) + wave * IMP_SUB_STATS + s;
-                    float* lp = logits + (((size_t)(b * NKB + kb) * H + h) * DPAD + (db0 + nb) * 16 + 4 * g) * 16 + r;
+                    const int row0 = (db0 + nb) * 16 + 4 * g;
+                    float* lp = logits + (((size_t)(b * NKB + kb) * H + h) * max_D + row0) * 16 + r;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) lp[e * 16] = l2[s][e];
+                    for (int e = 0; e < 4; ++e)
+                        if (row0 + e < D) lp[e * 16] = l2[s][e];
                 }
             }
             // max over this wave's 64 keys first (in-lane, then the 16 key columns), then one exp2 per logit
@@ -267,8 +269,11 @@ __global__ __launch_bounds__(256) void imp_scores_bf16(
 // contiguous H x D x 64 bytes, subtracts each (head, decider) row's log-sum-exp and adds the exponentials
 // over deciders and heads, so the mean over heads is finished in the same pass (no per-head rows, no
 // third launch, K fetched once).
+// Bound by the chain metadata -> statistics -> exponentials -> reduction, so it has 16 waves: every thread holds one or two
+// (head, decider) rows of the statistics and at most 16 logits at 32 heads x 32 deciders, all requested at once.
 constexpr int IMP_KEEP_MAXD = IMP_KEEP_MAXD_WS;
-__global__ __launch_bounds__(256) void imp_scores_from_logits(
+constexpr int IMP_FL_THREADS = 1024, IMP_FL_GROUPS = IMP_FL_THREADS / 16, IMP_FL_ROWS = 16;
+__global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     int H, const int32_t* __restrict__ seq_off, const int32_t* __restrict__ dec_off,
     const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count, const int32_t* __restrict__ score_off,
     int max_D, int max_V, int DPAD, int NCH, int KC, int NKB, const float2* __restrict__ part, const float* __restrict__ logits,
@@ -279,25 +284,24 @@ __global__ __launch_bounds__(256) void imp_scores_from_logits(
     const int vs = min(max(vis_start[b], 0), N);
     const int V = min(min(vis_count[b], max_V), N - vs);
     const int key0 = kb * 16;
-    if (D <= 0 || key0 >= vs + V || key0 + 16 <= vs || key0 >= N) return;
-    extern __shared__ float c_lds[];                    // [H][DPAD] log2-sum-exp2, +inf for padded decider rows
-    __shared__ float red[16][16];
-    constexpr int NBK = IMP_KEEP_MAXD / 16;             // 16-decider blocks a kept set can have
-    const int nblk = (D + 15) >> 4;                     // decider blocks the first sweep has written
-    // thread (key = t % 16, group = t / 16) takes decider row 16 ib + group of every head: the 256 threads
-    // read whole 1 KB blocks of logits.  All loads of up to 32 heads are requested before anything else, so
-    // their latency (the logits come from another XCD's writes, i.e. from memory) overlaps the statistics below.
+    extern __shared__ float c_lds[];                    // [H][max_D] log2-sum-exp2, +inf for rows past the sample's deciders
+    __shared__ float red[IMP_FL_THREADS / 64][16];
+    // thread (key = t % 16, group = t / 16) takes rows group, group + 64, ... of the block's H x max_D logit rows: 64
+    // consecutive rows are 4 KB in one piece.  They are requested before anything else, so that their latency (they come
+    // from another XCD's writes, i.e. from memory) overlaps the statistics below.
     const int key = threadIdx.x & 15, grp = threadIdx.x >> 4;
-    const float* lb = logits + ((size_t)(b * NKB + kb) * H) * DPAD * 16 + (size_t)grp * 16 + key;
-    float l[32][NBK];
+    const int rows = H * max_D;
+    const float* lb = logits + ((size_t)(b * NKB + kb) * rows) * 16 + key;
+    float l[IMP_FL_ROWS];
 #pragma unroll
-    for (int h = 0; h < 32; ++h)
-#pragma unroll
-        for (int ib = 0; ib < NBK; ++ib)
-            l[h][ib] = (h < H && ib < nblk) ? lb[((size_t)h * DPAD + ib * 16) * 16] : -INFINITY;
+    for (int u = 0; u < IMP_FL_ROWS; ++u) {
+        const int row = grp + u * IMP_FL_GROUPS;
+        l[u] = (row < rows) ? lb[(size_t)row * 16] : 0.f;
+    }
+    if (D <= 0 || key0 >= vs + V || key0 + 16 <= vs || key0 >= N) return;
     const int nch = min((N + KC - 1) / KC, NCH);
-    for (int t = threadIdx.x; t < H * nblk * 16; t += 256) {
-        const int h = t / (nblk * 16), i = t - h * (nblk * 16);
+    for (int t = threadIdx.x; t < rows; t += IMP_FL_THREADS) {
+        const int h = t / max_D, i = t - h * max_D;
         float c = INFINITY;
         if (i < D) {
             const float2* p = part + ((size_t)(b * H + h) * NCH) * DPAD + i;
@@ -312,35 +316,35 @@ __global__ __launch_bounds__(256) void imp_scores_from_logits(
             }
             c = m + __builtin_amdgcn_logf(z);
         }
-        c_lds[h * DPAD + i] = c;
+        c_lds[t] = c;
     }
     __syncthreads();
     float acc = 0.f;
+    auto add_row = [&](int row, float v) {
+        // a row past the sample's deciders was never written: whatever it holds must not reach the sum
+        const float c = (row < rows) ? c_lds[row] : INFINITY;
+        acc += (c < INFINITY) ? __builtin_amdgcn_exp2f(v - c) : 0.f;
+    };
 #pragma unroll
-    for (int h = 0; h < 32; ++h)
+    for (int u = 0; u < IMP_FL_ROWS; ++u) add_row(grp + u * IMP_FL_GROUPS, l[u]);
+    for (int r0 = IMP_FL_ROWS * IMP_FL_GROUPS; r0 < rows; r0 += IMP_FL_ROWS * IMP_FL_GROUPS) {     // more than 1024 rows
 #pragma unroll
-        for (int ib = 0; ib < NBK; ++ib)
-            if (h < H && ib < nblk) acc += __builtin_amdgcn_exp2f(l[h][ib] - c_lds[h * DPAD + ib * 16 + grp]);
-    for (int h0 = 32; h0 < H; h0 += 32) {               // more than 32 heads: the same, 32 heads at a time
-        float l2[32][NBK];
+        for (int u = 0; u < IMP_FL_ROWS; ++u) {
+            const int row = r0 + grp + u * IMP_FL_GROUPS;
+            l[u] = (row < rows) ? lb[(size_t)row * 16] : 0.f;
+        }
 #pragma unroll
-        for (int h = 0; h < 32; ++h)
-#pragma unroll
-            for (int ib = 0; ib < NBK; ++ib)
-                l2[h][ib] = (h0 + h < H && ib < nblk) ? lb[((size_t)(h0 + h) * DPAD + ib * 16) * 16] : -INFINITY;
-#pragma unroll
-        for (int h = 0; h < 32; ++h)
-#pragma unroll
-            for (int ib = 0; ib < NBK; ++ib)
-                if (h0 + h < H && ib < nblk) acc += __builtin_amdgcn_exp2f(l2[h][ib] - c_lds[(h0 + h) * DPAD + ib * 16 + grp]);
+        for (int u = 0; u < IMP_FL_ROWS; ++u) add_row(r0 + grp + u * IMP_FL_GROUPS, l[u]);
     }
-    red[grp][key] = acc;
+    acc += __shfl_xor(acc, 16, WAVE);
+    acc += __shfl_xor(acc, 32, WAVE);
+    if ((threadIdx.x & 63) < 16) red[threadIdx.x >> 6][key] = acc;
     __syncthreads();
     const int j = key0 + (int)threadIdx.x - vs;          // visual index of key threadIdx.x of this block
     if (threadIdx.x < 16 && j >= 0 && j < V) {
         float sum = 0.f;
 #pragma unroll
-        for (int gq = 0; gq < 16; ++gq) sum += red[gq][threadIdx.x];      // groups in ascending order
+        for (int w = 0; w < IMP_FL_THREADS / 64; ++w) sum += red[w][threadIdx.x];      // waves in ascending order
         scores[score_off[b] + j] = sum / (float)H;
     }
 }
@@ -402,14 +406,14 @@ __global__ __launch_bounds__(256) void imp_stats_generic(
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void imp_scores_generic(
-    const T* __restrict__ q, const T* __restrict__ k, int H, int dh, float scale2,
-    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ dec_idx, const int32_t* __restrict__ dec_off,
 // One workgroup per 8 visual keys: thread = (key, one of 32 groups), the groups take the (head, decider) pairs in turn,
 // 16-byte loads.  (One thread per key looping over every head, decider and channel was one serial chain of H * D * dh
 // scalar loads on a single compute unit: 363 us at 144 keys x 4 heads x 16 deciders x 64; this takes 7.7 us.)
 constexpr int IMG_KEYS = 8, IMG_GROUPS = 256 / IMG_KEYS;
+template <typename T>
+__global__ __launch_bounds__(256) void imp_scores_generic(
+    const T* __restrict__ q, const T* __restrict__ k, int H, int dh, float scale2,
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ dec_idx, const int32_t* __restrict__ dec_off,
     const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count, const int32_t* __restrict__ score_off,
     int max_D, int max_V, const float* __restrict__ cws, float* __restrict__ scores) {
     const int b = blockIdx.y;
@@ -494,7 +498,7 @@ int d3tom::importance_run(const void* q, const void* k, int dt,
 #undef D3TOM_IMP_STATS
         if (keep) {
             const dim3 g2k(ceil_div(max_N, 16), B);
-            D3TOM_LAUNCH(IMP_SCORES, st, imp_scores_from_logits<<<g2k, 256, (size_t)H * w.DPAD * sizeof(float), st>>>(
+            D3TOM_LAUNCH(IMP_SCORES, st, imp_scores_from_logits<<<g2k, IMP_FL_THREADS, (size_t)H * max_D * sizeof(float), st>>>(
                 H, seq_off, dec_off, vis_start, vis_count, score_off, max_D, max_V, w.DPAD, w.NCH, w.KC, w.NKB, part, logits,
                 scores));
             return D3TOM_OK;
