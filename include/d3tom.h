@@ -356,8 +356,8 @@ int d3tom_rope(void* q, void* k, const int32_t* pos, int rows, int H, int dh, fl
 typedef enum { D3TOM_LINEAR_PLAIN = 0, D3TOM_LINEAR_RESIDUAL = 1, D3TOM_LINEAR_SWIGLU = 2 } d3tom_linear_epilogue;
 int d3tom_linear(const void* a, const void* w, int rows, int n_w_rows, int K, int epilogue,
                  const void* residual, void* out, int out_chunk, void* stream);
-/* The same with the workgroup's row-tile height fixed to tile * 64 rows (tile = 1, 2 or 4) instead of
- * chosen from the problem size; for tuning and tests. */
+/* The same with the workgroup's tile fixed instead of chosen from the problem size: (tile & 15) * 64 rows (1, 2 or 4) and, unless
+ * tile >> 4 is zero, (tile >> 4) * 64 rows of w (2, 3 or 4; 64 x 192 is not built); for tuning and tests. */
 int d3tom_linear_tile(const void* a, const void* w, int rows, int n_w_rows, int K, int epilogue,
                       const void* residual, void* out, int out_chunk, int tile, void* stream);
 

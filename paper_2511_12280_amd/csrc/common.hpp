@@ -29,6 +29,15 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
+// V values rounded to bf16 and stored in one piece (p aligned to V elements)
+template <int V>
+__device__ __forceinline__ void store_bf16(uint16_t* p, const float (&v)[V]) {
+    uint32_t w[V / 2];
+#pragma unroll
+    for (int e = 0; e < V / 2; ++e) w[e] = pack_bf16x2(v[2 * e], v[2 * e + 1]);
+    __builtin_memcpy(__builtin_assume_aligned(p, V * 2), w, V * 2);
+}
+
 // element load as float for the generic (untuned) kernels
 template <typename T> struct Elem;
 template <> struct Elem<float> {
@@ -40,15 +49,6 @@ template <> struct Elem<uint16_t> {   // bf16 storage
     static __device__ __forceinline__ void store(uint16_t* p, float v) { *p = f32_to_bf16_bits(v); }
 };
 
-// ---- wave / block reductions ----------------------------------------------------------------
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-    return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, WAVE));
 // Dot product of two rows of n elements (16-byte aligned, n a multiple of the elements per 16 bytes), chunks c0, c0 + step, ...:
 // 16-byte loads, eight chunks requested before the first is used, float32 accumulation in that order.  For the
 // generic kernels, whose time is load latency: one scalar load per multiply made them 10-50 times slower.
@@ -86,6 +86,15 @@ __device__ __forceinline__ float row_dot(const T* __restrict__ a, const T* __res
     return acc;
 }
 
+// ---- wave / block reductions ----------------------------------------------------------------
+__device__ __forceinline__ float wave_sum(float v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
+    return v;
+}
+__device__ __forceinline__ float wave_max(float v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, WAVE));
     return v;
 }
 __device__ __forceinline__ int wave_sum_i(int v) {

@@ -5,8 +5,7 @@
 //   RESIDUAL  out = residual + a w^T                      (the block's two skip connections)
 //   SWIGLU    out = silu(a w_gate^T) * (a w_up^T)         (w holds the F gate rows, then the F up rows)
 //   ROPE      (inside the stack only) PLAIN for the stacked q | k | v weight with the rotary embedding of the q and k
-//             sections folded in: a 128-column tile holds whole heads, so both channels of a rotation pair are in
-//             the tile; the projection is rounded to bf16 first (the value the separate rotary kernel would have
+//             sections folded in; the projection is rounded to bf16 first (the value the separate rotary kernel would have
 //             read), turned by the token's angle from a per-step table, and rounded again
 //   PARTIAL   (inside the stack only) the contraction is cut into gridDim.y slices and every slice writes
 //             its float32 products to its own [rows, n] matrix; the row-wise kernel that follows adds the
@@ -14,359 +13,405 @@
 //             output and down projections with too few tall tiles to fill the chip.
 // One rounding to bf16, at the store (ROPE: one for the projection, one for the rotated value).
 //
-// Workgroup tile: (TM*64) rows x 128 columns of a w^T.  Eight waves with two jobs: waves 0..3 (2 x 2, wave
-// tile (TM*32) x 64) only feed the matrix cores, waves 4..7 only move data.  Both operands are
-// contraction-contiguous, so both tiles travel HBM/L2 -> LDS with direct loads (16 bytes per lane, no
-// register staging) into a ring of 64-element k-stages, one s_barrier per stage.  A wave that issues such a
-// load waits for room in the CU's single vector-memory queue (64 bytes per clock); kept in the computing
-// waves, that wait stalled their MFMA stream (measured: 6-20 % slower), so the loads have waves of their own.
-// The 16-byte chunk stored at position p of tile row r is chunk p ^ ((r >> 1) & 7), which makes the MFMA
-// operand reads bank-conflict free.
-// For SWIGLU the 128 tile columns are 64 gate rows and the 64 up rows of the same output columns, so the
-// epilogue finds both factors of an output element in the same tile.
+// One workgroup per tile of BM x BN, eight waves in two groups of four.  Group i owns rows i*BM/2 .. of the tile, its four
+// waves a quarter of the columns each; wave i and wave i + 4 share a SIMD.  The groups alternate (ping-pong): in one phase a
+// group reads the operand fragments of a whole 64-element k-stage from LDS into registers (and issues direct loads) while
+// the other group issues nothing but the MFMAs of the stage it holds; a barrier ends the phase.  Measured on gfx950 with
+// 256 x 256 tiles (clocks of a k-stage; the MFMAs alone are 2048): all waves on one schedule 3270, phases of 32 elements
+// 2570, phases of 64 2307.  MFMA streams of two waves of one SIMD slow each other down, hence the phases.
 //
-// Workgroup ids are dealt round-robin to the 8 XCDs; each XCD owns a contiguous range of column tiles
-// (its private L2 sees only its share of w) and walks it in panels of a few column tiles, row tile
-// fastest, so that the workgroups running together share operand rows.
+// MFMA 16x16x32 and not 32x32x16: at full load the card is power bound (it clocks down to 1.5 GHz), and the smaller shape
+// moves fewer accumulator bytes per flop: 2.09 against 1.86 PFLOP/s with operands in registers and random data, 1.24 against
+// 1.10 in this loop.  It adds the products in the same order as two 32x32x16 steps; the results are the same bits.
+//
+// Both operands are contraction-contiguous, so both tiles travel HBM/L2 -> LDS with direct loads (16 bytes per lane, no
+// register staging): group 0 fetches the rows of a, group 1 the rows of w, 128 bytes of every row per stage (a whole cache
+// line: half lines halve the rate of a compute unit's load path).  Two rings fill the 160 KB of LDS; the one of w is the
+// deeper one, its rows come cold from HBM.  The 16-byte chunk stored at position p of tile row r is chunk p ^ f(r), with f
+// such that the 16 rows of a fragment read hit all 64 banks.
+//
+// The product is formed as w a^T, so that a lane ends up with one row of out and 4 * TN consecutive columns of it: the
+// epilogue works on registers and stores 16 bytes per lane, no LDS pass.  For SWIGLU and ROPE rows of w are laid out in the
+// tile so that both partners of a pair (gate and up of one output; channels c and c + dh/2) land in the same lane.
+//
+// Tiles are numbered band by band and cut into 8 equal runs, one per XCD (see linear_tile), so that the 32 workgroups that run
+// together on an XCD form a compact block and its private L2 sees few operand rows.
+#include <type_traits>
 #include "common.hpp"
 #include "direct_load.hpp"
 
 namespace d3tom {
 
 enum { LIN_PLAIN = 0, LIN_RESIDUAL = 1, LIN_SWIGLU = 2, LIN_PARTIAL = 3, LIN_ROPE = 4 };
-constexpr int LIN_BN = 128;
 constexpr int LIN_BK = 64;
-constexpr int LIN_PAD = 136;      // floats per row of the epilogue staging tile (see the epilogue)
 
-template <int TM> struct LinCfg {
-    static constexpr int BM = TM * 64;
-    static constexpr int NS = (TM == 4) ? 3 : 4;                       // ring stages
-    static constexpr int STAGE = (BM + LIN_BN) * 128;                  // bytes per stage
-    static constexpr int LDS = (NS * STAGE > BM * LIN_PAD * 4) ? NS * STAGE : BM * LIN_PAD * 4;
+// TM: 16-row fragments of a wave (BM = 32 TM rows), TN: 16-column fragments of a wave (BN = 64 TN columns)
+template <int TM, int TN> struct LinCfg {
+    static constexpr int BM = 32 * TM, BN = 64 * TN;
+    static constexpr int A_BYTES = BM * 128, W_BYTES = BN * 128;       // one k-stage of either operand
+    // ring depths: w first (deeper), both within 160 KB
+    static constexpr int NW = (TN == 4) ? (TM == 8 ? 3 : TM == 4 ? 3 : 4) : (TN == 3) ? 4 : (TM == 2 ? 6 : TM == 4 ? 5 : 4);
+    static constexpr int NA_MAX = (163840 - NW * W_BYTES) / A_BYTES;
+    static constexpr int NA = NA_MAX > 6 ? 6 : NA_MAX;
+    static constexpr int LDS = NA * A_BYTES + NW * W_BYTES;
+    static_assert(NA >= 2 && NW >= 2 && LDS <= 163840, "rings must fit");
 };
 
-template <int TM, int EPI>
-__global__ __launch_bounds__(512) void linear_bf16_kernel(
+// Tile (rt, ct) of workgroup id.  Ids are dealt round-robin to the 8 XCDs; the tiles are numbered in bands of RB row tiles,
+// column-major inside a band, and that sequence is cut into 8 runs of `per` tiles, one per XCD.
+__device__ __forceinline__ bool linear_tile(int id, int per, int RB, int NRT, int NCT, int& rt, int& ct) {
+    const int t = (id & 7) * per + (id >> 3);
+    if (t >= NRT * NCT) return false;
+    const int band = RB * NCT, nfull = NRT / RB;
+    if (t < nfull * band) { const int rem = t % band; rt = (t / band) * RB + rem % RB; ct = rem / RB; }
+    else { const int t2 = t - nfull * band, rl = NRT - nfull * RB; rt = nfull * RB + t2 % rl; ct = t2 / rl; }
+    return true;
+}
+
+template <int TM, int TN, int EPI>
+__global__ __launch_bounds__(512, 2) void linear_bf16_kernel(
     const uint16_t* __restrict__ a, const uint16_t* __restrict__ w, int M, int N, int K,
-    const uint16_t* residual, uint16_t* out, int out_chunk, int NRT, int NCT, int cpx, int PC, int col0, int col_end,
+    const uint16_t* residual, uint16_t* out, int out_chunk, int NRT, int NCT, int per, int RB, int col0, int col_end,
     const float2* __restrict__ rope_cs, int rope_dh) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    using C = LinCfg<TM>;
-    constexpr int BM = C::BM, NS = C::NS, STAGE = C::STAGE;
-    constexpr int A_LD = BM / 32;                       // direct loads per wave and stage, a tile (8 rows each)
-    constexpr int B_LD = LIN_BN / 32;
-    constexpr int LPS = A_LD + B_LD;
-    extern __shared__ __attribute__((aligned(16))) char ring[];
+    using C = LinCfg<TM, TN>;
+    constexpr int BM = C::BM, BN = C::BN, NA = C::NA, NW = C::NW;
+    constexpr int LA = BM / 32, LW = BN / 32;           // direct loads per wave and stage (8 rows each)
+    constexpr bool PAIR = EPI == LIN_SWIGLU || EPI == LIN_ROPE;
+    extern __shared__ __attribute__((aligned(16))) char ring[];     // NA stages of a, then NW stages of w
 
-    // tile of this workgroup
-    const int xcd = blockIdx.x & 7, li = blockIdx.x >> 3;
-    const int panel = li / (NRT * PC), within = li % (NRT * PC);
-    const int cl = panel * PC + within % PC;            // column tile inside this XCD's range
-    const int rt = within / PC, ct = xcd * cpx + cl;
-    if (cl >= cpx || ct >= NCT) return;
+    int rt, ct;
+    if (!linear_tile(blockIdx.x, per, RB, NRT, NCT, rt, ct)) return;
 
-    constexpr int NT = 512;
-    const int tid = threadIdx.x, wave = (tid >> 6) & 3, lane = tid & 63;
-    const bool loader = tid >> 8;                       // waves 4..7 only move data, waves 0..3 only compute
-    const int wm = wave >> 1, wn = wave & 1;
-    const int c = lane & 31, g = lane >> 5;
-    // out columns per tile and rows of w behind the 128 tile columns
-    constexpr int OUT_BN = (EPI == LIN_SWIGLU) ? 64 : 128;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int grp = __builtin_amdgcn_readfirstlane(tid >> 8), wn = (tid >> 6) & 3;
+    const int r = lane & 15, g = lane >> 4;
     const int n_out = (EPI == LIN_SWIGLU) ? N / 2 : N;  // SWIGLU: N counts gate and up rows
+    // What a tile's columns are: plain columns, or pairs (SWIGLU: output o = rows o and o + F of w; ROPE: channels c, c + dh/2)
+    constexpr int UNITS = PAIR ? BN / 2 : BN;
+    const int unit0 = ((EPI == LIN_ROPE) ? col0 / 2 : col0) + ct * UNITS;
+    const int unit_end = (EPI == LIN_ROPE) ? col_end / 2 : col_end;
+    const int half = rope_dh >> 1;
 
-    const __amdgpu_buffer_rsrc_t rs_a = make_uniform_rsrc(a, (uint32_t)((size_t)M * K * 2));
-    const __amdgpu_buffer_rsrc_t rs_w = make_uniform_rsrc(w, (uint32_t)((size_t)N * K * 2));
-    // byte offset of this lane inside its operand for each of its direct loads; rows past the end re-read
-    // row 0 (their results are never stored); the k-slice moves through the scalar offset
-    int a_off[A_LD], b_off[B_LD];
+    // rows past the end re-read row 0 (their results are never stored); the k-stage moves through the scalar offset
+    constexpr int LMAX = LA > LW ? LA : LW;
+    int off[LMAX];
 #pragma unroll
-    for (int i = 0; i < A_LD; ++i) {
-        const int row = wave * (BM / 4) + i * 8 + (lane >> 3);
-        const int cg = (lane & 7) ^ ((row >> 1) & 7);
-        const int m = rt * BM + row;
-        a_off[i] = ((m < M) ? m : 0) * K * 2 + cg * 16;
-    }
-#pragma unroll
-    for (int i = 0; i < B_LD; ++i) {
-        const int row = wave * (LIN_BN / 4) + i * 8 + (lane >> 3);
-        const int cg = (lane & 7) ^ ((row >> 1) & 7);
-        int n;
-        if constexpr (EPI == LIN_SWIGLU) {
-            const int o = col0 + ct * 64 + (row & 63);
-            n = (o < col_end) ? o + (row >> 6) * n_out : 0;
+    for (int i = 0; i < LMAX; ++i) {
+        const int pos = lane & 7;
+        if (grp == 0) {
+            const int row = wn * (BM / 4) + i * 8 + (lane >> 3), m = rt * BM + row;
+            off[i] = ((m < M && i < LA) ? m : 0) * K * 2 + ((pos ^ ((row >> 1) & 7)) << 4);
         } else {
-            n = col0 + ct * LIN_BN + row;
-            n = (n < col_end) ? n : 0;
+            const int row = wn * (BN / 4) + i * 8 + (lane >> 3);
+            const int part = row / (16 * TN), q = row - part * 16 * TN, qg = q / (4 * TN);
+            int n, ok;
+            if constexpr (PAIR) {
+                const int u = unit0 + part * 8 * TN + qg * 2 * TN + ((q - qg * 4 * TN) >> 2) * 2 + (q & 1);
+                const int second = (q >> 1) & 1;
+                ok = u < unit_end;
+                if constexpr (EPI == LIN_SWIGLU) n = u + second * n_out;
+                else { const int h = u / half; n = h * rope_dh + (u - h * half) + second * half; }
+            } else {
+                n = unit0 + row;
+                ok = n < unit_end;
+            }
+            off[i] = ((ok && i < LW) ? n : 0) * K * 2 + ((pos ^ (((q >> 1) & 1) | (qg << 1))) << 4);
         }
-        b_off[i] = n * K * 2 + cg * 16;
     }
-    const int nkt = (K / LIN_BK) / (int)gridDim.y;         // k-stages of this workgroup's slice of the contraction
-    const int kt0 = (int)blockIdx.y * nkt;
+    const int nst = (K / LIN_BK) / (int)gridDim.y;         // k-stages of this workgroup's slice of the contraction
+    const int st0 = (int)blockIdx.y * nst;
     const uint32_t ring0 = (uint32_t)(size_t)(lds_ptr_t)ring;
-    const uint32_t a_lds = __builtin_amdgcn_readfirstlane(ring0 + wave * (BM / 4) * 128);
-    const uint32_t b_lds = __builtin_amdgcn_readfirstlane(ring0 + BM * 128 + wave * (LIN_BN / 4) * 128);
-    auto issue_part = [&](int kt, int stage, int n0, int n1) {
-#pragma unroll
-        for (int i = 0; i < A_LD; ++i)
-            if (i >= n0 && i < n1)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, (lds_ptr_t)(size_t)(a_lds + stage * STAGE + i * 8 * 128), 16,
-                                                         a_off[i], (kt0 + kt) * (LIN_BK * 2), 0, 0);
-#pragma unroll
-        for (int i = 0; i < B_LD; ++i)
-            if (A_LD + i >= n0 && A_LD + i < n1)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, (lds_ptr_t)(size_t)(b_lds + stage * STAGE + i * 8 * 128), 16,
-                                                         b_off[i], (kt0 + kt) * (LIN_BK * 2), 0, 0);
-    };
+    const uint32_t a_lds = __builtin_amdgcn_readfirstlane(ring0 + wn * (BM / 4) * 128);
+    const uint32_t w_lds = __builtin_amdgcn_readfirstlane(ring0 + NA * C::A_BYTES + wn * (BN / 4) * 128);
 
-    f32x16 acc[TM][2];
+    f32x4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // fragment addresses inside a stage: a fragment of a is 16 consecutive rows; row x of w fragment j is tile row
+    // (x / 4) * 4 TN + 4 j + x % 4 of the wave's part
+    int a_addr[2], w_addr[2];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-    int a_row[TM], b_row[2], a_sw[TM], b_sw[2];
+    for (int kk = 0; kk < 2; ++kk) {
+        const int ra = grp * (BM / 2) + r, q = (r >> 2) * 4 * TN + (r & 3);
+        a_addr[kk] = ra * 128 + (((kk * 4 + g) ^ ((ra >> 1) & 7)) << 4);
+        w_addr[kk] = NA * C::A_BYTES + (wn * 16 * TN + q) * 128 + (((kk * 4 + g) ^ (((q >> 1) & 1) | ((r >> 2) << 1))) << 4);
+    }
+    bf16x8 af[2][TM], wf[2][TN];
+    auto read = [&](int sa, int sw) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i) { const int Rr = wm * (TM * 32) + i * 32 + c; a_row[i] = Rr * 128; a_sw[i] = (Rr >> 1) & 7; }
+        for (int kk = 0; kk < 2; ++kk) {
+            const char* pw = ring + sw * C::W_BYTES + w_addr[kk];
+            const char* pa = ring + sa * C::A_BYTES + a_addr[kk];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) { const int Rr = wn * 64 + j * 32 + c; b_row[j] = BM * 128 + Rr * 128; b_sw[j] = (Rr >> 1) & 7; }
-
-    // one stage: feed stage kt to the MFMAs, operand fragments read one k-step ahead
-    auto stage = [&](int kt) {
-        const char* sb = ring + (kt % NS) * STAGE;
-        bf16x8 af[2][TM], bfr[2][2];
-        auto read_frags = [&](int kk, int buf) {
+            for (int j = 0; j < TN; ++j) wf[kk][j] = *reinterpret_cast<const bf16x8*>(pw + j * 4 * 128);
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
-                af[buf][i] = *reinterpret_cast<const bf16x8*>(sb + a_row[i] + (((kk * 2 + g) ^ a_sw[i]) << 4));
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                bfr[buf][j] = *reinterpret_cast<const bf16x8*>(sb + b_row[j] + (((kk * 2 + g) ^ b_sw[j]) << 4));
-        };
-        read_frags(0, 0);
-#pragma unroll
-        for (int kk = 0; kk < LIN_BK / 16; ++kk) {
-            if (kk + 1 < LIN_BK / 16) read_frags(kk + 1, (kk + 1) & 1);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk & 1][i], bfr[kk & 1][j], acc[i][j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int i = 0; i < TM; ++i) af[kk][i] = *reinterpret_cast<const bf16x8*>(pa + i * 16 * 128);
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
-    if (loader) {
+    auto compute = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int st = 0; st < NS - 1; ++st)
-            if (st < nkt) issue_part(st, st, 0, LPS);
-        for (int kt = 0; kt < nkt; ++kt) {
-            // stage kt has landed (the NS-2 stages behind it may still be in flight), then everyone meets
-            if (kt + NS - 2 <= nkt - 1) wait_loads_and_barrier<(NS - 2) * LPS>();
-            else wait_loads_and_barrier<0>();
-            // the consumers are past stage kt-1: its slot takes stage kt+NS-1
-            if (kt + NS - 1 < nkt) issue_part(kt + NS - 1, (kt + NS - 1) % NS, 0, LPS);
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[kk][j], af[kk][i], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto next = [](int slot, int n) { return slot + 1 == n ? 0 : slot + 1; };
+    // Stage s sits in slot s mod NA (NW).  Group 0 reads it in phase 2s, group 1 in phase 2s + 1; from phase 2s + 2 on its
+    // slots may be refilled, which group 0 does for a in that phase and group 1 for w one later.  Before the barrier that ends
+    // phase 2s + 1 both groups wait for their own loads of stage s + 1.
+    if (grp == 0) {
+        const __amdgpu_buffer_rsrc_t rs = make_uniform_rsrc(a, (uint32_t)((size_t)M * K * 2));
+        auto issue = [&](int s, int slot) {
+#pragma unroll
+            for (int i = 0; i < LA; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(size_t)(a_lds + slot * C::A_BYTES + i * 1024), 16, off[i], (st0 + s) * 128, 0, 0);
+        };
+#pragma unroll
+        for (int s = 0; s < NA; ++s) if (s < nst) issue(s, s);
+        if (nst >= NA) wait_loads<(NA - 1) * LA>(); else wait_loads<0>();
+        phase_barrier();
+        int sa = 0, sw = 0, fill = NA - 1;
+#pragma unroll 1
+        for (int s = 0; s < nst; ++s) {
+            const bool more = s + NA - 1 < nst;
+            read(sa, sw);
+            if (s > 0 && more) issue(s + NA - 1, fill);
+            wait_lds();
+            phase_barrier();
+            compute();
+            if (more) wait_loads<(NA - 2) * LA>(); else wait_loads<0>();
+            phase_barrier();
+            fill = sa; sa = next(sa, NA); sw = next(sw, NW);
         }
+        phase_barrier();
     } else {
-        for (int kt = 0; kt < nkt; ++kt) {
-            wait_loads_and_barrier<0>();
-            stage(kt);
+        const __amdgpu_buffer_rsrc_t rs = make_uniform_rsrc(w, (uint32_t)((size_t)N * K * 2));
+        auto issue = [&](int s, int slot) {
+#pragma unroll
+            for (int i = 0; i < LW; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(size_t)(w_lds + slot * C::W_BYTES + i * 1024), 16, off[i], (st0 + s) * 128, 0, 0);
+        };
+#pragma unroll
+        for (int s = 0; s < NW; ++s) if (s < nst) issue(s, s);
+        if (nst >= NW) wait_loads<(NW - 1) * LW>(); else wait_loads<0>();
+        phase_barrier();
+        phase_barrier();
+        int sa = 0, sw = 0, fill = NW - 1;
+#pragma unroll 1
+        for (int s = 0; s < nst; ++s) {
+            const bool more = s + NW - 1 < nst;
+            read(sa, sw);
+            if (s > 0 && more) issue(s + NW - 1, fill);
+            wait_lds();
+            if (more) wait_loads<(NW - 2) * LW>(); else wait_loads<0>();
+            phase_barrier();
+            compute();
+            phase_barrier();
+            fill = sw; sa = next(sa, NA); sw = next(sw, NW);
         }
     }
 
-    // epilogue: the float32 tile goes through LDS (the ring is free now) so that every thread ends up with
-    // 8 consecutive columns of one row: 16-byte stores, residual rows read the same way.  Rows are padded
-    // to LIN_PAD floats: the two half-waves of an accumulator store (rows 4 apart) then fall into different
-    // bank halves.
-    __syncthreads();
-    float* tile = reinterpret_cast<float*>(ring);
-    if (!loader) {
+    // epilogue, in registers: lane (r, g) holds row r of every 16-row fragment and, over the TN fragments, 4 TN consecutive
+    // values of its part: plain columns, or (PAIR) 2 TN consecutive outputs with their partners in elements 2 and 3
+    const int u0 = unit0 + wn * (UNITS / 4) + g * (UNITS / 16);
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i) {
+        const int m = rt * BM + grp * (BM / 2) + i * 16 + r;
+        if (m >= M) continue;
+        if constexpr (EPI == LIN_PARTIAL) {
+            float* po = reinterpret_cast<float*>(out) + ((size_t)blockIdx.y * M + m) * N + u0;
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < TN; ++j)
+                if (u0 + j * 4 < unit_end) *reinterpret_cast<f32x4*>(po + j * 4) = acc[i][j];
+        } else if constexpr (!PAIR) {
+            constexpr int V = (TN % 2 == 0) ? 8 : 4;        // columns per store (never across an out_chunk: a multiple of 8)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int row = wm * (TM * 32) + i * 32 + (e >> 2) * 8 + g * 4 + (e & 3);
-                    tile[row * LIN_PAD + wn * 64 + j * 32 + c] = acc[i][j][e];
+            for (int v0 = 0; v0 < 4 * TN; v0 += V) {
+                const int col = u0 + v0;
+                if (col >= unit_end) continue;
+                const size_t o = (size_t)(col / out_chunk) * M * out_chunk + (size_t)m * out_chunk + col % out_chunk;
+                float v[V];
+#pragma unroll
+                for (int e = 0; e < V; ++e) v[e] = acc[i][(v0 + e) >> 2][e & 3];
+                if constexpr (EPI == LIN_RESIDUAL) {
+                    uint32_t rr[V / 2];
+                    __builtin_memcpy(rr, __builtin_assume_aligned(residual + o, V * 2), V * 2);
+#pragma unroll
+                    for (int e = 0; e < V / 2; ++e) { v[2 * e] += bf16_lo(rr[e]); v[2 * e + 1] += bf16_hi(rr[e]); }
                 }
-    }
-    __syncthreads();
-    if constexpr (EPI == LIN_ROPE) {
-        // A unit is an 8-column group of the first half of a head together with its partner group half a head
-        // further: the two share their angles, so one thread rotates both (one table read for 16 outputs).  Heads
-        // start at multiples of their size, so a 128-column tile holds whole heads.
-        const int half = rope_dh >> 1, gph = half >> 3;                // 8-column groups in half a head: 8 or 4
-        constexpr int UPR = OUT_BN / 16;                               // units per tile row
-        for (int u = tid; u < BM * UPR; u += NT) {
-            const int row = u / UPR, un = u % UPR;
-            const int hd = un / gph, gi = un - hd * gph;
-            const int tc = hd * rope_dh + gi * 8;                      // tile column of the first-half group
-            const int m = rt * BM + row, col = col0 + ct * OUT_BN + tc;
-            if (m >= M || col >= col_end) continue;
-            const float* pa = tile + row * LIN_PAD + tc;
-            const float4 a0 = *reinterpret_cast<const float4*>(pa), a1 = *reinterpret_cast<const float4*>(pa + 4);
-            const float4 b0 = *reinterpret_cast<const float4*>(pa + half), b1 = *reinterpret_cast<const float4*>(pa + half + 4);
-            float va[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-            float vb[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-            if (col < 2 * out_chunk) {                                 // q and k sections; v passes through
-                const float4* cs = reinterpret_cast<const float4*>(rope_cs + (size_t)m * half + gi * 8);
+                store_bf16<V>(out + o, v);
+            }
+        } else {
+            constexpr int V = (TN == 4) ? 8 : (TN == 2) ? 4 : 2;      // outputs per store
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float4 t = cs[e];                            // (cos, sin) of channels 2e and 2e + 1
-                    const float cc[2] = {t.x, t.z}, ss[2] = {t.y, t.w};
+            for (int v0 = 0; v0 < 2 * TN; v0 += V) {
+                const int u = u0 + v0;
+                if (u >= unit_end) continue;
+                float x[V], y[V];
 #pragma unroll
-                    for (int f = 0; f < 2; ++f) {
-                        // both channels as the stored bf16 projection, then the rotation in float32
-                        const float x0 = bf16_bits_to_f32(f32_to_bf16_bits(va[2 * e + f]));
-                        const float x1 = bf16_bits_to_f32(f32_to_bf16_bits(vb[2 * e + f]));
-                        rope_rotate(x0, x1, cc[f], ss[f], va[2 * e + f], vb[2 * e + f]);
+                for (int e = 0; e < V; ++e) { x[e] = acc[i][(v0 + e) >> 1][e & 1]; y[e] = acc[i][(v0 + e) >> 1][2 + (e & 1)]; }
+                if constexpr (EPI == LIN_SWIGLU) {
+#pragma unroll
+                    for (int e = 0; e < V; ++e) x[e] = x[e] / (1.f + expf(-x[e])) * y[e];
+                    store_bf16<V>(out + (size_t)m * n_out + u, x);
+                } else {
+                    const int h = u / half, c = u - h * half, col = h * rope_dh + c;
+                    if (col < 2 * out_chunk) {                         // q and k sections; v passes through
+                        const float4* cs = reinterpret_cast<const float4*>(rope_cs + (size_t)m * half + c);
+#pragma unroll
+                        for (int e = 0; e < V / 2; ++e) {
+                            const float4 t = cs[e];                    // (cos, sin) of channels 2e and 2e + 1
+                            // both channels as the stored bf16 projection, then the rotation in float32
+#pragma unroll
+                            for (int f = 0; f < 2; ++f) {
+                                const float x0 = bf16_bits_to_f32(f32_to_bf16_bits(x[2 * e + f])), x1 = bf16_bits_to_f32(f32_to_bf16_bits(y[2 * e + f]));
+                                rope_rotate(x0, x1, f ? t.z : t.x, f ? t.w : t.y, x[2 * e + f], y[2 * e + f]);
+                            }
+                        }
                     }
+                    const size_t o = (size_t)(col / out_chunk) * M * out_chunk + (size_t)m * out_chunk + col % out_chunk;
+                    store_bf16<V>(out + o, x);
+                    store_bf16<V>(out + o + half, y);
                 }
             }
-            const size_t o = (size_t)(col / out_chunk) * M * out_chunk + (size_t)m * out_chunk + col % out_chunk;
-            uint4 pk;
-            pk.x = pack_bf16x2(va[0], va[1]); pk.y = pack_bf16x2(va[2], va[3]);
-            pk.z = pack_bf16x2(va[4], va[5]); pk.w = pack_bf16x2(va[6], va[7]);
-            *reinterpret_cast<uint4*>(out + o) = pk;
-            pk.x = pack_bf16x2(vb[0], vb[1]); pk.y = pack_bf16x2(vb[2], vb[3]);
-            pk.z = pack_bf16x2(vb[4], vb[5]); pk.w = pack_bf16x2(vb[6], vb[7]);
-            *reinterpret_cast<uint4*>(out + o + half) = pk;
         }
-        return;
-    }
-    constexpr int CG = OUT_BN / 8;                         // 8-column groups per tile row
-    for (int u = tid; u < BM * CG; u += NT) {
-        const int row = u / CG, cg = u % CG;
-        const int m = rt * BM + row, col = col0 + ct * OUT_BN + cg * 8;      // this launch covers columns [col0, col_end)
-        if (m >= M || col >= col_end) continue;
-        const float4 v0 = *reinterpret_cast<const float4*>(tile + row * LIN_PAD + cg * 8);
-        const float4 v1 = *reinterpret_cast<const float4*>(tile + row * LIN_PAD + cg * 8 + 4);
-        float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
-        if constexpr (EPI == LIN_PARTIAL) {
-            float* po = reinterpret_cast<float*>(out) + ((size_t)blockIdx.y * M + m) * N + col;
-            *reinterpret_cast<float4*>(po) = v0;
-            *reinterpret_cast<float4*>(po + 4) = v1;
-            continue;
-        }
-        const size_t o = (size_t)(col / out_chunk) * M * out_chunk + (size_t)m * out_chunk + col % out_chunk;
-        if constexpr (EPI == LIN_SWIGLU) {
-            const float4 u0 = *reinterpret_cast<const float4*>(tile + row * LIN_PAD + 64 + cg * 8);
-            const float4 u1 = *reinterpret_cast<const float4*>(tile + row * LIN_PAD + 64 + cg * 8 + 4);
-            const float up[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = v[e] / (1.f + expf(-v[e])) * up[e];
-        }
-        if constexpr (EPI == LIN_RESIDUAL) {
-            const uint4 r = *reinterpret_cast<const uint4*>(residual + o);
-            const uint32_t rr[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { v[2 * e] += bf16_lo(rr[e]); v[2 * e + 1] += bf16_hi(rr[e]); }
-        }
-        uint4 pk;
-        pk.x = pack_bf16x2(v[0], v[1]); pk.y = pack_bf16x2(v[2], v[3]);
-        pk.z = pack_bf16x2(v[4], v[5]); pk.w = pack_bf16x2(v[6], v[7]);
-        *reinterpret_cast<uint4*>(out + o) = pk;
     }
 #endif
 }
 
 namespace {
-template <int TM, int EPI>
+template <int TM, int TN, int EPI>
 int launch_linear(const void* a, const void* w, int M, int N, int K, const void* residual, void* out, int out_chunk,
                   int ksplit, int col0, int col_end, hipStream_t st, const float2* rope_cs = nullptr, int rope_dh = 0) {
-    using C = LinCfg<TM>;
+    using C = LinCfg<TM, TN>;
     static PerDeviceOnce lds_setup;      // per instantiation
-    if (!lds_setup.run([] { return raise_dynamic_lds(linear_bf16_kernel<TM, EPI>, C::LDS); })) return D3TOM_ERR_DEVICE;
-    const int out_bn = (EPI == LIN_SWIGLU) ? 64 : 128;
+    if (!lds_setup.run([] { return raise_dynamic_lds(linear_bf16_kernel<TM, TN, EPI>, C::LDS); })) return D3TOM_ERR_DEVICE;
+    const int out_bn = (EPI == LIN_SWIGLU) ? C::BN / 2 : C::BN;
     const int NRT = ceil_div(M, C::BM), NCT = ceil_div(col_end - col0, out_bn);
-    const int cpx = ceil_div(NCT, 8);
-    int PC = 32 / NRT;
-    PC = PC < 4 ? 4 : (PC > 16 ? 16 : PC);
-    if (PC > cpx) PC = cpx;
-    const int panels = ceil_div(cpx, PC);
-    const dim3 grid(8u * (unsigned)(panels * PC * NRT), (unsigned)ksplit);
-    D3TOM_LAUNCH(LINEAR, st, (linear_bf16_kernel<TM, EPI><<<grid, 512, C::LDS, st>>>(
+    const int per = ceil_div(NRT * NCT, 8);
+    // the (at most) 32 workgroups that run together on an XCD: a block of RB row tiles whose operand rows are as few as
+    // possible, i.e. RB * BM close to (32 / RB) * BN
+    const int conc = per < 32 ? per : 32;
+    int RB = 1;
+    while ((RB + 1) * (RB + 1) * C::BM <= conc * C::BN) ++RB;
+    if (RB > NRT) RB = NRT;
+    D3TOM_LAUNCH(LINEAR, st, (linear_bf16_kernel<TM, TN, EPI><<<dim3(8u * (unsigned)per, (unsigned)ksplit), 512, C::LDS, st>>>(
         (const uint16_t*)a, (const uint16_t*)w, M, N, K, (const uint16_t*)residual, (uint16_t*)out, out_chunk,
-        NRT, NCT, cpx, PC, col0, col_end, rope_cs, rope_dh)));
+        NRT, NCT, per, RB, col0, col_end, rope_cs, rope_dh)));
     return D3TOM_OK;
 }
 
 template <int EPI>
-int launch_linear_tm(int tm, const void* a, const void* w, int M, int N, int K, const void* residual, void* out,
-                     int out_chunk, int col0, int col_end, hipStream_t st, const float2* rope_cs = nullptr, int rope_dh = 0) {
-    switch (tm) {
-        case 1: return launch_linear<1, EPI>(a, w, M, N, K, residual, out, out_chunk, 1, col0, col_end, st, rope_cs, rope_dh);
-        case 2: return launch_linear<2, EPI>(a, w, M, N, K, residual, out, out_chunk, 1, col0, col_end, st, rope_cs, rope_dh);
-        default: return launch_linear<4, EPI>(a, w, M, N, K, residual, out, out_chunk, 1, col0, col_end, st, rope_cs, rope_dh);
+int launch_linear_cfg(int cfg, const void* a, const void* w, int M, int N, int K, const void* residual, void* out, int out_chunk,
+                      int ksplit, int col0, int col_end, hipStream_t st, const float2* rope_cs = nullptr, int rope_dh = 0) {
+#define D3TOM_LIN(TM, TN) return launch_linear<TM, TN, EPI>(a, w, M, N, K, residual, out, out_chunk, ksplit, col0, col_end, st, rope_cs, rope_dh)
+    switch (cfg) {
+        case 0: D3TOM_LIN(2, 2);
+        case 1: D3TOM_LIN(2, 4);
+        case 2: D3TOM_LIN(4, 2);
+        case 3: D3TOM_LIN(4, 3);
+        case 4: D3TOM_LIN(4, 4);
+        case 5: D3TOM_LIN(8, 2);
+        case 6: D3TOM_LIN(8, 3);
+        default: D3TOM_LIN(8, 4);
     }
+#undef D3TOM_LIN
 }
 }  // namespace
 
-// Row-tile height for a problem.  Taller tiles move fewer operand bytes per flop, and fewer workgroups then
-// share (and ask at the same moment for) the same rows of w, which matters when w comes cold from HBM, as a
-// block's weights do (read once per step).  Measured per-flop throughput of a full machine with cold weights:
-// 64 rows 0.55, 128 rows 0.72 of what 256 rows reach (0.75 / 0.92 with w resident in the memory-side cache).
-// But the grid runs in whole rounds of 256 workgroups (one per compute unit), so a partly filled last
-// round can cost more than the tile gains.  Estimated time = rounds * rows per tile / efficiency; the
-// smallest estimate wins, ties go to the smaller tile.
-static double linear_estimate(int tm, int M, int n_tiles_n) {
-    static const double eff[5] = {0.0, 0.55, 0.72, 0.0, 1.0};
-    const long tiles = (long)ceil_div(M, tm * 64) * n_tiles_n;
-    return (double)((tiles + 255) / 256) * tm / eff[tm];
+// ---- choice of the tile -----------------------------------------------------------------------------
+// What a k-stage of a tile takes when the chip is full of them (microseconds, measured at 3773 x 12288 x 4096 and
+// 3773 x 22016 x 4096 with weights cold in HBM), and what a round of workgroups costs beside its k-stages (filling the ring,
+// the epilogue).  A grid runs in rounds of 256 workgroups, one per compute unit, and a mostly empty last round costs as much as
+// a full one: the estimate is rounds * (stages * stage + round), and the smallest one wins.
+struct LinTile { int bm, bn; double stage; };
+static constexpr LinTile LIN_TILES[] = {{64, 128, 0.42}, {64, 256, 0.64}, {128, 128, 0.565}, {128, 192, 0.76}, {128, 256, 0.88},
+                                        {256, 128, 0.89}, {256, 192, 1.19}, {256, 256, 1.40}};
+constexpr int LIN_NTILES = sizeof(LIN_TILES) / sizeof(LIN_TILES[0]);
+constexpr double LIN_ROUND_US = 3.0, LIN_LAUNCH_US = 4.0;
+
+// `cols` counts rows of w (SWIGLU: gate and up)
+static double linear_estimate(int cfg, int M, int cols, int nst, int ksplit) {
+    const LinTile& t = LIN_TILES[cfg];
+    const long tiles = (long)ceil_div(M, t.bm) * ceil_div(cols, t.bn) * ksplit;
+    return (double)((tiles + 255) / 256) * (nst * t.stage + LIN_ROUND_US) + LIN_LAUNCH_US;
 }
-int linear_pick_tm(int M, int n_tiles_n, double* est) {
-    int best = 1;
+static int linear_pick(int M, int cols, int nst, int ksplit, int bm, double* est) {
+    int best = -1;
     double best_t = 0.0;
-    for (int tm = 1; tm <= 4; tm <<= 1) {
-        const double t = linear_estimate(tm, M, n_tiles_n);
-        if (tm == 1 || t < best_t - 1e-9) { best = tm; best_t = t; }
+    for (int c = 0; c < LIN_NTILES; ++c) {
+        if (bm && LIN_TILES[c].bm != bm) continue;
+        const double t = linear_estimate(c, M, cols, nst, ksplit);
+        if (best < 0 || t < best_t) { best = c; best_t = t; }
     }
-    if (est) *est = best_t;
+    *est = best_t;
     return best;
 }
-// A last round that is mostly empty can be cut off: the leading column tiles that fill whole rounds of
-// 256-row tiles go in one launch, the remaining columns in a second launch with whatever tile suits them.
-// Returns the number of column tiles of the first launch (0 = one launch is as good) and both tile heights.
-int linear_plan_two(int M, int n_tiles_n, int* tm_a, int* tm_b) {
-    double single;
-    *tm_a = linear_pick_tm(M, n_tiles_n, &single);
-    *tm_b = 0;
-    const int nrt4 = ceil_div(M, 256);
-    const int rounds = (int)((long)nrt4 * n_tiles_n / 256);
-    if (rounds < 1) return 0;
-    const int cols_a = rounds * 256 / nrt4;
-    if (cols_a >= n_tiles_n) return 0;
-    double rest;
-    const int tb = linear_pick_tm(M, n_tiles_n - cols_a, &rest);
-    if (rounds * 4.0 + rest > 0.93 * single) return 0;         // not worth a second launch
-    *tm_a = 4; *tm_b = tb;
-    return cols_a;
+// A last round that is mostly empty can be cut off: the leading columns that fill whole rounds go in one launch, the
+// remaining ones in a second launch with whatever tile suits them (gate | up at 3773 rows: 1290 tiles of 256 x 256 are five
+// full rounds and ten tiles).  `cols` in rows of w; *cols_a: rows of w of the first launch (all of them: one launch), a
+// multiple of its tile width.
+struct LinPlan { int cfg_a, cols_a, cfg_b; double est; };
+static LinPlan linear_plan(int M, int cols, int nst) {
+    LinPlan p;
+    p.cfg_a = linear_pick(M, cols, nst, 1, 0, &p.est);
+    p.cols_a = cols;
+    p.cfg_b = 0;
+    const double single = p.est;
+    for (int c = 0; c < LIN_NTILES; ++c) {
+        const int nrt = ceil_div(M, LIN_TILES[c].bm), nct = ceil_div(cols, LIN_TILES[c].bn);
+        const int rounds = (int)((long)nrt * nct / 256);
+        const int lead = rounds > 0 ? rounds * 256 / nrt : 0;
+        if (lead < 1 || lead >= nct) continue;
+        double rest;
+        const int cb = linear_pick(M, cols - lead * LIN_TILES[c].bn, nst, 1, 0, &rest);
+        const double t = linear_estimate(c, M, lead * LIN_TILES[c].bn, nst, 1) + rest;
+        if (t < p.est && t < 0.95 * single) { p.cfg_a = c; p.cols_a = lead * LIN_TILES[c].bn; p.cfg_b = cb; p.est = t; }
+    }
+    return p;
 }
 
-// Number of contraction slices for a projection whose result goes through the row-wise add-and-normalise
-// kernel anyway: 4 when the 256-row tiles of the whole problem fill at most a quarter of the chip and each
-// slice still has a long enough k-loop, else 1 (no split).
-int linear_split_plan(int M, int N, int K) {
-    const long tiles = (long)ceil_div(M, 256) * ceil_div(N, LIN_BN);
-    const int nkt = K / LIN_BK;
-    return (K % LIN_BK == 0 && N % 8 == 0 && tiles * 4 <= 256 && nkt % 4 == 0 && nkt >= 32) ? 4 : 1;
+// Contraction slices for a projection whose result goes through the row-wise add-and-normalise kernel anyway: cutting the
+// contraction fills the chip where the tiles of a short sequence do not, at the price of writing and reading `ksplit` float32
+// matrices (about 3 TB/s together) and of the row kernel reading them.  Returns 1 (no split), 2 or 4; *cfg is the tile.
+// max_floats bounds the partial matrices together.
+int linear_split_plan(int M, int N, int K, size_t max_floats, int* cfg) {
+    const int nst = K / LIN_BK;
+    const LinPlan whole = linear_plan(M, N, nst);
+    int best = 1;
+    double best_t = whole.est;
+    *cfg = whole.cfg_a;
+    if (K % LIN_BK != 0 || N % 8 != 0) return 1;
+    for (int ks = 2; ks <= 4; ks <<= 1) {
+        if (nst % ks || nst / ks < 8 || (size_t)M * N * ks > max_floats) continue;
+        double t;
+        const int c = linear_pick(M, N, nst / ks, ks, 0, &t);
+        t += (double)M * N * ks * 8.0 / 3e6;
+        if (t < 0.95 * best_t) { best = ks; best_t = t; *cfg = c; }
+    }
+    return best;
 }
 
-// a w^T as `ksplit` float32 partial matrices [ksplit][M][N] (256-row tiles)
-int linear_partial_run(const void* a, const void* w, int M, int N, int K, int ksplit, float* partial, hipStream_t st) {
-    if (!a || !w || !partial || M < 1 || N < 1 || K < 1 || ksplit < 1) return D3TOM_ERR_INVALID_ARG;
+// a w^T as `ksplit` float32 partial matrices [ksplit][M][N]
+int linear_partial_run(const void* a, const void* w, int M, int N, int K, int ksplit, int cfg, float* partial, hipStream_t st) {
+    if (!a || !w || !partial || M < 1 || N < 1 || K < 1 || ksplit < 1 || cfg < 0 || cfg >= LIN_NTILES) return D3TOM_ERR_INVALID_ARG;
     if (!aligned16(a) || !aligned16(w) || !aligned16(partial)) return D3TOM_ERR_INVALID_ARG;
     if (K % (LIN_BK * ksplit) != 0 || N % 8 != 0) return D3TOM_ERR_UNSUPPORTED;
     if ((size_t)M * K * 2 >= (1ull << 31) || (size_t)N * K * 2 >= (1ull << 31)) return D3TOM_ERR_UNSUPPORTED;
-    return launch_linear<4, LIN_PARTIAL>(a, w, M, N, K, nullptr, partial, N, ksplit, 0, N, st);
+    return launch_linear_cfg<LIN_PARTIAL>(cfg, a, w, M, N, K, nullptr, partial, N, ksplit, 0, N, st);
 }
 
 // rope_cs != nullptr (PLAIN only, stacked q | k | v weight with out_chunk = d, head size rope_dh of 64 or 128): the
 // rotary embedding of the q and k sections is applied in the epilogue; rope_cs[row * rope_dh / 2 + c] = (cos, sin)
 int linear_run(const void* a, const void* w, int M, int N, int K, int epilogue, const void* residual, void* out,
-               int out_chunk, int tm_override, hipStream_t st, const float2* rope_cs, int rope_dh) {
+               int out_chunk, int tile, hipStream_t st, const float2* rope_cs, int rope_dh) {
     if (!a || !w || !out || M < 1 || N < 1 || K < 1) return D3TOM_ERR_INVALID_ARG;
     if (epilogue < LIN_PLAIN || epilogue > LIN_SWIGLU) return D3TOM_ERR_INVALID_ARG;
     if (rope_cs && (epilogue != LIN_PLAIN || (rope_dh != 64 && rope_dh != 128) || out_chunk <= 0 || out_chunk % rope_dh != 0 ||
@@ -383,22 +428,29 @@ int linear_run(const void* a, const void* w, int M, int N, int K, int epilogue, 
     if (epilogue != LIN_PLAIN && out_chunk != n_out) return D3TOM_ERR_INVALID_ARG;
     // 32-bit byte offsets inside each operand
     if ((size_t)M * K * 2 >= (1ull << 31) || (size_t)N * K * 2 >= (1ull << 31)) return D3TOM_ERR_UNSUPPORTED;
-    const int out_bn = (epilogue == LIN_SWIGLU) ? 64 : 128;
-    auto launch = [&](int tm, int col0, int col_end) {
+    // from here on columns are counted in rows of w; SWIGLU stores half as many columns
+    const int per_col = (epilogue == LIN_SWIGLU) ? 2 : 1;
+    auto launch = [&](int cfg, int c0, int c1) {
+        c0 /= per_col; c1 /= per_col;
         switch (epilogue) {
             case LIN_PLAIN:
-                if (rope_cs) return launch_linear_tm<LIN_ROPE>(tm, a, w, M, N, K, residual, out, out_chunk, col0, col_end, st, rope_cs, rope_dh);
-                return launch_linear_tm<LIN_PLAIN>(tm, a, w, M, N, K, residual, out, out_chunk, col0, col_end, st);
-            case LIN_RESIDUAL: return launch_linear_tm<LIN_RESIDUAL>(tm, a, w, M, N, K, residual, out, out_chunk, col0, col_end, st);
-            default: return launch_linear_tm<LIN_SWIGLU>(tm, a, w, M, N, K, residual, out, out_chunk, col0, col_end, st);
+                if (rope_cs) return launch_linear_cfg<LIN_ROPE>(cfg, a, w, M, N, K, residual, out, out_chunk, 1, c0, c1, st, rope_cs, rope_dh);
+                return launch_linear_cfg<LIN_PLAIN>(cfg, a, w, M, N, K, residual, out, out_chunk, 1, c0, c1, st);
+            case LIN_RESIDUAL: return launch_linear_cfg<LIN_RESIDUAL>(cfg, a, w, M, N, K, residual, out, out_chunk, 1, c0, c1, st);
+            default: return launch_linear_cfg<LIN_SWIGLU>(cfg, a, w, M, N, K, residual, out, out_chunk, 1, c0, c1, st);
         }
     };
-    if (tm_override == 1 || tm_override == 2 || tm_override == 4) return launch(tm_override, 0, n_out);
-    int tm_a, tm_b;
-    const int cols_a = linear_plan_two(M, ceil_div(n_out, out_bn), &tm_a, &tm_b);
-    if (cols_a == 0) return launch(tm_a, 0, n_out);
-    const int status = launch(tm_a, 0, cols_a * out_bn);
-    return status != D3TOM_OK ? status : launch(tm_b, cols_a * out_bn, n_out);
+    if (tile) {
+        const int bm = (tile & 15) * 64, bn = (tile >> 4) * 64;
+        for (int c = 0; c < LIN_NTILES; ++c)
+            if (LIN_TILES[c].bm == bm && LIN_TILES[c].bn == bn) return launch(c, 0, N);
+        if (bn) return D3TOM_ERR_INVALID_ARG;
+        double est;
+        return launch(linear_pick(M, N, K / LIN_BK, 1, bm, &est), 0, N);
+    }
+    const LinPlan p = linear_plan(M, N, K / LIN_BK);
+    const int status = launch(p.cfg_a, 0, p.cols_a);
+    return (status != D3TOM_OK || p.cols_a >= N) ? status : launch(p.cfg_b, p.cols_a, N);
 }
 
 }  // namespace d3tom
@@ -408,9 +460,11 @@ extern "C" int d3tom_linear(const void* a, const void* w, int rows, int n_w_rows
     return d3tom::linear_run(a, w, rows, n_w_rows, K, epilogue, residual, out, out_chunk, 0, (hipStream_t)stream, nullptr, 0);
 }
 
-// Same as d3tom_linear with the row-tile height fixed (64, 128 or 256 rows: tile = 1, 2, 4); for tuning.
+// Same as d3tom_linear with the tile fixed: its height (64, 128 or 256 rows: low four bits 1, 2, 4) and, unless zero, its width in
+// rows of w (128, 192 or 256: the bits above 2, 3, 4; 64 x 192 is not built); for tuning and tests.
 extern "C" int d3tom_linear_tile(const void* a, const void* w, int rows, int n_w_rows, int K, int epilogue,
                                  const void* residual, void* out, int out_chunk, int tile, void* stream) {
-    if (tile != 1 && tile != 2 && tile != 4) return D3TOM_ERR_INVALID_ARG;
+    const int h = tile & 15, wd = tile >> 4;
+    if (tile < 0 || (h != 1 && h != 2 && h != 4) || (wd != 0 && (wd < 2 || wd > 4))) return D3TOM_ERR_INVALID_ARG;
     return d3tom::linear_run(a, w, rows, n_w_rows, K, epilogue, residual, out, out_chunk, tile, (hipStream_t)stream, nullptr, 0);
 }

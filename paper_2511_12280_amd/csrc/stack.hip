@@ -6,16 +6,15 @@
 
 namespace d3tom {
 int linear_run(const void* a, const void* w, int M, int N, int K, int epilogue, const void* residual, void* out,
-               int out_chunk, int tm_override, hipStream_t st, const float2* rope_cs = nullptr, int rope_dh = 0);
+               int out_chunk, int tile, hipStream_t st, const float2* rope_cs = nullptr, int rope_dh = 0);
 int rope_table_run(const int32_t* pos, int rows, int dh, float theta, float2* table, hipStream_t st);
 int rmsnorm_run(const void* x, const void* gain, int rows, int d, float eps, void* y, hipStream_t st);
 int rope_run(void* q, void* k, const int32_t* pos, int rows, int H, int dh, float theta, hipStream_t st);
-int linear_split_plan(int M, int N, int K);
-int linear_partial_run(const void* a, const void* w, int M, int N, int K, int ksplit, float* partial, hipStream_t st);
+int linear_split_plan(int M, int N, int K, size_t max_floats, int* cfg);
+int linear_partial_run(const void* a, const void* w, int M, int N, int K, int ksplit, int cfg, float* partial, hipStream_t st);
 int add_norm_run(const float* part, int nsplit, const void* residual, const void* gain, int rows, int d, float eps,
                  void* h, void* y, hipStream_t st);
-// float32 partial products of a split projection: the plan only splits while the 256 x 128 tiles of the result
-// number at most 64, i.e. at most 2 Mi elements per slice, 4 slices
+// float32 partial products of a split projection: the plan only splits while all slices fit
 constexpr size_t STACK_PARTIAL_BYTES = (size_t)4 * 64 * 256 * 128 * sizeof(float);
 
 enum { LIN_PLAIN = 0, LIN_RESIDUAL = 1, LIN_SWIGLU = 2 };
@@ -215,9 +214,10 @@ extern "C" int d3tom_stack_step_batch(const void* x, int B, const int32_t* N_h, 
         // caller's input is never written
         void* post = (cur == x) ? h : const_cast<void*>(cur);
         bool ffn_nrm_ready = false;
-        const int ks_o = linear_split_plan(n, d, d);
+        int cfg_o, cfg_d;
+        const int ks_o = linear_split_plan(n, d, d, STACK_PARTIAL_BYTES / sizeof(float), &cfg_o);
         if (ks_o > 1) {
-            D3TOM_TRY(linear_partial_run(att, b.w_o, n, d, d, ks_o, part, st));
+            D3TOM_TRY(linear_partial_run(att, b.w_o, n, d, d, ks_o, cfg_o, part, st));
             D3TOM_TRY(add_norm_run(part, ks_o, cur, merge_here ? nullptr : b.ffn_norm, n, d, eps, post, nrm, st));
             ffn_nrm_ready = !merge_here;
         } else {
@@ -252,9 +252,9 @@ extern "C" int d3tom_stack_step_batch(const void* x, int B, const int32_t* N_h, 
         if (!ffn_nrm_ready) D3TOM_TRY(rmsnorm_run(ht, b.ffn_norm, n, d, eps, nrm, st));
         D3TOM_TRY(linear_run(nrm, b.w_gate_up, n, 2 * F, d, LIN_SWIGLU, nullptr, act, 0, 0, st));
         void* outp = last ? y : ht;                  // in place, except that the last block writes the caller's y
-        const int ks_d = linear_split_plan(n, d, F);
+        const int ks_d = linear_split_plan(n, d, F, STACK_PARTIAL_BYTES / sizeof(float), &cfg_d);
         if (ks_d > 1) {
-            D3TOM_TRY(linear_partial_run(act, b.w_down, n, d, F, ks_d, part, st));
+            D3TOM_TRY(linear_partial_run(act, b.w_down, n, d, F, ks_d, cfg_d, part, st));
             D3TOM_TRY(add_norm_run(part, ks_d, ht, last ? nullptr : blocks[l].attn_norm, n, d, eps, outp, nrm, st));
             nrm_ready = !last;
         } else {

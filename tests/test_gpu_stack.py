@@ -152,6 +152,24 @@ def test_linear_swiglu(B, M, F, K, tile):
     _one_step(_host(out), ref, f"swiglu {M}x{F}x{K} tile {tile}")
 
 
+@pytest.mark.parametrize("height,width", [(1, 2), (1, 4), (2, 2), (2, 3), (2, 4), (4, 2), (4, 3), (4, 4)])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 64), (257, 392, 192), (300, 520, 576)])       # one row; one past a tile, odd ring tails
+def test_linear_every_tile(B, M, N, K, height, width):
+    rng = np.random.default_rng([M, N, K, width])
+    a = W.round_to(rng.standard_normal((M, K)).astype(np.float32), "bf16")
+    w = W.round_to((2.0 * rng.standard_normal((2 * N, K)) / np.sqrt(K)).astype(np.float32), "bf16")
+    r = W.round_to(rng.standard_normal((M, N)).astype(np.float32), "bf16")
+    ta, tw, tr = _dev(a), _dev(w), _dev(r)
+    out = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    B.d3tom_linear_tile(ta, tw[:N].contiguous(), B.D3TOM_LINEAR_RESIDUAL, out, height + 16 * width, residual=tr)
+    act = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    B.d3tom_linear_tile(ta, tw, B.D3TOM_LINEAR_SWIGLU, act, height + 16 * width)
+    torch.cuda.synchronize()
+    up = OS.linear(a, w[N:])
+    _one_step(_host(out), OS.round_bf16(r.astype(np.float64) + OS.linear(a, w[:N])), "residual")
+    _one_step(_host(act), OS.round_bf16(OS.swiglu(OS.linear(a, w[:N]), up)), "swiglu")
+
+
 def test_linear_two_launch_plan(B):
     """Shapes whose 256-row tiles fill one round of the chip and a bit: the library cuts the columns into a
     full round of tall tiles and a remainder with smaller tiles (two launches, one result)."""
