@@ -1,40 +1,56 @@
 // d3tom_attend: bidirectional (unmasked) attention over the shortened sequence (Section 3.2: the
 // shortened tensor runs through the later layers; Section 4.3: the 2 n^2 d term of FLOPs_layer).
 //
-// bf16 path — flash-style, MFMA 32x32x16, written "transposed" so that everything per query stays
-// inside one lane:
+// bf16 path — flash-style, MFMA 16x16x32, written "transposed" so that everything per query stays
+// inside one lane column:
 //     S^T = K Q^T      A = K tile (LDS, row-major), B = Q^T (registers, loaded once per workgroup)
 //     P^T = exp2(S^T * scale*log2e - m)            in registers, the MFMA accumulator layout
 //     O^T += V^T P^T   A = V^T, read from the row-major V tile in LDS with the transposing LDS read
 //                      (ds_read_b64_tr_b16), B = P^T straight from the accumulator registers of the
 //                      first product (no LDS round trip for P)
-// In the accumulator layout a lane owns ONE query column (lane % 32) and 16 of the 32 key rows, so
-// the running max / sum of the online softmax need one cross-lane exchange (lane ^ 32) per tile and
+// In the accumulator layout lane (r, g) = (lane % 16, lane / 16) owns query column r and, of every 16 keys, keys
+// 4g .. 4g + 3, so the running max / sum of the online softmax need exchanges between four lanes only, and
 // the rescale of O^T is a per-lane scalar.  The contraction index of the second product (keys) is
 // fed in the order the accumulator holds it; V^T is read from LDS in that same order.
 //
-// Workgroup = 4 waves x 32 queries of one head, 64 keys per LDS stage.  K and V tiles go HBM/L2 -> LDS
-// with direct loads (buffer_load ... lds, no register staging; rows past the end of the sample load as
-// zeros through the buffer bounds check) into a two-stage ring; rows are unpadded and their 16-byte
-// chunks XOR-swizzled by the row index instead.  Per tile a wave requests all 16 K fragments before the
-// first MFMA, runs the two accumulation chains of S^T interleaved, requests the V^T fragments of the
-// first 32 keys and starts the direct loads of the next stage, then does the softmax arithmetic while
-// those are in flight (measured on gfx950: direct loads overlap vector-ALU work but not MFMAs), and
-// finally the 16 MFMAs of the second product.  Softmax state and accumulators are float32; two
-// workgroups fit a CU.  A wave raises its priority (s_setprio) for its MFMA bursts: the SIMD's arbiter
-// otherwise favours the older of its two waves, and while that one issues softmax arithmetic back to back
-// the other's next MFMA waits although the matrix core is idle (measured: 3-5 % at 1.2k-2k keys).
+// A workgroup has eight waves of 32 (or 16) queries in two groups of four; wave i and wave i + 4 share a SIMD.  The groups
+// alternate (ping-pong): while one issues the MFMAs of a 64-key tile (S of tile i + 1, O += V P of tile i: 64 of them, 1024
+// clocks), the other does the softmax arithmetic of its tile; a barrier ends the phase.  That pays because the smaller MFMA
+// shape lets another wave's vector instructions through: per tile 1058 clocks of MFMAs and 756 of softmax arithmetic of the
+// other wave take 1250 clocks together, whereas beside MFMA 32x32x16 the exponentials do not issue at all (1029 + 756 -> 1780).
+// Measured at 32 heads of 128 (four independent waves on the larger shape before): 3773 keys 240 -> 197 us, 1951 keys
+// 70 -> 58 us, 4096 keys 214 us = 1280 TFLOP/s, at 1.95 GHz: the card lowers its clock under this load (2960 clocks per
+// tile and pair of groups; at 3170 clocks it ran at 2.02 GHz and took as long), so what remains is set by power.
+//
+// K and V tiles go HBM/L2 -> LDS with direct loads (buffer_load ... lds, no register staging; rows past the end of the sample
+// load as zeros through the buffer bounds check) into a ring; rows are unpadded and their 16-byte chunks XOR-swizzled by the
+// row index instead.  Loads are issued in the softmax phase, and the first K fragments of a tile are read there, so that the
+// MFMA phase starts at once.
+//
+// The softmax arithmetic paces the loop (every MFMA of the other wave takes 8 clocks of the vector issue port as well), so
+// it is cut to one fma and one exp2 per logit and the packing to bf16:
+//   - the row sums come from the matrix core too, a fragment of ones times P^T (two MFMAs per 32 keys instead of 32 adds);
+//   - the weights and the tail mask of the weighted form enter as the C operand of S^T (log2 w / scale2, -inf);
+//   - no running maximum: the reference is the maximum of the first tile, and probabilities are scaled by 2^-24 under it.
+//     A logit that exceeds it by 2^25 shows in the top exponent bit of the packed probabilities (one OR over them
+//     finds it, infinities included); only then the tile's true maximum is taken, the accumulators rescaled and the tile
+//     redone.  Numerator and denominator carry the same factor, float32 and bf16 keep their relative precision, and what falls
+//     below the normal range is 2^-77 of the largest term at least.
+// ONLINE is the form with the running maximum of the tiles seen so far and float32 row sums: 3800 clocks per tile, 222 us at
+// 3773 keys.  Blocks whose output a merge still compares use it: the probabilities are rounded to bf16 relative to their
+// reference, and between near-duplicate rows that rounding decides a cosine's order.
 //
 // The generic path (float32 or any head size) is one workgroup per (query, head) with a chunked
 // online softmax in plain float arithmetic.
 #include "common.hpp"
+#include "direct_load.hpp"
 #include <type_traits>
 
 namespace d3tom {
 
-constexpr int ATT_BQ = 128;     // queries per workgroup
-constexpr int ATT_BK = 64;      // keys per stage
-constexpr int ATT_NS = 2;       // LDS ring depth
+constexpr int ATT_BK = 64;      // keys per tile
+constexpr int ATT_SLOTS = 4;    // ring slots of one K tile and one V tile
+constexpr float ATT_BIAS = 24.f;    // without a running maximum the probabilities are kept 2^24 below their usual scale
 
 typedef __attribute__((address_space(3))) void* att_lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* att_glb_ptr_t;
@@ -48,11 +64,6 @@ __device__ __forceinline__ att_short4 lds_read_tr16(const char* p) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)p);
 }
 
-// all of this wave's direct loads have landed and all its LDS reads are done; then meet the other waves
-__device__ __forceinline__ void att_wait_and_barrier() {
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 #if defined(__HIP_DEVICE_COMPILE__)
 // buffer resource over [p, p + bytes), built from values the compiler can see are wave-uniform
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t att_uniform_rsrc(const void* p, uint32_t bytes) {
@@ -62,7 +73,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t att_uniform_rsrc(const void* p
 }
 // One wave-wide direct load HBM/L2 -> LDS: lane i fetches 16 bytes at byte offset `voff` of the buffer
 // (zeros when that is past the end of the buffer) into LDS byte lds_base + 16 i.  Issued from inline
-// assembly on purpose: the waits for these loads are placed by hand (att_wait_and_barrier), and the
+// assembly on purpose: the waits for these loads are placed by hand (wait_loads), and the
 // compiler, when it sees such a load, makes every later transposing LDS read wait for all of them.
 __device__ __forceinline__ void att_direct_load(__amdgpu_buffer_rsrc_t rsrc, int voff, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
@@ -79,6 +90,17 @@ __device__ __forceinline__ float att_pair_sum(float x) {
     typedef unsigned att_u2 __attribute__((ext_vector_type(2)));
     const att_u2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// the four lanes (l, l ^ 16, l ^ 32, l ^ 48) that share a query column
+__device__ __forceinline__ float att_quad_max(float x) {
+    typedef unsigned att_u2 __attribute__((ext_vector_type(2)));
+    const att_u2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return att_pair_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float att_quad_sum(float x) {
+    typedef unsigned att_u2 __attribute__((ext_vector_type(2)));
+    const att_u2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return att_pair_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 #endif
 
@@ -97,24 +119,27 @@ __device__ __forceinline__ float key_log2_weight(const KeyWeights& kw, int b, in
     const int k0 = kw.kept_off[b], kn = kw.kept_off[b + 1] - k0;
     return (r >= 0 && r < kn) ? __log2f((float)max(kw.counts[k0 + r], 1)) : 0.f;
 }
-constexpr int ATT_WKEYS = 3584;     // longest sample of the weighted tiled kernel: its log2 weights sit in LDS, and two
-                                    // workgroups (64 KB ring + weights each) still fit the 160 KB of a CU
+constexpr int ATT_WKEYS = 3584;     // longest sample of the weighted tiled kernel: its log2 weights sit in LDS beside the ring
 
-template <int DH, bool WGT>
-__global__ __launch_bounds__(256, 2) void attend_bf16_kernel(
+template <int DH, bool WGT, int NQ, bool ONLINE>
+__global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ cu, int H, int nB, int nqt, float scale2, uint16_t* __restrict__ o, KeyWeights kw) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    constexpr int KS = DH / 16;                 // k-steps of the first product
-    constexpr int DT = DH / 32;                 // 32-dim tiles of O^T
+    constexpr int KS = DH / 32;                 // k-steps of the first product
+    constexpr int DB = DH / 16;                 // 16-dim blocks of O^T
     constexpr int ROWB = DH * 2;                // bytes per K / V row in LDS (unpadded, chunks swizzled)
     constexpr int NCHK = DH / 8;                // 16-byte chunks per row
     constexpr int RPI = 64 / NCHK;              // rows covered by one wave-wide direct load (1 KB)
-    constexpr int LD = ATT_BK / (4 * RPI);      // direct loads per wave, per operand, per stage
+    constexpr int LD = ATT_BK / (8 * RPI);      // direct loads per wave and operand tile
     constexpr int TILE = ATT_BK * ROWB;         // bytes of one K (or V) tile
-    constexpr int STAGE = 2 * TILE;
+    constexpr int STAGE = 2 * TILE;             // stage j: K of tile j, V of tile j - 1
+    constexpr int NS = ATT_SLOTS;
+    constexpr int AHEAD = NS - 1;               // the softmax phase of tile j fetches stage j + AHEAD
+    constexpr int BQ = NQ * 128;                // queries of the workgroup: NQ blocks of 16 per wave
+    constexpr int KPRE = 2 * KS;                // K fragments read ahead: the first 32 keys
     extern __shared__ __attribute__((aligned(16))) char ring[];
-    __shared__ __attribute__((aligned(16))) float lw_s[WGT ? ATT_WKEYS + ATT_BK : 4];
+    __shared__ __attribute__((aligned(16))) float w_s[WGT ? ATT_WKEYS : 4];
 
     const int xcd = blockIdx.x & 7, li = blockIdx.x >> 3;
     const int hb = (li / nqt) * 8 + xcd, qt = li % nqt;         // hb = sample * H + head
@@ -122,247 +147,289 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_kernel(
     const int h = hb % H, b = hb / H;
     const int tok0 = cu[b];
     const int n = min(cu[b + 1] - tok0, WGT ? ATT_WKEYS : 0x7FFFFFFF);
-    if (qt * ATT_BQ >= n) return;
+    if (qt * BQ >= n) return;
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), grp = wave >> 2;
     if constexpr (WGT) {
-        for (int j = tid; j < ((n + ATT_BK - 1) / ATT_BK) * ATT_BK; j += 256) lw_s[j] = (j < n) ? key_log2_weight(kw, b, j) : 0.f;
-        __syncthreads();
+        // what the logits start from; -inf past the end of the sample: those keys then need no other mask
+        for (int j = tid; j < ((n + ATT_BK - 1) / ATT_BK) * ATT_BK; j += 512)
+            w_s[j] = (j < n) ? key_log2_weight(kw, b, j) / scale2 : -INFINITY;
     }
-    const int c = lane & 31, g = lane >> 5;
+    const int r = lane & 15, g = lane >> 4;
     const size_t rs = (size_t)H * DH;                      // token stride (elements)
-    const uint16_t* kb = k + (size_t)tok0 * rs + (size_t)h * DH;
-    const uint16_t* vb = v + (size_t)tok0 * rs + (size_t)h * DH;
+    const uint16_t* kb_ = k + (size_t)tok0 * rs + (size_t)h * DH;
+    const uint16_t* vb_ = v + (size_t)tok0 * rs + (size_t)h * DH;
     // this head's K / V rows of this sample; a row index >= n is past the end and loads as zeros
     const uint32_t span = (uint32_t)(((size_t)(n - 1) * rs + DH) * 2);
-    const __amdgpu_buffer_rsrc_t rk = att_uniform_rsrc(kb, span), rv = att_uniform_rsrc(vb, span);
+    const __amdgpu_buffer_rsrc_t rk = att_uniform_rsrc(kb_, span), rv = att_uniform_rsrc(vb_, span);
     const int row_bytes = (int)(rs * 2);
 
-    const int qrow = qt * ATT_BQ + wave * 32 + c;
-    const bool qvalid = qrow < n;
-    bf16x8 qf[KS];
-    {
-        const uint16_t* qp = q + (size_t)(tok0 + (qvalid ? qrow : 0)) * rs + (size_t)h * DH + g * 8;
+    const int q0 = qt * BQ + wave * NQ * 16 + r;            // query of column block 0; block 1 is 16 further
+    bf16x8 qf[NQ][KS];
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
+    for (int qb = 0; qb < NQ; ++qb) {
+        const bool valid = q0 + qb * 16 < n;
+        const uint16_t* qp = q + (size_t)(tok0 + (valid ? q0 + qb * 16 : 0)) * rs + (size_t)h * DH + g * 8;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
             bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-            qf[kk] = qvalid ? *reinterpret_cast<const bf16x8*>(qp + kk * 16) : z;
+            qf[qb][ks] = valid ? *reinterpret_cast<const bf16x8*>(qp + ks * 32) : z;
         }
     }
-    f32x16 ot[DT];
+    f32x4 ot[DB][NQ];
 #pragma unroll
-    for (int t = 0; t < DT; ++t)
+    for (int t = 0; t < DB; ++t)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) ot[t][e] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;       // running max of the RAW logits, running sum of exp2
+        for (int qb = 0; qb < NQ; ++qb) ot[t][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // m_run: what the exponents refer to, in RAW logits; ms: what they subtract; l_run: sum of this lane's probabilities (ONLINE);
+    // lt: sum of the column's probabilities, all four elements alike (else)
+    float m_run[NQ], ms[NQ], l_run[NQ];
+    f32x4 lt[NQ];
+    bf16x8 ones;
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) { m_run[qb] = -INFINITY; ms[qb] = 0.f; l_run[qb] = 0.f; lt[qb] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
 
-    // direct loads: lane -> (row, chunk position); the chunk fetched into position p of row r is
-    // p ^ (r mod NCHK) for K (operand reads walk 16+ consecutive rows) and p ^ ((r & 3) * 4) for V
-    // (transposing reads touch 4 consecutive rows per 16-lane group)
-    const int ld_pos = lane % NCHK;
+    // direct loads: lane -> (row, chunk position).  The chunk fetched into position p of row x is p ^ f(x): K fragments are 16
+    // consecutive rows of one chunk, transposing reads of V four consecutive rows (per 16 lanes) of one 32-byte piece.
     int k_off[LD], v_off[LD];                   // byte offsets inside the head's K / V for key0 = 0
 #pragma unroll
     for (int i = 0; i < LD; ++i) {
-        const int r = wave * (ATT_BK / 4) + lane / NCHK + i * RPI;
-        k_off[i] = r * row_bytes + (((ld_pos ^ (r & 15)) & (NCHK - 1)) << 4);
-        v_off[i] = r * row_bytes + (((ld_pos ^ ((r & 3) * 4)) & (NCHK - 1)) << 4);
+        const int x = (wave * LD + i) * RPI + lane / NCHK, pos = lane % NCHK;
+        k_off[i] = x * row_bytes + ((pos ^ (DH == 128 ? (x & 15) : ((x >> 1) & 7))) << 4);
+        v_off[i] = x * row_bytes + ((pos ^ (DH == 128 ? (x & 7) << 1 : ((x >> 1) & 3) << 1)) << 4);
     }
     const uint32_t ring0 = (uint32_t)(size_t)(att_lds_ptr_t)ring;
-    const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(ring0 + wave * (ATT_BK / 4) * ROWB);
-    auto issue = [&](int key0, int stage) {
-        const int kofs = key0 * row_bytes;
+    const uint32_t wave_lds = ring0 + wave * LD * 1024;
+    auto issue_one = [&](int j, int i) {        // one of the 2 LD loads of stage j
+        const uint32_t dst = wave_lds + (j % NS) * STAGE + (i >> 1) * 1024;
+        if (i & 1) att_direct_load(rv, v_off[i >> 1] + (j > 0 ? j - 1 : 0) * ATT_BK * row_bytes, dst + TILE);
+        else att_direct_load(rk, k_off[i >> 1] + j * ATT_BK * row_bytes, dst);
+    };
+    auto issue = [&](int j) {
 #pragma unroll
-        for (int i = 0; i < LD; ++i) {
-            att_direct_load(rk, k_off[i] + kofs, wave_lds + stage * STAGE + i * RPI * ROWB);
-            att_direct_load(rv, v_off[i] + kofs, wave_lds + stage * STAGE + TILE + i * RPI * ROWB);
+        for (int i = 0; i < 2 * LD; ++i) issue_one(j, i);
+    };
+    // addresses inside a stage; what varies from fragment to fragment goes in by exclusive or
+    const int k_addr = r * ROWB + ((g ^ (DH == 128 ? r : (r >> 1) & 7)) << 4);      // K fragment of rows 0..15, chunk 4 ks + g
+    // transposing read: row 4 g + tj, 4-dim quad tq of a 16-dim block; the block number goes in by exclusive or (32-byte pieces)
+    const int tj = (lane & 15) >> 2, tq = lane & 3, tx = 4 * g + tj;
+    const int v_addr = TILE + tx * ROWB + (((tq >> 1) ^ (DH == 128 ? (tx & 7) << 1 : ((tx >> 1) & 3) << 1)) << 4) + (tq & 1) * 8;
+
+    bf16x8 kf[KPRE];                            // the first 32 keys' fragments of the next tile
+    auto read_first = [&](const char* sb, int f) {
+        kf[f] = *reinterpret_cast<const bf16x8*>(sb + (k_addr ^ ((f / 2) << 6)) + (f % 2) * 16 * ROWB);
+    };
+    f32x4 st[4][NQ];                            // S^T: [16-key block][query block]
+    bf16x8 pf[2][NQ];                           // P^T: [32-key half][query block]
+    // S of tile j (QK) and O += V P of tile j - 1 (PV).  A wave that issues LDS reads back to back waits for the CU's one LDS at each
+    // of them while the matrix core idles; every fragment of what comes next is therefore read right behind the MFMAs that used
+    // up the registers it goes into (a bunch of reads in front of each part: 1710 clocks per phase; dealt: 1350).
+    static_assert(KPRE == DB, "a V fragment follows every K fragment");
+    auto mfma_phase = [&](int j, auto qk_c, auto pv_c) {
+        constexpr bool QK = decltype(qk_c)::value, PV = decltype(pv_c)::value;
+        typedef __attribute__((__vector_size__(8 * sizeof(short)))) short att_short8;
+        const char* sb = ring + (j % NS) * STAGE;
+        att_short8 vf[DB];                      // V^T of 32 keys, 16 dims each
+        auto read_v = [&](int kt, int t) {
+            const char* p = sb + (v_addr ^ (t << 5)) + kt * 32 * ROWB;
+            vf[t] = __builtin_shufflevector(lds_read_tr16(p), lds_read_tr16(p + 16 * ROWB), 0, 1, 2, 3, 4, 5, 6, 7);
+        };
+        auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
+        fence();
+        if constexpr (QK) {
+            f32x4 c0[4];                        // what S^T starts from, per 16-key block
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) {
+                if constexpr (WGT) c0[kb] = *reinterpret_cast<const f32x4*>(&w_s[j * ATT_BK + kb * 16 + g * 4]);
+                else c0[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int i = 0; i < 2 * KPRE; ++i) {
+                const int f = i % KPRE, ks = f / 2, kb = (i / KPRE) * 2 + f % 2;
+#pragma unroll
+                for (int qb = 0; qb < NQ; ++qb)
+                    st[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[f], qf[qb][ks], ks ? st[kb][qb] : c0[kb], 0, 0, 0);
+                fence();
+                if (i < KPRE) kf[f] = *reinterpret_cast<const bf16x8*>(sb + (k_addr ^ (ks << 6)) + (kb + 2) * 16 * ROWB);
+                else if constexpr (PV) read_v(0, f);
+                fence();
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < DB; ++t) read_v(0, t);
+        }
+        if constexpr (PV) {
+#pragma unroll
+            for (int i = 0; i < 2 * DB; ++i) {
+                const int kt = i / DB, t = i % DB;
+#pragma unroll
+                for (int qb = 0; qb < NQ; ++qb)
+                    ot[t][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf[t]), pf[kt][qb], ot[t][qb], 0, 0, 0);
+                fence();
+                if (kt == 0) read_v(1, t);
+                fence();
+            }
+            if constexpr (!ONLINE) {
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                    for (int qb = 0; qb < NQ; ++qb) lt[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[kt][qb], lt[qb], 0, 0, 0);
+            }
+        }
+        fence();
+    };
+    auto softmax_phase = [&](int j, auto last_c) {
+        constexpr bool LAST = decltype(last_c)::value;
+        if (LAST && !WGT && (j + 1) * ATT_BK > n) {
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (j * ATT_BK + kb * 16 + g * 4 + e >= n) st[kb][qb][e] = -INFINITY;
+        }
+        // In eight steps, with the loads of stage j + AHEAD and the reads of tile j + 1's first fragments dealt among them: issued
+        // in one go they hold the wave up (464 of 1466 clocks).
+        float sum[NQ];
+        auto probabilities = [&](auto deal_c) {
+#pragma unroll
+            for (int qb = 0; qb < NQ; ++qb) sum[qb] = 0.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int kb = i >> 1, qb = NQ == 2 ? i & 1 : 0, e0 = NQ == 2 ? 0 : (i & 1) * 2;
+#pragma unroll
+                for (int e = e0; e < e0 + 2 * NQ; ++e) {
+                    const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(st[kb][qb][e], scale2, -ms[qb]));
+                    if constexpr (ONLINE) sum[qb] += p;
+                    pf[kb >> 1][qb][(kb & 1) * 4 + e] = (__bf16)p;
+                }
+                if constexpr (decltype(deal_c)::value) {
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int f = i * KPRE / 8; f < (i + 1) * KPRE / 8; ++f) read_first(ring + ((j + 1) % NS) * STAGE, f);
+#pragma unroll
+                    for (int f = i * 2 * LD / 8; f < (i + 1) * 2 * LD / 8; ++f) issue_one(j + AHEAD, f);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        };
+        float m_new[NQ];
+        auto maximum = [&](int qb) {
+            float t = m_run[qb];
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) t = fmaxf(t, st[kb][qb][e]);
+            m_new[qb] = att_quad_max(t);        // finite: every tile holds at least one key of the sample
+            ms[qb] = ONLINE ? m_new[qb] * scale2 : __builtin_fmaf(m_new[qb], scale2, ATT_BIAS);
+        };
+        auto rescale = [&](int qb) {
+            const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_new[qb]) * scale2);
+            if constexpr (ONLINE) l_run[qb] *= alpha;
+            else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) lt[qb][e] *= alpha;
+            }
+#pragma unroll
+            for (int x = 0; x < DB; ++x)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ot[x][qb][e] *= alpha;
+            m_run[qb] = m_new[qb];
+        };
+        using dealt = std::integral_constant<bool, !LAST>;
+        if constexpr (ONLINE) {
+            bool moved = false;
+#pragma unroll
+            for (int qb = 0; qb < NQ; ++qb) { maximum(qb); moved |= m_new[qb] > m_run[qb]; }
+            probabilities(dealt());
+            if (__builtin_amdgcn_ballot_w64(moved) != 0) {                  // some query of this wave moved its maximum
+#pragma unroll
+                for (int qb = 0; qb < NQ; ++qb) rescale(qb);
+            }
+#pragma unroll
+            for (int qb = 0; qb < NQ; ++qb) l_run[qb] += sum[qb];
+        } else {
+            probabilities(dealt());
+            uint32_t seen = 0;                  // bit 14 of a half: one of the packed probabilities is at least 2
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int qb = 0; qb < NQ; ++qb) {
+                    typedef uint32_t att_u4 __attribute__((ext_vector_type(4)));
+                    const att_u4 w = __builtin_bit_cast(att_u4, pf[kt][qb]);
+                    seen |= (w[0] | w[1]) | (w[2] | w[3]);
+                }
+            if (j == 0 || __builtin_amdgcn_ballot_w64((seen & 0x40004000u) != 0) != 0) {
+#pragma unroll
+                for (int qb = 0; qb < NQ; ++qb) { maximum(qb); rescale(qb); }
+                probabilities(std::integral_constant<bool, false>());
+            }
         }
     };
-    // K operand fragments: lane (key row c, g) reads chunk (2 kk + g) of its row, swizzled by the row
-    int k_addr[KS];
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) k_addr[kk] = c * ROWB + ((((kk * 2 + g) ^ (c & 15)) & (NCHK - 1)) << 4);
-    // transposing-read geometry of this lane: 16-lane group -> (g, dim half), lane in group -> (row j, 4-dim quad t)
-    const int tr_j = (lane & 15) >> 2, tr_t = lane & 3, tr_half = (lane >> 4) & 1;
-    int v_addr[DT];
-#pragma unroll
-    for (int t = 0; t < DT; ++t) {
-        const int chunk = t * 4 + tr_half * 2 + (tr_t >> 1);
-        v_addr[t] = TILE + (g * 4 + tr_j) * ROWB + (tr_t % 2) * 8 + (((chunk ^ (tr_j * 4)) & (NCHK - 1)) << 4);
-    }
 
     const int ntile = (n + ATT_BK - 1) / ATT_BK;
-    // one 64-key tile out of ring stage STG (a compile-time constant so that every LDS offset folds
-    // into the instruction)
-    auto tile = [&](auto stg_c, int it) {
-        constexpr int STG = decltype(stg_c)::value;
-        const int key0 = it * ATT_BK;
-        att_wait_and_barrier();                             // stage STG has landed; the other stage is free
-        const char* sb = ring + STG * STAGE;
-
-        // all K fragments of the tile are requested before the first MFMA
-        bf16x8 kf[2][KS];
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-            for (int kk = 0; kk < KS; ++kk)
-                kf[kt][kk] = *reinterpret_cast<const bf16x8*>(sb + k_addr[kk] + kt * 32 * ROWB);
-        __builtin_amdgcn_sched_barrier(0);
-        // S^T = K Q^T for two 32-key blocks, the two accumulation chains interleaved
-        f32x16 st[2];
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) st[kt][e] = 0.f;
-        __builtin_amdgcn_s_setprio(3);
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-            st[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][kk], qf[kk], st[0], 0, 0, 0);
-            st[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][kk], qf[kk], st[1], 0, 0, 0);
-        }
-        __builtin_amdgcn_s_setprio(0);
-        __builtin_amdgcn_sched_barrier(0);
-        // V^T fragments of the first 32 keys are requested now and land during the softmax arithmetic
-        att_short4 vf[2][2][DT][2];                 // [kt][hh][t][a/b]
-        auto read_v = [&](int kt) {
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int t = 0; t < DT; ++t) {
-                    const char* pa = sb + v_addr[t] + (kt * 32 + hh * 16) * ROWB;
-                    vf[kt][hh][t][0] = lds_read_tr16(pa);
-                    vf[kt][hh][t][1] = lds_read_tr16(pa + 8 * ROWB);
-                }
-        };
-        read_v(0);
-        __builtin_amdgcn_sched_barrier(0);
-        // the loads of the next stage start here, beside the softmax arithmetic: direct loads and MFMAs
-        // slow each other down, direct loads and vector-ALU work do not
-        if (it + 1 < ntile) issue(key0 + ATT_BK, STG ^ 1);
-        __builtin_amdgcn_sched_barrier(0);
-        // online softmax in base 2 on the raw logits; element e of st[kt]: key kt*32 + (e/4)*8 + 4g + e%4, query c
-        if constexpr (WGT) {
-            // weighted: the maximum is taken on scale2 * logit + log2 w (m_run lives in that scaled domain)
-#pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                for (int e4 = 0; e4 < 4; ++e4) {
-                    const f32x4 w4 = *reinterpret_cast<const f32x4*>(&lw_s[key0 + kt * 32 + e4 * 8 + g * 4]);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int key = key0 + kt * 32 + e4 * 8 + g * 4 + e;
-                        const float t = __builtin_fmaf(st[kt][e4 * 4 + e], scale2, w4[e]);
-                        st[kt][e4 * 4 + e] = (key < n) ? t : -INFINITY;
-                    }
-                }
-            float tmax = st[0][0];
-#pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) tmax = fmaxf(tmax, st[kt][e]);
-            tmax = att_pair_max(tmax);
-            const float m_new = fmaxf(m_run, tmax);
-            float psum = 0.f;
-#pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const float p = __builtin_amdgcn_exp2f(st[kt][e] - m_new);
-                    st[kt][e] = p;
-                    psum += p;
-                }
-            if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-                l_run *= alpha;
-#pragma unroll
-                for (int t = 0; t < DT; ++t)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) ot[t][e] *= alpha;
-            }
-            l_run += psum;
-            m_run = m_new;
-        } else {
-        if (key0 + ATT_BK > n) {
-#pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int key = key0 + kt * 32 + (e >> 2) * 8 + g * 4 + (e & 3);
-                    if (key >= n) st[kt][e] = -INFINITY;
-                }
-        }
-        float tmax = st[0][0];
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) tmax = fmaxf(tmax, st[kt][e]);
-        tmax = att_pair_max(tmax);
-        const float m_new = fmaxf(m_run, tmax);            // finite: every stage holds >= 1 valid key
-        const float ms = m_new * scale2;
-        float psum = 0.f;
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(st[kt][e], scale2, -ms));
-                st[kt][e] = p;
-                psum += p;
-            }
-        if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {      // some query of this wave moved its max
-            const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale2);
-            l_run *= alpha;
-#pragma unroll
-            for (int t = 0; t < DT; ++t)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) ot[t][e] *= alpha;
-        }
-        l_run += psum;                               // per-lane partial; the two halves meet after the last tile
-        m_run = m_new;
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        read_v(1);
-        __builtin_amdgcn_sched_barrier(0);
-        // O^T += V^T P^T
-        __builtin_amdgcn_s_setprio(3);
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                bf16x8 pf;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) pf[j] = (__bf16)st[kt][hh * 8 + j];
-#pragma unroll
-                for (int t = 0; t < DT; ++t) {
-                    const att_short4 va = vf[kt][hh][t][0], vb2 = vf[kt][hh][t][1];
-                    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short att_short8;
-                    const att_short8 v8 = __builtin_shufflevector(va, vb2, 0, 1, 2, 3, 4, 5, 6, 7);
-                    ot[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v8), pf, ot[t], 0, 0, 0);
-                }
-            }
-        __builtin_amdgcn_s_setprio(0);
-    };
     // The query fragments must have arrived before the first direct load is issued: otherwise the
-    // compiler's own wait for them would sit inside the loop, where it would also wait for the direct
-    // loads of the next stage.
+    // compiler's own wait for them would sit inside the loop, where it would also wait for the direct loads.
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) asm volatile("" :: "v"(qf[kk]));
-    issue(0, 0);
-    for (int it = 0; it < ntile; it += 2) {
-        tile(std::integral_constant<int, 0>{}, it);
-        if (it + 1 < ntile) tile(std::integral_constant<int, 1>{}, it + 1);
+    for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) asm volatile("" :: "v"(qf[qb][ks]));
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) issue(j);
+    wait_loads<(AHEAD - 1) * 2 * LD>();
+    if constexpr (WGT) wait_lds();              // the weights
+    phase_barrier();
+#pragma unroll
+    for (int f = 0; f < KPRE; ++f) read_first(ring, f);
+    // Stage j + 1 has to have landed when the softmax phase of tile j begins (its first fragments are read there).  Groups that
+    // share the ring: both wait for their loads before the barrier that ends group 0's MFMA phase of tile j.  Stages behind
+    // j + 1 stay in flight.
+    constexpr int KEEP = (NS - 3) * 2 * LD;
+    if (grp == 1) { wait_loads<KEEP>(); phase_barrier(); }
+    using yes = std::integral_constant<bool, true>;
+    using no = std::integral_constant<bool, false>;
+    mfma_phase(0, yes(), no());
+    // The last tile is peeled off: a loop left in its middle keeps both the accumulators before and after the MFMA phase alive.
+#pragma unroll 1
+    for (int j = 0; j + 1 < ntile; ++j) {
+        if (grp == 0) wait_loads<KEEP>();
+        phase_barrier();
+        softmax_phase(j, no());
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): the fragments are there (a wait the compiler knows of)
+        if (grp == 1) wait_loads<KEEP>();
+        phase_barrier();
+        __builtin_amdgcn_s_setprio(3);
+        mfma_phase(j + 1, yes(), yes());
+        __builtin_amdgcn_s_setprio(0);
     }
-    l_run = att_pair_sum(l_run);
-    if (!qvalid) return;
-    const float inv = 1.0f / l_run;
-    uint16_t* op = o + (size_t)(tok0 + qrow) * rs + (size_t)h * DH;
+    if (grp == 0) wait_loads<0>();
+    phase_barrier();
+    softmax_phase(ntile - 1, yes());
+    if (grp == 1) wait_loads<0>();
+    phase_barrier();
+    mfma_phase(ntile, no(), yes());
+    wait_loads<0>();                            // nothing may be in flight into LDS when the workgroup ends
+    if (grp == 0) phase_barrier();
+
 #pragma unroll
-    for (int t = 0; t < DT; ++t)
+    for (int qb = 0; qb < NQ; ++qb) {
+        const int row = q0 + qb * 16;
+        const float inv = 1.0f / (ONLINE ? att_quad_sum(l_run[qb]) : lt[qb][0]);
+        if (row >= n) continue;
+        uint16_t* op = o + (size_t)(tok0 + row) * rs + (size_t)h * DH + g * 4;
 #pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
+        for (int t = 0; t < DB; ++t) {
             uint2 w;
-            w.x = pack_bf16x2(ot[t][e4 * 4 + 0] * inv, ot[t][e4 * 4 + 1] * inv);
-            w.y = pack_bf16x2(ot[t][e4 * 4 + 2] * inv, ot[t][e4 * 4 + 3] * inv);
-            *reinterpret_cast<uint2*>(op + t * 32 + e4 * 8 + g * 4) = w;
+            w.x = pack_bf16x2(ot[t][qb][0] * inv, ot[t][qb][1] * inv);
+            w.y = pack_bf16x2(ot[t][qb][2] * inv, ot[t][qb][3] * inv);
+            *reinterpret_cast<uint2*>(op + t * 16) = w;
         }
+    }
 #endif
 }
 // ---- short sequences: the keys are split across the four waves -------------------------------------
@@ -716,9 +783,8 @@ __global__ __launch_bounds__(256) void attend_generic_kernel(
 
 using namespace d3tom;
 
-static int attend_run(const void* q, const void* k, const void* v, int dt,
-                      int B, const int32_t* cu_seqlens, int max_seqlen, int H, int dh, float scale,
-                      const int32_t* counts, const int32_t* kept_off, const int32_t* vis_start, void* o, void* stream) {
+static int attend_any(const void* q, const void* k, const void* v, int dt, int B, const int32_t* cu_seqlens, int max_seqlen, int H, int dh,
+                      float scale, const int32_t* counts, const int32_t* kept_off, const int32_t* vis_start, bool online, void* o, void* stream) {
     if (!q || !k || !v || !o || !cu_seqlens) return D3TOM_ERR_INVALID_ARG;
     if (B < 1 || max_seqlen < 1 || H < 1 || dh < 1) return D3TOM_ERR_INVALID_ARG;
     if (!(scale > 0.f) || !(scale < 3.0e38f)) return D3TOM_ERR_INVALID_ARG;      // the running max is taken on raw logits
@@ -730,16 +796,17 @@ static int attend_run(const void* q, const void* k, const void* v, int dt,
     hipStream_t st = (hipStream_t)stream;
     const float scale2 = scale * LOG2E;
     // the tiled kernel addresses one sample's K / V rows with 32-bit byte offsets
-    const bool fits32 = ((size_t)max_seqlen + ATT_BK) * (size_t)H * (size_t)dh * 2 < ((size_t)1 << 31);
+    const bool fits32 = ((size_t)max_seqlen + 8 * ATT_BK) * (size_t)H * (size_t)dh * 2 < ((size_t)1 << 31);
     const bool mfma = dt == D3TOM_BF16 && (dh == 128 || dh == 64) && fits32;
-    // the weighted MFMA kernels keep a sample's log2 weights in LDS
+    // the weighted MFMA kernels keep a sample's weights in LDS
     if (wgt && mfma && max_seqlen > ATT_WKEYS) return D3TOM_ERR_UNSUPPORTED;
     // short samples and too few 128-query tiles to fill the chip: keys split across the waves (measured
     // crossover with the tiled kernel: ~550 keys at 32 heads)
-    if (mfma && max_seqlen <= ATS_MAX_KEYS && (long)ceil_div(max_seqlen, ATT_BQ) * H * B <= 512) {
+    if (mfma && max_seqlen <= ATS_MAX_KEYS && (long)ceil_div(max_seqlen, 128) * H * B <= 512) {
         const int nqt = ceil_div(max_seqlen, 32);
         const dim3 g((unsigned)(8 * ceil_div(H * B, 8) * nqt));
         const size_t lds = (size_t)4 * 2 * ATS_BK * dh * 2;
+        const int threads = 256;
         static PerDeviceOnce lds_setup_s;
         if (!lds_setup_s.run([] {
                 return raise_dynamic_lds(attend_bf16_short_kernel<128, false>, 4 * 2 * ATS_BK * 128 * 2) &&
@@ -749,24 +816,38 @@ static int attend_run(const void* q, const void* k, const void* v, int dt,
             }))
             return D3TOM_ERR_DEVICE;
 #define D3TOM_ATT(KERNEL)                                                                                            \
-    D3TOM_LAUNCH(ATTEND, st, (KERNEL<<<g, 256, lds, st>>>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, \
+    D3TOM_LAUNCH(ATTEND, st, (KERNEL<<<g, threads, lds, st>>>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, \
                                                            cu_seqlens, H, B, nqt, scale2, (uint16_t*)o, kw)))
         if (dh == 128) { if (wgt) D3TOM_ATT((attend_bf16_short_kernel<128, true>)); else D3TOM_ATT((attend_bf16_short_kernel<128, false>)); }
         else           { if (wgt) D3TOM_ATT((attend_bf16_short_kernel<64, true>));  else D3TOM_ATT((attend_bf16_short_kernel<64, false>)); }
     } else if (mfma) {
-        const int nqt = ceil_div(max_seqlen, ATT_BQ);
+        // Rounds of workgroups over the 256 compute units.  A round of 128-query tiles costs 0.7 of one of 256-query tiles (every
+        // fragment read from LDS feeds one MFMA instead of two; 1024 keys, 32 heads: 23.5 us against 29.1, 1198: 45.5 against 33.3).
+        const long heads = (long)H * B;
+        const long wide = (ceil_div(max_seqlen, 256) * heads + 255) / 256, narrow = (ceil_div(max_seqlen, 128) * heads + 255) / 256;
+        const int nq = 7 * narrow < 10 * wide ? 1 : 2;
+        const int nqt = ceil_div(max_seqlen, nq * 128);
         const dim3 g((unsigned)(8 * ceil_div(H * B, 8) * nqt));
-        const size_t lds = (size_t)ATT_NS * 2 * ATT_BK * dh * 2;
-        static PerDeviceOnce lds_setup;
-        if (!lds_setup.run([] {
-                return raise_dynamic_lds(attend_bf16_kernel<128, false>, ATT_NS * 2 * ATT_BK * 128 * 2) &&
-                       raise_dynamic_lds(attend_bf16_kernel<64, false>, ATT_NS * 2 * ATT_BK * 64 * 2) &&
-                       raise_dynamic_lds(attend_bf16_kernel<128, true>, ATT_NS * 2 * ATT_BK * 128 * 2) &&
-                       raise_dynamic_lds(attend_bf16_kernel<64, true>, ATT_NS * 2 * ATT_BK * 64 * 2);
-            }))
-            return D3TOM_ERR_DEVICE;
-        if (dh == 128) { if (wgt) D3TOM_ATT((attend_bf16_kernel<128, true>)); else D3TOM_ATT((attend_bf16_kernel<128, false>)); }
-        else           { if (wgt) D3TOM_ATT((attend_bf16_kernel<64, true>));  else D3TOM_ATT((attend_bf16_kernel<64, false>)); }
+        const size_t lds = (size_t)ATT_SLOTS * 2 * ATT_BK * dh * 2;
+        const int threads = 512;
+#define D3TOM_ATT8(DHV, WGTV, NQV, ONLINEV)                                                                                 \
+    do {                                                                                                                    \
+        static PerDeviceOnce lds_setup;                                                                                     \
+        if (!lds_setup.run([] { return raise_dynamic_lds(attend_bf16_kernel<DHV, WGTV, NQV, ONLINEV>, ATT_SLOTS * 2 * ATT_BK * DHV * 2); })) \
+            return D3TOM_ERR_DEVICE;                                                                                        \
+        D3TOM_ATT((attend_bf16_kernel<DHV, WGTV, NQV, ONLINEV>));                                                           \
+    } while (0)
+#define D3TOM_ATT8_NQ(DHV, WGTV, ONLINEV) do { if (nq == 1) D3TOM_ATT8(DHV, WGTV, 1, ONLINEV); else D3TOM_ATT8(DHV, WGTV, 2, ONLINEV); } while (0)
+#define D3TOM_ATT8_FORM(DHV)                                                                                                \
+    do {                                                                                                                    \
+        if (wgt) D3TOM_ATT8_NQ(DHV, true, false);                                                                           \
+        else if (online) D3TOM_ATT8_NQ(DHV, false, true);                                                                   \
+        else D3TOM_ATT8_NQ(DHV, false, false);                                                                              \
+    } while (0)
+        if (dh == 128) D3TOM_ATT8_FORM(128); else D3TOM_ATT8_FORM(64);
+#undef D3TOM_ATT8_FORM
+#undef D3TOM_ATT8_NQ
+#undef D3TOM_ATT8
 #undef D3TOM_ATT
     } else {
         const dim3 g(max_seqlen, H, B);
@@ -780,11 +861,19 @@ static int attend_run(const void* q, const void* k, const void* v, int dt,
     return D3TOM_OK;
 }
 
+namespace d3tom {
+// the stack's entry: `online` keeps the running maximum (see the softmax phase)
+int attend_run(const void* q, const void* k, const void* v, int B, const int32_t* cu_seqlens, int max_seqlen, int H, int dh, float scale,
+               bool online, void* o, hipStream_t st) {
+    return attend_any(q, k, v, D3TOM_BF16, B, cu_seqlens, max_seqlen, H, dh, scale, nullptr, nullptr, nullptr, online, o, st);
+}
+}  // namespace d3tom
+
 extern "C" int d3tom_attend(const void* q, const void* k, const void* v, int dt,
                             int B, const int32_t* cu_seqlens, int max_seqlen, int H, int dh, float scale,
                             void* o, void* ws, size_t ws_bytes, void* stream) {
     (void)ws; (void)ws_bytes;
-    return attend_run(q, k, v, dt, B, cu_seqlens, max_seqlen, H, dh, scale, nullptr, nullptr, nullptr, o, stream);
+    return attend_any(q, k, v, dt, B, cu_seqlens, max_seqlen, H, dh, scale, nullptr, nullptr, nullptr, false, o, stream);
 }
 
 extern "C" int d3tom_attend_weighted(const void* q, const void* k, const void* v, int dt,
@@ -793,5 +882,5 @@ extern "C" int d3tom_attend_weighted(const void* q, const void* k, const void* v
                                      void* o, void* ws, size_t ws_bytes, void* stream) {
     (void)ws; (void)ws_bytes;
     if (!counts || !kept_off || !vis_start) return D3TOM_ERR_INVALID_ARG;
-    return attend_run(q, k, v, dt, B, cu_seqlens, max_seqlen, H, dh, scale, counts, kept_off, vis_start, o, stream);
+    return attend_any(q, k, v, dt, B, cu_seqlens, max_seqlen, H, dh, scale, counts, kept_off, vis_start, false, o, stream);
 }

@@ -165,6 +165,32 @@ def test_attend_both_sides_of_the_short_sample_limit(H, dh, longest):
         check_attend(o, q, k, v, "bf16")
 
 
+@pytest.mark.parametrize("rise", [0.0, 9.0])
+@pytest.mark.parametrize("H,dh,weighted,lens", [
+    (3, 128, False, [513, 640, 641, 1, 128, 129]),                  # few heads: 128-query tiles
+    (3, 64, True, [577, 640, 64, 65]),
+    (32, 128, False, [513, 512, 257, 256, 255, 63, 1, 65]),         # enough heads for 256-query tiles
+    (32, 64, True, [512, 513, 257, 64, 192, 193, 33, 128]),
+])
+def test_attend_tile_widths_and_rising_logits(H, dh, weighted, lens, rise):
+    """Both query tile widths of the tiled kernel; with `rise` later keys exceed the first tile's largest logit by far more than
+    2^25, so that the reference of the exponents has to move."""
+    qkv = []
+    for n in lens:
+        q, k, v = W.random_qkv(800 + n, n, H, dh, "bf16")
+        k = W.round_to(k * (1 + rise * np.arange(n, dtype=np.float32) / n)[:, None, None], "bf16")
+        qkv.append((q, k, v))
+    if weighted:
+        vis = [n // 5 for n in lens]
+        counts = [(1 + np.arange(n // 2) % 37).astype(np.int32) for n in lens]
+        outs = gpu_attend_weighted(qkv, counts, vis, "bf16")
+        for (q, k, v), o, vs, c in zip(qkv, outs, vis, counts):
+            check_attend(o, q, k, v, "bf16", key_weight=key_weights(len(q), vs, c))
+    else:
+        for (q, k, v), o in zip(qkv, gpu_attend(qkv, "bf16")):
+            check_attend(o, q, k, v, "bf16")
+
+
 def test_attend_special_cases_bf16():
     q, k, v = W.random_qkv(5, 150, 2, 128, "bf16", spread=2.0)
     v1 = np.broadcast_to(v[:1], v.shape).copy()
