@@ -163,20 +163,11 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     // this head's K / V rows of this sample; a row index >= n is past the end and loads as zeros
     const uint32_t span = (uint32_t)(((size_t)(n - 1) * rs + DH) * 2);
     const __amdgpu_buffer_rsrc_t rk = att_uniform_rsrc(kb_, span), rv = att_uniform_rsrc(vb_, span);
+    const __amdgpu_buffer_rsrc_t rq = att_uniform_rsrc(q + (size_t)tok0 * rs + (size_t)h * DH, span);
     const int row_bytes = (int)(rs * 2);
 
-    const int q0 = qt * BQ + wave * NQ * 16 + r;            // query of column block 0; block 1 is 16 further
+    const int q0 = qt * BQ + wave * NQ * 16;                // this wave's first query
     bf16x8 qf[NQ][KS];
-#pragma unroll
-    for (int qb = 0; qb < NQ; ++qb) {
-        const bool valid = q0 + qb * 16 < n;
-        const uint16_t* qp = q + (size_t)(tok0 + (valid ? q0 + qb * 16 : 0)) * rs + (size_t)h * DH + g * 8;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-            qf[qb][ks] = valid ? *reinterpret_cast<const bf16x8*>(qp + ks * 32) : z;
-        }
-    }
     f32x4 ot[DB][NQ];
 #pragma unroll
     for (int t = 0; t < DB; ++t)
@@ -372,17 +363,28 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     };
 
     const int ntile = (n + ATT_BK - 1) / ATT_BK;
-    // The query fragments must have arrived before the first direct load is issued: otherwise the
-    // compiler's own wait for them would sit inside the loop, where it would also wait for the direct loads.
+    // The queries go through the ring's last two slots, each wave's rows in its own part: whole lines, and in flight together with
+    // the first tiles.  Every wave has read them when stage 2 is started.
+    constexpr int QROWS = NQ * 16, QLD = QROWS / RPI;
+    static_assert(8 * QROWS * ROWB <= 2 * STAGE, "the queries fit into two slots");
+    const int q_lds = 2 * STAGE + wave * QROWS * ROWB;
+    auto row_swizzle = [](int x) { return DH == 128 ? (x & 15) : ((x >> 1) & 7); };
+#pragma unroll
+    for (int i = 0; i < QLD; ++i) {
+        const int x = i * RPI + lane / NCHK;
+        att_direct_load(rq, (q0 + x) * row_bytes + (((lane % NCHK) ^ row_swizzle(x)) << 4), ring0 + q_lds + i * 1024);
+    }
+    issue(0);
+    issue(1);
+    wait_loads<2 * LD>();
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb)
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) asm volatile("" :: "v"(qf[qb][ks]));
-#pragma unroll
-    for (int j = 0; j < AHEAD; ++j) issue(j);
-    wait_loads<(AHEAD - 1) * 2 * LD>();
-    if constexpr (WGT) wait_lds();              // the weights
+        for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const bf16x8*>(ring + q_lds + (k_addr ^ (ks << 6)) + qb * 16 * ROWB);
+    __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0): the queries are there (and the weights written)
     phase_barrier();
+    issue(2);
+    static_assert(AHEAD == 3, "three stages are under way when the loop starts");
 #pragma unroll
     for (int f = 0; f < KPRE; ++f) read_first(ring, f);
     // Stage j + 1 has to have landed when the softmax phase of tile j begins (its first fragments are read there).  Groups that
@@ -416,19 +418,28 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     wait_loads<0>();                            // nothing may be in flight into LDS when the workgroup ends
     if (grp == 0) phase_barrier();
 
+    // O^T lies in the registers as 4 dims of a row per lane; through LDS the rows are stored in whole lines.  Slot ntile % NS may
+    // still be read by group 1 (V of its last tile); the two behind the next one are free.
+    char* ow = ring + ((ntile + 2 + grp) % NS) * STAGE + (wave & 3) * QROWS * ROWB;
+    static_assert(4 * QROWS * ROWB <= STAGE, "a group's rows fit into a slot");
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
-        const int row = q0 + qb * 16;
         const float inv = 1.0f / (ONLINE ? att_quad_sum(l_run[qb]) : lt[qb][0]);
-        if (row >= n) continue;
-        uint16_t* op = o + (size_t)(tok0 + row) * rs + (size_t)h * DH + g * 4;
 #pragma unroll
         for (int t = 0; t < DB; ++t) {
             uint2 w;
             w.x = pack_bf16x2(ot[t][qb][0] * inv, ot[t][qb][1] * inv);
             w.y = pack_bf16x2(ot[t][qb][2] * inv, ot[t][qb][3] * inv);
-            *reinterpret_cast<uint2*>(op + t * 16) = w;
+            *reinterpret_cast<uint2*>(ow + (qb * 16 + r) * ROWB + (((t * 2 + (g >> 1)) ^ row_swizzle(r)) << 4) + (g & 1) * 8) = w;
         }
+    }
+    wait_lds();
+    uint16_t* op = o + (size_t)tok0 * rs + (size_t)h * DH + (lane % NCHK) * 8;
+#pragma unroll
+    for (int i = 0; i < QLD; ++i) {
+        const int x = i * RPI + lane / NCHK;
+        const uint4 w = *reinterpret_cast<const uint4*>(ow + x * ROWB + (((lane % NCHK) ^ row_swizzle(x)) << 4));
+        if (q0 + x < n) *reinterpret_cast<uint4*>(op + (size_t)(q0 + x) * rs) = w;
     }
 #endif
 }
