@@ -6,7 +6,7 @@
 //             kept slots of dot / (|m| |k|) does not depend on |m|, the pruned row's own norm; the same
 //             waves write the ascending list of pruned visual tokens (the gaps of the ascending kept_idx)
 //             and initialise the token -> (best value, slot) table
-//   cosine    pruned x kept similarity GEMM on MFMA 32x32x16 bf16 with the argmax fused into the
+//   cosine    pruned x kept similarity GEMM on MFMA 16x16x32 bf16 with the argmax fused into the
 //             epilogue: only (best value, best slot) per (pruned row, 128-slot column tile) ever
 //             leaves the registers, as ONE 64-bit integer atomic max on the row's table entry (value in
 //             the high word as an order-preserving integer, 2^32-1-slot in the low word: the maximum is
@@ -117,15 +117,21 @@ __global__ __launch_bounds__(256) void merge_norms_kernel(
 // run covers a compact block of about RB x (run / RB) tiles, so its private L2 sees few operand rows.
 // The loads are buffer loads: each lane's byte offset (row and swizzled chunk) is fixed for the whole
 // sweep and the k-slice moves through the scalar offset, so a stage costs no address arithmetic.
+//
+// What bounds it is what one CU takes in: 55 .. 60 bytes per clock when another CU of the XCD has had the rows, 27 when none
+// has; 32 KB a stage at 44 are 745 clocks, the MFMAs of a 128-row tile 512.  The computing waves therefore only have to keep
+// out of the way: fragments one k-step ahead across the stage's barrier, the smaller MFMA shape (less power: 1.6 GHz
+// against 1.5), the kept rows' norms read once in the epilogue (read for every row, 400 clocks each, it took 5 us of 35).
+// Measured at d = 4096: 1822 x 1823 rows 37.9 -> 31.8 us, 2733 x 912 32.4 -> 28.5, 16 samples of 2304 rows 195 -> 167.
 constexpr int cos_ring_stages(int TM) { return TM >= 4 ? 3 : 4; }     // 256-row tiles: 3 stages of 48 KB fit the 160 KB of LDS
-constexpr int COS_NS_MIN = 3;
 
 template <int TM>
 __global__ __launch_bounds__(512) void cos_argmax_bf16(
     const uint16_t* __restrict__ f, int d, const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_start,
     const int32_t* __restrict__ vis_count, const int32_t* __restrict__ kept_idx, const int32_t* __restrict__ kept_off,
     int max_V, int max_keep, const int32_t* __restrict__ pruned, const float* __restrict__ rnorm,
-    table_t* __restrict__ table, int VP, int per, int RB, int ksplit, float* __restrict__ dots, int nrt_launch, int nct_launch, int rn_by_token) {
+    table_t* __restrict__ table, int VP, int per, int RB, int ksplit, float* __restrict__ dots, int nrt_launch, int nct_launch, int rn_by_token,
+    int nB, int NG) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = TM * 64;
     constexpr int COS_NS = cos_ring_stages(TM);
@@ -136,18 +142,21 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     extern __shared__ __attribute__((aligned(16))) char ring[];
     __shared__ float rnB[COS_BN];
 
-    // blockIdx.x = sample * 8 * per + id; id & 7 is the XCD the hardware puts the workgroup on.  The launch is sized
-    // for the largest sample (per = an eighth of its tiles); every sample numbers ITS OWN tiles and cuts that sequence
-    // into 8 equal runs, so that a sample with fewer tiles still loads the 8 XCDs alike (numbered on the launch's
+    // blockIdx.x & 7 is the XCD the hardware puts the workgroup on.  The XCDs form NG groups of 8 / NG; group g has the samples g,
+    // g + NG, ...  The launch is sized
+    // for the largest sample (per = one XCD's share of its tiles); every sample numbers ITS OWN tiles and cuts that sequence
+    // into 8 / NG equal runs, so that a sample with fewer tiles still loads its XCDs alike (numbered on the launch's
     // grid, the tiles of a short sample would all fall to the first XCDs).
-    const int b = blockIdx.x / (8 * per);
-    const int id = blockIdx.x % (8 * per);
+    const int xcd = blockIdx.x & 7, XG = 8 / NG;
+    const int b = (xcd / XG) + NG * (int)((blockIdx.x >> 3) / per);
+    const int id = (blockIdx.x >> 3) % per;
+    if (b >= nB) return;
     const SampleGeom s = sample_geom(b, seq_off, vis_start, vis_count, kept_off, max_V, max_keep);
     const int nrt_b = min((s.M + BM - 1) / BM, nrt_launch), nct_b = min((s.k + COS_BN - 1) / COS_BN, nct_launch);
     const int tiles_b = nrt_b * nct_b;
-    const int per_b = (tiles_b + 7) >> 3;
-    if ((id >> 3) >= per_b) return;
-    const int t_lin = (id & 7) * per_b + (id >> 3);
+    const int per_b = (tiles_b + XG - 1) / XG;
+    if (id >= per_b) return;
+    const int t_lin = (xcd % XG) * per_b + id;
     if (t_lin >= tiles_b) return;
     int rt, ct;
     {
@@ -164,7 +173,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     const int tid = threadIdx.x, wave = (tid >> 6) & 3, lane = tid & 63;
     const bool loader = tid >> 8;                          // waves 4..7 only move data, waves 0..3 only compute
     const int wm = wave >> 1, wn = wave & 1;
-    const int c = lane & 31, g = lane >> 5;
+    const int r16 = lane & 15, g4 = lane >> 4;
     const int32_t* pr = pruned + (size_t)b * max_V;
     const int32_t* kp = kept_idx + kept_off[b];
     const float* rn = rnorm + (size_t)b * max_V;
@@ -218,51 +227,16 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     };
     auto issue = [&](int kt, int stage) { issue_part(kt, stage, 0, LPS); };
 
-    f32x16 acc[TM][2];
+    constexpr int RBK = TM * 2, CBK = 4;                // 16-row and 16-column blocks of a wave's (TM*32) x 64 tile
+    f32x4 acc[RBK][CBK];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < RBK; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+        for (int j = 0; j < CBK; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // byte offsets of this lane's operand fragments inside a stage (k-step kk adds the swizzled chunk)
-    int a_row[TM], b_row[2], a_sw[TM], b_sw[2];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) { const int Rr = wm * (TM * 32) + i * 32 + c; a_row[i] = Rr * 128; a_sw[i] = (Rr >> 1) & 7; }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) { const int Rr = wn * 64 + j * 32 + c; b_row[j] = BM * 128 + Rr * 128; b_sw[j] = (Rr >> 1) & 7; }
-
-    // one stage: feed stage kt to the MFMAs
-    auto stage = [&](int kt) {
-        const char* sb = ring + (kt % COS_NS) * STAGE;
-        // operand fragments are read one k-step ahead of the MFMAs that use them, so the LDS latency
-        // of step kk + 1 is covered by the matrix work of step kk
-        bf16x8 af[2][TM], bfr[2][2];
-        auto read_frags = [&](int kk, int buf) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-                af[buf][i] = *reinterpret_cast<const bf16x8*>(sb + a_row[i] + (((kk * 2 + g) ^ a_sw[i]) << 4));
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                bfr[buf][j] = *reinterpret_cast<const bf16x8*>(sb + b_row[j] + (((kk * 2 + g) ^ b_sw[j]) << 4));
-        };
-        read_frags(0, 0);
-#pragma unroll
-        for (int kk = 0; kk < COS_BK / 16; ++kk) {
-            if (kk + 1 < COS_BK / 16) read_frags(kk + 1, (kk + 1) & 1);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk & 1][i], bfr[kk & 1][j], acc[i][j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
     // A wave that issues a direct load waits for room in the CU's vector-memory queue; in a computing wave
     // that wait stalls the MFMA stream, so the loads have waves of their own.  One s_barrier per stage:
-    // the loaders arrive once stage kt has landed, the consumers once they are done with stage kt-1,
+    // the loaders arrive at the kt-th once stage kt has landed, the consumers once they have read stage kt-1 out of LDS,
     // whose slot the loaders then refill with stage kt+COS_NS-1.
     if (loader) {
 #pragma unroll
@@ -274,59 +248,96 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
             if (kt + COS_NS - 1 < nkt) issue(kt + COS_NS - 1, (kt + COS_NS - 1) % COS_NS);
         }
     } else {
-        for (int kt = 0; kt < nkt; ++kt) {
-            wait_loads_and_barrier<0>();
-            stage(kt);
+        // A stage is two k-steps of 32.  The fragments of the next k-step are read behind the first MFMAs of this one, across
+        // the barrier too (the one for stage kt+1 lies between the two k-steps of stage kt), so that neither LDS latency nor the
+        // barrier leaves the matrix core idle.
+        const int sw = (r16 >> 1) & 7;                  // rows 16 i + r16 all share it
+        const int fa = (wm * (TM * 32) + r16) * 128, fb = BM * 128 + (wn * 64 + r16) * 128;
+        const int ch0 = (g4 ^ sw) << 4, ch1 = ((4 + g4) ^ sw) << 4;
+        bf16x8 fr[2][RBK + CBK];                        // [k-step][row blocks, column blocks]
+        auto read_one = [&](const char* sb, int ks, int f) {
+            fr[ks][f] = *reinterpret_cast<const bf16x8*>(sb + (f < RBK ? fa + f * 2048 : fb + (f - RBK) * 2048) + (ks ? ch1 : ch0));
+        };
+        auto multiply = [&](int ks, const char* next, bool read) {  // MFMAs of k-step ks; reads the other one's fragments from `next`
+#pragma unroll
+            for (int n = 0; n < RBK * CBK; ++n) {
+                const int i = n / CBK, j = n % CBK;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[ks][i], fr[ks][RBK + j], acc[i][j], 0, 0, 0);
+                if (read && n < RBK + CBK) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    read_one(next, ks ^ 1, n);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        wait_loads_and_barrier<0>();
+#pragma unroll
+        for (int f = 0; f < RBK + CBK; ++f) read_one(ring, 0, f);
+        int slot = 0;
+        for (int kt = 0; kt + 1 < nkt; ++kt) {
+            const char* sb = ring + slot * STAGE;
+            slot = slot + 1 == COS_NS ? 0 : slot + 1;
+            multiply(0, sb, true);
+            __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0): stage kt is in registers
+            phase_barrier();
+            multiply(1, ring + slot * STAGE, true);
         }
+        multiply(0, ring + slot * STAGE, true);
+        multiply(1, nullptr, false);
     }
 
     if (ksplit > 1) {
         // partial products of this k-slice: block (slice, tile) of BM x 128 floats, summed by cos_reduce_argmax
         const int tile_id = (b * nrt_launch + rt) * nct_launch + ct;
-        const int n_tiles = (int)(gridDim.x / (8 * per)) * nrt_launch * nct_launch;
+        const int n_tiles = nB * nrt_launch * nct_launch;
         float* blk = dots + ((size_t)blockIdx.y * n_tiles + tile_id) * (BM * COS_BN);
         if (loader) return;
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < RBK; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < CBK; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int row = wm * (TM * 32) + i * 32 + (e >> 2) * 8 + g * 4 + (e & 3);
-                    blk[row * COS_BN + wn * 64 + j * 32 + c] = acc[i][j][e];
-                }
+                for (int e = 0; e < 4; ++e)
+                    blk[(wm * (TM * 32) + i * 16 + g4 * 4 + e) * COS_BN + wn * 64 + j * 16 + r16] = acc[i][j][e];
         return;
     }
     // epilogue: dot * rn_col (the cosine up to the row's own positive norm, which is the same for all of
     // its candidates); per row, best (value, slot) over this tile's columns.
-    // The 64 candidates of a row (32 lanes x 2 wave columns) meet in LDS (the ring is free once all waves
-    // are past the loop): every lane folds its two columns of a row into one candidate (branch-free; equal
-    // values keep the lower slot) and stores it, then two threads per row scan 32 candidates each in
-    // ascending slot order.  Rows are padded to 33 entries so that the scan of 32 different rows hits 32
+    // The 32 candidates of a row (16 lanes x 2 wave columns) meet in LDS (the ring is free once all waves
+    // are past the loop): every lane folds its four columns of a row into one candidate (branch-free; equal
+    // values keep the lower slot) and stores it, then two threads per row scan 16 candidates each in
+    // ascending slot order.  Rows are padded to 17 entries so that the scan of 32 different rows hits 32
     // different banks.
     __syncthreads();                                           // all waves are done with the ring
-    float2* cand = reinterpret_cast<float2*>(ring);            // [BM][2][33]
+    float2* cand = reinterpret_cast<float2*>(ring);            // [BM][2][17]
     if (!loader) {
+        float rn_col[CBK];                                     // read once: the compiler takes the stores below for possible changes
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int j = 0; j < CBK; ++j) rn_col[j] = rnB[wn * 64 + j * 16 + r16];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int row = wm * (TM * 32) + i * 32 + (e >> 2) * 8 + g * 4 + (e & 3);
-                const int col0 = wn * 64 + c, col1 = col0 + 32;
-                const int s0 = ct * COS_BN + col0, s1 = s0 + 32;
-                const float v0 = (s0 < s.k) ? acc[i][0][e] * rnB[col0] : -INFINITY;
-                const float v1 = (s1 < s.k) ? acc[i][1][e] * rnB[col1] : -INFINITY;
-                const bool t1 = v1 > v0;                       // equal values: the lower slot stays
-                cand[(row * 2 + wn) * 33 + c] = make_float2(t1 ? v1 : v0, __int_as_float(t1 ? s1 : s0));
+        for (int i = 0; i < RBK; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int row = wm * (TM * 32) + i * 16 + g4 * 4 + e;
+                float best = -INFINITY; int bidx = 0x7FFFFFFF;
+#pragma unroll
+                for (int j = 0; j < CBK; ++j) {
+                    const int col = wn * 64 + j * 16 + r16, slot = ct * COS_BN + col;
+                    const float v = (slot < s.k) ? acc[i][j][e] * rn_col[j] : -INFINITY;
+                    const bool take = v > best;                // equal values: the lower slot stays
+                    best = take ? v : best; bidx = take ? slot : bidx;
+                }
+                cand[(row * 2 + wn) * 17 + r16] = make_float2(best, __int_as_float(bidx));
             }
     }
     __syncthreads();
     for (int t = tid; t < BM * 2; t += 512) {
         const int row = t >> 1, half = t & 1;                  // half 0: slots of wave column 0 (lower slots)
-        const float2* cr = cand + (row * 2 + half) * 33;
+        const float2* cr = cand + (row * 2 + half) * 17;
         float best = -INFINITY; int bidx = 0x7FFFFFFF;
-#pragma unroll 8
-        for (int q2 = 0; q2 < 32; ++q2) {
+#pragma unroll
+        for (int q2 = 0; q2 < 16; ++q2) {
             const float2 a = cr[q2];
             const int ia = __float_as_int(a.y);
             const bool take = (a.x > best) | ((a.x == best) & (ia < bidx));
@@ -710,26 +721,30 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
         const int BM = TM * 64;
         const int nrt = ceil_div(max_pruned, BM);
         // tiles of a sample in 8 equal runs (one per XCD); bands about as high as a run's block is wide
-        const int per = ceil_div(nrt * nct, 8);
+        // Batches of several rounds: a sample's tiles on two XCDs instead of eight, so that an XCD's L2 serves each operand row to more of
+        // them (16 samples of 2304 rows: 181 us on eight XCDs, 177 on four, 167 on two, 173 on one).  Only where the four pairs
+        // get equal numbers of samples, and enough of them for their sizes to even out.
+        const int NG = (TM == 4 && B >= 12 && B % 4 == 0) ? 4 : 1;
+        const int per = ceil_div(nrt * nct, 8 / NG);
         int RB = 1;
         while ((RB + 1) * (RB + 1) <= per) ++RB;
         if (RB > nrt) RB = nrt;
-        const dim3 g((unsigned)(8 * per * B), (unsigned)ksplit);
+        const dim3 g((unsigned)(8 * per * ceil_div(B, NG)), (unsigned)ksplit);
         float* dots = (float*)(wsb + w.dots_off);
         const size_t lds = (size_t)cos_ring_stages(TM) * (BM + COS_BN) * 128;
         const int by_token = prepared ? 1 : 0;
         if (TM == 4)
             D3TOM_LAUNCH(COS_ARGMAX, st, cos_argmax_bf16<4><<<g, 512, lds, st>>>(
                 (const uint16_t*)sim, d_sim, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep, pruned,
-                rnorm, table, w.VP, per, RB, 1, dots, nrt, nct, by_token));
+                rnorm, table, w.VP, per, RB, 1, dots, nrt, nct, by_token, B, NG));
         else if (TM == 1)
             D3TOM_LAUNCH(COS_ARGMAX, st, cos_argmax_bf16<1><<<g, 512, lds, st>>>(
                 (const uint16_t*)sim, d_sim, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep, pruned,
-                rnorm, table, w.VP, per, RB, ksplit, dots, nrt, nct, by_token));
+                rnorm, table, w.VP, per, RB, ksplit, dots, nrt, nct, by_token, B, NG));
         else
             D3TOM_LAUNCH(COS_ARGMAX, st, cos_argmax_bf16<2><<<g, 512, lds, st>>>(
                 (const uint16_t*)sim, d_sim, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep, pruned,
-                rnorm, table, w.VP, per, RB, 1, dots, nrt, nct, by_token));
+                rnorm, table, w.VP, per, RB, 1, dots, nrt, nct, by_token, B, NG));
         if (ksplit > 1) {
             const dim3 gr(ceil_div(max_pruned, 4), B);
             D3TOM_LAUNCH(COS_REDUCE, st, cos_reduce_argmax<<<gr, 256, 0, st>>>(
