@@ -11,38 +11,42 @@
 //   sweep 2 (scores)  per (head, visual key): sum over deciders of exp2(logit - logsumexp), one row
 //                     per head; a small third kernel adds the H rows in head order (no atomics)
 //
-// bf16 path: logits on MFMA 16x16x32 (rows = 16 deciders, cols = 16 keys, contraction = dh), both
-// operands read straight from HBM/L2 in the MFMA operand layout (each lane reads dh/4 contiguous
-// elements of its row; the contraction index is permuted identically for both operands, which a
-// dot product does not see).  Everything is bandwidth bound: K is streamed twice, the second time
+// bf16 path: logits on MFMA 16x16x32 (rows = 16 deciders, cols = 16 keys, contraction = dh), the keys
+// read straight from HBM/L2 in the MFMA operand layout, the decider rows through LDS.  K is streamed twice, the second time
 // usually from the memory-side cache; with many deciders (64 and up) the exp2 / max arithmetic per logit
 // becomes a comparable share of the run time.
 //
 // The generic path (any float type / head size) is a kernel pair in plain float arithmetic.
 #include <mutex>
 #include "internal.hpp"
+#include "direct_load.hpp"
 
 namespace d3tom {
 
-// keys per workgroup (4 waves x SUB sub-tiles x 16): every workgroup re-fetches the decider rows of its
-// head, so few large chunks (one workgroup per CU at 3.7k tokens x 32 heads) beat many small ones; when
-// 512-key chunks would leave CUs idle (short sequences) the first sweep takes 256-key chunks instead
-// (8.5 instead of 11.5 us at 1152 tokens)
-constexpr int IMP_KC_STATS = 512;
-constexpr int IMP_KC_SCORES = 512, IMP_SUB_SCORES = IMP_KC_SCORES / (4 * 16);
+// Keys per workgroup: 4 waves x SUB sub-tiles x 16.  Every workgroup fetches the decider rows of its head, so few large chunks (one
+// workgroup per CU at 3.7k tokens x 32 heads) beat many small ones; when 512-key chunks would leave CUs idle (short sequences)
+// the first sweep takes 256-key chunks instead (8.5 instead of 11.5 us at 1152 tokens).  With several rounds of workgroups and
+// more deciders than keep their logits, 384-key chunks fit three workgroups on a CU instead of two: one computes while another's
+// keys arrive (16 samples of 2688 tokens, 132 deciders on average: 150 -> 122 us; all at once, loads and arithmetic added
+// up).  The second sweep has no statistics to amortise: 384 keys there too, 256 otherwise (256 x 64 deciders x 32 heads: 11.3 -> 9.8 us).
+constexpr int IMP_KC_STATS = 512, IMP_KC_MANY = 384;
+constexpr long IMP_MANY = 1024;        // 512-key chunks from which on a launch counts as several rounds
 
 constexpr int IMP_KEEP_MAXD_WS = 32;   // largest decider set whose logits are kept (workspace is sized for it)
 struct ImpWs {
     size_t part_off, sp_off, cnt_off, c_off, logit_off, total;
-    int KC, NCH, NCHV, DPAD, VPAD, NKB;
+    int KC, KCS, NCH, NCHV, DPAD, VPAD, NKB;
 };
 __host__ inline ImpWs imp_ws_layout(int B, int max_N, int max_V, int H, int max_D) {
     ImpWs w;
-    w.KC = ((long)ceil_div(max_N, IMP_KC_STATS) * H * B < 256) ? IMP_KC_STATS / 2 : IMP_KC_STATS;     // keys per chunk of the first sweep
+    const long chunks = (long)ceil_div(max_N, IMP_KC_STATS) * H * B;
+    const bool many = chunks >= IMP_MANY && max_D > IMP_KEEP_MAXD_WS;
+    w.KC = many ? IMP_KC_MANY : chunks < 256 ? IMP_KC_STATS / 2 : IMP_KC_STATS;       // keys per chunk of the first sweep
+    w.KCS = many ? IMP_KC_MANY : 256;                                                 // ... of the second
     w.NCH = ceil_div(max_N, w.KC);
-    w.NCHV = ceil_div(max_V, IMP_KC_SCORES);
+    w.NCHV = ceil_div(max_V, w.KCS);
     w.DPAD = ceil_div(max_D, 16) * 16;
-    w.VPAD = w.NCHV * IMP_KC_SCORES;
+    w.VPAD = w.NCHV * w.KCS;
     size_t o = 0;
     w.part_off = o; o += align_up((size_t)B * H * w.NCH * w.DPAD * sizeof(float2), 256);
     w.sp_off = o;   o += align_up((size_t)B * H * w.VPAD * sizeof(float), 256);
@@ -63,24 +67,91 @@ size_t importance_ws_bytes(int B, int max_N, int max_V, int H, int dh, int max_D
     return a > b ? a : b;
 }
 
-// Load one MFMA operand row fragment: lane (r = lane % 16, g = lane / 16) takes elements
+// MFMA operand fragments of SUB x 16 key rows of one head, straight from memory: lane (r = lane % 16, g = lane / 16) takes elements
 // [kk*32 + g*8, +8) of its row for k-step kk, so the four lanes of a row fetch 64 contiguous bytes per
-// load instruction.
-template <int DH>
-__device__ __forceinline__ void load_frag(const uint16_t* row, int g, bool valid, bf16x8 (&f)[DH / 32]) {
-    const bf16x8* p = reinterpret_cast<const bf16x8*>(row + g * 8);
+// load instruction.  `first` = the workgroup's first row, of which `rows` exist; others (and rows past the end) read as zeros.
+template <int DH, int SUB>
+__device__ __forceinline__ void load_keys(const uint16_t* first, int rows, int H, int row0, int r, int g, bf16x8 (&f)[SUB][DH / 32]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const int row_bytes = H * DH * 2;
+    const __amdgpu_buffer_rsrc_t rsrc = make_uniform_rsrc(first, (uint32_t)(rows - 1) * row_bytes + DH * 2);
+    const int voff = (row0 + r) * row_bytes + g * 16;
 #pragma unroll
-    for (int kk = 0; kk < DH / 32; ++kk) {
-        bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-        f[kk] = valid ? p[kk * 4] : z;
+    for (int s = 0; s < SUB; ++s)
+#pragma unroll
+        for (int kk = 0; kk < DH / 32; ++kk)
+            f[s][kk] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff + kk * 64, s * 16 * row_bytes, 0));
+#endif
+}
+
+// The decider rows of one head, [16 * nblk rows][DH] with 16-byte chunks swizzled by the row, go to LDS once per workgroup, by
+// direct loads that run beside those of the keys; rows past the sample's deciders repeat the last one.  (Fetched by every wave
+// for itself, 64 rows at a time, they cost a trip to memory per 64 rows in each of them.)  At most IMP_QROWS of them at a time, so
+// that LDS leaves room for as many workgroups as the registers do.  Positions first, keys behind them, rows last: `positions` and
+// `rows` are called around the key loads.
+constexpr int IMP_QROWS = 128, IMP_QBLK = IMP_QROWS / 16;
+template <int DH>
+struct ImpQueries {
+    static constexpr int ROWB = DH * 2, NCHK = DH / 8, RPI = 64 / NCHK, MAXL = IMP_QROWS / RPI / 4;
+    int pos[MAXL];
+    __device__ __forceinline__ static int swizzle(int x) { return DH == 128 ? (x & 15) : ((x >> 1) & 7); }
+    // rows i0 .. i0 + 16 * nblk - 1
+    __device__ __forceinline__ void positions(const int32_t* dec, int i0, int D, int N, int nblk) {
+        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+        for (int u = 0; u < MAXL; ++u) {
+            const int l = wave + 4 * u;
+            pos[u] = (l * RPI < nblk * 16) ? min(max(dec[min(i0 + l * RPI + lane / NCHK, D - 1)], 0), N - 1) : 0;
+        }
+    }
+    __device__ __forceinline__ void rows(const uint16_t* q, int tok0, int H, int h, int nblk, char* lds) const {
+#if defined(__HIP_DEVICE_COMPILE__)
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+#pragma unroll
+        for (int u = 0; u < MAXL; ++u) {
+            const int l = wave + 4 * u;
+            if (l * RPI < nblk * 16) {
+                const int x = l * RPI + lane / NCHK;
+                const uint16_t* p = q + ((size_t)(tok0 + pos[u]) * H + h) * DH + (((lane % NCHK) ^ swizzle(x)) << 3);
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p,
+                                                 (lds_ptr_t)(lds + l * 1024), 16, 0, 0);
+            }
+        }
+#endif
+    }
+    // operand fragments of decider rows blk * 16 + r
+    __device__ __forceinline__ static void fragments(const char* lds, int blk, int r, int g, bf16x8 (&f)[DH / 32]) {
+        const char* p = lds + (blk * 16 + r) * ROWB;
+#pragma unroll
+        for (int kk = 0; kk < DH / 32; ++kk) f[kk] = *reinterpret_cast<const bf16x8*>(p + (((kk * 4 + g) ^ swizzle(r)) << 4));
+    }
+};
+// block(blk, fragments) for every 16-decider block; AHEAD: the next one's fragments are read before it (where registers allow)
+template <int DH, bool AHEAD, typename F>
+__device__ __forceinline__ void imp_for_blocks(const char* lds, int nblk, int r, int g, F&& block) {
+    bf16x8 f0[DH / 32], f1[DH / 32];
+    if constexpr (!AHEAD) {
+#pragma unroll 1
+        for (int blk = 0; blk < nblk; ++blk) {
+            ImpQueries<DH>::fragments(lds, blk, r, g, f0);
+            block(blk, f0);
+        }
+    } else {
+        ImpQueries<DH>::fragments(lds, 0, r, g, f0);
+#pragma unroll 1
+        for (int blk = 0; blk < nblk; blk += 2) {
+            ImpQueries<DH>::fragments(lds, min(blk + 1, nblk - 1), r, g, f1);
+            block(blk, f0);
+            if (blk + 1 >= nblk) break;
+            ImpQueries<DH>::fragments(lds, min(blk + 2, nblk - 1), r, g, f0);
+            block(blk + 1, f1);
+        }
     }
 }
 
-constexpr int IMP_NB = 4;       // 16-decider blocks whose query fragments are fetched together
-
 // (running max, running sum of exp2) of decider rows over one chunk of IMP_SUB_STATS x 64 keys of one head
 template <int DH, bool KEEP, int IMP_SUB_STATS>
-__global__ __launch_bounds__(256) void imp_stats_bf16(
+__global__ __launch_bounds__(256, IMP_SUB_STATS == 6 ? 3 : 2) void imp_stats_bf16(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int H, float scale2,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ dec_idx, const int32_t* __restrict__ dec_off,
     int max_D, int DPAD, int NCH, float2* __restrict__ part, int NKB, float* __restrict__ logits) {
@@ -96,90 +167,89 @@ __global__ __launch_bounds__(256) void imp_stats_bf16(
     if (key_base >= N || D <= 0) return;
 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-    __shared__ float2 wstat[4][D3TOM_MAX_DECIDERS];
-
-    // decider positions of the first group are requested before the key fragments, so that the
-    // position -> query-row chain runs beside the key loads instead of behind them
-    int pos0[IMP_NB];
-#pragma unroll
-    for (int nb = 0; nb < IMP_NB; ++nb) pos0[nb] = (nb * 16 + r < D) ? dec[nb * 16 + r] : 0;
-
-    bf16x8 kf[IMP_SUB_STATS][KS];
-    bool kvalid[IMP_SUB_STATS];
-#pragma unroll
-    for (int s = 0; s < IMP_SUB_STATS; ++s) {
-        const int key = key_base + (wave * IMP_SUB_STATS + s) * 16 + r;
-        kvalid[s] = key < N;
-        const uint16_t* row = k + ((size_t)(tok0 + (kvalid[s] ? key : 0)) * H + h) * DH;
-        load_frag<DH>(row, g, kvalid[s], kf[s]);
-    }
     const int nblk = (D + 15) >> 4;
-    for (int db0 = 0; db0 < nblk; db0 += IMP_NB) {
-        bf16x8 qf[IMP_NB][KS];
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    char* qs = smem;                                                    // the decider rows
+    float2* wstat = reinterpret_cast<float2*>(smem + min(DPAD, IMP_QROWS) * DH * 2);   // [4][IMP_QROWS]
+
+    ImpQueries<DH> queries;
+    queries.positions(dec, 0, D, N, min(nblk, IMP_QBLK));
+    bf16x8 kf[IMP_SUB_STATS][KS];
+    const int wave_key = key_base + wave * IMP_SUB_STATS * 16;
+    load_keys<DH, IMP_SUB_STATS>(k + ((size_t)(tok0 + key_base) * H + h) * DH, min(N - key_base, KC), H, wave * IMP_SUB_STATS * 16, r, g, kf);
+    queries.rows(q, tok0, H, h, min(nblk, IMP_QBLK), qs);
+    const bool ragged = wave_key + IMP_SUB_STATS * 16 > N;              // uniform: some of the wave's keys lie past the end
+    for (int b0 = 0; b0 < nblk; b0 += IMP_QBLK) {
+    const int nb = min(nblk - b0, IMP_QBLK);
+    if (b0 > 0) queries.rows(q, tok0, H, h, nb, qs);
+    __syncthreads();
+    if (b0 + IMP_QBLK < nblk) queries.positions(dec, (b0 + IMP_QBLK) * 16, D, N, min(nblk - b0 - IMP_QBLK, IMP_QBLK));
+    imp_for_blocks<DH, true>(qs, nb, r, g, [&](int blk, const bf16x8 (&qf)[KS]) {
+        // acc[s][e]: scaled logit of decider row (b0+blk)*16 + 4g + e and key column r of sub-tile s
+        f32x4 acc[IMP_SUB_STATS];
 #pragma unroll
-        for (int nb = 0; nb < IMP_NB; ++nb) {
-            const int i = (db0 + nb) * 16 + r;
-            const bool qv = i < D;
-            const int pos = min(max(db0 == 0 ? pos0[nb] : (qv ? dec[i] : 0), 0), N - 1);
-            load_frag<DH>(q + ((size_t)(tok0 + pos) * H + h) * DH, g, qv, qf[nb]);
-        }
-#pragma unroll
-        for (int nb = 0; nb < IMP_NB; ++nb) {
-            if (db0 + nb >= nblk) break;
-            // l2[s][e]: scaled logit of decider row (db0+nb)*16 + 4g + e and key column r of sub-tile s
-            f32x4 l2[IMP_SUB_STATS];
+        for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
             for (int s = 0; s < IMP_SUB_STATS; ++s) {
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kk = 0; kk < KS; ++kk)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[nb][kk], kf[s][kk], acc, 0, 0, 0);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) l2[s][e] = kvalid[s] ? acc[e] * scale2 : -INFINITY;
-                if constexpr (KEEP) {
-                    // [key block][head][decider][key in block]: the 16 lanes of a decider row write 64 contiguous bytes
-                    const int kb = (key_base >> 4) + wave * IMP_SUB_STATS + s;
-                    const int row0 = (db0 + nb) * 16 + 4 * g;
-                    float* lp = logits + (((size_t)(b * NKB + kb) * H + h) * max_D + row0) * 16 + r;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (row0 + e < D) lp[e * 16] = l2[s][e];
-                }
+                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[kk], kf[s][kk], kk ? acc[s] : zero, 0, 0, 0);
             }
-            // max over this wave's 64 keys first (in-lane, then the 16 key columns), then one exp2 per logit
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float mx = l2[0][e];
+        for (int s = 0; s < IMP_SUB_STATS; ++s) acc[s] *= scale2;
+        if (ragged) {
 #pragma unroll
-                for (int s = 1; s < IMP_SUB_STATS; ++s) mx = fmaxf(mx, l2[s][e]);
-                mx = row16_max(mx);
-                float zz = 0.f;
-                if (mx != -INFINITY) {
+            for (int s = 0; s < IMP_SUB_STATS; ++s)
+                if (wave_key + s * 16 + r >= N) acc[s] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        }
+        if constexpr (KEEP) {
+            // [key block][head][decider][key in block]: the 16 lanes of a decider row write 64 contiguous bytes
 #pragma unroll
-                    for (int s = 0; s < IMP_SUB_STATS; ++s) zz += __builtin_amdgcn_exp2f(l2[s][e] - mx);
-                }
-                zz = row16_sum(zz);
-                if (r == 0) wstat[wave][(db0 + nb) * 16 + 4 * g + e] = make_float2(mx, zz);
+            for (int s = 0; s < IMP_SUB_STATS; ++s) {
+                const int kb = (key_base >> 4) + wave * IMP_SUB_STATS + s;
+                const int row0 = (b0 + blk) * 16 + 4 * g;
+                float* lp = logits + (((size_t)(b * NKB + kb) * H + h) * max_D + row0) * 16 + r;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (row0 + e < D) lp[e * 16] = acc[s][e];
             }
         }
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < nblk * 16; t += 256) {
-        float2 a = wstat[0][t];
+        // max over this wave's keys first (in-lane, then the 16 key columns), then one exp2 per logit
+        float mx[4], zz[4];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) lse2_combine_fast(a.x, a.y, wstat[w][t].x, wstat[w][t].y);
-        part[((size_t)(b * H + h) * NCH + chunk) * DPAD + t] = a;
+        for (int e = 0; e < 4; ++e) {
+            float m = acc[0][e];
+#pragma unroll
+            for (int s = 1; s < IMP_SUB_STATS; ++s) m = fmaxf(m, acc[s][e]);
+            mx[e] = row16_max(m);
+            const float ref = (mx[e] == -INFINITY) ? 0.f : mx[e];       // no key at all: the sum stays 0
+            zz[e] = 0.f;
+#pragma unroll
+            for (int s = 0; s < IMP_SUB_STATS; ++s) zz[e] += __builtin_amdgcn_exp2f(acc[s][e] - ref);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            zz[e] = row16_sum(zz[e]);
+            if (r == 0) wstat[wave * IMP_QROWS + blk * 16 + 4 * g + e] = make_float2(mx[e], zz[e]);
+        }
+    });
+    __syncthreads();
+    for (int t = threadIdx.x; t < nb * 16; t += 256) {
+        float2 a = wstat[t];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) lse2_combine_fast(a.x, a.y, wstat[w * IMP_QROWS + t].x, wstat[w * IMP_QROWS + t].y);
+        part[((size_t)(b * H + h) * NCH + chunk) * DPAD + b0 * 16 + t] = a;
+    }
     }
 }
 
 // per-head score rows: sp[h][j] = sum over deciders of exp2(logit - log2sumexp2)
-template <int DH>
-__global__ __launch_bounds__(256) void imp_scores_bf16(
+template <int DH, int IMP_SUB_SCORES>
+__global__ __launch_bounds__(256, IMP_SUB_SCORES == 4 ? 4 : 3) void imp_scores_bf16(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int H, float scale2,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ dec_idx, const int32_t* __restrict__ dec_off,
     const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count,
     int max_D, int max_V, int DPAD, int NCH, int KC, int VPAD, const float2* __restrict__ part, float* __restrict__ sp) {
-    constexpr int KS = DH / 32;
+    constexpr int KS = DH / 32, KCS = IMP_SUB_SCORES * 64;
     // heads vary fastest over the grid: workgroups that run together read neighbouring 2*DH-byte pieces of the same key rows
     const int h = blockIdx.x, chunk = blockIdx.y, b = blockIdx.z;
     const int tok0 = seq_off[b];
@@ -188,70 +258,61 @@ __global__ __launch_bounds__(256) void imp_scores_bf16(
     const int32_t* dec = dec_idx + dec_off[b];
     const int vs = min(max(vis_start[b], 0), N);
     const int V = min(min(vis_count[b], max_V), N - vs);
-    const int key_base = chunk * IMP_KC_SCORES;
+    const int key_base = chunk * KCS;
     if (key_base >= V || D <= 0) return;
 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-    __shared__ float c_lds[D3TOM_MAX_DECIDERS];
+    const int nblk = (D + 15) >> 4;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    char* qs = smem;                                                    // the decider rows
+    float* c_lds = reinterpret_cast<float*>(smem + min(DPAD, IMP_QROWS) * DH * 2);     // [DPAD] log2-sum-exp2
 
-    int pos0[IMP_NB];
-#pragma unroll
-    for (int nb = 0; nb < IMP_NB; ++nb) pos0[nb] = (nb * 16 + r < D) ? dec[nb * 16 + r] : 0;
+    ImpQueries<DH> queries;
+    queries.positions(dec, 0, D, N, min(nblk, IMP_QBLK));
     // log2-sum-exp2 of every decider row of this head, key chunks combined in ascending order
     const int nch = (N + KC - 1) / KC;
-    for (int t = threadIdx.x; t < D; t += 256) {
+    for (int t = threadIdx.x; t < nblk * 16; t += 256) {
         const float2* p = part + ((size_t)(b * H + h) * NCH) * DPAD + t;
         float m = -INFINITY, z = 0.f;
-        for (int c0 = 0; c0 < nch; c0 += 16) {             // 16 independent loads in flight, combined in order
-            float2 a[16];
+        for (int c0 = 0; c0 < nch; c0 += 8) {              // 8 independent loads in flight, combined in order
+            float2 a[8];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) a[u] = (c0 + u < nch) ? p[(size_t)(c0 + u) * DPAD] : make_float2(-INFINITY, 0.f);
+            for (int u = 0; u < 8; ++u) a[u] = (c0 + u < nch) ? p[(size_t)(c0 + u) * DPAD] : make_float2(-INFINITY, 0.f);
 #pragma unroll
-            for (int u = 0; u < 16; ++u) lse2_combine_fast(m, z, a[u].x, a[u].y);
+            for (int u = 0; u < 8; ++u) lse2_combine_fast(m, z, a[u].x, a[u].y);
         }
-        c_lds[t] = m + __builtin_amdgcn_logf(z);
+        c_lds[t] = t < D ? m + __builtin_amdgcn_logf(z) : INFINITY;     // padded rows contribute exp2(-inf) = 0
     }
     bf16x8 kf[IMP_SUB_SCORES][KS];
     float acc_s[IMP_SUB_SCORES];
+    load_keys<DH, IMP_SUB_SCORES>(k + ((size_t)(tok0 + vs + key_base) * H + h) * DH, min(V - key_base, KCS), H,
+                                  wave * IMP_SUB_SCORES * 16, r, g, kf);
 #pragma unroll
-    for (int s = 0; s < IMP_SUB_SCORES; ++s) {
-        const int j = key_base + (wave * IMP_SUB_SCORES + s) * 16 + r;
-        const bool kv = j < V;
-        const uint16_t* row = k + ((size_t)(tok0 + vs + (kv ? j : 0)) * H + h) * DH;
-        load_frag<DH>(row, g, kv, kf[s]);
-        acc_s[s] = 0.f;
+    for (int s = 0; s < IMP_SUB_SCORES; ++s) acc_s[s] = 0.f;
+    queries.rows(q, tok0, H, h, min(nblk, IMP_QBLK), qs);
+    for (int b0 = 0; b0 < nblk; b0 += IMP_QBLK) {
+    const int nb = min(nblk - b0, IMP_QBLK);
+    if (b0 > 0) {
+        __syncthreads();
+        queries.rows(q, tok0, H, h, nb, qs);
     }
     __syncthreads();
-
-    const int nblk = (D + 15) >> 4;
-    for (int db0 = 0; db0 < nblk; db0 += IMP_NB) {
-        bf16x8 qf[IMP_NB][KS];
+    if (b0 + IMP_QBLK < nblk) queries.positions(dec, (b0 + IMP_QBLK) * 16, D, N, min(nblk - b0 - IMP_QBLK, IMP_QBLK));
+    imp_for_blocks<DH, false>(qs, nb, r, g, [&](int blk, const bf16x8 (&qf)[KS]) {
+        const f32x4 cc = *reinterpret_cast<const f32x4*>(c_lds + (b0 + blk) * 16 + 4 * g);
+        f32x4 acc[IMP_SUB_SCORES];
 #pragma unroll
-        for (int nb = 0; nb < IMP_NB; ++nb) {
-            const int i = (db0 + nb) * 16 + r;
-            const bool qv = i < D;
-            const int pos = min(max(db0 == 0 ? pos0[nb] : (qv ? dec[i] : 0), 0), N - 1);
-            load_frag<DH>(q + ((size_t)(tok0 + pos) * H + h) * DH, g, qv, qf[nb]);
-        }
-#pragma unroll
-        for (int nb = 0; nb < IMP_NB; ++nb) {
-            if (db0 + nb >= nblk) break;
-            float cc[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int row = (db0 + nb) * 16 + 4 * g + e;
-                cc[e] = (row < D) ? c_lds[row] : INFINITY;       // padded rows contribute exp2(-inf) = 0
-            }
+        for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
             for (int s = 0; s < IMP_SUB_SCORES; ++s) {
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kk = 0; kk < KS; ++kk)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[nb][kk], kf[s][kk], acc, 0, 0, 0);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc_s[s] += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[e], scale2, -cc[e]));
+                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[kk], kf[s][kk], kk ? acc[s] : zero, 0, 0, 0);
             }
-        }
+#pragma unroll
+        for (int s = 0; s < IMP_SUB_SCORES; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc_s[s] += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[s][e], scale2, -cc[e]));
+    });
     }
     float* sp_row = sp + (size_t)(b * H + h) * VPAD;
 #pragma unroll
@@ -484,16 +545,19 @@ int d3tom::importance_run(const void* q, const void* k, int dt,
         // small decider sets: the first sweep keeps its logits and the scores come from them (K fetched once)
         const bool keep = max_D <= IMP_KEEP_MAXD;
         float* logits = (float*)(wsb + w.logit_off);
+        // the decider rows and each wave's statistics (or the log-sum-exps)
+        const int qrows = w.DPAD < IMP_QROWS ? w.DPAD : IMP_QROWS;
+        const size_t lds1 = (size_t)qrows * dh * 2 + 4 * IMP_QROWS * sizeof(float2), lds2 = (size_t)qrows * dh * 2 + w.DPAD * sizeof(float);
 #define D3TOM_IMP_STATS(DHV, KEEPV, SUBV)                                                                     \
-    D3TOM_LAUNCH(IMP_STATS, st, (imp_stats_bf16<DHV, KEEPV, SUBV><<<g1, 256, 0, st>>>(                           \
+    D3TOM_LAUNCH(IMP_STATS, st, (imp_stats_bf16<DHV, KEEPV, SUBV><<<g1, 256, lds1, st>>>(                        \
         qq, kk, H, scale2, seq_off, dec_idx, dec_off, max_D, w.DPAD, w.NCH, part, w.NKB, logits)))
-        const bool big = w.KC == IMP_KC_STATS;
+        const bool big = w.KC == IMP_KC_STATS, mid = w.KC == IMP_KC_MANY;
         if (dh == 128) {
             if (keep) { if (big) D3TOM_IMP_STATS(128, true, 8); else D3TOM_IMP_STATS(128, true, 4); }
-            else      { if (big) D3TOM_IMP_STATS(128, false, 8); else D3TOM_IMP_STATS(128, false, 4); }
+            else      { if (big) D3TOM_IMP_STATS(128, false, 8); else if (mid) D3TOM_IMP_STATS(128, false, 6); else D3TOM_IMP_STATS(128, false, 4); }
         } else {
             if (keep) { if (big) D3TOM_IMP_STATS(64, true, 8); else D3TOM_IMP_STATS(64, true, 4); }
-            else      { if (big) D3TOM_IMP_STATS(64, false, 8); else D3TOM_IMP_STATS(64, false, 4); }
+            else      { if (big) D3TOM_IMP_STATS(64, false, 8); else if (mid) D3TOM_IMP_STATS(64, false, 6); else D3TOM_IMP_STATS(64, false, 4); }
         }
 #undef D3TOM_IMP_STATS
         if (keep) {
@@ -503,14 +567,12 @@ int d3tom::importance_run(const void* q, const void* k, int dt,
                 scores));
             return D3TOM_OK;
         }
-        if (dh == 128)
-            D3TOM_LAUNCH(IMP_SCORES, st, imp_scores_bf16<128><<<g2, 256, 0, st>>>(
-                qq, kk, H, scale2, seq_off, dec_idx, dec_off, vis_start, vis_count, max_D, max_V, w.DPAD, w.NCH, w.KC, w.VPAD,
-                part, sp));
-        else
-            D3TOM_LAUNCH(IMP_SCORES, st, imp_scores_bf16<64><<<g2, 256, 0, st>>>(
-                qq, kk, H, scale2, seq_off, dec_idx, dec_off, vis_start, vis_count, max_D, max_V, w.DPAD, w.NCH, w.KC, w.VPAD,
-                part, sp));
+#define D3TOM_IMP_SCORES(DHV, SUBV)                                                                           \
+    D3TOM_LAUNCH(IMP_SCORES, st, (imp_scores_bf16<DHV, SUBV><<<g2, 256, lds2, st>>>(                              \
+        qq, kk, H, scale2, seq_off, dec_idx, dec_off, vis_start, vis_count, max_D, max_V, w.DPAD, w.NCH, w.KC, w.VPAD, part, sp)))
+        if (dh == 128) { if (w.KCS == 256) D3TOM_IMP_SCORES(128, 4); else D3TOM_IMP_SCORES(128, 6); }
+        else           { if (w.KCS == 256) D3TOM_IMP_SCORES(64, 4);  else D3TOM_IMP_SCORES(64, 6); }
+#undef D3TOM_IMP_SCORES
         D3TOM_LAUNCH(IMP_FINISH, st, imp_finish_kernel<<<g3, 256, 0, st>>>(
             sp, H, w.VPAD, seq_off, vis_start, vis_count, score_off, max_V, scores));
         return D3TOM_OK;

@@ -101,6 +101,23 @@ def test_merge_large_batch_tiles(batch):
     _chain(samples, keeps, "bf16", check=[0, 1, 2, 5, batch - 1])
 
 
+@pytest.mark.parametrize("dh,copies", [(64, 8), (128, 8), (64, 1), (128, 1)])
+def test_importance_decider_groups_and_chunks(dh, copies):
+    """Decider counts around the 128 rows staged at a time and around 16-row blocks, key counts around the key chunks of both
+    sweeps; `copies` of the batch make enough workgroups for the smaller chunks of large launches."""
+    shapes = [(383, 127, 33), (384, 256, 128), (385, 257, 129), (520, 255, 256), (170, 1, 144)]      # tokens, visual, deciders
+    samples = [W.random_case(600 + i, N, 8 * dh, 8, 3, V, D, dtype="bf16") for i, (N, V, D) in enumerate(shapes)]
+    for s, (_, _, D) in zip(samples, shapes):
+        s["dec_idx"] = np.resize(s["dec_idx"], D).astype(np.int32)         # (repeats where there are fewer positions)
+        s["D"] = D
+    batch = samples * copies * (16 if copies > 1 else 1)
+    S = GpuStep(batch, [max(1, s["V"] // 4) for s in batch], "bf16").importance()
+    for i, s in enumerate(samples):
+        ref = oracle.importance(s["q"], s["k"], s["dec_idx"], s["vis_start"], s["V"])
+        check_scores(S[i], ref)
+        np.testing.assert_array_equal(S[i], S[len(batch) - len(samples) + i])
+
+
 # ---- top-k in isolation: exact, ties, extremes ---------------------------------------------------------
 def _topk_only(scores_list, ks):
     V = [len(s) for s in scores_list]
