@@ -22,7 +22,7 @@
 
 namespace d3tom {
 
-constexpr int COS_BN = 128;        // kept slots per column tile
+constexpr int COS_BN = 128;        // kept slots per column tile (96 where that fills the chip better)
 constexpr int COS_BK = 64;         // contraction elements per LDS stage
 
 // split-K partial products: at most COS_SPLIT_BLOCKS (tile, k-slice) blocks of 64 x 128 floats
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256) void merge_norms_kernel(
 // Measured at d = 4096: 1822 x 1823 rows 37.9 -> 31.8 us, 2733 x 912 32.4 -> 28.5, 16 samples of 2304 rows 195 -> 167.
 constexpr int cos_ring_stages(int TM) { return TM >= 4 ? 3 : 4; }     // 256-row tiles: 3 stages of 48 KB fit the 160 KB of LDS
 
-template <int TM>
+template <int TM, int CBK>     // CBK: 16-column blocks of a wave
 __global__ __launch_bounds__(512) void cos_argmax_bf16(
     const uint16_t* __restrict__ f, int d, const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_start,
     const int32_t* __restrict__ vis_count, const int32_t* __restrict__ kept_idx, const int32_t* __restrict__ kept_off,
@@ -133,14 +133,14 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     table_t* __restrict__ table, int VP, int per, int RB, int ksplit, float* __restrict__ dots, int nrt_launch, int nct_launch, int rn_by_token,
     int nB, int NG) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    constexpr int BM = TM * 64;
+    constexpr int BM = TM * 64, BN = CBK * 32;
     constexpr int COS_NS = cos_ring_stages(TM);
-    constexpr int STAGE = (BM + COS_BN) * 128;          // bytes per ring stage (64 bf16 = 128 B per row)
+    constexpr int STAGE = (BM + BN) * 128;          // bytes per ring stage (64 bf16 = 128 B per row)
     constexpr int A_LD = BM / 32;                       // direct loads per wave and stage, A tile (8 rows each)
-    constexpr int B_LD = COS_BN / 32;
+    constexpr int B_LD = BN / 32;
     constexpr int LPS = A_LD + B_LD;                    // loads per wave and stage
     extern __shared__ __attribute__((aligned(16))) char ring[];
-    __shared__ float rnB[COS_BN];
+    __shared__ float rnB[BN];
 
     // blockIdx.x & 7 is the XCD the hardware puts the workgroup on.  The XCDs form NG groups of 8 / NG; group g has the samples g,
     // g + NG, ...  The launch is sized
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     const int id = (blockIdx.x >> 3) % per;
     if (b >= nB) return;
     const SampleGeom s = sample_geom(b, seq_off, vis_start, vis_count, kept_off, max_V, max_keep);
-    const int nrt_b = min((s.M + BM - 1) / BM, nrt_launch), nct_b = min((s.k + COS_BN - 1) / COS_BN, nct_launch);
+    const int nrt_b = min((s.M + BM - 1) / BM, nrt_launch), nct_b = min((s.k + BN - 1) / BN, nct_launch);
     const int tiles_b = nrt_b * nct_b;
     const int per_b = (tiles_b + XG - 1) / XG;
     if (id >= per_b) return;
@@ -193,14 +193,14 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     }
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
-        const int row = wave * (COS_BN / 4) + i * 8 + (lane >> 3);
+        const int row = wave * (BN / 4) + i * 8 + (lane >> 3);
         const int cg = (lane & 7) ^ ((row >> 1) & 7);
-        const int r = ct * COS_BN + row;
+        const int r = ct * BN + row;
         const int j = min(max(kp[(r < s.k) ? r : 0], 0), s.V - 1);
         b_off[i] = j * d * 2 + cg * 16;
     }
-    for (int t = tid; t < COS_BN; t += 512) {
-        const int r = ct * COS_BN + t;
+    for (int t = tid; t < BN; t += 512) {
+        const int r = ct * BN + t;
         // 1 / norm of the kept row in slot r: stored by slot, or by token when the selection launch computed them
         rnB[t] = (r < s.k) ? rn[rn_by_token ? min(max(kp[r], 0), s.V - 1) : r] : 0.f;
     }
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     // that a load costs one scalar add for its M0 value and no vector instruction
     const uint32_t ring0 = (uint32_t)(size_t)(lds_ptr_t)ring;
     const uint32_t a_lds = __builtin_amdgcn_readfirstlane(ring0 + wave * (BM / 4) * 128);
-    const uint32_t b_lds = __builtin_amdgcn_readfirstlane(ring0 + BM * 128 + wave * (COS_BN / 4) * 128);
+    const uint32_t b_lds = __builtin_amdgcn_readfirstlane(ring0 + BM * 128 + wave * (BN / 4) * 128);
     // loads [n0, n1) of a stage's LPS loads (A tile first, then B tile)
     auto issue_part = [&](int kt, int stage, int n0, int n1) {
 #pragma unroll
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     };
     auto issue = [&](int kt, int stage) { issue_part(kt, stage, 0, LPS); };
 
-    constexpr int RBK = TM * 2, CBK = 4;                // 16-row and 16-column blocks of a wave's (TM*32) x 64 tile
+    constexpr int RBK = TM * 2;                         // 16-row blocks of a wave's (TM*32) x (CBK*16) tile
     f32x4 acc[RBK][CBK];
 #pragma unroll
     for (int i = 0; i < RBK; ++i)
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         // the barrier too (the one for stage kt+1 lies between the two k-steps of stage kt), so that neither LDS latency nor the
         // barrier leaves the matrix core idle.
         const int sw = (r16 >> 1) & 7;                  // rows 16 i + r16 all share it
-        const int fa = (wm * (TM * 32) + r16) * 128, fb = BM * 128 + (wn * 64 + r16) * 128;
+        const int fa = (wm * (TM * 32) + r16) * 128, fb = BM * 128 + (wn * (BN / 2) + r16) * 128;
         const int ch0 = (g4 ^ sw) << 4, ch1 = ((4 + g4) ^ sw) << 4;
         bf16x8 fr[2][RBK + CBK];                        // [k-step][row blocks, column blocks]
         auto read_one = [&](const char* sb, int ks, int f) {
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         // partial products of this k-slice: block (slice, tile) of BM x 128 floats, summed by cos_reduce_argmax
         const int tile_id = (b * nrt_launch + rt) * nct_launch + ct;
         const int n_tiles = nB * nrt_launch * nct_launch;
-        float* blk = dots + ((size_t)blockIdx.y * n_tiles + tile_id) * (BM * COS_BN);
+        float* blk = dots + ((size_t)blockIdx.y * n_tiles + tile_id) * (BM * BN);
         if (loader) return;
 #pragma unroll
         for (int i = 0; i < RBK; ++i)
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
             for (int j = 0; j < CBK; ++j)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    blk[(wm * (TM * 32) + i * 16 + g4 * 4 + e) * COS_BN + wn * 64 + j * 16 + r16] = acc[i][j][e];
+                    blk[(wm * (TM * 32) + i * 16 + g4 * 4 + e) * BN + wn * (BN / 2) + j * 16 + r16] = acc[i][j][e];
         return;
     }
     // epilogue: dot * rn_col (the cosine up to the row's own positive norm, which is the same for all of
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     if (!loader) {
         float rn_col[CBK];                                     // read once: the compiler takes the stores below for possible changes
 #pragma unroll
-        for (int j = 0; j < CBK; ++j) rn_col[j] = rnB[wn * 64 + j * 16 + r16];
+        for (int j = 0; j < CBK; ++j) rn_col[j] = rnB[wn * (BN / 2) + j * 16 + r16];
 #pragma unroll
         for (int i = 0; i < RBK; ++i)
 #pragma unroll
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
                 float best = -INFINITY; int bidx = 0x7FFFFFFF;
 #pragma unroll
                 for (int j = 0; j < CBK; ++j) {
-                    const int col = wn * 64 + j * 16 + r16, slot = ct * COS_BN + col;
+                    const int col = wn * (BN / 2) + j * 16 + r16, slot = ct * BN + col;
                     const float v = (slot < s.k) ? acc[i][j][e] * rn_col[j] : -INFINITY;
                     const bool take = v > best;                // equal values: the lower slot stays
                     best = take ? v : best; bidx = take ? slot : bidx;
@@ -682,9 +682,11 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
 
     static PerDeviceOnce lds_setup;
     if (!lds_setup.run([] {
-            return raise_dynamic_lds(cos_argmax_bf16<1>, cos_ring_stages(1) * (64 + COS_BN) * 128) &&
-                   raise_dynamic_lds(cos_argmax_bf16<2>, cos_ring_stages(2) * (128 + COS_BN) * 128) &&
-                   raise_dynamic_lds(cos_argmax_bf16<4>, cos_ring_stages(4) * (256 + COS_BN) * 128);
+            return raise_dynamic_lds(cos_argmax_bf16<1, 4>, cos_ring_stages(1) * (64 + 128) * 128) &&
+                   raise_dynamic_lds(cos_argmax_bf16<1, 3>, cos_ring_stages(1) * (64 + 96) * 128) &&
+                   raise_dynamic_lds(cos_argmax_bf16<2, 4>, cos_ring_stages(2) * (128 + 128) * 128) &&
+                   raise_dynamic_lds(cos_argmax_bf16<2, 3>, cos_ring_stages(2) * (128 + 96) * 128) &&
+                   raise_dynamic_lds(cos_argmax_bf16<4, 4>, cos_ring_stages(4) * (256 + 128) * 128);
         }))
         return D3TOM_ERR_DEVICE;
 
@@ -703,7 +705,7 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
 
     const bool mfma = (dt == D3TOM_BF16) && (d_sim % COS_BK == 0) && ((size_t)max_V * d_sim * 2 < ((size_t)1 << 31));
     if (mfma && max_pruned > 0) {
-        const int nct = ceil_div(max_keep, COS_BN);
+        int nct = ceil_div(max_keep, COS_BN);
         // as long as the 64-row tiles still fit one round of the 256 CUs they finish sooner than half as many
         // 128-row tiles (a 64-row tile's k-loop is ~0.7 of a 128-row tile's)
         // with several rounds of 128-row tiles (large batches) 256-row tiles move a third less operand data per flop
@@ -720,6 +722,11 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
         }
         const int BM = TM * 64;
         const int nrt = ceil_div(max_pruned, BM);
+        // one round of workgroups with CUs to spare: tiles of 96 slots, if they still fit one round, spread the loads over more CUs
+        // (3280 x 365 rows: 156 tiles of 24 KB a stage or 208 of 20 KB, 22.6 -> 20.1 us; 2733 x 912: 28.5 -> 26.4)
+        const int nct96 = ceil_div(max_keep, 96);
+        const bool narrow = ksplit == 1 && TM < 4 && (long)nrt * nct96 * B <= 256;
+        if (narrow) nct = nct96;
         // tiles of a sample in 8 equal runs (one per XCD); bands about as high as a run's block is wide
         // Batches of several rounds: a sample's tiles on two XCDs instead of eight, so that an XCD's L2 serves each operand row to more of
         // them (16 samples of 2304 rows: 181 us on eight XCDs, 177 on four, 167 on two, 173 on one).  Only where the four pairs
@@ -731,20 +738,16 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
         if (RB > nrt) RB = nrt;
         const dim3 g((unsigned)(8 * per * ceil_div(B, NG)), (unsigned)ksplit);
         float* dots = (float*)(wsb + w.dots_off);
-        const size_t lds = (size_t)cos_ring_stages(TM) * (BM + COS_BN) * 128;
+        const size_t lds = (size_t)cos_ring_stages(TM) * (BM + (narrow ? 96 : COS_BN)) * 128;
         const int by_token = prepared ? 1 : 0;
-        if (TM == 4)
-            D3TOM_LAUNCH(COS_ARGMAX, st, cos_argmax_bf16<4><<<g, 512, lds, st>>>(
-                (const uint16_t*)sim, d_sim, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep, pruned,
-                rnorm, table, w.VP, per, RB, 1, dots, nrt, nct, by_token, B, NG));
-        else if (TM == 1)
-            D3TOM_LAUNCH(COS_ARGMAX, st, cos_argmax_bf16<1><<<g, 512, lds, st>>>(
-                (const uint16_t*)sim, d_sim, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep, pruned,
-                rnorm, table, w.VP, per, RB, ksplit, dots, nrt, nct, by_token, B, NG));
-        else
-            D3TOM_LAUNCH(COS_ARGMAX, st, cos_argmax_bf16<2><<<g, 512, lds, st>>>(
-                (const uint16_t*)sim, d_sim, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep, pruned,
-                rnorm, table, w.VP, per, RB, 1, dots, nrt, nct, by_token, B, NG));
+#define D3TOM_COS(TMV, CBKV)                                                                                            \
+    D3TOM_LAUNCH(COS_ARGMAX, st, (cos_argmax_bf16<TMV, CBKV><<<g, 512, lds, st>>>(                                      \
+        (const uint16_t*)sim, d_sim, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep, pruned, rnorm, table, \
+        w.VP, per, RB, ksplit, dots, nrt, nct, by_token, B, NG)))
+        if (TM == 4) D3TOM_COS(4, 4);
+        else if (TM == 2) { if (narrow) D3TOM_COS(2, 3); else D3TOM_COS(2, 4); }
+        else              { if (narrow) D3TOM_COS(1, 3); else D3TOM_COS(1, 4); }
+#undef D3TOM_COS
         if (ksplit > 1) {
             const dim3 gr(ceil_div(max_pruned, 4), B);
             D3TOM_LAUNCH(COS_REDUCE, st, cos_reduce_argmax<<<gr, 256, 0, st>>>(

@@ -118,6 +118,13 @@ def test_importance_decider_groups_and_chunks(dh, copies):
         np.testing.assert_array_equal(S[i], S[len(batch) - len(samples) + i])
 
 
+@pytest.mark.parametrize("V,k", [(2100, 97), (2200, 96), (2300, 193), (3000, 900), (2801, 768)])
+def test_merge_column_tiles_of_96(V, k):
+    """Single samples whose cosine tiles fill one round with 96 kept slots per tile: k around multiples of 96 and 128."""
+    c = W.random_case(500 + k, 5 + V + 6, 256, 2, 5, V, 3, dtype="bf16", centres=max(3, k // 3))
+    _chain([c], [k], "bf16")
+
+
 # ---- top-k in isolation: exact, ties, extremes ---------------------------------------------------------
 def _topk_only(scores_list, ks):
     V = [len(s) for s in scores_list]
