@@ -28,7 +28,7 @@ constexpr int COS_BK = 64;         // contraction elements per LDS stage
 // split-K partial products: at most COS_SPLIT_BLOCKS (tile, k-slice) blocks of 64 x 128 floats
 constexpr int COS_SPLIT_BLOCKS = 256;
 struct MergeWs {
-    size_t pruned_off, rnorm_off, table_off, dots_off, total;
+    size_t pruned_off, rnorm_off, table_off, dots_off, sq_off, total;
     int VP;                    // table entries per sample
 };
 __host__ inline MergeWs merge_ws_layout(int B, int max_V) {
@@ -39,6 +39,7 @@ __host__ inline MergeWs merge_ws_layout(int B, int max_V) {
     w.rnorm_off = o;  o += align_up((size_t)B * max_V * 4, 256);
     w.table_off = o;  o += align_up((size_t)B * w.VP * 8, 256);     // token -> (best value, slot) table
     w.dots_off = o;   o += (size_t)COS_SPLIT_BLOCKS * 64 * 128 * sizeof(float);
+    w.sq_off = o;     o += (size_t)COS_SPLIT_BLOCKS * 128 * sizeof(float);           // sums of squares per (k-slice, kept slot)
     w.total = o;
     return w;
 }
@@ -125,13 +126,17 @@ __global__ __launch_bounds__(256) void merge_norms_kernel(
 // Measured at d = 4096: 1822 x 1823 rows 37.9 -> 31.8 us, 2733 x 912 32.4 -> 28.5, 16 samples of 2304 rows 195 -> 167.
 constexpr int cos_ring_stages(int TM) { return TM >= 4 ? 3 : 4; }     // 256-row tiles: 3 stages of 48 KB fit the 160 KB of LDS
 
-template <int TM, int CBK>     // CBK: 16-column blocks of a wave
+// BARE (split contraction, no preparing launch): the kernel derives the pruned tokens from the kept list itself, writes the pruned
+// list and the kept tokens' table entries for the kernels behind it, and its workgroups of row tile 0 sum the squares of their
+// kept rows (the diagonal of B B^T, two MFMAs per block of 16 rows and stage where the load path leaves the matrix core idle):
+// no norms launch (4 of the 21 us that a merge of 356 tokens takes).
+template <int TM, int CBK, bool BARE>     // CBK: 16-column blocks of a wave
 __global__ __launch_bounds__(512) void cos_argmax_bf16(
     const uint16_t* __restrict__ f, int d, const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_start,
     const int32_t* __restrict__ vis_count, const int32_t* __restrict__ kept_idx, const int32_t* __restrict__ kept_off,
-    int max_V, int max_keep, const int32_t* __restrict__ pruned, const float* __restrict__ rnorm,
+    int max_V, int max_keep, int32_t* __restrict__ pruned, const float* __restrict__ rnorm,
     table_t* __restrict__ table, int VP, int per, int RB, int ksplit, float* __restrict__ dots, int nrt_launch, int nct_launch, int rn_by_token,
-    int nB, int NG) {
+    int nB, int NG, float* __restrict__ sq) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = TM * 64, BN = CBK * 32;
     constexpr int COS_NS = cos_ring_stages(TM);
@@ -154,6 +159,12 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     const SampleGeom s = sample_geom(b, seq_off, vis_start, vis_count, kept_off, max_V, max_keep);
     const int nrt_b = min((s.M + BM - 1) / BM, nrt_launch), nct_b = min((s.k + BN - 1) / BN, nct_launch);
     const int tiles_b = nrt_b * nct_b;
+    if constexpr (BARE) {
+        // a sample that keeps everything has no tiles: its table entries are written here
+        if (s.M <= 0 && id == 0 && xcd % XG == 0 && blockIdx.y == 0)
+            for (int r = threadIdx.x; r < s.k; r += 512)
+                table[(size_t)b * VP + min(max(kept_idx[kept_off[b] + r], 0), s.V - 1)] = table_entry_kept(r);
+    }
     const int per_b = (tiles_b + XG - 1) / XG;
     if (id >= per_b) return;
     const int t_lin = (xcd % XG) * per_b + id;
@@ -174,7 +185,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     const bool loader = tid >> 8;                          // waves 4..7 only move data, waves 0..3 only compute
     const int wm = wave >> 1, wn = wave & 1;
     const int r16 = lane & 15, g4 = lane >> 4;
-    const int32_t* pr = pruned + (size_t)b * max_V;
+    int32_t* pr = pruned + (size_t)b * max_V;
     const int32_t* kp = kept_idx + kept_off[b];
     const float* rn = rnorm + (size_t)b * max_V;
     const size_t base = (size_t)(s.tok0 + s.vs) * d;
@@ -183,6 +194,28 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     // re-read row 0; masked later); the k-slice is added through the scalar offset
     const __amdgpu_buffer_rsrc_t rsrc = make_uniform_rsrc(f + base, (uint32_t)((size_t)s.V * d * sizeof(uint16_t)));
     int a_off[A_LD], b_off[B_LD];
+    if constexpr (BARE) {
+        // the p-th pruned token is p + the number r of kept tokens in front of it: the first r with kept[r] - r > p
+        int* kl = reinterpret_cast<int*>(ring);
+        for (int t = tid; t < s.k; t += 512) kl[t] = min(max(kp[t], 0), s.V - 1);
+        __syncthreads();
+        if (loader) {
+#pragma unroll
+            for (int i = 0; i < A_LD; ++i) {
+                const int row = wave * (BM / 4) + i * 8 + (lane >> 3);
+                const int p = min(rt * BM + row, s.M - 1);
+                int lo = 0, hi = s.k;
+                while (lo < hi) { const int mid = (lo + hi) >> 1; if (kl[mid] - mid > p) hi = mid; else lo = mid + 1; }
+                const int m = min(p + lo, s.V - 1);
+                a_off[i] = m * d * 2 + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+                if (ct == 0 && blockIdx.y == 0 && (lane & 7) == 0 && rt * BM + row < s.M) pr[p] = m;
+            }
+        } else if (rt == 0 && blockIdx.y == 0) {
+            for (int t = tid; t < BN; t += 256)
+                if (ct * BN + t < s.k) table[(size_t)b * VP + kl[ct * BN + t]] = table_entry_kept(ct * BN + t);
+        }
+        __syncthreads();                                   // the ring is free for the tiles
+    } else {
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) {
         const int row = wave * (BM / 4) + i * 8 + (lane >> 3);
@@ -190,6 +223,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         const int p = rt * BM + row;
         const int m = min(max((p < s.M) ? pr[p] : pr[0], 0), s.V - 1);
         a_off[i] = m * d * 2 + cg * 16;
+    }
     }
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
@@ -199,6 +233,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         const int j = min(max(kp[(r < s.k) ? r : 0], 0), s.V - 1);
         b_off[i] = j * d * 2 + cg * 16;
     }
+    if constexpr (!BARE)
     for (int t = tid; t < BN; t += 512) {
         const int r = ct * BN + t;
         // 1 / norm of the kept row in slot r: stored by slot, or by token when the selection launch computed them
@@ -233,6 +268,10 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     for (int i = 0; i < RBK; ++i)
 #pragma unroll
         for (int j = 0; j < CBK; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 bb[BARE ? CBK : 1];                           // BARE: B B^T of each column block
+#pragma unroll
+    for (int j = 0; j < (BARE ? CBK : 1); ++j) bb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const bool squares = BARE && rt == 0 && wm == 0;    // uniform
 
     // A wave that issues a direct load waits for room in the CU's vector-memory queue; in a computing wave
     // that wait stalls the MFMA stream, so the loads have waves of their own.  One s_barrier per stage:
@@ -269,6 +308,10 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
+            if (squares) {
+#pragma unroll
+                for (int j = 0; j < (BARE ? CBK : 0); ++j) bb[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[ks][RBK + j], fr[ks][RBK + j], bb[j], 0, 0, 0);
+            }
             __builtin_amdgcn_sched_barrier(0);
         };
         wait_loads_and_barrier<0>();
@@ -293,6 +336,14 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         const int n_tiles = nB * nrt_launch * nct_launch;
         float* blk = dots + ((size_t)blockIdx.y * n_tiles + tile_id) * (BM * BN);
         if (loader) return;
+        if (squares && (r16 >> 2) == g4) {
+            float* sb = sq + (((size_t)blockIdx.y * nB + b) * nct_launch + ct) * 128 + wn * (BN / 2) + r16;
+#pragma unroll
+            for (int j = 0; j < (BARE ? CBK : 0); ++j) {
+                const f32x4 v = bb[j];
+                sb[j * 16] = (r16 & 2) ? ((r16 & 1) ? v[3] : v[2]) : ((r16 & 1) ? v[1] : v[0]);
+            }
+        }
 #pragma unroll
         for (int i = 0; i < RBK; ++i)
 #pragma unroll
@@ -361,18 +412,34 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
 // then cut along the contraction instead, and one wave per pruned row finishes the job here.  Slices
 // are added in ascending order and slots are visited in ascending order, so the result is deterministic
 // and ties go to the lowest slot.  The wave writes the row's table entry itself.
+template <bool BARE>     // BARE: the norms come from the k-slices' sums of squares
 __global__ __launch_bounds__(256) void cos_reduce_argmax(
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count,
     const int32_t* __restrict__ kept_off,
     int max_V, int max_keep, const int32_t* __restrict__ pruned, const float* __restrict__ rnorm,
     const float* __restrict__ dots, int ksplit, int n_tiles, int nrt_launch, int nct_launch,
-    table_t* __restrict__ table, int VP, const int32_t* __restrict__ kept_idx /* != nullptr: rnorm is indexed by token */) {
+    table_t* __restrict__ table, int VP, const int32_t* __restrict__ kept_idx /* != nullptr: rnorm is indexed by token */,
+    const float* __restrict__ sq, int nB) {
     constexpr int BM = 64;
+    extern __shared__ float rn_s[];             // BARE: [kept slots] 1 / norm
     const int b = blockIdx.y;
     const SampleGeom s = sample_geom(b, seq_off, vis_start, vis_count, kept_off, max_V, max_keep);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int p = blockIdx.x * 4 + wave;
-    if (s.k <= 0 || p >= s.M) return;
+    if (s.k <= 0 || (int)blockIdx.x * 4 >= s.M) return;
+    if constexpr (BARE) {
+        for (int t = threadIdx.x; t < s.k; t += 256) {
+            float part[16], ss = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < 16; ++ks)
+                part[ks] = (ks < ksplit) ? sq[(((size_t)ks * nB + b) * nct_launch + t / COS_BN) * 128 + t % COS_BN] : 0.f;
+#pragma unroll
+            for (int ks = 0; ks < 16; ++ks) ss += part[ks];
+            rn_s[t] = reciprocal_norm(ss);
+        }
+        __syncthreads();
+    }
+    if (p >= s.M) return;
     const float* rn = rnorm + (size_t)b * max_V;
     const int rt = p / BM, lr = p % BM;
     const int nct = (s.k + COS_BN - 1) / COS_BN;
@@ -396,7 +463,8 @@ __global__ __launch_bounds__(256) void cos_reduce_argmax(
                 float sum = 0.f;
 #pragma unroll
                 for (int ks = 0; ks < 16; ++ks) sum += v[half][ks];        // ascending slices; absent ones add 0
-                const float val = sum * rn[kept_idx ? min(max(kept_idx[kept_off[b] + slot], 0), s.V - 1) : slot];
+                const float rnv = BARE ? rn_s[slot] : rn[kept_idx ? min(max(kept_idx[kept_off[b] + slot], 0), s.V - 1) : slot];
+                const float val = sum * rnv;
                 if (val > best) { best = val; bidx = slot; }
             }
         }
@@ -682,18 +750,39 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
 
     static PerDeviceOnce lds_setup;
     if (!lds_setup.run([] {
-            return raise_dynamic_lds(cos_argmax_bf16<1, 4>, cos_ring_stages(1) * (64 + 128) * 128) &&
-                   raise_dynamic_lds(cos_argmax_bf16<1, 3>, cos_ring_stages(1) * (64 + 96) * 128) &&
-                   raise_dynamic_lds(cos_argmax_bf16<2, 4>, cos_ring_stages(2) * (128 + 128) * 128) &&
-                   raise_dynamic_lds(cos_argmax_bf16<2, 3>, cos_ring_stages(2) * (128 + 96) * 128) &&
-                   raise_dynamic_lds(cos_argmax_bf16<4, 4>, cos_ring_stages(4) * (256 + 128) * 128);
+            return raise_dynamic_lds(cos_argmax_bf16<1, 4, true>, cos_ring_stages(1) * (64 + 128) * 128) &&
+                   raise_dynamic_lds(cos_argmax_bf16<1, 4, false>, cos_ring_stages(1) * (64 + 128) * 128) &&
+                   raise_dynamic_lds(cos_argmax_bf16<1, 3, false>, cos_ring_stages(1) * (64 + 96) * 128) &&
+                   raise_dynamic_lds(cos_argmax_bf16<2, 4, false>, cos_ring_stages(2) * (128 + 128) * 128) &&
+                   raise_dynamic_lds(cos_argmax_bf16<2, 3, false>, cos_ring_stages(2) * (128 + 96) * 128) &&
+                   raise_dynamic_lds(cos_argmax_bf16<4, 4, false>, cos_ring_stages(4) * (256 + 128) * 128);
         }))
         return D3TOM_ERR_DEVICE;
 
+    const bool mfma = (dt == D3TOM_BF16) && (d_sim % COS_BK == 0) && ((size_t)max_V * d_sim * 2 < ((size_t)1 << 31));
+    int TM = 1, ksplit = 1;
+    if (mfma && max_pruned > 0) {
+        const int nct = ceil_div(max_keep, COS_BN);
+        // as long as the 64-row tiles still fit one round of the 256 CUs they finish sooner than half as many
+        // 128-row tiles (a 64-row tile's k-loop is ~0.7 of a 128-row tile's)
+        // with several rounds of 128-row tiles (large batches) 256-row tiles move a third less operand data per flop
+        TM = ((long)nct * ceil_div(max_pruned, 128) * B > 768) ? 4 : ((long)nct * ceil_div(max_pruned, 64) * B > 256) ? 2 : 1;
+        // too few 64 x 128 tiles for 256 CUs (short sequences): cut the contraction into k-slices as well
+        if (TM == 1) {
+            const long tiles = (long)ceil_div(max_pruned, 64) * nct * B;
+            const int stages = d_sim / COS_BK;
+            if (tiles <= COS_SPLIT_BLOCKS / 2) {
+                ksplit = 16;
+                while (ksplit > 1 && (tiles * ksplit > COS_SPLIT_BLOCKS || stages % ksplit || stages / ksplit < cos_ring_stages(1))) ksplit >>= 1;
+            }
+        }
+    }
+    // a split contraction computes the norms and the list itself
+    const bool bare = ksplit > 1 && !prepared;
     // prepared: the selection launch has left 1 / norm of every visual row (by token), the pruned list and the
     // initial table in the workspace
     const dim3 gn(ceil_div(max_keep, 4), B);
-    if (prepared) {
+    if (prepared || bare) {
     } else if (dt == D3TOM_BF16)
         D3TOM_LAUNCH(MERGE_NORMS, st, merge_norms_kernel<uint16_t><<<gn, 256, 0, st>>>(
             (const uint16_t*)sim, d_sim, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep, rnorm, pruned,
@@ -703,23 +792,8 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
             (const float*)sim, d_sim, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep, rnorm, pruned,
             table, w.VP));
 
-    const bool mfma = (dt == D3TOM_BF16) && (d_sim % COS_BK == 0) && ((size_t)max_V * d_sim * 2 < ((size_t)1 << 31));
     if (mfma && max_pruned > 0) {
         int nct = ceil_div(max_keep, COS_BN);
-        // as long as the 64-row tiles still fit one round of the 256 CUs they finish sooner than half as many
-        // 128-row tiles (a 64-row tile's k-loop is ~0.7 of a 128-row tile's)
-        // with several rounds of 128-row tiles (large batches) 256-row tiles move a third less operand data per flop
-        const int TM = ((long)nct * ceil_div(max_pruned, 128) * B > 768) ? 4 : ((long)nct * ceil_div(max_pruned, 64) * B > 256) ? 2 : 1;
-        // too few 64 x 128 tiles for 256 CUs (short sequences): cut the contraction into k-slices as well
-        int ksplit = 1;
-        if (TM == 1) {
-            const long tiles = (long)ceil_div(max_pruned, 64) * nct * B;
-            const int stages = d_sim / COS_BK;
-            if (tiles <= COS_SPLIT_BLOCKS / 2) {
-                ksplit = 16;
-                while (ksplit > 1 && (tiles * ksplit > COS_SPLIT_BLOCKS || stages % ksplit || stages / ksplit < cos_ring_stages(1))) ksplit >>= 1;
-            }
-        }
         const int BM = TM * 64;
         const int nrt = ceil_div(max_pruned, BM);
         // one round of workgroups with CUs to spare: tiles of 96 slots, if they still fit one round, spread the loads over more CUs
@@ -738,21 +812,26 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
         if (RB > nrt) RB = nrt;
         const dim3 g((unsigned)(8 * per * ceil_div(B, NG)), (unsigned)ksplit);
         float* dots = (float*)(wsb + w.dots_off);
+        float* sq = (float*)(wsb + w.sq_off);
         const size_t lds = (size_t)cos_ring_stages(TM) * (BM + (narrow ? 96 : COS_BN)) * 128;
         const int by_token = prepared ? 1 : 0;
-#define D3TOM_COS(TMV, CBKV)                                                                                            \
-    D3TOM_LAUNCH(COS_ARGMAX, st, (cos_argmax_bf16<TMV, CBKV><<<g, 512, lds, st>>>(                                      \
+#define D3TOM_COS(TMV, CBKV, BAREV)                                                                                         \
+    D3TOM_LAUNCH(COS_ARGMAX, st, (cos_argmax_bf16<TMV, CBKV, BAREV><<<g, 512, lds, st>>>(                                      \
         (const uint16_t*)sim, d_sim, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep, pruned, rnorm, table, \
-        w.VP, per, RB, ksplit, dots, nrt, nct, by_token, B, NG)))
-        if (TM == 4) D3TOM_COS(4, 4);
-        else if (TM == 2) { if (narrow) D3TOM_COS(2, 3); else D3TOM_COS(2, 4); }
-        else              { if (narrow) D3TOM_COS(1, 3); else D3TOM_COS(1, 4); }
+        w.VP, per, RB, ksplit, dots, nrt, nct, by_token, B, NG, sq)))
+        if (TM == 4) D3TOM_COS(4, 4, false);
+        else if (TM == 2) { if (narrow) D3TOM_COS(2, 3, false); else D3TOM_COS(2, 4, false); }
+        else if (bare) D3TOM_COS(1, 4, true);
+        else { if (narrow) D3TOM_COS(1, 3, false); else D3TOM_COS(1, 4, false); }
 #undef D3TOM_COS
         if (ksplit > 1) {
             const dim3 gr(ceil_div(max_pruned, 4), B);
-            D3TOM_LAUNCH(COS_REDUCE, st, cos_reduce_argmax<<<gr, 256, 0, st>>>(
-                seq_off, vis_start, vis_count, kept_off, max_V, max_keep, pruned, rnorm, dots, ksplit,
-                nrt * nct * B, nrt, nct, table, w.VP, prepared ? kept_idx : nullptr));
+#define D3TOM_REDUCE(BAREV, LDS)                                                                                        \
+    D3TOM_LAUNCH(COS_REDUCE, st, cos_reduce_argmax<BAREV><<<gr, 256, LDS, st>>>(                                        \
+        seq_off, vis_start, vis_count, kept_off, max_V, max_keep, pruned, rnorm, dots, ksplit, nrt * nct * B, nrt, nct, \
+        table, w.VP, prepared ? kept_idx : nullptr, sq, B))
+            if (bare) D3TOM_REDUCE(true, (size_t)max_keep * sizeof(float)); else D3TOM_REDUCE(false, 0);
+#undef D3TOM_REDUCE
         }
     } else if (max_pruned > 0) {
         const dim3 g(max_pruned, B);
