@@ -12,6 +12,7 @@ SOURCES = ["api.hip", "importance.hip", "topk.hip", "merge.hip", "attend.hip", "
            "stack.hip", "pipeline.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 VALU forms
+         "-mllvm", "-amdgpu-kernarg-preload-count=16",                  # first arguments arrive in registers: one load less in front of every kernel
          "-Wall", "-Wno-unused-function"]
 
 
