@@ -332,8 +332,11 @@ __global__ __launch_bounds__(256, IMP_SUB_SCORES == 4 ? 4 : 3) void imp_scores_b
 // third launch, K fetched once).
 // Bound by the chain metadata -> statistics -> exponentials -> reduction, so it has 16 waves: every thread holds one or two
 // (head, decider) rows of the statistics and at most 16 logits at 32 heads x 32 deciders, all requested at once.
+// GENERIC: the logits of the generic first sweep, whose `part` is one finished log-sum-exp per (head, decider) (144 keys x
+// 4 heads x 16 deciders of 64 float32 channels: 7.5 us when every score's dot products were formed again, 4.3 from the logits).
 constexpr int IMP_KEEP_MAXD = IMP_KEEP_MAXD_WS;
 constexpr int IMP_FL_THREADS = 1024, IMP_FL_GROUPS = IMP_FL_THREADS / 16, IMP_FL_ROWS = 16;
+template <bool GENERIC>
 __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     int H, const int32_t* __restrict__ seq_off, const int32_t* __restrict__ dec_off,
     const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count, const int32_t* __restrict__ score_off,
@@ -364,7 +367,9 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     for (int t = threadIdx.x; t < rows; t += IMP_FL_THREADS) {
         const int h = t / max_D, i = t - h * max_D;
         float c = INFINITY;
-        if (i < D) {
+        if (GENERIC) {
+            if (i < D) c = reinterpret_cast<const float*>(part)[(size_t)b * rows + t];
+        } else if (i < D) {
             const float2* p = part + ((size_t)(b * H + h) * NCH) * DPAD + i;
             float m = -INFINITY, z = 0.f;
             for (int c0 = 0; c0 < nch; c0 += 8) {           // 8 independent loads in flight, combined in chunk order
@@ -384,7 +389,7 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     auto add_row = [&](int row, float v) {
         // a row past the sample's deciders was never written: whatever it holds must not reach the sum
         const float c = (row < rows) ? c_lds[row] : INFINITY;
-        acc += (c < INFINITY) ? __builtin_amdgcn_exp2f(v - c) : 0.f;
+        acc += (c < INFINITY) ? (GENERIC ? exp2f(v - c) : __builtin_amdgcn_exp2f(v - c)) : 0.f;
     };
 #pragma unroll
     for (int u = 0; u < IMP_FL_ROWS; ++u) add_row(grp + u * IMP_FL_GROUPS, l[u]);
@@ -432,14 +437,15 @@ __global__ __launch_bounds__(256) void imp_finish_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// generic path: one workgroup per (decider, head) for the stats, one per 8 visual keys for the scores.
+// generic path: one workgroup per (decider, head) for the stats, which also keeps the logits of a small decider set
+// (scores from those as on the bf16 path); one per 8 visual keys for the scores of larger sets.
 // Plain float arithmetic, any head size up to 256.
 // ---------------------------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(256) void imp_stats_generic(
     const T* __restrict__ q, const T* __restrict__ k, int H, int dh, float scale2,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ dec_idx, const int32_t* __restrict__ dec_off,
-    int max_D, float* __restrict__ cws) {
+    int max_D, int NKB, float* __restrict__ logits, float* __restrict__ cws) {
     const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int tok0 = seq_off[b];
     const int N = seq_off[b + 1] - tok0;
@@ -450,8 +456,9 @@ __global__ __launch_bounds__(256) void imp_stats_generic(
     const T* qr = q + ((size_t)(tok0 + pos) * H + h) * dh;
     float m = -INFINITY, z = 0.f;
     for (int j = threadIdx.x; j < N; j += 256) {
-        const float s = row_dot<T>(k + ((size_t)(tok0 + j) * H + h) * dh, qr, dh);
-        lse2_combine(m, z, s * scale2, 1.0f);
+        const float s = row_dot<T>(k + ((size_t)(tok0 + j) * H + h) * dh, qr, dh) * scale2;
+        if (logits && j < NKB * 16) logits[(((size_t)b * NKB + (j >> 4)) * H * max_D + h * max_D + i) * 16 + (j & 15)] = s;
+        lse2_combine(m, z, s, 1.0f);
     }
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -525,6 +532,9 @@ int d3tom::importance_check(const void* q, const void* k, int dt, int B, const i
     return D3TOM_OK;
 }
 
+// The scores come from kept logits if the workspace has them and the log-sum-exps of all (head, decider) pairs fit in 48 KB of LDS.
+static bool imp_keeps_logits(int H, int max_D) { return max_D <= IMP_KEEP_MAXD && (long)H * max_D <= 12288; }
+
 // The launches; arguments and workspace have been checked.
 int d3tom::importance_run(const void* q, const void* k, int dt,
                           int B, const int32_t* seq_off, int H, int dh, float scale,
@@ -543,7 +553,7 @@ int d3tom::importance_run(const void* q, const void* k, int dt,
         const uint16_t* qq = (const uint16_t*)q;
         const uint16_t* kk = (const uint16_t*)k;
         // small decider sets: the first sweep keeps its logits and the scores come from them (K fetched once)
-        const bool keep = max_D <= IMP_KEEP_MAXD;
+        const bool keep = imp_keeps_logits(H, max_D);
         float* logits = (float*)(wsb + w.logit_off);
         // the decider rows and each wave's statistics (or the log-sum-exps)
         const int qrows = w.DPAD < IMP_QROWS ? w.DPAD : IMP_QROWS;
@@ -562,7 +572,7 @@ int d3tom::importance_run(const void* q, const void* k, int dt,
 #undef D3TOM_IMP_STATS
         if (keep) {
             const dim3 g2k(ceil_div(max_N, 16), B);
-            D3TOM_LAUNCH(IMP_SCORES, st, imp_scores_from_logits<<<g2k, IMP_FL_THREADS, (size_t)H * max_D * sizeof(float), st>>>(
+            D3TOM_LAUNCH(IMP_SCORES, st, imp_scores_from_logits<false><<<g2k, IMP_FL_THREADS, (size_t)H * max_D * sizeof(float), st>>>(
                 H, seq_off, dec_off, vis_start, vis_count, score_off, max_D, max_V, w.DPAD, w.NCH, w.KC, w.NKB, part, logits,
                 scores));
             return D3TOM_OK;
@@ -578,16 +588,25 @@ int d3tom::importance_run(const void* q, const void* k, int dt,
         return D3TOM_OK;
     }
     float* cws = (float*)(wsb + w.c_off);
-    const dim3 g1(max_D, H, B), g2(ceil_div(max_V, IMG_KEYS), B);
+    const bool keep = imp_keeps_logits(H, max_D);
+    float* logits = keep ? (float*)(wsb + w.logit_off) : nullptr;
+    const dim3 g1(max_D, H, B), g2(ceil_div(max_V, IMG_KEYS), B), g2k(ceil_div(max_N, 16), B);
     if (dt == D3TOM_F32) {
         D3TOM_LAUNCH(IMP_STATS, st, imp_stats_generic<float><<<g1, 256, 0, st>>>(
-            (const float*)q, (const float*)k, H, dh, scale2, seq_off, dec_idx, dec_off, max_D, cws));
+            (const float*)q, (const float*)k, H, dh, scale2, seq_off, dec_idx, dec_off, max_D, w.NKB, logits, cws));
+    } else {
+        D3TOM_LAUNCH(IMP_STATS, st, imp_stats_generic<uint16_t><<<g1, 256, 0, st>>>(
+            (const uint16_t*)q, (const uint16_t*)k, H, dh, scale2, seq_off, dec_idx, dec_off, max_D, w.NKB, logits, cws));
+    }
+    if (keep) {
+        D3TOM_LAUNCH(IMP_SCORES, st, imp_scores_from_logits<true><<<g2k, IMP_FL_THREADS, (size_t)H * max_D * sizeof(float), st>>>(
+            H, seq_off, dec_off, vis_start, vis_count, score_off, max_D, max_V, w.DPAD, w.NCH, w.KC, w.NKB, (const float2*)cws,
+            logits, scores));
+    } else if (dt == D3TOM_F32) {
         D3TOM_LAUNCH(IMP_SCORES, st, imp_scores_generic<float><<<g2, 256, 0, st>>>(
             (const float*)q, (const float*)k, H, dh, scale2, seq_off, dec_idx, dec_off, vis_start, vis_count, score_off,
             max_D, max_V, cws, scores));
     } else {
-        D3TOM_LAUNCH(IMP_STATS, st, imp_stats_generic<uint16_t><<<g1, 256, 0, st>>>(
-            (const uint16_t*)q, (const uint16_t*)k, H, dh, scale2, seq_off, dec_idx, dec_off, max_D, cws));
         D3TOM_LAUNCH(IMP_SCORES, st, imp_scores_generic<uint16_t><<<g2, 256, 0, st>>>(
             (const uint16_t*)q, (const uint16_t*)k, H, dh, scale2, seq_off, dec_idx, dec_off, vis_start, vis_count,
             score_off, max_D, max_V, cws, scores));

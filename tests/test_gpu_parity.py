@@ -118,6 +118,21 @@ def test_importance_decider_groups_and_chunks(dh, copies):
         np.testing.assert_array_equal(S[i], S[len(batch) - len(samples) + i])
 
 
+@pytest.mark.parametrize("dtype,H,dh", [("f32", 4, 64), ("f32", 3, 36), ("bf16", 2, 40), ("f32", 400, 8)])
+def test_importance_generic_kept_logits(dtype, H, dh):
+    """Generic kernels: decider counts around the largest set that keeps its logits, key counts around blocks of 16 and 256; with
+    400 heads the statistics of 32 deciders no longer fit beside them."""
+    shapes = [(40, 16, 1), (257, 239, 32), (256, 17, 5)]                   # tokens, visual, deciders
+    for extra in (0, 1):
+        samples = [W.random_case(640 + i, N, H * dh, H, 3, V, D + extra, dtype=dtype) for i, (N, V, D) in enumerate(shapes)]
+        for s, (_, _, D) in zip(samples, shapes):
+            s["dec_idx"] = np.resize(s["dec_idx"], D + extra).astype(np.int32)
+            s["D"] = D + extra
+        S = GpuStep(samples, [max(1, s["V"] // 4) for s in samples], dtype).importance()
+        for i, s in enumerate(samples):
+            check_scores(S[i], oracle.importance(s["q"], s["k"], s["dec_idx"], s["vis_start"], s["V"]))
+
+
 @pytest.mark.parametrize("V,k", [(2100, 97), (2200, 96), (2300, 193), (3000, 900), (2801, 768)])
 def test_merge_column_tiles_of_96(V, k):
     """Single samples whose cosine tiles fill one round with 96 kept slots per tile: k around multiples of 96 and 128."""
