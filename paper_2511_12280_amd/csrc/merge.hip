@@ -409,53 +409,74 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
 
 // ---- split-K second step: sum the k-slices, scale by the kept row's 1/norm, argmax over all slots ----
 // Used when the similarity matrix has too few tiles to occupy the chip (short sequences): the GEMM is
-// then cut along the contraction instead, and one wave per pruned row finishes the job here.  Slices
-// are added in ascending order and slots are visited in ascending order, so the result is deterministic
-// and ties go to the lowest slot.  The wave writes the row's table entry itself.
-template <bool BARE>     // BARE: the norms come from the k-slices' sums of squares
+// then cut along the contraction instead, and one, two or four waves per pruned row finish the job here, each taking every
+// `wpr`-th column tile.  Slices are added in ascending order and ties go to the lowest slot, so the result is deterministic.
+// Bound by the latency of its loads, so a wave should go round its loop once, and all loads of a turn (16 slices of both halves of
+// the tile, the norms) are requested together: without a branch around any of them, since each branch costs a wait and some tens
+// of cycles.  (One wave per row, loads under conditions: 1400 rows x 600 slots x 2 slices 14.0 us, now 6.2; 486 x 243 x 4 slices
+// 6.8 us, now 3.8; 921 x 103 x 16 4.5 us, now 3.9.)
+template <bool BARE, int wpr>     // BARE: the norms come from the k-slices' sums of squares (else from rnorm, by token)
 __global__ __launch_bounds__(256) void cos_reduce_argmax(
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count,
     const int32_t* __restrict__ kept_off,
     int max_V, int max_keep, const int32_t* __restrict__ pruned, const float* __restrict__ rnorm,
     const float* __restrict__ dots, int ksplit, int n_tiles, int nrt_launch, int nct_launch,
-    table_t* __restrict__ table, int VP, const int32_t* __restrict__ kept_idx /* != nullptr: rnorm is indexed by token */,
+    table_t* __restrict__ table, int VP, const int32_t* __restrict__ kept_idx,
     const float* __restrict__ sq, int nB) {
+#if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = 64;
     extern __shared__ float rn_s[];             // BARE: [kept slots] 1 / norm
+    __shared__ float2 join[4];
     const int b = blockIdx.y;
     const SampleGeom s = sample_geom(b, seq_off, vis_start, vis_count, kept_off, max_V, max_keep);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int p = blockIdx.x * 4 + wave;
-    if (s.k <= 0 || (int)blockIdx.x * 4 >= s.M) return;
-    if constexpr (BARE) {
-        for (int t = threadIdx.x; t < s.k; t += 256) {
-            float part[16], ss = 0.f;
+    constexpr int rows = 4 / wpr;
+    const int p = blockIdx.x * rows + wave / wpr, part = wave % wpr;
+    if (s.k <= 0 || (int)blockIdx.x * rows >= s.M) return;
+    const float* rn = rnorm + (size_t)b * max_V;
+    const int rt = p / BM, lr = p % BM;
+    const int nct = (p < s.M) ? (s.k + COS_BN - 1) / COS_BN : 0;
+    // Loads without branches: slices beyond the launch's, and tiles beyond the sample's, lie outside the buffer and read as 0
+    // (columns beyond the sample's slots hold whatever the tile held; they are not looked at).
+    const uint32_t slice = (uint32_t)n_tiles * (BM * COS_BN * 4);
+    const __amdgpu_buffer_rsrc_t dots_r = make_uniform_rsrc(dots, (uint32_t)ksplit * slice);
+    float v[2][16], rnv[2];
+    auto request = [&](int ct) {
+        const uint32_t tile_id = (uint32_t)((b * nrt_launch + rt) * nct_launch + ct);
+        const uint32_t at = ct < nct ? (tile_id * BM + lr) * (COS_BN * 4) + lane * 4 : 0xC0000000u;
+        int tok_at[2];
+        if constexpr (!BARE) {
+#pragma unroll
+            for (int half = 0; half < 2; ++half) tok_at[half] = kept_idx[kept_off[b] + min(ct * COS_BN + half * 64 + lane, s.k - 1)];
+        }
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
 #pragma unroll
             for (int ks = 0; ks < 16; ++ks)
-                part[ks] = (ks < ksplit) ? sq[(((size_t)ks * nB + b) * nct_launch + t / COS_BN) * 128 + t % COS_BN] : 0.f;
+                v[half][ks] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dots_r, at + ks * slice + half * 256, 0, 0));
+        if constexpr (!BARE) {
 #pragma unroll
-            for (int ks = 0; ks < 16; ++ks) ss += part[ks];
+            for (int half = 0; half < 2; ++half) rnv[half] = rn[min(max(tok_at[half], 0), s.V - 1)];
+        }
+    };
+    request(part);
+    const int tok = (p < s.M) ? min(max(pruned[(size_t)b * max_V + p], 0), s.V - 1) : 0;
+    if constexpr (BARE) {
+        const __amdgpu_buffer_rsrc_t sq_r = make_uniform_rsrc(sq, (uint32_t)(ksplit * nB * nct_launch) * 512u);
+        for (int t = threadIdx.x; t < s.k; t += 256) {
+            float sl[16], ss = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < 16; ++ks)
+                sl[ks] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sq_r, (((ks * nB + b) * nct_launch + t / COS_BN) * 128 + t % COS_BN) * 4, 0, 0));
+#pragma unroll
+            for (int ks = 0; ks < 16; ++ks) ss += sl[ks];
             rn_s[t] = reciprocal_norm(ss);
         }
         __syncthreads();
     }
-    if (p >= s.M) return;
-    const float* rn = rnorm + (size_t)b * max_V;
-    const int rt = p / BM, lr = p % BM;
-    const int nct = (s.k + COS_BN - 1) / COS_BN;
     float best = -INFINITY; int bidx = 0x7FFFFFFF;
-    for (int ct = 0; ct < nct; ++ct) {
-        const int tile_id = (b * nrt_launch + rt) * nct_launch + ct;
-        // all slices of both column halves are requested before the first add (at most 16 slices)
-        float v[2][16];
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int col = half * 64 + lane;
-            const bool ok = ct * COS_BN + col < s.k;
-#pragma unroll
-            for (int ks = 0; ks < 16; ++ks)
-                v[half][ks] = (ok && ks < ksplit) ? dots[((size_t)ks * n_tiles + tile_id) * (BM * COS_BN) + lr * COS_BN + col] : 0.f;
-        }
+    for (int ct = part; ct < nct; ct += wpr) {
+        if (ct != part) request(ct);
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             const int slot = ct * COS_BN + half * 64 + lane;
@@ -463,8 +484,7 @@ __global__ __launch_bounds__(256) void cos_reduce_argmax(
                 float sum = 0.f;
 #pragma unroll
                 for (int ks = 0; ks < 16; ++ks) sum += v[half][ks];        // ascending slices; absent ones add 0
-                const float rnv = BARE ? rn_s[slot] : rn[kept_idx ? min(max(kept_idx[kept_off[b] + slot], 0), s.V - 1) : slot];
-                const float val = sum * rnv;
+                const float val = sum * (BARE ? rn_s[slot] : rnv[half]);
                 if (val > best) { best = val; bidx = slot; }
             }
         }
@@ -476,11 +496,18 @@ __global__ __launch_bounds__(256) void cos_reduce_argmax(
         const bool take = (ov > best) | ((ov == best) & (oi < bidx));
         best = take ? ov : best; bidx = take ? oi : bidx;
     }
-    if (lane == 0) {
-        const int slot = min(max(bidx, 0), s.k - 1);
-        const int tok = min(max(pruned[(size_t)b * max_V + p], 0), s.V - 1);
-        table[(size_t)b * VP + tok] = table_entry(best, slot);
+    if (wpr > 1) {
+        if (lane == 0) join[wave] = make_float2(best, __int_as_float(bidx));
+        __syncthreads();
+        for (int w = 1; w < wpr; ++w) {
+            const float2 o = join[(wave & ~(wpr - 1)) + w];
+            const int oi = __float_as_int(o.y);
+            const bool take = (o.x > best) | ((o.x == best) & (oi < bidx));
+            best = take ? o.x : best; bidx = take ? oi : bidx;
+        }
     }
+    if (lane == 0 && part == 0 && p < s.M) table[(size_t)b * VP + tok] = table_entry(best, min(max(bidx, 0), s.k - 1));
+#endif
 }
 
 // ---- cosine + argmax, generic: one workgroup per pruned row ---
@@ -825,12 +852,16 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
         else { if (narrow) D3TOM_COS(1, 3, false); else D3TOM_COS(1, 4, false); }
 #undef D3TOM_COS
         if (ksplit > 1) {
-            const dim3 gr(ceil_div(max_pruned, 4), B);
-#define D3TOM_REDUCE(BAREV, LDS)                                                                                        \
-    D3TOM_LAUNCH(COS_REDUCE, st, cos_reduce_argmax<BAREV><<<gr, 256, LDS, st>>>(                                        \
+            const int wpr = nct >= 3 ? 4 : nct;            // waves per pruned row: one column tile each, as far as four go
+            const dim3 gr(ceil_div(max_pruned, 4 / wpr), B);
+#define D3TOM_REDUCE(BAREV, WPRV, LDS)                                                                                  \
+    D3TOM_LAUNCH(COS_REDUCE, st, (cos_reduce_argmax<BAREV, WPRV><<<gr, 256, LDS, st>>>(                                 \
         seq_off, vis_start, vis_count, kept_off, max_V, max_keep, pruned, rnorm, dots, ksplit, nrt * nct * B, nrt, nct, \
-        table, w.VP, prepared ? kept_idx : nullptr, sq, B))
-            if (bare) D3TOM_REDUCE(true, (size_t)max_keep * sizeof(float)); else D3TOM_REDUCE(false, 0);
+        table, w.VP, kept_idx, sq, B)))
+#define D3TOM_REDUCE_WPR(BAREV, LDS)                                                                                    \
+    do { if (wpr == 1) D3TOM_REDUCE(BAREV, 1, LDS); else if (wpr == 2) D3TOM_REDUCE(BAREV, 2, LDS); else D3TOM_REDUCE(BAREV, 4, LDS); } while (0)
+            if (bare) D3TOM_REDUCE_WPR(true, (size_t)max_keep * sizeof(float)); else D3TOM_REDUCE_WPR(false, 0);
+#undef D3TOM_REDUCE_WPR
 #undef D3TOM_REDUCE
         }
     } else if (max_pruned > 0) {

@@ -374,6 +374,23 @@ def test_merge_layer_one_call_on_every_kernel_path(dtype, d, H, shapes):
             np.testing.assert_array_equal(m1[key][b], mout[key][b])
 
 
+@pytest.mark.parametrize("shapes", [
+    [(3, 300, 5, 2, 128.4 / 300), (2, 301, 4, 3, 129 / 301), (4, 260, 4, 1, 258 / 260)],       # one, two and three column tiles
+    [(6, 700, 9, 4, 640 / 700), (5, 640, 3, 2, 513 / 640)],                                    # five: a second turn for one wave
+])
+def test_merge_split_contraction_waves_per_row(shapes):
+    """Cosines cut along the contraction: kept counts around multiples of the 128-slot tiles and of four tiles (one per wave of a
+    pruned row), both through the one call and through the separate ones (their norms differ in the last bit)."""
+    samples = [W.random_case(520 + i, P + V + O, 2048, 16, P, V, D, dtype="bf16", centres=max(3, V // 6)) for i, (P, V, O, D, _) in enumerate(shapes)]
+    ratios = [r for *_, r in shapes]
+    ref = GpuStep(samples, [oracle.keep_count(s["V"], r) for s, r in zip(samples, ratios)], "bf16")
+    S = ref.importance(); kept, slot = ref.select_topk(); mout = ref.merge()
+    S1, kept1, m1 = ref.merge_layer(ratios)
+    for b in range(len(samples)):
+        check_full_sample(ref, b, S, kept, slot, mout)
+        check_full_sample(ref, b, S1, kept1, slot, m1)
+
+
 @pytest.mark.parametrize("d_sim", [128, 72])          # MFMA cosine path (a multiple of 64) and the generic one
 def test_merge_layer_one_call_with_separate_similarity_features(d_sim):
     """`sim` != x in the one-call merge layer: the selection launch takes its row norms from `sim` (other row length
