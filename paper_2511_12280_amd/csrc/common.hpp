@@ -86,6 +86,38 @@ __device__ __forceinline__ float row_dot(const T* __restrict__ a, const T* __res
     return acc;
 }
 
+// Makes the kernel hold all of these wave-uniform values at one point.  Reads of a sample's offsets written one after the other are
+// otherwise scheduled each behind the wait for the one before, a trip to memory each (a third of a microsecond at a kernel's start).
+
+// Makes a kernel hold all of these wave-uniform values at one point, so that they are read together.  A sample's offsets written one
+// after the other are otherwise scheduled each behind the wait for the one before it: three trips to memory instead of one
+// before a merge kernel knows its sample.
+__device__ __forceinline__ void request_together(int& v0, int& v1, int& v2, int& v3) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(v0), "+s"(v1), "+s"(v2), "+s"(v3));
+#endif
+}
+__device__ __forceinline__ void request_together(int& v0, int& v1, int& v2, int& v3, int& v4) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(v0), "+s"(v1), "+s"(v2), "+s"(v3), "+s"(v4));
+#endif
+}
+__device__ __forceinline__ void request_together(int& v0, int& v1, int& v2, int& v3, int& v4, int& v5) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(v0), "+s"(v1), "+s"(v2), "+s"(v3), "+s"(v4), "+s"(v5));
+#endif
+}
+__device__ __forceinline__ void request_together(int& v0, int& v1, int& v2, int& v3, int& v4, int& v5, int& v6) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(v0), "+s"(v1), "+s"(v2), "+s"(v3), "+s"(v4), "+s"(v5), "+s"(v6));
+#endif
+}
+__device__ __forceinline__ void request_together(int& v0, int& v1, int& v2, int& v3, int& v4, int& v5, int& v6, int& v7) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(v0), "+s"(v1), "+s"(v2), "+s"(v3), "+s"(v4), "+s"(v5), "+s"(v6), "+s"(v7));
+#endif
+}
+
 // ---- wave / block reductions ----------------------------------------------------------------
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

@@ -158,11 +158,12 @@ __global__ __launch_bounds__(256, IMP_SUB_STATS == 6 ? 3 : 2) void imp_stats_bf1
     constexpr int KS = DH / 32;
     // heads vary fastest over the grid: workgroups that run together read neighbouring 2*DH-byte pieces of the same key rows
     const int h = blockIdx.x, chunk = blockIdx.y, b = blockIdx.z;
-    const int tok0 = seq_off[b];
     constexpr int KC = IMP_SUB_STATS * 64;
-    const int N = min(seq_off[b + 1] - tok0, NCH * KC);               // the workspace holds NCH chunks per head
-    const int D = min(dec_off[b + 1] - dec_off[b], max_D);
-    const int32_t* dec = dec_idx + dec_off[b];
+    int tok0 = seq_off[b], tok1 = seq_off[b + 1], d0 = dec_off[b], d1 = dec_off[b + 1];
+    request_together(tok0, tok1, d0, d1);
+    const int N = min(tok1 - tok0, NCH * KC);                         // the workspace holds NCH chunks per head
+    const int D = min(d1 - d0, max_D);
+    const int32_t* dec = dec_idx + d0;
     const int key_base = chunk * KC;
     if (key_base >= N || D <= 0) return;
 
@@ -252,12 +253,13 @@ __global__ __launch_bounds__(256, IMP_SUB_SCORES == 4 ? 4 : 3) void imp_scores_b
     constexpr int KS = DH / 32, KCS = IMP_SUB_SCORES * 64;
     // heads vary fastest over the grid: workgroups that run together read neighbouring 2*DH-byte pieces of the same key rows
     const int h = blockIdx.x, chunk = blockIdx.y, b = blockIdx.z;
-    const int tok0 = seq_off[b];
-    const int N = min(seq_off[b + 1] - tok0, NCH * KC);
-    const int D = min(dec_off[b + 1] - dec_off[b], max_D);
-    const int32_t* dec = dec_idx + dec_off[b];
-    const int vs = min(max(vis_start[b], 0), N);
-    const int V = min(min(vis_count[b], max_V), N - vs);
+    int tok0 = seq_off[b], tok1 = seq_off[b + 1], d0 = dec_off[b], d1 = dec_off[b + 1], vs0 = vis_start[b], vc = vis_count[b];
+    request_together(tok0, tok1, d0, d1, vs0, vc);
+    const int N = min(tok1 - tok0, NCH * KC);
+    const int D = min(d1 - d0, max_D);
+    const int32_t* dec = dec_idx + d0;
+    const int vs = min(max(vs0, 0), N);
+    const int V = min(min(vc, max_V), N - vs);
     const int key_base = chunk * KCS;
     if (key_base >= V || D <= 0) return;
 
@@ -277,9 +279,10 @@ __global__ __launch_bounds__(256, IMP_SUB_SCORES == 4 ? 4 : 3) void imp_scores_b
         for (int c0 = 0; c0 < nch; c0 += 8) {              // 8 independent loads in flight, combined in order
             float2 a[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) a[u] = (c0 + u < nch) ? p[(size_t)(c0 + u) * DPAD] : make_float2(-INFINITY, 0.f);
+            for (int u = 0; u < 8; ++u) a[u] = p[(size_t)min(c0 + u, nch - 1) * DPAD];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) lse2_combine_fast(m, z, a[u].x, a[u].y);
+            for (int u = 0; u < 8; ++u)
+                if (c0 + u < nch) lse2_combine_fast(m, z, a[u].x, a[u].y);
         }
         c_lds[t] = t < D ? m + __builtin_amdgcn_logf(z) : INFINITY;     // padded rows contribute exp2(-inf) = 0
     }
@@ -342,11 +345,14 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count, const int32_t* __restrict__ score_off,
     int max_D, int max_V, int DPAD, int NCH, int KC, int NKB, const float2* __restrict__ part, const float* __restrict__ logits,
     float* __restrict__ scores) {
+#if defined(__HIP_DEVICE_COMPILE__)
     const int kb = blockIdx.x, b = blockIdx.y;
-    const int N = min(seq_off[b + 1] - seq_off[b], NCH * KC);
-    const int D = min(dec_off[b + 1] - dec_off[b], max_D);
-    const int vs = min(max(vis_start[b], 0), N);
-    const int V = min(min(vis_count[b], max_V), N - vs);
+    int tok0 = seq_off[b], tok1 = seq_off[b + 1], d0 = dec_off[b], d1 = dec_off[b + 1], vs0 = vis_start[b], vc = vis_count[b], s0 = score_off[b];
+    request_together(tok0, tok1, d0, d1, vs0, vc, s0);
+    const int N = min(tok1 - tok0, NCH * KC);
+    const int D = min(d1 - d0, max_D);
+    const int vs = min(max(vs0, 0), N);
+    const int V = min(min(vc, max_V), N - vs);
     const int key0 = kb * 16;
     extern __shared__ float c_lds[];                    // [H][max_D] log2-sum-exp2, +inf for rows past the sample's deciders
     __shared__ float red[IMP_FL_THREADS / 64][16];
@@ -355,13 +361,14 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     // from another XCD's writes, i.e. from memory) overlaps the statistics below.
     const int key = threadIdx.x & 15, grp = threadIdx.x >> 4;
     const int rows = H * max_D;
-    const float* lb = logits + ((size_t)(b * NKB + kb) * rows) * 16 + key;
+    const __amdgpu_buffer_rsrc_t lb = make_uniform_rsrc(logits + ((size_t)(b * NKB + kb) * rows) * 16, (uint32_t)rows * 64u);   // rows past the block's read as 0
     float l[IMP_FL_ROWS];
+    auto request = [&](int r0) {
 #pragma unroll
-    for (int u = 0; u < IMP_FL_ROWS; ++u) {
-        const int row = grp + u * IMP_FL_GROUPS;
-        l[u] = (row < rows) ? lb[(size_t)row * 16] : 0.f;
-    }
+        for (int u = 0; u < IMP_FL_ROWS; ++u)
+            l[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(lb, (uint32_t)((r0 + grp + u * IMP_FL_GROUPS) * 16 + key) * 4u, 0, 0));
+    };
+    request(0);
     if (D <= 0 || key0 >= vs + V || key0 + 16 <= vs || key0 >= N) return;
     const int nch = min((N + KC - 1) / KC, NCH);
     for (int t = threadIdx.x; t < rows; t += IMP_FL_THREADS) {
@@ -375,7 +382,7 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
             for (int c0 = 0; c0 < nch; c0 += 8) {           // 8 independent loads in flight, combined in chunk order
                 float2 a[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) a[u] = (c0 + u < nch) ? p[(size_t)(c0 + u) * DPAD] : make_float2(-INFINITY, 0.f);
+                for (int u = 0; u < 8; ++u) a[u] = p[(size_t)min(c0 + u, nch - 1) * DPAD];
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
                     if (c0 + u < nch) lse2_combine_fast(m, z, a[u].x, a[u].y);
@@ -394,11 +401,7 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
 #pragma unroll
     for (int u = 0; u < IMP_FL_ROWS; ++u) add_row(grp + u * IMP_FL_GROUPS, l[u]);
     for (int r0 = IMP_FL_ROWS * IMP_FL_GROUPS; r0 < rows; r0 += IMP_FL_ROWS * IMP_FL_GROUPS) {     // more than 1024 rows
-#pragma unroll
-        for (int u = 0; u < IMP_FL_ROWS; ++u) {
-            const int row = r0 + grp + u * IMP_FL_GROUPS;
-            l[u] = (row < rows) ? lb[(size_t)row * 16] : 0.f;
-        }
+        request(r0);
 #pragma unroll
         for (int u = 0; u < IMP_FL_ROWS; ++u) add_row(r0 + grp + u * IMP_FL_GROUPS, l[u]);
     }
@@ -411,8 +414,9 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
         float sum = 0.f;
 #pragma unroll
         for (int w = 0; w < IMP_FL_THREADS / 64; ++w) sum += red[w][threadIdx.x];      // waves in ascending order
-        scores[score_off[b] + j] = sum / (float)H;
+        scores[s0 + j] = sum / (float)H;
     }
+#endif
 }
 
 // S_j = mean over heads of the per-head rows, heads added in ascending order
@@ -421,19 +425,21 @@ __global__ __launch_bounds__(256) void imp_finish_kernel(
     const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count, const int32_t* __restrict__ score_off,
     int max_V, float* __restrict__ scores) {
     const int b = blockIdx.y, j = blockIdx.x * 256 + threadIdx.x;
-    const int N = seq_off[b + 1] - seq_off[b];
-    const int vs = min(max(vis_start[b], 0), N);
-    const int V = min(min(vis_count[b], max_V), N - vs);
+    int tok0 = seq_off[b], tok1 = seq_off[b + 1], vs0 = vis_start[b], vc = vis_count[b], s0 = score_off[b];
+    request_together(tok0, tok1, vs0, vc, s0);
+    const int N = tok1 - tok0;
+    const int vs = min(max(vs0, 0), N);
+    const int V = min(min(vc, max_V), N - vs);
     if (j >= V) return;
     float s = 0.f;
     for (int h0 = 0; h0 < H; h0 += 32) {                   // 32 independent loads in flight, added in head order
         float a[32];
 #pragma unroll
-        for (int u = 0; u < 32; ++u) a[u] = (h0 + u < H) ? sp[(size_t)(b * H + h0 + u) * VPAD + j] : 0.f;
+        for (int u = 0; u < 32; ++u) a[u] = sp[(size_t)(b * H + min(h0 + u, H - 1)) * VPAD + j];
 #pragma unroll
-        for (int u = 0; u < 32; ++u) s += a[u];
+        for (int u = 0; u < 32; ++u) s += (h0 + u < H) ? a[u] : 0.f;
     }
-    scores[score_off[b] + j] = s / (float)H;
+    scores[s0 + j] = s / (float)H;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -447,12 +453,13 @@ __global__ __launch_bounds__(256) void imp_stats_generic(
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ dec_idx, const int32_t* __restrict__ dec_off,
     int max_D, int NKB, float* __restrict__ logits, float* __restrict__ cws) {
     const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    const int tok0 = seq_off[b];
-    const int N = seq_off[b + 1] - tok0;
-    const int D = min(dec_off[b + 1] - dec_off[b], max_D);
+    int tok0 = seq_off[b], tok1 = seq_off[b + 1], d0 = dec_off[b], d1 = dec_off[b + 1];
+    request_together(tok0, tok1, d0, d1);
+    const int N = tok1 - tok0;
+    const int D = min(d1 - d0, max_D);
     if (i >= D) return;
     __shared__ float2 red[4];
-    const int pos = min(max(dec_idx[dec_off[b] + i], 0), N - 1);
+    const int pos = min(max(dec_idx[d0 + i], 0), N - 1);
     const T* qr = q + ((size_t)(tok0 + pos) * H + h) * dh;
     float m = -INFINITY, z = 0.f;
     for (int j = threadIdx.x; j < N; j += 256) {

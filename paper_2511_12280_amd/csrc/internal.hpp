@@ -1,6 +1,7 @@
 // Entry-point bodies shared between the C ABI functions of different source files (not part of the C ABI).
 #pragma once
 #include "common.hpp"
+#include "direct_load.hpp"
 
 namespace d3tom {
 
@@ -23,16 +24,16 @@ size_t importance_ws_bytes(int B, int max_N, int max_V, int H, int dh, int max_D
 // every kernel that needs a row norm gets the same bits.
 template <typename T>
 __device__ __forceinline__ float row_sum_squares(const T* __restrict__ row, int d, int lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
     constexpr int EPC = 16 / sizeof(T);       // elements per 16-byte chunk
     float ss = 0.f;
     const int nch = d / EPC;
+    const __amdgpu_buffer_rsrc_t rows = make_uniform_rsrc(row, (uint32_t)d * sizeof(T));      // past the row: reads as 0
     for (int c0 = 0; c0 < nch; c0 += 64 * 8) {
         uint4 w8[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int c = c0 + u * 64 + lane;
-            w8[u] = (c < nch) ? *reinterpret_cast<const uint4*>(row + (size_t)c * EPC) : make_uint4(0, 0, 0, 0);
-        }
+        for (int u = 0; u < 8; ++u)
+            w8[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rows, (uint32_t)(c0 + u * 64 + lane) * 16u, 0, 0));
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const uint4 w = w8[u];
@@ -47,6 +48,9 @@ __device__ __forceinline__ float row_sum_squares(const T* __restrict__ row, int 
         }
     }
     return wave_sum(ss);
+#else
+    return 0.f;
+#endif
 }
 __device__ __forceinline__ float reciprocal_norm(float sum_squares) { return 1.0f / fmaxf(sqrtf(sum_squares), 1e-15f); }
 
@@ -101,12 +105,14 @@ inline bool merge_prep_usable(const MergePrep* q, int B, int max_V, const int32_
 // wave_id, wave_id + nwaves, ... (rows clamped to the sample)
 __device__ __forceinline__ void stream_row_norms(const MergePrep& prep, int max_V, int b, const int32_t* __restrict__ seq_off,
                                                  int wave_id, int nwaves, int lane) {
-    const int n = seq_off[b + 1] - seq_off[b];
-    const int vs = min(max(prep.vis_start[b], 0), n);
-    const int cnt = min(min(max(prep.vis_count[b], 0), n - vs), max_V);
+    int tok0 = seq_off[b], tok1 = seq_off[b + 1], vs0 = prep.vis_start[b], vc = prep.vis_count[b];
+    request_together(tok0, tok1, vs0, vc);
+    const int n = tok1 - tok0;
+    const int vs = min(max(vs0, 0), n);
+    const int cnt = min(min(max(vc, 0), n - vs), max_V);
     float* rn = prep.rnorm + (size_t)b * max_V;
     for (int r = wave_id; r < cnt; r += nwaves) {
-        const size_t row = (size_t)(seq_off[b] + vs + r) * prep.d;
+        const size_t row = (size_t)(tok0 + vs + r) * prep.d;
         const float ss = (prep.dt == D3TOM_BF16) ? row_sum_squares(static_cast<const uint16_t*>(prep.feat) + row, prep.d, lane)
                                                  : row_sum_squares(static_cast<const float*>(prep.feat) + row, prep.d, lane);
         if (lane == 0) rn[r] = reciprocal_norm(ss);

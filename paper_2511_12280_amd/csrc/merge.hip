@@ -53,17 +53,26 @@ void merge_prep_targets(void* merge_ws, int B, int max_V, MergePrep* prep) {
     prep->VP = w.VP;
 }
 
-struct SampleGeom { int tok0, N, vs, V, k, M; };
-__device__ __forceinline__ SampleGeom sample_geom(int b, const int32_t* seq_off, const int32_t* vis_start,
-                                                  const int32_t* vis_count, const int32_t* kept_off, int max_V, int max_keep) {
+struct SampleGeom { int tok0, N, vs, V, k, M, k0; };
+// more0, more1: further offsets to be read with the sample's
+__device__ __forceinline__ SampleGeom sample_geom(int b, const int32_t* seq_off, const int32_t* vis_start, const int32_t* vis_count,
+                                                  const int32_t* kept_off, int max_V, int max_keep, int& more0, int& more1) {
     SampleGeom s;
-    s.tok0 = seq_off[b];
-    s.N = seq_off[b + 1] - s.tok0;
-    s.vs = min(max(vis_start[b], 0), s.N);
-    s.V = min(min(vis_count[b], max_V), s.N - s.vs);
-    s.k = min(min(kept_off[b + 1] - kept_off[b], max_keep), s.V);
+    int t0 = seq_off[b], t1 = seq_off[b + 1], vs = vis_start[b], vc = vis_count[b], k0 = kept_off[b], k1 = kept_off[b + 1];
+    request_together(t0, t1, vs, vc, k0, k1, more0, more1);
+    s.tok0 = t0;
+    s.N = t1 - t0;
+    s.vs = min(max(vs, 0), s.N);
+    s.V = min(min(vc, max_V), s.N - s.vs);
+    s.k0 = k0;
+    s.k = min(min(k1 - k0, max_keep), s.V);
     s.M = s.V - s.k;
     return s;
+}
+__device__ __forceinline__ SampleGeom sample_geom(int b, const int32_t* seq_off, const int32_t* vis_start,
+                                                  const int32_t* vis_count, const int32_t* kept_off, int max_V, int max_keep) {
+    int none0 = 0, none1 = 0;
+    return sample_geom(b, seq_off, vis_start, vis_count, kept_off, max_V, max_keep, none0, none1);
 }
 
 // ---- norms + pruned list + table init --------------------------------------------------------------
@@ -83,7 +92,7 @@ __global__ __launch_bounds__(256) void merge_norms_kernel(
     const int r = blockIdx.x * 4 + (threadIdx.x >> 6);      // kept slot
     const int lane = threadIdx.x & 63;
     if (r >= s.k) return;
-    const int32_t* kp = kept_idx + kept_off[b];
+    const int32_t* kp = kept_idx + s.k0;
     const int j = min(max(kp[r], 0), s.V - 1);
     {
         int32_t* pr = pruned + (size_t)b * max_V;
@@ -163,7 +172,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         // a sample that keeps everything has no tiles: its table entries are written here
         if (s.M <= 0 && id == 0 && xcd % XG == 0 && blockIdx.y == 0)
             for (int r = threadIdx.x; r < s.k; r += 512)
-                table[(size_t)b * VP + min(max(kept_idx[kept_off[b] + r], 0), s.V - 1)] = table_entry_kept(r);
+                table[(size_t)b * VP + min(max(kept_idx[s.k0 + r], 0), s.V - 1)] = table_entry_kept(r);
     }
     const int per_b = (tiles_b + XG - 1) / XG;
     if (id >= per_b) return;
@@ -186,7 +195,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     const int wm = wave >> 1, wn = wave & 1;
     const int r16 = lane & 15, g4 = lane >> 4;
     int32_t* pr = pruned + (size_t)b * max_V;
-    const int32_t* kp = kept_idx + kept_off[b];
+    const int32_t* kp = kept_idx + s.k0;
     const float* rn = rnorm + (size_t)b * max_V;
     const size_t base = (size_t)(s.tok0 + s.vs) * d;
 
@@ -447,7 +456,7 @@ __global__ __launch_bounds__(256) void cos_reduce_argmax(
         int tok_at[2];
         if constexpr (!BARE) {
 #pragma unroll
-            for (int half = 0; half < 2; ++half) tok_at[half] = kept_idx[kept_off[b] + min(ct * COS_BN + half * 64 + lane, s.k - 1)];
+            for (int half = 0; half < 2; ++half) tok_at[half] = kept_idx[s.k0 + min(ct * COS_BN + half * 64 + lane, s.k - 1)];
         }
 #pragma unroll
         for (int half = 0; half < 2; ++half)
@@ -526,7 +535,7 @@ __global__ __launch_bounds__(256) void cos_argmax_generic(
     __shared__ float2 red[16];
     const int grp = threadIdx.x >> 4, l16 = threadIdx.x & 15;
     const int m = min(max(pruned[(size_t)b * max_V + p], 0), s.V - 1);
-    const int32_t* kp = kept_idx + kept_off[b];
+    const int32_t* kp = kept_idx + s.k0;
     const float* rn = rnorm + (size_t)b * max_V;
     const T* xm = f + (size_t)(s.tok0 + s.vs + m) * d;
     float bv = -INFINITY; int bi = 0x7FFFFFFF;
@@ -558,8 +567,11 @@ __global__ __launch_bounds__(256) void cos_argmax_generic(
 // rows are then streamed four at a time so that eight 16-byte loads per thread are in flight;
 // accumulation order is ascending token index, so the result does not depend on the unrolling.  A slot
 // with more members than the LDS list holds is processed in windows of SCAT_LIST members (re-scan).
+// Bound by its chain of trips to memory (the sample's offsets; table and kept position; rows) in small launches, by the rows' traffic
+// in large ones.  No load is under a condition: each one that was cost a branch and often a wait (231 rows of 8 KB from
+// 1024: 9.4 -> 7.5 us, 1951 from 3773: 16.5 -> 13.0, two payloads of 1040 from 3709: 20 -> 17.5).
 constexpr int SCAT_LIST = 256;     // members staged per pass
-constexpr int SCAT_WAVE = SCAT_LIST / 4;
+[[maybe_unused]] constexpr int SCAT_WAVE = SCAT_LIST / 4;
 template <typename T, int CPT>     // CPT: 16-byte chunks per thread per pass
 __global__ __launch_bounds__(256) void merge_scatter_kernel(
     const T* __restrict__ x0, const T* __restrict__ x1, int d, const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_start,
@@ -567,6 +579,7 @@ __global__ __launch_bounds__(256) void merge_scatter_kernel(
     int max_V, int max_keep, int mode, const int32_t* __restrict__ out_off, const table_t* __restrict__ table, int VP,
     const int32_t* __restrict__ vis_off, T* __restrict__ y0, T* __restrict__ y1, int32_t* __restrict__ assign_out,
     int32_t* __restrict__ counts_out, int32_t* __restrict__ src_pos_out, int nslice) {
+#if defined(__HIP_DEVICE_COMPILE__)
     constexpr int EPC = 16 / sizeof(T);
     // a row may be cut into nslice column slices, one workgroup each (few output rows: more workgroups)
     const int o = blockIdx.x / nslice, slice = blockIdx.x % nslice, b = blockIdx.y;
@@ -576,22 +589,23 @@ __global__ __launch_bounds__(256) void merge_scatter_kernel(
     T* __restrict__ y = blockIdx.z ? y1 : y0;
     int32_t* counts = (blockIdx.z || slice) ? nullptr : counts_out;
     int32_t* src_pos = (blockIdx.z || slice) ? nullptr : src_pos_out;
-    int32_t* assign = (blockIdx.z || slice || !assign_out) ? nullptr : assign_out + vis_off[b];
-    const SampleGeom s = sample_geom(b, seq_off, vis_start, vis_count, kept_off, max_V, max_keep);
+    int vo0 = vis_off[b], oo0 = out_off[b];
+    const SampleGeom s = sample_geom(b, seq_off, vis_start, vis_count, kept_off, max_V, max_keep, vo0, oo0);
+    int32_t* assign = (blockIdx.z || slice || !assign_out) ? nullptr : assign_out + vo0;
     const int N_m = s.N - s.M;
     if (o >= N_m) return;
     __shared__ int list[SCAT_LIST];
     __shared__ int stage[4][SCAT_WAVE];
     __shared__ int wcnt[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    T* yrow = y + (size_t)(out_off[b] + o) * d;
+    T* yrow = y + (size_t)(oo0 + o) * d;
     const int nch = d / EPC;
     const int c_per = (nch + nslice - 1) / nslice;
     const int c_lo = slice * c_per, c_hi = min(nch, c_lo + c_per);          // this workgroup's 16-byte chunks
     int src = -1, len = 1, r = 0;
     // table of this sample, read two entries (16 bytes) per lane; a wave takes a contiguous part of it
     // (a multiple of 128 entries so that every lane takes part in each ballot)
-    const uint4* tab2 = reinterpret_cast<const uint4*>(table + (size_t)b * VP);
+    const __amdgpu_buffer_rsrc_t tab = make_uniform_rsrc(table + (size_t)b * VP, (uint32_t)VP * 8u);
     const int part_len = ((s.V + 511) >> 9) << 7;
     const int e0 = wave * part_len;
     const int n_it = part_len >> 7;
@@ -606,7 +620,8 @@ __global__ __launch_bounds__(256) void merge_scatter_kernel(
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int i = e0 + (it0 + u) * 128 + lane * 2;
-                v[u] = (it0 + u < n_it && i < s.V) ? tab2[i >> 1] : make_uint4(0, 0, 0, 0);
+                // beyond this wave's part: outside the buffer, reads as 0, which no slot's low word is
+                v[u] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(tab, it0 + u < n_it ? (uint32_t)i * 8u : 0xFFFFFFF0u, 0, 0));
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -627,6 +642,7 @@ __global__ __launch_bounds__(256) void merge_scatter_kernel(
     else {
         r = o - s.vs;
         want = 0xFFFFFFFFu - (uint32_t)r;
+        const int kept_tok = min(max(kept_idx[s.k0 + r], 0), s.V - 1);
         const int cnt = scan([&](int tok, int ord) {
             if (ord < SCAT_WAVE) stage[wave][ord] = tok;
             if (assign) assign[tok] = r;
@@ -636,10 +652,9 @@ __global__ __launch_bounds__(256) void merge_scatter_kernel(
         len = wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
         fits = wcnt[0] <= SCAT_WAVE && wcnt[1] <= SCAT_WAVE && wcnt[2] <= SCAT_WAVE && wcnt[3] <= SCAT_WAVE;
         for (int w = 0; w < wave; ++w) wbase += wcnt[w];
-        const int kept_tok = min(max(kept_idx[kept_off[b] + r], 0), s.V - 1);
         if (tid == 0) {
-            if (src_pos) src_pos[out_off[b] + o] = s.vs + kept_tok;
-            if (counts) counts[kept_off[b] + r] = len;
+            if (src_pos) src_pos[oo0 + o] = s.vs + kept_tok;
+            if (counts) counts[s.k0 + r] = len;
         }
         if (len <= 1) src = s.vs + kept_tok;               // nothing absorbed: bit-exact copy
         else if (fits) {
@@ -648,10 +663,14 @@ __global__ __launch_bounds__(256) void merge_scatter_kernel(
         }
     }
     if (src >= 0) {
-        if (tid == 0 && src_pos && (o < s.vs || o >= s.vs + s.k)) src_pos[out_off[b] + o] = src;
+        if (tid == 0 && src_pos && (o < s.vs || o >= s.vs + s.k)) src_pos[oo0 + o] = src;
         const uint4* in = reinterpret_cast<const uint4*>(x + (size_t)(s.tok0 + src) * d);
         uint4* out = reinterpret_cast<uint4*>(yrow);
-        for (int c = c_lo + tid; c < c_hi; c += 256) out[c] = in[c];
+        for (int c = c_lo + tid; c < c_hi; c += 512) {
+            const uint4 w0 = in[c], w1 = in[min(c + 256, c_hi - 1)];
+            out[c] = w0;
+            if (c + 256 < c_hi) out[c + 256] = w1;
+        }
         return;
     }
     // members with ordinal in [win0, win0 + SCAT_LIST) -> list (only when the first scan did not fit)
@@ -676,6 +695,9 @@ __global__ __launch_bounds__(256) void merge_scatter_kernel(
     };
     for (int cb = c_lo; cb < c_hi; cb += 256 * CPT) {     // uniform trip count: the loop body has barriers
         const int c0 = cb + tid;
+        int cc[CPT];                                       // chunks to read; what a thread beyond the slice's end adds up is not stored
+#pragma unroll
+        for (int u = 0; u < CPT; ++u) cc[u] = min(c0 + 256 * u, c_hi - 1);
         float acc[CPT][EPC];
 #pragma unroll
         for (int u = 0; u < CPT; ++u)
@@ -696,7 +718,7 @@ __global__ __launch_bounds__(256) void merge_scatter_kernel(
                 for (int m = 0; m < 8; ++m) {
                     const uint4* row = reinterpret_cast<const uint4*>(xv + (size_t)list[t + m] * d);
 #pragma unroll
-                    for (int u = 0; u < CPT; ++u) { const int c = c0 + 256 * u; w[m][u] = (c < c_hi) ? row[c] : make_uint4(0, 0, 0, 0); }
+                    for (int u = 0; u < CPT; ++u) w[m][u] = row[cc[u]];
                 }
 #pragma unroll
                 for (int m = 0; m < 8; ++m) add_row(acc, w[m]);
@@ -707,7 +729,7 @@ __global__ __launch_bounds__(256) void merge_scatter_kernel(
                 for (int m = 0; m < 4; ++m) {
                     const uint4* row = reinterpret_cast<const uint4*>(xv + (size_t)list[t + m] * d);
 #pragma unroll
-                    for (int u = 0; u < CPT; ++u) { const int c = c0 + 256 * u; w[m][u] = (c < c_hi) ? row[c] : make_uint4(0, 0, 0, 0); }
+                    for (int u = 0; u < CPT; ++u) w[m][u] = row[cc[u]];
                 }
 #pragma unroll
                 for (int m = 0; m < 4; ++m) add_row(acc, w[m]);
@@ -716,7 +738,7 @@ __global__ __launch_bounds__(256) void merge_scatter_kernel(
                 uint4 w[CPT];
                 const uint4* row = reinterpret_cast<const uint4*>(xv + (size_t)list[t] * d);
 #pragma unroll
-                for (int u = 0; u < CPT; ++u) { const int c = c0 + 256 * u; w[u] = (c < c_hi) ? row[c] : make_uint4(0, 0, 0, 0); }
+                for (int u = 0; u < CPT; ++u) w[u] = row[cc[u]];
                 add_row(acc, w);
             }
         }
@@ -738,6 +760,7 @@ __global__ __launch_bounds__(256) void merge_scatter_kernel(
             }
         }
     }
+#endif
 }
 
 }  // namespace d3tom

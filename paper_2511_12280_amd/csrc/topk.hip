@@ -38,7 +38,7 @@ __device__ __forceinline__ int keep_count_device(int V, double ratio) {
 
 constexpr int TOPK_PER = D3TOM_MAX_VISUAL / TOPK_THREADS;      // keys per thread at most
 constexpr int TOPK_BINS = 2048;
-constexpr int TOPK_CAND = 1024;                                // members of one bin that are ranked directly
+[[maybe_unused]] constexpr int TOPK_CAND = 1024;                                // members of one bin that are ranked directly
 
 // inclusive prefix sum over the 64 lanes of a wave
 __device__ __forceinline__ int wave_incl_scan(int v, int lane) {
@@ -55,6 +55,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
     const int32_t* __restrict__ kept_off, int max_V, int32_t* __restrict__ kept_idx, int32_t* __restrict__ slot_of,
     const double* __restrict__ keep_ratio, const int32_t* __restrict__ seq_off, int32_t* __restrict__ keep_k_out,
     int32_t* __restrict__ kept_off_out, int32_t* __restrict__ out_off_out, MergePrep prep) {
+#if defined(__HIP_DEVICE_COMPILE__)
     if (blockIdx.y > 0) {
         // streaming workgroups: norms of the sample's visual rows
         stream_row_norms(prep, max_V, blockIdx.x, seq_off, (int)(blockIdx.y - 1) * (TOPK_THREADS / 64) + (int)(threadIdx.x >> 6),
@@ -70,19 +71,16 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
     __shared__ uint32_t thr_s[2];                 // threshold key, highest index kept among the keys equal to it
     __shared__ int plan[2];                       // kept count of this sample, first slot of this sample in kept_idx
     const int b = blockIdx.x;
-    const int s0 = score_off[b];
-    const int V = min(score_off[b + 1] - s0, max_V);
+    int s0 = score_off[b], s1 = score_off[b + 1];
+    const int V = min(s1 - s0, max_V);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
 
     // thread t holds keys t, t + 1024, ...
     uint32_t key[TOPK_PER];
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+    const __amdgpu_buffer_rsrc_t mine = make_uniform_rsrc(scores + s0, (uint32_t)max(V, 0) * 4u);       // beyond the sample: 0, not fetched
 #pragma unroll
-    for (int c = 0; c < TOPK_PER; ++c) {
-        if (c * TOPK_THREADS >= V) break;
-        const int j = c * TOPK_THREADS + tid;
-        key[c] = (j < V) ? __float_as_uint(scores[s0 + j]) : 0u;
-    }
+    for (int c = 0; c < TOPK_PER; ++c) key[c] = __builtin_amdgcn_raw_buffer_load_b32(mine, (c * TOPK_THREADS + tid) * 4, 0, 0);
     if (keep_ratio && wave == 15) {
         // kept counts from the ratios, on the device: this sample's count and the prefix sums over the samples
         // in front of it (every workgroup repeats that, a sample per lane; the last one also writes the totals)
@@ -254,6 +252,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
         }
         base += __shfl(inc, 63, WAVE);
     }
+#endif
 }
 
 }  // namespace d3tom
