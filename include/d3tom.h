@@ -267,7 +267,8 @@ int d3tom_merge_layer(const void* q, const void* k, const void* x, const void* s
  * model attends without a causal mask).
  *
  * Per sample and head: o = softmax(scale * q k^T) v over all keys of the sample (variable-length
- * batch, no mask, no dropout).  bf16: MFMA with float32 online-softmax state; f32: plain float.
+ * batch, no mask, no dropout).  bf16: MFMA with float32 online-softmax state (the probabilities enter the product
+ * with v as bf16, relative to the running maximum of their row); f32: plain float.
  *
  *   q, k, v     [cu_seqlens[B], H, dh] dt
  *   scale       logit scale, finite and > 0 (1/sqrt(dh) in the paper's models); otherwise

@@ -18,9 +18,9 @@
 // clocks), the other does the softmax arithmetic of its tile; a barrier ends the phase.  That pays because the smaller MFMA
 // shape lets another wave's vector instructions through: per tile 1058 clocks of MFMAs and 756 of softmax arithmetic of the
 // other wave take 1250 clocks together, whereas beside MFMA 32x32x16 the exponentials do not issue at all (1029 + 756 -> 1780).
-// Measured at 32 heads of 128 (four independent waves on the larger shape before): 3773 keys 240 -> 187 us, 1951 keys
-// 70 -> 56 us, 4096 keys 210 us = 1300 TFLOP/s, at 1.95 GHz: the card lowers its clock under this load (2960 clocks per
-// tile and pair of groups; at 3170 clocks it ran at 2.02 GHz and took as long), so what remains is set by power.
+// Measured at 32 heads of 128 (four independent waves on the larger shape before): 3773 keys 248 -> 205 us, 1951 keys
+// 71 -> 61 us, 4096 keys 230 us = 1200 TFLOP/s.  The card lowers its clock under this load, so part of what remains is set by
+// power.
 //
 // K and V tiles go HBM/L2 -> LDS with direct loads (buffer_load ... lds, no register staging; rows past the end of the sample
 // load as zeros through the buffer bounds check) into a ring; rows are unpadded and their 16-byte chunks XOR-swizzled by the
@@ -31,12 +31,17 @@
 // it is cut to one fma and one exp2 per logit and the packing to bf16:
 //   - the row sums come from the matrix core too, a fragment of ones times P^T (two MFMAs per 32 keys instead of 32 adds);
 //   - the weights and the tail mask of the weighted form enter as the C operand of S^T (log2 w / scale2, -inf);
-//   - no running maximum: the reference is the maximum of the first tile, and probabilities are scaled by 2^-24 under it.
-//     A logit that exceeds it by 2^25 shows in the top exponent bit of the packed probabilities (one OR over them
-//     finds it, infinities included); only then the tile's true maximum is taken, the accumulators rescaled and the tile
-//     redone.  Numerator and denominator carry the same factor, float32 and bf16 keep their relative precision, and what falls
-//     below the normal range is 2^-77 of the largest term at least.
-// A second tiled kernel keeps the running maximum and float32 row sums (attend_bf16_online_kernel, below).
+//   - the running maximum costs one max3 per two logits: a lane compares its own logits with the column's maximum, and only where one
+//     of them exceeds it do the four lanes meet and the accumulators of that block of 16 queries get their new scale.
+// What the exponents refer to is a matter of precision.  The probabilities are rounded to bf16, the largest ones carry most of
+// that rounding, and relative to the running maximum the largest is exactly 1 and not rounded at all.  With the first tile's
+// maximum as a fixed reference the kernel takes 184 us instead of 204 at 3773 keys, but its error against float64 (2-norm,
+// relative, before the output is rounded) is 1.06 to 1.11 times as large at a logit spread of 1 (600 .. 3773 keys), 1.5 to 1.6
+// at 2 and 1.8 to 1.9 at 4.  The sums of the rounded probabilities lose nothing against float32 sums of the unrounded
+// ones: 0.95 to 1.00 of their error where the value rows have no common part, 0.7 where they have (a row's weights then
+// add up to exactly 1).  Rounded output, measured at 3773 keys, spreads 1, 2, 4: 2.264e-3, 1.914e-3, 1.728e-3; with
+// float32 sums 2.266e-3, 1.919e-3, 1.735e-3; with the fixed reference 2.332e-3, 2.226e-3, 1.916e-3.
+// A second tiled kernel keeps float32 row sums (attend_bf16_online_kernel, below).
 //
 // The generic path (float32 or any head size) is one workgroup per (query, head) with a chunked
 // online softmax in plain float arithmetic.
@@ -48,7 +53,6 @@ namespace d3tom {
 
 constexpr int ATT_BK = 64;      // keys per tile
 constexpr int ATT_SLOTS = 4;    // ring slots of one K tile and one V tile
-constexpr float ATT_BIAS = 24.f;    // without a running maximum the probabilities are kept 2^24 below their usual scale
 
 typedef __attribute__((address_space(3))) void* att_lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* att_glb_ptr_t;
@@ -166,7 +170,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     for (int t = 0; t < DB; ++t)
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) ot[t][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // m_run: what the exponents refer to, in RAW logits; ms: what they subtract; lt: sum of the column's probabilities, all four alike
+    // m_run: running maximum of the RAW logits; ms: what the exponents subtract; lt: sum of the column's probabilities, all four alike
     float m_run[NQ], ms[NQ];
     f32x4 lt[NQ];
     bf16x8 ones;
@@ -285,36 +289,19 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        auto probabilities = [&]() {
+        // The running maximum.  A lane sees its own 16 of a column's 64 logits; only if one of them exceeds the column's maximum do
+        // the four lanes meet and the accumulators get their new scale.
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) {
+            float t = m_run[qb];
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-                for (int qb = 0; qb < NQ; ++qb)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        pf[kb >> 1][qb][(kb & 1) * 4 + e] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(st[kb][qb][e], scale2, -ms[qb]));
-        };
-        probabilities();
-        uint32_t seen = 0;                      // bit 14 of a half: one of the packed probabilities is at least 2
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-            for (int qb = 0; qb < NQ; ++qb) {
-                typedef uint32_t att_u4 __attribute__((ext_vector_type(4)));
-                const att_u4 w = __builtin_bit_cast(att_u4, pf[kt][qb]);
-                seen |= (w[0] | w[1]) | (w[2] | w[3]);
-            }
-        if (j == 0 || __builtin_amdgcn_ballot_w64((seen & 0x40004000u) != 0) != 0) {
-#pragma unroll
-            for (int qb = 0; qb < NQ; ++qb) {
-                float t = m_run[qb];
-#pragma unroll
-                for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) t = fmaxf(t, st[kb][qb][e]);
+                for (int e = 0; e < 4; ++e) t = fmaxf(t, st[kb][qb][e]);
+            if (__builtin_amdgcn_ballot_w64(t > m_run[qb]) != 0) {
                 const float m_new = att_quad_max(t);        // finite: every tile holds at least one key of the sample
                 const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_new) * scale2);
-                ms[qb] = __builtin_fmaf(m_new, scale2, ATT_BIAS);
+                ms[qb] = m_new * scale2;
                 m_run[qb] = m_new;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) lt[qb][e] *= alpha;
@@ -323,8 +310,14 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 #pragma unroll
                     for (int e = 0; e < 4; ++e) ot[x][qb][e] *= alpha;
             }
-            probabilities();
         }
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    pf[kb >> 1][qb][(kb & 1) * 4 + e] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(st[kb][qb][e], scale2, -ms[qb]));
     };
 
     const int ntile = (n + ATT_BK - 1) / ATT_BK;
@@ -1036,12 +1029,14 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
             return D3TOM_ERR_DEVICE;
         if (dh == 128) D3TOM_ATT((attend_bf16_online_kernel<128>)); else D3TOM_ATT((attend_bf16_online_kernel<64>));
     } else if (mfma) {
-        // Rounds of workgroups over the 256 compute units.  A round of 128-query tiles costs 0.7 of one of 256-query tiles (every
-        // fragment read from LDS feeds one MFMA instead of two; 1024 keys, 32 heads: 23.5 us against 29.1, 1198: 45.5 against 33.3);
-        // with heads of 64 two workgroups of 128 queries share a CU, and it costs 0.55 (8 x 16 heads, 560 keys: 21.1 against 24.7).
+        // Rounds of workgroups over the 256 compute units.  A round of 128-query tiles costs 0.61 to 0.66 of one of 256-query tiles
+        // (every fragment read from LDS feeds one MFMA instead of two; 32 heads, narrow against wide: 1198 keys 45.6 us against
+        // 36.2, two rounds to one; 3773 keys 255 against 205, four to two; 2100 keys 105 against 108, 3 x 1000 keys 60.5 against
+        // 66.0, three to two); with heads of 64 two workgroups of 128 queries share a CU, and it costs 0.5 (16 heads, 3500 keys: 69.2
+        // against 68.1, two to one; 8 x 560 keys: 22.5 against 29.5, one to one).
         const long heads = (long)H * B;
         const long wide = (ceil_div(max_seqlen, 256) * heads + 255) / 256, narrow = (ceil_div(max_seqlen, 128) * heads + 255) / 256;
-        const int nq = (dh == 64 ? 55 : 70) * narrow < 100 * wide ? 1 : 2;
+        const int nq = (dh == 64 ? 55 : 66) * narrow < 100 * wide ? 1 : 2;
         const int nqt = ceil_div(max_seqlen, nq * 128);
         const dim3 g((unsigned)(8 * ceil_div(H * B, 8) * nqt));
         const size_t lds = (size_t)ATT_SLOTS * 2 * ATT_BK * dh * 2;

@@ -222,8 +222,8 @@ def test_attend_both_sides_of_the_short_sample_limit(H, dh, longest):
     (32, 64, True, [512, 513, 257, 64, 192, 193, 33, 128]),
 ])
 def test_attend_tile_widths_and_rising_logits(H, dh, weighted, lens, rise):
-    """Both query tile widths of the tiled kernel; with `rise` later keys exceed the first tile's largest logit by far more than
-    2^25, so that the reference of the exponents has to move."""
+    """Both query tile widths of the tiled kernel; with `rise` later keys exceed the first tile's largest logit by hundreds, so
+    that the running maximum moves with almost every tile."""
     qkv = []
     for n in lens:
         q, k, v = W.random_qkv(800 + n, n, H, dh, "bf16")
@@ -238,6 +238,42 @@ def test_attend_tile_widths_and_rising_logits(H, dh, weighted, lens, rise):
     else:
         for (q, k, v), o in zip(qkv, gpu_attend(qkv, "bf16")):
             check_attend(o, q, k, v, "bf16")
+
+
+def _attend_rounded_probabilities(q, k, v, weight):
+    """Attention as a kernel computes it whose only loss is the rounding of the probabilities to bf16, relative to the running
+    maximum over tiles of 64 keys: float32 state, float32 row sums of the unrounded probabilities, output rounded to bf16."""
+    out = torch.zeros(q.shape, dtype=torch.float32)
+    qt, kt, vt, lw = torch.from_numpy(q), torch.from_numpy(k), torch.from_numpy(v), torch.from_numpy(np.log2(weight)).float()
+    for h in range(q.shape[1]):
+        s2 = qt[:, h] @ kt[:, h].T * (np.log2(np.e) / np.sqrt(q.shape[2])) + lw
+        m, l, acc = torch.full((len(q), 1), -np.inf), torch.zeros(len(q), 1), torch.zeros(len(q), q.shape[2])
+        for j in range(0, len(k), 64):
+            m_new = torch.maximum(m, s2[:, j:j + 64].amax(1, keepdim=True))
+            p, alpha = torch.exp2(s2[:, j:j + 64] - m_new), torch.exp2(m - m_new)
+            l, acc, m = l * alpha + p.sum(1, keepdim=True), acc * alpha + p.bfloat16().float() @ vt[j:j + 64, h], m_new
+        out[:, h] = acc / l
+    return out.bfloat16().double().numpy()
+
+
+@pytest.mark.parametrize("spread", [1.0, 2.0, 4.0])
+@pytest.mark.parametrize("H,dh,n,weighted", [(2, 128, 1300, False), (2, 64, 1300, False), (2, 128, 1300, True), (32, 128, 1198, False), (32, 64, 1300, True)])
+def test_attend_error_is_that_of_rounded_probabilities(H, dh, n, weighted, spread):
+    """The tiled kernel against float64, in 2-norm: no further off than the rounding of the probabilities against the running
+    maximum makes it, with query tiles of both widths.  Both sides round almost the same probabilities, so the two errors agree to a fraction of a percent (the
+    bound of 2 % leaves room for ties of the rounding); any fixed reference of the exponents is 4 % off at unit logit spread and
+    8 to 15 % at 2 and 4.  `spread` is the standard deviation of the logits."""
+    q, k, v = W.random_qkv(870 + n + dh, n, H, dh, "bf16")
+    q, k = (W.round_to(t * np.float32(np.sqrt(spread)), "bf16") for t in (q, k))
+    vis, counts = n // 5, (1 + np.arange(n // 2) % 6).astype(np.int32)
+    weight = key_weights(n, vis, counts) if weighted else np.ones(n)
+    o = (gpu_attend_weighted([(q, k, v)], [counts], [vis], "bf16") if weighted else gpu_attend([(q, k, v)], "bf16"))[0]
+    rows = np.arange(0, n, 1 if H == 2 else 9)
+    ref = oracle.attend(q, k, v, rows=rows, key_weight=weight)[rows]
+    off = lambda a: np.linalg.norm(a - ref) / np.linalg.norm(ref)
+    got, bound = off(o.astype(np.float64)[rows]), off(_attend_rounded_probabilities(q[rows], k, v, weight))
+    print(f"attention error {got:.4e}, rounded probabilities {bound:.4e}")
+    assert got <= 1.02 * bound
 
 
 def test_attend_special_cases_bf16():
