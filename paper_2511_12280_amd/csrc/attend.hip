@@ -41,7 +41,6 @@
 // ones: 0.95 to 1.00 of their error where the value rows have no common part, 0.7 where they have (a row's weights then
 // add up to exactly 1).  Rounded output, measured at 3773 keys, spreads 1, 2, 4: 2.264e-3, 1.914e-3, 1.728e-3; with
 // float32 sums 2.266e-3, 1.919e-3, 1.735e-3; with the fixed reference 2.332e-3, 2.226e-3, 1.916e-3.
-// A second tiled kernel keeps float32 row sums (attend_bf16_online_kernel, below).
 //
 // The generic path (float32 or any head size) is one workgroup per (query, head) with a chunked
 // online softmax in plain float arithmetic.
@@ -401,233 +400,6 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     }
 #endif
 }
-// ---- running maximum --------------------------------------------------------------------------------
-// For the blocks of the stack whose output a merge still compares: probabilities are rounded to bf16 relative to what their
-// exponents refer to, and between near-duplicate rows that rounding decides which of two cosines is the larger; here it
-// is the maximum of the tiles seen so far, whatever the tile width, and the row sums are float32 sums in key order.
-// Four independent waves of 32 queries on MFMA 32x32x16, two workgroups per CU; 240 us at 3773 keys, 32 heads of 128.  (The same
-// arithmetic in the two-group form above took 214 us alone and 243 between the stack's projections: its longer softmax phase
-// paces the loop.)
-constexpr int ATO_BQ = 128;     // queries per workgroup
-constexpr int ATO_NS = 2;       // LDS ring depth
-template <int DH>
-__global__ __launch_bounds__(256, 2) void attend_bf16_online_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-    const int32_t* __restrict__ cu, int H, int nB, int nqt, float scale2, uint16_t* __restrict__ o, KeyWeights) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    constexpr int KS = DH / 16;                 // k-steps of the first product
-    constexpr int DT = DH / 32;                 // 32-dim tiles of O^T
-    constexpr int ROWB = DH * 2;                // bytes per K / V row in LDS (unpadded, chunks swizzled)
-    constexpr int NCHK = DH / 8;                // 16-byte chunks per row
-    constexpr int RPI = 64 / NCHK;              // rows covered by one wave-wide direct load (1 KB)
-    constexpr int LD = ATT_BK / (4 * RPI);      // direct loads per wave, per operand, per stage
-    constexpr int TILE = ATT_BK * ROWB;         // bytes of one K (or V) tile
-    constexpr int STAGE = 2 * TILE;
-    extern __shared__ __attribute__((aligned(16))) char ring[];
-
-    const int xcd = blockIdx.x & 7, li = blockIdx.x >> 3;
-    const int hb = (li / nqt) * 8 + xcd, qt = li % nqt;         // hb = sample * H + head
-    if (hb >= H * nB) return;
-    const int h = hb % H, b = hb / H;
-    const int tok0 = cu[b];
-    const int n = cu[b + 1] - tok0;
-    if (qt * ATO_BQ >= n) return;
-
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int c = lane & 31, g = lane >> 5;
-    const size_t rs = (size_t)H * DH;                      // token stride (elements)
-    const uint16_t* kb = k + (size_t)tok0 * rs + (size_t)h * DH;
-    const uint16_t* vb = v + (size_t)tok0 * rs + (size_t)h * DH;
-    // this head's K / V rows of this sample; a row index >= n is past the end and loads as zeros
-    const uint32_t span = (uint32_t)(((size_t)(n - 1) * rs + DH) * 2);
-    const __amdgpu_buffer_rsrc_t rk = att_uniform_rsrc(kb, span), rv = att_uniform_rsrc(vb, span);
-    const int row_bytes = (int)(rs * 2);
-
-    const int qrow = qt * ATO_BQ + wave * 32 + c;
-    const bool qvalid = qrow < n;
-    bf16x8 qf[KS];
-    {
-        const uint16_t* qp = q + (size_t)(tok0 + (qvalid ? qrow : 0)) * rs + (size_t)h * DH + g * 8;
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-            bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-            qf[kk] = qvalid ? *reinterpret_cast<const bf16x8*>(qp + kk * 16) : z;
-        }
-    }
-    f32x16 ot[DT];
-#pragma unroll
-    for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) ot[t][e] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;       // running max of the RAW logits, running sum of exp2
-
-    // direct loads: lane -> (row, chunk position); the chunk fetched into position p of row r is
-    // p ^ (r mod NCHK) for K (operand reads walk 16+ consecutive rows) and p ^ ((r & 3) * 4) for V
-    // (transposing reads touch 4 consecutive rows per 16-lane group)
-    const int ld_pos = lane % NCHK;
-    int k_off[LD], v_off[LD];                   // byte offsets inside the head's K / V for key0 = 0
-#pragma unroll
-    for (int i = 0; i < LD; ++i) {
-        const int r = wave * (ATT_BK / 4) + lane / NCHK + i * RPI;
-        k_off[i] = r * row_bytes + (((ld_pos ^ (r & 15)) & (NCHK - 1)) << 4);
-        v_off[i] = r * row_bytes + (((ld_pos ^ ((r & 3) * 4)) & (NCHK - 1)) << 4);
-    }
-    const uint32_t ring0 = (uint32_t)(size_t)(att_lds_ptr_t)ring;
-    const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(ring0 + wave * (ATT_BK / 4) * ROWB);
-    auto issue = [&](int key0, int stage) {
-        const int kofs = key0 * row_bytes;
-#pragma unroll
-        for (int i = 0; i < LD; ++i) {
-            att_direct_load(rk, k_off[i] + kofs, wave_lds + stage * STAGE + i * RPI * ROWB);
-            att_direct_load(rv, v_off[i] + kofs, wave_lds + stage * STAGE + TILE + i * RPI * ROWB);
-        }
-    };
-    // K operand fragments: lane (key row c, g) reads chunk (2 kk + g) of its row, swizzled by the row
-    int k_addr[KS];
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) k_addr[kk] = c * ROWB + ((((kk * 2 + g) ^ (c & 15)) & (NCHK - 1)) << 4);
-    // transposing-read geometry of this lane: 16-lane group -> (g, dim half), lane in group -> (row j, 4-dim quad t)
-    const int tr_j = (lane & 15) >> 2, tr_t = lane & 3, tr_half = (lane >> 4) & 1;
-    int v_addr[DT];
-#pragma unroll
-    for (int t = 0; t < DT; ++t) {
-        const int chunk = t * 4 + tr_half * 2 + (tr_t >> 1);
-        v_addr[t] = TILE + (g * 4 + tr_j) * ROWB + (tr_t % 2) * 8 + (((chunk ^ (tr_j * 4)) & (NCHK - 1)) << 4);
-    }
-
-    const int ntile = (n + ATT_BK - 1) / ATT_BK;
-    // one 64-key tile out of ring stage STG (a compile-time constant so that every LDS offset folds
-    // into the instruction)
-    auto tile = [&](auto stg_c, int it) {
-        constexpr int STG = decltype(stg_c)::value;
-        const int key0 = it * ATT_BK;
-        wait_loads_and_barrier<0>();                         // stage STG has landed; the other stage is free
-        const char* sb = ring + STG * STAGE;
-
-        // all K fragments of the tile are requested before the first MFMA
-        bf16x8 kf[2][KS];
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-            for (int kk = 0; kk < KS; ++kk)
-                kf[kt][kk] = *reinterpret_cast<const bf16x8*>(sb + k_addr[kk] + kt * 32 * ROWB);
-        __builtin_amdgcn_sched_barrier(0);
-        // S^T = K Q^T for two 32-key blocks, the two accumulation chains interleaved
-        f32x16 st[2];
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) st[kt][e] = 0.f;
-        __builtin_amdgcn_s_setprio(3);
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-            st[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][kk], qf[kk], st[0], 0, 0, 0);
-            st[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][kk], qf[kk], st[1], 0, 0, 0);
-        }
-        __builtin_amdgcn_s_setprio(0);
-        __builtin_amdgcn_sched_barrier(0);
-        // V^T fragments of the first 32 keys are requested now and land during the softmax arithmetic
-        att_short4 vf[2][2][DT][2];                 // [kt][hh][t][a/b]
-        auto read_v = [&](int kt) {
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-                for (int t = 0; t < DT; ++t) {
-                    const char* pa = sb + v_addr[t] + (kt * 32 + hh * 16) * ROWB;
-                    vf[kt][hh][t][0] = lds_read_tr16(pa);
-                    vf[kt][hh][t][1] = lds_read_tr16(pa + 8 * ROWB);
-                }
-        };
-        read_v(0);
-        __builtin_amdgcn_sched_barrier(0);
-        // the loads of the next stage start here, beside the softmax arithmetic: direct loads and MFMAs
-        // slow each other down, direct loads and vector-ALU work do not
-        if (it + 1 < ntile) issue(key0 + ATT_BK, STG ^ 1);
-        __builtin_amdgcn_sched_barrier(0);
-        // online softmax in base 2 on the raw logits; element e of st[kt]: key kt*32 + (e/4)*8 + 4g + e%4, query c
-        if (key0 + ATT_BK > n) {
-#pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int key = key0 + kt * 32 + (e >> 2) * 8 + g * 4 + (e & 3);
-                    if (key >= n) st[kt][e] = -INFINITY;
-                }
-        }
-        float tmax = st[0][0];
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) tmax = fmaxf(tmax, st[kt][e]);
-        tmax = att_pair_max(tmax);
-        const float m_new = fmaxf(m_run, tmax);            // finite: every stage holds >= 1 valid key
-        const float ms = m_new * scale2;
-        float psum = 0.f;
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(st[kt][e], scale2, -ms));
-                st[kt][e] = p;
-                psum += p;
-            }
-        if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {      // some query of this wave moved its max
-            const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale2);
-            l_run *= alpha;
-#pragma unroll
-            for (int t = 0; t < DT; ++t)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) ot[t][e] *= alpha;
-        }
-        l_run += psum;                               // per-lane partial; the two halves meet after the last tile
-        m_run = m_new;
-        __builtin_amdgcn_sched_barrier(0);
-        read_v(1);
-        __builtin_amdgcn_sched_barrier(0);
-        // O^T += V^T P^T
-        __builtin_amdgcn_s_setprio(3);
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                bf16x8 pf;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) pf[j] = (__bf16)st[kt][hh * 8 + j];
-#pragma unroll
-                for (int t = 0; t < DT; ++t) {
-                    const att_short4 va = vf[kt][hh][t][0], vb2 = vf[kt][hh][t][1];
-                    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short att_short8;
-                    const att_short8 v8 = __builtin_shufflevector(va, vb2, 0, 1, 2, 3, 4, 5, 6, 7);
-                    ot[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v8), pf, ot[t], 0, 0, 0);
-                }
-            }
-        __builtin_amdgcn_s_setprio(0);
-    };
-    // The query fragments must have arrived before the first direct load is issued: otherwise the
-    // compiler's own wait for them would sit inside the loop, where it would also wait for the direct
-    // loads of the next stage.
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) asm volatile("" :: "v"(qf[kk]));
-    issue(0, 0);
-    for (int it = 0; it < ntile; it += 2) {
-        tile(std::integral_constant<int, 0>{}, it);
-        if (it + 1 < ntile) tile(std::integral_constant<int, 1>{}, it + 1);
-    }
-    l_run = att_pair_sum(l_run);
-    if (!qvalid) return;
-    const float inv = 1.0f / l_run;
-    uint16_t* op = o + (size_t)(tok0 + qrow) * rs + (size_t)h * DH;
-#pragma unroll
-    for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-            uint2 w;
-            w.x = pack_bf16x2(ot[t][e4 * 4 + 0] * inv, ot[t][e4 * 4 + 1] * inv);
-            w.y = pack_bf16x2(ot[t][e4 * 4 + 2] * inv, ot[t][e4 * 4 + 3] * inv);
-            *reinterpret_cast<uint2*>(op + t * 32 + e4 * 8 + g * 4) = w;
-        }
-#endif
-}
 // ---- short sequences: the keys are split across the four waves -------------------------------------
 // With a few hundred keys the kernel above is one short serial chain per workgroup (8 stages at 493 keys)
 // on half of the CUs.  Here a workgroup owns 32 queries of one head and its four waves take the 32-key
@@ -980,7 +752,7 @@ __global__ __launch_bounds__(256) void attend_generic_kernel(
 using namespace d3tom;
 
 static int attend_any(const void* q, const void* k, const void* v, int dt, int B, const int32_t* cu_seqlens, int max_seqlen, int H, int dh,
-                      float scale, const int32_t* counts, const int32_t* kept_off, const int32_t* vis_start, bool online, void* o, void* stream) {
+                      float scale, const int32_t* counts, const int32_t* kept_off, const int32_t* vis_start, void* o, void* stream) {
     if (!q || !k || !v || !o || !cu_seqlens) return D3TOM_ERR_INVALID_ARG;
     if (B < 1 || max_seqlen < 1 || H < 1 || dh < 1) return D3TOM_ERR_INVALID_ARG;
     if (!(scale > 0.f) || !(scale < 3.0e38f)) return D3TOM_ERR_INVALID_ARG;      // the running max is taken on raw logits
@@ -1016,18 +788,6 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
                                                            cu_seqlens, H, B, nqt, scale2, (uint16_t*)o, kw)))
         if (dh == 128) { if (wgt) D3TOM_ATT((attend_bf16_short_kernel<128, true>)); else D3TOM_ATT((attend_bf16_short_kernel<128, false>)); }
         else           { if (wgt) D3TOM_ATT((attend_bf16_short_kernel<64, true>));  else D3TOM_ATT((attend_bf16_short_kernel<64, false>)); }
-    } else if (mfma && online) {
-        const int nqt = ceil_div(max_seqlen, ATO_BQ);
-        const dim3 g((unsigned)(8 * ceil_div(H * B, 8) * nqt));
-        const size_t lds = (size_t)ATO_NS * 2 * ATT_BK * dh * 2;
-        const int threads = 256;
-        static PerDeviceOnce lds_setup;
-        if (!lds_setup.run([] {
-                return raise_dynamic_lds(attend_bf16_online_kernel<128>, ATO_NS * 2 * ATT_BK * 128 * 2) &&
-                       raise_dynamic_lds(attend_bf16_online_kernel<64>, ATO_NS * 2 * ATT_BK * 64 * 2);
-            }))
-            return D3TOM_ERR_DEVICE;
-        if (dh == 128) D3TOM_ATT((attend_bf16_online_kernel<128>)); else D3TOM_ATT((attend_bf16_online_kernel<64>));
     } else if (mfma) {
         // Rounds of workgroups over the 256 compute units.  A round of 128-query tiles costs 0.61 to 0.66 of one of 256-query tiles
         // (every fragment read from LDS feeds one MFMA instead of two; 32 heads, narrow against wide: 1198 keys 45.6 us against
@@ -1067,19 +827,11 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
     return D3TOM_OK;
 }
 
-namespace d3tom {
-// the stack's entry: `online` keeps the running maximum
-int attend_run(const void* q, const void* k, const void* v, int B, const int32_t* cu_seqlens, int max_seqlen, int H, int dh, float scale,
-               bool online, void* o, hipStream_t st) {
-    return attend_any(q, k, v, D3TOM_BF16, B, cu_seqlens, max_seqlen, H, dh, scale, nullptr, nullptr, nullptr, online, o, st);
-}
-}  // namespace d3tom
-
 extern "C" int d3tom_attend(const void* q, const void* k, const void* v, int dt,
                             int B, const int32_t* cu_seqlens, int max_seqlen, int H, int dh, float scale,
                             void* o, void* ws, size_t ws_bytes, void* stream) {
     (void)ws; (void)ws_bytes;
-    return attend_any(q, k, v, dt, B, cu_seqlens, max_seqlen, H, dh, scale, nullptr, nullptr, nullptr, false, o, stream);
+    return attend_any(q, k, v, dt, B, cu_seqlens, max_seqlen, H, dh, scale, nullptr, nullptr, nullptr, o, stream);
 }
 
 extern "C" int d3tom_attend_weighted(const void* q, const void* k, const void* v, int dt,
@@ -1088,5 +840,5 @@ extern "C" int d3tom_attend_weighted(const void* q, const void* k, const void* v
                                      void* o, void* ws, size_t ws_bytes, void* stream) {
     (void)ws; (void)ws_bytes;
     if (!counts || !kept_off || !vis_start) return D3TOM_ERR_INVALID_ARG;
-    return attend_any(q, k, v, dt, B, cu_seqlens, max_seqlen, H, dh, scale, counts, kept_off, vis_start, false, o, stream);
+    return attend_any(q, k, v, dt, B, cu_seqlens, max_seqlen, H, dh, scale, counts, kept_off, vis_start, o, stream);
 }

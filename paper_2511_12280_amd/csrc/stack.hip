@@ -8,8 +8,6 @@ namespace d3tom {
 int linear_run(const void* a, const void* w, int M, int N, int K, int epilogue, const void* residual, void* out,
                int out_chunk, int tile, hipStream_t st, const float2* rope_cs = nullptr, int rope_dh = 0);
 int rope_table_run(const int32_t* pos, int rows, int dh, float theta, float2* table, hipStream_t st);
-int attend_run(const void* q, const void* k, const void* v, int B, const int32_t* cu_seqlens, int max_seqlen, int H, int dh, float scale,
-               bool online, void* o, hipStream_t st);
 int rmsnorm_run(const void* x, const void* gain, int rows, int d, float eps, void* y, hipStream_t st);
 int rope_run(void* q, void* k, const int32_t* pos, int rows, int H, int dh, float theta, hipStream_t st);
 int linear_split_plan(int M, int N, int K, size_t max_floats, int* cfg);
@@ -211,10 +209,7 @@ extern "C" int d3tom_stack_step_batch(const void* x, int B, const int32_t* N_h, 
         void* vv = (char*)qkv + (size_t)2 * n * d * 2;
         // the rotation of q and k happens in the projection's epilogue
         D3TOM_TRY(linear_run(nrm, b.w_qkv, n, 3 * d, d, LIN_PLAIN, nullptr, qkv, d, 0, st, rope_cs, dh));
-        // up to the merge the probabilities are rounded against the running maximum: that rounding is part of the hidden states whose
-        // cosines decide which of several near-duplicates a token is merged into (also in the steps that merge nothing: those
-        // are the unmerged model to the bit)
-        D3TOM_TRY(attend_run(qq, kk, vv, B, cu, longest, H, dh, scale, layer_ok && l <= merge_layer, att, st));
+        D3TOM_TRY(d3tom_attend(qq, kk, vv, D3TOM_BF16, B, cu, longest, H, dh, scale, att, nullptr, 0, st));
         // post-attention hidden state = residual + attention output projection; in place, except that the
         // caller's input is never written
         void* post = (cur == x) ? h : const_cast<void*>(cur);

@@ -375,6 +375,16 @@ def test_stack_step_without_deciders_runs_full_length(B):
     np.testing.assert_array_equal(off["y"], got["y"])
 
 
+@pytest.mark.parametrize("V", [450, 520, 1300])
+def test_spellings_of_the_unmerged_model_agree(B, V):
+    """No deciders, a merge layer outside 1 .. L and every token kept are one model, bit for bit, on both sides of the length up to
+    which attention runs on its short-sample kernel (512 tokens)."""
+    case = W.stack_case(81, L=2, d=256, H=2, F=320, P=8, V=V, O=12, D=3, std=1.0 / 16, gain_jitter=0.1)
+    plain = _run_stack(B, case, 10, 0, D=0)
+    for got in (_run_stack(B, case, 10, 2, D=0), _run_stack(B, case, 10, 1, D=0), _run_stack(B, case, 10, 0), _run_stack(B, case, V, 1)):
+        np.testing.assert_array_equal(got["y"], plain["y"])
+
+
 def test_stack_step_sum_mode(B):
     case = W.stack_case(78, L=2, d=256, H=4, F=512, P=8, V=120, O=12, D=6, std=1.0 / 16, gain_jitter=0.1)
     got = _run_stack(B, case, 30, 1, mode=1)
