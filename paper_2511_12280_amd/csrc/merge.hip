@@ -805,7 +805,9 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
                    raise_dynamic_lds(cos_argmax_bf16<1, 3, false>, cos_ring_stages(1) * (64 + 96) * 128) &&
                    raise_dynamic_lds(cos_argmax_bf16<2, 4, false>, cos_ring_stages(2) * (128 + 128) * 128) &&
                    raise_dynamic_lds(cos_argmax_bf16<2, 3, false>, cos_ring_stages(2) * (128 + 96) * 128) &&
-                   raise_dynamic_lds(cos_argmax_bf16<4, 4, false>, cos_ring_stages(4) * (256 + 128) * 128);
+                   raise_dynamic_lds(cos_argmax_bf16<4, 4, false>, cos_ring_stages(4) * (256 + 128) * 128) &&
+                   // the norms of every kept slot: above 16376 of them more than 64 KB with the kernel's own array
+                   raise_dynamic_lds(cos_reduce_argmax<true, 4>, D3TOM_MAX_VISUAL * (int)sizeof(float));
         }))
         return D3TOM_ERR_DEVICE;
 

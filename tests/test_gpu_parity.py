@@ -427,6 +427,18 @@ def test_merge_split_contraction_waves_per_row(shapes):
         check_full_sample(ref, b, S1, kept1, slot, m1)
 
 
+@pytest.mark.parametrize("pruned", [1, 4, 64])
+def test_merge_largest_kept_set_with_split_contraction(pruned):
+    """Almost all of the largest supported number of visual tokens kept: few rows against 16320 to 16383 slots are cut along the
+    contraction, and the step behind it holds the norms of all slots in LDS (above 16376 of them more than 64 KB)."""
+    V = B.D3TOM_MAX_VISUAL
+    c = W.random_case(530 + pruned, 3 + V + 2, 512, 4, 3, V, 2, dtype="bf16", centres=V // 3)
+    kept = np.delete(np.arange(V), np.linspace(0, V - 1, pruned).astype(int)).astype(np.int32)
+    out = GpuStep([c], [V - pruned], "bf16").merge([kept])
+    check_assign(out["assign"][0], c["x"], 3, V, kept)
+    check_merge({key: out[key][0] for key in out}, c["x"], 3, V, kept, "bf16")
+
+
 @pytest.mark.parametrize("d_sim", [128, 72])          # MFMA cosine path (a multiple of 64) and the generic one
 def test_merge_layer_one_call_with_separate_similarity_features(d_sim):
     """`sim` != x in the one-call merge layer: the selection launch takes its row norms from `sim` (other row length
