@@ -21,7 +21,8 @@ size_t importance_ws_bytes(int B, int max_N, int max_V, int H, int dh, int max_D
 // Sum of squares of one row of d elements (bf16 or float32, 16-byte aligned, d a multiple of the elements per 16
 // bytes), computed by one wave: lane-strided 16-byte chunks, eight loads in flight per lane, elements added in
 // storage order inside a lane, lanes combined by wave_sum.  Every lane returns the total.  One definition, so that
-// every kernel that needs a row norm gets the same bits.
+// every launch that leaves norms for a cosine kernel leaves the same bits.  (A split contraction takes its norms from its own slices
+// instead, in the one-call merge layer too: which of two near-equal cosines wins must not depend on how the merge is called.)
 template <typename T>
 __device__ __forceinline__ float row_sum_squares(const T* __restrict__ row, int d, int lane) {
 #if defined(__HIP_DEVICE_COMPILE__)

@@ -135,16 +135,18 @@ __global__ __launch_bounds__(256) void merge_norms_kernel(
 // Measured at d = 4096: 1822 x 1823 rows 37.9 -> 31.8 us, 2733 x 912 32.4 -> 28.5, 16 samples of 2304 rows 195 -> 167.
 constexpr int cos_ring_stages(int TM) { return TM >= 4 ? 3 : 4; }     // 256-row tiles: 3 stages of 48 KB fit the 160 KB of LDS
 
-// BARE (split contraction, no preparing launch): the kernel derives the pruned tokens from the kept list itself, writes the pruned
-// list and the kept tokens' table entries for the kernels behind it, and its workgroups of row tile 0 sum the squares of their
-// kept rows (the diagonal of B B^T, two MFMAs per block of 16 rows and stage where the load path leaves the matrix core idle):
-// no norms launch (4 of the 21 us that a merge of 356 tokens takes).
-template <int TM, int CBK, bool BARE>     // CBK: 16-column blocks of a wave
+// SPLIT (contraction cut into ksplit > 1 slices): the workgroups of row tile 0 sum the squares of their kept rows (the diagonal of
+// B B^T, two MFMAs per block of 16 rows and stage where the load path leaves the matrix core idle), and without a preparing launch
+// the kernel derives the pruned tokens from the kept list itself and writes the pruned list and the kept tokens' table entries
+// for the kernels behind it: no norms launch (4 of the 21 us that a merge of 356 tokens takes).  The norms are summed here whether
+// or not the selection launch has left others: near-ties of two cosines go by their last bits, and the one call and the
+// separate calls have to agree.
+template <int TM, int CBK, bool SPLIT>     // CBK: 16-column blocks of a wave
 __global__ __launch_bounds__(512) void cos_argmax_bf16(
     const uint16_t* __restrict__ f, int d, const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_start,
     const int32_t* __restrict__ vis_count, const int32_t* __restrict__ kept_idx, const int32_t* __restrict__ kept_off,
     int max_V, int max_keep, int32_t* __restrict__ pruned, const float* __restrict__ rnorm,
-    table_t* __restrict__ table, int VP, int per, int RB, int ksplit, float* __restrict__ dots, int nrt_launch, int nct_launch, int rn_by_token,
+    table_t* __restrict__ table, int VP, int per, int RB, int ksplit, float* __restrict__ dots, int nrt_launch, int nct_launch, int prepared,
     int nB, int NG, float* __restrict__ sq) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = TM * 64, BN = CBK * 32;
@@ -168,7 +170,8 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     const SampleGeom s = sample_geom(b, seq_off, vis_start, vis_count, kept_off, max_V, max_keep);
     const int nrt_b = min((s.M + BM - 1) / BM, nrt_launch), nct_b = min((s.k + BN - 1) / BN, nct_launch);
     const int tiles_b = nrt_b * nct_b;
-    if constexpr (BARE) {
+    const bool derive = SPLIT && !prepared;                // uniform
+    if (derive) {
         // a sample that keeps everything has no tiles: its table entries are written here
         if (s.M <= 0 && id == 0 && xcd % XG == 0 && blockIdx.y == 0)
             for (int r = threadIdx.x; r < s.k; r += 512)
@@ -203,7 +206,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     // re-read row 0; masked later); the k-slice is added through the scalar offset
     const __amdgpu_buffer_rsrc_t rsrc = make_uniform_rsrc(f + base, (uint32_t)((size_t)s.V * d * sizeof(uint16_t)));
     int a_off[A_LD], b_off[B_LD];
-    if constexpr (BARE) {
+    if (derive) {
         // the p-th pruned token is p + the number r of kept tokens in front of it: the first r with kept[r] - r > p
         int* kl = reinterpret_cast<int*>(ring);
         for (int t = tid; t < s.k; t += 512) kl[t] = min(max(kp[t], 0), s.V - 1);
@@ -226,13 +229,13 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         __syncthreads();                                   // the ring is free for the tiles
     } else {
 #pragma unroll
-    for (int i = 0; i < A_LD; ++i) {
-        const int row = wave * (BM / 4) + i * 8 + (lane >> 3);
-        const int cg = (lane & 7) ^ ((row >> 1) & 7);
-        const int p = rt * BM + row;
-        const int m = min(max((p < s.M) ? pr[p] : pr[0], 0), s.V - 1);
-        a_off[i] = m * d * 2 + cg * 16;
-    }
+        for (int i = 0; i < A_LD; ++i) {
+            const int row = wave * (BM / 4) + i * 8 + (lane >> 3);
+            const int cg = (lane & 7) ^ ((row >> 1) & 7);
+            const int p = rt * BM + row;
+            const int m = min(max((p < s.M) ? pr[p] : pr[0], 0), s.V - 1);
+            a_off[i] = m * d * 2 + cg * 16;
+        }
     }
 #pragma unroll
     for (int i = 0; i < B_LD; ++i) {
@@ -242,14 +245,14 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         const int j = min(max(kp[(r < s.k) ? r : 0], 0), s.V - 1);
         b_off[i] = j * d * 2 + cg * 16;
     }
-    if constexpr (!BARE)
-    for (int t = tid; t < BN; t += 512) {
-        const int r = ct * BN + t;
-        // 1 / norm of the kept row in slot r: stored by slot, or by token when the selection launch computed them
-        rnB[t] = (r < s.k) ? rn[rn_by_token ? min(max(kp[r], 0), s.V - 1) : r] : 0.f;
-    }
-    // split-K: slice blockIdx.y of the contraction (ksplit slices of nkt stages each)
-    const int nkt = (d / COS_BK) / ksplit;
+    if constexpr (!SPLIT)
+        for (int t = tid; t < BN; t += 512) {
+            const int r = ct * BN + t;
+            // 1 / norm of the kept row in slot r: stored by slot, or by token when the selection launch computed them
+            rnB[t] = (r < s.k) ? rn[prepared ? min(max(kp[r], 0), s.V - 1) : r] : 0.f;
+        }
+    // slice blockIdx.y of the contraction (ksplit slices of nkt stages each)
+    const int nkt = SPLIT ? (d / COS_BK) / ksplit : d / COS_BK;
     const int kt0 = (int)blockIdx.y * nkt;
     // LDS destinations are wave-uniform: this wave's first row of the A (B) tile, made a scalar once so
     // that a load costs one scalar add for its M0 value and no vector instruction
@@ -277,10 +280,10 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     for (int i = 0; i < RBK; ++i)
 #pragma unroll
         for (int j = 0; j < CBK; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    f32x4 bb[BARE ? CBK : 1];                           // BARE: B B^T of each column block
+    f32x4 bb[SPLIT ? CBK : 1];                           // SPLIT: B B^T of each column block
 #pragma unroll
-    for (int j = 0; j < (BARE ? CBK : 1); ++j) bb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const bool squares = BARE && rt == 0 && wm == 0;    // uniform
+    for (int j = 0; j < (SPLIT ? CBK : 1); ++j) bb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const bool squares = SPLIT && rt == 0 && wm == 0;    // uniform
 
     // A wave that issues a direct load waits for room in the CU's vector-memory queue; in a computing wave
     // that wait stalls the MFMA stream, so the loads have waves of their own.  One s_barrier per stage:
@@ -319,7 +322,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
             }
             if (squares) {
 #pragma unroll
-                for (int j = 0; j < (BARE ? CBK : 0); ++j) bb[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[ks][RBK + j], fr[ks][RBK + j], bb[j], 0, 0, 0);
+                for (int j = 0; j < (SPLIT ? CBK : 0); ++j) bb[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[ks][RBK + j], fr[ks][RBK + j], bb[j], 0, 0, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
         };
@@ -339,7 +342,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         multiply(1, nullptr, false);
     }
 
-    if (ksplit > 1) {
+    if constexpr (SPLIT) {
         // partial products of this k-slice: block (slice, tile) of BM x 128 floats, summed by cos_reduce_argmax
         const int tile_id = (b * nrt_launch + rt) * nct_launch + ct;
         const int n_tiles = nB * nrt_launch * nct_launch;
@@ -348,7 +351,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         if (squares && (r16 >> 2) == g4) {
             float* sb = sq + (((size_t)blockIdx.y * nB + b) * nct_launch + ct) * 128 + wn * (BN / 2) + r16;
 #pragma unroll
-            for (int j = 0; j < (BARE ? CBK : 0); ++j) {
+            for (int j = 0; j < (SPLIT ? CBK : 0); ++j) {
                 const f32x4 v = bb[j];
                 sb[j * 16] = (r16 & 2) ? ((r16 & 1) ? v[3] : v[2]) : ((r16 & 1) ? v[1] : v[0]);
             }
@@ -424,17 +427,16 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
 // the tile, the norms) are requested together: without a branch around any of them, since each branch costs a wait and some tens
 // of cycles.  (One wave per row, loads under conditions: 1400 rows x 600 slots x 2 slices 14.0 us, now 6.2; 486 x 243 x 4 slices
 // 6.8 us, now 3.8; 921 x 103 x 16 4.5 us, now 3.9.)
-template <bool BARE, int wpr>     // BARE: the norms come from the k-slices' sums of squares (else from rnorm, by token)
+template <int wpr>
 __global__ __launch_bounds__(256) void cos_reduce_argmax(
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count,
     const int32_t* __restrict__ kept_off,
-    int max_V, int max_keep, const int32_t* __restrict__ pruned, const float* __restrict__ rnorm,
+    int max_V, int max_keep, const int32_t* __restrict__ pruned,
     const float* __restrict__ dots, int ksplit, int n_tiles, int nrt_launch, int nct_launch,
-    table_t* __restrict__ table, int VP, const int32_t* __restrict__ kept_idx,
-    const float* __restrict__ sq, int nB) {
+    table_t* __restrict__ table, int VP, const float* __restrict__ sq, int nB) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = 64;
-    extern __shared__ float rn_s[];             // BARE: [kept slots] 1 / norm
+    extern __shared__ float rn_s[];             // [kept slots] 1 / norm, from the k-slices' sums of squares
     __shared__ float2 join[4];
     const int b = blockIdx.y;
     const SampleGeom s = sample_geom(b, seq_off, vis_start, vis_count, kept_off, max_V, max_keep);
@@ -442,47 +444,35 @@ __global__ __launch_bounds__(256) void cos_reduce_argmax(
     constexpr int rows = 4 / wpr;
     const int p = blockIdx.x * rows + wave / wpr, part = wave % wpr;
     if (s.k <= 0 || (int)blockIdx.x * rows >= s.M) return;
-    const float* rn = rnorm + (size_t)b * max_V;
     const int rt = p / BM, lr = p % BM;
     const int nct = (p < s.M) ? (s.k + COS_BN - 1) / COS_BN : 0;
     // Loads without branches: slices beyond the launch's, and tiles beyond the sample's, lie outside the buffer and read as 0
     // (columns beyond the sample's slots hold whatever the tile held; they are not looked at).
     const uint32_t slice = (uint32_t)n_tiles * (BM * COS_BN * 4);
     const __amdgpu_buffer_rsrc_t dots_r = make_uniform_rsrc(dots, (uint32_t)ksplit * slice);
-    float v[2][16], rnv[2];
+    float v[2][16];
     auto request = [&](int ct) {
         const uint32_t tile_id = (uint32_t)((b * nrt_launch + rt) * nct_launch + ct);
         const uint32_t at = ct < nct ? (tile_id * BM + lr) * (COS_BN * 4) + lane * 4 : 0xC0000000u;
-        int tok_at[2];
-        if constexpr (!BARE) {
-#pragma unroll
-            for (int half = 0; half < 2; ++half) tok_at[half] = kept_idx[s.k0 + min(ct * COS_BN + half * 64 + lane, s.k - 1)];
-        }
 #pragma unroll
         for (int half = 0; half < 2; ++half)
 #pragma unroll
             for (int ks = 0; ks < 16; ++ks)
                 v[half][ks] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dots_r, at + ks * slice + half * 256, 0, 0));
-        if constexpr (!BARE) {
-#pragma unroll
-            for (int half = 0; half < 2; ++half) rnv[half] = rn[min(max(tok_at[half], 0), s.V - 1)];
-        }
     };
     request(part);
     const int tok = (p < s.M) ? min(max(pruned[(size_t)b * max_V + p], 0), s.V - 1) : 0;
-    if constexpr (BARE) {
-        const __amdgpu_buffer_rsrc_t sq_r = make_uniform_rsrc(sq, (uint32_t)(ksplit * nB * nct_launch) * 512u);
-        for (int t = threadIdx.x; t < s.k; t += 256) {
-            float sl[16], ss = 0.f;
+    const __amdgpu_buffer_rsrc_t sq_r = make_uniform_rsrc(sq, (uint32_t)(ksplit * nB * nct_launch) * 512u);
+    for (int t = threadIdx.x; t < s.k; t += 256) {
+        float sl[16], ss = 0.f;
 #pragma unroll
-            for (int ks = 0; ks < 16; ++ks)
-                sl[ks] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sq_r, (((ks * nB + b) * nct_launch + t / COS_BN) * 128 + t % COS_BN) * 4, 0, 0));
+        for (int ks = 0; ks < 16; ++ks)
+            sl[ks] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sq_r, (((ks * nB + b) * nct_launch + t / COS_BN) * 128 + t % COS_BN) * 4, 0, 0));
 #pragma unroll
-            for (int ks = 0; ks < 16; ++ks) ss += sl[ks];
-            rn_s[t] = reciprocal_norm(ss);
-        }
-        __syncthreads();
+        for (int ks = 0; ks < 16; ++ks) ss += sl[ks];
+        rn_s[t] = reciprocal_norm(ss);
     }
+    __syncthreads();
     float best = -INFINITY; int bidx = 0x7FFFFFFF;
     for (int ct = part; ct < nct; ct += wpr) {
         if (ct != part) request(ct);
@@ -493,7 +483,7 @@ __global__ __launch_bounds__(256) void cos_reduce_argmax(
                 float sum = 0.f;
 #pragma unroll
                 for (int ks = 0; ks < 16; ++ks) sum += v[half][ks];        // ascending slices; absent ones add 0
-                const float val = sum * (BARE ? rn_s[slot] : rnv[half]);
+                const float val = sum * rn_s[slot];
                 if (val > best) { best = val; bidx = slot; }
             }
         }
@@ -807,7 +797,7 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
                    raise_dynamic_lds(cos_argmax_bf16<2, 3, false>, cos_ring_stages(2) * (128 + 96) * 128) &&
                    raise_dynamic_lds(cos_argmax_bf16<4, 4, false>, cos_ring_stages(4) * (256 + 128) * 128) &&
                    // the norms of every kept slot: above 16376 of them more than 64 KB with the kernel's own array
-                   raise_dynamic_lds(cos_reduce_argmax<true, 4>, D3TOM_MAX_VISUAL * (int)sizeof(float));
+                   raise_dynamic_lds(cos_reduce_argmax<4>, D3TOM_MAX_VISUAL * (int)sizeof(float));
         }))
         return D3TOM_ERR_DEVICE;
 
@@ -829,12 +819,10 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
             }
         }
     }
-    // a split contraction computes the norms and the list itself
-    const bool bare = ksplit > 1 && !prepared;
     // prepared: the selection launch has left 1 / norm of every visual row (by token), the pruned list and the
-    // initial table in the workspace
+    // initial table in the workspace; a split contraction computes the norms itself, and without that launch the list as well
     const dim3 gn(ceil_div(max_keep, 4), B);
-    if (prepared || bare) {
+    if (prepared || ksplit > 1) {
     } else if (dt == D3TOM_BF16)
         D3TOM_LAUNCH(MERGE_NORMS, st, merge_norms_kernel<uint16_t><<<gn, 256, 0, st>>>(
             (const uint16_t*)sim, d_sim, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep, rnorm, pruned,
@@ -866,27 +854,23 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
         float* dots = (float*)(wsb + w.dots_off);
         float* sq = (float*)(wsb + w.sq_off);
         const size_t lds = (size_t)cos_ring_stages(TM) * (BM + (narrow ? 96 : COS_BN)) * 128;
-        const int by_token = prepared ? 1 : 0;
-#define D3TOM_COS(TMV, CBKV, BAREV)                                                                                         \
-    D3TOM_LAUNCH(COS_ARGMAX, st, (cos_argmax_bf16<TMV, CBKV, BAREV><<<g, 512, lds, st>>>(                                      \
+#define D3TOM_COS(TMV, CBKV, SPLITV)                                                                                        \
+    D3TOM_LAUNCH(COS_ARGMAX, st, (cos_argmax_bf16<TMV, CBKV, SPLITV><<<g, 512, lds, st>>>(                                     \
         (const uint16_t*)sim, d_sim, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep, pruned, rnorm, table, \
-        w.VP, per, RB, ksplit, dots, nrt, nct, by_token, B, NG, sq)))
+        w.VP, per, RB, ksplit, dots, nrt, nct, prepared ? 1 : 0, B, NG, sq)))
         if (TM == 4) D3TOM_COS(4, 4, false);
         else if (TM == 2) { if (narrow) D3TOM_COS(2, 3, false); else D3TOM_COS(2, 4, false); }
-        else if (bare) D3TOM_COS(1, 4, true);
+        else if (ksplit > 1) D3TOM_COS(1, 4, true);
         else { if (narrow) D3TOM_COS(1, 3, false); else D3TOM_COS(1, 4, false); }
 #undef D3TOM_COS
         if (ksplit > 1) {
             const int wpr = nct >= 3 ? 4 : nct;            // waves per pruned row: one column tile each, as far as four go
             const dim3 gr(ceil_div(max_pruned, 4 / wpr), B);
-#define D3TOM_REDUCE(BAREV, WPRV, LDS)                                                                                  \
-    D3TOM_LAUNCH(COS_REDUCE, st, (cos_reduce_argmax<BAREV, WPRV><<<gr, 256, LDS, st>>>(                                 \
-        seq_off, vis_start, vis_count, kept_off, max_V, max_keep, pruned, rnorm, dots, ksplit, nrt * nct * B, nrt, nct, \
-        table, w.VP, kept_idx, sq, B)))
-#define D3TOM_REDUCE_WPR(BAREV, LDS)                                                                                    \
-    do { if (wpr == 1) D3TOM_REDUCE(BAREV, 1, LDS); else if (wpr == 2) D3TOM_REDUCE(BAREV, 2, LDS); else D3TOM_REDUCE(BAREV, 4, LDS); } while (0)
-            if (bare) D3TOM_REDUCE_WPR(true, (size_t)max_keep * sizeof(float)); else D3TOM_REDUCE_WPR(false, 0);
-#undef D3TOM_REDUCE_WPR
+#define D3TOM_REDUCE(WPRV)                                                                                              \
+    D3TOM_LAUNCH(COS_REDUCE, st, (cos_reduce_argmax<WPRV><<<gr, 256, (size_t)max_keep * sizeof(float), st>>>(           \
+        seq_off, vis_start, vis_count, kept_off, max_V, max_keep, pruned, dots, ksplit, nrt * nct * B, nrt, nct,        \
+        table, w.VP, sq, B)))
+            if (wpr == 1) D3TOM_REDUCE(1); else if (wpr == 2) D3TOM_REDUCE(2); else D3TOM_REDUCE(4);
 #undef D3TOM_REDUCE
         }
     } else if (max_pruned > 0) {

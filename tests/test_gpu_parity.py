@@ -416,7 +416,7 @@ def test_merge_layer_one_call_on_every_kernel_path(dtype, d, H, shapes):
 ])
 def test_merge_split_contraction_waves_per_row(shapes):
     """Cosines cut along the contraction: kept counts around multiples of the 128-slot tiles and of four tiles (one per wave of a
-    pruned row), both through the one call and through the separate ones (their norms differ in the last bit)."""
+    pruned row), both through the one call and through the separate ones."""
     samples = [W.random_case(520 + i, P + V + O, 2048, 16, P, V, D, dtype="bf16", centres=max(3, V // 6)) for i, (P, V, O, D, _) in enumerate(shapes)]
     ratios = [r for *_, r in shapes]
     ref = GpuStep(samples, [oracle.keep_count(s["V"], r) for s, r in zip(samples, ratios)], "bf16")
@@ -425,6 +425,36 @@ def test_merge_split_contraction_waves_per_row(shapes):
     for b in range(len(samples)):
         check_full_sample(ref, b, S, kept, slot, mout)
         check_full_sample(ref, b, S1, kept1, slot, m1)
+
+
+@pytest.mark.parametrize("dtype,d,H,V,k", [
+    ("bf16", 4096, 32, 300, 100),         # contraction cut in 16
+    ("bf16", 2048, 16, 700, 513),         # cut in 2, five column tiles
+    ("bf16", 512, 4, 2400, 1000),         # not cut
+    ("bf16", 200, 5, 300, 100),           # generic kernels
+    ("f32", 256, 4, 300, 100),
+])
+def test_merge_layer_one_call_breaks_ties_like_the_separate_calls(dtype, d, H, V, k):
+    """Kept rows that are the same up to the order of the elements inside blocks, pruned rows constant on such blocks: all
+    cosines of a pruned row are equal, and which slot wins goes by the last bit of dot products and norms (elements of very
+    different size, so that sums in another order round otherwise).  The one call has to decide every one of them as the
+    separate calls do."""
+    P, blk = 5, 40 if d == 200 else 128
+    c = W.random_case(540 + d, P + V + 6, d, H, P, V, 3, dtype=dtype)
+    ref = GpuStep([c], [k], dtype)
+    ref.importance(); kept, slot = ref.select_topk()
+    rng = np.random.default_rng(541)
+    x = c["x"].copy()
+    base = ((1 + rng.random((d // blk, blk))) * 2.0 ** rng.integers(-8, 3, (d // blk, blk))).astype(np.float32)
+    x[P:P + V] = np.repeat(rng.standard_normal((V, d // blk)).astype(np.float32), blk, axis=1)
+    x[P + kept[0]] = np.stack([rng.permuted(base, axis=1).reshape(d) for _ in range(k)])
+    ref.x.copy_(B.to_device(W.round_to(x, dtype), dtype))
+    mout = ref.merge()
+    S1, kept1, m1 = ref.merge_layer([k / V])
+    np.testing.assert_array_equal(kept1[0], kept[0])
+    assert len(np.unique(np.delete(mout["assign"][0], kept[0]))) > 3           # the last bits do decide
+    for key in m1:
+        np.testing.assert_array_equal(m1[key][0], mout[key][0])
 
 
 @pytest.mark.parametrize("pruned", [1, 4, 64])
