@@ -134,8 +134,9 @@ int d3tom_importance(const void* q, const void* k, int dt,
  * hipMalloc / hipFree, no allocating library routine); the first call on a device only looks up
  * the array's device address.
  *
- * Shapes whose workspace (d3tom_workspace_bytes(D3TOM_OP_IMPORTANCE, ...)) exceeds
- * D3TOM_IMPORTANCE_STATIC_BYTES return D3TOM_ERR_UNSUPPORTED before anything is enqueued.  All calls
+ * Shapes that need more than D3TOM_IMPORTANCE_STATIC_BYTES of scratch return D3TOM_ERR_UNSUPPORTED before
+ * anything is enqueued.  (What counts is the need at this max_D; d3tom_workspace_bytes(D3TOM_OP_IMPORTANCE, ...)
+ * can be larger, since its workspace also serves every smaller decider set, and small sets keep their logits.)  All calls
  * on one GPU share that GPU's array, which keeps the previous call's contents (no kernel relies on
  * them): two calls that overlap on one GPU (different streams or threads) race and give
  * unspecified scores; calls on one stream are ordered and safe.

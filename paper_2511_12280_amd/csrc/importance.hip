@@ -34,13 +34,12 @@ constexpr long IMP_MANY = 1024;        // 512-key chunks from which on a launch 
 
 constexpr int IMP_KEEP_MAXD_WS = 32;   // largest decider set whose logits are kept (workspace is sized for it)
 struct ImpWs {
-    size_t part_off, sp_off, cnt_off, c_off, logit_off, total;
+    size_t part_off, sp_off, c_off, logit_off, total;
     int KC, KCS, NCH, NCHV, DPAD, VPAD, NKB;
 };
-__host__ inline ImpWs imp_ws_layout(int B, int max_N, int max_V, int H, int max_D) {
+__host__ inline ImpWs imp_ws_layout(int B, int max_N, int max_V, int H, int max_D, bool many) {
     ImpWs w;
     const long chunks = (long)ceil_div(max_N, IMP_KC_STATS) * H * B;
-    const bool many = chunks >= IMP_MANY && max_D > IMP_KEEP_MAXD_WS;
     w.KC = many ? IMP_KC_MANY : chunks < 256 ? IMP_KC_STATS / 2 : IMP_KC_STATS;       // keys per chunk of the first sweep
     w.KCS = many ? IMP_KC_MANY : 256;                                                 // ... of the second
     w.NCH = ceil_div(max_N, w.KC);
@@ -50,13 +49,21 @@ __host__ inline ImpWs imp_ws_layout(int B, int max_N, int max_V, int H, int max_
     size_t o = 0;
     w.part_off = o; o += align_up((size_t)B * H * w.NCH * w.DPAD * sizeof(float2), 256);
     w.sp_off = o;   o += align_up((size_t)B * H * w.VPAD * sizeof(float), 256);
-    w.cnt_off = o;  o += align_up((size_t)B * w.NCHV * sizeof(int), 256);
     w.c_off = o;    o += align_up((size_t)B * H * max_D * sizeof(float), 256);   // generic path
     w.NKB = w.NCH * (w.KC / 16);
     w.logit_off = o;                                                              // kept logits (small decider sets)
     if (max_D <= IMP_KEEP_MAXD_WS) o += align_up((size_t)B * w.NKB * H * max_D * 16 * sizeof(float), 256);
     w.total = o;
     return w;
+}
+// Smaller chunks mean more statistics (a third more): not where only they would push the layout out of the library's static array.
+// Both entry points follow this rule, so that their scores are the same bits.
+__host__ inline ImpWs imp_ws_layout(int B, int max_N, int max_V, int H, int max_D) {
+    const ImpWs w = imp_ws_layout(B, max_N, max_V, H, max_D, false);
+    if ((long)ceil_div(max_N, IMP_KC_STATS) * H * B < IMP_MANY || max_D <= IMP_KEEP_MAXD_WS) return w;
+    const ImpWs m = imp_ws_layout(B, max_N, max_V, H, max_D, true);
+    const size_t lim = D3TOM_IMPORTANCE_STATIC_BYTES;
+    return (m.total > lim && w.total <= lim) ? w : m;
 }
 size_t importance_ws_bytes(int B, int max_N, int max_V, int H, int dh, int max_D) {
     (void)dh;

@@ -55,3 +55,24 @@ def test_static_scratch_entry_point_rejects_what_does_not_fit():
         B.d3tom_importance_static(q, q, lay, 0.1, scores)
     assert e.value.status == B.D3TOM_ERR_UNSUPPORTED
     torch.cuda.synchronize()
+
+
+def test_static_scratch_entry_point_takes_large_batches_of_long_samples():
+    """A batch whose statistics fit the static array in chunks of 512 keys but not in the chunks of 384 that large launches prefer:
+    accepted, with the bits of the workspace entry point, and right (the short sample against the oracle)."""
+    import oracle
+    from parity import check_scores
+    H, dh, D, lens = 32, 64, 256, [520] + [8192] * 7
+    V = [256] + [7000] * 7
+    small = W.random_case(63, 520, H * dh, H, 0, V[0], D, dtype="bf16")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(64)
+    q, k = (torch.empty((sum(lens), H, dh), dtype=torch.bfloat16, device="cuda").normal_(generator=gen) for _ in range(2))
+    q[:520], k[:520] = B.to_device(small["q"], "bf16"), B.to_device(small["k"], "bf16")
+    lay = B.Layout(lens, [0] * 8, V, [small["dec_idx"]] + [list(range(v, v + D)) for v in V[1:]], [1] * 8)
+    ref, out = (torch.full((sum(V),), -1.0, dtype=torch.float32, device="cuda") for _ in range(2))
+    B.d3tom_importance(q, k, lay, 1.0 / np.sqrt(dh), ref, B.workspace(B.d3tom_workspace_bytes(B.D3TOM_OP_IMPORTANCE, 8, 8192, max(V), H, dh, D)))
+    B.d3tom_importance_static(q, k, lay, 1.0 / np.sqrt(dh), out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref)
+    check_scores(out[:V[0]].cpu().numpy(), oracle.importance(small["q"], small["k"], small["dec_idx"], 0, V[0]))
