@@ -843,9 +843,11 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
         if (narrow) nct = nct96;
         // tiles of a sample in 8 equal runs (one per XCD); bands about as high as a run's block is wide
         // Batches of several rounds: a sample's tiles on two XCDs instead of eight, so that an XCD's L2 serves each operand row to more of
-        // them (16 samples of 2304 rows: 181 us on eight XCDs, 177 on four, 167 on two, 173 on one).  Only where the four pairs
-        // get equal numbers of samples, and enough of them for their sizes to even out.
-        const int NG = (TM == 4 && B >= 12 && B % 4 == 0) ? 4 : 1;
+        // them (16 samples of 2304 rows: 181 us on eight XCDs, 177 on four, 167 on two, 173 on one).  Only where the four pairs get
+        // enough samples for their sizes to even out.  Time of the merge on eight XCDs over that on two, median of 16 draws of sizes
+        // 1152 .. 2304 and keep ratios 0.1 .. 0.5: 8 samples 1.00, 10 1.01, 12 (three a pair) 1.02, 13 1.00 (and 0.95 in the
+        // mean), 14 1.03, 15 1.03, 16 1.04, 17 1.02, 18 1.03, 19 1.06, 22 1.02.
+        const int NG = (TM == 4 && (B == 12 || B >= 14)) ? 4 : 1;
         const int per = ceil_div(nrt * nct, 8 / NG);
         int RB = 1;
         while ((RB + 1) * (RB + 1) <= per) ++RB;

@@ -91,11 +91,11 @@ def test_ragged_batch_bf16():
     np.testing.assert_array_equal(kept[4], np.arange(64))
 
 
-@pytest.mark.parametrize("batch", [12, 13])
+@pytest.mark.parametrize("batch", [12, 13, 14])
 def test_merge_large_batch_tiles(batch):
-    """Batches of several rounds of cosine tiles: samples on pairs of XCDs (a multiple of four samples) and on all of them, sizes
+    """Batches of several rounds of cosine tiles: samples on pairs of XCDs (as many on each, or not) and on all of them, sizes
     from one row over a tile to the largest."""
-    V = [2304, 1, 129, 257, 700, 2303, 64, 1900, 513, 1025, 2048, 300, 1111][:batch]
+    V = [2304, 1, 129, 257, 700, 2303, 64, 1900, 513, 1025, 2048, 300, 1111, 1536][:batch]
     samples = [W.random_case(400 + i, 4 + v + 8, 128, 1, 4, v, 3, dtype="bf16", centres=max(2, v // 6)) for i, v in enumerate(V)]
     keeps = [oracle.keep_count(v, 0.5 if i % 3 == 0 else 0.11) for i, v in enumerate(V)]
     _chain(samples, keeps, "bf16", check=[0, 1, 2, 5, batch - 1])
