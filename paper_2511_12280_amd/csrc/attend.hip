@@ -53,8 +53,6 @@ namespace d3tom {
 constexpr int ATT_BK = 64;      // keys per tile
 constexpr int ATT_SLOTS = 4;    // ring slots of one K tile and one V tile
 
-typedef __attribute__((address_space(3))) void* att_lds_ptr_t;
-typedef const __attribute__((address_space(1))) void* att_glb_ptr_t;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short att_short4;
 
 // 4 keys x 16 dims of a row-major LDS tile, transposed on the way to the registers: within each group
@@ -66,12 +64,6 @@ __device__ __forceinline__ att_short4 lds_read_tr16(const char* p) {
 }
 
 #if defined(__HIP_DEVICE_COMPILE__)
-// buffer resource over [p, p + bytes), built from values the compiler can see are wave-uniform
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t att_uniform_rsrc(const void* p, uint32_t bytes) {
-    const uint64_t a = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-    return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), 0, (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
-}
 // One wave-wide direct load HBM/L2 -> LDS: lane i fetches 16 bytes at byte offset `voff` of the buffer
 // (zeros when that is past the end of the buffer) into LDS byte lds_base + 16 i.  Issued from inline
 // assembly on purpose: the waits for these loads are placed by hand (wait_loads), and the
@@ -158,8 +150,8 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     const uint16_t* vb_ = v + (size_t)tok0 * rs + (size_t)h * DH;
     // this head's K / V rows of this sample; a row index >= n is past the end and loads as zeros
     const uint32_t span = (uint32_t)(((size_t)(n - 1) * rs + DH) * 2);
-    const __amdgpu_buffer_rsrc_t rk = att_uniform_rsrc(kb_, span), rv = att_uniform_rsrc(vb_, span);
-    const __amdgpu_buffer_rsrc_t rq = att_uniform_rsrc(q + (size_t)tok0 * rs + (size_t)h * DH, span);
+    const __amdgpu_buffer_rsrc_t rk = make_uniform_rsrc(kb_, span), rv = make_uniform_rsrc(vb_, span);
+    const __amdgpu_buffer_rsrc_t rq = make_uniform_rsrc(q + (size_t)tok0 * rs + (size_t)h * DH, span);
     const int row_bytes = (int)(rs * 2);
 
     const int q0 = qt * BQ + wave * NQ * 16;                // this wave's first query
@@ -187,7 +179,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
         k_off[i] = x * row_bytes + ((pos ^ (DH == 128 ? (x & 15) : ((x >> 1) & 7))) << 4);
         v_off[i] = x * row_bytes + ((pos ^ (DH == 128 ? (x & 7) << 1 : ((x >> 1) & 3) << 1)) << 4);
     }
-    const uint32_t ring0 = (uint32_t)(size_t)(att_lds_ptr_t)ring;
+    const uint32_t ring0 = (uint32_t)(size_t)(lds_ptr_t)ring;
     const uint32_t wave_lds = ring0 + wave * LD * 1024;
     auto issue_one = [&](int j, int i) {        // one of the 2 LD loads of stage j
         const uint32_t dst = wave_lds + (j % NS) * STAGE + (i >> 1) * 1024;
@@ -413,9 +405,6 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 constexpr int ATS_BK = 32;      // keys per wave tile
 constexpr int ATS_MAX_KEYS = 512;
 
-template <int N>
-__device__ __forceinline__ void att_wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-
 template <int DH, bool WGT>
 __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -452,7 +441,7 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
     const uint16_t* kb = k + (size_t)tok0 * rs + (size_t)h * DH;
     const uint16_t* vb = v + (size_t)tok0 * rs + (size_t)h * DH;
     const uint32_t span = (uint32_t)(((size_t)(n - 1) * rs + DH) * 2);      // rows past the end load as zeros
-    const __amdgpu_buffer_rsrc_t rk = att_uniform_rsrc(kb, span), rv = att_uniform_rsrc(vb, span);
+    const __amdgpu_buffer_rsrc_t rk = make_uniform_rsrc(kb, span), rv = make_uniform_rsrc(vb, span);
     const int row_bytes = (int)(rs * 2);
 
     const int qrow = qt * 32 + c;
@@ -483,7 +472,7 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
         v_off[i] = r * row_bytes + (((ld_pos ^ ((r & 3) * 4)) & (NCHK - 1)) << 4);
     }
     char* wreg = ring + wave * WREG;
-    const uint32_t wave_lds = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(att_lds_ptr_t)ring + wave * WREG);
+    const uint32_t wave_lds = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lds_ptr_t)ring + wave * WREG);
     auto issue_k = [&](int key0) {
         const int kofs = key0 * row_bytes;
 #pragma unroll
@@ -512,7 +501,7 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
     for (int it = wave; it < ntile; it += 4) {
         const int key0 = it * ATS_BK;
         const bool more = it + 4 < ntile;
-        att_wait_loads<LD>();                                  // K of this tile has landed (V may still be on its way)
+        wait_loads<LD>();                                  // K of this tile has landed (V may still be on its way)
         bf16x8 kf[KS];
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(wreg + k_addr[kk]);
@@ -596,7 +585,7 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
         }
         __builtin_amdgcn_sched_barrier(0);
         // V of this tile: everything older than the K loads just issued has landed
-        if (more) att_wait_loads<LD>(); else att_wait_loads<0>();
+        if (more) wait_loads<LD>(); else wait_loads<0>();
         att_short4 vf[2][DT][2];
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh)

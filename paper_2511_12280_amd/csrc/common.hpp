@@ -86,9 +86,6 @@ __device__ __forceinline__ float row_dot(const T* __restrict__ a, const T* __res
     return acc;
 }
 
-// Makes the kernel hold all of these wave-uniform values at one point.  Reads of a sample's offsets written one after the other are
-// otherwise scheduled each behind the wait for the one before, a trip to memory each (a third of a microsecond at a kernel's start).
-
 // Makes a kernel hold all of these wave-uniform values at one point, so that they are read together.  A sample's offsets written one
 // after the other are otherwise scheduled each behind the wait for the one before it: three trips to memory instead of one
 // before a merge kernel knows its sample.

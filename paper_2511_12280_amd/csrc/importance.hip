@@ -341,7 +341,7 @@ __global__ __launch_bounds__(256, IMP_SUB_SCORES == 4 ? 4 : 3) void imp_scores_b
 // over deciders and heads, so the mean over heads is finished in the same pass (no per-head rows, no
 // third launch, K fetched once).
 // Bound by the chain metadata -> statistics -> exponentials -> reduction, so it has 16 waves: every thread holds one or two
-// (head, decider) rows of the statistics and at most 16 logits at 32 heads x 32 deciders, all requested at once.
+// (head, decider) rows of the statistics and at most 16 logits at 32 heads x 32 deciders, each kind requested at once.
 // GENERIC: the logits of the generic first sweep, whose `part` is one finished log-sum-exp per (head, decider) (144 keys x
 // 4 heads x 16 deciders of 64 float32 channels: 7.5 us when every score's dot products were formed again, 4.3 from the logits).
 constexpr int IMP_KEEP_MAXD = IMP_KEEP_MAXD_WS;
@@ -364,8 +364,8 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     extern __shared__ float c_lds[];                    // [H][max_D] log2-sum-exp2, +inf for rows past the sample's deciders
     __shared__ float red[IMP_FL_THREADS / 64][16];
     // thread (key = t % 16, group = t / 16) takes rows group, group + 64, ... of the block's H x max_D logit rows: 64
-    // consecutive rows are 4 KB in one piece.  They are requested before anything else, so that their latency (they come
-    // from another XCD's writes, i.e. from memory) overlaps the statistics below.
+    // consecutive rows are 4 KB in one piece, requested together (they come from another XCD's writes, i.e. from memory).  The
+    // statistics below are a trip of their own behind them: the compiler waits for the logits before that loop.
     const int key = threadIdx.x & 15, grp = threadIdx.x >> 4;
     const int rows = H * max_D;
     const __amdgpu_buffer_rsrc_t lb = make_uniform_rsrc(logits + ((size_t)(b * NKB + kb) * rows) * 16, (uint32_t)rows * 64u);   // rows past the block's read as 0

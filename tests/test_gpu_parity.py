@@ -391,8 +391,8 @@ def test_merge_layer_one_call_with_device_side_keep_counts(tight):
 ])
 def test_merge_layer_one_call_on_every_kernel_path(dtype, d, H, shapes):
     """The one-call merge layer prepares the merge inside its selection launch (row norms by token, pruned list,
-    token table); every cosine kernel reads that form.  Each path against the separate calls, bit for bit, and
-    the separate calls against the oracle."""
+    token table); every cosine kernel reads that form (a split contraction its list and table only).  Each path against the
+    separate calls, bit for bit, and the separate calls against the oracle."""
     samples, ratios = [], []
     for i, (P, V, O, D, keep) in enumerate(shapes):
         samples.append(W.random_case(500 + i, P + V + O, d, H, P, V, D, dtype=dtype, centres=max(3, V // 6)))

@@ -293,7 +293,8 @@ STACK_CASES = [
 def _merge_block_inputs(B, case, l_star, eps=1e-5, theta=10000.0):
     """What the merge layer of block l_star sees on the GPU: the block's rotated q, k and its post-attention
     hidden state, rebuilt from the same entry points in the same order (the kernels are deterministic, so
-    these are the very values inside d3tom_stack_step)."""
+    these are the very values inside d3tom_stack_step, up to the order of the float32 sums of an output projection
+    that the step cuts along its contraction)."""
     N, d, H, F, V = case["N"], case["d"], case["H"], case["F"], case["V"]
     dh = d // H
     x = _dev(case["x"])
