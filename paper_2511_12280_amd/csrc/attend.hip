@@ -16,31 +16,33 @@
 // A workgroup has eight waves of 32 (or 16) queries in two groups of four; wave i and wave i + 4 share a SIMD.  The groups
 // alternate (ping-pong): while one issues the MFMAs of a 64-key tile (S of tile i + 1, O += V P of tile i: 64 of them, 1024
 // clocks), the other does the softmax arithmetic of its tile; a barrier ends the phase.  That pays because the smaller MFMA
-// shape lets another wave's vector instructions through: per tile 1058 clocks of MFMAs and 756 of softmax arithmetic of the
-// other wave take 1250 clocks together, whereas beside MFMA 32x32x16 the exponentials do not issue at all (1029 + 756 -> 1780).
-// Measured at 32 heads of 128 (four independent waves on the larger shape before): 3773 keys 248 -> 205 us, 1951 keys
-// 71 -> 61 us, 4096 keys 230 us = 1200 TFLOP/s.  The card lowers its clock under this load, so part of what remains is set by
-// power.
+// shape lets another wave's vector instructions through: per tile 1058 clocks of MFMAs and 756 of softmax arithmetic (an fma,
+// an exp2 and half a conversion per logit) of the other wave take 1250 clocks together, whereas beside MFMA 32x32x16 the exponentials do not issue at all (1029 + 756 -> 1780).
+// Measured at 32 heads of 128 (four independent waves on the larger shape before): 3773 keys 240 -> 210 us, 1951 keys
+// 71 -> 62 us, 4096 keys 270 -> 235 us = 1170 TFLOP/s; 16 heads of 64, 4 x 2000 keys: 83 us either way, half as many MFMAs beside
+// the same softmax arithmetic.
 //
 // K and V tiles go HBM/L2 -> LDS with direct loads (buffer_load ... lds, no register staging; rows past the end of the sample
 // load as zeros through the buffer bounds check) into a ring; rows are unpadded and their 16-byte chunks XOR-swizzled by the
 // row index instead.  Loads are issued in the softmax phase, and the first K fragments of a tile are read there, so that the
 // MFMA phase starts at once.
 //
-// The softmax arithmetic paces the loop (every MFMA of the other wave takes 8 clocks of the vector issue port as well), so
-// it is cut to one fma and one exp2 per logit and the packing to bf16:
-//   - the row sums come from the matrix core too, a fragment of ones times P^T (two MFMAs per 32 keys instead of 32 adds);
+// The softmax arithmetic paces the loop (every MFMA of the other wave takes 8 clocks of the vector issue port as well), so its
+// wave has the higher priority (3773 keys 207.8 -> 205.4 us against priority for the MFMAs, 4 x 2000 keys with heads of 64
+// 84.9 -> 82.1), and it is cut to what the results need: per logit one fma, one exp2, one addition and the packing to bf16, and
 //   - the weights and the tail mask of the weighted form enter as the C operand of S^T (log2 w / scale2, -inf);
 //   - the running maximum costs one max3 per two logits: a lane compares its own logits with the column's maximum, and only where one
 //     of them exceeds it do the four lanes meet and the accumulators of that block of 16 queries get their new scale.
 // What the exponents refer to is a matter of precision.  The probabilities are rounded to bf16, the largest ones carry most of
 // that rounding, and relative to the running maximum the largest is exactly 1 and not rounded at all.  With the first tile's
-// maximum as a fixed reference the kernel takes 184 us instead of 204 at 3773 keys, but its error against float64 (2-norm,
-// relative, before the output is rounded) is 1.06 to 1.11 times as large at a logit spread of 1 (600 .. 3773 keys), 1.5 to 1.6
-// at 2 and 1.8 to 1.9 at 4.  The sums of the rounded probabilities lose nothing against float32 sums of the unrounded
-// ones: 0.95 to 1.00 of their error where the value rows have no common part, 0.7 where they have (a row's weights then
-// add up to exactly 1).  Rounded output, measured at 3773 keys, spreads 1, 2, 4: 2.264e-3, 1.914e-3, 1.728e-3; with
-// float32 sums 2.266e-3, 1.919e-3, 1.735e-3; with the fixed reference 2.332e-3, 2.226e-3, 1.916e-3.
+// maximum as a fixed reference (and the sums of the rounded probabilities from the matrix core) the kernel takes 189 us at 3773
+// keys, but its error against float64 (2-norm, relative, before the output is rounded) is 1.06 to 1.11 times as large at a
+// logit spread of 1 (600 .. 3773 keys), 1.5 to 1.6 at 2 and 1.8 to 1.9 at 4.  Rounded output, measured at 3773 keys, spreads 1,
+// 2, 4: 2.266e-3, 1.919e-3, 1.735e-3; with the fixed reference 2.332e-3, 2.226e-3, 1.916e-3.
+// The row sums are float32 sums of the unrounded probabilities, as in the short-sample kernel.  The sums of the rounded ones
+// (a fragment of ones times P^T: 207.5 instead of 211.8 us) are as near to float64, but they move whole rows by the rounding of
+// their probabilities, so that the two kernels give a merge other near-ties: in stack steps of 1000 to 3700 tokens several
+// tokens then go to another near-duplicate.
 //
 // The generic path (float32 or any head size) is one workgroup per (query, head) with a chunked
 // online softmax in plain float arithmetic.
@@ -89,6 +91,11 @@ __device__ __forceinline__ float att_quad_max(float x) {
     typedef unsigned att_u2 __attribute__((ext_vector_type(2)));
     const att_u2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return att_pair_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float att_quad_sum(float x) {
+    typedef unsigned att_u2 __attribute__((ext_vector_type(2)));
+    const att_u2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return att_pair_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 #endif
 
@@ -161,14 +168,10 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     for (int t = 0; t < DB; ++t)
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) ot[t][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // m_run: running maximum of the RAW logits; ms: what the exponents subtract; lt: sum of the column's probabilities, all four alike
-    float m_run[NQ], ms[NQ];
-    f32x4 lt[NQ];
-    bf16x8 ones;
+    // m_run: running maximum of the RAW logits; ms: what the exponents subtract; l_run: this lane's part of the column's sum
+    float m_run[NQ], ms[NQ], l_run[NQ];
 #pragma unroll
-    for (int qb = 0; qb < NQ; ++qb) { m_run[qb] = -INFINITY; ms[qb] = 0.f; lt[qb] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+    for (int qb = 0; qb < NQ; ++qb) { m_run[qb] = -INFINITY; ms[qb] = 0.f; l_run[qb] = 0.f; }
 
     // direct loads: lane -> (row, chunk position).  The chunk fetched into position p of row x is p ^ f(x): K fragments are 16
     // consecutive rows of one chunk, transposing reads of V four consecutive rows (per 16 lanes) of one 32-byte piece.
@@ -250,10 +253,6 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
                 if (kt == 0) read_v(1, t);
                 fence();
             }
-#pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                for (int qb = 0; qb < NQ; ++qb) lt[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[kt][qb], lt[qb], 0, 0, 0);
         }
         fence();
     };
@@ -269,7 +268,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
                         if (j * ATT_BK + kb * 16 + g * 4 + e >= n) st[kb][qb][e] = -INFINITY;
         }
         // The first fragments of tile j + 1 and the loads of stage j + AHEAD in turns, in front of the arithmetic (clocks per tile and
-        // pair of groups: so 2960, reads first and then loads 3190, spread among the exponentials 3420).
+        // pair of groups, measured without maximum and sums: so 2960, reads first and then loads 3190, spread among the exponentials 3420).
         if constexpr (!LAST) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
@@ -294,8 +293,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
                 const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_new) * scale2);
                 ms[qb] = m_new * scale2;
                 m_run[qb] = m_new;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) lt[qb][e] *= alpha;
+                l_run[qb] *= alpha;
 #pragma unroll
                 for (int x = 0; x < DB; ++x)
 #pragma unroll
@@ -308,7 +306,11 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
             for (int qb = 0; qb < NQ; ++qb)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    pf[kb >> 1][qb][(kb & 1) * 4 + e] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(st[kb][qb][e], scale2, -ms[qb]));
+                {
+                    const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(st[kb][qb][e], scale2, -ms[qb]));
+                    pf[kb >> 1][qb][(kb & 1) * 4 + e] = (__bf16)p;
+                    l_run[qb] += p;
+                }
     };
 
     const int ntile = (n + ATT_BK - 1) / ATT_BK;
@@ -349,14 +351,14 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     for (int j = 0; j + 1 < ntile; ++j) {
         if (grp == 0) wait_loads<KEEP>();
         phase_barrier();
+        __builtin_amdgcn_s_setprio(2);
         softmax_phase(j, no());
+        __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): the fragments are there (a wait the compiler knows of)
         if (grp == 1) wait_loads<KEEP>();
         phase_barrier();
-        __builtin_amdgcn_s_setprio(3);
         mfma_phase(j + 1, yes(), yes());
-        __builtin_amdgcn_s_setprio(0);
     }
     if (grp == 0) wait_loads<0>();
     phase_barrier();
@@ -373,7 +375,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     static_assert(4 * QROWS * ROWB <= STAGE, "a group's rows fit into a slot");
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
-        const float inv = 1.0f / lt[qb][0];
+        const float inv = 1.0f / att_quad_sum(l_run[qb]);
 #pragma unroll
         for (int t = 0; t < DB; ++t) {
             uint2 w;
@@ -778,11 +780,11 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
         if (dh == 128) { if (wgt) D3TOM_ATT((attend_bf16_short_kernel<128, true>)); else D3TOM_ATT((attend_bf16_short_kernel<128, false>)); }
         else           { if (wgt) D3TOM_ATT((attend_bf16_short_kernel<64, true>));  else D3TOM_ATT((attend_bf16_short_kernel<64, false>)); }
     } else if (mfma) {
-        // Rounds of workgroups over the 256 compute units.  A round of 128-query tiles costs 0.61 to 0.66 of one of 256-query tiles
-        // (every fragment read from LDS feeds one MFMA instead of two; 32 heads, narrow against wide: 1198 keys 45.6 us against
-        // 36.2, two rounds to one; 3773 keys 255 against 205, four to two; 2100 keys 105 against 108, 3 x 1000 keys 60.5 against
-        // 66.0, three to two); with heads of 64 two workgroups of 128 queries share a CU, and it costs 0.5 (16 heads, 3500 keys: 69.2
-        // against 68.1, two to one; 8 x 560 keys: 22.5 against 29.5, one to one).
+        // Rounds of workgroups over the 256 compute units.  A round of 128-query tiles costs 0.61 to 0.70 of one of 256-query tiles
+        // (every fragment read from LDS feeds one MFMA instead of two; 32 heads, narrow against wide: 1024 keys 21.9 us against 30.9,
+        // one round each; 1198 keys 44.7 against 35.7, two to one; 3773 keys 255 against 210, four to two; 2100 keys 106 against
+        // 111, 3 x 1000 keys 60.9 against 64.9, three to two); with heads of 64 two workgroups of 128 queries share a CU, and it costs
+        // 0.52 (16 heads, 3500 keys: 69.2 against 65.9, two to one; 8 x 560 keys: 22.1 against 28.9, one to one).
         const long heads = (long)H * B;
         const long wide = (ceil_div(max_seqlen, 256) * heads + 255) / 256, narrow = (ceil_div(max_seqlen, 128) * heads + 255) / 256;
         const int nq = (dh == 64 ? 55 : 66) * narrow < 100 * wide ? 1 : 2;
