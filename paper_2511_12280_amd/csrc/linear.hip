@@ -1,5 +1,5 @@
 // d3tom_linear: out = a w^T for the projections of a transformer block (the per-layer 4 n d^2 and 3 n d m
-// terms of the cost model in Section 4.3), bf16 operands, float32 accumulation on MFMA 32x32x16, with the
+// terms of the cost model in Section 4.3), bf16 operands, float32 accumulation on MFMA 16x16x32, with the
 // element-wise tail of the projection folded into the epilogue:
 //   PLAIN     out = a w^T, optionally written as several [rows, out_chunk] matrices (q | k | v)
 //   RESIDUAL  out = residual + a w^T                      (the block's two skip connections)

@@ -2,7 +2,8 @@
 // FORALL block and the "Remove positions" line).
 //
 // Stages, all on the caller's stream:
-//   norms     1 / ||row|| of every KEPT row of the similarity features (1 wave / row): the argmax over
+//   norms     1 / ||row|| of every KEPT row of the similarity features (1 wave / row; a split contraction sums the
+//             squares itself and needs no such launch): the argmax over
 //             kept slots of dot / (|m| |k|) does not depend on |m|, the pruned row's own norm; the same
 //             waves write the ascending list of pruned visual tokens (the gaps of the ascending kept_idx)
 //             and initialise the token -> (best value, slot) table
@@ -426,7 +427,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
 // Bound by the latency of its loads, so a wave should go round its loop once, and all loads of a turn (16 slices of both halves of
 // the tile, the norms) are requested together: without a branch around any of them, since each branch costs a wait and some tens
 // of cycles.  (One wave per row, loads under conditions: 1400 rows x 600 slots x 2 slices 14.0 us, now 6.2; 486 x 243 x 4 slices
-// 6.8 us, now 3.8; 921 x 103 x 16 4.5 us, now 3.9.)
+// 6.8 us, now 3.8; 921 x 103 x 16 4.5 us, 3.9 with norms read by token, now 4.4.)
 template <int wpr>
 __global__ __launch_bounds__(256) void cos_reduce_argmax(
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count,
