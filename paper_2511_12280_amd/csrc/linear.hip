@@ -13,21 +13,27 @@
 //             output and down projections with too few tall tiles to fill the chip.
 // One rounding to bf16, at the store (ROPE: one for the projection, one for the rotated value).
 //
-// One workgroup per tile of BM x BN, eight waves in two groups of four.  Group i owns rows i*BM/2 .. of the tile, its four
-// waves a quarter of the columns each; wave i and wave i + 4 share a SIMD.  The groups alternate (ping-pong): in one phase a
+// One workgroup per tile of BM x BN, eight waves, in one of two forms.
+// Ping-pong (WC = 4): two groups of four.  Group i owns rows i*BM/2 .. of the tile, its four
+// waves a quarter of the columns each; wave i and wave i + 4 share a SIMD.  The groups alternate: in one phase a
 // group reads the operand fragments of a whole 64-element k-stage from LDS into registers (and issues direct loads) while
 // the other group issues nothing but the MFMAs of the stage it holds; a barrier ends the phase.  Measured on gfx950 with
 // 256 x 256 tiles (clocks of a k-stage; the MFMAs alone are 2048): all waves on one schedule 3270, phases of 32 elements
 // 2570, phases of 64 2307.  MFMA streams of two waves of one SIMD slow each other down, hence the phases.
+// Loading waves (WC = 2): four waves compute a quarter of the tile each, their fragments read one k-step ahead, four only issue the
+// direct loads; one barrier a k-stage.  For small tiles, whose phases above would be mostly latency: 2048 x 2048 weights, 493 rows
+// 14.9 -> 9.3 us, 11008 channels into 4096 at 1400 rows 127 -> 107 us.  Such a tile is bound by what a compute unit takes in, 62 to 77
+// bytes per ns of rows that no other one has had (a deeper ring does not help, and loads that touch the rows ahead of time cost more
+// than they give); large tiles are bound by the MFMAs and by power, for which the first form is the better one.
 //
 // MFMA 16x16x32 and not 32x32x16: at full load the card is power bound (it clocks down to 1.5 GHz), and the smaller shape
 // moves fewer accumulator bytes per flop: 2.09 against 1.86 PFLOP/s with operands in registers and random data, 1.24 against
 // 1.10 in this loop.  It adds the products in the same order as two 32x32x16 steps; the results are the same bits.
 //
 // Both operands are contraction-contiguous, so both tiles travel HBM/L2 -> LDS with direct loads (16 bytes per lane, no
-// register staging): group 0 fetches the rows of a, group 1 the rows of w, 128 bytes of every row per stage (a whole cache
-// line: half lines halve the rate of a compute unit's load path).  Two rings fill the 160 KB of LDS; the one of w is the
-// deeper one, its rows come cold from HBM.  The 16-byte chunk stored at position p of tile row r is chunk p ^ f(r), with f
+// register staging), 128 bytes of every row per stage (a whole cache line: half lines halve the rate of a compute unit's load
+// path).  In the first form group 0 fetches the rows of a, group 1 the rows of w; two rings fill the 160 KB of LDS, and the one of w is
+// the deeper one, its rows come cold from HBM.  The 16-byte chunk stored at position p of tile row r is chunk p ^ f(r), with f
 // such that the 16 rows of a fragment read hit all 64 banks.
 //
 // The product is formed as w a^T, so that a lane ends up with one row of out and 4 * TN consecutive columns of it: the
@@ -45,16 +51,18 @@ namespace d3tom {
 enum { LIN_PLAIN = 0, LIN_RESIDUAL = 1, LIN_SWIGLU = 2, LIN_PARTIAL = 3, LIN_ROPE = 4 };
 constexpr int LIN_BK = 64;
 
-// TM: 16-row fragments of a wave (BM = 32 TM rows), TN: 16-column fragments of a wave (BN = 64 TN columns)
-template <int TM, int TN> struct LinCfg {
-    static constexpr int BM = 32 * TM, BN = 64 * TN;
+// A tile of BM x BN.  WC = 4: two groups of four waves in turn, 2 x 4 waves over the tile; WC = 2: four computing waves, 2 x 2, and
+// four that load.  TM, TN: 16-row and 16-column fragments of a computing wave.
+template <int TM, int TN, int WC> struct LinCfg {
+    static constexpr int BM = 32 * TM, BN = 16 * TN * WC;
     static constexpr int A_BYTES = BM * 128, W_BYTES = BN * 128;       // one k-stage of either operand
-    // ring depths: w first (deeper), both within 160 KB
-    static constexpr int NW = (TN == 4) ? (TM == 8 ? 3 : TM == 4 ? 3 : 4) : (TN == 3) ? 4 : (TM == 2 ? 6 : TM == 4 ? 5 : 4);
+    // ring depths within 160 KB.  WC = 4: that of w first (deeper); WC = 2: a stage is one thing, at most six of them
+    static constexpr int NS_MAX = 163840 / (A_BYTES + W_BYTES), NS = NS_MAX > 6 ? 6 : NS_MAX;
+    static constexpr int NW = WC == 2 ? NS : (TN == 4) ? (TM >= 3 ? 3 : 4) : (TN == 3) ? 4 : (TM == 2 ? 6 : TM <= 5 ? 5 : 4);
     static constexpr int NA_MAX = (163840 - NW * W_BYTES) / A_BYTES;
-    static constexpr int NA = NA_MAX > 6 ? 6 : NA_MAX;
+    static constexpr int NA = WC == 2 ? NS : NA_MAX > 6 ? 6 : NA_MAX;
     static constexpr int LDS = NA * A_BYTES + NW * W_BYTES;
-    static_assert(NA >= 2 && NW >= 2 && LDS <= 163840, "rings must fit");
+    static_assert(NA >= 2 && NW >= 2 && LDS <= 163840 && (WC == 4 || NS >= 3), "rings must fit");
 };
 
 // Tile (rt, ct) of workgroup id.  Ids are dealt round-robin to the 8 XCDs; the tiles are numbered in bands of RB row tiles,
@@ -68,15 +76,15 @@ __device__ __forceinline__ bool linear_tile(int id, int per, int RB, int NRT, in
     return true;
 }
 
-template <int TM, int TN, int EPI>
+template <int TM, int TN, int WC, int EPI>
 __global__ __launch_bounds__(512, 2) void linear_bf16_kernel(
     const uint16_t* __restrict__ a, const uint16_t* __restrict__ w, int M, int N, int K,
     const uint16_t* residual, uint16_t* out, int out_chunk, int NRT, int NCT, int per, int RB, int col0, int col_end,
     const float2* __restrict__ rope_cs, int rope_dh) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    using C = LinCfg<TM, TN>;
+    using C = LinCfg<TM, TN, WC>;
     constexpr int BM = C::BM, BN = C::BN, NA = C::NA, NW = C::NW;
-    constexpr int LA = BM / 32, LW = BN / 32;           // direct loads per wave and stage (8 rows each)
+    constexpr int LA = BM / 32, LW = BN / 32;           // direct loads per loading wave and stage (8 rows each)
     constexpr bool PAIR = EPI == LIN_SWIGLU || EPI == LIN_ROPE;
     extern __shared__ __attribute__((aligned(16))) char ring[];     // NA stages of a, then NW stages of w
 
@@ -84,8 +92,10 @@ __global__ __launch_bounds__(512, 2) void linear_bf16_kernel(
     if (!linear_tile(blockIdx.x, per, RB, NRT, NCT, rt, ct)) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int grp = __builtin_amdgcn_readfirstlane(tid >> 8), wn = (tid >> 6) & 3;
+    const int half_wg = __builtin_amdgcn_readfirstlane(tid >> 8), wn = (tid >> 6) & 3;
     const int r = lane & 15, g = lane >> 4;
+    // a computing wave's part of the tile: rows grp * BM/2 .., columns wcol * BN/WC ..
+    const int grp = WC == 4 ? half_wg : wn >> 1, wcol = WC == 4 ? wn : wn & 1;
     const int n_out = (EPI == LIN_SWIGLU) ? N / 2 : N;  // SWIGLU: N counts gate and up rows
     // What a tile's columns are: plain columns, or pairs (SWIGLU: output o = rows o and o + F of w; ROPE: channels c, c + dh/2)
     constexpr int UNITS = PAIR ? BN / 2 : BN;
@@ -94,31 +104,26 @@ __global__ __launch_bounds__(512, 2) void linear_bf16_kernel(
     const int half = rope_dh >> 1;
 
     // rows past the end re-read row 0 (their results are never stored); the k-stage moves through the scalar offset
-    constexpr int LMAX = LA > LW ? LA : LW;
-    int off[LMAX];
-#pragma unroll
-    for (int i = 0; i < LMAX; ++i) {
-        const int pos = lane & 7;
-        if (grp == 0) {
-            const int row = wn * (BM / 4) + i * 8 + (lane >> 3), m = rt * BM + row;
-            off[i] = ((m < M && i < LA) ? m : 0) * K * 2 + ((pos ^ ((row >> 1) & 7)) << 4);
+    auto a_offset = [&](int i) {
+        const int row = wn * (BM / 4) + i * 8 + (lane >> 3), m = rt * BM + row;
+        return (m < M ? m : 0) * K * 2 + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+    };
+    auto w_offset = [&](int i) {
+        const int row = wn * (BN / 4) + i * 8 + (lane >> 3);
+        const int part = row / (16 * TN), q = row - part * 16 * TN, qg = q / (4 * TN);
+        int n, ok;
+        if constexpr (PAIR) {
+            const int u = unit0 + part * 8 * TN + qg * 2 * TN + ((q - qg * 4 * TN) >> 2) * 2 + (q & 1);
+            const int second = (q >> 1) & 1;
+            ok = u < unit_end;
+            if constexpr (EPI == LIN_SWIGLU) n = u + second * n_out;
+            else { const int h = u / half; n = h * rope_dh + (u - h * half) + second * half; }
         } else {
-            const int row = wn * (BN / 4) + i * 8 + (lane >> 3);
-            const int part = row / (16 * TN), q = row - part * 16 * TN, qg = q / (4 * TN);
-            int n, ok;
-            if constexpr (PAIR) {
-                const int u = unit0 + part * 8 * TN + qg * 2 * TN + ((q - qg * 4 * TN) >> 2) * 2 + (q & 1);
-                const int second = (q >> 1) & 1;
-                ok = u < unit_end;
-                if constexpr (EPI == LIN_SWIGLU) n = u + second * n_out;
-                else { const int h = u / half; n = h * rope_dh + (u - h * half) + second * half; }
-            } else {
-                n = unit0 + row;
-                ok = n < unit_end;
-            }
-            off[i] = ((ok && i < LW) ? n : 0) * K * 2 + ((pos ^ (((q >> 1) & 1) | (qg << 1))) << 4);
+            n = unit0 + row;
+            ok = n < unit_end;
         }
-    }
+        return (ok ? n : 0) * K * 2 + (((lane & 7) ^ (((q >> 1) & 1) | (qg << 1))) << 4);
+    };
     const int nst = (K / LIN_BK) / (int)gridDim.y;         // k-stages of this workgroup's slice of the contraction
     const int st0 = (int)blockIdx.y * nst;
     const uint32_t ring0 = (uint32_t)(size_t)(lds_ptr_t)ring;
@@ -137,90 +142,159 @@ __global__ __launch_bounds__(512, 2) void linear_bf16_kernel(
     for (int kk = 0; kk < 2; ++kk) {
         const int ra = grp * (BM / 2) + r, q = (r >> 2) * 4 * TN + (r & 3);
         a_addr[kk] = ra * 128 + (((kk * 4 + g) ^ ((ra >> 1) & 7)) << 4);
-        w_addr[kk] = NA * C::A_BYTES + (wn * 16 * TN + q) * 128 + (((kk * 4 + g) ^ (((q >> 1) & 1) | ((r >> 2) << 1))) << 4);
+        w_addr[kk] = NA * C::A_BYTES + (wcol * 16 * TN + q) * 128 + (((kk * 4 + g) ^ (((q >> 1) & 1) | ((r >> 2) << 1))) << 4);
     }
     bf16x8 af[2][TM], wf[2][TN];
-    auto read = [&](int sa, int sw) {
+    if constexpr (WC == 4) {
+        auto read = [&](int sa, int sw) {
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-            const char* pw = ring + sw * C::W_BYTES + w_addr[kk];
-            const char* pa = ring + sa * C::A_BYTES + a_addr[kk];
+            for (int kk = 0; kk < 2; ++kk) {
+                const char* pw = ring + sw * C::W_BYTES + w_addr[kk];
+                const char* pa = ring + sa * C::A_BYTES + a_addr[kk];
 #pragma unroll
-            for (int j = 0; j < TN; ++j) wf[kk][j] = *reinterpret_cast<const bf16x8*>(pw + j * 4 * 128);
+                for (int j = 0; j < TN; ++j) wf[kk][j] = *reinterpret_cast<const bf16x8*>(pw + j * 4 * 128);
 #pragma unroll
-            for (int i = 0; i < TM; ++i) af[kk][i] = *reinterpret_cast<const bf16x8*>(pa + i * 16 * 128);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto compute = [&]() {
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[kk][j], af[kk][i], acc[i][j], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto next = [](int slot, int n) { return slot + 1 == n ? 0 : slot + 1; };
-    // Stage s sits in slot s mod NA (NW).  Group 0 reads it in phase 2s, group 1 in phase 2s + 1; from phase 2s + 2 on its
-    // slots may be refilled, which group 0 does for a in that phase and group 1 for w one later.  Before the barrier that ends
-    // phase 2s + 1 both groups wait for their own loads of stage s + 1.
-    if (grp == 0) {
-        const __amdgpu_buffer_rsrc_t rs = make_uniform_rsrc(a, (uint32_t)((size_t)M * K * 2));
-        auto issue = [&](int s, int slot) {
-#pragma unroll
-            for (int i = 0; i < LA; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(size_t)(a_lds + slot * C::A_BYTES + i * 1024), 16, off[i], (st0 + s) * 128, 0, 0);
+                for (int i = 0; i < TM; ++i) af[kk][i] = *reinterpret_cast<const bf16x8*>(pa + i * 16 * 128);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         };
+        auto compute = [&]() {
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int s = 0; s < NA; ++s) if (s < nst) issue(s, s);
-        if (nst >= NA) wait_loads<(NA - 1) * LA>(); else wait_loads<0>();
-        phase_barrier();
-        int sa = 0, sw = 0, fill = NA - 1;
+            for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[kk][j], af[kk][i], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto next = [](int slot, int n) { return slot + 1 == n ? 0 : slot + 1; };
+        // Stage s sits in slot s mod NA (NW).  Group 0 reads it in phase 2s, group 1 in phase 2s + 1; from phase 2s + 2 on its
+        // slots may be refilled, which group 0 does for a in that phase and group 1 for w one later.  Before the barrier that ends
+        // phase 2s + 1 both groups wait for their own loads of stage s + 1.
+        if (half_wg == 0) {
+            int off[LA];
+#pragma unroll
+            for (int i = 0; i < LA; ++i) off[i] = a_offset(i);
+            const __amdgpu_buffer_rsrc_t rs = make_uniform_rsrc(a, (uint32_t)((size_t)M * K * 2));
+            auto issue = [&](int s, int slot) {
+#pragma unroll
+                for (int i = 0; i < LA; ++i)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(size_t)(a_lds + slot * C::A_BYTES + i * 1024), 16, off[i], (st0 + s) * 128, 0, 0);
+            };
+#pragma unroll
+            for (int s = 0; s < NA; ++s) if (s < nst) issue(s, s);
+            if (nst >= NA) wait_loads<(NA - 1) * LA>(); else wait_loads<0>();
+            phase_barrier();
+            int sa = 0, sw = 0, fill = NA - 1;
 #pragma unroll 1
-        for (int s = 0; s < nst; ++s) {
-            const bool more = s + NA - 1 < nst;
-            read(sa, sw);
-            if (s > 0 && more) issue(s + NA - 1, fill);
-            wait_lds();
+            for (int s = 0; s < nst; ++s) {
+                const bool more = s + NA - 1 < nst;
+                read(sa, sw);
+                if (s > 0 && more) issue(s + NA - 1, fill);
+                wait_lds();
+                phase_barrier();
+                compute();
+                if (more) wait_loads<(NA - 2) * LA>(); else wait_loads<0>();
+                phase_barrier();
+                fill = sa; sa = next(sa, NA); sw = next(sw, NW);
+            }
             phase_barrier();
-            compute();
-            if (more) wait_loads<(NA - 2) * LA>(); else wait_loads<0>();
+        } else {
+            int off[LW];
+#pragma unroll
+            for (int i = 0; i < LW; ++i) off[i] = w_offset(i);
+            const __amdgpu_buffer_rsrc_t rs = make_uniform_rsrc(w, (uint32_t)((size_t)N * K * 2));
+            auto issue = [&](int s, int slot) {
+#pragma unroll
+                for (int i = 0; i < LW; ++i)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(size_t)(w_lds + slot * C::W_BYTES + i * 1024), 16, off[i], (st0 + s) * 128, 0, 0);
+            };
+#pragma unroll
+            for (int s = 0; s < NW; ++s) if (s < nst) issue(s, s);
+            if (nst >= NW) wait_loads<(NW - 1) * LW>(); else wait_loads<0>();
             phase_barrier();
-            fill = sa; sa = next(sa, NA); sw = next(sw, NW);
+            phase_barrier();
+            int sa = 0, sw = 0, fill = NW - 1;
+#pragma unroll 1
+            for (int s = 0; s < nst; ++s) {
+                const bool more = s + NW - 1 < nst;
+                read(sa, sw);
+                if (s > 0 && more) issue(s + NW - 1, fill);
+                wait_lds();
+                if (more) wait_loads<(NW - 2) * LW>(); else wait_loads<0>();
+                phase_barrier();
+                compute();
+                phase_barrier();
+                fill = sw; sa = next(sa, NA); sw = next(sw, NW);
+            }
         }
-        phase_barrier();
-    } else {
-        const __amdgpu_buffer_rsrc_t rs = make_uniform_rsrc(w, (uint32_t)((size_t)N * K * 2));
+    } else if (half_wg == 1) {
+        // the loading waves: stage s + NA - 1 goes into the slot of stage s - 1 once the computing waves have that in registers
+        const __amdgpu_buffer_rsrc_t ra = make_uniform_rsrc(a, (uint32_t)((size_t)M * K * 2)), rw = make_uniform_rsrc(w, (uint32_t)((size_t)N * K * 2));
+        int off_a[LA], off_w[LW];
+#pragma unroll
+        for (int i = 0; i < LA; ++i) off_a[i] = a_offset(i);
+#pragma unroll
+        for (int i = 0; i < LW; ++i) off_w[i] = w_offset(i);
         auto issue = [&](int s, int slot) {
 #pragma unroll
             for (int i = 0; i < LW; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(size_t)(w_lds + slot * C::W_BYTES + i * 1024), 16, off[i], (st0 + s) * 128, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_ptr_t)(size_t)(w_lds + slot * C::W_BYTES + i * 1024), 16, off_w[i], (st0 + s) * 128, 0, 0);
+#pragma unroll
+            for (int i = 0; i < LA; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr_t)(size_t)(a_lds + slot * C::A_BYTES + i * 1024), 16, off_a[i], (st0 + s) * 128, 0, 0);
         };
 #pragma unroll
-        for (int s = 0; s < NW; ++s) if (s < nst) issue(s, s);
-        if (nst >= NW) wait_loads<(NW - 1) * LW>(); else wait_loads<0>();
-        phase_barrier();
-        phase_barrier();
-        int sa = 0, sw = 0, fill = NW - 1;
+        for (int s = 0; s < NA - 1; ++s) if (s < nst) issue(s, s);
+        int fill = NA - 1;
 #pragma unroll 1
         for (int s = 0; s < nst; ++s) {
-            const bool more = s + NW - 1 < nst;
-            read(sa, sw);
-            if (s > 0 && more) issue(s + NW - 1, fill);
-            wait_lds();
-            if (more) wait_loads<(NW - 2) * LW>(); else wait_loads<0>();
-            phase_barrier();
-            compute();
-            phase_barrier();
-            fill = sw; sa = next(sa, NA); sw = next(sw, NW);
+            if (s + NA - 2 < nst) wait_loads_and_barrier<(NA - 2) * (LA + LW)>(); else wait_loads_and_barrier<0>();
+            if (s + NA - 1 < nst) issue(s + NA - 1, fill);
+            fill = fill + 1 == NA ? 0 : fill + 1;
         }
+        return;
+    } else {
+        // the computing waves: the fragments of the next k-step of 32 are read behind the first MFMAs of this one, across the
+        // barrier too (the one for stage s + 1 lies between the two k-steps of stage s)
+        auto read_one = [&](int slot, int kk, int f) {
+            if (f < TN) wf[kk][f] = *reinterpret_cast<const bf16x8*>(ring + slot * C::W_BYTES + w_addr[kk] + f * 4 * 128);
+            else af[kk][f - TN] = *reinterpret_cast<const bf16x8*>(ring + slot * C::A_BYTES + a_addr[kk] + (f - TN) * 16 * 128);
+        };
+        auto multiply = [&](int kk, int slot, bool read) {     // MFMAs of k-step kk; the other one's fragments from `slot`
+#pragma unroll
+            for (int n = 0; n < TM * TN; ++n) {
+                const int i = n / TN, j = n % TN;
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[kk][j], af[kk][i], acc[i][j], 0, 0, 0);
+                if (read && n < TM + TN) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    read_one(slot, kk ^ 1, n);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        static_assert(TM * TN >= TM + TN, "a fragment is read behind every MFMA");
+        wait_loads_and_barrier<0>();
+#pragma unroll
+        for (int f = 0; f < TM + TN; ++f) read_one(0, 0, f);
+        int slot = 0;
+#pragma unroll 1
+        for (int s = 0; s + 1 < nst; ++s) {
+            multiply(0, slot, true);
+            __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0): stage s is in registers
+            phase_barrier();
+            slot = slot + 1 == NA ? 0 : slot + 1;
+            multiply(1, slot, true);
+        }
+        multiply(0, slot, true);
+        multiply(1, slot, false);
     }
 
     // epilogue, in registers: lane (r, g) holds row r of every 16-row fragment and, over the TN fragments, 4 TN consecutive
     // values of its part: plain columns, or (PAIR) 2 TN consecutive outputs with their partners in elements 2 and 3
-    const int u0 = unit0 + wn * (UNITS / 4) + g * (UNITS / 16);
+    const int u0 = unit0 + wcol * (UNITS / WC) + g * (UNITS / (4 * WC));
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int m = rt * BM + grp * (BM / 2) + i * 16 + r;
@@ -249,7 +323,7 @@ __global__ __launch_bounds__(512, 2) void linear_bf16_kernel(
                 store_bf16<V>(out + o, v);
             }
         } else {
-            constexpr int V = (TN == 4) ? 8 : (TN == 2) ? 4 : 2;      // outputs per store
+            constexpr int V = (TN % 4 == 0) ? 8 : (TN % 2 == 0) ? 4 : 2;      // outputs per store
 #pragma unroll
             for (int v0 = 0; v0 < 2 * TN; v0 += V) {
                 const int u = u0 + v0;
@@ -287,12 +361,12 @@ __global__ __launch_bounds__(512, 2) void linear_bf16_kernel(
 }
 
 namespace {
-template <int TM, int TN, int EPI>
+template <int TM, int TN, int WC, int EPI>
 int launch_linear(const void* a, const void* w, int M, int N, int K, const void* residual, void* out, int out_chunk,
                   int ksplit, int col0, int col_end, hipStream_t st, const float2* rope_cs = nullptr, int rope_dh = 0) {
-    using C = LinCfg<TM, TN>;
+    using C = LinCfg<TM, TN, WC>;
     static PerDeviceOnce lds_setup;      // per instantiation
-    if (!lds_setup.run([] { return raise_dynamic_lds(linear_bf16_kernel<TM, TN, EPI>, C::LDS); })) return D3TOM_ERR_DEVICE;
+    if (!lds_setup.run([] { return raise_dynamic_lds(linear_bf16_kernel<TM, TN, WC, EPI>, C::LDS); })) return D3TOM_ERR_DEVICE;
     const int out_bn = (EPI == LIN_SWIGLU) ? C::BN / 2 : C::BN;
     const int NRT = ceil_div(M, C::BM), NCT = ceil_div(col_end - col0, out_bn);
     const int per = ceil_div(NRT * NCT, 8);
@@ -302,7 +376,7 @@ int launch_linear(const void* a, const void* w, int M, int N, int K, const void*
     int RB = 1;
     while ((RB + 1) * (RB + 1) * C::BM <= conc * C::BN) ++RB;
     if (RB > NRT) RB = NRT;
-    D3TOM_LAUNCH(LINEAR, st, (linear_bf16_kernel<TM, TN, EPI><<<dim3(8u * (unsigned)per, (unsigned)ksplit), 512, C::LDS, st>>>(
+    D3TOM_LAUNCH(LINEAR, st, (linear_bf16_kernel<TM, TN, WC, EPI><<<dim3(8u * (unsigned)per, (unsigned)ksplit), 512, C::LDS, st>>>(
         (const uint16_t*)a, (const uint16_t*)w, M, N, K, (const uint16_t*)residual, (uint16_t*)out, out_chunk,
         NRT, NCT, per, RB, col0, col_end, rope_cs, rope_dh)));
     return D3TOM_OK;
@@ -311,37 +385,57 @@ int launch_linear(const void* a, const void* w, int M, int N, int K, const void*
 template <int EPI>
 int launch_linear_cfg(int cfg, const void* a, const void* w, int M, int N, int K, const void* residual, void* out, int out_chunk,
                       int ksplit, int col0, int col_end, hipStream_t st, const float2* rope_cs = nullptr, int rope_dh = 0) {
-#define D3TOM_LIN(TM, TN) return launch_linear<TM, TN, EPI>(a, w, M, N, K, residual, out, out_chunk, ksplit, col0, col_end, st, rope_cs, rope_dh)
-    switch (cfg) {
-        case 0: D3TOM_LIN(2, 2);
-        case 1: D3TOM_LIN(2, 4);
-        case 2: D3TOM_LIN(4, 2);
-        case 3: D3TOM_LIN(4, 3);
-        case 4: D3TOM_LIN(4, 4);
-        case 5: D3TOM_LIN(8, 2);
-        case 6: D3TOM_LIN(8, 3);
-        default: D3TOM_LIN(8, 4);
+#define D3TOM_LIN(TM, TN, WC) return launch_linear<TM, TN, WC, EPI>(a, w, M, N, K, residual, out, out_chunk, ksplit, col0, col_end, st, rope_cs, rope_dh)
+    switch (cfg) {              // in the order of LIN_TILES
+        case 0: D3TOM_LIN(2, 2, 2);
+        case 1: D3TOM_LIN(2, 3, 2);
+        case 2: D3TOM_LIN(2, 4, 2);
+        case 3: D3TOM_LIN(2, 4, 4);
+        case 4: D3TOM_LIN(3, 4, 2);
+        case 5: D3TOM_LIN(4, 2, 4);
+        case 6: D3TOM_LIN(4, 6, 2);
+        case 7: D3TOM_LIN(4, 4, 4);
+        case 8: D3TOM_LIN(5, 4, 2);
+        case 9: D3TOM_LIN(5, 4, 4);
+        case 10: D3TOM_LIN(6, 4, 2);
+        case 11: D3TOM_LIN(6, 4, 4);
+        case 12: D3TOM_LIN(7, 4, 4);
+        case 13: D3TOM_LIN(8, 2, 4);
+        case 14: D3TOM_LIN(8, 4, 2);
+        case 15: D3TOM_LIN(8, 3, 4);
+        default: D3TOM_LIN(8, 4, 4);
     }
 #undef D3TOM_LIN
 }
 }  // namespace
 
 // ---- choice of the tile -----------------------------------------------------------------------------
-// What a k-stage of a tile takes when the chip is full of them (microseconds, measured at 3773 x 12288 x 4096 and
-// 3773 x 22016 x 4096 with weights cold in HBM), and what a round of workgroups costs beside its k-stages (filling the ring,
-// the epilogue).  A grid runs in rounds of 256 workgroups, one per compute unit, and a mostly empty last round costs as much as
-// a full one: the estimate is rounds * (stages * stage + round), and the smallest one wins.
-struct LinTile { int bm, bn; double stage; };
-static constexpr LinTile LIN_TILES[] = {{64, 128, 0.42}, {64, 256, 0.64}, {128, 128, 0.565}, {128, 192, 0.76}, {128, 256, 0.88},
-                                        {256, 128, 0.89}, {256, 192, 1.19}, {256, 256, 1.40}};
+// A grid runs in rounds of 256 workgroups, one per compute unit, and a mostly empty last round costs as much time as a full one:
+// hence tiles of many heights.  What a launch takes (microseconds), fitted to 112 shapes (96 .. 4600 rows; widths and contractions of
+// projections of 2048 and 4096 channels, weights cold in HBM):
+//   rounds * (stages * stage + round) + tiles / 256 * stages * fill + launch
+// `stage` is what a k-stage takes however few tiles there are, `fill` what it takes longer when the chip is full of them (operands, and
+// above all power), `round` the filling of the ring and the epilogue.  The smallest estimate wins; it misses the best tile of the table
+// by 1.5 % on average, at most 15 %.  (Eight tiles of 64, 128 and 256 rows and one constant each: 14 %.  Three blocks at 738 rows 1148 -> 986 us,
+// four at 1900 to 2100 rows 3929 -> 3685.)  `part`: what a million values of a partial matrix take when the contraction is cut.
+struct LinTile { int bm, bn; double stage, fill, round, launch, part; };
+static constexpr LinTile LIN_TILES[] = {
+    {64, 64, 0.225, 0.000, 0.7, 1.9, 1.08}, {64, 96, 0.275, 0.026, 0.2, 3.3, 0.78},
+    {64, 128, 0.337, 0.031, 0.0, 2.5, 1.75}, {64, 256, 0.602, 0.051, 0.2, 3.5, 1.57},
+    {96, 128, 0.393, 0.048, 0.0, 2.5, 1.55}, {128, 128, 0.465, 0.059, 2.4, 2.1, 0.73},
+    {128, 192, 0.584, 0.101, 0.5, 3.5, 1.43}, {128, 256, 0.723, 0.117, 2.7, 1.3, 1.40},
+    {160, 128, 0.479, 0.099, 1.0, 2.5, 1.55}, {160, 256, 0.773, 0.168, 4.7, 0.1, 1.34},
+    {192, 128, 0.494, 0.136, 2.5, 2.1, 1.35}, {192, 256, 0.838, 0.221, 5.6, 0.0, 1.44},
+    {224, 256, 0.901, 0.283, 6.5, 0.0, 1.40}, {256, 128, 0.649, 0.169, 4.9, 0.7, 0.67},
+    {256, 128, 0.573, 0.186, 3.4, 3.1, 1.40}, {256, 192, 0.838, 0.236, 7.0, 1.4, 0.48},
+    {256, 256, 0.951, 0.355, 7.8, 0.0, 1.35}};
 constexpr int LIN_NTILES = sizeof(LIN_TILES) / sizeof(LIN_TILES[0]);
-constexpr double LIN_ROUND_US = 3.0, LIN_LAUNCH_US = 4.0;
 
 // `cols` counts rows of w (SWIGLU: gate and up)
 static double linear_estimate(int cfg, int M, int cols, int nst, int ksplit) {
     const LinTile& t = LIN_TILES[cfg];
     const long tiles = (long)ceil_div(M, t.bm) * ceil_div(cols, t.bn) * ksplit;
-    return (double)((tiles + 255) / 256) * (nst * t.stage + LIN_ROUND_US) + LIN_LAUNCH_US;
+    return (double)((tiles + 255) / 256) * (nst * t.stage + t.round) + (double)tiles / 256.0 * nst * t.fill + t.launch;
 }
 static int linear_pick(int M, int cols, int nst, int ksplit, int bm, double* est) {
     int best = -1;
@@ -355,9 +449,10 @@ static int linear_pick(int M, int cols, int nst, int ksplit, int bm, double* est
     return best;
 }
 // A last round that is mostly empty can be cut off: the leading columns that fill whole rounds go in one launch, the
-// remaining ones in a second launch with whatever tile suits them (gate | up at 3773 rows: 1290 tiles of 256 x 256 are five
-// full rounds and ten tiles).  `cols` in rows of w; *cols_a: rows of w of the first launch (all of them: one launch), a
+// remaining ones in a second launch with whatever tile suits them (4600 rows x 22016 x 4096: 1548 tiles of 256 x 256 are six full rounds
+// and twelve, 627 us in one launch, 599 in two).  `cols` in rows of w; *cols_a: rows of w of the first launch (all of them: one launch), a
 // multiple of its tile width.
+constexpr double LIN_SECOND_US = 4.0;       // the first launch drains and the second fills its rings
 struct LinPlan { int cfg_a, cols_a, cfg_b; double est; };
 static LinPlan linear_plan(int M, int cols, int nst) {
     LinPlan p;
@@ -372,7 +467,7 @@ static LinPlan linear_plan(int M, int cols, int nst) {
         if (lead < 1 || lead >= nct) continue;
         double rest;
         const int cb = linear_pick(M, cols - lead * LIN_TILES[c].bn, nst, 1, 0, &rest);
-        const double t = linear_estimate(c, M, lead * LIN_TILES[c].bn, nst, 1) + rest;
+        const double t = linear_estimate(c, M, lead * LIN_TILES[c].bn, nst, 1) + rest + LIN_SECOND_US;
         if (t < p.est && t < 0.95 * single) { p.cfg_a = c; p.cols_a = lead * LIN_TILES[c].bn; p.cfg_b = cb; p.est = t; }
     }
     return p;
@@ -380,7 +475,7 @@ static LinPlan linear_plan(int M, int cols, int nst) {
 
 // Contraction slices for a projection whose result goes through the row-wise add-and-normalise kernel anyway: cutting the
 // contraction fills the chip where the tiles of a short sequence do not, at the price of writing and reading `ksplit` float32
-// matrices (about 3 TB/s together) and of the row kernel reading them.  Returns 1 (no split), 2 or 4; *cfg is the tile.
+// matrices and of the row kernel reading them (0.45 us per million values more than without).  Returns 1 (no split), 2 or 4; *cfg is the tile.
 // max_floats bounds the partial matrices together.
 int linear_split_plan(int M, int N, int K, size_t max_floats, int* cfg) {
     const int nst = K / LIN_BK;
@@ -391,10 +486,10 @@ int linear_split_plan(int M, int N, int K, size_t max_floats, int* cfg) {
     if (K % LIN_BK != 0 || N % 8 != 0) return 1;
     for (int ks = 2; ks <= 4; ks <<= 1) {
         if (nst % ks || nst / ks < 8 || (size_t)M * N * ks > max_floats) continue;
-        double t;
-        const int c = linear_pick(M, N, nst / ks, ks, 0, &t);
-        t += (double)M * N * ks * 8.0 / 3e6;
-        if (t < 0.95 * best_t) { best = ks; best_t = t; *cfg = c; }
+        for (int c = 0; c < LIN_NTILES; ++c) {
+            const double t = linear_estimate(c, M, N, nst / ks, ks) + (double)M * N * ks * 1e-6 * (LIN_TILES[c].part + 0.45);
+            if (t < best_t) { best = ks; best_t = t; *cfg = c; }
+        }
     }
     return best;
 }

@@ -170,6 +170,31 @@ def test_linear_every_tile(B, M, N, K, height, width):
     _one_step(_host(act), OS.round_bf16(OS.swiglu(OS.linear(a, w[:N]), up)), "swiglu")
 
 
+# (rows, rows of w, contraction) for which the library takes the tile named, ragged in both directions; the last is cut into two launches
+LIN_CHOSEN = [("64x64", 100, 1008, 64), ("64x64", 100, 48, 64), ("64x128", 250, 4112, 64), ("96x128", 900, 3008, 64), ("160x128", 1500, 3008, 320),
+              ("128x256", 2050, 3008, 320), ("192x256", 2500, 4112, 320), ("224x256", 3000, 4112, 320), ("160x256", 3300, 3008, 320),
+              ("192x128", 1300, 4112, 640), ("128x192", 500, 12288, 320), ("64x96", 70, 12288, 4096), ("256x128", 1850, 4080, 4096),
+              ("256x256 + 64x64", 1400, 22016, 4096)]
+
+
+@pytest.mark.parametrize("tile,M,N,K", LIN_CHOSEN)
+def test_linear_chosen_tiles(B, tile, M, N, K):
+    """Every tile the estimate can choose, with both kinds of epilogue, against float32 products of the same bf16 values."""
+    g = torch.Generator(device="cuda"); g.manual_seed(M + N)
+    rnd = lambda *sh: torch.randn(*sh, generator=g, device="cuda")
+    a, w, r = rnd(M, K).bfloat16(), (2.0 * rnd(N, K) / np.sqrt(K)).bfloat16(), rnd(M, N).bfloat16()
+    prod = a.float() @ w.float().t()
+    out = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    act = torch.full((M, N // 2), 7.0, dtype=torch.bfloat16, device="cuda")
+    B.d3tom_linear(a, w, B.D3TOM_LINEAR_RESIDUAL, out, residual=r)
+    B.d3tom_linear(a, w, B.D3TOM_LINEAR_SWIGLU, act)
+    for got, ref in ((out, prod + r.float()), (act, torch.nn.functional.silu(prod[:, :N // 2]) * prod[:, N // 2:])):
+        # one bf16 step and the two sides' float32 sums, as in _one_step
+        excess = ((got.float() - ref).abs() - 2.0 ** -7 * ref.abs()).max().item()
+        assert excess <= 1e-3 * ref.square().mean().sqrt().item(), (tile, excess)
+        assert (got == ref.bfloat16()).float().mean().item() > 0.97
+
+
 def test_linear_two_launch_plan(B):
     """Shapes whose 256-row tiles fill one round of the chip and a bit: the library cuts the columns into a
     full round of tall tiles and a remainder with smaller tiles (two launches, one result)."""
