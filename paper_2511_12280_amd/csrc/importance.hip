@@ -178,7 +178,8 @@ __global__ __launch_bounds__(256, IMP_SUB_STATS == 6 ? 3 : 2) void imp_stats_bf1
     const int nblk = (D + 15) >> 4;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     char* qs = smem;                                                    // the decider rows
-    float2* wstat = reinterpret_cast<float2*>(smem + min(DPAD, IMP_QROWS) * DH * 2);   // [4][IMP_QROWS]
+    float2* wstat = reinterpret_cast<float2*>(smem + min(DPAD, IMP_QROWS) * DH * 2);   // [4 waves][4 key groups][min(DPAD, IMP_QROWS)]
+    const int wrows = min(DPAD, IMP_QROWS);
 
     ImpQueries<DH> queries;
     queries.positions(dec, 0, D, N, min(nblk, IMP_QBLK));
@@ -193,59 +194,58 @@ __global__ __launch_bounds__(256, IMP_SUB_STATS == 6 ? 3 : 2) void imp_stats_bf1
     __syncthreads();
     if (b0 + IMP_QBLK < nblk) queries.positions(dec, (b0 + IMP_QBLK) * 16, D, N, min(nblk - b0 - IMP_QBLK, IMP_QBLK));
     imp_for_blocks<DH, true>(qs, nb, r, g, [&](int blk, const bf16x8 (&qf)[KS]) {
-        // acc[s][e]: scaled logit of decider row (b0+blk)*16 + 4g + e and key column r of sub-tile s
+        // acc[s][e]: logit of decider (b0 + blk) * 16 + r and key 4 g + e of sub-tile s
         f32x4 acc[IMP_SUB_STATS];
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
             for (int s = 0; s < IMP_SUB_STATS; ++s) {
                 const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-                acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[kk], kf[s][kk], kk ? acc[s] : zero, 0, 0, 0);
+                acc[s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[s][kk], qf[kk], kk ? acc[s] : zero, 0, 0, 0);
             }
-#pragma unroll
-        for (int s = 0; s < IMP_SUB_STATS; ++s) acc[s] *= scale2;
         if (ragged) {
 #pragma unroll
             for (int s = 0; s < IMP_SUB_STATS; ++s)
-                if (wave_key + s * 16 + r >= N) acc[s] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-        }
-        if constexpr (KEEP) {
-            // [key block][head][decider][key in block]: the 16 lanes of a decider row write 64 contiguous bytes
-#pragma unroll
-            for (int s = 0; s < IMP_SUB_STATS; ++s) {
-                const int kb = (key_base >> 4) + wave * IMP_SUB_STATS + s;
-                const int row0 = (b0 + blk) * 16 + 4 * g;
-                float* lp = logits + (((size_t)(b * NKB + kb) * H + h) * max_D + row0) * 16 + r;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (row0 + e < D) lp[e * 16] = acc[s][e];
+                    if (wave_key + s * 16 + 4 * g + e >= N) acc[s][e] = -INFINITY;
+        }
+        if constexpr (KEEP) {
+            // [key block][head][decider][key in block]: a lane stores four keys of its decider, a wave 1 KB in one piece
+            const int row = (b0 + blk) * 16 + r;
+#pragma unroll
+            for (int s = 0; s < IMP_SUB_STATS; ++s) {
+                acc[s] *= scale2;
+                const int kb = (key_base >> 4) + wave * IMP_SUB_STATS + s;
+                if (row < D) *reinterpret_cast<f32x4*>(logits + (((size_t)(b * NKB + kb) * H + h) * max_D + row) * 16 + 4 * g) = acc[s];
             }
         }
-        // max over this wave's keys first (in-lane, then the 16 key columns), then one exp2 per logit
-        float mx[4], zz[4];
+        // maximum of this lane's keys first, then one exp2 per logit; lanes and waves meet at the end
+        float m = acc[0][0];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            float m = acc[0][e];
+        for (int s = 0; s < IMP_SUB_STATS; ++s)
 #pragma unroll
-            for (int s = 1; s < IMP_SUB_STATS; ++s) m = fmaxf(m, acc[s][e]);
-            mx[e] = row16_max(m);
-            const float ref = (mx[e] == -INFINITY) ? 0.f : mx[e];       // no key at all: the sum stays 0
-            zz[e] = 0.f;
+            for (int e = 0; e < 4; ++e) m = fmaxf(m, acc[s][e]);
+        const float scl = KEEP ? 1.f : scale2, ms = m * scl;
+        const float ref = (m == -INFINITY) ? 0.f : ms;                  // no key at all: the sum stays 0
+        float z = 0.f;
 #pragma unroll
-            for (int s = 0; s < IMP_SUB_STATS; ++s) zz[e] += __builtin_amdgcn_exp2f(acc[s][e] - ref);
-        }
+        for (int s = 0; s < IMP_SUB_STATS; ++s)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            zz[e] = row16_sum(zz[e]);
-            if (r == 0) wstat[wave * IMP_QROWS + blk * 16 + 4 * g + e] = make_float2(mx[e], zz[e]);
-        }
+            for (int e = 0; e < 4; ++e) z += __builtin_amdgcn_exp2f(KEEP ? acc[s][e] - ref : __builtin_fmaf(acc[s][e], scale2, -ref));
+        wstat[(wave * 4 + g) * wrows + blk * 16 + r] = make_float2(ms, z);
     });
     __syncthreads();
     for (int t = threadIdx.x; t < nb * 16; t += 256) {
-        float2 a = wstat[t];
+        float2 a[16];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) lse2_combine_fast(a.x, a.y, wstat[w * IMP_QROWS + t].x, wstat[w * IMP_QROWS + t].y);
-        part[((size_t)(b * H + h) * NCH + chunk) * DPAD + b0 * 16 + t] = a;
+        for (int w = 0; w < 16; ++w) a[w] = wstat[w * wrows + t];
+        float m = a[0].x, z = 0.f;
+#pragma unroll
+        for (int w = 1; w < 16; ++w) m = fmaxf(m, a[w].x);              // finite: the chunk's first key exists
+#pragma unroll
+        for (int w = 0; w < 16; ++w) z += a[w].y * __builtin_amdgcn_exp2f(a[w].x - m);
+        part[((size_t)(b * H + h) * NCH + chunk) * DPAD + b0 * 16 + t] = make_float2(m, z);
     }
     }
 }
@@ -571,7 +571,7 @@ int d3tom::importance_run(const void* q, const void* k, int dt,
         float* logits = (float*)(wsb + w.logit_off);
         // the decider rows and each wave's statistics (or the log-sum-exps)
         const int qrows = w.DPAD < IMP_QROWS ? w.DPAD : IMP_QROWS;
-        const size_t lds1 = (size_t)qrows * dh * 2 + 4 * IMP_QROWS * sizeof(float2), lds2 = (size_t)qrows * dh * 2 + w.DPAD * sizeof(float);
+        const size_t lds1 = (size_t)qrows * (dh * 2 + 16 * sizeof(float2)), lds2 = (size_t)qrows * dh * 2 + w.DPAD * sizeof(float);
 #define D3TOM_IMP_STATS(DHV, KEEPV, SUBV)                                                                     \
     D3TOM_LAUNCH(IMP_STATS, st, (imp_stats_bf16<DHV, KEEPV, SUBV><<<g1, 256, lds1, st>>>(                        \
         qq, kk, H, scale2, seq_off, dec_idx, dec_off, max_D, w.DPAD, w.NCH, part, w.NKB, logits)))
