@@ -66,14 +66,6 @@ __device__ __forceinline__ att_short4 lds_read_tr16(const char* p) {
 }
 
 #if defined(__HIP_DEVICE_COMPILE__)
-// One wave-wide direct load HBM/L2 -> LDS: lane i fetches 16 bytes at byte offset `voff` of the buffer
-// (zeros when that is past the end of the buffer) into LDS byte lds_base + 16 i.  Issued from inline
-// assembly on purpose: the waits for these loads are placed by hand (wait_loads), and the
-// compiler, when it sees such a load, makes every later transposing LDS read wait for all of them.
-__device__ __forceinline__ void att_direct_load(__amdgpu_buffer_rsrc_t rsrc, int voff, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :: "s"(lds_base), "v"(voff), "s"(rsrc) : "memory", "m0");
-}
 // the two lanes (l, l ^ 32) that share a query column combine their values: after the swap of the upper
 // half of one copy with the lower half of the other, the two results hold {own, partner} in some order
 __device__ __forceinline__ float att_pair_max(float x) {
@@ -186,8 +178,8 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     const uint32_t wave_lds = ring0 + wave * LD * 1024;
     auto issue_one = [&](int j, int i) {        // one of the 2 LD loads of stage j
         const uint32_t dst = wave_lds + (j % NS) * STAGE + (i >> 1) * 1024;
-        if (i & 1) att_direct_load(rv, v_off[i >> 1] + (j > 0 ? j - 1 : 0) * ATT_BK * row_bytes, dst + TILE);
-        else att_direct_load(rk, k_off[i >> 1] + j * ATT_BK * row_bytes, dst);
+        if (i & 1) direct_load_16(rv, v_off[i >> 1] + (j > 0 ? j - 1 : 0) * ATT_BK * row_bytes, dst + TILE);
+        else direct_load_16(rk, k_off[i >> 1] + j * ATT_BK * row_bytes, dst);
     };
     auto issue = [&](int j) {
 #pragma unroll
@@ -323,7 +315,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 #pragma unroll
     for (int i = 0; i < QLD; ++i) {
         const int x = i * RPI + lane / NCHK;
-        att_direct_load(rq, (q0 + x) * row_bytes + (((lane % NCHK) ^ row_swizzle(x)) << 4), ring0 + q_lds + i * 1024);
+        direct_load_16(rq, (q0 + x) * row_bytes + (((lane % NCHK) ^ row_swizzle(x)) << 4), ring0 + q_lds + i * 1024);
     }
     issue(0);
     issue(1);
@@ -478,12 +470,12 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
     auto issue_k = [&](int key0) {
         const int kofs = key0 * row_bytes;
 #pragma unroll
-        for (int i = 0; i < LD; ++i) att_direct_load(rk, k_off[i] + kofs, wave_lds + i * RPI * ROWB);
+        for (int i = 0; i < LD; ++i) direct_load_16(rk, k_off[i] + kofs, wave_lds + i * RPI * ROWB);
     };
     auto issue_v = [&](int key0) {
         const int kofs = key0 * row_bytes;
 #pragma unroll
-        for (int i = 0; i < LD; ++i) att_direct_load(rv, v_off[i] + kofs, wave_lds + TILE + i * RPI * ROWB);
+        for (int i = 0; i < LD; ++i) direct_load_16(rv, v_off[i] + kofs, wave_lds + TILE + i * RPI * ROWB);
     };
     int k_addr[KS];
 #pragma unroll

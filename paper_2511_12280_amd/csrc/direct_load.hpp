@@ -16,6 +16,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_uniform_rsrc(const void* 
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
     return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), 0, (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
 }
+// One wave-wide direct load HBM/L2 -> LDS: lane i fetches 16 bytes at byte offset `voff` of the buffer
+// (zeros when that is past the end of the buffer) into LDS byte lds_base + 16 i.  Issued from inline
+// assembly on purpose: the waits for these loads are placed by hand (wait_loads), and the
+// compiler, when it sees such a load, makes every later transposing LDS read wait for all of them.
+__device__ __forceinline__ void direct_load_16(__amdgpu_buffer_rsrc_t rsrc, int voff, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :: "s"(lds_base), "v"(voff), "s"(rsrc) : "memory", "m0");
+}
 #endif
 
 template <int N>

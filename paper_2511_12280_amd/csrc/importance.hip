@@ -7,17 +7,17 @@
 // the D x N x H logits of the first sweep and finish from those (imp_scores_from_logits):
 //
 //   sweep 1 (stats)   per (head, decider): running max and sum of exp2 over all keys, computed per
-//                     512-key chunk by one workgroup each and combined later in a fixed order
+//                     chunk of keys by one workgroup each and combined later in a fixed order
 //   sweep 2 (scores)  per (head, visual key): sum over deciders of exp2(logit - logsumexp), one row
 //                     per head; a small third kernel adds the H rows in head order (no atomics)
 //
-// bf16 path: logits on MFMA 16x16x32 (rows = 16 deciders, cols = 16 keys, contraction = dh), the keys
-// read straight from HBM/L2 in the MFMA operand layout, the decider rows through LDS.  K is streamed twice, the second time
-// usually from the memory-side cache; with many deciders (64 and up) the exp2 / max arithmetic per logit
-// becomes a comparable share of the run time.
+// bf16 path: logits on MFMA 16x16x32.  Either a workgroup has its keys in registers, read straight from HBM/L2 in the MFMA operand
+// layout, and the decider rows pass through LDS; or (large launches with many deciders) the decider rows are in registers and the keys
+// pass through LDS.  K is streamed twice, the second time from the memory-side cache if it fits.
 //
 // The generic path (any float type / head size) is a kernel pair in plain float arithmetic.
 #include <mutex>
+#include <type_traits>
 #include "internal.hpp"
 #include "direct_load.hpp"
 
@@ -25,23 +25,39 @@ namespace d3tom {
 
 // Keys per workgroup: 4 waves x SUB sub-tiles x 16.  Every workgroup fetches the decider rows of its head, so few large chunks (one
 // workgroup per CU at 3.7k tokens x 32 heads) beat many small ones; when 512-key chunks would leave CUs idle (short sequences)
-// the first sweep takes 256-key chunks instead (8.5 instead of 11.5 us at 1152 tokens).  With several rounds of workgroups and
-// more deciders than keep their logits, 384-key chunks fit three workgroups on a CU instead of two: one computes while another's
-// keys arrive (16 samples of 2688 tokens, 132 deciders on average: 150 -> 122 us; all at once, loads and arithmetic added
-// up).  The second sweep has no statistics to amortise: 384 keys there too, 256 otherwise (256 x 64 deciders x 32 heads: 11.3 -> 9.8 us).
-constexpr int IMP_KC_STATS = 512, IMP_KC_MANY = 384;
+// the first sweep takes 256-key chunks instead (8.5 instead of 11.5 us at 1152 tokens).  The second sweep has no statistics to
+// amortise: 256 (x 64 deciders x 32 heads: 11.3 -> 9.8 us).  With several rounds of such workgroups and more deciders than keep
+// their logits, loads and arithmetic of a workgroup that fetches all its keys at once add up: there the keys stream
+// through LDS (imp_stream_bf16).
+constexpr int IMP_KC_STATS = 512, IMP_KC_SCORES = 256;
 constexpr long IMP_MANY = 1024;        // 512-key chunks from which on a launch counts as several rounds
+constexpr int IMP_STREAM_KEYS = 4096, IMP_STREAM_HEADS = 1024;     // a chunk's rows are addressed with 32-bit byte offsets
+// Streaming launches: from how many deciders on, workgroups they should have, keys of a workgroup at least (the decider rows and the
+// first stages are paid once in each).  Both sweeps, 384 keys at once / streaming: 16 samples of 1200 .. 2300 tokens, at most 38 deciders 97 /
+// 104 us, 77 105 / 113, 127 111 / 116, 254 167 / 149; 10 samples, 74 58 / 63, 225 97 / 86: with few of them the sweeps are bound by the keys,
+// of which the other form has more in flight.  16 samples of 2688 tokens, 169 deciders on average: 512 workgroups 188 us, 1024 182, 1536
+// 186, 3072 226; ragged ones, 1024 157, 1536 149.
+constexpr int IMP_STREAM_D = 128, IMP_STREAM_WGS = 1536, IMP_STREAM_MIN = 448;
 
 constexpr int IMP_KEEP_MAXD_WS = 32;   // largest decider set whose logits are kept (workspace is sized for it)
 struct ImpWs {
     size_t part_off, sp_off, c_off, logit_off, total;
     int KC, KCS, NCH, NCHV, DPAD, VPAD, NKB;
+    bool many;
 };
 __host__ inline ImpWs imp_ws_layout(int B, int max_N, int max_V, int H, int max_D, bool many) {
     ImpWs w;
     const long chunks = (long)ceil_div(max_N, IMP_KC_STATS) * H * B;
-    w.KC = many ? IMP_KC_MANY : chunks < 256 ? IMP_KC_STATS / 2 : IMP_KC_STATS;       // keys per chunk of the first sweep
-    w.KCS = many ? IMP_KC_MANY : 256;                                                 // ... of the second
+    // keys per chunk of the first sweep and of the second
+    auto stream_chunk = [&](int keys) {
+        const int want = ceil_div(IMP_STREAM_WGS, H * B < IMP_STREAM_WGS ? H * B : IMP_STREAM_WGS), most = keys < 2 * IMP_STREAM_MIN ? 1 : keys / IMP_STREAM_MIN;
+        const int cuts = want < most ? want : most;
+        const int c = ceil_div(ceil_div(keys, cuts), 64) * 64;
+        return c < IMP_STREAM_KEYS ? c : IMP_STREAM_KEYS;
+    };
+    w.many = many;
+    w.KC = many ? stream_chunk(max_N) : chunks < 256 ? IMP_KC_STATS / 2 : IMP_KC_STATS;
+    w.KCS = many ? stream_chunk(max_V) : IMP_KC_SCORES;
     w.NCH = ceil_div(max_N, w.KC);
     w.NCHV = ceil_div(max_V, w.KCS);
     w.DPAD = ceil_div(max_D, 16) * 16;
@@ -56,13 +72,14 @@ __host__ inline ImpWs imp_ws_layout(int B, int max_N, int max_V, int H, int max_
     w.total = o;
     return w;
 }
-// Smaller chunks mean more statistics (a third more): not where only they would push the layout out of the library's static array.
+// The two forms pad statistics and per-head rows differently: where only one of them fits the library's static array, it is that one.
 // Both entry points follow this rule, so that their scores are the same bits.
 __host__ inline ImpWs imp_ws_layout(int B, int max_N, int max_V, int H, int max_D) {
     const ImpWs w = imp_ws_layout(B, max_N, max_V, H, max_D, false);
-    if ((long)ceil_div(max_N, IMP_KC_STATS) * H * B < IMP_MANY || max_D <= IMP_KEEP_MAXD_WS) return w;
+    if ((long)ceil_div(max_N, IMP_KC_STATS) * H * B < IMP_MANY || max_D <= IMP_KEEP_MAXD_WS || H > IMP_STREAM_HEADS) return w;
     const ImpWs m = imp_ws_layout(B, max_N, max_V, H, max_D, true);
     const size_t lim = D3TOM_IMPORTANCE_STATIC_BYTES;
+    if (max_D <= IMP_STREAM_D) return (w.total > lim && m.total <= lim) ? m : w;
     return (m.total > lim && w.total <= lim) ? w : m;
 }
 size_t importance_ws_bytes(int B, int max_N, int max_V, int H, int dh, int max_D) {
@@ -158,7 +175,7 @@ __device__ __forceinline__ void imp_for_blocks(const char* lds, int nblk, int r,
 
 // (running max, running sum of exp2) of decider rows over one chunk of IMP_SUB_STATS x 64 keys of one head
 template <int DH, bool KEEP, int IMP_SUB_STATS>
-__global__ __launch_bounds__(256, IMP_SUB_STATS == 6 ? 3 : 2) void imp_stats_bf16(
+__global__ __launch_bounds__(256, 2) void imp_stats_bf16(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int H, float scale2,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ dec_idx, const int32_t* __restrict__ dec_off,
     int max_D, int DPAD, int NCH, float2* __restrict__ part, int NKB, float* __restrict__ logits) {
@@ -251,13 +268,13 @@ __global__ __launch_bounds__(256, IMP_SUB_STATS == 6 ? 3 : 2) void imp_stats_bf1
 }
 
 // per-head score rows: sp[h][j] = sum over deciders of exp2(logit - log2sumexp2)
-template <int DH, int IMP_SUB_SCORES>
-__global__ __launch_bounds__(256, IMP_SUB_SCORES == 4 ? 4 : 3) void imp_scores_bf16(
+template <int DH>
+__global__ __launch_bounds__(256, 4) void imp_scores_bf16(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int H, float scale2,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ dec_idx, const int32_t* __restrict__ dec_off,
     const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count,
     int max_D, int max_V, int DPAD, int NCH, int KC, int VPAD, const float2* __restrict__ part, float* __restrict__ sp) {
-    constexpr int KS = DH / 32, KCS = IMP_SUB_SCORES * 64;
+    constexpr int KS = DH / 32, IMP_SUB_SCORES = 4, KCS = IMP_SUB_SCORES * 64;
     // heads vary fastest over the grid: workgroups that run together read neighbouring 2*DH-byte pieces of the same key rows
     const int h = blockIdx.x, chunk = blockIdx.y, b = blockIdx.z;
     int tok0 = seq_off[b], tok1 = seq_off[b + 1], d0 = dec_off[b], d1 = dec_off[b + 1], vs0 = vis_start[b], vc = vis_count[b];
@@ -332,6 +349,208 @@ __global__ __launch_bounds__(256, IMP_SUB_SCORES == 4 ? 4 : 3) void imp_scores_b
         v += __shfl_xor(v, 32, WAVE);
         if (g == 0) sp_row[key_base + (wave * IMP_SUB_SCORES + s) * 16 + r] = v;
     }
+}
+
+// Both sweeps of large launches: the keys of a chunk go through a ring of 64-key stages in LDS, the decider rows stay in registers, a
+// quarter of the 16-decider blocks per wave.  Key loads run beside the arithmetic, each key row is fetched once per workgroup, each
+// decider row once, and the statistics of a decider live in one lane column from the first key to the last.
+//   SCORES = false: D = K Q^T, lane (r, g) = decider r, keys 4 g + e of every 16: running maximum and sum over the chunk
+//   SCORES = true:  D = Q K^T, lane (r, g) = key r, deciders 4 g + e: sum over the deciders; the four waves' sums of a stage meet in LDS
+// 16 samples of 2688 tokens, 169 deciders on average: 115 -> 98 and 99 -> 77 us, 3.6 and 3.9 TB/s.  The loads alone take 58 us, the
+// arithmetic alone 75 (480 clocks per block and stage for two waves of a SIMD, 452 of them vector issue); together the card's clock
+// falls to 1.63 GHz, and the order of heavy and light samples no longer matters.
+constexpr int IMP_NS = 4;                   // stages in the ring
+constexpr float IMP_NONE = -3.0e38f;        // the maximum of no logits
+constexpr int IMP_WBLK = D3TOM_MAX_DECIDERS / 64;      // 16-decider blocks of a wave at most
+template <int DH, bool SCORES>
+__global__ __launch_bounds__(256, 2) void imp_stream_bf16(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, int H, float scale2,
+    const int32_t* __restrict__ seq_off, const int32_t* __restrict__ dec_idx, const int32_t* __restrict__ dec_off,
+    const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count,
+    int max_D, int max_V, int DPAD, int NCH, int KC, int KCS, int VPAD, float2* __restrict__ part, float* __restrict__ sp) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int KS = DH / 32, ROWB = DH * 2, NCHK = DH / 8, RPI = 64 / NCHK, LD = 64 / RPI / 4, STAGE = 64 * ROWB;
+    __shared__ __attribute__((aligned(16))) char ring[IMP_NS * STAGE];
+    __shared__ float c_lds[SCORES ? D3TOM_MAX_DECIDERS : 1];            // log2-sum-exp2 of the deciders
+    __shared__ float sums[SCORES ? 2 : 1][4][64];                       // [stage parity][wave][key]
+    // heads vary fastest over the grid: workgroups that run together read neighbouring 2*DH-byte pieces of the same key rows
+    const int h = blockIdx.x, chunk = blockIdx.y, b = blockIdx.z;
+    int tok0 = seq_off[b], tok1 = seq_off[b + 1], d0 = dec_off[b], d1 = dec_off[b + 1], vs0 = vis_start[b], vc = vis_count[b];
+    request_together(tok0, tok1, d0, d1, vs0, vc);
+    const int N = min(tok1 - tok0, NCH * KC);                         // the workspace holds NCH chunks per head
+    const int D = min(d1 - d0, max_D);
+    const int32_t* dec = dec_idx + d0;
+    const int vs = min(max(vs0, 0), N);
+    const int V = min(min(vc, max_V), N - vs);
+    const int key_base = chunk * (SCORES ? KCS : KC);
+    const int keys = SCORES ? min(V - key_base, KCS) : min(N - key_base, KC);      // of this chunk
+    if (keys <= 0 || D <= 0) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    const int nblk = (D + 15) >> 4;
+    // this wave's blocks: w0, w0 + 4, ...; which wave has one more than others goes by the head
+    const int w0 = (wave + h) & 3, nb = (nblk - w0 + 3) >> 2;
+
+    const int row_bytes = H * ROWB;
+    const __amdgpu_buffer_rsrc_t rk = make_uniform_rsrc(k + ((size_t)(tok0 + (SCORES ? vs : 0) + key_base) * H + h) * DH,
+                                                        (uint32_t)(keys - 1) * (uint32_t)row_bytes + ROWB);    // rows past the chunk read as 0
+    auto swizzle = [](int x) { return DH == 128 ? (x & 15) : ((x >> 1) & 7); };
+    const uint32_t ring0 = (uint32_t)(size_t)(lds_ptr_t)ring;
+    int k_off[LD];
+#pragma unroll
+    for (int i = 0; i < LD; ++i) {
+        const int x = (wave * LD + i) * RPI + lane / NCHK;
+        k_off[i] = x * row_bytes + (((lane % NCHK) ^ swizzle(x)) << 4);
+    }
+    auto issue = [&](int j) {
+#pragma unroll
+        for (int i = 0; i < LD; ++i)
+            direct_load_16(rk, k_off[i] + j * 64 * row_bytes, ring0 + (j % IMP_NS) * STAGE + (wave * LD + i) * 1024);
+    };
+    int pos[IMP_WBLK];
+#pragma unroll
+    for (int i = 0; i < IMP_WBLK; ++i) pos[i] = min(max(dec[min((w0 + 4 * i) * 16 + r, D - 1)], 0), N - 1);
+    issue(0);
+    issue(1);
+    issue(2);
+    static_assert(IMP_NS == 4, "three stages ahead");
+    bf16x8 qf[IMP_WBLK][KS];
+#pragma unroll
+    for (int i = 0; i < IMP_WBLK; ++i)
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk)
+            qf[i][kk] = *reinterpret_cast<const bf16x8*>(q + ((size_t)(tok0 + pos[i]) * H + h) * DH + kk * 32 + g * 8);
+    f32x4 cc[IMP_WBLK];                     // SCORES: log2-sum-exp2 of deciders 4 g + e of each block
+    if constexpr (SCORES) {
+        const int nch = (N + KC - 1) / KC;
+        for (int t = threadIdx.x; t < nblk * 16; t += 256) {
+            const float2* p = part + ((size_t)(b * H + h) * NCH) * DPAD + t;
+            float m = -INFINITY, z = 0.f;
+            for (int c0 = 0; c0 < nch; c0 += 4) {          // 4 independent loads in flight, combined in order
+                float2 a[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) a[u] = p[(size_t)min(c0 + u, nch - 1) * DPAD];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (c0 + u < nch) lse2_combine_fast(m, z, a[u].x, a[u].y);
+            }
+            c_lds[t] = t < D ? m + __builtin_amdgcn_logf(z) : INFINITY;     // padded rows contribute exp2(-inf) = 0
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < IMP_WBLK; ++i) cc[i] = *reinterpret_cast<const f32x4*>(c_lds + min(w0 + 4 * i, nblk - 1) * 16 + 4 * g);
+    }
+    // running maximum of the raw logits (a value below every logit until there is one) and sum, of this lane's keys
+    float m[IMP_WBLK], z[IMP_WBLK];
+#pragma unroll
+    for (int i = 0; i < IMP_WBLK; ++i) { m[i] = IMP_NONE; z[i] = 0.f; }
+    int f_addr[KS];
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) f_addr[kk] = r * ROWB + (((kk * 4 + g) ^ swizzle(r)) << 4);
+    float* sp_row = sp + (size_t)(b * H + h) * VPAD + key_base;
+
+    const int nst = (keys + 63) >> 6;
+    // one loop for each number of blocks, without branches between them
+    auto sweep = [&](auto nb_c) {
+    constexpr int NB = decltype(nb_c)::value;
+#pragma unroll 1
+    for (int j = 0; j < nst; ++j) {
+        // stage j is there (later ones stay in flight), and everybody is done with stage j - 1
+        wait_loads<2 * LD>();
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        phase_barrier();
+        issue(j + 3);                       // past the last stage: rows of the buffer's end, zeros
+        if (SCORES && j > 0 && wave == (j & 3)) {
+            const float* s = &sums[(j - 1) & 1][0][lane];
+            sp_row[(j - 1) * 64 + lane] = (s[0] + s[64]) + (s[128] + s[192]);
+        }
+        const char* st = ring + (j % IMP_NS) * STAGE;
+        bf16x8 kf[4][KS];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) kf[s][kk] = *reinterpret_cast<const bf16x8*>(st + s * 16 * ROWB + f_addr[kk]);
+        const bool ragged = !SCORES && (j + 1) * 64 > keys;
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            f32x4 acc[4];
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                    acc[s] = SCORES ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(qf[i][kk], kf[s][kk], kk ? acc[s] : zero, 0, 0, 0)
+                                    : __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[s][kk], qf[i][kk], kk ? acc[s] : zero, 0, 0, 0);
+                }
+            if constexpr (SCORES) {
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[s] += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[s][e], scale2, -cc[i][e]));
+            } else {
+                if (ragged) {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (j * 64 + s * 16 + 4 * g + e >= keys) acc[s][e] = -INFINITY;
+                }
+                float t = m[i];
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) t = fmaxf(t, acc[s][e]);
+                float zi = z[i] * __builtin_amdgcn_exp2f((m[i] - t) * scale2);
+                m[i] = t;
+                const float ms = t > IMP_NONE ? t * scale2 : 0.f;      // no key yet: the sum stays 0
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) zi += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[s][e], scale2, -ms));
+                z[i] = zi;
+            }
+        }
+        if constexpr (SCORES) {
+            // over the four lane groups: after the exchanges lane l has the sum of key l of the stage
+            typedef unsigned u2 __attribute__((ext_vector_type(2)));
+            auto swap_add = [](float a, float c, bool wide) {
+                const u2 x = wide ? __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(c), false, false)
+                                  : __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(c), false, false);
+                return __uint_as_float(x[0]) + __uint_as_float(x[1]);
+            };
+            sums[j & 1][wave][lane] = swap_add(swap_add(v[0], v[2], true), swap_add(v[1], v[3], true), false);
+        }
+    }
+    };
+    static_assert(IMP_WBLK == 4, "five cases");
+    switch (nb) {
+        case 0: sweep(std::integral_constant<int, 0>()); break;
+        case 1: sweep(std::integral_constant<int, 1>()); break;
+        case 2: sweep(std::integral_constant<int, 2>()); break;
+        case 3: sweep(std::integral_constant<int, 3>()); break;
+        default: sweep(std::integral_constant<int, 4>());
+    }
+    wait_loads<0>();                        // nothing may be in flight into LDS when the workgroup ends
+    if constexpr (SCORES) {
+        __syncthreads();
+        if (wave == (nst & 3)) {
+            const float* s = &sums[(nst - 1) & 1][0][lane];
+            sp_row[(nst - 1) * 64 + lane] = (s[0] + s[64]) + (s[128] + s[192]);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < IMP_WBLK; ++i) {
+            if (i >= nb) break;
+            float mq = m[i], zq;
+            mq = fmaxf(mq, __shfl_xor(mq, 16, WAVE));
+            mq = fmaxf(mq, __shfl_xor(mq, 32, WAVE));
+            zq = z[i] * __builtin_amdgcn_exp2f((m[i] - mq) * scale2);
+            zq += __shfl_xor(zq, 16, WAVE);
+            zq += __shfl_xor(zq, 32, WAVE);
+            if (g == 0) part[((size_t)(b * H + h) * NCH + chunk) * DPAD + (w0 + 4 * i) * 16 + r] = make_float2(mq * scale2, zq);
+        }
+    }
+#endif
 }
 
 // Small decider sets (at most IMP_KEEP_MAXD): the first sweep also writes its scaled logits, D x N x H
@@ -572,18 +791,25 @@ int d3tom::importance_run(const void* q, const void* k, int dt,
         // the decider rows and each wave's statistics (or the log-sum-exps)
         const int qrows = w.DPAD < IMP_QROWS ? w.DPAD : IMP_QROWS;
         const size_t lds1 = (size_t)qrows * (dh * 2 + 16 * sizeof(float2)), lds2 = (size_t)qrows * dh * 2 + w.DPAD * sizeof(float);
+#define D3TOM_IMP_STREAM(ID, GRID, DHV, SCORESV)                                                              \
+    D3TOM_LAUNCH(ID, st, (imp_stream_bf16<DHV, SCORESV><<<GRID, 256, 0, st>>>(                                   \
+        qq, kk, H, scale2, seq_off, dec_idx, dec_off, vis_start, vis_count, max_D, max_V, w.DPAD, w.NCH, w.KC, w.KCS, w.VPAD, part, sp)))
 #define D3TOM_IMP_STATS(DHV, KEEPV, SUBV)                                                                     \
     D3TOM_LAUNCH(IMP_STATS, st, (imp_stats_bf16<DHV, KEEPV, SUBV><<<g1, 256, lds1, st>>>(                        \
         qq, kk, H, scale2, seq_off, dec_idx, dec_off, max_D, w.DPAD, w.NCH, part, w.NKB, logits)))
-        const bool big = w.KC == IMP_KC_STATS, mid = w.KC == IMP_KC_MANY;
-        if (dh == 128) {
+        const bool big = w.KC == IMP_KC_STATS;
+        if (w.many) {
+            if (dh == 128) { D3TOM_IMP_STREAM(IMP_STATS, g1, 128, false); D3TOM_IMP_STREAM(IMP_SCORES, g2, 128, true); }
+            else           { D3TOM_IMP_STREAM(IMP_STATS, g1, 64, false);  D3TOM_IMP_STREAM(IMP_SCORES, g2, 64, true); }
+        } else if (dh == 128) {
             if (keep) { if (big) D3TOM_IMP_STATS(128, true, 8); else D3TOM_IMP_STATS(128, true, 4); }
-            else      { if (big) D3TOM_IMP_STATS(128, false, 8); else if (mid) D3TOM_IMP_STATS(128, false, 6); else D3TOM_IMP_STATS(128, false, 4); }
+            else      { if (big) D3TOM_IMP_STATS(128, false, 8); else D3TOM_IMP_STATS(128, false, 4); }
         } else {
             if (keep) { if (big) D3TOM_IMP_STATS(64, true, 8); else D3TOM_IMP_STATS(64, true, 4); }
-            else      { if (big) D3TOM_IMP_STATS(64, false, 8); else if (mid) D3TOM_IMP_STATS(64, false, 6); else D3TOM_IMP_STATS(64, false, 4); }
+            else      { if (big) D3TOM_IMP_STATS(64, false, 8); else D3TOM_IMP_STATS(64, false, 4); }
         }
 #undef D3TOM_IMP_STATS
+#undef D3TOM_IMP_STREAM
         if (keep) {
             const dim3 g2k(ceil_div(max_N, 16), B);
             D3TOM_LAUNCH(IMP_SCORES, st, imp_scores_from_logits<false><<<g2k, IMP_FL_THREADS, (size_t)H * max_D * sizeof(float), st>>>(
@@ -591,11 +817,10 @@ int d3tom::importance_run(const void* q, const void* k, int dt,
                 scores));
             return D3TOM_OK;
         }
-#define D3TOM_IMP_SCORES(DHV, SUBV)                                                                           \
-    D3TOM_LAUNCH(IMP_SCORES, st, (imp_scores_bf16<DHV, SUBV><<<g2, 256, lds2, st>>>(                              \
+#define D3TOM_IMP_SCORES(DHV)                                                                                 \
+    D3TOM_LAUNCH(IMP_SCORES, st, (imp_scores_bf16<DHV><<<g2, 256, lds2, st>>>(                                   \
         qq, kk, H, scale2, seq_off, dec_idx, dec_off, vis_start, vis_count, max_D, max_V, w.DPAD, w.NCH, w.KC, w.VPAD, part, sp)))
-        if (dh == 128) { if (w.KCS == 256) D3TOM_IMP_SCORES(128, 4); else D3TOM_IMP_SCORES(128, 6); }
-        else           { if (w.KCS == 256) D3TOM_IMP_SCORES(64, 4);  else D3TOM_IMP_SCORES(64, 6); }
+        if (!w.many) { if (dh == 128) D3TOM_IMP_SCORES(128); else D3TOM_IMP_SCORES(64); }
 #undef D3TOM_IMP_SCORES
         D3TOM_LAUNCH(IMP_FINISH, st, imp_finish_kernel<<<g3, 256, 0, st>>>(
             sp, H, w.VPAD, seq_off, vis_start, vis_count, score_off, max_V, scores));

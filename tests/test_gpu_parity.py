@@ -118,6 +118,22 @@ def test_importance_decider_groups_and_chunks(dh, copies):
         np.testing.assert_array_equal(S[i], S[len(batch) - len(samples) + i])
 
 
+@pytest.mark.parametrize("dh", [64, 128])
+def test_importance_streaming_stages(dh):
+    """Large launches: key and visual counts around the 64-key stages, the four stages in flight and the chunks a sample is cut into,
+    decider counts that leave waves with none to four blocks of 16."""
+    shapes = [(1, 1, 1), (64, 63, 16), (65, 64, 17), (129, 65, 33), (576, 513, 64), (705, 577, 65), (1100, 1024, 256), (1025, 1, 200)]
+    samples = [W.random_case(660 + i, N, 8 * dh, 8, 0, V, D, dtype="bf16") for i, (N, V, D) in enumerate(shapes)]
+    for s, (_, _, D) in zip(samples, shapes):
+        s["dec_idx"] = np.resize(s["dec_idx"], D).astype(np.int32)         # (repeats where there are fewer positions)
+        s["D"] = D
+    batch = samples * 8                                                     # 64 samples x 8 heads, two chunks each
+    S = GpuStep(batch, [max(1, s["V"] // 4) for s in batch], "bf16").importance()
+    for i, s in enumerate(samples):
+        check_scores(S[i], oracle.importance(s["q"], s["k"], s["dec_idx"], s["vis_start"], s["V"]))
+        np.testing.assert_array_equal(S[i], S[len(batch) - len(samples) + i])
+
+
 @pytest.mark.parametrize("dtype,H,dh", [("f32", 4, 64), ("f32", 3, 36), ("bf16", 2, 40), ("f32", 400, 8)])
 def test_importance_generic_kept_logits(dtype, H, dh):
     """Generic kernels: decider counts around the largest set that keeps its logits, key counts around blocks of 16 and 256; with
