@@ -18,6 +18,7 @@
 //             other rows are copied; one store per element, no float atomics
 //
 // All similarities are taken on the rows as given (assignment first, aggregation afterwards).
+#include <type_traits>
 #include "internal.hpp"
 #include "direct_load.hpp"
 
@@ -701,36 +702,30 @@ __global__ __launch_bounds__(256) void merge_scatter_kernel(
                 fill_window(l0);
                 __syncthreads();
             }
+            // as many rows as registers allow requested together, the last ones (each of which would cost a trip of its own) too
+            auto rows = [&](int t, auto n) {
+                constexpr int R = decltype(n)::value;
+                uint4 w[R][CPT];
+#pragma unroll
+                for (int m = 0; m < R; ++m) {
+                    const uint4* row = reinterpret_cast<const uint4*>(xv + (size_t)list[t + m] * d);
+#pragma unroll
+                    for (int u = 0; u < CPT; ++u) w[m][u] = row[cc[u]];
+                }
+#pragma unroll
+                for (int m = 0; m < R; ++m) add_row(acc, w[m]);
+            };
+            constexpr int NB = 8 / CPT;
             int t = 0;
-            if constexpr (CPT == 1)                        // half-row workgroups: registers to spare for 8 rows in flight
-            for (; t + 8 <= ln; t += 8) {
-                uint4 w[8][CPT];
-#pragma unroll
-                for (int m = 0; m < 8; ++m) {
-                    const uint4* row = reinterpret_cast<const uint4*>(xv + (size_t)list[t + m] * d);
-#pragma unroll
-                    for (int u = 0; u < CPT; ++u) w[m][u] = row[cc[u]];
-                }
-#pragma unroll
-                for (int m = 0; m < 8; ++m) add_row(acc, w[m]);
-            }
-            for (; t + 4 <= ln; t += 4) {
-                uint4 w[4][CPT];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const uint4* row = reinterpret_cast<const uint4*>(xv + (size_t)list[t + m] * d);
-#pragma unroll
-                    for (int u = 0; u < CPT; ++u) w[m][u] = row[cc[u]];
-                }
-#pragma unroll
-                for (int m = 0; m < 4; ++m) add_row(acc, w[m]);
-            }
-            for (; t < ln; ++t) {
-                uint4 w[CPT];
-                const uint4* row = reinterpret_cast<const uint4*>(xv + (size_t)list[t] * d);
-#pragma unroll
-                for (int u = 0; u < CPT; ++u) w[u] = row[cc[u]];
-                add_row(acc, w);
+            for (; t + NB <= ln; t += NB) rows(t, std::integral_constant<int, NB>());
+            switch (ln - t) {
+                case 1: rows(t, std::integral_constant<int, 1>()); break;
+                case 2: rows(t, std::integral_constant<int, 2>()); break;
+                case 3: rows(t, std::integral_constant<int, 3>()); break;
+                case 4: if constexpr (NB > 4) rows(t, std::integral_constant<int, 4>()); break;
+                case 5: if constexpr (NB > 4) rows(t, std::integral_constant<int, 5>()); break;
+                case 6: if constexpr (NB > 4) rows(t, std::integral_constant<int, 6>()); break;
+                case 7: if constexpr (NB > 4) rows(t, std::integral_constant<int, 7>()); break;
             }
         }
 #pragma unroll
