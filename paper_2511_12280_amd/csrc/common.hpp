@@ -126,11 +126,6 @@ __device__ __forceinline__ float wave_max(float v) {
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, WAVE));
     return v;
 }
-__device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-    return v;
-}
 
 // Reductions over the 16 lanes of a DPP row (lanes 16 i .. 16 i + 15), every lane ends with the result.
 // Four data-parallel-primitive steps inside the vector ALU (no LDS traffic): swap neighbours, swap

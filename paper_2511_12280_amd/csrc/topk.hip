@@ -9,7 +9,8 @@
 // threshold are taken lowest index first, which makes the selection identical to ranking by
 // (score descending, index ascending).  Integer LDS atomics only: deterministic.
 // Bound by its chain of barriers on one compute unit: this takes 9 of them.  (A digit-by-digit radix selection with one
-// histogram per wave and keys in LDS took about 25: 8.0 us instead of 5.7 at 729 keys, 13.1 instead of 9.9 at 16 x 2304.)
+// histogram per wave and keys in LDS took about 25: 8.0 us instead of 5.7 at 729 keys, 13.1 instead of 9.9 at 16 x 2304.)  Between them
+// exchanges and sums stay in the vector ALU, and the members are ranked sixteen lanes to each (729 keys 5.4 -> 4.4 us, 16 x 2304 8.6 -> 7.8).
 //
 // The selection is a chain of short dependent passes on one compute unit per sample.  Called from the one-call
 // merge layer, the launch carries further workgroups (blockIdx.y > 0) that do not select anything: one wave per
@@ -40,15 +41,41 @@ constexpr int TOPK_PER = D3TOM_MAX_VISUAL / TOPK_THREADS;      // keys per threa
 constexpr int TOPK_BINS = 2048;
 [[maybe_unused]] constexpr int TOPK_CAND = 1024;                                // members of one bin that are ranked directly
 
-// inclusive prefix sum over the 64 lanes of a wave
-__device__ __forceinline__ int wave_incl_scan(int v, int lane) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(v, o, WAVE);
-        if (lane >= o) v += t;
-    }
+// Exchanges between lanes inside the vector ALU (data-parallel moves and row swaps: some 8 clocks a step, a __shfl goes through LDS and
+// takes some 100).
+#if defined(__HIP_DEVICE_COMPILE__)
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ int dpp_move_i(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, ROWS == 0xF); }
+// inclusive prefix sum over the 64 lanes of a wave: inside rows of 16, then the last lane of row 0 (2) to row 1 (3), of row 1 to rows 2, 3
+__device__ __forceinline__ int wave_incl_scan(int v) {
+    v += dpp_move_i<0x111>(v);
+    v += dpp_move_i<0x112>(v);
+    v += dpp_move_i<0x114>(v);
+    v += dpp_move_i<0x118>(v);
+    v += dpp_move_i<0x142, 0xA>(v);
+    v += dpp_move_i<0x143, 0xC>(v);
     return v;
 }
+__device__ __forceinline__ int row16_sum_i(int v) {
+    v += dpp_move_i<0xB1>(v);
+    v += dpp_move_i<0x4E>(v);
+    v += dpp_move_i<0x141>(v);
+    v += dpp_move_i<0x140>(v);
+    return v;
+}
+__device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_incl_scan(v), 63); }
+__device__ __forceinline__ uint32_t wave_min_u(uint32_t v) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    v = min(v, (uint32_t)dpp_move_i<0xB1>((int)v));
+    v = min(v, (uint32_t)dpp_move_i<0x4E>((int)v));
+    v = min(v, (uint32_t)dpp_move_i<0x141>((int)v));
+    v = min(v, (uint32_t)dpp_move_i<0x140>((int)v));
+    u2 r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = min(r[0], r[1]);
+    r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return min(r[0], r[1]);
+}
+#endif
 
 __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
     const float* __restrict__ scores, const int32_t* __restrict__ score_off, const int32_t* __restrict__ keep_k,
@@ -73,14 +100,18 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
     const int b = blockIdx.x;
     int s0 = score_off[b], s1 = score_off[b + 1];
     const int V = min(s1 - s0, max_V);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
 
     // thread t holds keys t, t + 1024, ...
     uint32_t key[TOPK_PER];
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
     const __amdgpu_buffer_rsrc_t mine = make_uniform_rsrc(scores + s0, (uint32_t)max(V, 0) * 4u);       // beyond the sample: 0, not fetched
 #pragma unroll
-    for (int c = 0; c < TOPK_PER; ++c) key[c] = __builtin_amdgcn_raw_buffer_load_b32(mine, (c * TOPK_THREADS + tid) * 4, 0, 0);
+    for (int c = 0; c < 4; ++c) key[c] = __builtin_amdgcn_raw_buffer_load_b32(mine, (c * TOPK_THREADS + tid) * 4, 0, 0);
+    if (V > 4 * TOPK_THREADS) {                   // requests beyond the sample take their turn in the load path too
+#pragma unroll
+        for (int c = 4; c < TOPK_PER; ++c) key[c] = __builtin_amdgcn_raw_buffer_load_b32(mine, (c * TOPK_THREADS + tid) * 4, 0, 0);
+    }
     if (keep_ratio && wave == 15) {
         // kept counts from the ratios, on the device: this sample's count and the prefix sums over the samples
         // in front of it (every workgroup repeats that, a sample per lane; the last one also writes the totals)
@@ -93,10 +124,10 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
                 kcur = Vb > 0 ? keep_count_device(Vb, keep_ratio[bb]) : 0;
                 ncur = (seq_off[bb + 1] - seq_off[bb]) - (Vb - kcur);
             }
-            koff += wave_sum_i(bb < b ? kcur : 0);
-            ooff += wave_sum_i(bb < b ? ncur : 0);
-            kb += wave_sum_i(bb == b ? kcur : 0);
-            nb += wave_sum_i(bb == b ? ncur : 0);
+            koff += wave_total(bb < b ? kcur : 0);
+            ooff += wave_total(bb < b ? ncur : 0);
+            kb += wave_total(bb == b ? kcur : 0);
+            nb += wave_total(bb == b ? ncur : 0);
         }
         if (lane == 0) {
             plan[0] = kb; plan[1] = koff;
@@ -114,11 +145,8 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
             kmin = min(kmin, key[c]); kmax = max(kmax, key[c]);
         }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o, WAVE));
-        kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o, WAVE));
-    }
+    kmin = wave_min_u(kmin);
+    kmax = ~wave_min_u(~kmax);
     if (lane == 0) { wrange[wave] = kmin; wrange[16 + wave] = kmax; }
     __syncthreads();
     if (V <= 0) return;
@@ -149,7 +177,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
         __syncthreads();
         // thread t owns bins 2047 - 2t and 2046 - 2t: keys above its bins = the bins of the threads before it
         const int h0 = hist[TOPK_BINS - 1 - 2 * tid], h1 = hist[TOPK_BINS - 2 - 2 * tid];
-        const int inc = wave_incl_scan(h0 + h1, lane);
+        const int inc = wave_incl_scan(h0 + h1);
         if (lane == 63) wsum[wave] = inc;
         __syncthreads();
         int before = inc - h0 - h1;
@@ -178,9 +206,22 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
             if (j < V && key[c] >= lo && key[c] <= hi) cand[atomicAdd(&sel[3], 1)] = make_uint2(key[c], (uint32_t)j);
         }
         __syncthreads();
-        if (tid < members) {
+        if (members <= TOPK_THREADS / 16) {
+            // sixteen lanes to a member (one to a member: a chain of that many trips to LDS)
+            const int c = tid >> 4;
+            const uint2 me = cand[min(c, members - 1)];
+            int rank = 0;
+#pragma unroll
+            for (int u = 0; u < TOPK_THREADS / 256; ++u) {
+                const int t = u * 16 + (tid & 15);
+                const uint2 o = cand[min(t, members - 1)];
+                rank += (t < members) && ((o.x > me.x) || (o.x == me.x && o.y < me.y));
+            }
+            if (row16_sum_i(rank) == remaining - 1 && c < members) { thr_s[0] = me.x; thr_s[1] = me.y; }
+        } else if (tid < members) {
             const uint2 me = cand[tid];
             int rank = 0;
+#pragma unroll 8
             for (int t = 0; t < members; ++t) {
                 const uint2 o = cand[t];
                 rank += (o.x > me.x) || (o.x == me.x && o.y < me.y);
@@ -230,7 +271,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
     for (int c4 = 0; c4 < TOPK_PER; c4 += 4) {
         if (c4 * TOPK_THREADS >= V) break;
         const int mine = ((c4 * 16 + lane) * 64 < V) ? wcnt[c4 * 16 + lane] : 0;
-        const int inc = wave_incl_scan(mine, lane);
+        const int inc = wave_incl_scan(mine);
         const int exc = inc - mine;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -238,7 +279,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
             if (c * TOPK_THREADS >= V) break;
             const bool keep = kept(c);
             const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
-            const int slot = base + __shfl(exc, u * 16 + wave, WAVE) + __popcll(m & ((1ull << lane) - 1ull));
+            const int slot = base + __builtin_amdgcn_readlane(exc, u * 16 + wave) + __popcll(m & ((1ull << lane) - 1ull));
             const int j = c * TOPK_THREADS + tid;
             if (j < V) {
                 slot_of[s0 + j] = keep ? slot : -1;
@@ -250,7 +291,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
                 if (keep) kept_idx[k0 + slot] = j;
             }
         }
-        base += __shfl(inc, 63, WAVE);
+        base += __builtin_amdgcn_readlane(inc, 63);
     }
 #endif
 }
