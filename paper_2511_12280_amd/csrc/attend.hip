@@ -54,6 +54,7 @@ namespace d3tom {
 
 constexpr int ATT_BK = 64;      // keys per tile
 constexpr int ATT_SLOTS = 4;    // ring slots of one K tile and one V tile
+constexpr int ATT_TURNS_WGS = 32;       // workgroups per XCD that take several tiles in turn: one per compute unit
 
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short att_short4;
 
@@ -108,7 +109,7 @@ __device__ __forceinline__ float key_log2_weight(const KeyWeights& kw, int b, in
 }
 constexpr int ATT_WKEYS = 3584;     // longest sample of the weighted tiled kernel: its log2 weights sit in LDS beside the ring
 
-template <int DH, bool WGT, int NQ>
+template <int DH, bool WGT, int NQ, bool TURNS>
 __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ cu, int H, int nB, int nqt, float scale2, uint16_t* __restrict__ o, KeyWeights kw) {
@@ -125,45 +126,88 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     constexpr int AHEAD = NS - 1;               // the softmax phase of tile j fetches stage j + AHEAD
     constexpr int BQ = NQ * 128;                // queries of the workgroup: NQ blocks of 16 per wave
     constexpr int KPRE = 2 * KS;                // K fragments read ahead: the first 32 keys
+    typedef unsigned att_u4 __attribute__((ext_vector_type(4)));
     extern __shared__ __attribute__((aligned(16))) char ring[];
     __shared__ __attribute__((aligned(16))) float w_s[WGT ? ATT_WKEYS : 4];
 
-    const int xcd = blockIdx.x & 7, li = blockIdx.x >> 3;
-    const int hb = (li / nqt) * 8 + xcd, qt = li % nqt;         // hb = sample * H + head
-    if (hb >= H * nB) return;
-    const int h = hb % H, b = hb / H;
-    const int tok0 = cu[b];
-    const int n = min(cu[b + 1] - tok0, WGT ? ATT_WKEYS : 0x7FFFFFFF);
-    if (qt * BQ >= n) return;
-
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), grp = wave >> 2;
-    if constexpr (WGT) {
-        // what the logits start from; -inf past the end of the sample: those keys then need no other mask
-        for (int j = tid; j < ((n + ATT_BK - 1) / ATT_BK) * ATT_BK; j += 512)
-            w_s[j] = (j < n) ? key_log2_weight(kw, b, j) / scale2 : -INFINITY;
-    }
     const int r = lane & 15, g = lane >> 4;
     const size_t rs = (size_t)H * DH;                      // token stride (elements)
-    const uint16_t* kb_ = k + (size_t)tok0 * rs + (size_t)h * DH;
-    const uint16_t* vb_ = v + (size_t)tok0 * rs + (size_t)h * DH;
-    // this head's K / V rows of this sample; a row index >= n is past the end and loads as zeros
-    const uint32_t span = (uint32_t)(((size_t)(n - 1) * rs + DH) * 2);
-    const __amdgpu_buffer_rsrc_t rk = make_uniform_rsrc(kb_, span), rv = make_uniform_rsrc(vb_, span);
-    const __amdgpu_buffer_rsrc_t rq = make_uniform_rsrc(q + (size_t)tok0 * rs + (size_t)h * DH, span);
     const int row_bytes = (int)(rs * 2);
 
-    const int q0 = qt * BQ + wave * NQ * 16;                // this wave's first query
+    // An item is a tile of BQ queries of one head.  XCD x has the heads hb = x, x + 8, ... of hb = (the sample's place) * H + head, the
+    // tiles of a head one after the other.  One item per workgroup (places = samples as they come), or (TURNS) workgroup li of the W of
+    // an XCD takes its items li, 2 W - 1 - li, 2 W + li, ..., samples in order of falling length.
+    const int xcd = blockIdx.x & 7, li = blockIdx.x >> 3;
+    constexpr int W = ATT_TURNS_WGS;
+    __shared__ int tab[4][TURNS ? WAVE : 1];               // by place: first token, tokens, sample, items up to and with this one
+    int tok0, n, h, b, qt;
+    auto item = [&](int pass) {
+        const int idx = pass * W + ((pass & 1) ? W - 1 - li : li);
+        const int end = tab[3][TURNS ? lane : 0];
+        const int place = __popcll(__builtin_amdgcn_ballot_w64(end <= idx));
+        if (place >= nB) return false;
+        const int rem = idx - (place ? __builtin_amdgcn_readlane(end, place - 1) : 0);
+        tok0 = __builtin_amdgcn_readfirstlane(tab[0][place]);
+        n = __builtin_amdgcn_readfirstlane(tab[1][place]);
+        b = __builtin_amdgcn_readfirstlane(tab[2][place]);
+        const int tiles = (n + BQ - 1) / BQ;
+        h = ((xcd - place * H) & 7) + 8 * (rem / tiles);
+        qt = rem % tiles;
+        return true;
+    };
+    if constexpr (TURNS) {
+        if (wave == 0) {
+            const int c0 = cu[min(lane, nB - 1)], c1 = cu[min(lane + 1, nB)];
+            const int len = lane < nB ? min(c1 - c0, WGT ? ATT_WKEYS : 0x7FFFFFFF) : -1;
+            int rank = 0;
+            for (int j = 0; j < nB; ++j) {
+                const int other = __builtin_amdgcn_readlane(len, j);
+                rank += (other > len) || (other == len && j < lane);
+            }
+            if (lane < nB) { tab[0][rank] = c0; tab[1][rank] = len; tab[2][rank] = lane; }
+            const int h0 = (xcd - lane * H) & 7;
+            const int heads = h0 < H ? (H - h0 + 7) >> 3 : 0;
+            const int tiles = lane < nB ? (max(tab[1][min(lane, nB - 1)], 0) + BQ - 1) / BQ : 0;
+            tab[3][lane] = wave_incl_scan(heads * tiles);
+        }
+        __syncthreads();
+        if (!item(0)) return;
+    } else {
+        const int hb = (li / nqt) * 8 + xcd;
+        if (hb >= H * nB) return;
+        h = hb % H; b = hb / H; qt = li % nqt;
+        tok0 = cu[b];
+        n = min(cu[b + 1] - tok0, WGT ? ATT_WKEYS : 0x7FFFFFFF);
+        if (qt * BQ >= n) return;
+    }
+    // what the logits start from; -inf past the end of the sample: those keys then need no other mask
+    auto write_weights = [&] {
+        for (int j = tid; j < ((n + ATT_BK - 1) / ATT_BK) * ATT_BK; j += 512)
+            w_s[j] = (j < n) ? key_log2_weight(kw, b, j) / scale2 : -INFINITY;
+    };
+    if constexpr (WGT) write_weights();
+    // this head's rows of this sample; a row index >= n is past the end and loads as zeros
+    auto rows_of = [&](const uint16_t* p) {
+        return make_uniform_rsrc(p + (size_t)tok0 * rs + (size_t)h * DH, (uint32_t)(((size_t)(n - 1) * rs + DH) * 2));
+    };
+    __amdgpu_buffer_rsrc_t rk = rows_of(k), rv = rows_of(v), rq = rows_of(q);
+
+    int q0 = qt * BQ + wave * NQ * 16;          // this wave's first query
     bf16x8 qf[NQ][KS];
     f32x4 ot[DB][NQ];
-#pragma unroll
-    for (int t = 0; t < DB; ++t)
-#pragma unroll
-        for (int qb = 0; qb < NQ; ++qb) ot[t][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
     // m_run: running maximum of the RAW logits; ms: what the exponents subtract; l_run: this lane's part of the column's sum
     float m_run[NQ], ms[NQ], l_run[NQ];
+    auto clear = [&] {
 #pragma unroll
-    for (int qb = 0; qb < NQ; ++qb) { m_run[qb] = -INFINITY; ms[qb] = 0.f; l_run[qb] = 0.f; }
+        for (int t = 0; t < DB; ++t)
+#pragma unroll
+            for (int qb = 0; qb < NQ; ++qb) ot[t][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) { m_run[qb] = -INFINITY; ms[qb] = 0.f; l_run[qb] = 0.f; }
+    };
+    clear();
 
     // direct loads: lane -> (row, chunk position).  The chunk fetched into position p of row x is p ^ f(x): K fragments are 16
     // consecutive rows of one chunk, transposing reads of V four consecutive rows (per 16 lanes) of one 32-byte piece.
@@ -178,7 +222,8 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     const uint32_t wave_lds = ring0 + wave * LD * 1024;
     auto issue_one = [&](int j, int i) {        // one of the 2 LD loads of stage j
         const uint32_t dst = wave_lds + (j % NS) * STAGE + (i >> 1) * 1024;
-        if (i & 1) direct_load_16(rv, v_off[i >> 1] + (j > 0 ? j - 1 : 0) * ATT_BK * row_bytes, dst + TILE);
+        // (stage 0 has no V tile: its offsets lie outside the buffer)
+        if (i & 1) direct_load_16(rv, v_off[i >> 1] + (j - 1) * ATT_BK * row_bytes, dst + TILE);
         else direct_load_16(rk, k_off[i >> 1] + j * ATT_BK * row_bytes, dst);
     };
     auto issue = [&](int j) {
@@ -305,7 +350,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
                 }
     };
 
-    const int ntile = (n + ATT_BK - 1) / ATT_BK;
+    int ntile = (n + ATT_BK - 1) / ATT_BK;
     // The queries go through the ring's last two slots, each wave's rows in its own part: whole lines, and in flight together with
     // the first tiles.  Every wave has read them when stage 2 is started.
     constexpr int QROWS = NQ * 16, QLD = QROWS / RPI;
@@ -326,63 +371,104 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
         for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const bf16x8*>(ring + q_lds + (k_addr ^ (ks << 6)) + qb * 16 * ROWB);
     __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0): the queries are there (and the weights written)
     phase_barrier();
-    issue(2);
     static_assert(AHEAD == 3, "three stages are under way when the loop starts");
-#pragma unroll
-    for (int f = 0; f < KPRE; ++f) read_first(ring, f);
-    // Stage j + 1 has to have landed when the softmax phase of tile j begins (its first fragments are read there).  Groups that
-    // share the ring: both wait for their loads before the barrier that ends group 0's MFMA phase of tile j.  Stages behind
-    // j + 1 stay in flight.
-    constexpr int KEEP = (NS - 3) * 2 * LD;
-    if (grp == 1) { wait_loads<KEEP>(); phase_barrier(); }
     using yes = std::integral_constant<bool, true>;
     using no = std::integral_constant<bool, false>;
-    mfma_phase(0, yes(), no());
-    // The last tile is peeled off: a loop left in its middle keeps both the accumulators before and after the MFMA phase alive.
+    constexpr int KEEP = (NS - 3) * 2 * LD;
+    bool first = true;
+    for (int pass = 1;; ++pass) {
+        issue(2);
+#pragma unroll
+        for (int f = 0; f < KPRE; ++f) read_first(ring, f);
+        // Stage j + 1 has to have landed when the softmax phase of tile j begins (its first fragments are read there).  Groups that
+        // share the ring: both wait for their loads before the barrier that ends group 0's MFMA phase of tile j.  Stages behind
+        // j + 1 stay in flight.
+        if (grp == 1) { if (first) wait_loads<KEEP>(); phase_barrier(); }
+        bool wait0 = grp == 0 && first;         // (behind another item the first two stages have landed, and its stores may still be on their way)
+        mfma_phase(0, yes(), no());
+        // The last tile is peeled off: a loop left in its middle keeps both the accumulators before and after the MFMA phase alive.
 #pragma unroll 1
-    for (int j = 0; j + 1 < ntile; ++j) {
-        if (grp == 0) wait_loads<KEEP>();
-        phase_barrier();
-        __builtin_amdgcn_s_setprio(2);
-        softmax_phase(j, no());
-        __builtin_amdgcn_s_setprio(0);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): the fragments are there (a wait the compiler knows of)
-        if (grp == 1) wait_loads<KEEP>();
-        phase_barrier();
-        mfma_phase(j + 1, yes(), yes());
-    }
-    if (grp == 0) wait_loads<0>();
-    phase_barrier();
-    softmax_phase(ntile - 1, yes());
-    if (grp == 1) wait_loads<0>();
-    phase_barrier();
-    mfma_phase(ntile, no(), yes());
-    wait_loads<0>();                            // nothing may be in flight into LDS when the workgroup ends
-    if (grp == 0) phase_barrier();
-
-    // O^T lies in the registers as 4 dims of a row per lane; through LDS the rows are stored in whole lines.  Slot ntile % NS may
-    // still be read by group 1 (V of its last tile); the two behind the next one are free.
-    char* ow = ring + ((ntile + 2 + grp) % NS) * STAGE + (wave & 3) * QROWS * ROWB;
-    static_assert(4 * QROWS * ROWB <= STAGE, "a group's rows fit into a slot");
-#pragma unroll
-    for (int qb = 0; qb < NQ; ++qb) {
-        const float inv = 1.0f / att_quad_sum(l_run[qb]);
-#pragma unroll
-        for (int t = 0; t < DB; ++t) {
-            uint2 w;
-            w.x = pack_bf16x2(ot[t][qb][0] * inv, ot[t][qb][1] * inv);
-            w.y = pack_bf16x2(ot[t][qb][2] * inv, ot[t][qb][3] * inv);
-            *reinterpret_cast<uint2*>(ow + (qb * 16 + r) * ROWB + (((t * 2 + (g >> 1)) ^ row_swizzle(r)) << 4) + (g & 1) * 8) = w;
+        for (int j = 0; j + 1 < ntile; ++j) {
+            if (wait0) wait_loads<KEEP>();
+            wait0 = grp == 0;
+            phase_barrier();
+            __builtin_amdgcn_s_setprio(2);
+            softmax_phase(j, no());
+            __builtin_amdgcn_s_setprio(0);
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): the fragments are there (a wait the compiler knows of)
+            if (grp == 1) wait_loads<KEEP>();
+            phase_barrier();
+            mfma_phase(j + 1, yes(), yes());
         }
-    }
-    wait_lds();
-    uint16_t* op = o + (size_t)tok0 * rs + (size_t)h * DH + (lane % NCHK) * 8;
+        if (grp == 0) wait_loads<0>();
+        phase_barrier();
+        softmax_phase(ntile - 1, yes());
+        if (grp == 1) wait_loads<0>();
+        phase_barrier();
+        mfma_phase(ntile, no(), yes());
+        wait_loads<0>();                        // nothing may be in flight into LDS when the workgroup ends
+        if (grp == 0) phase_barrier();
+
+        // O^T lies in the registers as 4 dims of a row per lane; through LDS the rows are stored in whole lines.  Slot ntile % NS may
+        // still be read by group 1 (V of its last tile); the two behind the next one are free.
+        const __amdgpu_buffer_rsrc_t ro = rows_of(o);
+        // the lane's number anew, so that no address of this part is kept in a register through the loop above
+        int el = threadIdx.x;
+        asm volatile("" : "+v"(el));
+        el &= 63;
+        const int er = el & 15, eg = el >> 4;
+        const int o0 = q0;
+        int slot = (ntile + 2 + grp) % NS;
+        bool more = false;
+        if constexpr (TURNS) {
+            // The next item's first stages and queries are requested in front of this one's epilogue.  (The next workgroup on a CU
+            // starts 2 us after the one before has ended, and waits another 2.8 .. 4.5 us for its first loads.)
+            const int before = b;
+            more = item(pass);
+            if (more) {
+                phase_barrier();                // everybody is done with the ring and the weights
+                rk = rows_of(k); rv = rows_of(v); rq = rows_of(q);
+                q0 = qt * BQ + wave * NQ * 16;
+                ntile = (n + ATT_BK - 1) / ATT_BK;
+                issue(0);
+                issue(1);
+                slot = 2 + grp;
 #pragma unroll
-    for (int i = 0; i < QLD; ++i) {
-        const int x = i * RPI + lane / NCHK;
-        const uint4 w = *reinterpret_cast<const uint4*>(ow + x * ROWB + (((lane % NCHK) ^ row_swizzle(x)) << 4));
-        if (q0 + x < n) *reinterpret_cast<uint4*>(op + (size_t)(q0 + x) * rs) = w;
+                for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks)
+                        qf[qb][ks] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rq, (q0 + qb * 16 + er) * row_bytes + ks * 64 + eg * 16, 0, 0));
+                if constexpr (WGT) { if (b != before) write_weights(); }
+            }
+        }
+        char* ow = ring + slot * STAGE + (wave & 3) * QROWS * ROWB;
+        static_assert(4 * QROWS * ROWB <= STAGE, "a group's rows fit into a slot");
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) {
+            const float inv = 1.0f / att_quad_sum(l_run[qb]);
+#pragma unroll
+            for (int t = 0; t < DB; ++t) {
+                uint2 w;
+                w.x = pack_bf16x2(ot[t][qb][0] * inv, ot[t][qb][1] * inv);
+                w.y = pack_bf16x2(ot[t][qb][2] * inv, ot[t][qb][3] * inv);
+                *reinterpret_cast<uint2*>(ow + (qb * 16 + er) * ROWB + (((t * 2 + (eg >> 1)) ^ row_swizzle(er)) << 4) + (eg & 1) * 8) = w;
+            }
+        }
+        wait_lds();
+#pragma unroll
+        for (int i = 0; i < QLD; ++i) {
+            const int x = i * RPI + el / NCHK;
+            const uint4 w = *reinterpret_cast<const uint4*>(ow + x * ROWB + (((el % NCHK) ^ row_swizzle(x)) << 4));
+            // rows past the end of the sample lie outside the buffer and are not written
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(att_u4, w), ro, (o0 + x) * row_bytes + (el % NCHK) * 16, 0, 0);
+        }
+        if (!more) break;
+        clear();
+        first = false;
+        wait_loads<QLD>();                      // all loads have landed; the stores may be on their way
+        __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): the rows are out of the slots, the weights are written
+        phase_barrier();
     }
 #endif
 }
@@ -781,21 +867,28 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
         const long wide = (ceil_div(max_seqlen, 256) * heads + 255) / 256, narrow = (ceil_div(max_seqlen, 128) * heads + 255) / 256;
         const int nq = (dh == 64 ? 55 : 66) * narrow < 100 * wide ? 1 : 2;
         const int nqt = ceil_div(max_seqlen, nq * 128);
-        const dim3 g((unsigned)(8 * ceil_div(H * B, 8) * nqt));
+        // Several rounds of workgroups that have a compute unit to themselves: one per unit, which takes its tiles in turn, samples by
+        // falling length (one tile per workgroup / in turn: 16 x 700 .. 1505 keys 440 / 422 us, 4 x 575 .. 1951 141 / 133, 12 x 270 .. 800
+        // 114 / 82, 8 x 1000 149 / 145, one sample of 3773 211 / 211; 8 heads, 16 x 1000 .. 3000 303 / 262).
+        const bool turns = nqt * heads > 256 && !(dh == 64 && nq == 1) && B <= WAVE;
+        const dim3 g(turns ? 8u * ATT_TURNS_WGS : (unsigned)(8 * ceil_div(H * B, 8) * nqt));
         const size_t lds = (size_t)ATT_SLOTS * 2 * ATT_BK * dh * 2;
         const int threads = 512;
-#define D3TOM_ATT8(DHV, WGTV, NQV)                                                                                          \
+#define D3TOM_ATT8(DHV, WGTV, NQV, TURNSV)                                                                                  \
     do {                                                                                                                    \
         static PerDeviceOnce lds_setup;                                                                                     \
-        if (!lds_setup.run([] { return raise_dynamic_lds(attend_bf16_kernel<DHV, WGTV, NQV>, ATT_SLOTS * 2 * ATT_BK * DHV * 2); })) \
+        if (!lds_setup.run([] { return raise_dynamic_lds(attend_bf16_kernel<DHV, WGTV, NQV, TURNSV>, ATT_SLOTS * 2 * ATT_BK * DHV * 2); })) \
             return D3TOM_ERR_DEVICE;                                                                                        \
-        D3TOM_ATT((attend_bf16_kernel<DHV, WGTV, NQV>));                                                                    \
+        D3TOM_ATT((attend_bf16_kernel<DHV, WGTV, NQV, TURNSV>));                                                            \
     } while (0)
-#define D3TOM_ATT8_NQ(DHV, WGTV) do { if (nq == 1) D3TOM_ATT8(DHV, WGTV, 1); else D3TOM_ATT8(DHV, WGTV, 2); } while (0)
-#define D3TOM_ATT8_FORM(DHV) do { if (wgt) D3TOM_ATT8_NQ(DHV, true); else D3TOM_ATT8_NQ(DHV, false); } while (0)
-        if (dh == 128) D3TOM_ATT8_FORM(128); else D3TOM_ATT8_FORM(64);
-#undef D3TOM_ATT8_FORM
-#undef D3TOM_ATT8_NQ
+#define D3TOM_ATT8_TURNS(DHV, WGTV, NQV) do { if (turns) D3TOM_ATT8(DHV, WGTV, NQV, true); else D3TOM_ATT8(DHV, WGTV, NQV, false); } while (0)
+#define D3TOM_ATT8_128(WGTV) do { if (nq == 2) D3TOM_ATT8_TURNS(128, WGTV, 2); else D3TOM_ATT8_TURNS(128, WGTV, 1); } while (0)
+#define D3TOM_ATT8_64(WGTV) do { if (nq == 2) D3TOM_ATT8_TURNS(64, WGTV, 2); else D3TOM_ATT8(64, WGTV, 1, false); } while (0)
+        if (dh == 128) { if (wgt) D3TOM_ATT8_128(true); else D3TOM_ATT8_128(false); }
+        else           { if (wgt) D3TOM_ATT8_64(true);  else D3TOM_ATT8_64(false); }
+#undef D3TOM_ATT8_64
+#undef D3TOM_ATT8_128
+#undef D3TOM_ATT8_TURNS
 #undef D3TOM_ATT8
 #undef D3TOM_ATT
     } else {

@@ -149,6 +149,21 @@ __device__ __forceinline__ float row16_sum(float v) {
     return v;
 }
 
+#if defined(__HIP_DEVICE_COMPILE__)
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ int dpp_move_i(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, ROWS == 0xF); }
+// inclusive prefix sum over the 64 lanes of a wave: inside rows of 16, then the last lane of row 0 (2) to row 1 (3), of row 1 to rows 2, 3
+__device__ __forceinline__ int wave_incl_scan(int v) {
+    v += dpp_move_i<0x111>(v);
+    v += dpp_move_i<0x112>(v);
+    v += dpp_move_i<0x114>(v);
+    v += dpp_move_i<0x118>(v);
+    v += dpp_move_i<0x142, 0xA>(v);
+    v += dpp_move_i<0x143, 0xC>(v);
+    return v;
+}
+#endif
+
 // Combine two (running max, running sum of exp2) pairs.  -inf max means "empty".
 __device__ __forceinline__ void lse2_combine(float& m, float& z, float m2, float z2) {
     float mn = fmaxf(m, m2);

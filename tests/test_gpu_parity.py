@@ -292,6 +292,26 @@ def test_attend_error_is_that_of_rounded_probabilities(H, dh, n, weighted, sprea
     assert got <= 1.02 * bound
 
 
+@pytest.mark.parametrize("H,dh,longest,batch,weighted", [
+    (5, 128, 300, 40, False),            # several rounds of 128-query tiles, heads that do not divide among the XCDs
+    (5, 128, 600, 32, True),             # ... of 256-query tiles
+    (9, 64, 1030, 16, False), (9, 64, 1030, 16, True),
+    (12, 128, 520, 64, False), (12, 128, 520, 65, False),       # as many samples as a wave has lanes, one more
+])
+def test_attend_tiles_in_turn(H, dh, longest, batch, weighted):
+    """Ragged batches of several rounds: a workgroup takes one tile after the other, from samples of one key to the longest."""
+    edge = [longest, 1, 2, 63, 64, 65, 127, 128, 129, 192, 193, 255, 256, 257]
+    lens = [min(longest, n) for n in (edge + [17 + 37 * i % longest for i in range(batch)])[:batch]]
+    lens = lens[batch // 2:] + lens[:batch // 2]
+    base = W.random_qkv(880 + dh, longest, H, dh, "bf16")
+    qkv = [tuple(np.roll(t, i, axis=0)[:n] for t in base) for i, n in enumerate(lens)]
+    vis, counts = [n // 5 for n in lens], [(1 + np.arange(n // 2) % 37).astype(np.int32) for n in lens]
+    outs = gpu_attend_weighted(qkv, counts, vis, "bf16") if weighted else gpu_attend(qkv, "bf16")
+    for i, ((q, k, v), o, vs, c) in enumerate(zip(qkv, outs, vis, counts)):
+        rows = np.arange(0, len(q), 1 if len(q) < 130 else 7)
+        check_attend(o, q, k, v, "bf16", rows=np.union1d(rows, [len(q) - 1]), key_weight=key_weights(len(q), vs, c) if weighted else None)
+
+
 def test_attend_special_cases_bf16():
     q, k, v = W.random_qkv(5, 150, 2, 128, "bf16", spread=2.0)
     v1 = np.broadcast_to(v[:1], v.shape).copy()
