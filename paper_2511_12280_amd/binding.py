@@ -1,4 +1,4 @@
-"""ctypes binding of libd3tom.so (include/d3tom.h): argument marshalling only.
+"""Binding of libd3tom.so (include/d3tom.h): argument marshalling only.
 
 Every function here has the name of the C entry point it calls and does no arithmetic of the
 method: it turns torch tensors into device pointers, passes sizes through and raises on a non-zero
@@ -17,10 +17,14 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libd3tom.so")
 
-if not os.path.exists(LIB_PATH):
-    raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_2511_12280_amd.build` "
-                      "(hipcc, --offload-arch=gfx950); there is no CPU fallback")
+for _path in (LIB_PATH, os.path.join(_HERE, "_native.so")):
+    if not os.path.exists(_path):
+        raise ImportError(f"{_path} is missing: build it with `python -m paper_2511_12280_amd.build` "
+                          "(hipcc, --offload-arch=gfx950); there is no CPU fallback")
 _lib = ctypes.CDLL(LIB_PATH)
+# Device entry points with several tensors go through an extension that reads the tensors itself (csrc/native.cpp): the host time
+# of a short step is a good part of the step.  The others, and everything host-only, stay with ctypes.
+from . import _native  # noqa: E402
 
 D3TOM_OK, D3TOM_ERR_INVALID_ARG, D3TOM_ERR_NO_DECIDERS, D3TOM_ERR_WORKSPACE_TOO_SMALL, \
     D3TOM_ERR_UNSUPPORTED, D3TOM_ERR_DEVICE = range(6)
@@ -47,38 +51,8 @@ _lib.d3tom_workspace_bytes.restype = _sz
 _lib.d3tom_workspace_bytes.argtypes = [_i] * 7
 _lib.d3tom_status_string.restype = ctypes.c_char_p
 _lib.d3tom_status_string.argtypes = [_i]
-_lib.d3tom_importance.restype = _i
-_lib.d3tom_importance.argtypes = [_vp, _vp, _i, _i, _vp, _i, _i, _f, _vp, _vp, _i, _i, _vp, _vp, _vp, _i, _i,
-                                  _vp, _vp, _sz, _vp]
-_lib.d3tom_importance_static.restype = _i
-_lib.d3tom_importance_static.argtypes = [_vp, _vp, _i, _i, _vp, _i, _i, _f, _vp, _vp, _i, _i, _vp, _vp, _vp, _i, _i, _vp, _vp]
-_lib.d3tom_select_topk.restype = _i
-_lib.d3tom_select_topk.argtypes = [_vp, _i, _vp, _vp, _vp, _i, _vp, _vp, _vp, _sz, _vp]
-_lib.d3tom_merge.restype = _i
-_lib.d3tom_merge.argtypes = [_vp, _vp, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _i, _i, _i,
-                             _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]
-_lib.d3tom_merge_kv.restype = _i
-_lib.d3tom_merge_kv.argtypes = [_vp, _vp, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _i, _i, _i,
-                                _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]
 _lib.d3tom_merge_layer_workspace_bytes.restype = _sz
 _lib.d3tom_merge_layer_workspace_bytes.argtypes = [_i] * 6
-_lib.d3tom_merge_layer.restype = _i
-_lib.d3tom_merge_layer.argtypes = [_vp, _vp, _vp, _vp, _i, _i, _i, _i, _vp, _i, _i, _f, _vp, _vp, _i, _i, _vp, _vp, _vp,
-                                   _vp, _i, _i, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp]
-_lib.d3tom_update_deciders.restype = _i
-_lib.d3tom_update_deciders.argtypes = [_vp, _vp, _i, _i, _vp, _i, _vp, _vp, _vp, _vp]
-_lib.d3tom_attend.restype = _i
-_lib.d3tom_attend.argtypes = [_vp, _vp, _vp, _i, _i, _vp, _i, _i, _i, _f, _vp, _vp, _sz, _vp]
-_lib.d3tom_attend_weighted.restype = _i
-_lib.d3tom_attend_weighted.argtypes = [_vp, _vp, _vp, _i, _i, _vp, _i, _i, _i, _f, _vp, _vp, _vp, _vp, _vp, _sz, _vp]
-_lib.d3tom_rmsnorm.restype = _i
-_lib.d3tom_rmsnorm.argtypes = [_vp, _vp, _i, _i, _f, _vp, _vp]
-_lib.d3tom_rope.restype = _i
-_lib.d3tom_rope.argtypes = [_vp, _vp, _vp, _i, _i, _i, _f, _vp]
-_lib.d3tom_linear.restype = _i
-_lib.d3tom_linear.argtypes = [_vp, _vp, _i, _i, _i, _i, _vp, _vp, _i, _vp]
-_lib.d3tom_linear_tile.restype = _i
-_lib.d3tom_linear_tile.argtypes = [_vp, _vp, _i, _i, _i, _i, _vp, _vp, _i, _i, _vp]
 
 
 class BlockWeights(ctypes.Structure):
@@ -128,12 +102,14 @@ def _ptr(t: Optional[torch.Tensor]):
     return t.data_ptr()
 
 
+_DTYPES = {torch.float32: D3TOM_F32, torch.bfloat16: D3TOM_BF16}
+
+
 def _dt(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return D3TOM_F32
-    if t.dtype == torch.bfloat16:
-        return D3TOM_BF16
-    raise ValueError(f"unsupported element type {t.dtype}")
+    try:
+        return _DTYPES[t.dtype]
+    except KeyError:
+        raise ValueError(f"unsupported element type {t.dtype}") from None
 
 
 def _stream(stream):
@@ -233,31 +209,31 @@ def workspace(nbytes: int, device="cuda") -> torch.Tensor:
 def d3tom_importance(q: torch.Tensor, k: torch.Tensor, lay: Layout, scale: float,
                      scores: torch.Tensor, ws: torch.Tensor, stream=None) -> torch.Tensor:
     """q, k [sum N, H, dh]; scores float32 [sum V] (written)."""
-    H, dh = q.shape[-2], q.shape[-1]
-    _check(_lib.d3tom_importance(_ptr(q), _ptr(k), _dt(q), lay.B, _ptr(lay.seq_off), H, dh, float(scale),
-                                 _ptr(lay.dec_idx), _ptr(lay.dec_off), lay.min_D, lay.max_D,
-                                 _ptr(lay.vis_start), _ptr(lay.vis_count), _ptr(lay.vis_off), lay.max_N, lay.max_V,
-                                 _ptr(scores), _ptr(ws), ws.numel(), _stream(stream)), "d3tom_importance")
+    H, dh = q.shape[-2:]
+    _check(_native.d3tom_importance(q, k, _dt(q), lay.B, lay.seq_off, H, dh, float(scale),
+                                    lay.dec_idx, lay.dec_off, lay.min_D, lay.max_D,
+                                    lay.vis_start, lay.vis_count, lay.vis_off, lay.max_N, lay.max_V,
+                                    scores, ws, ws.numel(), _stream(stream)), "d3tom_importance")
     return scores
 
 
 def d3tom_importance_static(q: torch.Tensor, k: torch.Tensor, lay: Layout, scale: float,
                             scores: torch.Tensor, stream=None) -> torch.Tensor:
     """d3tom_importance without a workspace argument (the library's own static scratch array)."""
-    H, dh = q.shape[-2], q.shape[-1]
-    _check(_lib.d3tom_importance_static(_ptr(q), _ptr(k), _dt(q), lay.B, _ptr(lay.seq_off), H, dh, float(scale),
-                                        _ptr(lay.dec_idx), _ptr(lay.dec_off), lay.min_D, lay.max_D,
-                                        _ptr(lay.vis_start), _ptr(lay.vis_count), _ptr(lay.vis_off), lay.max_N, lay.max_V,
-                                        _ptr(scores), _stream(stream)), "d3tom_importance_static")
+    H, dh = q.shape[-2:]
+    _check(_native.d3tom_importance_static(q, k, _dt(q), lay.B, lay.seq_off, H, dh, float(scale),
+                                           lay.dec_idx, lay.dec_off, lay.min_D, lay.max_D,
+                                           lay.vis_start, lay.vis_count, lay.vis_off, lay.max_N, lay.max_V,
+                                           scores, _stream(stream)), "d3tom_importance_static")
     return scores
 
 
 def d3tom_select_topk(scores: torch.Tensor, lay: Layout, kept_idx: torch.Tensor, slot_of: torch.Tensor,
                       ws: Optional[torch.Tensor] = None, stream=None):
     """scores float32 [sum V]; kept_idx int32 [sum keep], slot_of int32 [sum V] (written)."""
-    _check(_lib.d3tom_select_topk(_ptr(scores), lay.B, _ptr(lay.vis_off), _ptr(lay.keep_k), _ptr(lay.kept_off),
-                                  lay.max_V, _ptr(kept_idx), _ptr(slot_of), _ptr(ws), ws.numel() if ws is not None else 0,
-                                  _stream(stream)), "d3tom_select_topk")
+    _check(_native.d3tom_select_topk(scores, lay.B, lay.vis_off, lay.keep_k, lay.kept_off,
+                                     lay.max_V, kept_idx, slot_of, ws, ws.numel() if ws is not None else 0,
+                                     _stream(stream)), "d3tom_select_topk")
     return kept_idx, slot_of
 
 
@@ -268,10 +244,10 @@ def d3tom_merge(x: torch.Tensor, sim: Optional[torch.Tensor], lay: Layout, kept_
     src_pos int32 [sum N_m] optional outputs."""
     d = x.shape[-1]
     d_sim = sim.shape[-1] if sim is not None else d
-    _check(_lib.d3tom_merge(_ptr(x), _ptr(sim), d, d_sim, _dt(x), lay.B, _ptr(lay.seq_off), _ptr(lay.vis_start),
-                            _ptr(lay.vis_count), _ptr(lay.vis_off), _ptr(kept_idx), _ptr(lay.kept_off),
-                            lay.max_N, lay.max_V, lay.max_keep, lay.max_pruned, lay.max_Nm, int(mode), _ptr(lay.out_off), _ptr(y),
-                            _ptr(assign), _ptr(counts), _ptr(src_pos), _ptr(ws), ws.numel(), _stream(stream)),
+    _check(_native.d3tom_merge(x, sim, d, d_sim, _dt(x), lay.B, lay.seq_off, lay.vis_start,
+                               lay.vis_count, lay.vis_off, kept_idx, lay.kept_off,
+                               lay.max_N, lay.max_V, lay.max_keep, lay.max_pruned, lay.max_Nm, int(mode), lay.out_off, y,
+                               assign, counts, src_pos, ws, ws.numel(), _stream(stream)),
            "d3tom_merge")
     return y
 
@@ -281,11 +257,11 @@ def d3tom_merge_kv(k_cache: torch.Tensor, v_cache: torch.Tensor, lay: Layout, ke
                    counts: Optional[torch.Tensor], src_pos: Optional[torch.Tensor], ws: torch.Tensor, stream=None):
     """k_cache, v_cache [sum N, d]; k_out, v_out [sum N_m, d] (written); index outputs as in d3tom_merge."""
     d = k_cache.shape[-1]
-    _check(_lib.d3tom_merge_kv(_ptr(k_cache), _ptr(v_cache), d, _dt(k_cache), lay.B, _ptr(lay.seq_off),
-                               _ptr(lay.vis_start), _ptr(lay.vis_count), _ptr(lay.vis_off), _ptr(kept_idx),
-                               _ptr(lay.kept_off), lay.max_N, lay.max_V, lay.max_keep, lay.max_pruned, lay.max_Nm,
-                               int(mode), _ptr(lay.out_off), _ptr(k_out), _ptr(v_out), _ptr(assign), _ptr(counts),
-                               _ptr(src_pos), _ptr(ws), ws.numel(), _stream(stream)),
+    _check(_native.d3tom_merge_kv(k_cache, v_cache, d, _dt(k_cache), lay.B, lay.seq_off,
+                                  lay.vis_start, lay.vis_count, lay.vis_off, kept_idx,
+                                  lay.kept_off, lay.max_N, lay.max_V, lay.max_keep, lay.max_pruned, lay.max_Nm,
+                                  int(mode), lay.out_off, k_out, v_out, assign, counts,
+                                  src_pos, ws, ws.numel(), _stream(stream)),
            "d3tom_merge_kv")
     return k_out, v_out
 
@@ -301,26 +277,26 @@ def d3tom_merge_layer(q: torch.Tensor, k: torch.Tensor, x: torch.Tensor, sim: Op
                       src_pos: Optional[torch.Tensor], ws: torch.Tensor, stream=None):
     """The three merge-layer calls in one, kept counts from keep_ratio (float64 [B] on the device).  Only the sizes
     and decider lists of `lay` are used; its keep counts are not."""
-    H, dh = q.shape[-2], q.shape[-1]
+    H, dh = q.shape[-2:]
     d = x.shape[-1]
     d_sim = sim.shape[-1] if sim is not None else d
     assert keep_ratio.dtype == torch.float64 and keep_ratio.numel() == lay.B
-    _check(_lib.d3tom_merge_layer(_ptr(q), _ptr(k), _ptr(x), _ptr(sim), d, d_sim, _dt(x), lay.B, _ptr(lay.seq_off), H, dh,
-                                  float(scale), _ptr(lay.dec_idx), _ptr(lay.dec_off), lay.min_D, lay.max_D,
-                                  _ptr(lay.vis_start), _ptr(lay.vis_count), _ptr(lay.vis_off), _ptr(keep_ratio),
-                                  lay.max_N, lay.max_V, int(min_keep), int(max_keep), int(mode), _ptr(scores), _ptr(keep_k),
-                                  _ptr(kept_off), _ptr(kept_idx), _ptr(out_off), _ptr(y), _ptr(assign), _ptr(counts),
-                                  _ptr(src_pos), _ptr(ws), ws.numel(), _stream(stream)), "d3tom_merge_layer")
+    _check(_native.d3tom_merge_layer(q, k, x, sim, d, d_sim, _dt(x), lay.B, lay.seq_off, H, dh,
+                                     float(scale), lay.dec_idx, lay.dec_off, lay.min_D, lay.max_D,
+                                     lay.vis_start, lay.vis_count, lay.vis_off, keep_ratio,
+                                     lay.max_N, lay.max_V, int(min_keep), int(max_keep), int(mode), scores, keep_k,
+                                     kept_off, kept_idx, out_off, y, assign, counts,
+                                     src_pos, ws, ws.numel(), _stream(stream)), "d3tom_merge_layer")
     return y
 
 
 def d3tom_attend(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, cu_seqlens: torch.Tensor, max_seqlen: int,
                  scale: float, o: torch.Tensor, ws: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """q, k, v, o [sum n, H, dh]; cu_seqlens int32 [B+1] on the device."""
-    H, dh = q.shape[-2], q.shape[-1]
+    H, dh = q.shape[-2:]
     B = cu_seqlens.numel() - 1
-    _check(_lib.d3tom_attend(_ptr(q), _ptr(k), _ptr(v), _dt(q), B, _ptr(cu_seqlens), int(max_seqlen), H, dh,
-                             float(scale), _ptr(o), _ptr(ws), ws.numel() if ws is not None else 0, _stream(stream)),
+    _check(_native.d3tom_attend(q, k, v, _dt(q), B, cu_seqlens, int(max_seqlen), H, dh,
+                                float(scale), o, ws, ws.numel() if ws is not None else 0, _stream(stream)),
            "d3tom_attend")
     return o
 
@@ -330,11 +306,11 @@ def d3tom_attend_weighted(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, cu_
                           o: torch.Tensor, stream=None) -> torch.Tensor:
     """d3tom_attend with the merge's member counts as key weights (counts int32 [sum keep], kept_off int32 [B+1],
     vis_start int32 [B], all on the device)."""
-    H, dh = q.shape[-2], q.shape[-1]
+    H, dh = q.shape[-2:]
     B = cu_seqlens.numel() - 1
-    _check(_lib.d3tom_attend_weighted(_ptr(q), _ptr(k), _ptr(v), _dt(q), B, _ptr(cu_seqlens), int(max_seqlen), H, dh,
-                                      float(scale), _ptr(counts), _ptr(kept_off), _ptr(vis_start), _ptr(o), None, 0,
-                                      _stream(stream)), "d3tom_attend_weighted")
+    _check(_native.d3tom_attend_weighted(q, k, v, _dt(q), B, cu_seqlens, int(max_seqlen), H, dh,
+                                         float(scale), counts, kept_off, vis_start, o, None, 0,
+                                         _stream(stream)), "d3tom_attend_weighted")
     return o
 
 
@@ -344,8 +320,8 @@ def d3tom_update_deciders(prev_ids: torch.Tensor, cur_ids: torch.Tensor, mask_id
     """prev_ids, cur_ids int32 [sum N]; dec_idx int32 [B * max_D], dec_off int32 [B + 1], dec_count int32 [B] (written)."""
     Bn = seq_off.numel() - 1
     assert dec_idx.numel() >= Bn * max_D and dec_off.numel() >= Bn + 1
-    _check(_lib.d3tom_update_deciders(_ptr(prev_ids), _ptr(cur_ids), int(mask_id), Bn, _ptr(seq_off), int(max_D),
-                                      _ptr(dec_idx), _ptr(dec_off), _ptr(dec_count), _stream(stream)),
+    _check(_native.d3tom_update_deciders(prev_ids, cur_ids, int(mask_id), Bn, seq_off, int(max_D),
+                                         dec_idx, dec_off, dec_count, _stream(stream)),
            "d3tom_update_deciders")
     return dec_idx, dec_off
 
@@ -353,13 +329,13 @@ def d3tom_update_deciders(prev_ids: torch.Tensor, cur_ids: torch.Tensor, mask_id
 # ---- tensor <-> numpy helpers for the storage types (bit moves only) ---------------------------------
 def d3tom_rmsnorm(x: torch.Tensor, gain: torch.Tensor, eps: float, y: torch.Tensor, stream=None) -> None:
     rows, d = x.shape
-    _check(_lib.d3tom_rmsnorm(_ptr(x), _ptr(gain), rows, d, eps, _ptr(y), _stream(stream)), "d3tom_rmsnorm")
+    _check(_native.d3tom_rmsnorm(x, gain, rows, d, eps, y, _stream(stream)), "d3tom_rmsnorm")
 
 
 def d3tom_rope(q: torch.Tensor, k: torch.Tensor, pos: torch.Tensor, theta: float, stream=None) -> None:
     rows, H, dh = q.shape
     assert k.shape == q.shape and pos.dtype == torch.int32 and pos.numel() >= rows
-    _check(_lib.d3tom_rope(_ptr(q), _ptr(k), _ptr(pos), rows, H, dh, theta, _stream(stream)), "d3tom_rope")
+    _check(_native.d3tom_rope(q, k, pos, rows, H, dh, theta, _stream(stream)), "d3tom_rope")
 
 
 def _linear_sizes(a, w, epilogue, out, residual):
@@ -374,15 +350,15 @@ def _linear_sizes(a, w, epilogue, out, residual):
 def d3tom_linear(a: torch.Tensor, w: torch.Tensor, epilogue: int, out: torch.Tensor,
                  residual: Optional[torch.Tensor] = None, out_chunk: int = 0, stream=None) -> None:
     rows, n_w_rows, K = _linear_sizes(a, w, epilogue, out, residual)
-    _check(_lib.d3tom_linear(_ptr(a), _ptr(w), rows, n_w_rows, K, epilogue, _ptr(residual), _ptr(out), out_chunk,
-                             _stream(stream)), "d3tom_linear")
+    _check(_native.d3tom_linear(a, w, rows, n_w_rows, K, epilogue, residual, out, out_chunk,
+                                _stream(stream)), "d3tom_linear")
 
 
 def d3tom_linear_tile(a: torch.Tensor, w: torch.Tensor, epilogue: int, out: torch.Tensor, tile: int,
                       residual: Optional[torch.Tensor] = None, out_chunk: int = 0, stream=None) -> None:
     rows, n_w_rows, K = _linear_sizes(a, w, epilogue, out, residual)
-    _check(_lib.d3tom_linear_tile(_ptr(a), _ptr(w), rows, n_w_rows, K, epilogue, _ptr(residual), _ptr(out), out_chunk,
-                                  tile, _stream(stream)), "d3tom_linear_tile")
+    _check(_native.d3tom_linear_tile(a, w, rows, n_w_rows, K, epilogue, residual, out, out_chunk,
+                                     tile, _stream(stream)), "d3tom_linear_tile")
 
 
 def block_weights(blocks: Sequence[dict]):

@@ -91,3 +91,27 @@ def test_schedule_variants_share_their_mean(lib):
     assert sum(fwd) / T == pytest.approx((lo + hi) / 2) and sum(rev) / T == pytest.approx((lo + hi) / 2)
     assert rev == pytest.approx(fwd[::-1])
 
+
+
+def test_native_binding_refuses_what_it_cannot_pass_on(lib):
+    # argument count, tensors that are not on the GPU, addresses in a tensor's place, a float for an int: refused before the
+    # library is called; None reaches it as a null pointer and an int as its low 32 bits (status 1: invalid argument)
+    import torch
+    from paper_2511_12280_amd import _native
+    t = torch.zeros(4, 64)
+    class Sub(torch.Tensor):
+        pass
+    assert _native.d3tom_rmsnorm(None, None, 4, 64, 1e-5, None, None) == 1
+    assert _native.d3tom_rmsnorm(None, None, 4 + (1 << 32), -64, 1, None, 0) == 1
+    with pytest.raises(TypeError):
+        _native.d3tom_rmsnorm(None, None, 4, 64, 1e-5, None)
+    for bad in (t, t.t(), t.as_subclass(Sub), torch.nn.Parameter(t)):
+        with pytest.raises(ValueError, match="contiguous tensors on the GPU"):
+            _native.d3tom_rmsnorm(bad, None, 4, 64, 1e-5, None, None)
+    for bad in (4096, 0.5, "x"):
+        with pytest.raises(AttributeError):
+            _native.d3tom_rmsnorm(bad, None, 4, 64, 1e-5, None, None)
+    with pytest.raises(TypeError):
+        _native.d3tom_rmsnorm(None, None, 4.0, 64, 1e-5, None, None)
+    with pytest.raises(TypeError):
+        _native.d3tom_rmsnorm(None, None, 4, 64, 1e-5, None, t)
