@@ -134,8 +134,21 @@ __global__ __launch_bounds__(256) void merge_norms_kernel(
 // has; 32 KB a stage at 44 are 745 clocks, the MFMAs of a 128-row tile 512.  The computing waves therefore only have to keep
 // out of the way: fragments one k-step ahead across the stage's barrier, the smaller MFMA shape (less power: 1.6 GHz
 // against 1.5), the kept rows' norms read once in the epilogue (read for every row, 400 clocks each, it took 5 us of 35).
+// Workgroups behind the last sample's tiles, if the launch has any, are helpers: they pull rows from HBM for the others.
 // Measured at d = 4096: 1822 x 1823 rows 37.9 -> 31.8 us, 2733 x 912 32.4 -> 28.5, 16 samples of 2304 rows 195 -> 167.
 constexpr int cos_ring_stages(int TM) { return TM >= 4 ? 3 : 4; }     // 256-row tiles: 3 stages of 48 KB fit the 160 KB of LDS
+
+// Helpers (see the launch): the first lines of a helper's rows answer within this time, in ticks of 10 ns, where the rows lie in the
+// memory-side cache, and later where they lie in HBM.  (0.45 and 0.55 us tell the two apart at all sizes measured; from 0.65 us
+// on, rows in HBM are taken for cached ones more and more often.)
+constexpr uint32_t COS_CACHED_TICKS = 55;
+
+// row tiles of a band, for a sample with per_b tiles on each XCD in a launch sized for `per`
+__device__ __forceinline__ int band_height(int RB, int per_b, int per, int nrt_b) {
+    int rb = RB;
+    if (per_b < per) { rb = 1; while ((rb + 1) * (rb + 1) <= per_b) ++rb; }
+    return min(rb, nrt_b);
+}
 
 // SPLIT (contraction cut into ksplit > 1 slices): the workgroups of row tile 0 sum the squares of their kept rows (the diagonal of
 // B B^T, two MFMAs per block of 16 rows and stage where the load path leaves the matrix core idle), and without a preparing launch
@@ -168,7 +181,55 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     const int xcd = blockIdx.x & 7, XG = 8 / NG;
     const int b = (xcd / XG) + NG * (int)((blockIdx.x >> 3) / per);
     const int id = (blockIdx.x >> 3) % per;
-    if (b >= nB) return;
+    if (b >= nB) {
+        if constexpr (!SPLIT && TM < 4) {
+            // A helper (NG is 1): requests a dword of every 128-byte line of pruned rows that tiles of this XCD use, four lines of each
+            // row at a time, so that the rows come from HBM into the XCD's L2 ahead of the tiles that walk through them.  Of the
+            // XCDs that use a row tile, the one with its tile in column `pick` has it.
+            const int hx = (int)(blockIdx.x >> 3) - per * nB, nx = (int)(gridDim.x >> 3) - per * nB;   // helper hx of the XCD's nx
+            const int hb = hx % nB, h0 = hx / nB, hn = (nx - hb + nB - 1) / nB;                        // the h0-th of sample hb's hn
+            const SampleGeom s = sample_geom(hb, seq_off, vis_start, vis_count, kept_off, max_V, max_keep);
+            const int nrt_b = min((s.M + BM - 1) / BM, nrt_launch), nct_b = min((s.k + BN - 1) / BN, nct_launch);
+            const int per_b = (nrt_b * nct_b + 7) / 8;
+            const int tid = threadIdx.x, wave = tid >> 6;
+            uint64_t* owned = reinterpret_cast<uint64_t*>(ring);                 // bit per row tile (one round: at most 256)
+            const int rb = band_height(RB, per_b, per, nrt_b);
+            bool mine = false;
+            if (tid < nrt_b && nct_b > 0) {
+                const int first = tid / rb * rb, high = min(rb, nrt_b - first);  // the band's first row tile and height
+                const int pick = ((tid - first) * 2 + 1) * nct_b / (high * 2);
+                mine = (first * nct_b + pick * high + tid - first) / per_b == xcd;
+            }
+            const uint64_t bits = __builtin_amdgcn_ballot_w64(mine);
+            if ((tid & 63) == 0) owned[wave] = bits;
+            __syncthreads();
+            // the helpers of a sample share each of these row tiles; thread t takes a quarter of each line group of the t / 4-th row
+            const int rows = (BM + hn - 1) / hn;
+            int p = -1, cnt = 0;
+            for (int w = 0; w < 4; ++w)
+                for (uint64_t m = owned[w]; m && cnt < 128; m &= m - 1, cnt += rows) {
+                    const int i = (tid >> 2) - cnt, rt = w * 64 + __builtin_ctzll(m);
+                    if (i >= 0 && i < rows && h0 * rows + i < BM) p = rt * BM + h0 * rows + i;
+                }
+            __syncthreads();                                                    // the list is read; the loads below land on it
+            const __amdgpu_buffer_rsrc_t rsrc = make_uniform_rsrc(f + (size_t)(s.tok0 + s.vs) * d, (uint32_t)((size_t)s.V * d * sizeof(uint16_t)));
+            const uint32_t sink = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lds_ptr_t)ring + wave * 256);
+            if (p >= 0 && p < s.M) {
+                const int off = min(max(pruned[(size_t)hb * max_V + p], 0), s.V - 1) * d * 2 + (tid & 3) * 128;
+                const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+                for (int c = 0; c < d * 2; c += 512) {                           // behind the sample's rows: outside the buffer, not read
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(size_t)sink, 4, off, c, 0, 0);
+                    if (c == 0) {
+                        wait_loads<0>();
+                        if (__builtin_amdgcn_s_memrealtime() - t0 < COS_CACHED_TICKS) break;    // in a cache already: nothing to help with
+                    }
+                    __builtin_amdgcn_s_sleep(20);                                // 0.7 us: no faster than the tiles
+                }
+            }
+            wait_loads<0>();
+        }
+        return;
+    }
     const SampleGeom s = sample_geom(b, seq_off, vis_start, vis_count, kept_off, max_V, max_keep);
     const int nrt_b = min((s.M + BM - 1) / BM, nrt_launch), nct_b = min((s.k + BN - 1) / BN, nct_launch);
     const int tiles_b = nrt_b * nct_b;
@@ -187,9 +248,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     {
         // bands about as high as a run's block is wide (RB was chosen that way for the launch's grid; a smaller
         // sample gets its own)
-        int rb = RB;
-        if (per_b < per) { rb = 1; while ((rb + 1) * (rb + 1) <= per_b) ++rb; }
-        rb = min(rb, nrt_b);
+        const int rb = band_height(RB, per_b, per, nrt_b);
         const int band = rb * nct_b, nfull = nrt_b / rb;
         if (t_lin < nfull * band) { const int rem = t_lin % band; rt = (t_lin / band) * rb + rem % rb; ct = rem / rb; }
         else { const int t2 = t_lin - nfull * band, rl = nrt_b - nfull * rb; rt = nfull * rb + t2 % rl; ct = t2 / rl; }
@@ -848,7 +907,16 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
         int RB = 1;
         while ((RB + 1) * (RB + 1) <= per) ++RB;
         if (RB > nrt) RB = nrt;
-        const dim3 g((unsigned)(8 * per * ceil_div(B, NG)), (unsigned)ksplit);
+        const int tiles_launch = 8 * per * ceil_div(B, NG);
+        // Without a selection launch in front that has read the rows, they may come from HBM (key and value caches: one of each per layer,
+        // written a step ago).  A CU takes in 48 bytes per ns from there, 95 from the memory-side cache, and its tile waits for
+        // the slowest row; CUs that a single round of tiles leaves idle then request rows ahead of the tiles.  Rows cold:
+        // 3645 rows keeping 365 38.9 -> 33.6 us, 729 48.7 -> 41.4, 1822 52.0 -> 49.9; rows cached: within 1 % (without the test of the
+        // first answers 0 to 4 % lost).  Not where a helper would have more rows than the 128 it can request at a time: helping
+        // with part of the rows gains nothing (5600 rows, 32 idle CUs: 0 % cold, 1 % lost cached).
+        const int idle = 256 - tiles_launch;
+        const bool help = !prepared && ksplit == 1 && TM < 4 && idle > 0 && (long)max_pruned * B <= (long)idle * 128;
+        const dim3 g((unsigned)(help ? 256 : tiles_launch), (unsigned)ksplit);
         float* dots = (float*)(wsb + w.dots_off);
         float* sq = (float*)(wsb + w.sq_off);
         const size_t lds = (size_t)cos_ring_stages(TM) * (BM + (narrow ? 96 : COS_BN)) * 128;

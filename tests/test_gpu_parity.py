@@ -745,6 +745,34 @@ def test_merge_kv_ragged_batch(mode):
         np.testing.assert_array_equal(ref["assign"][b], out["assign"][b])
 
 
+@pytest.mark.parametrize("d,shapes", [(64, [(150, 7)]), (192, [(300, 40)]), (320, [(500, 60), (90, 90), (257, 256), (31, 1)]),
+                                      (256, [(3000, 700)]), (1024, [(3645, 912)])])
+def test_merge_kv_with_helping_workgroups(d, shapes):
+    # sizes at which the cosine launch carries workgroups that only request rows (unsplit, one round, CUs to spare): row bytes that
+    # are no multiple of a helper's 512, samples with nothing pruned and with one kept row.  They compute nothing, so caches and routing
+    # have to be the same whether or not the rows are cached (helpers stop early where they are), and those of the merge of one payload
+    g = torch.Generator(device="cuda"); g.manual_seed(d)
+    P = 5
+    lay = B.Layout([P + V for V, _ in shapes], [P] * len(shapes), [V for V, _ in shapes], [[0]] * len(shapes), [k for _, k in shapes])
+    kc, vc = (torch.randn(lay.sum_N, d, generator=g, device="cuda").bfloat16() for _ in range(2))
+    kept = torch.cat([torch.sort(torch.randperm(V, generator=g, device="cuda")[:k])[0] for V, k in shapes]).to(torch.int32)
+    ws = B.workspace(B.d3tom_workspace_bytes(B.D3TOM_OP_MERGE, lay.B, lay.max_N, lay.max_V, 1, d, 1))
+
+    def outputs():
+        return [torch.full((lay.sum_Nm, d), -1.0, dtype=torch.bfloat16, device="cuda")] + \
+               [torch.full((n,), -1, dtype=torch.int32, device="cuda") for n in (lay.sum_V, lay.sum_keep, lay.sum_Nm)]
+    got, got_v = outputs(), outputs()[0]
+    torch.zeros(1 << 29, dtype=torch.uint8, device="cuda")                  # evicts the rows
+    B.d3tom_merge_kv(kc, vc, lay, kept, 0, got[0], got_v, *got[1:], ws)
+    check_assign(got[1].cpu().numpy()[:shapes[0][0]], kc[P:P + shapes[0][0]].float().cpu().numpy(), 0, shapes[0][0],
+                 kept[:shapes[0][1]].cpu().numpy())
+    for x, y in ((kc, got[0]), (vc, got_v)):
+        ref = outputs()
+        B.d3tom_merge(x, kc, lay, kept, 0, ref[0], *ref[1:], ws)
+        for a, r in zip([y] + got[1:], ref):
+            assert torch.equal(a, r)
+
+
 # ---- decider bookkeeping on the device (Section 3.2) ----------------------------------------------------
 def test_update_deciders_batch_and_chain_into_importance():
     M = 126336
