@@ -56,12 +56,8 @@ void merge_prep_targets(void* merge_ws, int B, int max_V, MergePrep* prep) {
 }
 
 struct SampleGeom { int tok0, N, vs, V, k, M, k0; };
-// more0, more1: further offsets to be read with the sample's
-__device__ __forceinline__ SampleGeom sample_geom(int b, const int32_t* seq_off, const int32_t* vis_start, const int32_t* vis_count,
-                                                  const int32_t* kept_off, int max_V, int max_keep, int& more0, int& more1) {
+__device__ __forceinline__ SampleGeom geom_of(int t0, int t1, int vs, int vc, int k0, int k1, int max_V, int max_keep) {
     SampleGeom s;
-    int t0 = seq_off[b], t1 = seq_off[b + 1], vs = vis_start[b], vc = vis_count[b], k0 = kept_off[b], k1 = kept_off[b + 1];
-    request_together(t0, t1, vs, vc, k0, k1, more0, more1);
     s.tok0 = t0;
     s.N = t1 - t0;
     s.vs = min(max(vs, 0), s.N);
@@ -70,6 +66,13 @@ __device__ __forceinline__ SampleGeom sample_geom(int b, const int32_t* seq_off,
     s.k = min(min(k1 - k0, max_keep), s.V);
     s.M = s.V - s.k;
     return s;
+}
+// more0, more1: further offsets to be read with the sample's
+__device__ __forceinline__ SampleGeom sample_geom(int b, const int32_t* seq_off, const int32_t* vis_start, const int32_t* vis_count,
+                                                  const int32_t* kept_off, int max_V, int max_keep, int& more0, int& more1) {
+    int t0 = seq_off[b], t1 = seq_off[b + 1], vs = vis_start[b], vc = vis_count[b], k0 = kept_off[b], k1 = kept_off[b + 1];
+    request_together(t0, t1, vs, vc, k0, k1, more0, more1);
+    return geom_of(t0, t1, vs, vc, k0, k1, max_V, max_keep);
 }
 __device__ __forceinline__ SampleGeom sample_geom(int b, const int32_t* seq_off, const int32_t* vis_start,
                                                   const int32_t* vis_count, const int32_t* kept_off, int max_V, int max_keep) {
@@ -162,28 +165,73 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     const int32_t* __restrict__ vis_count, const int32_t* __restrict__ kept_idx, const int32_t* __restrict__ kept_off,
     int max_V, int max_keep, int32_t* __restrict__ pruned, const float* __restrict__ rnorm,
     table_t* __restrict__ table, int VP, int per, int RB, int ksplit, float* __restrict__ dots, int nrt_launch, int nct_launch, int prepared,
-    int nB, int NG, float* __restrict__ sq) {
+    int nB, float* __restrict__ sq) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = TM * 64, BN = CBK * 32;
     constexpr int COS_NS = cos_ring_stages(TM);
     constexpr int STAGE = (BM + BN) * 128;          // bytes per ring stage (64 bf16 = 128 B per row)
     constexpr int A_LD = BM / 32;                       // direct loads per wave and stage, A tile (8 rows each)
     constexpr int B_LD = BN / 32;
-    constexpr int LPS = A_LD + B_LD;                    // loads per wave and stage
     extern __shared__ __attribute__((aligned(16))) char ring[];
     __shared__ float rnB[BN];
 
-    // blockIdx.x & 7 is the XCD the hardware puts the workgroup on.  The XCDs form NG groups of 8 / NG; group g has the samples g,
-    // g + NG, ...  The launch is sized
-    // for the largest sample (per = one XCD's share of its tiles); every sample numbers ITS OWN tiles and cuts that sequence
-    // into 8 / NG equal runs, so that a sample with fewer tiles still loads its XCDs alike (numbered on the launch's
-    // grid, the tiles of a short sample would all fall to the first XCDs).
-    const int xcd = blockIdx.x & 7, XG = 8 / NG;
-    const int b = (xcd / XG) + NG * (int)((blockIdx.x >> 3) / per);
-    const int id = (blockIdx.x >> 3) % per;
+    // blockIdx.x & 7 is the XCD the hardware puts the workgroup on.  The launch is sized for the largest sample (per = one XCD's share
+    // of its tiles); every sample numbers ITS OWN tiles and cuts that sequence into 8 equal runs, so that a sample with fewer tiles
+    // still loads its XCDs alike (numbered on the launch's grid, the tiles of a short sample would all fall to the first XCDs).
+    // Where the runs do not come out even the first XCDs have the longer ones, so sample b begins at another XCD than b - 1 does (64
+    // samples of 100 .. 144 rows: 91 -> 68 us, 16 of 200 .. 300 42 -> 36).
+    //
+    // TM 4, for launches of several rounds: the tiles of all samples, one behind the other, are cut into 8 equal runs, one per XCD,
+    // so that the XCDs end together whatever the sizes of the samples (which the host does not know), and a sample's rows
+    // are read by two or three XCDs.  An XCD's run is rounds of 32 tiles, one a CU, and a rest, which would be a round as long as
+    // the others: rests of up to 16 or 8 tiles are cut into half or quarter row tiles (of 0.67 and 0.5 of the time).  Merges at d = 4096 against
+    // runs of a sample's tiles on two XCDs and no cuts: 16 samples of 1152 .. 2304 rows keeping 0.1 .. 0.5 of them 181 -> 163 us,
+    // 12 135 -> 118, 24 274 -> 257, 16 of 2304 251 -> 247, 13 of 2304 keeping a quarter 210 -> 173.
+    const int wx = blockIdx.x >> 3;
+    int b = wx / per, id = wx % per, xcd = blockIdx.x & 7;
+    if (TM < 4) xcd = (xcd + (b < nB ? b : (wx - per * nB) % nB)) & 7;     // (helpers: as the sample that they help)
+    int cut = 0, part = 0;                                 // TM 4: this is part `part` of a row tile cut into 1 << cut
+    if constexpr (TM == 4) {
+        const int lane = threadIdx.x & 63;
+        auto tiles_upto = [&](int b0) {                    // of samples b0 .. b0 + lane
+            int n = 0;
+            if (b0 + lane < nB) {
+                const int i = b0 + lane;
+                const SampleGeom g = geom_of(seq_off[i], seq_off[i + 1], vis_start[i], vis_count[i], kept_off[i], kept_off[i + 1], max_V, max_keep);
+                n = min((g.M + BM - 1) / BM, nrt_launch) * min((g.k + BN - 1) / BN, nct_launch);
+            }
+            return wave_incl_scan(n);
+        };
+        const int first = tiles_upto(0);
+        int all = __builtin_amdgcn_readlane(first, 63);
+        for (int b0 = 64; b0 < nB; b0 += 64) all += __builtin_amdgcn_readlane(tiles_upto(b0), 63);
+        const int lo = (int)((long)all * xcd / 8), n = (int)((long)all * (xcd + 1) / 8) - lo;      // this XCD's run
+        const int odd = n & 31, whole = n - odd;
+        int t = wx;
+        if (t >= whole) {
+            cut = odd <= 8 ? 2 : odd <= 16 ? 1 : 0;
+            t = whole + ((wx - whole) >> cut);
+            part = (wx - whole) & ((1 << cut) - 1);
+        }
+        if (t >= n) return;
+        t += lo;
+        int before = 0;
+        b = nB;
+        for (int b0 = 0; b0 < nB; b0 += 64) {              // t < all: some sample has it
+            const int upto = b0 ? before + tiles_upto(b0) : first;
+            const uint64_t behind = __builtin_amdgcn_ballot_w64(upto > t);
+            if (behind) {
+                const int j = __builtin_ctzll(behind);
+                b = b0 + j;
+                id = t - (j ? __builtin_amdgcn_readlane(upto, j - 1) : before);
+                break;
+            }
+            before = __builtin_amdgcn_readlane(upto, 63);
+        }
+    }
     if (b >= nB) {
         if constexpr (!SPLIT && TM < 4) {
-            // A helper (NG is 1): requests a dword of every 128-byte line of pruned rows that tiles of this XCD use, four lines of each
+            // A helper: requests a dword of every 128-byte line of pruned rows that tiles of this XCD use, four lines of each
             // row at a time, so that the rows come from HBM into the XCD's L2 ahead of the tiles that walk through them.  Of the
             // XCDs that use a row tile, the one with its tile in column `pick` has it.
             const int hx = (int)(blockIdx.x >> 3) - per * nB, nx = (int)(gridDim.x >> 3) - per * nB;   // helper hx of the XCD's nx
@@ -236,13 +284,13 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     const bool derive = SPLIT && !prepared;                // uniform
     if (derive) {
         // a sample that keeps everything has no tiles: its table entries are written here
-        if (s.M <= 0 && id == 0 && xcd % XG == 0 && blockIdx.y == 0)
+        if (s.M <= 0 && id == 0 && xcd == 0 && blockIdx.y == 0)
             for (int r = threadIdx.x; r < s.k; r += 512)
                 table[(size_t)b * VP + min(max(kept_idx[s.k0 + r], 0), s.V - 1)] = table_entry_kept(r);
     }
-    const int per_b = (tiles_b + XG - 1) / XG;
-    if (id >= per_b) return;
-    const int t_lin = (xcd % XG) * per_b + id;
+    const int per_b = TM == 4 ? 32 : (tiles_b + 7) / 8;
+    if (TM < 4 && id >= per_b) return;
+    const int t_lin = TM == 4 ? id : xcd * per_b + id;
     if (t_lin >= tiles_b) return;
     int rt, ct;
     {
@@ -266,6 +314,13 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     // byte offset of this lane inside the visual block for each of its direct loads (rows past the end
     // re-read row 0; masked later); the k-slice is added through the scalar offset
     const __amdgpu_buffer_rsrc_t rsrc = make_uniform_rsrc(f + base, (uint32_t)((size_t)s.V * d * sizeof(uint16_t)));
+    // The A rows of a wave's loads: the first half (quarter) of its loads are the rows of the first half (quarter) of every computing
+    // wave's 16-row blocks, so that a part of a row tile is the first part of everybody's work.
+    auto a_row = [&](int i) { return (wave >> 1) * (BM / 2) + (i >> 1) * 32 + (wave & 1) * 16 + (i & 1) * 8; };
+    // the sample's pruned row behind row `row` of the LDS tile, for the rows that a part has
+    const int p0 = rt * BM + part * (BM >> cut);
+    auto pruned_row = [&](int row) { return p0 + row / (BM / 2) * (BM / 2 >> cut) + row % (BM / 2); };
+    if (p0 >= s.M) return;
     int a_off[A_LD], b_off[B_LD];
     if (derive) {
         // the p-th pruned token is p + the number r of kept tokens in front of it: the first r with kept[r] - r > p
@@ -275,7 +330,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         if (loader) {
 #pragma unroll
             for (int i = 0; i < A_LD; ++i) {
-                const int row = wave * (BM / 4) + i * 8 + (lane >> 3);
+                const int row = a_row(i) + (lane >> 3);
                 const int p = min(rt * BM + row, s.M - 1);
                 int lo = 0, hi = s.k;
                 while (lo < hi) { const int mid = (lo + hi) >> 1; if (kl[mid] - mid > p) hi = mid; else lo = mid + 1; }
@@ -291,9 +346,9 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     } else {
 #pragma unroll
         for (int i = 0; i < A_LD; ++i) {
-            const int row = wave * (BM / 4) + i * 8 + (lane >> 3);
+            const int row = a_row(i) + (lane >> 3);
             const int cg = (lane & 7) ^ ((row >> 1) & 7);
-            const int p = rt * BM + row;
+            const int p = pruned_row(row);
             const int m = min(max((p < s.M) ? pr[p] : pr[0], 0), s.V - 1);
             a_off[i] = m * d * 2 + cg * 16;
         }
@@ -318,22 +373,19 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     // LDS destinations are wave-uniform: this wave's first row of the A (B) tile, made a scalar once so
     // that a load costs one scalar add for its M0 value and no vector instruction
     const uint32_t ring0 = (uint32_t)(size_t)(lds_ptr_t)ring;
-    const uint32_t a_lds = __builtin_amdgcn_readfirstlane(ring0 + wave * (BM / 4) * 128);
+    const uint32_t a_lds = __builtin_amdgcn_readfirstlane(ring0 + a_row(0) * 128);
     const uint32_t b_lds = __builtin_amdgcn_readfirstlane(ring0 + BM * 128 + wave * (BN / 4) * 128);
-    // loads [n0, n1) of a stage's LPS loads (A tile first, then B tile)
-    auto issue_part = [&](int kt, int stage, int n0, int n1) {
+    auto issue = [&](int kt, int stage, auto rows) {
+        constexpr int A_N = A_LD * decltype(rows)::value / (TM * 2);
 #pragma unroll
-        for (int i = 0; i < A_LD; ++i)
-            if (i >= n0 && i < n1)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(size_t)(a_lds + stage * STAGE + i * 8 * 128), 16,
-                                                         a_off[i], (kt0 + kt) * (COS_BK * 2), 0, 0);
+        for (int i = 0; i < A_N; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(size_t)(a_lds + stage * STAGE + ((i >> 1) * 32 + (i & 1) * 8) * 128), 16,
+                                                     a_off[i], (kt0 + kt) * (COS_BK * 2), 0, 0);
 #pragma unroll
         for (int i = 0; i < B_LD; ++i)
-            if (A_LD + i >= n0 && A_LD + i < n1)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(size_t)(b_lds + stage * STAGE + i * 8 * 128), 16,
-                                                         b_off[i], (kt0 + kt) * (COS_BK * 2), 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_ptr_t)(size_t)(b_lds + stage * STAGE + i * 8 * 128), 16,
+                                                     b_off[i], (kt0 + kt) * (COS_BK * 2), 0, 0);
     };
-    auto issue = [&](int kt, int stage) { issue_part(kt, stage, 0, LPS); };
 
     constexpr int RBK = TM * 2;                         // 16-row blocks of a wave's (TM*32) x (CBK*16) tile
     f32x4 acc[RBK][CBK];
@@ -350,14 +402,17 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     // that wait stalls the MFMA stream, so the loads have waves of their own.  One s_barrier per stage:
     // the loaders arrive at the kt-th once stage kt has landed, the consumers once they have read stage kt-1 out of LDS,
     // whose slot the loaders then refill with stage kt+COS_NS-1.
+    auto sweep = [&](auto rows) {
+    constexpr int NR = decltype(rows)::value;              // 16-row blocks of a computing wave: all RBK, or the first of them
     if (loader) {
+        constexpr int LPS = A_LD * NR / RBK + B_LD;         // loads per wave and stage
 #pragma unroll
         for (int st = 0; st < COS_NS - 1; ++st)
-            if (st < nkt) issue(st, st);
+            if (st < nkt) issue(st, st, rows);
         for (int kt = 0; kt < nkt; ++kt) {
             if (kt + COS_NS - 2 <= nkt - 1) wait_loads_and_barrier<(COS_NS - 2) * LPS>();
             else wait_loads_and_barrier<0>();
-            if (kt + COS_NS - 1 < nkt) issue(kt + COS_NS - 1, (kt + COS_NS - 1) % COS_NS);
+            if (kt + COS_NS - 1 < nkt) issue(kt + COS_NS - 1, (kt + COS_NS - 1) % COS_NS, rows);
         }
     } else {
         // A stage is two k-steps of 32.  The fragments of the next k-step are read behind the first MFMAs of this one, across
@@ -372,12 +427,12 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         };
         auto multiply = [&](int ks, const char* next, bool read) {  // MFMAs of k-step ks; reads the other one's fragments from `next`
 #pragma unroll
-            for (int n = 0; n < RBK * CBK; ++n) {
+            for (int n = 0; n < NR * CBK; ++n) {
                 const int i = n / CBK, j = n % CBK;
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[ks][i], fr[ks][RBK + j], acc[i][j], 0, 0, 0);
-                if (read && n < RBK + CBK) {
+                if (read && n < NR + CBK) {
                     __builtin_amdgcn_sched_barrier(0);
-                    read_one(next, ks ^ 1, n);
+                    read_one(next, ks ^ 1, n < NR ? n : RBK + n - NR);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -389,7 +444,7 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         };
         wait_loads_and_barrier<0>();
 #pragma unroll
-        for (int f = 0; f < RBK + CBK; ++f) read_one(ring, 0, f);
+        for (int f = 0; f < NR + CBK; ++f) read_one(ring, 0, f < NR ? f : RBK + f - NR);
         int slot = 0;
         for (int kt = 0; kt + 1 < nkt; ++kt) {
             const char* sb = ring + slot * STAGE;
@@ -402,6 +457,12 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         multiply(0, ring + slot * STAGE, true);
         multiply(1, nullptr, false);
     }
+    };
+    if constexpr (TM == 4) {
+        if (cut == 2) sweep(std::integral_constant<int, RBK / 4>{});
+        else if (cut) sweep(std::integral_constant<int, RBK / 2>{});
+        else sweep(std::integral_constant<int, RBK>{});
+    } else sweep(std::integral_constant<int, RBK>{});
 
     if constexpr (SPLIT) {
         // partial products of this k-slice: block (slice, tile) of BM x 128 floats, summed by cos_reduce_argmax
@@ -457,8 +518,8 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     }
     __syncthreads();
     for (int t = tid; t < BM * 2; t += 512) {
-        const int row = t >> 1, half = t & 1;                  // half 0: slots of wave column 0 (lower slots)
-        const float2* cr = cand + (row * 2 + half) * 17;
+        const int row = t >> 1, side = t & 1;                  // side 0: slots of wave column 0 (lower slots)
+        const float2* cr = cand + (row * 2 + side) * 17;
         float best = -INFINITY; int bidx = 0x7FFFFFFF;
 #pragma unroll
         for (int q2 = 0; q2 < 16; ++q2) {
@@ -471,8 +532,8 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
         const int oi = __shfl_xor(bidx, 1, WAVE);
         const bool take = (ov > best) | ((ov == best) & (oi < bidx));
         best = take ? ov : best; bidx = take ? oi : bidx;
-        const int p = rt * BM + row;
-        if (half == 0 && p < s.M) {
+        const int p = pruned_row(row);
+        if (side == 0 && p < s.M && row % (BM / 2) < (BM / 2 >> cut)) {
             const int tok = min(max(pr[p], 0), s.V - 1);
             atomicMax(table + (size_t)b * VP + tok, table_entry(best, bidx));
         }
@@ -861,16 +922,19 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
     if (mfma && max_pruned > 0) {
         const int nct = ceil_div(max_keep, COS_BN);
         // as long as the 64-row tiles still fit one round of the 256 CUs they finish sooner than half as many
-        // 128-row tiles (a 64-row tile's k-loop is ~0.7 of a 128-row tile's)
-        // with several rounds of 128-row tiles (large batches) 256-row tiles move a third less operand data per flop
-        TM = ((long)nct * ceil_div(max_pruned, 128) * B > 768) ? 4 : ((long)nct * ceil_div(max_pruned, 64) * B > 256) ? 2 : 1;
+        // 128-row tiles (a 64-row tile's k-loop is ~0.7 of a 128-row tile's); several rounds of 128-row tiles are 256-row tiles, which
+        // move a third less operand data per flop and whose rests the kernel cuts (against 128-row tiles, merges at d = 4096: 4500 rows keeping
+        // 0.2 .. 0.5 70 -> 59 us, 5 samples of 2304 90 -> 76, 9 of 1152 .. 2304 114 -> 83).  From 16 samples on, where the bounds that the
+        // host has are far above what the samples need, they are also better than one round by those bounds: 24 samples of 300 .. 400 rows
+        // at d = 2048 45 -> 39, 100 of 100 .. 144 at 1024 44 -> 42; two to ten samples lose up to 17 %.
+        const long t64 = (long)nct * ceil_div(max_pruned, 64) * B, t128 = (long)nct * ceil_div(max_pruned, 128) * B;
+        TM = (t128 > 256 || (B >= 16 && t64 > COS_SPLIT_BLOCKS / 2)) ? 4 : t64 > 256 ? 2 : 1;
         // too few 64 x 128 tiles for 256 CUs (short sequences): cut the contraction into k-slices as well
         if (TM == 1) {
-            const long tiles = (long)ceil_div(max_pruned, 64) * nct * B;
             const int stages = d_sim / COS_BK;
-            if (tiles <= COS_SPLIT_BLOCKS / 2) {
+            if (t64 <= COS_SPLIT_BLOCKS / 2) {
                 ksplit = 16;
-                while (ksplit > 1 && (tiles * ksplit > COS_SPLIT_BLOCKS || stages % ksplit || stages / ksplit < cos_ring_stages(1))) ksplit >>= 1;
+                while (ksplit > 1 && (t64 * ksplit > COS_SPLIT_BLOCKS || stages % ksplit || stages / ksplit < cos_ring_stages(1))) ksplit >>= 1;
             }
         }
     }
@@ -896,18 +960,13 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
         const int nct96 = ceil_div(max_keep, 96);
         const bool narrow = ksplit == 1 && TM < 4 && (long)nrt * nct96 * B <= 256;
         if (narrow) nct = nct96;
-        // tiles of a sample in 8 equal runs (one per XCD); bands about as high as a run's block is wide
-        // Batches of several rounds: a sample's tiles on two XCDs instead of eight, so that an XCD's L2 serves each operand row to more of
-        // them (16 samples of 2304 rows: 181 us on eight XCDs, 177 on four, 167 on two, 173 on one).  Only where the four pairs get
-        // enough samples for their sizes to even out.  Time of the merge on eight XCDs over that on two, median of 16 draws of sizes
-        // 1152 .. 2304 and keep ratios 0.1 .. 0.5: 8 samples 1.00, 10 1.01, 12 (three a pair) 1.02, 13 1.00 (and 0.95 in the
-        // mean), 14 1.03, 15 1.03, 16 1.04, 17 1.02, 18 1.03, 19 1.06, 22 1.02.
-        const int NG = (TM == 4 && (B == 12 || B >= 14)) ? 4 : 1;
-        const int per = ceil_div(nrt * nct, 8 / NG);
+        // tiles of a sample in 8 equal runs (one per XCD); bands about as high as a run's block is wide.  256-row tiles: the tiles of all
+        // samples in 8 equal runs of whole tiles and parts of tiles behind them (a rest of 8 tiles, 32 parts, has the most workgroups more than tiles).
+        const int per = TM == 4 ? ceil_div(nrt * nct * B, 8) + 24 : ceil_div(nrt * nct, 8);
         int RB = 1;
-        while ((RB + 1) * (RB + 1) <= per) ++RB;
+        while ((RB + 1) * (RB + 1) <= (TM == 4 ? 32 : per)) ++RB;
         if (RB > nrt) RB = nrt;
-        const int tiles_launch = 8 * per * ceil_div(B, NG);
+        const int tiles_launch = 8 * per * (TM == 4 ? 1 : B);
         // Without a selection launch in front that has read the rows, they may come from HBM (key and value caches: one of each per layer,
         // written a step ago).  A CU takes in 48 bytes per ns from there, 95 from the memory-side cache, and its tile waits for
         // the slowest row; CUs that a single round of tiles leaves idle then request rows ahead of the tiles.  Rows cold:
@@ -923,7 +982,7 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
 #define D3TOM_COS(TMV, CBKV, SPLITV)                                                                                        \
     D3TOM_LAUNCH(COS_ARGMAX, st, (cos_argmax_bf16<TMV, CBKV, SPLITV><<<g, 512, lds, st>>>(                                     \
         (const uint16_t*)sim, d_sim, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep, pruned, rnorm, table, \
-        w.VP, per, RB, ksplit, dots, nrt, nct, prepared ? 1 : 0, B, NG, sq)))
+        w.VP, per, RB, ksplit, dots, nrt, nct, prepared ? 1 : 0, B, sq)))
         if (TM == 4) D3TOM_COS(4, 4, false);
         else if (TM == 2) { if (narrow) D3TOM_COS(2, 3, false); else D3TOM_COS(2, 4, false); }
         else if (ksplit > 1) D3TOM_COS(1, 4, true);

@@ -101,6 +101,23 @@ def test_merge_large_batch_tiles(batch):
     _chain(samples, keeps, "bf16", check=[0, 1, 2, 5, batch - 1])
 
 
+@pytest.mark.parametrize("big,small", [(1, 15), (2, 14), (4, 12), (7, 9), (1, 69), (3, 66), (0, 130), (0, 31)])
+def test_merge_batch_tiles_in_equal_runs(big, small):
+    """The tiles of a whole batch cut into one run per XCD, whose rest of the last round is cut into quarter, half or no parts of a
+    tile: totals of 7 to 32 tiles a run, samples before and behind the 64 looked at together, pruned counts around a tile and its parts."""
+    sizes = [(2304, 1152), (2303, 1279), (2100, 900), (1409, 1153), (2304, 1024), (2047, 1000), (1700, 1100)][:big]
+    sizes += [[(400, 144), (1, 1), (129, 64), (321, 64), (90, 90), (577, 320), (65, 1), (256, 255), (513, 256)][i % 9] for i in range(small)]
+    sizes = [sizes[i] for i in np.random.default_rng(big).permutation(len(sizes))]
+    rng = np.random.default_rng(small)
+    samples = [W.random_case(700 + i, V + 5, 64, 1, 5, V, 1, dtype="bf16", centres=max(2, V // 6)) for i, (V, _) in enumerate(sizes)]
+    kept = [np.sort(rng.choice(V, size=k, replace=False)).astype(np.int32) for V, k in sizes]
+    out = GpuStep(samples, [k for _, k in sizes], "bf16").merge(kept)
+    for b, s in enumerate(samples):
+        check_assign(out["assign"][b], s["x"], s["vis_start"], s["V"], kept[b],
+                     only=None if s["V"] < 700 else np.sort(rng.choice(s["V"], 200, replace=False)))
+        check_merge({key: out[key][b] for key in out}, s["x"], s["vis_start"], s["V"], kept[b], "bf16")
+
+
 @pytest.mark.parametrize("dh,copies", [(64, 8), (128, 8), (64, 1), (128, 1)])
 def test_importance_decider_groups_and_chunks(dh, copies):
     """Decider counts around the 128 rows staged at a time and around 16-row blocks, key counts around the key chunks of both
