@@ -319,6 +319,8 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     auto a_row = [&](int i) { return (wave >> 1) * (BM / 2) + (i >> 1) * 32 + (wave & 1) * 16 + (i & 1) * 8; };
     // the sample's pruned row behind row `row` of the LDS tile, for the rows that a part has
     const int p0 = rt * BM + part * (BM >> cut);
+    if (TM == 4)
+        while (cut < 2 && s.M - p0 <= (BM / 2 >> cut)) ++cut;                   // few rows left: a smaller part has them
     auto pruned_row = [&](int row) { return p0 + row / (BM / 2) * (BM / 2 >> cut) + row % (BM / 2); };
     if (p0 >= s.M) return;
     int a_off[A_LD], b_off[B_LD];
@@ -398,6 +400,10 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
     for (int j = 0; j < (SPLIT ? CBK : 1); ++j) bb[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const bool squares = SPLIT && rt == 0 && wm == 0;    // uniform
 
+    // a wave whose rows or columns all lie past the sample's only keeps step: its products would cost power, and clock with it
+    // (with the smaller parts for few rows above: 80 samples of 300 .. 800 rows at d = 2048 118 -> 111 us, 32 of 600 .. 1200 at 4096 149 -> 148)
+    const bool none = ct * BN + wn * (BN / 2) >= s.k || pruned_row(wm * (BM / 2)) >= s.M;
+
     // A wave that issues a direct load waits for room in the CU's vector-memory queue; in a computing wave
     // that wait stalls the MFMA stream, so the loads have waves of their own.  One s_barrier per stage:
     // the loaders arrive at the kt-th once stage kt has landed, the consumers once they have read stage kt-1 out of LDS,
@@ -443,6 +449,10 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
             __builtin_amdgcn_sched_barrier(0);
         };
         wait_loads_and_barrier<0>();
+        if (none) {
+            for (int kt = 0; kt + 1 < nkt; ++kt) phase_barrier();
+            return;
+        }
 #pragma unroll
         for (int f = 0; f < NR + CBK; ++f) read_one(ring, 0, f < NR ? f : RBK + f - NR);
         int slot = 0;
