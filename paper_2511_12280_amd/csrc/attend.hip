@@ -376,37 +376,51 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     using no = std::integral_constant<bool, false>;
     constexpr int KEEP = (NS - 3) * 2 * LD;
     bool first = true;
-    for (int pass = 1;; ++pass) {
+    // all tiles of keys; LIVE = false for a wave whose queries all lie past the end of the sample, which only requests its part of the
+    // tiles and keeps step: in a last tile of at most 128 queries a SIMD has one wave to serve instead of two, in others the card has
+    // less to do.  (Last tiles computed in full before: 16 samples of 614 .. 1536 keys 346 -> 332 us, 64 of 300 .. 1000 at 8
+    // heads 166 -> 155, 12 of 270 .. 800 84.6 -> 82.3, one of 1951 61.4 -> 60.5, of 3700 203 -> 201; 8 of 1000, 232 queries in the last, 133.)
+    auto sweep = [&](auto live_c) {
+        constexpr bool LIVE = decltype(live_c)::value;
         issue(2);
+        if constexpr (LIVE) {
 #pragma unroll
-        for (int f = 0; f < KPRE; ++f) read_first(ring, f);
+            for (int f = 0; f < KPRE; ++f) read_first(ring, f);
+        }
         // Stage j + 1 has to have landed when the softmax phase of tile j begins (its first fragments are read there).  Groups that
         // share the ring: both wait for their loads before the barrier that ends group 0's MFMA phase of tile j.  Stages behind
         // j + 1 stay in flight.
         if (grp == 1) { if (first) wait_loads<KEEP>(); phase_barrier(); }
         bool wait0 = grp == 0 && first;         // (behind another item the first two stages have landed, and its stores may still be on their way)
-        mfma_phase(0, yes(), no());
+        if constexpr (LIVE) mfma_phase(0, yes(), no());
         // The last tile is peeled off: a loop left in its middle keeps both the accumulators before and after the MFMA phase alive.
 #pragma unroll 1
         for (int j = 0; j + 1 < ntile; ++j) {
             if (wait0) wait_loads<KEEP>();
             wait0 = grp == 0;
             phase_barrier();
-            __builtin_amdgcn_s_setprio(2);
-            softmax_phase(j, no());
-            __builtin_amdgcn_s_setprio(0);
-            __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): the fragments are there (a wait the compiler knows of)
+            if constexpr (LIVE) {
+                __builtin_amdgcn_s_setprio(2);
+                softmax_phase(j, no());
+                __builtin_amdgcn_s_setprio(0);
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): the fragments are there (a wait the compiler knows of)
+            } else {
+                issue(j + AHEAD);
+            }
             if (grp == 1) wait_loads<KEEP>();
             phase_barrier();
-            mfma_phase(j + 1, yes(), yes());
+            if constexpr (LIVE) mfma_phase(j + 1, yes(), yes());
         }
         if (grp == 0) wait_loads<0>();
         phase_barrier();
-        softmax_phase(ntile - 1, yes());
+        if constexpr (LIVE) softmax_phase(ntile - 1, yes());
         if (grp == 1) wait_loads<0>();
         phase_barrier();
-        mfma_phase(ntile, no(), yes());
+        if constexpr (LIVE) mfma_phase(ntile, no(), yes());
+    };
+    for (int pass = 1;; ++pass) {
+        if (q0 < n) sweep(yes()); else sweep(no());
         wait_loads<0>();                        // nothing may be in flight into LDS when the workgroup ends
         if (grp == 0) phase_barrier();
 

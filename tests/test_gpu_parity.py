@@ -329,6 +329,18 @@ def test_attend_tiles_in_turn(H, dh, longest, batch, weighted):
         check_attend(o, q, k, v, "bf16", rows=np.union1d(rows, [len(q) - 1]), key_weight=key_weights(len(q), vs, c) if weighted else None)
 
 
+@pytest.mark.parametrize("H,dh,n,weighted", [(60, 128, 520, False), (60, 128, 640, True), (60, 128, 641, False), (60, 64, 705, True), (60, 64, 737, False),
+                                             (2, 128, 513, False), (2, 128, 560, True), (2, 64, 656, False)])
+def test_attend_last_tile_with_few_queries(H, dh, n, weighted):
+    """One round of 256-query tiles (60 heads) or 128-query tiles (2) whose last tile leaves one to seven of its eight waves without
+    a query: those only load and keep step."""
+    q, k, v = W.random_qkv(910 + n, n, H, dh, "bf16")
+    vs, c = n // 5, (1 + np.arange(n // 2) % 37).astype(np.int32)
+    o = (gpu_attend_weighted([(q, k, v)], [c], [vs], "bf16") if weighted else gpu_attend([(q, k, v)], "bf16"))[0]
+    rows = np.union1d(np.arange(0, n, 31), np.arange(max(n - 9, 0), n))
+    check_attend(o, q, k, v, "bf16", rows=rows, key_weight=key_weights(n, vs, c) if weighted else None)
+
+
 def test_attend_special_cases_bf16():
     q, k, v = W.random_qkv(5, 150, 2, 128, "bf16", spread=2.0)
     v1 = np.broadcast_to(v[:1], v.shape).copy()
