@@ -138,39 +138,63 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 
     // An item is a tile of BQ queries of one head.  XCD x has the heads hb = x, x + 8, ... of hb = (the sample's place) * H + head, the
     // tiles of a head one after the other.  One item per workgroup (places = samples as they come), or (TURNS) workgroup li of the W of
-    // an XCD takes its items li, 2 W - 1 - li, 2 W + li, ..., samples in order of falling length.
+    // an XCD takes its items li, 2 W - 1 - li, 2 W + li, ..., in order of falling time.  Up to 32 samples may have two places, one for the last
+    // tile if that leaves half of the waves without a query (0.72 of the others' time) and one for the other tiles: where the tiles fill
+    // the rounds better with the short ones behind all others (2060 .. 2100 keys 106 -> 98 us, 3 x 650 41 -> 38, 8 x 200 .. 700 41.5 -> 39.7,
+    // 24 x 600 .. 1500 at 16 heads of 64 195 -> 186).  Apart from its head's other tiles a short one does not find K and V in the XCD's L2: always
+    // behind the others, 6 x 800 keys take 82 instead of 76.
     const int xcd = blockIdx.x & 7, li = blockIdx.x >> 3;
     constexpr int W = ATT_TURNS_WGS;
-    __shared__ int tab[4][TURNS ? WAVE : 1];               // by place: first token, tokens, sample, items up to and with this one
+    __shared__ int4 tab[TURNS ? WAVE : 1];                 // by place: first token, tokens, sample (its complement: the last tile only), tiles
+    __shared__ int ends[TURNS ? WAVE : 1];                 // by place: items up to and with this one
     int tok0, n, h, b, qt;
     auto item = [&](int pass) {
         const int idx = pass * W + ((pass & 1) ? W - 1 - li : li);
-        const int end = tab[3][TURNS ? lane : 0];
+        const int end = ends[TURNS ? lane : 0];
         const int place = __popcll(__builtin_amdgcn_ballot_w64(end <= idx));
-        if (place >= nB) return false;
+        if (place >= WAVE) return false;
         const int rem = idx - (place ? __builtin_amdgcn_readlane(end, place - 1) : 0);
-        tok0 = __builtin_amdgcn_readfirstlane(tab[0][place]);
-        n = __builtin_amdgcn_readfirstlane(tab[1][place]);
-        b = __builtin_amdgcn_readfirstlane(tab[2][place]);
-        const int tiles = (n + BQ - 1) / BQ;
+        const int4 e = tab[place];
+        tok0 = __builtin_amdgcn_readfirstlane(e.x);
+        n = __builtin_amdgcn_readfirstlane(e.y);
+        const int smp = __builtin_amdgcn_readfirstlane(e.z), tiles = __builtin_amdgcn_readfirstlane(e.w);
+        b = smp < 0 ? ~smp : smp;
         h = ((xcd - place * H) & 7) + 8 * (rem / tiles);
-        qt = rem % tiles;
+        qt = smp < 0 ? (n - 1) / BQ : rem % tiles;
         return true;
     };
     if constexpr (TURNS) {
         if (wave == 0) {
-            const int c0 = cu[min(lane, nB - 1)], c1 = cu[min(lane + 1, nB)];
-            const int len = lane < nB ? min(c1 - c0, WGT ? ATT_WKEYS : 0x7FFFFFFF) : -1;
-            int rank = 0;
-            for (int j = 0; j < nB; ++j) {
-                const int other = __builtin_amdgcn_readlane(len, j);
-                rank += (other > len) || (other == len && j < lane);
+            const bool two = nB <= WAVE / 2, is_last = two && lane >= WAVE / 2;
+            const int smp = two ? lane & (WAVE / 2 - 1) : lane;
+            const int c0 = cu[min(smp, nB - 1)], c1 = cu[min(smp + 1, nB)];
+            const int len = smp < nB ? max(min(c1 - c0, WGT ? ATT_WKEYS : 0x7FFFFFFF), 0) : 0;
+            const int left = len % BQ, all = (len + BQ - 1) / BQ;
+            int lone = two && left > 0 && left <= BQ / 2;
+            {
+                // passes over the XCD's units with the last tiles among the others, and with them behind all others
+                const int sum = is_last ? 0 : all, sum_lone = is_last ? 0 : lone;
+                const int P = __builtin_amdgcn_readlane(wave_incl_scan(sum), 63) * H / 8, S = __builtin_amdgcn_readlane(wave_incl_scan(sum_lone), 63) * H / 8;
+                const int among = (P + W - 1) / W, full = (P - S + W - 1) / W, free = full * W - (P - S);
+                const float t0 = (float)among * ((float)P - 0.28f * (float)S) / (float)max(P, 1);
+                const float t1 = (float)full + 0.72f * (float)(S > free ? (S - free + W - 1) / W : 0);
+                if (t1 > 0.99f * t0) lone = 0;
             }
-            if (lane < nB) { tab[0][rank] = c0; tab[1][rank] = len; tab[2][rank] = lane; }
+            const int others = all - lone;
+            const int mine = is_last ? lone : others;
+            const float time = mine > 0 ? (float)len * (is_last ? 0.72f : 1.f) : -1.f;
+            int rank = 0;
+            for (uint64_t m = __builtin_amdgcn_ballot_w64(mine > 0); m; m &= m - 1) {
+                const int j = __builtin_ctzll(m);
+                const float other = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(time), j));
+                rank += (other > time) || (other == time && j < lane);
+            }
+            tab[lane].w = 0;
+            if (mine > 0) tab[rank] = make_int4(c0, len, is_last ? ~smp : smp, mine);
+            asm volatile("" ::: "memory");                  // what follows reads what other lanes have written
             const int h0 = (xcd - lane * H) & 7;
             const int heads = h0 < H ? (H - h0 + 7) >> 3 : 0;
-            const int tiles = lane < nB ? (max(tab[1][min(lane, nB - 1)], 0) + BQ - 1) / BQ : 0;
-            tab[3][lane] = wave_incl_scan(heads * tiles);
+            ends[lane] = wave_incl_scan(heads * tab[lane].w);
         }
         __syncthreads();
         if (!item(0)) return;
