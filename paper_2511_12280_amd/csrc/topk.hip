@@ -24,8 +24,9 @@
 namespace d3tom {
 
 constexpr int TOPK_THREADS = 1024;
-constexpr int TOPK_STREAM_WGS = 96;        // streaming workgroups per launch (measured at 3645 rows of 8 KB: 32 -> 22.5 us, 64 -> 13.8,
-                                           // 96 -> 13.1, 127 -> 13.5, 255 -> 14.5 us for the whole launch)
+constexpr int TOPK_STREAM_WGS = 128;       // streaming workgroups per launch.  Whole steps of 3645 cold rows of 8 KB, 2 and 64 deciders: 64
+                                           // of them 68.9 and 140.0 us, 96 67.3 and 137.9, 112 66.0 and 137.7, 128 65.5 and 135.7, 144 the same,
+                                           // 192 66.2 and 136.5; with the rows cached all within 0.5 %
 
 // Kept count at a keep ratio (Section 3.2: rank at most (1 - alpha)|V|; a fractional product is rounded up):
 // ceil(ratio * V - 1e-9) clamped to [1, V], in double with separately rounded product and difference, i.e.
