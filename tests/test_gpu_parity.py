@@ -329,6 +329,30 @@ def test_attend_tiles_in_turn(H, dh, longest, batch, weighted):
         check_attend(o, q, k, v, "bf16", rows=np.union1d(rows, [len(q) - 1]), key_weight=key_weights(len(q), vs, c) if weighted else None)
 
 
+def _drawn_lengths(seed, choices=(1, 64, 65, 128, 129, 192, 193, 256, 257, 320, 384, 385, 520, 300)):
+    import random
+    r = random.Random(seed)
+    r.choice([31, 32, 30])
+    return [r.choice(choices) for _ in range(32)]
+
+
+@pytest.mark.parametrize("H,dh,lens,weighted", [
+    (32, 128, [2060], False), (32, 128, [2060], True), (32, 128, [650] * 3, False), (20, 64, [1025, 1030, 260, 300, 513], True),
+    (9, 128, _drawn_lengths(9), True), (13, 128, _drawn_lengths(393), False), (12, 64, _drawn_lengths(352), False),     # as many samples as have two places
+])
+def test_attend_short_last_tiles_behind_the_others(H, dh, lens, weighted):
+    """Lengths at which the last tiles with at most half of their queries are items of their own behind all others (the estimate of the
+    passes over an XCD's 32 units says so), heads that do not divide among the XCDs too: every row has to be there."""
+    base = W.random_qkv(930 + H, max(lens), H, dh, "bf16")
+    qkv = [tuple(np.roll(t, i, axis=0)[:n] for t in base) for i, n in enumerate(lens)]
+    vis, counts = [n // 5 for n in lens], [(1 + np.arange(n // 2) % 37).astype(np.int32) for n in lens]
+    outs = gpu_attend_weighted(qkv, counts, vis, "bf16") if weighted else gpu_attend(qkv, "bf16")
+    for (q, k, v), o, vs, c in zip(qkv, outs, vis, counts):
+        n = len(q)
+        rows = np.union1d(np.arange(0, n, 1 if n < 66 else 41), np.arange(max(n - 12, 0), n))
+        check_attend(o, q, k, v, "bf16", rows=rows, key_weight=key_weights(n, vs, c) if weighted else None)
+
+
 @pytest.mark.parametrize("H,dh,n,weighted", [(60, 128, 520, False), (60, 128, 640, True), (60, 128, 641, False), (60, 64, 705, True), (60, 64, 737, False),
                                              (2, 128, 513, False), (2, 128, 560, True), (2, 64, 656, False)])
 def test_attend_last_tile_with_few_queries(H, dh, n, weighted):
