@@ -259,9 +259,10 @@ __global__ __launch_bounds__(256, 2) void imp_stats_bf16(
         for (int w = 0; w < 16; ++w) a[w] = wstat[w * wrows + t];
         float m = a[0].x, z = 0.f;
 #pragma unroll
-        for (int w = 1; w < 16; ++w) m = fmaxf(m, a[w].x);              // finite: the chunk's first key exists
+        for (int w = 1; w < 16; ++w) m = fmaxf(m, a[w].x);
+        const float ref = (m == -INFINITY) ? 0.f : m;                   // every logit of the chunk is -inf: it counts as empty, (-inf, 0)
 #pragma unroll
-        for (int w = 0; w < 16; ++w) z += a[w].y * __builtin_amdgcn_exp2f(a[w].x - m);
+        for (int w = 0; w < 16; ++w) z += a[w].y * __builtin_amdgcn_exp2f(a[w].x - ref);
         part[((size_t)(b * H + h) * NCH + chunk) * DPAD + b0 * 16 + t] = make_float2(m, z);
     }
     }

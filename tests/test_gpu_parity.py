@@ -151,6 +151,29 @@ def test_importance_streaming_stages(dh):
         np.testing.assert_array_equal(S[i], S[len(batch) - len(samples) + i])
 
 
+@pytest.mark.parametrize("dtype,H,dh,D,N,copies", [
+    ("bf16", 2, 128, 9, 1100, 1), ("bf16", 2, 64, 40, 1100, 1),           # chunks of 256 keys, logits kept or not
+    ("bf16", 16, 64, 9, 1100, 2), ("bf16", 16, 128, 40, 1100, 2),         # chunks of 512 keys, logits kept or not
+    ("bf16", 16, 128, 144, 1200, 16), ("bf16", 16, 64, 130, 1200, 16),    # keys streamed, chunks of 640
+    ("f32", 2, 64, 9, 300, 1), ("f32", 2, 64, 40, 300, 1)])               # generic kernels
+def test_importance_chunk_of_infinite_logits(dtype, H, dh, D, N, copies):
+    """Keys whose logits are all -inf (an infinite key channel) have probability 0, also where they are all the keys of a chunk of the
+    first sweep: the first chunk, one in the middle, the ragged last one."""
+    samples = []
+    for i, (j0, j1) in enumerate([(0, 640), (256, 1088), (512, N), (N - 1, N), (0, N - 1)]):
+        s = W.random_case(680 + i, N, H * dh, H, 3, N - 3 - D, D, dtype=dtype)
+        s["q"][:, :, 5] = 0.5
+        s["k"][j0:min(j1, N - 1 if j0 == 0 else N), :, 5] = -np.inf
+        samples.append(s)
+    batch = samples * copies
+    S = GpuStep(batch, [8] * len(batch), dtype).importance()
+    for i, s in enumerate(samples):
+        ref = oracle.importance(s["q"], s["k"], s["dec_idx"], s["vis_start"], s["V"])
+        assert np.isfinite(ref).all()
+        check_scores(S[i], ref)
+        np.testing.assert_array_equal(S[i], S[len(batch) - len(samples) + i])
+
+
 @pytest.mark.parametrize("dtype,H,dh", [("f32", 4, 64), ("f32", 3, 36), ("bf16", 2, 40), ("f32", 400, 8)])
 def test_importance_generic_kept_logits(dtype, H, dh):
     """Generic kernels: decider counts around the largest set that keeps its logits, key counts around blocks of 16 and 256; with
