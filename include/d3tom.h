@@ -364,6 +364,21 @@ int d3tom_linear(const void* a, const void* w, int rows, int n_w_rows, int K, in
 int d3tom_linear_tile(const void* a, const void* w, int rows, int n_w_rows, int K, int epilogue,
                       const void* residual, void* out, int out_chunk, int tile, void* stream);
 
+/* For tuning and tests: the tiles that the library chooses from, by index, and its choice for a projection (host only).
+ *   d3tom_linear_tile_name  "192x256" (rows x rows of w) or "64x128 loaders"; NULL past the last index
+ *   d3tom_linear_plan       int32 plan[4]: tile; how many leading rows of w it takes, and the tile of a second launch for the others (-1:
+ *                           there is none); slices of the contraction (1: not cut), at most partial_floats float32 values in all
+ *   d3tom_linear_pinned     d3tom_linear with the tile of that index, and with the two further epilogues of the stack:
+ *                           D3TOM_LINEAR_PARTIAL  out = float32 [slices, rows, n_w_rows], the products of each of `slices` equal parts of K
+ *                           D3TOM_LINEAR_ROPE     PLAIN for q | k | v (n_w_rows = 3 out_chunk), the first two rotated in heads of rope_dh
+ *                                                 (64 or 128) channels: extra = float32 (cos, sin) [rows, rope_dh / 2, 2]
+ *                           extra: the residual of D3TOM_LINEAR_RESIDUAL; slices and rope_dh are read by the epilogue that has them */
+enum { D3TOM_LINEAR_PARTIAL = 3, D3TOM_LINEAR_ROPE = 4 };
+const char* d3tom_linear_tile_name(int index);
+int d3tom_linear_plan(int rows, int n_w_rows, int K, size_t partial_floats, int32_t* plan /* host */);
+int d3tom_linear_pinned(const void* a, const void* w, int rows, int n_w_rows, int K, int epilogue, const void* extra, void* out,
+                        int out_chunk, int index, int slices, int rope_dh, void* stream);
+
 /* Weights of one block, device pointers, bf16. */
 typedef struct {
     const void* attn_norm;   /* [d]      RMSNorm gain in front of the attention part        */

@@ -33,11 +33,11 @@ D3TOM_MERGE_MEAN, D3TOM_MERGE_SUM = 0, 1
 D3TOM_OP_IMPORTANCE, D3TOM_OP_SELECT_TOPK, D3TOM_OP_MERGE, D3TOM_OP_ATTEND = range(4)
 D3TOM_MAX_VISUAL, D3TOM_MAX_DECIDERS = 16384, 256
 D3TOM_IMPORTANCE_STATIC_BYTES = 16 << 20
-D3TOM_LINEAR_PLAIN, D3TOM_LINEAR_RESIDUAL, D3TOM_LINEAR_SWIGLU = range(3)
+D3TOM_LINEAR_PLAIN, D3TOM_LINEAR_RESIDUAL, D3TOM_LINEAR_SWIGLU, D3TOM_LINEAR_PARTIAL, D3TOM_LINEAR_ROPE = range(5)
 
 EXPORTS = ["d3tom_keep_count", "d3tom_schedule", "d3tom_model_flops", "d3tom_workspace_bytes",
            "d3tom_status_string", "d3tom_importance", "d3tom_importance_static", "d3tom_select_topk", "d3tom_merge", "d3tom_merge_kv", "d3tom_merge_layer_workspace_bytes", "d3tom_merge_layer", "d3tom_attend", "d3tom_attend_weighted", "d3tom_update_deciders",
-           "d3tom_rmsnorm", "d3tom_rope", "d3tom_linear", "d3tom_linear_tile", "d3tom_stack_workspace_bytes", "d3tom_stack_step", "d3tom_stack_batch_workspace_bytes", "d3tom_stack_step_batch",
+           "d3tom_rmsnorm", "d3tom_rope", "d3tom_linear", "d3tom_linear_tile", "d3tom_linear_tile_name", "d3tom_linear_plan", "d3tom_linear_pinned", "d3tom_stack_workspace_bytes", "d3tom_stack_step", "d3tom_stack_batch_workspace_bytes", "d3tom_stack_step_batch",
            "d3tom_profile_enable", "d3tom_profile_kernel_count", "d3tom_profile_kernel_name", "d3tom_profile_collect"]
 
 _vp, _i, _f, _d, _sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_float, ctypes.c_double, ctypes.c_size_t
@@ -72,6 +72,13 @@ _lib.d3tom_stack_batch_workspace_bytes.argtypes = [_i] * 9
 _lib.d3tom_stack_step_batch.restype = _i
 _lib.d3tom_stack_step_batch.argtypes = [_vp, _i, _i32p, _i, _i, _i, _i, ctypes.POINTER(BlockWeights), _i, _vp, _i32p, _i32p, _i32p,
                                         _i32p, _i, _f, _f, _vp, _vp, _vp, _vp, _vp, ctypes.POINTER(_i), _vp, _sz, _vp]
+
+_lib.d3tom_linear_tile_name.restype = ctypes.c_char_p
+_lib.d3tom_linear_tile_name.argtypes = [_i]
+_lib.d3tom_linear_plan.restype = _i
+_lib.d3tom_linear_plan.argtypes = [_i, _i, _i, _sz, _i32p]
+_lib.d3tom_linear_pinned.restype = _i
+_lib.d3tom_linear_pinned.argtypes = [_vp, _vp, _i, _i, _i, _i, _vp, _vp, _i, _i, _i, _i, _vp]
 
 _lib.d3tom_profile_enable.restype = _i
 _lib.d3tom_profile_enable.argtypes = [_i]
@@ -359,6 +366,35 @@ def d3tom_linear_tile(a: torch.Tensor, w: torch.Tensor, epilogue: int, out: torc
     rows, n_w_rows, K = _linear_sizes(a, w, epilogue, out, residual)
     _check(_native.d3tom_linear_tile(a, w, rows, n_w_rows, K, epilogue, residual, out, out_chunk,
                                      tile, _stream(stream)), "d3tom_linear_tile")
+
+
+def d3tom_linear_tile_name(index: int) -> Optional[str]:
+    name = _lib.d3tom_linear_tile_name(int(index))
+    return None if name is None else name.decode()
+
+
+def d3tom_linear_plan(rows: int, n_w_rows: int, K: int, partial_floats: int = 0):
+    """(tile index, rows of w it takes, tile index for the others or -1, slices of the contraction); host only."""
+    plan = (ctypes.c_int32 * 4)()
+    _check(_lib.d3tom_linear_plan(rows, n_w_rows, K, partial_floats, plan), "d3tom_linear_plan")
+    return tuple(plan)
+
+
+def d3tom_linear_pinned(a: torch.Tensor, w: torch.Tensor, epilogue: int, out: torch.Tensor, index: int, extra: Optional[torch.Tensor] = None,
+                        out_chunk: int = 0, slices: int = 1, rope_dh: int = 0, stream=None) -> None:
+    (rows, K), (n_w_rows, K2) = a.shape, w.shape
+    assert K2 == K and a.dtype == w.dtype == torch.bfloat16
+    n_out = n_w_rows // 2 if epilogue == D3TOM_LINEAR_SWIGLU else n_w_rows
+    if epilogue == D3TOM_LINEAR_PARTIAL:
+        assert out.dtype == torch.float32 and out.numel() >= slices * rows * n_out
+    else:
+        assert out.dtype == torch.bfloat16 and out.numel() >= rows * n_out
+    if epilogue == D3TOM_LINEAR_ROPE:
+        assert extra is not None and extra.dtype == torch.float32 and extra.numel() >= rows * rope_dh
+    elif extra is not None:
+        assert extra.dtype == torch.bfloat16 and extra.numel() >= rows * n_out
+    _check(_lib.d3tom_linear_pinned(_ptr(a), _ptr(w), rows, n_w_rows, K, epilogue, _ptr(extra), _ptr(out), out_chunk, index, slices, rope_dh,
+                                    _stream(stream)), "d3tom_linear_pinned")
 
 
 def block_weights(blocks: Sequence[dict]):

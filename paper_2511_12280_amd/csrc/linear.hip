@@ -42,6 +42,7 @@
 //
 // Tiles are numbered band by band and cut into 8 equal runs, one per XCD (see linear_tile), so that the 32 workgroups that run
 // together on an XCD form a compact block and its private L2 sees few operand rows.
+#include <cstdio>
 #include <type_traits>
 #include "common.hpp"
 #include "direct_load.hpp"
@@ -418,17 +419,17 @@ int launch_linear_cfg(int cfg, const void* a, const void* w, int M, int N, int K
 // above all power), `round` the filling of the ring and the epilogue.  The smallest estimate wins; it misses the best tile of the table
 // by 1.5 % on average, at most 15 %.  (Eight tiles of 64, 128 and 256 rows and one constant each: 14 %.  Three blocks at 738 rows 1148 -> 986 us,
 // four at 1900 to 2100 rows 3929 -> 3685.)  `part`: what a million values of a partial matrix take when the contraction is cut.
-struct LinTile { int bm, bn; double stage, fill, round, launch, part; };
+struct LinTile { int bm, bn, wc; double stage, fill, round, launch, part; };
 static constexpr LinTile LIN_TILES[] = {
-    {64, 64, 0.225, 0.000, 0.7, 1.9, 1.08}, {64, 96, 0.275, 0.026, 0.2, 3.3, 0.78},
-    {64, 128, 0.337, 0.031, 0.0, 2.5, 1.75}, {64, 256, 0.602, 0.051, 0.2, 3.5, 1.57},
-    {96, 128, 0.393, 0.048, 0.0, 2.5, 1.55}, {128, 128, 0.465, 0.059, 2.4, 2.1, 0.73},
-    {128, 192, 0.584, 0.101, 0.5, 3.5, 1.43}, {128, 256, 0.723, 0.117, 2.7, 1.3, 1.40},
-    {160, 128, 0.479, 0.099, 1.0, 2.5, 1.55}, {160, 256, 0.773, 0.168, 4.7, 0.1, 1.34},
-    {192, 128, 0.494, 0.136, 2.5, 2.1, 1.35}, {192, 256, 0.838, 0.221, 5.6, 0.0, 1.44},
-    {224, 256, 0.901, 0.283, 6.5, 0.0, 1.40}, {256, 128, 0.649, 0.169, 4.9, 0.7, 0.67},
-    {256, 128, 0.573, 0.186, 3.4, 3.1, 1.40}, {256, 192, 0.838, 0.236, 7.0, 1.4, 0.48},
-    {256, 256, 0.951, 0.355, 7.8, 0.0, 1.35}};
+    {64, 64, 2, 0.225, 0.000, 0.7, 1.9, 1.08}, {64, 96, 2, 0.275, 0.026, 0.2, 3.3, 0.78},
+    {64, 128, 2, 0.337, 0.031, 0.0, 2.5, 1.75}, {64, 256, 4, 0.602, 0.051, 0.2, 3.5, 1.57},
+    {96, 128, 2, 0.393, 0.048, 0.0, 2.5, 1.55}, {128, 128, 4, 0.465, 0.059, 2.4, 2.1, 0.73},
+    {128, 192, 2, 0.584, 0.101, 0.5, 3.5, 1.43}, {128, 256, 4, 0.723, 0.117, 2.7, 1.3, 1.40},
+    {160, 128, 2, 0.479, 0.099, 1.0, 2.5, 1.55}, {160, 256, 4, 0.773, 0.168, 4.7, 0.1, 1.34},
+    {192, 128, 2, 0.494, 0.136, 2.5, 2.1, 1.35}, {192, 256, 4, 0.838, 0.221, 5.6, 0.0, 1.44},
+    {224, 256, 4, 0.901, 0.283, 6.5, 0.0, 1.40}, {256, 128, 4, 0.649, 0.169, 4.9, 0.7, 0.67},
+    {256, 128, 2, 0.573, 0.186, 3.4, 3.1, 1.40}, {256, 192, 4, 0.838, 0.236, 7.0, 1.4, 0.48},
+    {256, 256, 4, 0.951, 0.355, 7.8, 0.0, 1.35}};
 constexpr int LIN_NTILES = sizeof(LIN_TILES) / sizeof(LIN_TILES[0]);
 
 // `cols` counts rows of w (SWIGLU: gate and up)
@@ -503,6 +504,8 @@ int linear_partial_run(const void* a, const void* w, int M, int N, int K, int ks
     return launch_linear_cfg<LIN_PARTIAL>(cfg, a, w, M, N, K, nullptr, partial, N, ksplit, 0, N, st);
 }
 
+// tile: 0 the estimate's choice, (1 + c) * LIN_PIN entry c of LIN_TILES, otherwise height and width as in d3tom_linear_tile.
+constexpr int LIN_PIN = 256;
 // rope_cs != nullptr (PLAIN only, stacked q | k | v weight with out_chunk = d, head size rope_dh of 64 or 128): the
 // rotary embedding of the q and k sections is applied in the epilogue; rope_cs[row * rope_dh / 2 + c] = (cos, sin)
 int linear_run(const void* a, const void* w, int M, int N, int K, int epilogue, const void* residual, void* out,
@@ -535,6 +538,7 @@ int linear_run(const void* a, const void* w, int M, int N, int K, int epilogue, 
             default: return launch_linear_cfg<LIN_SWIGLU>(cfg, a, w, M, N, K, residual, out, out_chunk, 1, c0, c1, st);
         }
     };
+    if (tile >= LIN_PIN) return (tile / LIN_PIN > LIN_NTILES) ? D3TOM_ERR_INVALID_ARG : launch(tile / LIN_PIN - 1, 0, N);
     if (tile) {
         const int bm = (tile & 15) * 64, bn = (tile >> 4) * 64;
         for (int c = 0; c < LIN_NTILES; ++c)
@@ -562,4 +566,40 @@ extern "C" int d3tom_linear_tile(const void* a, const void* w, int rows, int n_w
     const int h = tile & 15, wd = tile >> 4;
     if (tile < 0 || (h != 1 && h != 2 && h != 4) || (wd != 0 && (wd < 2 || wd > 4))) return D3TOM_ERR_INVALID_ARG;
     return d3tom::linear_run(a, w, rows, n_w_rows, K, epilogue, residual, out, out_chunk, tile, (hipStream_t)stream, nullptr, 0);
+}
+
+// ---- for tuning and tests: the tiles by index, with every epilogue, and what the estimate chooses ----
+extern "C" const char* d3tom_linear_tile_name(int index) {
+    using namespace d3tom;
+    struct Names {
+        char text[LIN_NTILES][16];
+        Names() { for (int c = 0; c < LIN_NTILES; ++c) snprintf(text[c], sizeof text[c], "%dx%d%s", LIN_TILES[c].bm, LIN_TILES[c].bn, LIN_TILES[c].wc == 2 ? " loaders" : ""); }
+    };
+    static const Names names;
+    return index < 0 || index >= LIN_NTILES ? nullptr : names.text[index];
+}
+
+extern "C" int d3tom_linear_plan(int rows, int n_w_rows, int K, size_t partial_floats, int32_t* plan) {
+    using namespace d3tom;
+    if (!plan || rows < 1 || n_w_rows < 1 || K < LIN_BK || K % LIN_BK != 0) return D3TOM_ERR_INVALID_ARG;
+    const LinPlan p = linear_plan(rows, n_w_rows, K / LIN_BK);
+    int cfg = p.cfg_a;
+    plan[3] = partial_floats ? linear_split_plan(rows, n_w_rows, K, partial_floats, &cfg) : 1;
+    const bool two = plan[3] == 1 && p.cols_a < n_w_rows;
+    plan[0] = cfg;
+    plan[1] = two ? p.cols_a : n_w_rows;
+    plan[2] = two ? p.cfg_b : -1;
+    return D3TOM_OK;
+}
+
+extern "C" int d3tom_linear_pinned(const void* a, const void* w, int rows, int n_w_rows, int K, int epilogue, const void* extra, void* out,
+                                   int out_chunk, int index, int slices, int rope_dh, void* stream) {
+    using namespace d3tom;
+    hipStream_t st = (hipStream_t)stream;
+    if (index < 0 || index >= LIN_NTILES) return D3TOM_ERR_INVALID_ARG;
+    if (epilogue == LIN_PARTIAL) return linear_partial_run(a, w, rows, n_w_rows, K, slices, index, (float*)out, st);
+    const int tile = (1 + index) * LIN_PIN;
+    if (epilogue != LIN_ROPE) return linear_run(a, w, rows, n_w_rows, K, epilogue, extra, out, out_chunk, tile, st, nullptr, 0);
+    if (!extra) return D3TOM_ERR_INVALID_ARG;
+    return linear_run(a, w, rows, n_w_rows, K, LIN_PLAIN, nullptr, out, out_chunk, tile, st, (const float2*)extra, rope_dh);
 }

@@ -99,6 +99,26 @@ def test_rope(B, rows, H, dh, theta):
 
 
 # ---- projections -------------------------------------------------------------------------------
+def _linear_tiles():
+    if not torch.cuda.is_available():                  # collected without a GPU too, where the library may not be built yet
+        return []
+    from paper_2511_12280_amd import binding
+    names = []
+    while (name := binding.d3tom_linear_tile_name(len(names))) is not None:
+        names.append(name)
+    return names
+
+
+LIN_TILES = _linear_tiles()
+
+
+def _chosen(M, N, K):
+    from paper_2511_12280_amd import binding
+    first, cols, second, slices = binding.d3tom_linear_plan(M, N, K)
+    assert slices == 1 and (cols == N) == (second < 0)
+    return LIN_TILES[first] + (" + " + LIN_TILES[second] if second >= 0 else "")
+
+
 LIN_SHAPES = [(1, 8, 64), (5, 128, 64), (64, 128, 128), (200, 384, 256), (493, 512, 1024), (129, 200, 64), (300, 1000, 192),
               (1000, 256, 4096)]
 
@@ -170,16 +190,67 @@ def test_linear_every_tile(B, M, N, K, height, width):
     _one_step(_host(act), OS.round_bf16(OS.swiglu(OS.linear(a, w[:N]), up)), "swiglu")
 
 
+@pytest.mark.parametrize("stages,rows_over,cols_over", [(1, 1, -8), (3, -3, 40), (7, 0, 8), (12, 1, 72)])     # ring tails; remainders of a tile
+@pytest.mark.parametrize("epilogue", ["plain", "residual", "swiglu", "slices", "rope"])
+@pytest.mark.parametrize("index", range(len(LIN_TILES)))
+def test_linear_every_tile_with_every_epilogue(B, index, epilogue, stages, rows_over, cols_over):
+    """Operands of -1, 0 and 1: every product is a whole number below 256, so the sums are exact in float32 and in bf16."""
+    bm, bn = (int(x) for x in LIN_TILES[index].split()[0].split("x"))
+    M, N, K = 2 * bm + rows_over, 3 * bn + cols_over, 64 * stages
+    rng = np.random.default_rng([index, stages])
+    ints = lambda *sh: rng.integers(-1, 2, sh).astype(np.float32)
+    a, w = ints(M, K), ints(2 * N, K)
+    full = a.astype(np.float64) @ w.T.astype(np.float64)
+    prod = full[:, :N]
+    assert np.abs(full).max() <= 256
+    ta, tw = _dev(a), _dev(w[:N])
+    out = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    if epilogue == "plain":
+        B.d3tom_linear_pinned(ta, tw, B.D3TOM_LINEAR_PLAIN, out, index)
+        np.testing.assert_array_equal(_host(out), prod)
+        ch = torch.full((N // 8, M, 8), 7.0, dtype=torch.bfloat16, device="cuda")
+        B.d3tom_linear_pinned(ta, tw, B.D3TOM_LINEAR_PLAIN, ch, index, out_chunk=8)
+        np.testing.assert_array_equal(_host(ch).transpose(1, 0, 2).reshape(M, N), prod)
+    elif epilogue == "residual":
+        r = rng.integers(-100, 101, (M, N)).astype(np.float32)
+        B.d3tom_linear_pinned(ta, tw, B.D3TOM_LINEAR_RESIDUAL, out, index, extra=_dev(r))
+        np.testing.assert_array_equal(_host(out), OS.round_bf16(prod + r))
+    elif epilogue == "swiglu":
+        B.d3tom_linear_pinned(ta, _dev(w), B.D3TOM_LINEAR_SWIGLU, out, index)
+        _one_step(_host(out), OS.round_bf16(OS.swiglu(prod, full[:, N:])), "swiglu")
+    elif epilogue == "slices":
+        for slices in (1, 2, 4):
+            ak, wk = ints(M, K * slices), ints(N, K * slices)
+            part = torch.full((slices, M, N), 7.0, device="cuda")
+            B.d3tom_linear_pinned(_dev(ak), _dev(wk), B.D3TOM_LINEAR_PARTIAL, part, index, slices=slices)
+            for i in range(slices):
+                np.testing.assert_array_equal(part[i].cpu().numpy(), ak[:, i * K:(i + 1) * K] @ wk[:, i * K:(i + 1) * K].T)
+    else:
+        for dh, d in ((64, 192), (128, 384)):
+            wq = ints(3 * d, K)
+            ang = rng.uniform(-200, 200, (M, dh // 2))
+            cs = np.stack([np.cos(ang), np.sin(ang)], axis=2).astype(np.float32)
+            qkv = torch.full((3, M, d), 7.0, dtype=torch.bfloat16, device="cuda")
+            B.d3tom_linear_pinned(ta, _dev(wq), B.D3TOM_LINEAR_ROPE, qkv, index, extra=torch.from_numpy(cs).cuda(), out_chunk=d, rope_dh=dh)
+            ref = (a.astype(np.float64) @ wq.T).reshape(M, 3, d // dh, 2, dh // 2)
+            x0, x1, c, sn = ref[:, :2, :, 0], ref[:, :2, :, 1], cs[:, None, None, :, 0].astype(np.float64), cs[:, None, None, :, 1].astype(np.float64)
+            ref[:, :2, :, 0], ref[:, :2, :, 1] = x0 * c - x1 * sn, x1 * c + x0 * sn
+            ref = ref.transpose(1, 0, 2, 3, 4).reshape(3, M, d)
+            np.testing.assert_array_equal(_host(qkv)[2], ref[2])
+            _one_step(_host(qkv)[:2], OS.round_bf16(ref[:2]), "rope")
+
+
 # (rows, rows of w, contraction) for which the library takes the tile named, ragged in both directions; the last is cut into two launches
-LIN_CHOSEN = [("64x64", 100, 1008, 64), ("64x64", 100, 48, 64), ("64x128", 250, 4112, 64), ("96x128", 900, 3008, 64), ("160x128", 1500, 3008, 320),
+LIN_CHOSEN = [("64x64 loaders", 100, 1008, 64), ("64x64 loaders", 100, 48, 64), ("64x128 loaders", 250, 4112, 64), ("96x128 loaders", 900, 3008, 64), ("160x128 loaders", 1500, 3008, 320),
               ("128x256", 2050, 3008, 320), ("192x256", 2500, 4112, 320), ("224x256", 3000, 4112, 320), ("160x256", 3300, 3008, 320),
-              ("192x128", 1300, 4112, 640), ("128x192", 500, 12288, 320), ("64x96", 70, 12288, 4096), ("256x128", 1850, 4080, 4096),
-              ("256x256 + 64x64", 1400, 22016, 4096)]
+              ("192x128 loaders", 1300, 4112, 640), ("128x192 loaders", 500, 12288, 320), ("64x96 loaders", 70, 12288, 4096), ("256x128 loaders", 1850, 4080, 4096),
+              ("256x256 + 64x64 loaders", 1400, 22016, 4096)]
 
 
 @pytest.mark.parametrize("tile,M,N,K", LIN_CHOSEN)
 def test_linear_chosen_tiles(B, tile, M, N, K):
     """Every tile the estimate can choose, with both kinds of epilogue, against float32 products of the same bf16 values."""
+    assert _chosen(M, N, K) == tile
     g = torch.Generator(device="cuda"); g.manual_seed(M + N)
     rnd = lambda *sh: torch.randn(*sh, generator=g, device="cuda")
     a, w, r = rnd(M, K).bfloat16(), (2.0 * rnd(N, K) / np.sqrt(K)).bfloat16(), rnd(M, N).bfloat16()
