@@ -93,7 +93,8 @@ __global__ __launch_bounds__(512, 2) void linear_bf16_kernel(
     if (!linear_tile(blockIdx.x, per, RB, NRT, NCT, rt, ct)) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int half_wg = __builtin_amdgcn_readfirstlane(tid >> 8), wn = (tid >> 6) & 3;
+    // (the wave's number is kept in a scalar register where the tile needs every vector register: 256 x 128 with loading waves spilled one)
+    const int half_wg = __builtin_amdgcn_readfirstlane(tid >> 8), wn = (WC == 2 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6) & 3;
     const int r = lane & 15, g = lane >> 4;
     // a computing wave's part of the tile: rows grp * BM/2 .., columns wcol * BN/WC ..
     const int grp = WC == 4 ? half_wg : wn >> 1, wcol = WC == 4 ? wn : wn & 1;

@@ -115,3 +115,33 @@ def test_native_binding_refuses_what_it_cannot_pass_on(lib):
         _native.d3tom_rmsnorm(None, None, 4.0, 64, 1e-5, None, None)
     with pytest.raises(TypeError):
         _native.d3tom_rmsnorm(None, None, 4, 64, 1e-5, None, t)
+
+
+def _kernels(path):
+    """Metadata of the gfx950 kernels in the library: the notes of the ELF images inside it."""
+    import struct
+
+    import msgpack
+    data = open(path, "rb").read()
+    kernels, at = [], 0
+    while (at := data.find(b"\x7fELF", at + 1)) >= 0:
+        if struct.unpack_from("<H", data, at + 18)[0] != 224:              # EM_AMDGPU
+            continue
+        sh_off, = struct.unpack_from("<Q", data, at + 40)
+        sh_size, sh_num = struct.unpack_from("<HH", data, at + 58)
+        for i in range(sh_num):
+            kind, _, _, off, size = struct.unpack_from("<IQQQQ", data, at + sh_off + i * sh_size + 4)
+            if kind == 7:                                                  # SHT_NOTE: name size, description size, type
+                names, desc, _ = struct.unpack_from("<III", data, at + off)
+                first = at + off + 12 + (names + 3) // 4 * 4
+                kernels += msgpack.unpackb(data[first:first + desc])["amdhsa.kernels"]
+    return kernels
+
+
+def test_no_kernel_spills_vector_registers(lib):
+    pytest.importorskip("msgpack")
+    kernels = _kernels(LIB)
+    assert len(kernels) > 100
+    spilled = [(k[".name"], k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for k in kernels
+               if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]]
+    assert not spilled, spilled
