@@ -357,6 +357,58 @@ def run_cosine_cold_warm(reps: int = 6):
         print(f"{k:6d} {V - k:7d} {r['same_tensor']:12.1f} {r['cold']:8.1f} {r['read_before']:12.1f}")
 
 
+def run_projection_tiles(seed: int, count: int = 200):
+    """Microseconds of every built tile of the projections on `count` drawn shapes (a block's projections of 512 .. 5632 channels, 16 .. 4600
+    rows, weights cold in HBM), whole and, where the stack may, with the contraction in 2 or 4 slices: what the tile's choice is fitted to and
+    judged by.  HIP events around ten calls, the smaller of two; 'plan' is the library's choice."""
+    import random
+    from paper_2511_12280_amd import binding as B
+    rng = random.Random(seed)
+    names = []
+    while (name := B.d3tom_linear_tile_name(len(names))) is not None:
+        names.append(name)
+    room = 4 * 64 * 256 * 128
+    pool = torch.randn(900_000_000, device="cuda", dtype=torch.bfloat16).mul_(0.02)
+    print("# rows, rows of w, K, epilogue, slices, plan: " + "; ".join(f"{i} {n}" for i, n in enumerate(names)))
+    for _ in range(count):
+        d = 128 * rng.randint(4, 44)
+        F = 64 * rng.randint(d // 32, d // 21)
+        rows = int(round(16 * (4600 / 16) ** rng.random()))
+        n, K, epi = rng.choice([(3 * d, d, B.D3TOM_LINEAR_PLAIN), (d, d, B.D3TOM_LINEAR_RESIDUAL), (2 * F, d, B.D3TOM_LINEAR_SWIGLU),
+                                (d, F, B.D3TOM_LINEAR_RESIDUAL)])
+        copies = min(pool.numel() // (n * K), 1 + int(400e6 / (n * K)))       # 800 MB of weights, above every cache
+        ws = [pool[i * n * K:(i + 1) * n * K].view(n, K) for i in range(copies)]
+        a = torch.randn(rows, K, device="cuda").bfloat16()
+        res = torch.randn(rows, n, device="cuda").bfloat16() if epi == B.D3TOM_LINEAR_RESIDUAL else None
+        plan = B.d3tom_linear_plan(rows, n, K, room if res is not None else 0)
+        for slices in (1, 2, 4):
+            if slices > 1 and (res is None or K // 64 % slices or K // 64 // slices < 8 or rows * n * slices > room):
+                continue
+            part = slices > 1
+            out = torch.empty((slices, rows, n) if part else (rows, n // 2 if epi == B.D3TOM_LINEAR_SWIGLU else n), device="cuda",
+                              dtype=torch.float32 if part else torch.bfloat16)
+            times = []
+            for t in range(len(names)):
+                def call(i):
+                    B.d3tom_linear_pinned(a, ws[i % copies], B.D3TOM_LINEAR_PARTIAL if part else epi, out, t, extra=None if part else res, slices=slices)
+                best = float("inf")
+                try:
+                    for _ in range(2):
+                        for i in range(2):
+                            call(i)
+                        e0, e1 = torch.cuda.Event(True), torch.cuda.Event(True)
+                        e0.record()
+                        for i in range(10):
+                            call(i + 2)
+                        e1.record()
+                        torch.cuda.synchronize()
+                        best = min(best, e0.elapsed_time(e1) * 100.0)
+                    times.append(f"{best:.1f}")
+                except B.D3tomError:                                          # not built for this epilogue
+                    times.append("-")
+            print(rows, n, K, epi, slices, "/".join(str(x) for x in plan), *times, flush=True)
+
+
 def run_stack(traj_repeats: int = 1):
     """Whole denoising trajectory through the 32-block stack (the full-stack configuration): T steps, each
     = decider update on the device, embedding of the current response tokens (one row gather, plumbing),
@@ -523,6 +575,8 @@ def main():
                     help="run only the 32-block stack trajectory and print its record (for profiling that part alone)")
     ap.add_argument("--cosine-cold-warm", action="store_true",
                     help="time the cosine kernel alone with its rows cached / cold / read just before, print a table and exit")
+    ap.add_argument("--projection-tiles", type=int, metavar="SEED",
+                    help="time every tile of the projections on 200 drawn shapes, print a table and exit")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run one plain 256 MiB device copy, the known-size reference for HBM counters")
     args = ap.parse_args()
@@ -540,6 +594,9 @@ def main():
         del a, b
     if args.cosine_cold_warm:
         run_cosine_cold_warm()
+        return
+    if args.projection_tiles is not None:
+        run_projection_tiles(args.projection_tiles)
         return
     if args.stack_only:
         print(json.dumps(run_stack()))

@@ -66,6 +66,19 @@ template <int TM, int TN, int WC> struct LinCfg {
     static_assert(NA >= 2 && NW >= 2 && LDS <= 163840 && (WC == 4 || NS >= 3), "rings must fit");
 };
 
+// The tiles that there are.  uses: taken for whole projections, for slices of a contraction, or only where d3tom_linear_tile asks for it.  (Of
+// 20000 shapes, 1 .. 12000 rows, each tile is the estimate's choice for 20 or more in each of the uses that it is built for.)
+enum { LIN_WHOLE = 1, LIN_SLICES = 2, LIN_ASKED = 4 };
+struct LinTile { int bm, bn, wc, uses; };
+constexpr LinTile LIN_TILES[] = {
+    {64, 64, 2, LIN_WHOLE | LIN_SLICES}, {64, 96, 2, LIN_WHOLE | LIN_SLICES}, {64, 128, 2, LIN_WHOLE | LIN_SLICES}, {64, 256, 4, LIN_ASKED},
+    {96, 128, 2, LIN_WHOLE | LIN_SLICES}, {128, 128, 4, LIN_WHOLE | LIN_SLICES}, {128, 192, 2, LIN_WHOLE}, {128, 256, 4, LIN_WHOLE},
+    {160, 128, 2, LIN_WHOLE | LIN_SLICES}, {160, 256, 4, LIN_WHOLE}, {192, 128, 2, LIN_WHOLE | LIN_SLICES}, {192, 256, 4, LIN_WHOLE},
+    {224, 256, 4, LIN_WHOLE}, {256, 128, 4, LIN_SLICES | LIN_ASKED}, {256, 128, 2, LIN_WHOLE}, {256, 192, 4, LIN_WHOLE}, {256, 256, 4, LIN_WHOLE}};
+constexpr int LIN_NTILES = sizeof(LIN_TILES) / sizeof(LIN_TILES[0]);
+// the uses for which a tile is built with an epilogue
+constexpr int linear_uses(int epi) { return epi == LIN_PARTIAL ? LIN_SLICES : epi == LIN_ROPE ? LIN_WHOLE : LIN_WHOLE | LIN_ASKED; }
+
 // Tile (rt, ct) of workgroup id.  Ids are dealt round-robin to the 8 XCDs; the tiles are numbered in bands of RB row tiles,
 // column-major inside a band, and that sequence is cut into 8 runs of `per` tiles, one per XCD.
 __device__ __forceinline__ bool linear_tile(int id, int per, int RB, int NRT, int NCT, int& rt, int& ct) {
@@ -384,67 +397,53 @@ int launch_linear(const void* a, const void* w, int M, int N, int K, const void*
     return D3TOM_OK;
 }
 
-template <int EPI>
+// the kernel of entry `cfg` of LIN_TILES
+template <int EPI, int C = 0>
 int launch_linear_cfg(int cfg, const void* a, const void* w, int M, int N, int K, const void* residual, void* out, int out_chunk,
                       int ksplit, int col0, int col_end, hipStream_t st, const float2* rope_cs = nullptr, int rope_dh = 0) {
-#define D3TOM_LIN(TM, TN, WC) return launch_linear<TM, TN, WC, EPI>(a, w, M, N, K, residual, out, out_chunk, ksplit, col0, col_end, st, rope_cs, rope_dh)
-    switch (cfg) {              // in the order of LIN_TILES
-        case 0: D3TOM_LIN(2, 2, 2);
-        case 1: D3TOM_LIN(2, 3, 2);
-        case 2: D3TOM_LIN(2, 4, 2);
-        case 3: D3TOM_LIN(2, 4, 4);
-        case 4: D3TOM_LIN(3, 4, 2);
-        case 5: D3TOM_LIN(4, 2, 4);
-        case 6: D3TOM_LIN(4, 6, 2);
-        case 7: D3TOM_LIN(4, 4, 4);
-        case 8: D3TOM_LIN(5, 4, 2);
-        case 9: D3TOM_LIN(5, 4, 4);
-        case 10: D3TOM_LIN(6, 4, 2);
-        case 11: D3TOM_LIN(6, 4, 4);
-        case 12: D3TOM_LIN(7, 4, 4);
-        case 13: D3TOM_LIN(8, 2, 4);
-        case 14: D3TOM_LIN(8, 4, 2);
-        case 15: D3TOM_LIN(8, 3, 4);
-        default: D3TOM_LIN(8, 4, 4);
+    if constexpr (C < LIN_NTILES) {
+        if (cfg != C) return launch_linear_cfg<EPI, C + 1>(cfg, a, w, M, N, K, residual, out, out_chunk, ksplit, col0, col_end, st, rope_cs, rope_dh);
+        constexpr LinTile t = LIN_TILES[C];
+        if constexpr ((t.uses & linear_uses(EPI)) != 0)
+            return launch_linear<t.bm / 32, t.bn / (16 * t.wc), t.wc, EPI>(a, w, M, N, K, residual, out, out_chunk, ksplit, col0, col_end, st, rope_cs, rope_dh);
     }
-#undef D3TOM_LIN
+    return D3TOM_ERR_UNSUPPORTED;
 }
 }  // namespace
 
 // ---- choice of the tile -----------------------------------------------------------------------------
-// A grid runs in rounds of 256 workgroups, one per compute unit, and a mostly empty last round costs as much time as a full one:
-// hence tiles of many heights.  What a launch takes (microseconds), fitted to 112 shapes (96 .. 4600 rows; widths and contractions of
-// projections of 2048 and 4096 channels, weights cold in HBM):
-//   rounds * (stages * stage + round) + tiles / 256 * stages * fill + launch
-// `stage` is what a k-stage takes however few tiles there are, `fill` what it takes longer when the chip is full of them (operands, and
-// above all power), `round` the filling of the ring and the epilogue.  The smallest estimate wins; it misses the best tile of the table
-// by 1.5 % on average, at most 15 %.  (Eight tiles of 64, 128 and 256 rows and one constant each: 14 %.  Three blocks at 738 rows 1148 -> 986 us,
-// four at 1900 to 2100 rows 3929 -> 3685.)  `part`: what a million values of a partial matrix take when the contraction is cut.
-struct LinTile { int bm, bn, wc; double stage, fill, round, launch, part; };
-static constexpr LinTile LIN_TILES[] = {
-    {64, 64, 2, 0.225, 0.000, 0.7, 1.9, 1.08}, {64, 96, 2, 0.275, 0.026, 0.2, 3.3, 0.78},
-    {64, 128, 2, 0.337, 0.031, 0.0, 2.5, 1.75}, {64, 256, 4, 0.602, 0.051, 0.2, 3.5, 1.57},
-    {96, 128, 2, 0.393, 0.048, 0.0, 2.5, 1.55}, {128, 128, 4, 0.465, 0.059, 2.4, 2.1, 0.73},
-    {128, 192, 2, 0.584, 0.101, 0.5, 3.5, 1.43}, {128, 256, 4, 0.723, 0.117, 2.7, 1.3, 1.40},
-    {160, 128, 2, 0.479, 0.099, 1.0, 2.5, 1.55}, {160, 256, 4, 0.773, 0.168, 4.7, 0.1, 1.34},
-    {192, 128, 2, 0.494, 0.136, 2.5, 2.1, 1.35}, {192, 256, 4, 0.838, 0.221, 5.6, 0.0, 1.44},
-    {224, 256, 4, 0.901, 0.283, 6.5, 0.0, 1.40}, {256, 128, 4, 0.649, 0.169, 4.9, 0.7, 0.67},
-    {256, 128, 2, 0.573, 0.186, 3.4, 3.1, 1.40}, {256, 192, 4, 0.838, 0.236, 7.0, 1.4, 0.48},
-    {256, 256, 4, 0.951, 0.355, 7.8, 0.0, 1.35}};
-constexpr int LIN_NTILES = sizeof(LIN_TILES) / sizeof(LIN_TILES[0]);
-
-// `cols` counts rows of w (SWIGLU: gate and up)
+// A grid runs in rounds of 256 workgroups, one per compute unit, and a mostly empty last round costs as much time as a full one: hence
+// tiles of many heights.  What a launch takes, in microseconds:
+//   rounds * (stages * (rows a tile takes in of either operand) + epilogue and ring) + tiles / 256 * stages * products + launch
+// The rows count however few tiles there are; the products count by how full the chip is (above all power).  The two forms have constants of
+// their own, tiles of the same form share them; a wave whose fragments are three columns wide stores 8 bytes at a time instead of 16.
+// Cut contractions besides: what a million values of a partial matrix take to write (fragments of up to three columns fill the lines they
+// store, wider ones leave gaps between the lanes) and to read again.
+// Fitted to the times within 1.3 of a shape's best of 491 shapes, 159 of them with cut contractions too (16 .. 4600 rows; q | k | v, output,
+// gate | up and down projections of 512 .. 5632 channels; weights cold in HBM): there the choice is 0.5 % behind the best built tile on
+// average.  On 376 shapes that the fit has not seen it is 0.7 % behind, 3.2 % at the 90th percentile, 9.7 % at the 99th, 19.6 % at most.  (A
+// table of five constants for each of the 17 tiles: 0.8 %, 2.8, 17.5 and 24.7 %.)  profiles/projection_tiles.txt has the times.
 static double linear_estimate(int cfg, int M, int cols, int nst, int ksplit) {
+    struct Form { double a_rows, w_rows, products, round; };
+    constexpr Form PING_PONG = {0.49, 0.42, 0.37, 8.75}, LOADERS = {0.37, 0.56, 0.31, 3.24};       // of 256 rows, 256 x 256 tiles
+    constexpr double LAUNCH = 2.14, NARROW_STORES = 2.7, PART_FILLED = 0.73, PART_GAPS = 1.4, PART_READ = 0.45;
     const LinTile& t = LIN_TILES[cfg];
+    const Form& f = t.wc == 4 ? PING_PONG : LOADERS;
+    const int tn = t.bn / (16 * t.wc);
     const long tiles = (long)ceil_div(M, t.bm) * ceil_div(cols, t.bn) * ksplit;
-    return (double)((tiles + 255) / 256) * (nst * t.stage + t.round) + (double)tiles / 256.0 * nst * t.fill + t.launch;
+    const double area = (double)(t.bm * t.bn) / 65536.0, stages = nst / ksplit;
+    double us = (double)((tiles + 255) / 256) * (stages * (f.a_rows * t.bm + f.w_rows * t.bn) / 256.0 + (f.round + (tn == 3 ? NARROW_STORES : 0.0)) * area);
+    us += (double)tiles / 256.0 * stages * f.products * area + LAUNCH;
+    if (ksplit > 1) us += (double)M * cols * ksplit * 1e-6 * ((tn <= 3 ? PART_FILLED : PART_GAPS) + PART_READ);
+    return us;
 }
-static int linear_pick(int M, int cols, int nst, int ksplit, int bm, double* est) {
+// the best tile for a projection in one launch (`cols` counts rows of w; SWIGLU: gate and up); bm: of that height
+static int linear_pick(int M, int cols, int nst, int bm, double* est) {
     int best = -1;
     double best_t = 0.0;
     for (int c = 0; c < LIN_NTILES; ++c) {
-        if (bm && LIN_TILES[c].bm != bm) continue;
-        const double t = linear_estimate(c, M, cols, nst, ksplit);
+        if (!(LIN_TILES[c].uses & LIN_WHOLE) || (bm && LIN_TILES[c].bm != bm)) continue;
+        const double t = linear_estimate(c, M, cols, nst, 1);
         if (best < 0 || t < best_t) { best = c; best_t = t; }
     }
     *est = best_t;
@@ -458,17 +457,18 @@ constexpr double LIN_SECOND_US = 4.0;       // the first launch drains and the s
 struct LinPlan { int cfg_a, cols_a, cfg_b; double est; };
 static LinPlan linear_plan(int M, int cols, int nst) {
     LinPlan p;
-    p.cfg_a = linear_pick(M, cols, nst, 1, 0, &p.est);
+    p.cfg_a = linear_pick(M, cols, nst, 0, &p.est);
     p.cols_a = cols;
     p.cfg_b = 0;
     const double single = p.est;
     for (int c = 0; c < LIN_NTILES; ++c) {
+        if (!(LIN_TILES[c].uses & LIN_WHOLE)) continue;
         const int nrt = ceil_div(M, LIN_TILES[c].bm), nct = ceil_div(cols, LIN_TILES[c].bn);
         const int rounds = (int)((long)nrt * nct / 256);
         const int lead = rounds > 0 ? rounds * 256 / nrt : 0;
         if (lead < 1 || lead >= nct) continue;
         double rest;
-        const int cb = linear_pick(M, cols - lead * LIN_TILES[c].bn, nst, 1, 0, &rest);
+        const int cb = linear_pick(M, cols - lead * LIN_TILES[c].bn, nst, 0, &rest);
         const double t = linear_estimate(c, M, lead * LIN_TILES[c].bn, nst, 1) + rest + LIN_SECOND_US;
         if (t < p.est && t < 0.95 * single) { p.cfg_a = c; p.cols_a = lead * LIN_TILES[c].bn; p.cfg_b = cb; p.est = t; }
     }
@@ -476,8 +476,8 @@ static LinPlan linear_plan(int M, int cols, int nst) {
 }
 
 // Contraction slices for a projection whose result goes through the row-wise add-and-normalise kernel anyway: cutting the
-// contraction fills the chip where the tiles of a short sequence do not, at the price of writing and reading `ksplit` float32
-// matrices and of the row kernel reading them (0.45 us per million values more than without).  Returns 1 (no split), 2 or 4; *cfg is the tile.
+// contraction fills the chip where the tiles of a short sequence do not, at the price of writing `ksplit` float32 matrices and of the row
+// kernel reading them (0.45 us per million values more than without).  Returns 1 (no split), 2 or 4; *cfg is the tile.
 // max_floats bounds the partial matrices together.
 int linear_split_plan(int M, int N, int K, size_t max_floats, int* cfg) {
     const int nst = K / LIN_BK;
@@ -489,7 +489,8 @@ int linear_split_plan(int M, int N, int K, size_t max_floats, int* cfg) {
     for (int ks = 2; ks <= 4; ks <<= 1) {
         if (nst % ks || nst / ks < 8 || (size_t)M * N * ks > max_floats) continue;
         for (int c = 0; c < LIN_NTILES; ++c) {
-            const double t = linear_estimate(c, M, N, nst / ks, ks) + (double)M * N * ks * 1e-6 * (LIN_TILES[c].part + 0.45);
+            if (!(LIN_TILES[c].uses & LIN_SLICES)) continue;
+            const double t = linear_estimate(c, M, N, nst, ks);
             if (t < best_t) { best = ks; best_t = t; *cfg = c; }
         }
     }
@@ -546,7 +547,7 @@ int linear_run(const void* a, const void* w, int M, int N, int K, int epilogue, 
             if (LIN_TILES[c].bm == bm && LIN_TILES[c].bn == bn) return launch(c, 0, N);
         if (bn) return D3TOM_ERR_INVALID_ARG;
         double est;
-        return launch(linear_pick(M, N, K / LIN_BK, 1, bm, &est), 0, N);
+        return launch(linear_pick(M, N, K / LIN_BK, bm, &est), 0, N);
     }
     const LinPlan p = linear_plan(M, N, K / LIN_BK);
     const int status = launch(p.cfg_a, 0, p.cols_a);

@@ -190,6 +190,11 @@ def test_linear_every_tile(B, M, N, K, height, width):
     _one_step(_host(act), OS.round_bf16(OS.swiglu(OS.linear(a, w[:N]), up)), "swiglu")
 
 
+# what the estimate never takes with the stack's epilogues
+NOT_BUILT = [("slices", t) for t in ("64x256", "128x192 loaders", "128x256", "160x256", "192x256", "224x256", "256x128 loaders", "256x192", "256x256")]
+NOT_BUILT += [("rope", "64x256"), ("rope", "256x128")]
+
+
 @pytest.mark.parametrize("stages,rows_over,cols_over", [(1, 1, -8), (3, -3, 40), (7, 0, 8), (12, 1, 72)])     # ring tails; remainders of a tile
 @pytest.mark.parametrize("epilogue", ["plain", "residual", "swiglu", "slices", "rope"])
 @pytest.mark.parametrize("index", range(len(LIN_TILES)))
@@ -205,6 +210,14 @@ def test_linear_every_tile_with_every_epilogue(B, index, epilogue, stages, rows_
     assert np.abs(full).max() <= 256
     ta, tw = _dev(a), _dev(w[:N])
     out = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    if (epilogue, LIN_TILES[index]) in NOT_BUILT:
+        with pytest.raises(B.D3tomError) as e:
+            if epilogue == "slices":
+                B.d3tom_linear_pinned(ta, tw, B.D3TOM_LINEAR_PARTIAL, torch.empty(M, N, device="cuda"), index)
+            else:
+                B.d3tom_linear_pinned(ta, _dev(w[:192]), B.D3TOM_LINEAR_ROPE, out, index, extra=torch.empty(M, 64, device="cuda"), out_chunk=64, rope_dh=64)
+        assert e.value.status == B.D3TOM_ERR_UNSUPPORTED
+        return
     if epilogue == "plain":
         B.d3tom_linear_pinned(ta, tw, B.D3TOM_LINEAR_PLAIN, out, index)
         np.testing.assert_array_equal(_host(out), prod)
@@ -241,10 +254,12 @@ def test_linear_every_tile_with_every_epilogue(B, index, epilogue, stages, rows_
 
 
 # (rows, rows of w, contraction) for which the library takes the tile named, ragged in both directions; the last is cut into two launches
-LIN_CHOSEN = [("64x64 loaders", 100, 1008, 64), ("64x64 loaders", 100, 48, 64), ("64x128 loaders", 250, 4112, 64), ("96x128 loaders", 900, 3008, 64), ("160x128 loaders", 1500, 3008, 320),
-              ("128x256", 2050, 3008, 320), ("192x256", 2500, 4112, 320), ("224x256", 3000, 4112, 320), ("160x256", 3300, 3008, 320),
-              ("192x128 loaders", 1300, 4112, 640), ("128x192 loaders", 500, 12288, 320), ("64x96 loaders", 70, 12288, 4096), ("256x128 loaders", 1850, 4080, 4096),
-              ("256x256 + 64x64 loaders", 1400, 22016, 4096)]
+LIN_CHOSEN = [("64x64 loaders", 100, 1008, 64), ("64x64 loaders", 100, 48, 64), ("64x96 loaders", 70, 12288, 4096), ("64x128 loaders", 250, 4112, 64),
+              ("96x128 loaders", 900, 3008, 64), ("128x128", 700, 4112, 2048), ("128x192 loaders", 500, 12288, 320), ("128x256", 300, 16400, 640),
+              ("160x128 loaders", 1500, 3008, 320), ("160x128 loaders", 3300, 3008, 320), ("160x256", 300, 22016, 1024),
+              ("192x128 loaders", 1300, 4112, 640), ("192x128 loaders", 2500, 4112, 320), ("192x256", 493, 16400, 1024), ("224x256", 3000, 4112, 1024),
+              ("256x128 loaders", 1850, 4080, 4096), ("256x128 loaders", 2050, 3008, 320), ("256x128 loaders", 3000, 4112, 320),
+              ("256x192", 493, 22016, 2048), ("256x256", 700, 16400, 2048), ("256x256 + 64x64 loaders", 1400, 22016, 4096)]
 
 
 @pytest.mark.parametrize("tile,M,N,K", LIN_CHOSEN)
@@ -267,27 +282,28 @@ def test_linear_chosen_tiles(B, tile, M, N, K):
 
 
 def test_linear_two_launch_plan(B):
-    """Shapes whose 256-row tiles fill one round of the chip and a bit: the library cuts the columns into a
+    """Shapes whose tall tiles fill one round of the chip and a bit: the library cuts the columns into a
     full round of tall tiles and a remainder with smaller tiles (two launches, one result)."""
     rng = np.random.default_rng(21)
-    M, K, n = 300, 64, 22016
+    M, K, n = 540, 2048, 22016
+    assert _chosen(M, n, K) == "192x256 + 64x64 loaders"
     a = W.round_to(rng.standard_normal((M, K)).astype(np.float32), "bf16")
     w = W.round_to((rng.standard_normal((n, K)) / np.sqrt(K)).astype(np.float32), "bf16")
     r = W.round_to(rng.standard_normal((M, n)).astype(np.float32), "bf16")
+    prod = OS.linear(a, w)
     ta, tw, tr = _dev(a), _dev(w), _dev(r)
     out = torch.full((M, n), 7.0, dtype=torch.bfloat16, device="cuda")
     B.d3tom_linear(ta, tw, B.D3TOM_LINEAR_RESIDUAL, out, residual=tr)
     torch.cuda.synchronize()
-    _one_step(_host(out), OS.round_bf16(r.astype(np.float64) + OS.linear(a, w)), "two-launch residual")
+    _one_step(_host(out), OS.round_bf16(r.astype(np.float64) + prod), "two-launch residual")
     act = torch.full((M, n // 2), 7.0, dtype=torch.bfloat16, device="cuda")
     B.d3tom_linear(ta, tw, B.D3TOM_LINEAR_SWIGLU, act)
     torch.cuda.synchronize()
-    _one_step(_host(act), OS.round_bf16(OS.swiglu(OS.linear(a, w[:n // 2]), OS.linear(a, w[n // 2:]))), "two-launch swiglu")
+    _one_step(_host(act), OS.round_bf16(OS.swiglu(prod[:, :n // 2], prod[:, n // 2:])), "two-launch swiglu")
     ch = torch.full((n // 128, M, 128), 7.0, dtype=torch.bfloat16, device="cuda")
     B.d3tom_linear(ta, tw, B.D3TOM_LINEAR_PLAIN, ch, out_chunk=128)
     torch.cuda.synchronize()
-    ref = OS.round_bf16(OS.linear(a, w))
-    _one_step(_host(ch).transpose(1, 0, 2).reshape(M, n), ref, "two-launch chunked")
+    _one_step(_host(ch).transpose(1, 0, 2).reshape(M, n), OS.round_bf16(prod), "two-launch chunked")
 
 
 def test_linear_rejects(B):

@@ -145,3 +145,20 @@ def test_no_kernel_spills_vector_registers(lib):
     spilled = [(k[".name"], k[".vgpr_spill_count"], k[".private_segment_fixed_size"]) for k in kernels
                if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]]
     assert not spilled, spilled
+
+
+def test_projection_tiles_are_all_taken(lib):
+    """Every tile that is built for a use is the estimate's choice there for some sizes, and no other tile is."""
+    import random
+    from paper_2511_12280_amd import binding as B
+    rng, whole, sliced = random.Random(1), set(), set()
+    log_int = lambda lo, hi: int(lo * (hi / lo) ** rng.random())
+    for _ in range(20000):
+        rows, cols, K = log_int(1, 12000), 8 * log_int(8, 3500), 64 * log_int(1, 220)
+        room = 4 * 64 * 256 * 128 if cols <= 8192 else 0
+        first, lead, second, slices = B.d3tom_linear_plan(rows, cols, K, room)
+        assert 0 < lead <= cols and (lead < cols) == (second >= 0) and (slices == 1 or (K % (64 * slices) == 0 and rows * cols * slices <= room))
+        (sliced if slices > 1 else whole).add(B.d3tom_linear_tile_name(first))
+    assert sliced == {"64x64 loaders", "64x96 loaders", "64x128 loaders", "96x128 loaders", "128x128", "160x128 loaders", "192x128 loaders", "256x128"}
+    assert whole == {"64x64 loaders", "64x96 loaders", "64x128 loaders", "96x128 loaders", "128x128", "128x192 loaders", "128x256",
+                     "160x128 loaders", "160x256", "192x128 loaders", "192x256", "224x256", "256x128 loaders", "256x192", "256x256"}
