@@ -33,11 +33,13 @@ constexpr int IMP_KC_STATS = 512, IMP_KC_SCORES = 256;
 constexpr long IMP_MANY = 1024;        // 512-key chunks from which on a launch counts as several rounds
 constexpr int IMP_STREAM_KEYS = 4096, IMP_STREAM_HEADS = 1024;     // a chunk's rows are addressed with 32-bit byte offsets
 // Streaming launches: from how many deciders on, workgroups they should have, keys of a workgroup at least (the decider rows and the
-// first stages are paid once in each).  Both sweeps, 384 keys at once / streaming: 16 samples of 1200 .. 2300 tokens, at most 38 deciders 97 /
-// 104 us, 77 105 / 113, 127 111 / 116, 254 167 / 149; 10 samples, 74 58 / 63, 225 97 / 86: with few of them the sweeps are bound by the keys,
-// of which the other form has more in flight.  16 samples of 2688 tokens, 169 deciders on average: 512 workgroups 188 us, 1024 182, 1536
-// 186, 3072 226; ragged ones, 1024 157, 1536 149.
-constexpr int IMP_STREAM_D = 128, IMP_STREAM_WGS = 1536, IMP_STREAM_MIN = 448;
+// first stages are paid once in each).  Both sweeps, against keys at once, 2924 drawn batches of 2 to 32 samples of 500 to 4000 tokens, 8 to 32
+// heads of 64 and 128, by the largest decider count: 129 .. 143 0.99 x, 144 .. 159 1.01, 160 .. 175 1.04, to 223 1.06, to 239 1.08, 240 .. 256
+// 1.11 (single batches 0.85 to 1.36); with few of them the sweeps are bound by the keys, of which the other form has more in flight (16 samples of
+// 1200 .. 2300 tokens, at most 38 deciders 97 us at once and 104 streaming, 77 105 and 113, 127 111 and 116, 254 167 and 149).  On the same batches
+// 1024 or 2048 workgroups instead of 1536, or 640 keys instead of 448, change the mean by at most 0.6 % (single batches by 21 % either way),
+// 896 keys lose up to 3 %.
+constexpr int IMP_STREAM_D = 144, IMP_STREAM_WGS = 1536, IMP_STREAM_MIN = 448;
 
 constexpr int IMP_KEEP_MAXD_WS = 32;   // largest decider set whose logits are kept (workspace is sized for it)
 struct ImpWs {

@@ -154,7 +154,7 @@ def test_importance_streaming_stages(dh):
 @pytest.mark.parametrize("dtype,H,dh,D,N,copies", [
     ("bf16", 2, 128, 9, 1100, 1), ("bf16", 2, 64, 40, 1100, 1),           # chunks of 256 keys, logits kept or not
     ("bf16", 16, 64, 9, 1100, 2), ("bf16", 16, 128, 40, 1100, 2),         # chunks of 512 keys, logits kept or not
-    ("bf16", 16, 128, 144, 1200, 16), ("bf16", 16, 64, 130, 1200, 16),    # keys streamed, chunks of 640
+    ("bf16", 16, 128, 160, 1200, 16), ("bf16", 16, 64, 145, 1200, 16),    # keys streamed, chunks of 640
     ("f32", 2, 64, 9, 300, 1), ("f32", 2, 64, 40, 300, 1)])               # generic kernels
 def test_importance_chunk_of_infinite_logits(dtype, H, dh, D, N, copies):
     """Keys whose logits are all -inf (an infinite key channel) have probability 0, also where they are all the keys of a chunk of the
