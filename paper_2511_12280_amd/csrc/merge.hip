@@ -935,10 +935,11 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
         // 128-row tiles (a 64-row tile's k-loop is ~0.7 of a 128-row tile's); several rounds of 128-row tiles are 256-row tiles, which
         // move a third less operand data per flop and whose rests the kernel cuts (against 128-row tiles, merges at d = 4096: 4500 rows keeping
         // 0.2 .. 0.5 70 -> 59 us, 5 samples of 2304 90 -> 76, 9 of 1152 .. 2304 114 -> 83).  From 16 samples on, where the bounds that the
-        // host has are far above what the samples need, they are also better than one round by those bounds: 24 samples of 300 .. 400 rows
-        // at d = 2048 45 -> 39, 100 of 100 .. 144 at 1024 44 -> 42; two to ten samples lose up to 17 %.
+        // host has are far above what the samples need, they are also better above half a round: 450 drawn batches of 16 to 100 samples of 90 to
+        // 900 rows at d = 1024 .. 4096, merges and whole merge layers, 1.04 x at 1024, 1.05 at 2048, 1.09 at 4096, 0.93 at the least; below half a
+        // round (435 batches) 0.99, at the least 0.84.  Above half a round 14 and 15 samples gain 1.01, 5 to 7 0.99, and some lose 10 %.
         const long t64 = (long)nct * ceil_div(max_pruned, 64) * B, t128 = (long)nct * ceil_div(max_pruned, 128) * B;
-        TM = (t128 > 256 || (B >= 16 && t64 > COS_SPLIT_BLOCKS / 2)) ? 4 : t64 > 256 ? 2 : 1;
+        TM = t128 > (B >= 16 ? 128 : 256) ? 4 : t64 > 256 ? 2 : 1;
         // too few 64 x 128 tiles for 256 CUs (short sequences): cut the contraction into k-slices as well
         if (TM == 1) {
             const int stages = d_sim / COS_BK;

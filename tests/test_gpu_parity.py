@@ -101,6 +101,19 @@ def test_merge_large_batch_tiles(batch):
     _chain(samples, keeps, "bf16", check=[0, 1, 2, 5, batch - 1])
 
 
+@pytest.mark.parametrize("batch,V", [(16, 1088), (16, 1089), (15, 1089), (33, 576), (33, 448)])
+def test_merge_batches_around_half_a_round(batch, V):
+    """Batches of 16 and more samples take 256-row tiles above 128 tiles of 128 rows (bounds of 128, 144, 135, 132 and 99 of them)."""
+    rng = np.random.default_rng([batch, V])
+    sizes = [V] + [int(v) for v in rng.integers(70, V, batch - 1)]
+    samples = [W.random_case(740 + i, v + 5, 64, 1, 5, v, 1, dtype="bf16", centres=max(2, v // 6)) for i, v in enumerate(sizes)]
+    kept = [np.sort(rng.choice(v, size=64, replace=False)).astype(np.int32) for v in sizes]
+    out = GpuStep(samples, [64] * batch, "bf16").merge(kept)
+    for b, s in enumerate(samples):
+        check_assign(out["assign"][b], s["x"], s["vis_start"], s["V"], kept[b])
+        check_merge({key: out[key][b] for key in out}, s["x"], s["vis_start"], s["V"], kept[b], "bf16")
+
+
 @pytest.mark.parametrize("big,small", [(1, 15), (2, 14), (4, 12), (7, 9), (1, 69), (3, 66), (0, 130), (0, 31)])
 def test_merge_batch_tiles_in_equal_runs(big, small):
     """The tiles of a whole batch cut into one run per XCD, whose rest of the last round is cut into quarter, half or no parts of a
