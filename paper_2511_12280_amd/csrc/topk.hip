@@ -24,9 +24,11 @@
 namespace d3tom {
 
 constexpr int TOPK_THREADS = 1024;
-constexpr int TOPK_STREAM_WGS = 128;       // streaming workgroups per launch.  Whole steps of 3645 cold rows of 8 KB, 2 and 64 deciders: 64
-                                           // of them 68.9 and 140.0 us, 96 67.3 and 137.9, 112 66.0 and 137.7, 128 65.5 and 135.7, 144 the same,
-                                           // 192 66.2 and 136.5; with the rows cached all within 0.5 %
+// Streaming workgroups per launch, shared out among the samples.  Merge layers of 1 to 8 samples of 144 .. 3645 rows of 512 bytes .. 8 KB, rows cold
+// and cached: of one or two samples 64 lose up to 9 %, 96 up to 4 %, 160 to 256 lose or gain up to 3 %; below 400 rows a sample, 64 to 256 are the
+// same.  Of 8 samples of 729 rows or more, 64 lose 3 to 15 %, 192 gain 1 to 6 %.  (Whole steps of 3645 cold rows of 8 KB, 2 and 64 deciders: 64
+// of them 68.9 and 140.0 us, 96 67.3 and 137.9, 112 66.0 and 137.7, 128 65.5 and 135.7, 144 the same, 192 66.2 and 136.5.)
+constexpr int TOPK_STREAM_WGS = 128;
 
 // Kept count at a keep ratio (Section 3.2: rank at most (1 - alpha)|V|; a fractional product is rounded up):
 // ceil(ratio * V - 1e-9) clamped to [1, V], in double with separately rounded product and difference, i.e.
