@@ -131,16 +131,16 @@ def test_merge_batch_tiles_in_equal_runs(big, small):
         check_merge({key: out[key][b] for key in out}, s["x"], s["vis_start"], s["V"], kept[b], "bf16")
 
 
-@pytest.mark.parametrize("dh,copies", [(64, 8), (128, 8), (64, 1), (128, 1)])
+@pytest.mark.parametrize("dh,copies", [(64, 128), (128, 128), (64, 4), (128, 4), (64, 1), (128, 1)])
 def test_importance_decider_groups_and_chunks(dh, copies):
     """Decider counts around the 128 rows staged at a time and around 16-row blocks, key counts around the key chunks of both
-    sweeps; `copies` of the batch make enough workgroups for the smaller chunks of large launches."""
+    sweeps: one copy of the batch has chunks of 256 keys, 4 have chunks of 512, 128 stream the keys."""
     shapes = [(383, 127, 33), (384, 256, 128), (385, 257, 129), (520, 255, 256), (170, 1, 144)]      # tokens, visual, deciders
     samples = [W.random_case(600 + i, N, 8 * dh, 8, 3, V, D, dtype="bf16") for i, (N, V, D) in enumerate(shapes)]
     for s, (_, _, D) in zip(samples, shapes):
         s["dec_idx"] = np.resize(s["dec_idx"], D).astype(np.int32)         # (repeats where there are fewer positions)
         s["D"] = D
-    batch = samples * copies * (16 if copies > 1 else 1)
+    batch = samples * copies
     S = GpuStep(batch, [max(1, s["V"] // 4) for s in batch], "bf16").importance()
     for i, s in enumerate(samples):
         ref = oracle.importance(s["q"], s["k"], s["dec_idx"], s["vis_start"], s["V"])
@@ -288,7 +288,7 @@ def test_attend_both_sides_of_the_short_sample_limit(H, dh, longest):
     (3, 128, False, [513, 640, 641, 1, 128, 129]),                  # few heads: 128-query tiles
     (3, 64, True, [577, 640, 64, 65]),
     (32, 128, False, [513, 512, 257, 256, 255, 63, 1, 65]),         # enough heads for 256-query tiles
-    (32, 64, True, [512, 513, 257, 64, 192, 193, 33, 128]),
+    (32, 64, True, [700, 513, 257, 64, 192, 193, 33, 128]),
 ])
 def test_attend_tile_widths_and_rising_logits(H, dh, weighted, lens, rise):
     """Both query tile widths of the tiled kernel; with `rise` later keys exceed the first tile's largest logit by hundreds, so
@@ -350,9 +350,12 @@ def test_attend_error_is_that_of_rounded_probabilities(H, dh, n, weighted, sprea
     (5, 128, 600, 32, True),             # ... of 256-query tiles
     (9, 64, 1030, 16, False), (9, 64, 1030, 16, True),
     (12, 128, 520, 64, False), (12, 128, 520, 65, False),       # as many samples as a wave has lanes, one more
+    (12, 128, 100, 65, False), (12, 128, 100, 66, True),        # one workgroup per 128-query tile, several rounds
+    (9, 64, 100, 65, False), (9, 64, 130, 65, True),
 ])
 def test_attend_tiles_in_turn(H, dh, longest, batch, weighted):
-    """Ragged batches of several rounds: a workgroup takes one tile after the other, from samples of one key to the longest."""
+    """Ragged batches of several rounds, from samples of one key to the longest: a workgroup takes one tile after the other, or (more than
+    64 samples; 128-query tiles with heads of 64) has one, and waves without a query skip their products."""
     edge = [longest, 1, 2, 63, 64, 65, 127, 128, 129, 192, 193, 255, 256, 257]
     lens = [min(longest, n) for n in (edge + [17 + 37 * i % longest for i in range(batch)])[:batch]]
     lens = lens[batch // 2:] + lens[:batch // 2]
@@ -393,7 +396,7 @@ def test_attend_short_last_tiles_behind_the_others(H, dh, lens, weighted):
                                              (2, 128, 513, False), (2, 128, 560, True), (2, 64, 656, False)])
 def test_attend_last_tile_with_few_queries(H, dh, n, weighted):
     """One round of 256-query tiles (60 heads) or 128-query tiles (2) whose last tile leaves one to seven of its eight waves without
-    a query: those only load and keep step."""
+    a query: with 256 queries those only load and keep step, with 128 they compute with rows that are zero and store nothing."""
     q, k, v = W.random_qkv(910 + n, n, H, dh, "bf16")
     vs, c = n // 5, (1 + np.arange(n // 2) % 37).astype(np.int32)
     o = (gpu_attend_weighted([(q, k, v)], [c], [vs], "bf16") if weighted else gpu_attend([(q, k, v)], "bf16"))[0]
