@@ -417,16 +417,16 @@ int launch_linear_cfg(int cfg, const void* a, const void* w, int M, int N, int K
 //   rounds * (stages * (rows a tile takes in of either operand) + epilogue and ring) + tiles / 256 * stages * products + launch
 // The rows count however few tiles there are; the products count by how full the chip is (above all power).  The two forms have constants of
 // their own, tiles of the same form share them; a wave whose fragments are three columns wide stores 8 bytes at a time instead of 16.
-// Cut contractions besides: what a million values of a partial matrix take to write (fragments of up to three columns fill the lines they
-// store, wider ones leave gaps between the lanes) and to read again.
-// Fitted to the times within 1.3 of a shape's best of 491 shapes, 159 of them with cut contractions too (16 .. 4600 rows; q | k | v, output,
-// gate | up and down projections of 512 .. 5632 channels; weights cold in HBM): there the choice is 0.5 % behind the best built tile on
-// average.  On 376 shapes that the fit has not seen it is 0.7 % behind, 3.2 % at the 90th percentile, 9.7 % at the 99th, 19.6 % at most.  (A
-// table of five constants for each of the 17 tiles: 0.8 %, 2.8, 17.5 and 24.7 %.)  profiles/projection_tiles.txt has the times.
+// Cut contractions besides: what a million values of a partial matrix take to write (by eight waves or by four, whose fragments fill the
+// lines they store, or are more than three columns wide and leave gaps between the lanes) and to read again.
+// Fitted to the times within 1.3 of a shape's best of 782 shapes, 259 of them with cut contractions too (16 .. 4600 rows; q | k | v, output,
+// gate | up and down projections of 512 .. 5632 channels; weights cold in HBM): there the choice is 0.7 % behind the best built tile on
+// average.  On 654 shapes that the fit has not seen it is 0.8 % behind, 3.8 % at the 90th percentile, 9.8 % at the 99th, 19.6 % at most.  (A
+// table of five constants for each of the 17 tiles: 0.9 %, 3.8, 10.9 and 24.7 %.)  profiles/projection_tiles.txt has the times.
 static double linear_estimate(int cfg, int M, int cols, int nst, int ksplit) {
     struct Form { double a_rows, w_rows, products, round; };
-    constexpr Form PING_PONG = {0.49, 0.42, 0.37, 8.75}, LOADERS = {0.37, 0.56, 0.31, 3.24};       // of 256 rows, 256 x 256 tiles
-    constexpr double LAUNCH = 2.14, NARROW_STORES = 2.7, PART_FILLED = 0.73, PART_GAPS = 1.4, PART_READ = 0.45;
+    constexpr Form PING_PONG = {0.50, 0.40, 0.36, 9.31}, LOADERS = {0.36, 0.54, 0.32, 4.02};       // of 256 rows, 256 x 256 tiles
+    constexpr double LAUNCH = 2.18, NARROW_STORES = 1.85, PART_PING_PONG = 0.54, PART_LOADERS = 0.90, PART_GAPS = 1.45, PART_READ = 0.45;
     const LinTile& t = LIN_TILES[cfg];
     const Form& f = t.wc == 4 ? PING_PONG : LOADERS;
     const int tn = t.bn / (16 * t.wc);
@@ -434,7 +434,7 @@ static double linear_estimate(int cfg, int M, int cols, int nst, int ksplit) {
     const double area = (double)(t.bm * t.bn) / 65536.0, stages = nst / ksplit;
     double us = (double)((tiles + 255) / 256) * (stages * (f.a_rows * t.bm + f.w_rows * t.bn) / 256.0 + (f.round + (tn == 3 ? NARROW_STORES : 0.0)) * area);
     us += (double)tiles / 256.0 * stages * f.products * area + LAUNCH;
-    if (ksplit > 1) us += (double)M * cols * ksplit * 1e-6 * ((tn <= 3 ? PART_FILLED : PART_GAPS) + PART_READ);
+    if (ksplit > 1) us += (double)M * cols * ksplit * 1e-6 * ((tn > 3 ? PART_GAPS : t.wc == 4 ? PART_PING_PONG : PART_LOADERS) + PART_READ);
     return us;
 }
 // the best tile for a projection in one launch (`cols` counts rows of w; SWIGLU: gate and up); bm: of that height

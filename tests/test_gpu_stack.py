@@ -254,7 +254,7 @@ def test_linear_every_tile_with_every_epilogue(B, index, epilogue, stages, rows_
 
 
 # (rows, rows of w, contraction) for which the library takes the tile named, ragged in both directions; the last is cut into two launches
-LIN_CHOSEN = [("64x64 loaders", 100, 1008, 64), ("64x64 loaders", 100, 48, 64), ("64x96 loaders", 70, 12288, 4096), ("64x128 loaders", 250, 4112, 64),
+LIN_CHOSEN = [("64x64 loaders", 100, 1008, 64), ("64x64 loaders", 100, 48, 64), ("64x96 loaders", 70, 12288, 4096), ("64x96 loaders", 250, 4112, 64), ("64x128 loaders", 1500, 1008, 64),
               ("96x128 loaders", 900, 3008, 64), ("128x128", 700, 4112, 2048), ("128x192 loaders", 500, 12288, 320), ("128x256", 300, 16400, 640),
               ("160x128 loaders", 1500, 3008, 320), ("160x128 loaders", 3300, 3008, 320), ("160x256", 300, 22016, 1024),
               ("192x128 loaders", 1300, 4112, 640), ("192x128 loaders", 2500, 4112, 320), ("192x256", 493, 16400, 1024), ("224x256", 3000, 4112, 1024),
