@@ -111,7 +111,14 @@ constexpr int ATT_WKEYS = 3584;     // longest sample of the weighted tiled kern
 
 // SKIP: waves without queries skip their products.  Not in a single round of 128-query tiles, where the skipping gains nothing and the
 // second loop costs 1 to 3 % (900 keys, 16 heads of 64 13.2 us without it, 13.6 with it; 775 keys, 8 heads of 128 15.5 and 15.7).
-template <int DH, bool WGT, int NQ, bool TURNS, bool SKIP>
+//
+// SPLIT: the groups share their queries (64 of them) and take the tiles of keys in turn, each in its own half of the ring; at the end
+// each hands half of the channels of its O^T to the other through LDS.  A launch that leaves compute units idle is one chain of
+// phases per unit, and this is half as long a chain on twice as many units: 8 heads of 128, 775 keys 15.8 -> 11.3 us, 2000 keys 33.4 -> 23.1,
+// 16 heads of 64, 1024 keys 13.9 -> 9.4; 32 heads of 128, 493 keys 11.9 (the short-sample kernel) -> 9.0, each unit taking in
+// the keys of its head once instead of twice.  No part of a phase bounds it (without loads, exponentials, rescaling or reads of V it is 3 to 8 %
+// faster each).
+template <int DH, bool WGT, int NQ, bool TURNS, bool SKIP, bool SPLIT>
 __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ cu, int H, int nB, int nqt, float scale2, uint16_t* __restrict__ o, KeyWeights kw) {
@@ -121,12 +128,12 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     constexpr int ROWB = DH * 2;                // bytes per K / V row in LDS (unpadded, chunks swizzled)
     constexpr int NCHK = DH / 8;                // 16-byte chunks per row
     constexpr int RPI = 64 / NCHK;              // rows covered by one wave-wide direct load (1 KB)
-    constexpr int LD = ATT_BK / (8 * RPI);      // direct loads per wave and operand tile
+    constexpr int LD = ATT_BK / ((SPLIT ? 4 : 8) * RPI);        // direct loads per wave and operand tile
     constexpr int TILE = ATT_BK * ROWB;         // bytes of one K (or V) tile
     constexpr int STAGE = 2 * TILE;             // stage j: K of tile j, V of tile j - 1
     constexpr int NS = ATT_SLOTS;
-    constexpr int AHEAD = NS - 1;               // the softmax phase of tile j fetches stage j + AHEAD
-    constexpr int BQ = NQ * 128;                // queries of the workgroup: NQ blocks of 16 per wave
+    constexpr int AHEAD = SPLIT ? 2 : NS - 1;   // the softmax phase of tile j fetches stage j + AHEAD
+    constexpr int BQ = NQ * (SPLIT ? 64 : 128); // queries of the workgroup: NQ blocks of 16 per wave
     constexpr int KPRE = 2 * KS;                // K fragments read ahead: the first 32 keys
     typedef unsigned att_u4 __attribute__((ext_vector_type(4)));
     extern __shared__ __attribute__((aligned(16))) char ring[];
@@ -134,6 +141,9 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), grp = wave >> 2;
+    const int wq = SPLIT ? wave & 3 : wave;                // SPLIT: waves i and i + 4 have the same queries
+    auto tile_of = [&](int j) { return SPLIT ? 2 * j + grp : j; };     // the j-th tile of keys of this wave's group
+    auto slot_of = [&](int j) { return SPLIT ? (j & 1) * 2 + grp : j % NS; };
     const int r = lane & 15, g = lane >> 4;
     const size_t rs = (size_t)H * DH;                      // token stride (elements)
     const int row_bytes = (int)(rs * 2);
@@ -209,8 +219,10 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
         if (qt * BQ >= n) return;
     }
     // what the logits start from; -inf past the end of the sample: those keys then need no other mask
+    constexpr int KROUND = SPLIT ? 2 * ATT_BK : ATT_BK;
+    static_assert(ATT_WKEYS % KROUND == 0, "the weights of the last tiles fit");
     auto write_weights = [&] {
-        for (int j = tid; j < ((n + ATT_BK - 1) / ATT_BK) * ATT_BK; j += 512)
+        for (int j = tid; j < ((n + KROUND - 1) / KROUND) * KROUND; j += 512)
             w_s[j] = (j < n) ? key_log2_weight(kw, b, j) / scale2 : -INFINITY;
     };
     if constexpr (WGT) write_weights();
@@ -220,7 +232,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     };
     __amdgpu_buffer_rsrc_t rk = rows_of(k), rv = rows_of(v), rq = rows_of(q);
 
-    int q0 = qt * BQ + wave * NQ * 16;          // this wave's first query
+    int q0 = qt * BQ + wq * NQ * 16;            // this wave's first query
     bf16x8 qf[NQ][KS];
     f32x4 ot[DB][NQ];
     // m_run: running maximum of the RAW logits; ms: what the exponents subtract; l_run: this lane's part of the column's sum
@@ -240,17 +252,17 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     int k_off[LD], v_off[LD];                   // byte offsets inside the head's K / V for key0 = 0
 #pragma unroll
     for (int i = 0; i < LD; ++i) {
-        const int x = (wave * LD + i) * RPI + lane / NCHK, pos = lane % NCHK;
+        const int x = (wq * LD + i) * RPI + lane / NCHK, pos = lane % NCHK;
         k_off[i] = x * row_bytes + ((pos ^ (DH == 128 ? (x & 15) : ((x >> 1) & 7))) << 4);
         v_off[i] = x * row_bytes + ((pos ^ (DH == 128 ? (x & 7) << 1 : ((x >> 1) & 3) << 1)) << 4);
     }
     const uint32_t ring0 = (uint32_t)(size_t)(lds_ptr_t)ring;
-    const uint32_t wave_lds = ring0 + wave * LD * 1024;
+    const uint32_t wave_lds = ring0 + wq * LD * 1024;
     auto issue_one = [&](int j, int i) {        // one of the 2 LD loads of stage j
-        const uint32_t dst = wave_lds + (j % NS) * STAGE + (i >> 1) * 1024;
+        const uint32_t dst = wave_lds + slot_of(j) * STAGE + (i >> 1) * 1024;
         // (stage 0 has no V tile: its offsets lie outside the buffer)
-        if (i & 1) direct_load_16(rv, v_off[i >> 1] + (j - 1) * ATT_BK * row_bytes, dst + TILE);
-        else direct_load_16(rk, k_off[i >> 1] + j * ATT_BK * row_bytes, dst);
+        if (i & 1) direct_load_16(rv, v_off[i >> 1] + tile_of(j - 1) * ATT_BK * row_bytes, dst + TILE);
+        else direct_load_16(rk, k_off[i >> 1] + tile_of(j) * ATT_BK * row_bytes, dst);
     };
     auto issue = [&](int j) {
 #pragma unroll
@@ -275,7 +287,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     auto mfma_phase = [&](int j, auto qk_c, auto pv_c) {
         constexpr bool QK = decltype(qk_c)::value, PV = decltype(pv_c)::value;
         typedef __attribute__((__vector_size__(8 * sizeof(short)))) short att_short8;
-        const char* sb = ring + (j % NS) * STAGE;
+        const char* sb = ring + slot_of(j) * STAGE;
         att_short8 vf[DB];                      // V^T of 32 keys, 16 dims each
         auto read_v = [&](int kt, int t) {
             const char* p = sb + (v_addr ^ (t << 5)) + kt * 32 * ROWB;
@@ -287,7 +299,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
             f32x4 c0[4];                        // what S^T starts from, per 16-key block
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb) {
-                if constexpr (WGT) c0[kb] = *reinterpret_cast<const f32x4*>(&w_s[j * ATT_BK + kb * 16 + g * 4]);
+                if constexpr (WGT) c0[kb] = *reinterpret_cast<const f32x4*>(&w_s[tile_of(j) * ATT_BK + kb * 16 + g * 4]);
                 else c0[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
 #pragma unroll
@@ -321,24 +333,26 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     };
     auto softmax_phase = [&](int j, auto last_c) {
         constexpr bool LAST = decltype(last_c)::value;
-        if (LAST && !WGT && (j + 1) * ATT_BK > n) {
+        if (LAST && !WGT && (tile_of(j) + 1) * ATT_BK > n) {
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
                 for (int qb = 0; qb < NQ; ++qb)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (j * ATT_BK + kb * 16 + g * 4 + e >= n) st[kb][qb][e] = -INFINITY;
+                        if (tile_of(j) * ATT_BK + kb * 16 + g * 4 + e >= n) st[kb][qb][e] = -INFINITY;
         }
         // The first fragments of tile j + 1 and the loads of stage j + AHEAD in turns, in front of the arithmetic (clocks per tile and
         // pair of groups, measured without maximum and sums: so 2960, reads first and then loads 3190, spread among the exponentials 3420).
+        // SPLIT, with twice as many loads in a phase: half of them behind the maximum (64 to 500 keys 2 % faster).
+        constexpr int LATER = SPLIT ? LD : 0;
         if constexpr (!LAST) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
 #pragma unroll
-                for (int f = i * KPRE / 8; f < (i + 1) * KPRE / 8; ++f) read_first(ring + ((j + 1) % NS) * STAGE, f);
+                for (int f = i * KPRE / 8; f < (i + 1) * KPRE / 8; ++f) read_first(ring + slot_of(j + 1) * STAGE, f);
 #pragma unroll
-                for (int f = i * 2 * LD / 8; f < (i + 1) * 2 * LD / 8; ++f) issue_one(j + AHEAD, f);
+                for (int f = i * (2 * LD - LATER) / 8; f < (i + 1) * (2 * LD - LATER) / 8; ++f) issue_one(j + AHEAD, f);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -363,6 +377,12 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
                     for (int e = 0; e < 4; ++e) ot[x][qb][e] *= alpha;
             }
         }
+        if constexpr (!LAST && LATER > 0) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int f = 2 * LD - LATER; f < 2 * LD; ++f) issue_one(j + AHEAD, f);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
@@ -376,31 +396,57 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
                 }
     };
 
-    int ntile = (n + ATT_BK - 1) / ATT_BK;
+    int ntile = (n + KROUND - 1) / KROUND;      // tiles of a group (SPLIT: the last one may lie past the end in part or, of group 1, in full)
     // The queries go through the ring's last two slots, each wave's rows in its own part: whole lines, and in flight together with
     // the first tiles.  Every wave has read them when stage 2 is started.
     constexpr int QROWS = NQ * 16, QLD = QROWS / RPI;
-    static_assert(8 * QROWS * ROWB <= 2 * STAGE, "the queries fit into two slots");
-    const int q_lds = 2 * STAGE + wave * QROWS * ROWB;
     auto row_swizzle = [](int x) { return DH == 128 ? (x & 15) : ((x >> 1) & 7); };
+    if constexpr (SPLIT) {
+        // (Half of the rows of a pair of waves from each of them, in the place of the V tile that stage 0 has not.)
+        constexpr int HROWS = QROWS / 2;
+        static_assert(4 * HROWS * ROWB <= TILE && HROWS % RPI == 0, "the queries fit beside the first tile");
+        const int q_lds = TILE + wq * HROWS * ROWB;
 #pragma unroll
-    for (int i = 0; i < QLD; ++i) {
-        const int x = i * RPI + lane / NCHK;
-        direct_load_16(rq, (q0 + x) * row_bytes + (((lane % NCHK) ^ row_swizzle(x)) << 4), ring0 + q_lds + i * 1024);
+        for (int i = 0; i < HROWS / RPI; ++i) {
+            const int x = grp * HROWS + i * RPI + lane / NCHK;
+            direct_load_16(rq, (q0 + x) * row_bytes + (((lane % NCHK) ^ row_swizzle(x)) << 4), ring0 + grp * STAGE + q_lds + i * 1024);
+        }
+#pragma unroll
+        for (int i = 0; i < 2 * LD; i += 2) issue_one(0, i);
+        issue(1);
+        wait_loads<2 * LD>();
+        if constexpr (WGT) __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): the weights are written
+        phase_barrier();
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const int x = qb * 16 + r;
+                qf[qb][ks] = *reinterpret_cast<const bf16x8*>(ring + (x / HROWS) * STAGE + q_lds + (x % HROWS) * ROWB + (((ks * 4 + g) ^ row_swizzle(x)) << 4));
+            }
+        __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): read before the other group loads into their place
+    } else {
+        static_assert(8 * QROWS * ROWB <= 2 * STAGE, "the queries fit into two slots");
+        const int q_lds = 2 * STAGE + wave * QROWS * ROWB;
+#pragma unroll
+        for (int i = 0; i < QLD; ++i) {
+            const int x = i * RPI + lane / NCHK;
+            direct_load_16(rq, (q0 + x) * row_bytes + (((lane % NCHK) ^ row_swizzle(x)) << 4), ring0 + q_lds + i * 1024);
+        }
+        issue(0);
+        issue(1);
+        wait_loads<2 * LD>();
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const bf16x8*>(ring + q_lds + (k_addr ^ (ks << 6)) + qb * 16 * ROWB);
+        __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0): the queries are there (and the weights written)
+        phase_barrier();
     }
-    issue(0);
-    issue(1);
-    wait_loads<2 * LD>();
-#pragma unroll
-    for (int qb = 0; qb < NQ; ++qb)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const bf16x8*>(ring + q_lds + (k_addr ^ (ks << 6)) + qb * 16 * ROWB);
-    __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0): the queries are there (and the weights written)
-    phase_barrier();
-    static_assert(AHEAD == 3, "three stages are under way when the loop starts");
+    static_assert(SPLIT || AHEAD == 3, "three stages are under way when the loop starts");
     using yes = std::integral_constant<bool, true>;
     using no = std::integral_constant<bool, false>;
-    constexpr int KEEP = (NS - 3) * 2 * LD;
+    constexpr int KEEP = SPLIT ? 0 : (NS - 3) * 2 * LD;
     bool first = true;
     // all tiles of keys; LIVE = false for a wave whose queries all lie past the end of the sample, which only requests its part of the
     // tiles and keeps step: in a last tile of at most 128 queries a SIMD has one wave to serve instead of two, in others the card has
@@ -408,16 +454,17 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     // heads 166 -> 155, 12 of 270 .. 800 84.6 -> 82.3, one of 1951 61.4 -> 60.5, of 3700 203 -> 201; 8 of 1000, 232 queries in the last, 133.)
     auto sweep = [&](auto live_c) {
         constexpr bool LIVE = decltype(live_c)::value;
-        issue(2);
+        if constexpr (!SPLIT) issue(2);
         if constexpr (LIVE) {
 #pragma unroll
-            for (int f = 0; f < KPRE; ++f) read_first(ring, f);
+            for (int f = 0; f < KPRE; ++f) read_first(ring + slot_of(0) * STAGE, f);
         }
         // Stage j + 1 has to have landed when the softmax phase of tile j begins (its first fragments are read there).  Groups that
         // share the ring: both wait for their loads before the barrier that ends group 0's MFMA phase of tile j.  Stages behind
-        // j + 1 stay in flight.
-        if (grp == 1) { if (first) wait_loads<KEEP>(); phase_barrier(); }
-        bool wait0 = grp == 0 && first;         // (behind another item the first two stages have landed, and its stores may still be on their way)
+        // j + 1 stay in flight.  SPLIT: a group has a ring of two slots of its own, and stage j + 1, requested in the softmax phase of tile j - 1,
+        // is all that is on its way; the group waits for it before the barrier that ends its own MFMA phase of tile j.
+        if (grp == 1) { if (!SPLIT && first) wait_loads<KEEP>(); phase_barrier(); }
+        bool wait0 = SPLIT || (grp == 0 && first);         // (behind another item the first two stages have landed, and its stores may still be on their way)
         if constexpr (LIVE) mfma_phase(0, yes(), no());
         // The last tile is peeled off: a loop left in its middle keeps both the accumulators before and after the MFMA phase alive.
         // (The weighted form with heads of 128 gets its trip count in a scalar register by force: the compiler counted in a vector register and
@@ -427,7 +474,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 #pragma unroll 1
         for (int j = 0; COUNTED ? j < last : j + 1 < ntile; ++j) {
             if (wait0) wait_loads<KEEP>();
-            wait0 = grp == 0;
+            wait0 = SPLIT || grp == 0;
             phase_barrier();
             if constexpr (LIVE) {
                 __builtin_amdgcn_s_setprio(2);
@@ -438,16 +485,59 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
             } else {
                 issue(j + AHEAD);
             }
-            if (grp == 1) wait_loads<KEEP>();
+            if (!SPLIT && grp == 1) wait_loads<KEEP>();
             phase_barrier();
             if constexpr (LIVE) mfma_phase(j + 1, yes(), yes());
         }
-        if (grp == 0) wait_loads<0>();
+        if (SPLIT || grp == 0) wait_loads<0>();
         phase_barrier();
         if constexpr (LIVE) softmax_phase(ntile - 1, yes());
         if (grp == 1) wait_loads<0>();
         phase_barrier();
         if constexpr (LIVE) mfma_phase(ntile, no(), yes());
+    };
+    // SPLIT: the two parts of the keys meet.  A wave gives the channels that it does not finish to the wave with the same queries (group 0
+    // finishes the first half of them), takes that wave's part of its own, and stores its half rows through LDS.
+    auto join_groups = [&](auto grp_c) {
+        constexpr int HALF = DB / 2, KEPT = decltype(grp_c)::value * HALF, GIVEN = HALF - KEPT;
+        constexpr int XCH = NQ * HALF * 1024, HROWB = ROWB / 2, HCHK = NCHK / 2;
+        static_assert(!SPLIT || 8 * (XCH + NQ * 128 + QROWS * HROWB) <= NS * STAGE, "what is exchanged, the sums and the rows fit into the ring");
+        f32x4* mine = reinterpret_cast<f32x4*>(ring + wave * XCH);
+        const f32x4* theirs = reinterpret_cast<const f32x4*>(ring + (wave ^ 4) * XCH);
+        float* sums = reinterpret_cast<float*>(ring + 8 * XCH);         // [wave][query block]: maximum of 16 queries, sum of 16 queries
+        char* rows = ring + 8 * (XCH + NQ * 128) + wave * QROWS * HROWB;
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) {
+            l_run[qb] = att_quad_sum(l_run[qb]);
+            if (g == 0) { sums[(wave * NQ + qb) * 32 + r] = m_run[qb]; sums[(wave * NQ + qb) * 32 + 16 + r] = l_run[qb]; }
+#pragma unroll
+            for (int t = 0; t < HALF; ++t) mine[(qb * HALF + t) * 64 + lane] = ot[GIVEN + t][qb];
+        }
+        wait_lds();
+        phase_barrier();
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) {
+            const float m1 = sums[((wave ^ 4) * NQ + qb) * 32 + r], l1 = sums[((wave ^ 4) * NQ + qb) * 32 + 16 + r];
+            const float m = fmaxf(m_run[qb], m1);
+            const float f0 = __builtin_amdgcn_exp2f((m_run[qb] - m) * scale2), f1 = __builtin_amdgcn_exp2f((m1 - m) * scale2);    // 0 for a part without keys
+            const float inv = 1.0f / (l_run[qb] * f0 + l1 * f1);
+#pragma unroll
+            for (int t = 0; t < HALF; ++t) {
+                const f32x4 a = ot[KEPT + t][qb], c = theirs[(qb * HALF + t) * 64 + lane];
+                uint2 w;
+                w.x = pack_bf16x2((a[0] * f0 + c[0] * f1) * inv, (a[1] * f0 + c[1] * f1) * inv);
+                w.y = pack_bf16x2((a[2] * f0 + c[2] * f1) * inv, (a[3] * f0 + c[3] * f1) * inv);
+                *reinterpret_cast<uint2*>(rows + (qb * 16 + r) * HROWB + (((t * 2 + (g >> 1)) ^ (r & (HCHK - 1))) << 4) + (g & 1) * 8) = w;
+            }
+        }
+        wait_lds();
+        const __amdgpu_buffer_rsrc_t ro = rows_of(o);
+#pragma unroll
+        for (int i = 0; i < QROWS * HCHK / 64; ++i) {
+            const int x = i * (64 / HCHK) + lane / HCHK;
+            const uint4 w = *reinterpret_cast<const uint4*>(rows + x * HROWB + (((lane % HCHK) ^ (x & (HCHK - 1))) << 4));
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(att_u4, w), ro, (q0 + x) * row_bytes + KEPT * 32 + (lane % HCHK) * 16, 0, 0);
+        }
     };
     for (int pass = 1;; ++pass) {
         if constexpr (SKIP) {
@@ -457,6 +547,11 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
         }
         wait_loads<0>();                        // nothing may be in flight into LDS when the workgroup ends
         if (grp == 0) phase_barrier();
+        if constexpr (SPLIT) {
+            phase_barrier();                    // everybody is done with the ring
+            if (grp == 0) join_groups(std::integral_constant<int, 0>()); else join_groups(std::integral_constant<int, 1>());
+            break;
+        }
 
         // O^T lies in the registers as 4 dims of a row per lane; through LDS the rows are stored in whole lines.  Slot ntile % NS may
         // still be read by group 1 (V of its last tile); the two behind the next one are free.
@@ -528,15 +623,15 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 // waits for the wave's own loads: K of the next tile is requested as soon as the K fragments are in
 // registers, V of the next tile as soon as the V fragments are).  At the end the four partial results
 // (running max, sum, O^T) meet in LDS and wave t combines and stores the 32 output dims t*32 ..
-// Four times the K/V traffic per query of the kernel above, which is why it is only used while the whole
-// sample is short.
+// Four times the K/V traffic per query of the kernel above, which is why it is only used while every workgroup has a compute unit to
+// itself.
 constexpr int ATS_BK = 32;      // keys per wave tile
 constexpr int ATS_MAX_KEYS = 512;
 
-template <int DH, bool WGT>
+template <int DH>
 __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-    const int32_t* __restrict__ cu, int H, int nB, int nqt, float scale2, uint16_t* __restrict__ o, KeyWeights kw) {
+    const int32_t* __restrict__ cu, int H, int nB, int nqt, float scale2, uint16_t* __restrict__ o) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int KS = DH / 16;
     constexpr int DT = DH / 32;
@@ -549,7 +644,6 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
     static_assert(WREG == DT * 16 * 64 * 4, "a wave's region also holds its partial O^T");
     extern __shared__ __attribute__((aligned(16))) char ring[];
     __shared__ float part_m[4][32], part_l[4][32];
-    __shared__ __attribute__((aligned(16))) float lw_s[WGT ? ATS_MAX_KEYS : 4];
 
     const int xcd = blockIdx.x & 7, li = blockIdx.x >> 3;
     const int hb = (li / nqt) * 8 + xcd, qt = li % nqt;
@@ -560,10 +654,6 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
     if (qt * 32 >= n) return;
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    if constexpr (WGT) {
-        for (int j = tid; j < ATS_MAX_KEYS; j += 256) lw_s[j] = (j < n) ? key_log2_weight(kw, b, j) : 0.f;
-        __syncthreads();
-    }
     const int c = lane & 31, g = lane >> 5;
     const size_t rs = (size_t)H * DH;
     const uint16_t* kb = k + (size_t)tok0 * rs + (size_t)h * DH;
@@ -645,72 +735,36 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
         // the K fragments are in registers (the MFMAs above consumed them): the K tile is free
         if (more) issue_k(key0 + 4 * ATS_BK);
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (WGT) {
-            // weighted: maximum and exponent on scale2 * logit + log2 w (m_run lives in that scaled domain)
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {
-                const f32x4 w4 = *reinterpret_cast<const f32x4*>(&lw_s[min(key0 + e4 * 8 + g * 4, ATS_MAX_KEYS - 4)]);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int key = key0 + e4 * 8 + g * 4 + e;
-                    const float t = __builtin_fmaf(st[e4 * 4 + e], scale2, w4[e]);
-                    st[e4 * 4 + e] = (key < n) ? t : -INFINITY;
-                }
-            }
-            float tmax = st[0];
-#pragma unroll
-            for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, st[e]);
-            tmax = att_pair_max(tmax);
-            const float m_new = fmaxf(m_run, tmax);
-            float psum = 0.f;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const float p = __builtin_amdgcn_exp2f(st[e] - m_new);
-                st[e] = p;
-                psum += p;
-            }
-            if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-                l_run *= alpha;
-#pragma unroll
-                for (int t = 0; t < DT; ++t)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) ot[t][e] *= alpha;
-            }
-            l_run += psum;
-            m_run = m_new;
-        } else {
         if (key0 + ATS_BK > n) {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int key = key0 + (e >> 2) * 8 + g * 4 + (e & 3);
-                    if (key >= n) st[e] = -INFINITY;
-                }
-            }
-            float tmax = st[0];
-#pragma unroll
-            for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, st[e]);
-            tmax = att_pair_max(tmax);
-            const float m_new = fmaxf(m_run, tmax);                // finite: every tile holds >= 1 valid key
-            const float ms = m_new * scale2;
-            float psum = 0.f;
-#pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(st[e], scale2, -ms));
-                st[e] = p;
-                psum += p;
+                const int key = key0 + (e >> 2) * 8 + g * 4 + (e & 3);
+                if (key >= n) st[e] = -INFINITY;
             }
-            if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-                const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale2);
-                l_run *= alpha;
-#pragma unroll
-                for (int t = 0; t < DT; ++t)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) ot[t][e] *= alpha;
-            }
-            l_run += psum;
-            m_run = m_new;
         }
+        float tmax = st[0];
+#pragma unroll
+        for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, st[e]);
+        tmax = att_pair_max(tmax);
+        const float m_new = fmaxf(m_run, tmax);                // finite: every tile holds >= 1 valid key
+        const float ms = m_new * scale2;
+        float psum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(st[e], scale2, -ms));
+            st[e] = p;
+            psum += p;
+        }
+        if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+            const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale2);
+            l_run *= alpha;
+#pragma unroll
+            for (int t = 0; t < DT; ++t)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) ot[t][e] *= alpha;
+        }
+        l_run += psum;
+        m_run = m_new;
         __builtin_amdgcn_sched_barrier(0);
         // V of this tile: everything older than the K loads just issued has landed
         if (more) wait_loads<LD>(); else wait_loads<0>();
@@ -759,7 +813,7 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
 #pragma unroll
     for (int w2 = 0; w2 < 4; ++w2) {
         const float mw = part_m[w2][c];
-        f[w2] = (mw == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((mw - m) * (WGT ? 1.0f : scale2));
+        f[w2] = (mw == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((mw - m) * scale2);
         l += part_l[w2][c] * f[w2];
     }
     const float inv = 1.0f / l;
@@ -885,56 +939,70 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
     const bool mfma = dt == D3TOM_BF16 && (dh == 128 || dh == 64) && fits32;
     // the weighted MFMA kernels keep a sample's weights in LDS
     if (wgt && mfma && max_seqlen > ATT_WKEYS) return D3TOM_ERR_UNSUPPORTED;
-    // short samples and too few 128-query tiles to fill the chip: keys split across the waves (measured
-    // crossover with the tiled kernel: ~550 keys at 32 heads)
-    if (mfma && max_seqlen <= ATS_MAX_KEYS && (long)ceil_div(max_seqlen, 128) * H * B <= 512) {
+    const long heads = (long)H * B;
+    // Short samples without weights whose 32-query workgroups have a compute unit each: keys split across the waves.  (Against the 64-query
+    // tiles below: 231 keys, 32 heads of 128 6.3 us and 6.5, 493 keys, 8 heads of 128 7.5 and 8.2, 493 keys, 16 heads of 64 5.6 and 6.2; up to
+    // 128 keys 5.2 and 4.7; two workgroups to a unit 493 keys, 32 heads of 128 11.5 and 8.9.)
+    if (mfma && !wgt && max_seqlen > 128 && max_seqlen <= ATS_MAX_KEYS && ceil_div(max_seqlen, 32) * heads <= 256) {
         const int nqt = ceil_div(max_seqlen, 32);
         const dim3 g((unsigned)(8 * ceil_div(H * B, 8) * nqt));
         const size_t lds = (size_t)4 * 2 * ATS_BK * dh * 2;
         const int threads = 256;
         static PerDeviceOnce lds_setup_s;
         if (!lds_setup_s.run([] {
-                return raise_dynamic_lds(attend_bf16_short_kernel<128, false>, 4 * 2 * ATS_BK * 128 * 2) &&
-                       raise_dynamic_lds(attend_bf16_short_kernel<64, false>, 4 * 2 * ATS_BK * 64 * 2) &&
-                       raise_dynamic_lds(attend_bf16_short_kernel<128, true>, 4 * 2 * ATS_BK * 128 * 2) &&
-                       raise_dynamic_lds(attend_bf16_short_kernel<64, true>, 4 * 2 * ATS_BK * 64 * 2);
+                return raise_dynamic_lds(attend_bf16_short_kernel<128>, 4 * 2 * ATS_BK * 128 * 2) &&
+                       raise_dynamic_lds(attend_bf16_short_kernel<64>, 4 * 2 * ATS_BK * 64 * 2);
             }))
             return D3TOM_ERR_DEVICE;
-#define D3TOM_ATT(KERNEL)                                                                                            \
-    D3TOM_LAUNCH(ATTEND, st, (KERNEL<<<g, threads, lds, st>>>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, \
-                                                           cu_seqlens, H, B, nqt, scale2, (uint16_t*)o, kw)))
-        if (dh == 128) { if (wgt) D3TOM_ATT((attend_bf16_short_kernel<128, true>)); else D3TOM_ATT((attend_bf16_short_kernel<128, false>)); }
-        else           { if (wgt) D3TOM_ATT((attend_bf16_short_kernel<64, true>));  else D3TOM_ATT((attend_bf16_short_kernel<64, false>)); }
+#define D3TOM_ATT_SHORT(DHV)                                                                                                   \
+    D3TOM_LAUNCH(ATTEND, st, (attend_bf16_short_kernel<DHV><<<g, threads, lds, st>>>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, \
+                                                           cu_seqlens, H, B, nqt, scale2, (uint16_t*)o)))
+        if (dh == 128) D3TOM_ATT_SHORT(128); else D3TOM_ATT_SHORT(64);
+#undef D3TOM_ATT_SHORT
     } else if (mfma) {
+        // 64-query tiles whose groups share the keys, where they fill one round of compute units at most: half as long a chain as 128-query
+        // tiles on twice as many units.  Two workgroups of heads of 64 fit on a unit, and of ragged batches fewer tiles are real than the longest
+        // sample lets the host expect.  Means over 897 drawn batches (1 to 16 samples of 33 to 2400 keys), the better of 128 and 256 queries
+        // against this, by the number of 64-query tiles: heads of 128, up to 256 tiles 1.13 (samples of up to 128 keys) to 1.46 (more than 1024), 257
+        // to 384 0.68 to 1.02; heads of 64, up to 256 tiles 1.12 to 1.37, 257 to 512 0.99 to 1.15 (up to 128 keys 0.92), 513 to 640 1.12 to 1.28,
+        // 641 to 768 0.95 to 1.07.  (A sample of one tile of keys has nothing to share.)
+        const bool split = max_seqlen > ATT_BK && ceil_div(max_seqlen, 64) * heads <= (dh == 64 && max_seqlen > 128 ? 640 : 256);
         // Rounds of workgroups over the 256 compute units.  A round of 128-query tiles costs 0.61 to 0.70 of one of 256-query tiles
         // (every fragment read from LDS feeds one MFMA instead of two; 32 heads, narrow against wide: 1024 keys 21.9 us against 30.9,
         // one round each; 1198 keys 44.7 against 35.7, two to one; 3773 keys 255 against 210, four to two; 2100 keys 106 against
         // 111, 3 x 1000 keys 60.9 against 64.9, three to two); with heads of 64 two workgroups of 128 queries share a CU, and it costs
-        // 0.52 (16 heads, 3500 keys: 69.2 against 65.9, two to one; 8 x 560 keys: 22.1 against 28.9, one to one).
-        const long heads = (long)H * B;
+        // 0.52 (16 heads, 3500 keys: 69.2 against 65.9, two to one; 8 x 560 keys: 22.1 against 28.9, one to one).  In a batch, whose samples may all
+        // but one be shorter than the bound, two rounds against one go to the narrow tiles there (the 116 of those batches that it changes: 1.08 x on
+        // average, 0.86 to 1.43).
         const long wide = (ceil_div(max_seqlen, 256) * heads + 255) / 256, narrow = (ceil_div(max_seqlen, 128) * heads + 255) / 256;
-        const int nq = (dh == 64 ? 55 : 66) * narrow < 100 * wide ? 1 : 2;
-        const int nqt = ceil_div(max_seqlen, nq * 128);
+        const int nq = split || (dh == 128 ? 66 : B > 1 ? 49 : 55) * narrow < 100 * wide ? 1 : 2;
+        const int nqt = ceil_div(max_seqlen, split ? 64 : nq * 128);
         // Several rounds of workgroups that have a compute unit to themselves: one per unit, which takes its tiles in turn, samples by
         // falling length (one tile per workgroup / in turn: 16 x 700 .. 1505 keys 440 / 422 us, 4 x 575 .. 1951 141 / 133, 12 x 270 .. 800
         // 114 / 82, 8 x 1000 149 / 145, one sample of 3773 211 / 211; 8 heads, 16 x 1000 .. 3000 303 / 262).
-        const bool turns = nqt * heads > 256 && !(dh == 64 && nq == 1) && B <= WAVE;
+        const bool turns = !split && nqt * heads > 256 && !(dh == 64 && nq == 1) && B <= WAVE;
         const dim3 g(turns ? 8u * ATT_TURNS_WGS : (unsigned)(8 * ceil_div(H * B, 8) * nqt));
         const size_t lds = (size_t)ATT_SLOTS * 2 * ATT_BK * dh * 2;
         const int threads = 512;
         const bool skip = nqt * heads > (dh == 64 ? 512 : 256);            // more than one round (two workgroups of 128 queries with heads of 64 to a unit)
-#define D3TOM_ATT8(DHV, WGTV, NQV, TURNSV, SKIPV)                                                                           \
+#define D3TOM_ATT(KERNEL)                                                                                            \
+    D3TOM_LAUNCH(ATTEND, st, (KERNEL<<<g, threads, lds, st>>>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, \
+                                                           cu_seqlens, H, B, nqt, scale2, (uint16_t*)o, kw)))
+#define D3TOM_ATT8(DHV, WGTV, NQV, TURNSV, SKIPV, SPLITV)                                                                   \
     do {                                                                                                                    \
         static PerDeviceOnce lds_setup;                                                                                     \
-        if (!lds_setup.run([] { return raise_dynamic_lds(attend_bf16_kernel<DHV, WGTV, NQV, TURNSV, SKIPV>, ATT_SLOTS * 2 * ATT_BK * DHV * 2); })) \
+        if (!lds_setup.run([] { return raise_dynamic_lds(attend_bf16_kernel<DHV, WGTV, NQV, TURNSV, SKIPV, SPLITV>, ATT_SLOTS * 2 * ATT_BK * DHV * 2); })) \
             return D3TOM_ERR_DEVICE;                                                                                        \
-        D3TOM_ATT((attend_bf16_kernel<DHV, WGTV, NQV, TURNSV, SKIPV>));                                                     \
+        D3TOM_ATT((attend_bf16_kernel<DHV, WGTV, NQV, TURNSV, SKIPV, SPLITV>));                                                     \
     } while (0)
-#define D3TOM_ATT8_2(DHV, WGTV) do { if (turns) D3TOM_ATT8(DHV, WGTV, 2, true, true); else D3TOM_ATT8(DHV, WGTV, 2, false, true); } while (0)
-#define D3TOM_ATT8_1(DHV, WGTV) do { if (skip) D3TOM_ATT8(DHV, WGTV, 1, false, true); else D3TOM_ATT8(DHV, WGTV, 1, false, false); } while (0)
-#define D3TOM_ATT8_128(WGTV) do { if (nq == 2) D3TOM_ATT8_2(128, WGTV); else if (turns) D3TOM_ATT8(128, WGTV, 1, true, true); else D3TOM_ATT8_1(128, WGTV); } while (0)
+#define D3TOM_ATT8_2(DHV, WGTV) do { if (turns) D3TOM_ATT8(DHV, WGTV, 2, true, true, false); else D3TOM_ATT8(DHV, WGTV, 2, false, true, false); } while (0)
+#define D3TOM_ATT8_1(DHV, WGTV) do { if (skip) D3TOM_ATT8(DHV, WGTV, 1, false, true, false); else D3TOM_ATT8(DHV, WGTV, 1, false, false, false); } while (0)
+#define D3TOM_ATT8_128(WGTV) do { if (nq == 2) D3TOM_ATT8_2(128, WGTV); else if (turns) D3TOM_ATT8(128, WGTV, 1, true, true, false); else D3TOM_ATT8_1(128, WGTV); } while (0)
 #define D3TOM_ATT8_64(WGTV) do { if (nq == 2) D3TOM_ATT8_2(64, WGTV); else D3TOM_ATT8_1(64, WGTV); } while (0)
-        if (dh == 128) { if (wgt) D3TOM_ATT8_128(true); else D3TOM_ATT8_128(false); }
+        if (split) {
+            if (dh == 128) { if (wgt) D3TOM_ATT8(128, true, 1, false, false, true); else D3TOM_ATT8(128, false, 1, false, false, true); }
+            else           { if (wgt) D3TOM_ATT8(64, true, 1, false, false, true);  else D3TOM_ATT8(64, false, 1, false, false, true); }
+        } else if (dh == 128) { if (wgt) D3TOM_ATT8_128(true); else D3TOM_ATT8_128(false); }
         else           { if (wgt) D3TOM_ATT8_64(true);  else D3TOM_ATT8_64(false); }
 #undef D3TOM_ATT8_64
 #undef D3TOM_ATT8_128

@@ -404,6 +404,33 @@ def test_attend_last_tile_with_few_queries(H, dh, n, weighted):
     check_attend(o, q, k, v, "bf16", rows=rows, key_weight=key_weights(n, vs, c) if weighted else None)
 
 
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("rise", [0.0, 9.0])
+@pytest.mark.parametrize("H,dh,lens", [
+    (3, 128, [65]), (2, 128, [127]), (2, 128, [128]), (2, 64, [129]), (2, 128, [191]), (2, 64, [192]), (2, 128, [193]),     # one and two tiles of keys a group
+    (2, 128, [520, 577, 641, 1, 63, 64, 65, 129]),      # samples without a tile for group 1, a last tile of it past the end
+    (5, 64, [700, 130, 2, 66, 127, 320]),
+    (1, 128, [2050]), (9, 64, [1030]),
+    (32, 128, [520]), (36, 64, [520, 300]), (130, 64, [128]), (2, 128, [64]), (3, 64, [33]),      # 128-query tiles, one round of them
+])
+def test_attend_groups_that_share_queries(H, dh, lens, rise, weighted):
+    """64-query tiles whose two groups of waves take the tiles of keys in turn, at the edges of tiles and of pairs of tiles, and the one
+    round of 128-query tiles that is left beside them.  With `rise` later keys exceed earlier ones by far, so that one group's part of a row
+    outweighs the other's; reversed rows the other way round."""
+    qkv = []
+    for i, n in enumerate(lens):
+        q, k, v = W.random_qkv(990 + n, n, H, dh, "bf16")
+        up = np.arange(n, dtype=np.float32) / n
+        k = W.round_to(k * (1 + rise * (up if i % 2 == 0 else up[::-1]))[:, None, None], "bf16")
+        qkv.append((q, k, v))
+    vis, counts = [n // 5 for n in lens], [(1 + np.arange(n // 2) % 37).astype(np.int32) for n in lens]
+    outs = gpu_attend_weighted(qkv, counts, vis, "bf16") if weighted else gpu_attend(qkv, "bf16")
+    for (q, k, v), o, vs, c in zip(qkv, outs, vis, counts):
+        n = len(q)
+        rows = np.union1d(np.arange(0, n, 1 if n < 66 else 13), np.arange(max(n - 9, 0), n))
+        check_attend(o, q, k, v, "bf16", rows=rows, key_weight=key_weights(n, vs, c) if weighted else None)
+
+
 def test_attend_special_cases_bf16():
     q, k, v = W.random_qkv(5, 150, 2, 128, "bf16", spread=2.0)
     v1 = np.broadcast_to(v[:1], v.shape).copy()
