@@ -8,8 +8,12 @@ namespace d3tom {
 constexpr int NORM_MAX_CHUNKS = 4;     // 16-byte chunks per thread held in registers: d <= 256 * 4 * 8
 
 // y = x / sqrt(mean(x^2) + eps) * gain
+// ANGLES: each row's workgroup also leaves the row's dh/2 rotary angles in the table (behind the merge, where the positions of the rows
+// have changed; a launch of its own takes 5 us, this one 0.3 longer)
+template <bool ANGLES>
 __global__ __launch_bounds__(256) void rmsnorm_bf16_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ gain,
-                                                           int d, float eps, uint16_t* __restrict__ y) {
+                                                           int d, float eps, uint16_t* __restrict__ y, const int32_t* __restrict__ pos,
+                                                           int dh, double log2_theta, float2* __restrict__ table) {
     __shared__ float wsum[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const size_t row = (size_t)blockIdx.x * d;
@@ -29,6 +33,10 @@ __global__ __launch_bounds__(256) void rmsnorm_bf16_kernel(const uint16_t* __res
     }
     ss = wave_sum(ss);
     if (lane == 0) wsum[wave] = ss;
+    if constexpr (ANGLES) {
+        const int half = dh >> 1;
+        if (tid < half) table[(size_t)blockIdx.x * half + tid] = rope_cos_sin(pos[blockIdx.x], tid, dh, log2_theta);
+    }
     __syncthreads();
     const float total = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
     const float rinv = 1.0f / sqrtf(total / (float)d + eps);
@@ -105,9 +113,7 @@ __global__ __launch_bounds__(256) void add_norm_bf16_kernel(const float* __restr
 
 // Rotary embedding, in place on q and k [rows, H, dh]: channel c < dh/2 of every head is paired with
 // channel c + dh/2 and the pair is turned by pos * theta^(-2c/dh).  The dh/2 angles of a token are the
-// same for all heads and for q and k: the first dh/2 threads evaluate them once, in double precision
-// (positions reach the thousands, where a float32 angle would already be off by 1e-4), the workgroup
-// then streams the row.
+// same for all heads and for q and k: the first dh/2 threads evaluate them once, the workgroup then streams the row.
 __global__ __launch_bounds__(256) void rope_bf16_kernel(uint16_t* __restrict__ q, uint16_t* __restrict__ k,
                                                         const int32_t* __restrict__ pos, int H, int dh, double log2_theta) {
     __shared__ float cs[128], sn[128];
@@ -115,10 +121,8 @@ __global__ __launch_bounds__(256) void rope_bf16_kernel(uint16_t* __restrict__ q
     const int half = dh >> 1;
     const int p = pos[blockIdx.x];
     if (tid < half) {
-        const double inv_freq = exp2(-2.0 * (double)tid / (double)dh * log2_theta);
-        double s, c;
-        sincos((double)p * inv_freq, &s, &c);
-        cs[tid] = (float)c; sn[tid] = (float)s;
+        const float2 t = rope_cos_sin(p, tid, dh, log2_theta);
+        cs[tid] = t.x; sn[tid] = t.y;
     }
     __syncthreads();
     const int cpp = half / 8;                        // 16-byte chunks per half head
@@ -148,34 +152,19 @@ __global__ __launch_bounds__(256) void rope_bf16_kernel(uint16_t* __restrict__ q
     }
 }
 
-// (cos, sin) of every token's dh/2 rotary angles, the float32 values the kernel above uses: for the projection
-// epilogue that applies the rotation itself (one table per step instead of one rotary launch per block)
-__global__ __launch_bounds__(256) void rope_table_kernel(const int32_t* __restrict__ pos, int rows, int dh, double log2_theta,
-                                                         float2* __restrict__ table) {
-    const int half = dh >> 1;
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= rows * half) return;
-    const int r = t / half, c = t - r * half;
-    const double inv_freq = exp2(-2.0 * (double)c / (double)dh * log2_theta);
-    double s, co;
-    sincos((double)pos[r] * inv_freq, &s, &co);
-    table[t] = make_float2((float)co, (float)s);
-}
-
-int rope_table_run(const int32_t* pos, int rows, int dh, float theta, float2* table, hipStream_t st) {
-    if (!pos || !table || rows < 1 || dh < 2) return D3TOM_ERR_INVALID_ARG;
-    if (!(theta > 1.f) || !(theta < 3.0e38f)) return D3TOM_ERR_INVALID_ARG;
-    D3TOM_LAUNCH(ROPE, st, (rope_table_kernel<<<ceil_div(rows * (dh >> 1), 256), 256, 0, st>>>(pos, rows, dh, log2((double)theta), table)));
-    return D3TOM_OK;
-}
-
-int rmsnorm_run(const void* x, const void* gain, int rows, int d, float eps, void* y, hipStream_t st) {
+// table != nullptr: the rotary angles of the rows at positions pos as well
+int rmsnorm_run(const void* x, const void* gain, int rows, int d, float eps, void* y, hipStream_t st, const int32_t* pos, int dh,
+                double log2_theta, float2* table) {
     if (!x || !gain || !y || rows < 1 || d < 1) return D3TOM_ERR_INVALID_ARG;
     if (!aligned16(x) || !aligned16(gain) || !aligned16(y)) return D3TOM_ERR_INVALID_ARG;
     if (!(eps >= 0.f)) return D3TOM_ERR_INVALID_ARG;
     if (d % 8 != 0 || d > 256 * NORM_MAX_CHUNKS * 8) return D3TOM_ERR_UNSUPPORTED;
-    D3TOM_LAUNCH(RMSNORM, st, (rmsnorm_bf16_kernel<<<rows, 256, 0, st>>>((const uint16_t*)x, (const uint16_t*)gain, d, eps,
-                                                                          (uint16_t*)y)));
+    if (table && (!pos || dh < 2 || dh > 512)) return D3TOM_ERR_INVALID_ARG;
+#define D3TOM_RMSNORM(ANGLES)                                                                                             \
+    D3TOM_LAUNCH(RMSNORM, st, (rmsnorm_bf16_kernel<ANGLES><<<rows, 256, 0, st>>>((const uint16_t*)x, (const uint16_t*)gain, d, eps, \
+                                                                                 (uint16_t*)y, pos, dh, log2_theta, table)))
+    if (table) D3TOM_RMSNORM(true); else D3TOM_RMSNORM(false);
+#undef D3TOM_RMSNORM
     return D3TOM_OK;
 }
 
@@ -201,7 +190,7 @@ int rope_run(void* q, void* k, const int32_t* pos, int rows, int H, int dh, floa
 }  // namespace d3tom
 
 extern "C" int d3tom_rmsnorm(const void* x, const void* gain, int rows, int d, float eps, void* y, void* stream) {
-    return d3tom::rmsnorm_run(x, gain, rows, d, eps, y, (hipStream_t)stream);
+    return d3tom::rmsnorm_run(x, gain, rows, d, eps, y, (hipStream_t)stream, nullptr, 0, 0.0, nullptr);
 }
 
 extern "C" int d3tom_rope(void* q, void* k, const int32_t* pos, int rows, int H, int dh, float theta, void* stream) {

@@ -179,6 +179,15 @@ __device__ __forceinline__ void rope_rotate(float a, float b, float c, float s, 
     rb = __builtin_fmaf(b, c, a * s);
 }
 
+// (cos, sin) of the rotary angle p * theta^(-2c/dh), evaluated in double precision (positions reach the thousands, where a float32
+// angle is already off by 1e-4) and rounded to float32.
+__device__ __forceinline__ float2 rope_cos_sin(int p, int c, int dh, double log2_theta) {
+    const double inv_freq = exp2(-2.0 * (double)c / (double)dh * log2_theta);
+    double s, co;
+    sincos((double)p * inv_freq, &s, &co);
+    return make_float2((float)co, (float)s);
+}
+
 // The same with the hardware exponential (one instruction, about 1 ulp, results below the normal range flush to
 // zero): for the MFMA kernels, whose workgroups combine hundreds of pairs each.
 __device__ __forceinline__ void lse2_combine_fast(float& m, float& z, float m2, float z2) {

@@ -136,5 +136,7 @@ int merge_run(const void* x0, void* y0, const void* x1, void* y1, const void* si
               const int32_t* out_off, int32_t* assign, int32_t* counts, int32_t* src_pos,
               void* ws, size_t ws_bytes, void* stream, bool prepared = false, int out_rows_hint = 0);
 size_t merge_ws_bytes(int B, int max_V);
+// whether such a merge reads norms of the rows (one that cuts the contraction into slices sums the squares itself)
+bool merge_takes_norms(int B, int max_V, int max_keep, int max_pruned, int d_sim, int dt);
 
 }  // namespace d3tom

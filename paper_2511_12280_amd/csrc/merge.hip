@@ -883,6 +883,40 @@ __global__ __launch_bounds__(256) void merge_scatter_kernel(
 
 using namespace d3tom;
 
+// How the cosine kernel takes a batch: rows of a tile / 64, slices of the contraction; mfma: whether it is the MFMA kernel at all.
+namespace {
+struct CosPlan { bool mfma; int TM, ksplit; };
+CosPlan cos_plan(int B, int max_V, int max_keep, int max_pruned, int d_sim, int dt) {
+    const bool mfma = (dt == D3TOM_BF16) && (d_sim % COS_BK == 0) && ((size_t)max_V * d_sim * 2 < ((size_t)1 << 31));
+    int TM = 1, ksplit = 1;
+    if (mfma && max_pruned > 0) {
+        const int nct = ceil_div(max_keep, COS_BN);
+        // as long as the 64-row tiles still fit one round of the 256 CUs they finish sooner than half as many
+        // 128-row tiles (a 64-row tile's k-loop is ~0.7 of a 128-row tile's); several rounds of 128-row tiles are 256-row tiles, which
+        // move a third less operand data per flop and whose rests the kernel cuts (against 128-row tiles, merges at d = 4096: 4500 rows keeping
+        // 0.2 .. 0.5 70 -> 59 us, 5 samples of 2304 90 -> 76, 9 of 1152 .. 2304 114 -> 83).  From 16 samples on, where the bounds that the
+        // host has are far above what the samples need, they are also better above half a round: 450 drawn batches of 16 to 100 samples of 90 to
+        // 900 rows at d = 1024 .. 4096, merges and whole merge layers, 1.04 x at 1024, 1.05 at 2048, 1.09 at 4096, 0.93 at the least; below half a
+        // round (435 batches) 0.99, at the least 0.84.  Above half a round 14 and 15 samples gain 1.01, 5 to 7 0.99, and some lose 10 %.
+        const long t64 = (long)nct * ceil_div(max_pruned, 64) * B, t128 = (long)nct * ceil_div(max_pruned, 128) * B;
+        TM = t128 > (B >= 16 ? 128 : 256) ? 4 : t64 > 256 ? 2 : 1;
+        // too few 64 x 128 tiles for 256 CUs (short sequences): cut the contraction into k-slices as well
+        if (TM == 1) {
+            const int stages = d_sim / COS_BK;
+            if (t64 <= COS_SPLIT_BLOCKS / 2) {
+                ksplit = 16;
+                while (ksplit > 1 && (t64 * ksplit > COS_SPLIT_BLOCKS || stages % ksplit || stages / ksplit < cos_ring_stages(1))) ksplit >>= 1;
+            }
+        }
+    }
+    return {mfma, TM, ksplit};
+}
+}  // namespace
+bool d3tom::merge_takes_norms(int B, int max_V, int max_keep, int max_pruned, int d_sim, int dt) {
+    const CosPlan p = cos_plan(B, max_V, max_keep, max_pruned, d_sim, dt);
+    return max_pruned > 0 && p.ksplit == 1;
+}
+
 // Both entry points: norms + pruned list, cosine argmax, token -> slot table, scatter of one or two
 // payloads that share the routing.
 int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const void* sim, int d, int d_sim, int dt,
@@ -927,28 +961,9 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
         }))
         return D3TOM_ERR_DEVICE;
 
-    const bool mfma = (dt == D3TOM_BF16) && (d_sim % COS_BK == 0) && ((size_t)max_V * d_sim * 2 < ((size_t)1 << 31));
-    int TM = 1, ksplit = 1;
-    if (mfma && max_pruned > 0) {
-        const int nct = ceil_div(max_keep, COS_BN);
-        // as long as the 64-row tiles still fit one round of the 256 CUs they finish sooner than half as many
-        // 128-row tiles (a 64-row tile's k-loop is ~0.7 of a 128-row tile's); several rounds of 128-row tiles are 256-row tiles, which
-        // move a third less operand data per flop and whose rests the kernel cuts (against 128-row tiles, merges at d = 4096: 4500 rows keeping
-        // 0.2 .. 0.5 70 -> 59 us, 5 samples of 2304 90 -> 76, 9 of 1152 .. 2304 114 -> 83).  From 16 samples on, where the bounds that the
-        // host has are far above what the samples need, they are also better above half a round: 450 drawn batches of 16 to 100 samples of 90 to
-        // 900 rows at d = 1024 .. 4096, merges and whole merge layers, 1.04 x at 1024, 1.05 at 2048, 1.09 at 4096, 0.93 at the least; below half a
-        // round (435 batches) 0.99, at the least 0.84.  Above half a round 14 and 15 samples gain 1.01, 5 to 7 0.99, and some lose 10 %.
-        const long t64 = (long)nct * ceil_div(max_pruned, 64) * B, t128 = (long)nct * ceil_div(max_pruned, 128) * B;
-        TM = t128 > (B >= 16 ? 128 : 256) ? 4 : t64 > 256 ? 2 : 1;
-        // too few 64 x 128 tiles for 256 CUs (short sequences): cut the contraction into k-slices as well
-        if (TM == 1) {
-            const int stages = d_sim / COS_BK;
-            if (t64 <= COS_SPLIT_BLOCKS / 2) {
-                ksplit = 16;
-                while (ksplit > 1 && (t64 * ksplit > COS_SPLIT_BLOCKS || stages % ksplit || stages / ksplit < cos_ring_stages(1))) ksplit >>= 1;
-            }
-        }
-    }
+    const CosPlan plan = cos_plan(B, max_V, max_keep, max_pruned, d_sim, dt);
+    const bool mfma = plan.mfma;
+    const int TM = plan.TM, ksplit = plan.ksplit;
     // prepared: the selection launch has left 1 / norm of every visual row (by token), the pruned list and the
     // initial table in the workspace; a split contraction computes the norms itself, and without that launch the list as well
     const dim3 gn(ceil_div(max_keep, 4), B);

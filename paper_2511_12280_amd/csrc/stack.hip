@@ -2,13 +2,13 @@
 // the merge layer inside block l*: full-length blocks before it, the merge between that block's attention
 // and its feed-forward part, every later block on the shortened sequence.  Host-side sequencing only: every
 // stage is one of the library's kernels, enqueued on the caller's stream.
-#include "common.hpp"
+#include "internal.hpp"
 
 namespace d3tom {
 int linear_run(const void* a, const void* w, int M, int N, int K, int epilogue, const void* residual, void* out,
                int out_chunk, int tile, hipStream_t st, const float2* rope_cs = nullptr, int rope_dh = 0);
-int rope_table_run(const int32_t* pos, int rows, int dh, float theta, float2* table, hipStream_t st);
-int rmsnorm_run(const void* x, const void* gain, int rows, int d, float eps, void* y, hipStream_t st);
+int rmsnorm_run(const void* x, const void* gain, int rows, int d, float eps, void* y, hipStream_t st, const int32_t* pos = nullptr, int dh = 0,
+                double log2_theta = 0.0, float2* table = nullptr);
 int rope_run(void* q, void* k, const int32_t* pos, int rows, int H, int dh, float theta, hipStream_t st);
 int linear_split_plan(int M, int N, int K, size_t max_floats, int* cfg);
 int linear_partial_run(const void* a, const void* w, int M, int N, int K, int ksplit, int cfg, float* partial, hipStream_t st);
@@ -33,14 +33,16 @@ enum MetaSlot { META_SEQ_OFF = 0, META_VIS_START, META_VIS_COUNT, META_VIS_OFF, 
 constexpr int META_STRIDE = STACK_MAX_BATCH + 1;
 constexpr int META_INTS = META_ARRAYS * META_STRIDE;
 
-// prefix sums of the per-sample sizes (one thread: at most 64 samples) and the position of every token inside
-// its sample
-__global__ void stack_meta_kernel(int32_t* meta, int32_t* pos, BatchSizes sz, int sum_N) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < sum_N) {
+// prefix sums of the per-sample sizes (one thread: at most 64 samples), the position of every token inside its sample and the (cos, sin) of
+// the token's dh/2 rotary angles there, which the projection epilogue that applies the rotation reads (a thread has one of them)
+__global__ __launch_bounds__(256) void stack_meta_kernel(int32_t* meta, int32_t* pos, BatchSizes sz, int sum_N, int dh, double log2_theta,
+                                                         float2* __restrict__ table) {
+    const int t = blockIdx.x * 256 + threadIdx.x, half = dh >> 1, row = t / half, c = t - row * half;
+    if (row < sum_N) {
         int off = 0, b = 0;
-        while (b < sz.B - 1 && t >= off + sz.N[b]) { off += sz.N[b]; ++b; }
-        pos[t] = t - off;
+        while (b < sz.B - 1 && row >= off + sz.N[b]) { off += sz.N[b]; ++b; }
+        if (c == 0) pos[row] = row - off;
+        table[t] = rope_cos_sin(row - off, c, dh, log2_theta);
     }
     if (t == 0) {
         int so = 0, vo = 0, ko = 0, oo = 0, dof = 0;
@@ -61,11 +63,6 @@ __global__ void stack_meta_kernel(int32_t* meta, int32_t* pos, BatchSizes sz, in
         meta[META_OUT_OFF * META_STRIDE + sz.B] = oo;
         meta[META_DEC_OFF * META_STRIDE + sz.B] = dof;
     }
-}
-
-__global__ void stack_copy_i32_kernel(const int32_t* __restrict__ src, int32_t* __restrict__ dst, int n) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) dst[t] = src[t];
 }
 
 struct StackWs {
@@ -172,21 +169,22 @@ extern "C" int d3tom_stack_step_batch(const void* x, int B, const int32_t* N_h, 
     void *h = base + w.h, *hm = base + w.hm, *nrm = base + w.nrm, *qkv = base + w.qkv;
     void *att = base + w.att, *act = base + w.act;
     float* part = (float*)(base + w.part);
-    float* scores = (float*)(base + w.scores);
-    int32_t* kept = (int32_t*)(base + w.kept);
+    // what the caller wants of the merge goes to the caller's arrays at once
+    float* scores = scores_out ? scores_out : (float*)(base + w.scores);
+    int32_t* kept = kept_idx_out ? kept_idx_out : (int32_t*)(base + w.kept);
     int32_t* slot = (int32_t*)(base + w.slot);
-    int32_t* asg = (int32_t*)(base + w.assign);
+    int32_t* asg = assign_out ? assign_out : (int32_t*)(base + w.assign);
+    int32_t* pos_out = src_pos ? src_pos : pos;      // positions of the output rows
+    if (!merging) pos = pos_out;
     void* sub = base + w.sub;
     const float scale = 1.0f / sqrtf((float)dh);
     if (n_out)
         for (int b = 0; b < B; ++b) n_out[b] = merging ? N_h[b] - (V_h[b] - keep_h[b]) : N_h[b];
     auto M = [&](int slot_id) { return meta + slot_id * META_STRIDE; };
 
-    D3TOM_LAUNCH(STACK_META, st, (stack_meta_kernel<<<ceil_div(sum_N, 256), 256, 0, st>>>(meta, pos, sz, sum_N)));
-    {   // rotary angles of the tokens at their positions; renewed after the merge, when the positions change
-        const int rc = rope_table_run(pos, sum_N, dh, theta, rope_cs, st);
-        if (rc != D3TOM_OK) return rc;
-    }
+    const double log2_theta = log2((double)theta);
+    // (rotary angles: renewed behind the merge, where the positions of the rows change)
+    D3TOM_LAUNCH(STACK_META, st, (stack_meta_kernel<<<(unsigned)(((size_t)sum_N * (dh / 2) + 255) / 256), 256, 0, st>>>(meta, pos, sz, sum_N, dh, log2_theta, rope_cs)));
 
     const void* cur = x;          // hidden state entering the block (the input itself is never written)
     int n = sum_N;                // its row count
@@ -228,28 +226,30 @@ extern "C" int d3tom_stack_step_batch(const void* x, int B, const int32_t* N_h, 
             D3TOM_TRY(d3tom_importance(qq, kk, D3TOM_BF16, B, M(META_SEQ_OFF), H, dh, scale, dec_idx, M(META_DEC_OFF),
                                        min_D, max_D, M(META_VIS_START), M(META_VIS_COUNT), M(META_VIS_OFF), max_N, max_V,
                                        scores, sub, w.sub_bytes, st));
-            D3TOM_TRY(d3tom_select_topk(scores, B, M(META_VIS_OFF), M(META_KEEP_K), M(META_KEPT_OFF), max_V, kept,
-                                        slot, sub, w.sub_bytes, st));
+            // the selection prepares the merge where that saves the norms launch (5 us; the rows are no colder than its own launch finds them)
+            MergePrep prep;
+            prep.feat = post;
+            prep.d = d;
+            prep.dt = D3TOM_BF16;
+            prep.vis_start = M(META_VIS_START);
+            prep.vis_count = M(META_VIS_COUNT);
+            merge_prep_targets(sub, B, max_V, &prep);
+            const bool norms = merge_takes_norms(B, max_V, max_keep, max_pruned, d, D3TOM_BF16);
+            bool prepared = false;
+            D3TOM_TRY(topk_run(scores, B, M(META_VIS_OFF), M(META_KEEP_K), M(META_KEPT_OFF), max_V, kept, slot, nullptr, M(META_SEQ_OFF), nullptr,
+                               nullptr, nullptr, st, norms ? &prep : nullptr, &prepared));
             void* merged = (post == h) ? hm : h;
-            D3TOM_TRY(d3tom_merge(post, nullptr, d, d, D3TOM_BF16, B, M(META_SEQ_OFF), M(META_VIS_START),
-                                  M(META_VIS_COUNT), M(META_VIS_OFF), kept, M(META_KEPT_OFF), max_N, max_V, max_keep,
-                                  max_pruned, max_out, mode, M(META_OUT_OFF), merged, asg, nullptr, pos, sub, w.sub_bytes,
-                                  st));
-            // from here on every stage sees the shortened sequences; pos holds the original positions
+            D3TOM_TRY(merge_run(post, merged, nullptr, nullptr, nullptr, d, d, D3TOM_BF16, B, M(META_SEQ_OFF), M(META_VIS_START),
+                                M(META_VIS_COUNT), M(META_VIS_OFF), kept, M(META_KEPT_OFF), max_N, max_V, max_keep,
+                                max_pruned, max_out, mode, M(META_OUT_OFF), asg, nullptr, pos_out, sub, w.sub_bytes, st, prepared));
+            // from here on every stage sees the shortened sequences; pos_out holds the original positions
             ht = merged;
-            D3TOM_TRY(rope_table_run(pos, sum_out, dh, theta, rope_cs, st));
             n = sum_out;
             longest = max_out;
             cu = M(META_OUT_OFF);
-            const int sum_k = sum_out - (sum_N - sum_V);
-            if (scores_out)
-                D3TOM_LAUNCH(STACK_META, st, (stack_copy_i32_kernel<<<ceil_div(sum_V, 256), 256, 0, st>>>((const int32_t*)scores, (int32_t*)scores_out, sum_V)));
-            if (kept_idx_out)
-                D3TOM_LAUNCH(STACK_META, st, (stack_copy_i32_kernel<<<ceil_div(sum_k, 256), 256, 0, st>>>(kept, kept_idx_out, sum_k)));
-            if (assign_out)
-                D3TOM_LAUNCH(STACK_META, st, (stack_copy_i32_kernel<<<ceil_div(sum_V, 256), 256, 0, st>>>(asg, assign_out, sum_V)));
         }
-        if (!ffn_nrm_ready) D3TOM_TRY(rmsnorm_run(ht, b.ffn_norm, n, d, eps, nrm, st));
+        if (!ffn_nrm_ready)
+            D3TOM_TRY(rmsnorm_run(ht, b.ffn_norm, n, d, eps, nrm, st, pos_out, dh, log2_theta, merge_here ? rope_cs : nullptr));
         D3TOM_TRY(linear_run(nrm, b.w_gate_up, n, 2 * F, d, LIN_SWIGLU, nullptr, act, 0, 0, st));
         void* outp = last ? y : ht;                  // in place, except that the last block writes the caller's y
         const int ks_d = linear_split_plan(n, d, F, STACK_PARTIAL_BYTES / sizeof(float), &cfg_d);
@@ -264,8 +264,6 @@ extern "C" int d3tom_stack_step_batch(const void* x, int B, const int32_t* N_h, 
         cur = outp;
     }
 #undef D3TOM_TRY
-    if (src_pos)
-        D3TOM_LAUNCH(STACK_META, st, (stack_copy_i32_kernel<<<ceil_div(n, 256), 256, 0, st>>>(pos, src_pos, n)));
     return D3TOM_OK;
 }
 
