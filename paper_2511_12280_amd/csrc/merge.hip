@@ -29,6 +29,7 @@ constexpr int COS_BK = 64;         // contraction elements per LDS stage
 
 // split-K partial products: at most COS_SPLIT_BLOCKS (tile, k-slice) blocks of 64 x 128 floats
 constexpr int COS_SPLIT_BLOCKS = 256;
+constexpr int COS_MAX_SLICES = 16;
 struct MergeWs {
     size_t pruned_off, rnorm_off, table_off, dots_off, sq_off, total;
     int VP;                    // table entries per sample
@@ -555,16 +556,16 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
 // Used when the similarity matrix has too few tiles to occupy the chip (short sequences): the GEMM is
 // then cut along the contraction instead, and one, two or four waves per pruned row finish the job here, each taking every
 // `wpr`-th column tile.  Slices are added in ascending order and ties go to the lowest slot, so the result is deterministic.
-// Bound by the latency of its loads, so a wave should go round its loop once, and all loads of a turn (16 slices of both halves of
+// Bound by the latency of its loads, so a wave should go round its loop once, and all loads of a turn (all slices of both halves of
 // the tile, the norms) are requested together: without a branch around any of them, since each branch costs a wait and some tens
 // of cycles.  (One wave per row, loads under conditions: 1400 rows x 600 slots x 2 slices 14.0 us, now 6.2; 486 x 243 x 4 slices
 // 6.8 us, now 3.8; 921 x 103 x 16 4.5 us, 3.9 with norms read by token, now 4.4.)
-template <int wpr>
+template <int wpr, int SLICES>
 __global__ __launch_bounds__(256) void cos_reduce_argmax(
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count,
     const int32_t* __restrict__ kept_off,
     int max_V, int max_keep, const int32_t* __restrict__ pruned,
-    const float* __restrict__ dots, int ksplit, int n_tiles, int nrt_launch, int nct_launch,
+    const float* __restrict__ dots, int n_tiles, int nrt_launch, int nct_launch,
     table_t* __restrict__ table, int VP, const float* __restrict__ sq, int nB) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BM = 64;
@@ -578,30 +579,30 @@ __global__ __launch_bounds__(256) void cos_reduce_argmax(
     if (s.k <= 0 || (int)blockIdx.x * rows >= s.M) return;
     const int rt = p / BM, lr = p % BM;
     const int nct = (p < s.M) ? (s.k + COS_BN - 1) / COS_BN : 0;
-    // Loads without branches: slices beyond the launch's, and tiles beyond the sample's, lie outside the buffer and read as 0
+    // Loads without branches: tiles beyond the sample's lie outside the buffer and read as 0
     // (columns beyond the sample's slots hold whatever the tile held; they are not looked at).
     const uint32_t slice = (uint32_t)n_tiles * (BM * COS_BN * 4);
-    const __amdgpu_buffer_rsrc_t dots_r = make_uniform_rsrc(dots, (uint32_t)ksplit * slice);
-    float v[2][16];
+    const __amdgpu_buffer_rsrc_t dots_r = make_uniform_rsrc(dots, (uint32_t)SLICES * slice);
+    float v[2][SLICES];
     auto request = [&](int ct) {
         const uint32_t tile_id = (uint32_t)((b * nrt_launch + rt) * nct_launch + ct);
         const uint32_t at = ct < nct ? (tile_id * BM + lr) * (COS_BN * 4) + lane * 4 : 0xC0000000u;
 #pragma unroll
         for (int half = 0; half < 2; ++half)
 #pragma unroll
-            for (int ks = 0; ks < 16; ++ks)
+            for (int ks = 0; ks < SLICES; ++ks)
                 v[half][ks] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dots_r, at + ks * slice + half * 256, 0, 0));
     };
     request(part);
     const int tok = (p < s.M) ? min(max(pruned[(size_t)b * max_V + p], 0), s.V - 1) : 0;
-    const __amdgpu_buffer_rsrc_t sq_r = make_uniform_rsrc(sq, (uint32_t)(ksplit * nB * nct_launch) * 512u);
+    const __amdgpu_buffer_rsrc_t sq_r = make_uniform_rsrc(sq, (uint32_t)(SLICES * nB * nct_launch) * 512u);
     for (int t = threadIdx.x; t < s.k; t += 256) {
-        float sl[16], ss = 0.f;
+        float sl[SLICES], ss = 0.f;
 #pragma unroll
-        for (int ks = 0; ks < 16; ++ks)
+        for (int ks = 0; ks < SLICES; ++ks)
             sl[ks] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sq_r, (((ks * nB + b) * nct_launch + t / COS_BN) * 128 + t % COS_BN) * 4, 0, 0));
 #pragma unroll
-        for (int ks = 0; ks < 16; ++ks) ss += sl[ks];
+        for (int ks = 0; ks < SLICES; ++ks) ss += sl[ks];
         rn_s[t] = reciprocal_norm(ss);
     }
     __syncthreads();
@@ -614,7 +615,7 @@ __global__ __launch_bounds__(256) void cos_reduce_argmax(
             if (slot < s.k) {
                 float sum = 0.f;
 #pragma unroll
-                for (int ks = 0; ks < 16; ++ks) sum += v[half][ks];        // ascending slices; absent ones add 0
+                for (int ks = 0; ks < SLICES; ++ks) sum += v[half][ks];        // ascending slices
                 const float val = sum * rn_s[slot];
                 if (val > best) { best = val; bidx = slot; }
             }
@@ -903,9 +904,16 @@ CosPlan cos_plan(int B, int max_V, int max_keep, int max_pruned, int d_sim, int 
         // too few 64 x 128 tiles for 256 CUs (short sequences): cut the contraction into k-slices as well
         if (TM == 1) {
             const int stages = d_sim / COS_BK;
-            if (t64 <= COS_SPLIT_BLOCKS / 2) {
-                ksplit = 16;
-                while (ksplit > 1 && (t64 * ksplit > COS_SPLIT_BLOCKS || stages % ksplit || stages / ksplit < cos_ring_stages(1))) ksplit >>= 1;
+            // How many slices: one more stage of the contraction costs a workgroup 0.19 us, one more slice of a tile 0.022 us, most of it in
+            // the launch that adds them.  (Merges of 100 to 2500 rows at d = 1024, 2048 and 4096, 1 and 3 samples, with 2, 4, 8 and 16 slices
+            // each: the choice is within 2 % of the best.  As many slices as 256 compute units hold, and 16 of them requested in any case:
+            // 1024 rows keeping 0.1 at 4096 18.1 -> 16.3 us, keeping half 20.3 -> 19.8, at 1024 16.2 -> 15.0 and 18.6 -> 15.9; 1600 keeping half
+            // at 4096 28.6 -> 26.6; 3 samples of 105 to 150 rows 18.5 -> 15.0.)
+            double least = 0.0;
+            for (int s = 2; t64 <= COS_SPLIT_BLOCKS / 2 && s <= COS_MAX_SLICES; s *= 2) {
+                if (t64 * s > COS_SPLIT_BLOCKS || stages % s || stages / s < cos_ring_stages(1)) break;
+                const double cost = (double)(stages / s) + 0.114 * (double)(t64 * s);
+                if (s == 2 || cost < least) { least = cost; ksplit = s; }
             }
         }
     }
@@ -957,7 +965,10 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
                    raise_dynamic_lds(cos_argmax_bf16<2, 3, false>, cos_ring_stages(2) * (128 + 96) * 128) &&
                    raise_dynamic_lds(cos_argmax_bf16<4, 4, false>, cos_ring_stages(4) * (256 + 128) * 128) &&
                    // the norms of every kept slot: above 16376 of them more than 64 KB with the kernel's own array
-                   raise_dynamic_lds(cos_reduce_argmax<4>, D3TOM_MAX_VISUAL * (int)sizeof(float));
+                   raise_dynamic_lds(cos_reduce_argmax<4, 2>, D3TOM_MAX_VISUAL * (int)sizeof(float)) &&
+                   raise_dynamic_lds(cos_reduce_argmax<4, 4>, D3TOM_MAX_VISUAL * (int)sizeof(float)) &&
+                   raise_dynamic_lds(cos_reduce_argmax<4, 8>, D3TOM_MAX_VISUAL * (int)sizeof(float)) &&
+                   raise_dynamic_lds(cos_reduce_argmax<4, 16>, D3TOM_MAX_VISUAL * (int)sizeof(float));
         }))
         return D3TOM_ERR_DEVICE;
 
@@ -1017,11 +1028,13 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
         if (ksplit > 1) {
             const int wpr = nct >= 3 ? 4 : nct;            // waves per pruned row: one column tile each, as far as four go
             const dim3 gr(ceil_div(max_pruned, 4 / wpr), B);
-#define D3TOM_REDUCE(WPRV)                                                                                              \
-    D3TOM_LAUNCH(COS_REDUCE, st, (cos_reduce_argmax<WPRV><<<gr, 256, (size_t)max_keep * sizeof(float), st>>>(           \
-        seq_off, vis_start, vis_count, kept_off, max_V, max_keep, pruned, dots, ksplit, nrt * nct * B, nrt, nct,        \
-        table, w.VP, sq, B)))
-            if (wpr == 1) D3TOM_REDUCE(1); else if (wpr == 2) D3TOM_REDUCE(2); else D3TOM_REDUCE(4);
+#define D3TOM_REDUCE(WPRV, SLICESV)                                                                                     \
+    D3TOM_LAUNCH(COS_REDUCE, st, (cos_reduce_argmax<WPRV, SLICESV><<<gr, 256, (size_t)max_keep * sizeof(float), st>>>(  \
+        seq_off, vis_start, vis_count, kept_off, max_V, max_keep, pruned, dots, nrt * nct * B, nrt, nct, table, w.VP, sq, B)))
+#define D3TOM_REDUCE_OF(SLICESV)                                                                                        \
+    do { if (wpr == 1) D3TOM_REDUCE(1, SLICESV); else if (wpr == 2) D3TOM_REDUCE(2, SLICESV); else D3TOM_REDUCE(4, SLICESV); } while (0)
+            if (ksplit == 2) D3TOM_REDUCE_OF(2); else if (ksplit == 4) D3TOM_REDUCE_OF(4); else if (ksplit == 8) D3TOM_REDUCE_OF(8); else D3TOM_REDUCE_OF(16);
+#undef D3TOM_REDUCE_OF
 #undef D3TOM_REDUCE
         }
     } else if (max_pruned > 0) {

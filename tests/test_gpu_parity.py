@@ -582,6 +582,23 @@ def test_merge_split_contraction_waves_per_row(shapes):
         check_full_sample(ref, b, S1, kept1, slot, m1)
 
 
+@pytest.mark.parametrize("d,shapes", [
+    (4096, [(130, 20)]), (4096, [(400, 50)]), (4096, [(640, 200), (90, 30)]),            # 16, 8 and 4 slices, one and two column tiles
+    (2048, [(200, 30)]), (2048, [(900, 200)]), (2048, [(900, 300), (64, 63)]),           # 8, 4 and 2
+    (1024, [(300, 90), (129, 1)]), (1024, [(1300, 500)]), (512, [(300, 129)]),           # 4, 2 and 2
+])
+def test_merge_slices_of_the_contraction(d, shapes):
+    """Every number of slices that short samples have their contraction cut into, with one, two and more column tiles: assignments and rows
+    against the oracle."""
+    samples = [W.random_case(760 + V + k, V + 5, d, d // 128, 5, V, 1, dtype="bf16", centres=max(2, V // 6)) for V, k in shapes]
+    rng = np.random.default_rng(d)
+    kept = [np.sort(rng.choice(V, size=k, replace=False)).astype(np.int32) for V, k in shapes]
+    out = GpuStep(samples, [k for _, k in shapes], "bf16").merge(kept)
+    for b, s in enumerate(samples):
+        check_assign(out["assign"][b], s["x"], s["vis_start"], s["V"], kept[b])
+        check_merge({key: out[key][b] for key in out}, s["x"], s["vis_start"], s["V"], kept[b], "bf16")
+
+
 @pytest.mark.parametrize("dtype,d,H,V,k", [
     ("bf16", 4096, 32, 300, 100),         # contraction cut in 16
     ("bf16", 2048, 16, 700, 513),         # cut in 2, five column tiles
