@@ -11,6 +11,8 @@
 // Bound by its chain of barriers on one compute unit: this takes 9 of them.  (A digit-by-digit radix selection with one
 // histogram per wave and keys in LDS took about 25: 8.0 us instead of 5.7 at 729 keys, 13.1 instead of 9.9 at 16 x 2304.)  Between them
 // exchanges and sums stay in the vector ALU, and the members are ranked sixteen lanes to each (729 keys 5.4 -> 4.4 us, 16 x 2304 8.6 -> 7.8).
+// A kernel of a few us also pays for the code that it fetches: unrolled for 1, 4 or 16 keys a thread it is 7, 12 or 32 KB (the last one for
+// all sizes against these: 144 keys 4.8 -> 4.2 us, 729 4.6 -> 3.9, 1024 beside streamed rows 6.0 -> 5.0, 3645 8.4 -> 7.5).
 //
 // The selection is a chain of short dependent passes on one compute unit per sample.  Called from the one-call
 // merge layer, the launch carries further workgroups (blockIdx.y > 0) that do not select anything: one wave per
@@ -40,7 +42,6 @@ __device__ __forceinline__ int keep_count_device(int V, double ratio) {
     return (int)c;
 }
 
-constexpr int TOPK_PER = D3TOM_MAX_VISUAL / TOPK_THREADS;      // keys per thread at most
 constexpr int TOPK_BINS = 2048;
 [[maybe_unused]] constexpr int TOPK_CAND = 1024;                                // members of one bin that are ranked directly
 
@@ -68,6 +69,7 @@ __device__ __forceinline__ uint32_t wave_min_u(uint32_t v) {
 }
 #endif
 
+template <int TOPK_PER>                          // keys per thread at most
 __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
     const float* __restrict__ scores, const int32_t* __restrict__ score_off, const int32_t* __restrict__ keep_k,
     const int32_t* __restrict__ kept_off, int max_V, int32_t* __restrict__ kept_idx, int32_t* __restrict__ slot_of,
@@ -98,27 +100,27 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
     const __amdgpu_buffer_rsrc_t mine = make_uniform_rsrc(scores + s0, (uint32_t)max(V, 0) * 4u);       // beyond the sample: 0, not fetched
 #pragma unroll
-    for (int c = 0; c < 4; ++c) key[c] = __builtin_amdgcn_raw_buffer_load_b32(mine, (c * TOPK_THREADS + tid) * 4, 0, 0);
+    for (int c = 0; c < TOPK_PER && c < 4; ++c) key[c] = __builtin_amdgcn_raw_buffer_load_b32(mine, (c * TOPK_THREADS + tid) * 4, 0, 0);
     if (V > 4 * TOPK_THREADS) {                   // requests beyond the sample take their turn in the load path too
 #pragma unroll
         for (int c = 4; c < TOPK_PER; ++c) key[c] = __builtin_amdgcn_raw_buffer_load_b32(mine, (c * TOPK_THREADS + tid) * 4, 0, 0);
     }
     if (keep_ratio && wave == 15) {
-        // kept counts from the ratios, on the device: this sample's count and the prefix sums over the samples
+        // kept counts from the ratios, on the device: this sample's count, and the prefix sums over the samples
         // in front of it (every workgroup repeats that, a sample per lane; the last one also writes the totals)
-        int koff = 0, ooff = 0, kb = 0, nb = 0;
-        for (int b0 = 0; b0 <= b; b0 += 64) {
+        const int kb = V > 0 ? keep_count_device(V, keep_ratio[b]) : 0;
+        const int nb = (seq_off[b + 1] - seq_off[b]) - (V - kb);
+        int koff = 0, ooff = 0;
+        for (int b0 = 0; b0 < b; b0 += 64) {
             const int bb = b0 + lane;
             int kcur = 0, ncur = 0;
-            if (bb <= b) {
+            if (bb < b) {
                 const int Vb = min(score_off[bb + 1] - score_off[bb], max_V);
                 kcur = Vb > 0 ? keep_count_device(Vb, keep_ratio[bb]) : 0;
                 ncur = (seq_off[bb + 1] - seq_off[bb]) - (Vb - kcur);
             }
-            koff += wave_total(bb < b ? kcur : 0);
-            ooff += wave_total(bb < b ? ncur : 0);
-            kb += wave_total(bb == b ? kcur : 0);
-            nb += wave_total(bb == b ? ncur : 0);
+            koff += wave_total(kcur);
+            ooff += wave_total(ncur);
         }
         if (lane == 0) {
             plan[0] = kb; plan[1] = koff;
@@ -184,11 +186,11 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
         hi = min(hi, lo + (uint32_t)((1u << shift) - 1u));
         remaining = sel[1];
         members = sel[2];
-        if (members <= TOPK_CAND || shift == 0) break;
+        if (TOPK_PER == 1 || members <= TOPK_CAND || shift == 0) break;       // (at most 1024 keys)
         for (int t = tid; t < TOPK_BINS; t += TOPK_THREADS) hist[t] = 0;
         __syncthreads();
     }
-    if (members <= TOPK_CAND) {
+    if (TOPK_PER == 1 || members <= TOPK_CAND) {
         // gather the members (any order) and rank each: the one with remaining - 1 members in front of it is the threshold
 #pragma unroll
         for (int c = 0; c < TOPK_PER; ++c) {
@@ -267,7 +269,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int c = c4 + u;
-            if (c * TOPK_THREADS >= V) break;
+            if (c >= TOPK_PER || c * TOPK_THREADS >= V) break;
             const bool keep = kept(c);
             const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
             const int slot = base + __builtin_amdgcn_readlane(exc, u * 16 + wave) + __popcll(m & ((1ull << lane) - 1ull));
@@ -304,8 +306,13 @@ int d3tom::topk_run(const float* scores, int B, const int32_t* score_off, const 
     const bool streaming = merge_prep_usable(prep_in, B, max_V, seq_off);
     const MergePrep prep = streaming ? *prep_in : MergePrep();
     const int extra = streaming ? (B >= TOPK_STREAM_WGS ? 1 : TOPK_STREAM_WGS / B) : 0;
-    D3TOM_LAUNCH(TOPK_SELECT, st, topk_select_kernel<<<dim3(B, 1 + extra), TOPK_THREADS, 0, st>>>(
-        scores, score_off, keep_k, kept_off, max_V, kept_idx, slot_of, keep_ratio, seq_off, keep_k_out, kept_off_out, out_off_out, prep));
+#define D3TOM_SELECT(PER)                                                                                       \
+    D3TOM_LAUNCH(TOPK_SELECT, st, (topk_select_kernel<PER><<<dim3(B, 1 + extra), TOPK_THREADS, 0, st>>>(           \
+        scores, score_off, keep_k, kept_off, max_V, kept_idx, slot_of, keep_ratio, seq_off, keep_k_out, kept_off_out, out_off_out, prep)))
+    if (max_V <= TOPK_THREADS) D3TOM_SELECT(1);
+    else if (max_V <= 4 * TOPK_THREADS) D3TOM_SELECT(4);
+    else D3TOM_SELECT(D3TOM_MAX_VISUAL / TOPK_THREADS);
+#undef D3TOM_SELECT
     if (prepared) *prepared = streaming;
     return D3TOM_OK;
 }

@@ -241,6 +241,21 @@ def test_topk_exact_including_ties_and_extremes():
         np.testing.assert_array_equal(sg, sr)
 
 
+@pytest.mark.parametrize("V,k", [(1, 1), (1023, 77), (1024, 1), (1024, 1023), (1025, 300), (4095, 4095), (4096, 5), (4097, 2000)])
+@pytest.mark.parametrize("ties", [False, True])
+def test_topk_sizes_around_keys_per_thread(V, k, ties):
+    """Largest samples around the numbers of keys that a thread holds, alone and with a sample of other size in front; few distinct values:
+    the threshold's bin has more keys than are ranked at once, where there are that many."""
+    rng = np.random.default_rng(V + k)
+    both = [rng.integers(0, 3, n).astype(np.float32) if ties else rng.random(n).astype(np.float32) for n in (V, (V + 1) // 2)]
+    for scores, ks in ((both[:1], [k]), (both[::-1], [(k + 1) // 2, k])):
+        kept, slot = _topk_only(scores, ks)
+        for s, kk, kg, sg in zip(scores, ks, kept, slot):
+            kr, sr = oracle.select_topk(s, kk)
+            np.testing.assert_array_equal(kg, kr)
+            np.testing.assert_array_equal(sg, sr)
+
+
 # ---- workspace -------------------------------------------------------------------------------------------
 @pytest.mark.parametrize("P,V,O,D,k,d", [(8, 700, 16, 9, 150, 512),      # normal cosine path (several tiles)
                                           (4, 300, 8, 5, 40, 4096)])      # few tiles, long rows: split along k
