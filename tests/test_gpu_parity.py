@@ -202,6 +202,16 @@ def test_importance_generic_kept_logits(dtype, H, dh):
             check_scores(S[i], oracle.importance(s["q"], s["k"], s["dec_idx"], s["vis_start"], s["V"]))
 
 
+@pytest.mark.parametrize("dtype,H,dh,D", [("bf16", 8, 64, 8), ("bf16", 5, 128, 13), ("bf16", 16, 64, 16), ("bf16", 257, 64, 1), ("bf16", 64, 64, 16),
+                                          ("bf16", 35, 64, 31), ("f32", 4, 64, 16), ("f32", 5, 36, 13), ("f32", 8, 32, 32), ("f32", 9, 32, 29)])
+def test_importance_rows_per_thread(dtype, H, dh, D):
+    """(head, decider) rows around what one, four and sixteen a thread take: 64, 65, 256, 257, 1024 and 1085 of them."""
+    samples = [W.random_case(690 + N, N, H * dh, H, 2, N - 2 - n, n, dtype=dtype) for N, n in ((70, D), (49, 1))]
+    S = GpuStep(samples, [4, 4], dtype).importance()
+    for i, s in enumerate(samples):
+        check_scores(S[i], oracle.importance(s["q"], s["k"], s["dec_idx"], s["vis_start"], s["V"]))
+
+
 @pytest.mark.parametrize("V,k", [(2100, 97), (2200, 96), (2300, 193), (3000, 900), (2801, 768)])
 def test_merge_column_tiles_of_96(V, k):
     """Single samples whose cosine tiles fill one round with 96 kept slots per tile: k around multiples of 96 and 128."""
