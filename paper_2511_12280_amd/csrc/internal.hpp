@@ -128,7 +128,7 @@ int topk_run(const float* scores, int B, const int32_t* score_off, const int32_t
              bool* prepared = nullptr);
 
 // d3tom_merge / d3tom_merge_kv; prepared: the selection launch has filled the workspace as MergePrep describes;
-// out_rows_hint: output rows per sample to expect when max_out is only a loose bound (tuning only)
+// out_rows_hint: output rows per sample to expect when max_out is only a loose bound (a sample may have more)
 int merge_run(const void* x0, void* y0, const void* x1, void* y1, const void* sim, int d, int d_sim, int dt,
               int B, const int32_t* seq_off, const int32_t* vis_start, const int32_t* vis_count,
               const int32_t* vis_off, const int32_t* kept_idx, const int32_t* kept_off,

@@ -624,6 +624,22 @@ def test_merge_slices_of_the_contraction(d, shapes):
         check_merge({key: out[key][b] for key in out}, s["x"], s["vis_start"], s["V"], kept[b], "bf16")
 
 
+@pytest.mark.parametrize("dtype,d,H", [("bf16", 512, 4), ("bf16", 4096, 32), ("f32", 96, 2), ("f32", 2048, 16)])
+def test_merge_layer_one_call_with_more_rows_than_expected(dtype, d, H):
+    """Samples with more output rows than the longest one without the longest visual part has: their workgroups take several rows (a merged one,
+    then copied ones, or another merged one; one or two workgroups a row).  Against the separate calls, bit for bit."""
+    shapes = [(2, 300, 3, 2, 0.02), (40, 20, 90, 3, 0.5), (0, 31, 250, 1, 1.0), (1, 100, 2, 2, 0.9)]
+    samples = [W.random_case(810 + i, P + V + O, d, H, P, V, D, dtype=dtype) for i, (P, V, O, D, _) in enumerate(shapes)]
+    ratios = [r for *_, r in shapes]
+    ref = GpuStep(samples, [oracle.keep_count(s["V"], r) for s, r in zip(samples, ratios)], dtype)
+    ref.importance(); kept, _ = ref.select_topk(); mout = ref.merge()
+    _, kept1, m1 = ref.merge_layer(ratios)
+    for b in range(len(samples)):
+        np.testing.assert_array_equal(kept1[b], kept[b])
+        for key in m1:
+            np.testing.assert_array_equal(m1[key][b], mout[key][b])
+
+
 @pytest.mark.parametrize("dtype,d,H,V,k", [
     ("bf16", 4096, 32, 300, 100),         # contraction cut in 16
     ("bf16", 2048, 16, 700, 513),         # cut in 2, five column tiles
