@@ -562,10 +562,12 @@ __global__ __launch_bounds__(256, 2) void imp_stream_bf16(
 // contiguous H x D x 64 bytes, subtracts each (head, decider) row's log-sum-exp and adds the exponentials
 // over deciders and heads, so the mean over heads is finished in the same pass (no per-head rows, no
 // third launch, K fetched once).
-// Bound by the chain metadata -> statistics -> exponentials -> reduction, so it has 16 waves: every thread holds one or two
-// (head, decider) rows of the statistics and at most 16 logits at 32 heads x 32 deciders, each kind requested at once.
+// Bound by the chain request -> statistics -> exponentials -> reduction, so it has 16 waves: every thread holds one or two
+// (head, decider) rows of the statistics and at most 16 logits at 32 heads x 32 deciders, all requested at once.  (Statistics behind the
+// logits and offsets, each chunk rescaling the sum before it: 1024 rows of 1152 keys 5.6 us, now 5.0; 208 of 817 3.7, 3.3.  Blocks of 8 keys on
+// twice as many compute units 5.2.)
 // Unrolled for 1, 4 or 16 (head, decider) rows a thread: rows that a block does not have cost their instructions all the same, in four
-// waves per SIMD (16 for all against these: 64 rows of 1120 and of 3773 keys 4.2 -> 2.7 us (float32) and 4.8 -> 3.4, 208 rows of 817 4.6 -> 3.7).
+// waves per SIMD (16 for all against these: 64 rows of 208 keys 4.2 -> 2.7 us (float32), of 3773 4.8 -> 3.4, 208 rows of 817 4.6 -> 3.7).
 // GENERIC: the logits of the generic first sweep, whose `part` is one finished log-sum-exp per (head, decider) (144 keys x
 // 4 heads x 16 deciders of 64 float32 channels: 7.5 us when every score's dot products were formed again, 4.3 from the logits).
 constexpr int IMP_KEEP_MAXD = IMP_KEEP_MAXD_WS;
@@ -588,8 +590,8 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     extern __shared__ float c_lds[];                    // [H][max_D] log2-sum-exp2, +inf for rows past the sample's deciders
     __shared__ float red[IMP_FL_THREADS / 64][16];
     // thread (key = t % 16, group = t / 16) takes rows group, group + 64, ... of the block's H x max_D logit rows: 64
-    // consecutive rows are 4 KB in one piece, requested together (they come from another XCD's writes, i.e. from memory).  The
-    // statistics below are a trip of their own behind them: the compiler waits for the logits before that loop.
+    // consecutive rows are 4 KB in one piece.  They, the statistics and the sample's offsets are requested together (they come from another
+    // XCD's writes, i.e. from memory): no request depends on an offset, what a sample does not have is left out when it is there.
     const int key = threadIdx.x & 15, grp = threadIdx.x >> 4;
     const int rows = H * max_D;
     const __amdgpu_buffer_rsrc_t lb = make_uniform_rsrc(logits + ((size_t)(b * NKB + kb) * rows) * 16, (uint32_t)rows * 64u);   // rows past the block's read as 0
@@ -600,27 +602,50 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
             l[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(lb, (uint32_t)((r0 + grp + u * IMP_FL_GROUPS) * 16 + key) * 4u, 0, 0));
     };
     request(0);
+    // the statistics of row t: head t / max_D (exact: (t + 1/2) / max_D is 1/64 or more away from the integers, t below 12288), decider the rest
+    const float per_head = __builtin_amdgcn_rcpf((float)max_D);
+    constexpr int NA = GENERIC ? 1 : 8;                     // chunks of keys requested at once
+    float2 a[NA];
+    int i = 0;
+    const float2* p = nullptr;
+    auto statistics = [&](int t) {
+        const int h = (int)(((float)t + 0.5f) * per_head);
+        i = t - h * max_D;
+        if constexpr (GENERIC) a[0].x = reinterpret_cast<const float*>(part)[(size_t)b * rows + t];
+        else {
+            p = part + ((size_t)(b * H + h) * NCH) * DPAD + i;
+#pragma unroll
+            for (int u = 0; u < NA; ++u) a[u] = p[min(u, NCH - 1) * DPAD];
+        }
+    };
+    const int wave0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x & ~63);
+    if (wave0 < rows) statistics(min((int)threadIdx.x, rows - 1));
     if (D <= 0 || key0 >= vs + V || key0 + 16 <= vs || key0 >= N) return;
     const int nch = min((N + KC - 1) / KC, NCH);
-    for (int t = threadIdx.x; t < rows; t += IMP_FL_THREADS) {
-        const int h = t / max_D, i = t - h * max_D;
-        float c = INFINITY;
-        if (GENERIC) {
-            if (i < D) c = reinterpret_cast<const float*>(part)[(size_t)b * rows + t];
-        } else if (i < D) {
-            const float2* p = part + ((size_t)(b * H + h) * NCH) * DPAD + i;
+    for (int t0 = wave0; t0 < rows;) {
+        const int t = t0 + ((int)threadIdx.x & 63);
+        float c = a[0].x;
+        if constexpr (!GENERIC) {
             float m = -INFINITY, z = 0.f;
-            for (int c0 = 0; c0 < nch; c0 += 8) {           // 8 independent loads in flight, combined in chunk order
-                float2 a[8];
+            for (int c0 = 0;;) {                            // combined in chunk order
+                float mn = m;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) a[u] = p[(size_t)min(c0 + u, nch - 1) * DPAD];
+                for (int u = 0; u < NA; ++u) mn = fmaxf(mn, c0 + u < nch ? a[u].x : -INFINITY);
+                const float ref = (mn == -INFINITY) ? 0.f : mn;      // nothing but empty chunks so far
+                z *= __builtin_amdgcn_exp2f(m - ref);
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (c0 + u < nch) lse2_combine_fast(m, z, a[u].x, a[u].y);
+                for (int u = 0; u < NA; ++u) z += c0 + u < nch ? a[u].y * __builtin_amdgcn_exp2f(a[u].x - ref) : 0.f;
+                m = mn;
+                c0 += NA;
+                if (c0 >= nch) break;
+#pragma unroll
+                for (int u = 0; u < NA; ++u) a[u] = p[(size_t)min(c0 + u, NCH - 1) * DPAD];
             }
             c = m + __builtin_amdgcn_logf(z);
         }
-        c_lds[t] = c;
+        if (t < rows) c_lds[t] = i < D ? c : INFINITY;
+        t0 += IMP_FL_THREADS;
+        if (t0 < rows) statistics(min(t0 + ((int)threadIdx.x & 63), rows - 1));
     }
     __syncthreads();
     float acc = 0.f;
