@@ -559,7 +559,8 @@ __global__ __launch_bounds__(512) void cos_argmax_bf16(
 // Bound by the latency of its loads, so a wave should go round its loop once, and all loads of a turn (all slices of both halves of
 // the tile, the norms) are requested together: without a branch around any of them, since each branch costs a wait and some tens
 // of cycles.  (One wave per row, loads under conditions: 1400 rows x 600 slots x 2 slices 14.0 us, now 6.2; 486 x 243 x 4 slices
-// 6.8 us, now 3.8; 921 x 103 x 16 4.5 us, 3.9 with norms read by token, now 4.4.)
+// 6.8 us, now 3.8; 921 x 103 x 16 4.5 us, 3.9 with norms read by token, then 4.4.)  No request waits for the sample's
+// offsets either, which only say what of the answers counts (921 x 103 x 8 3.8 us, now 3.4; 486 x 243 x 4 3.6, 3.4).
 template <int wpr, int SLICES>
 __global__ __launch_bounds__(256) void cos_reduce_argmax(
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count,
@@ -572,21 +573,19 @@ __global__ __launch_bounds__(256) void cos_reduce_argmax(
     extern __shared__ float rn_s[];             // [kept slots] 1 / norm, from the k-slices' sums of squares
     __shared__ float2 join[4];
     const int b = blockIdx.y;
-    const SampleGeom s = sample_geom(b, seq_off, vis_start, vis_count, kept_off, max_V, max_keep);
+    int t0 = seq_off[b], t1 = seq_off[b + 1], vs0 = vis_start[b], vc = vis_count[b], k0 = kept_off[b], k1 = kept_off[b + 1];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     constexpr int rows = 4 / wpr;
     const int p = blockIdx.x * rows + wave / wpr, part = wave % wpr;
-    if (s.k <= 0 || (int)blockIdx.x * rows >= s.M) return;
     const int rt = p / BM, lr = p % BM;
-    const int nct = (p < s.M) ? (s.k + COS_BN - 1) / COS_BN : 0;
-    // Loads without branches: tiles beyond the sample's lie outside the buffer and read as 0
-    // (columns beyond the sample's slots hold whatever the tile held; they are not looked at).
+    // Loads without branches: tiles beyond the launch's lie outside the buffer and read as 0 (what a tile holds beyond the sample's rows
+    // and slots is not looked at).
     const uint32_t slice = (uint32_t)n_tiles * (BM * COS_BN * 4);
     const __amdgpu_buffer_rsrc_t dots_r = make_uniform_rsrc(dots, (uint32_t)SLICES * slice);
     float v[2][SLICES];
     auto request = [&](int ct) {
         const uint32_t tile_id = (uint32_t)((b * nrt_launch + rt) * nct_launch + ct);
-        const uint32_t at = ct < nct ? (tile_id * BM + lr) * (COS_BN * 4) + lane * 4 : 0xC0000000u;
+        const uint32_t at = ct < nct_launch && rt < nrt_launch ? (tile_id * BM + lr) * (COS_BN * 4) + lane * 4 : 0xC0000000u;
 #pragma unroll
         for (int half = 0; half < 2; ++half)
 #pragma unroll
@@ -594,16 +593,27 @@ __global__ __launch_bounds__(256) void cos_reduce_argmax(
                 v[half][ks] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dots_r, at + ks * slice + half * 256, 0, 0));
     };
     request(part);
-    const int tok = (p < s.M) ? min(max(pruned[(size_t)b * max_V + p], 0), s.V - 1) : 0;
+    const int entry = pruned[(size_t)b * max_V + min(p, max_V - 1)];
     const __amdgpu_buffer_rsrc_t sq_r = make_uniform_rsrc(sq, (uint32_t)(SLICES * nB * nct_launch) * 512u);
-    for (int t = threadIdx.x; t < s.k; t += 256) {
-        float sl[SLICES], ss = 0.f;
+    float sl[SLICES];
+    auto squares = [&](int t) {
 #pragma unroll
         for (int ks = 0; ks < SLICES; ++ks)
             sl[ks] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sq_r, (((ks * nB + b) * nct_launch + t / COS_BN) * 128 + t % COS_BN) * 4, 0, 0));
+    };
+    squares(min((int)threadIdx.x, max_keep - 1));
+    request_together(t0, t1, vs0, vc, k0, k1);
+    const SampleGeom s = geom_of(t0, t1, vs0, vc, k0, k1, max_V, max_keep);
+    if (s.k <= 0 || (int)blockIdx.x * rows >= s.M) return;
+    const int nct = (p < s.M) ? (s.k + COS_BN - 1) / COS_BN : 0;
+    const int tok = min(max(entry, 0), s.V - 1);
+    for (int t = threadIdx.x; t < s.k;) {
+        float ss = 0.f;
 #pragma unroll
         for (int ks = 0; ks < SLICES; ++ks) ss += sl[ks];
         rn_s[t] = reciprocal_norm(ss);
+        t += 256;
+        if (t < s.k) squares(t);
     }
     __syncthreads();
     float best = -INFINITY; int bidx = 0x7FFFFFFF;
