@@ -837,10 +837,10 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
 #endif
 }
 
-// generic: one workgroup per (query, head), keys in chunks of 256, plain float online softmax.  One thread per key for
-// the logits; for the output a thread takes one 16-byte chunk of the channels and every G-th key (G = 256 / chunks), and the
-// G partial rows meet in LDS at the end.  (A single row of dh threads walking all keys is one chain of n dependent loads:
-// 8.1 us at 100 keys, launch included; split over the groups 6.1 us.)
+// generic: one workgroup per (query, head), keys in chunks of 256, plain float online softmax.  A wave forms the logits of 64 keys, 16 lanes
+// to a key; for the output a thread takes one 16-byte chunk of the channels and every G-th key (G = 256 / chunks), and the
+// G partial rows meet in LDS at the end.  The first values are requested with the keys.  (A single row of dh threads walking all keys is one
+// chain of n dependent loads: 8.1 us at 100 keys, launch included; split over the groups, a key to a thread 5.8 us; now 5.0.)
 template <typename T>
 __global__ __launch_bounds__(256) void attend_generic_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restrict__ cu,
@@ -853,7 +853,7 @@ __global__ __launch_bounds__(256) void attend_generic_kernel(
     __shared__ float ps[256];
     __shared__ float red[8];
     __shared__ float part[256][EPC + 1];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const size_t rs = (size_t)H * dh;
     const T* qr = q + (size_t)(tok0 + i) * rs + (size_t)h * dh;
     const int nch = dh / EPC, G = 256 / nch;
@@ -863,11 +863,22 @@ __global__ __launch_bounds__(256) void attend_generic_kernel(
 #pragma unroll
     for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
     for (int j0 = 0; j0 < n; j0 += 256) {
-        const int j = j0 + tid;
+        const int cnt = (grp < G) ? min(256, n - j0) : 0;
+        const T* vr = v + (size_t)(tok0 + j0) * rs + (size_t)h * dh + ch * EPC;
+        uint4 w[8];
+        auto values = [&](int t0) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) w[u] = *reinterpret_cast<const uint4*>(vr + (size_t)min(t0 + u * G, max(cnt - 1, 0)) * rs);
+        };
+        values(grp);                               // before the logits, whose keys arrive with them
+        const int first = j0 + wave * 64, j = first + wave_dots_row(lane);
         float s2 = -INFINITY;
-        if (j < n) {
-            s2 = row_dot<T>(qr, k + (size_t)(tok0 + j) * rs + (size_t)h * dh, dh) * scale2;
-            if (kw.counts) s2 += key_log2_weight(kw, b, j);
+        if (first < n) {
+            const float dot = wave_row_dots<T>(qr, k + (size_t)(tok0 + first) * rs + (size_t)h * dh, rs, n - first, dh, lane);
+            if (j < n) {
+                s2 = dot * scale2;
+                if (kw.counts) s2 += key_log2_weight(kw, b, j);
+            }
         }
         float wm = wave_max(s2);
         if (lane == 0) red[wave] = wm;
@@ -876,7 +887,7 @@ __global__ __launch_bounds__(256) void attend_generic_kernel(
         const float m_new = fmaxf(m_run, cmax);
         const float alpha = exp2f(m_run - m_new);
         const float p = (j < n) ? exp2f(s2 - m_new) : 0.f;
-        ps[tid] = p;
+        ps[wave * 64 + wave_dots_row(lane)] = p;
         float wsum = wave_sum(p);
         if (lane == 0) red[4 + wave] = wsum;
         __syncthreads();
@@ -884,16 +895,12 @@ __global__ __launch_bounds__(256) void attend_generic_kernel(
         m_run = m_new;
 #pragma unroll
         for (int e = 0; e < EPC; ++e) acc[e] *= alpha;
-        const int cnt = (grp < G) ? min(256, n - j0) : 0;
-        const T* vr = v + (size_t)(tok0 + j0) * rs + (size_t)h * dh + ch * EPC;
-        for (int t0 = grp; t0 < cnt; t0 += 4 * G) {
-            uint4 w[4];
+        for (int t0 = grp; t0 < cnt; t0 += 8 * G) {
+            if (t0 != grp) values(t0);
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                w[u] = (t0 + u * G < cnt) ? *reinterpret_cast<const uint4*>(vr + (size_t)(t0 + u * G) * rs) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float pt = (t0 + u * G < cnt) ? ps[t0 + u * G] : 0.f;
+            for (int u = 0; u < 8; ++u) {
+                if (t0 + u * G >= cnt) break;
+                const float pt = ps[t0 + u * G];
                 const uint32_t ww[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {

@@ -49,7 +49,7 @@ template <> struct Elem<uint16_t> {   // bf16 storage
     static __device__ __forceinline__ void store(uint16_t* p, float v) { *p = f32_to_bf16_bits(v); }
 };
 
-// Dot product of two rows of n elements (16-byte aligned, n a multiple of the elements per 16 bytes), chunks c0, c0 + step, ...:
+// Dot product of two rows of n elements (16-byte aligned, n a multiple of the elements per 16 bytes):
 // 16-byte loads, eight chunks requested before the first is used, float32 accumulation in that order.  For the
 // generic kernels, whose time is load latency: one scalar load per multiply made them 10-50 times slower.
 template <typename T>
@@ -67,18 +67,18 @@ __device__ __forceinline__ float chunk_dot(const uint4& a, const uint4& b, float
     return acc;
 }
 template <typename T>
-__device__ __forceinline__ float row_dot(const T* __restrict__ a, const T* __restrict__ b, int n, int c0 = 0, int step = 1) {
+__device__ __forceinline__ float row_dot(const T* __restrict__ a, const T* __restrict__ b, int n) {
     const uint4* pa = reinterpret_cast<const uint4*>(a);
     const uint4* pb = reinterpret_cast<const uint4*>(b);
     const int nch = n / (int)(16 / sizeof(T));
     float acc = 0.f;
-    for (int c = c0; c < nch; c += 8 * step) {
+    for (int c = 0; c < nch; c += 8) {
         uint4 x[8], y[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const bool ok = c + u * step < nch;
-            x[u] = ok ? pa[c + u * step] : make_uint4(0, 0, 0, 0);
-            y[u] = ok ? pb[c + u * step] : make_uint4(0, 0, 0, 0);
+            const bool ok = c + u < nch;
+            x[u] = ok ? pa[c + u] : make_uint4(0, 0, 0, 0);
+            y[u] = ok ? pb[c + u] : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) acc = chunk_dot<T>(x[u], y[u], acc);
@@ -116,17 +116,6 @@ __device__ __forceinline__ void request_together(int& v0, int& v1, int& v2, int&
 }
 
 // ---- wave / block reductions ----------------------------------------------------------------
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-    return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, WAVE));
-    return v;
-}
-
 // Reductions over the 16 lanes of a DPP row (lanes 16 i .. 16 i + 15), every lane ends with the result.
 // Four data-parallel-primitive steps inside the vector ALU (no LDS traffic): swap neighbours, swap
 // pairs, mirror inside each half row, mirror the whole row.
@@ -147,6 +136,64 @@ __device__ __forceinline__ float row16_sum(float v) {
     v += dpp_move<0x141>(v);
     v += dpp_move<0x140>(v);
     return v;
+}
+// The four lanes (l, l ^ 16, l ^ 32, l ^ 48): after the swap of halves of two copies the two results hold {own, partner}.
+template <typename F>
+__device__ __forceinline__ float quad_combine(float v, F&& f) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    u2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+#else
+    return v;
+#endif
+}
+// All 64 lanes.  The sum combines lanes 32, 16, 8, 4, 2 and 1 apart, in this order (near-ties of two cosines go by the last bits of the
+// norms): rotations by 8 and 4 inside a row of 16 are what 8 and 4 apart are, once the lanes 8 apart agree.
+__device__ __forceinline__ float wave_sum(float v) {
+    v = quad_combine(v, [](float a, float b) { return a + b; });
+    v += dpp_move<0x128>(v);             // row_ror:8
+    v += dpp_move<0x124>(v);             // row_ror:4
+    v += dpp_move<0x4E>(v);
+    v += dpp_move<0xB1>(v);
+    return v;
+}
+__device__ __forceinline__ float wave_max(float v) { return quad_combine(row16_max(v), [](float a, float b) { return fmaxf(a, b); }); }
+
+// Dot products of a row with `count` rows (at least one) that lie `stride` elements apart, up to 64 of them, by one wave: lane l gets the one
+// with row wave_dots_row(l).  16 lanes to a row, so that a load takes in whole lines; all rows of a pass are requested at once, behind
+// them the row `a`, whose place may be the last thing to be known.  (A row to a lane: every load touches 64 lines.)
+// 64 rows span less than 4 GB (65535 heads of 256 float32 channels at most).
+__device__ __forceinline__ int wave_dots_row(int lane) { return (lane & 15) * 4 + (lane >> 4); }
+template <typename T>
+__device__ __forceinline__ float wave_row_dots(const T* __restrict__ a, const T* __restrict__ rows, size_t stride, int count, int n, int lane) {
+    const int l = lane & 15, g = lane >> 4, nch = n / (int)(16 / sizeof(T));
+    const uint32_t step = (uint32_t)(stride * sizeof(T));
+    const char* base = reinterpret_cast<const char*>(rows);
+    float d[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) d[u] = 0.f;
+    for (int c0 = 0; c0 < nch; c0 += 16) {
+        const uint32_t at = (uint32_t)min(c0 + l, nch - 1) * 16u;
+        uint4 y[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) y[u] = *reinterpret_cast<const uint4*>(base + ((uint32_t)min(u * 4 + g, count - 1) * step + at));
+        const uint4 x = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a) + at);
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const float v = chunk_dot<T>(x, y[u], d[u]);
+            d[u] = c0 + l < nch ? v : d[u];
+        }
+    }
+    float r = 0.f;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+        const float v = row16_sum(d[u]);
+        r = l == u ? v : r;
+    }
+    return r;
 }
 
 #if defined(__HIP_DEVICE_COMPILE__)

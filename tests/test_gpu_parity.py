@@ -61,6 +61,22 @@ def test_f32_generic_case_and_odd_head_size():
     _chain([c], [oracle.keep_count(80, 0.25)], "bf16")
 
 
+@pytest.mark.parametrize("dtype,H,dh,N,k", [
+    ("f32", 2, 4, 66, 1), ("f32", 1, 64, 65, 16), ("f32", 3, 68, 64, 17), ("f32", 2, 256, 257, 64), ("f32", 1, 252, 330, 65), ("f32", 4, 64, 577, 143),
+    ("bf16", 3, 8, 256, 63), ("bf16", 2, 136, 129, 33), ("bf16", 1, 256, 321, 129),
+])
+def test_generic_kernels_sixteen_lanes_to_a_row(dtype, H, dh, N, k):
+    """Generic kernels: keys around the 64 of a wave and the 256 of a turn, rows of 1 to 128 chunks (a row of lanes takes 16 of them, a
+    turn of the cosines 64), kept slots around 16 and 64."""
+    V = N - 6
+    samples = [W.random_case(830 + N, N, H * dh, H, 2, V, 4, dtype=dtype, centres=max(2, k // 3)), W.random_case(831, 7, H * dh, H, 1, 3, 2, dtype=dtype)]
+    _chain(samples, [k, 2], dtype)
+    qkv = [W.random_qkv(832 + N, n, H, dh, dtype) for n in (N, 1)]
+    qkv[0][1][:, H - 1, :] *= 4.0
+    for (q, kk, v), o in zip(qkv, gpu_attend(qkv, dtype)):
+        check_attend(o, q, kk, v, dtype)
+
+
 # ---- tile-edge shapes: counts that sit exactly on, one below and one above the kernels' tile sizes --------
 @pytest.mark.parametrize("P,V,O,D,k", [
     (0, 512, 16, 16, 128),       # keys = one 512-key chunk + deciders, kept = one 128-slot column tile, pruned = 6 x 64
