@@ -665,14 +665,10 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
     const int qrow = qt * 32 + c;
     const bool qvalid = qrow < n;
     bf16x8 qf[KS];
-    {
-        const uint16_t* qp = q + (size_t)(tok0 + (qvalid ? qrow : 0)) * rs + (size_t)h * DH + g * 8;
+    // rows past the end load as zeros here too (under a condition 32 heads of 128, 150 rows 5.9 us, now 5.7; 231 rows 6.44, 6.40; K or V in front 6.6)
+    const __amdgpu_buffer_rsrc_t rq = make_uniform_rsrc(q + (size_t)tok0 * rs + (size_t)h * DH, span);
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-            bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-            qf[kk] = qvalid ? *reinterpret_cast<const bf16x8*>(qp + kk * 16) : z;
-        }
-    }
+    for (int kk = 0; kk < KS; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rq, qrow * row_bytes + g * 16, kk * 32, 0));
     f32x16 ot[DT];
 #pragma unroll
     for (int t = 0; t < DT; ++t)
