@@ -4,7 +4,7 @@
 // S_j = (1/H) sum_h sum_{i in D} softmax_j(scale * q_{i,h} . k_{j,h}), softmax over ALL keys of the
 // sample, written for the visual columns only.  The N x N matrix is never formed: only the |D|
 // decider rows are ever evaluated.  Large decider sets take two sweeps over K (below); small ones keep
-// the D x N x H logits of the first sweep and finish from those (imp_scores_from_logits):
+// the D x N x H logits of the first sweep and finish from those (imp_scores_from_logits; the generic path keeps probabilities):
 //
 //   sweep 1 (stats)   per (head, decider): running max and sum of exp2 over all keys, computed per
 //                     chunk of keys by one workgroup each and combined later in a fixed order
@@ -587,11 +587,9 @@ __global__ __launch_bounds__(256, 2) void imp_stream_bf16(
 // twice as many compute units 5.2.)
 // Unrolled for 1, 4 or 16 (head, decider) rows a thread: rows that a block does not have cost their instructions all the same, in four
 // waves per SIMD (16 for all against these: 64 rows of 208 keys 4.2 -> 2.7 us (float32), of 3773 4.8 -> 3.4, 208 rows of 817 4.6 -> 3.7).
-// GENERIC: the logits of the generic first sweep, whose `part` is one finished log-sum-exp per (head, decider) (144 keys x
-// 4 heads x 16 deciders of 64 float32 channels: 7.5 us when every score's dot products were formed again, 4.3 from the logits).
 constexpr int IMP_KEEP_MAXD = IMP_KEEP_MAXD_WS;
 constexpr int IMP_FL_THREADS = 1024, IMP_FL_GROUPS = IMP_FL_THREADS / 16;
-template <bool GENERIC, int IMP_FL_ROWS>
+template <int IMP_FL_ROWS>
 __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     int H, const int32_t* __restrict__ seq_off, const int32_t* __restrict__ dec_off,
     const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count, const int32_t* __restrict__ score_off,
@@ -623,19 +621,15 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     request(0);
     // the statistics of row t: head t / max_D (exact: (t + 1/2) / max_D is 1/64 or more away from the integers, t below 12288), decider the rest
     const float per_head = __builtin_amdgcn_rcpf((float)max_D);
-    constexpr int NA = GENERIC ? 1 : 8;                     // chunks of keys requested at once
-    float2 a[NA];
+    float2 a[8];                                            // chunks of keys requested at once
     int i = 0;
     const float2* p = nullptr;
     auto statistics = [&](int t) {
         const int h = (int)(((float)t + 0.5f) * per_head);
         i = t - h * max_D;
-        if constexpr (GENERIC) a[0].x = reinterpret_cast<const float*>(part)[(size_t)b * rows + t];
-        else {
-            p = part + ((size_t)(b * H + h) * NCH) * DPAD + i;
+        p = part + ((size_t)(b * H + h) * NCH) * DPAD + i;
 #pragma unroll
-            for (int u = 0; u < NA; ++u) a[u] = p[min(u, NCH - 1) * DPAD];
-        }
+        for (int u = 0; u < 8; ++u) a[u] = p[min(u, NCH - 1) * DPAD];
     };
     const int wave0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x & ~63);
     if (wave0 < rows) statistics(min((int)threadIdx.x, rows - 1));
@@ -643,8 +637,7 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     const int nch = min((N + KC - 1) / KC, NCH);
     for (int t0 = wave0; t0 < rows;) {
         const int t = t0 + ((int)threadIdx.x & 63);
-        float c = a[0].x;
-        if constexpr (!GENERIC) c = imp_lse(a, p, nch, NCH, DPAD);
+        const float c = imp_lse(a, p, nch, NCH, DPAD);
         if (t < rows) c_lds[t] = i < D ? c : INFINITY;
         t0 += IMP_FL_THREADS;
         if (t0 < rows) statistics(min(t0 + ((int)threadIdx.x & 63), rows - 1));
@@ -654,7 +647,7 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     auto add_row = [&](int row, float v) {
         // a row past the sample's deciders was never written: whatever it holds must not reach the sum
         const float c = (row < rows) ? c_lds[row] : INFINITY;
-        acc += (c < INFINITY) ? (GENERIC ? exp2f(v - c) : __builtin_amdgcn_exp2f(v - c)) : 0.f;
+        acc += (c < INFINITY) ? __builtin_amdgcn_exp2f(v - c) : 0.f;
     };
 #pragma unroll
     for (int u = 0; u < IMP_FL_ROWS; ++u) add_row(grp + u * IMP_FL_GROUPS, l[u]);
@@ -707,45 +700,73 @@ __global__ __launch_bounds__(256) void imp_finish_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// generic path: one workgroup per (decider, head) for the stats, which also keeps the logits of a small decider set
-// (scores from those as on the bf16 path); one per 8 visual keys for the scores of larger sets.
+// generic path: one workgroup per (decider, head) for the stats; it has all logits of its row of the softmax and leaves the probabilities
+// of a small decider set, whose scores are then sums over (head, decider) rows; one per 8 visual keys for the scores of larger sets.
 // Plain float arithmetic, any head size up to 256.  Bound by latency: a wave takes 64 keys at a time, 16 lanes to a key (208 keys x 4 heads x
-// 16 deciders of 64 floats 5.0 us with a key to a lane, 3.8 so).
+// 16 deciders of 64 floats 5.0 us with a key to a lane, 3.8 so), and there are waves for up to 1024 keys at once (256 keys at once:
+// 420 keys x 72 rows 5.1 us, now 4.8; 576 x 36 8.2, now 6.9).
 // ---------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void imp_stats_generic(
+template <typename T, int THREADS>
+__global__ __launch_bounds__(THREADS) void imp_stats_generic(
     const T* __restrict__ q, const T* __restrict__ k, int H, int dh, float scale2,
     const int32_t* __restrict__ seq_off, const int32_t* __restrict__ dec_idx, const int32_t* __restrict__ dec_off,
-    int max_D, int NKB, float* __restrict__ logits, float* __restrict__ cws) {
+    int max_D, int NK, float* __restrict__ probs, float* __restrict__ cws) {
     const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     int tok0 = seq_off[b], tok1 = seq_off[b + 1], d0 = dec_off[b], d1 = dec_off[b + 1];
     request_together(tok0, tok1, d0, d1);
-    const int N = tok1 - tok0;
+    const int N = tok1 - tok0, kept = min(N, NK);
     const int D = min(d1 - d0, max_D);
-    if (i >= D) return;
-    __shared__ float2 red[4];
+    float* row = probs + ((size_t)(b * H + h) * max_D + i) * NK;       // if there are any
+    if (i >= D) {                                          // no such decider in this sample: it adds nothing
+        if (probs)
+            for (int j = threadIdx.x; j < kept; j += THREADS) row[j] = 0.f;
+        return;
+    }
+    __shared__ float2 red[THREADS / 64];
     const int pos = min(max(dec_idx[d0 + i], 0), N - 1);
     const T* qr = q + ((size_t)(tok0 + pos) * H + h) * dh;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
-    float m = -INFINITY, z = 0.f;
-    for (int j0 = wave * 64; j0 < N; j0 += 256) {
+    float m = -INFINITY, z = 0.f, first = 0.f;             // first: the logit of this thread's first key (the others wait in `row`)
+    for (int j0 = wave * 64; j0 < N; j0 += THREADS) {
         const int j = j0 + wave_dots_row(lane);
         const float s = wave_row_dots<T>(qr, k + ((size_t)(tok0 + j0) * H + h) * dh, (size_t)H * dh, N - j0, dh, lane) * scale2;
         if (j < N) {
-            if (logits && j < NKB * 16) logits[(((size_t)b * NKB + (j >> 4)) * H * max_D + h * max_D + i) * 16 + (j & 15)] = s;
+            if (j0 < THREADS) first = s;
+            else if (probs && j < kept) row[j] = s;
             lse2_combine(m, z, s, 1.0f);
         }
     }
     const float mw = wave_max(m);
     z = wave_sum(m == -INFINITY ? 0.f : z * exp2f(m - mw));
-    m = mw;
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = make_float2(m, z);
+    if (lane == 0) red[wave] = make_float2(mw, z);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        float2 a = red[0];
-        for (int w = 1; w < 4; ++w) lse2_combine(a.x, a.y, red[w].x, red[w].y);
-        cws[(size_t)(b * H + h) * max_D + i] = a.x + log2f(a.y);
+    float2 a = red[0];
+    for (int w = 1; w < THREADS / 64; ++w) lse2_combine(a.x, a.y, red[w].x, red[w].y);
+    const float c = a.x + log2f(a.y);
+    if (!probs) {
+        if (threadIdx.x == 0) cws[(size_t)(b * H + h) * max_D + i] = c;
+        return;
     }
+    for (int j0 = wave * 64; j0 < kept; j0 += THREADS) {
+        const int j = j0 + wave_dots_row(lane);
+        if (j < kept) row[j] = exp2f((j0 < THREADS ? first : row[j]) - c);
+    }
+}
+
+// Scores from the probabilities: a workgroup has 64 visual keys, a wave a quarter of the rows (375 keys x 72 rows 3.2 us; with every score's
+// dot products formed again 7.5 us for 144 x 64).
+__global__ __launch_bounds__(256) void imp_sum_generic(ScoreSums s, const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_count,
+                                                       const int32_t* __restrict__ score_off, int max_V, float* __restrict__ scores) {
+    const int b = blockIdx.y, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    int tok0 = seq_off[b], tok1 = seq_off[b + 1], vs0 = s.vis_start[b], vc = vis_count[b], s0 = score_off[b];
+    request_together(tok0, tok1, vs0, vc, s0);
+    const int N = tok1 - tok0, vs = min(max(vs0, 0), N), V = min(min(vc, max_V), N - vs);
+    const int j = blockIdx.x * 64 + lane;
+    if ((int)blockIdx.x * 64 >= V) return;
+    __shared__ float part[SUM_PARTS][64];
+    part[wave][lane] = score_sum_part<32>(s, b, vs + min(j, V - 1), wave);
+    __syncthreads();
+    if (wave == 0 && j < V) scores[s0 + j] = score_of_parts(part[0][lane], part[1][lane], part[2][lane], part[3][lane], s.H);
 }
 
 // One workgroup per 8 visual keys: thread = (key, one of 32 groups), the groups take the (head, decider) pairs in turn,
@@ -814,22 +835,13 @@ int d3tom::importance_run(const void* q, const void* k, int dt,
                           int B, const int32_t* seq_off, int H, int dh, float scale,
                           const int32_t* dec_idx, const int32_t* dec_off, int max_D,
                           const int32_t* vis_start, const int32_t* vis_count, const int32_t* score_off,
-                          int max_N, int max_V, float* scores, void* ws, void* stream) {
+                          int max_N, int max_V, float* scores, void* ws, void* stream, ScoreSums* left) {
+    if (left) *left = ScoreSums();
     const ImpWs w = imp_ws_layout(B, max_N, max_V, H, max_D);
     hipStream_t st = (hipStream_t)stream;
     char* wsb = (char*)ws;
     const float scale2 = scale * LOG2E;
     const int rows = H * max_D;
-#define D3TOM_IMP_FROM_LOGITS_ROWS(GENERIC, ROWS, PART)                                                                            \
-    D3TOM_LAUNCH(IMP_SCORES, st, (imp_scores_from_logits<GENERIC, ROWS><<<g2k, IMP_FL_THREADS, (size_t)rows * sizeof(float), st>>>(   \
-        H, seq_off, dec_off, vis_start, vis_count, score_off, max_D, max_V, w.DPAD, w.NCH, w.KC, w.NKB, PART, logits, scores)))
-#define D3TOM_IMP_FROM_LOGITS(GENERIC, PART)                                                  \
-    do {                                                                                      \
-        if (rows <= IMP_FL_GROUPS) D3TOM_IMP_FROM_LOGITS_ROWS(GENERIC, 1, PART);              \
-        else if (rows <= 4 * IMP_FL_GROUPS) D3TOM_IMP_FROM_LOGITS_ROWS(GENERIC, 4, PART);     \
-        else D3TOM_IMP_FROM_LOGITS_ROWS(GENERIC, 16, PART);                                   \
-    } while (0)
-
     if (dt == D3TOM_BF16 && (dh == 128 || dh == 64)) {
         float2* part = (float2*)(wsb + w.part_off);
         float* sp = (float*)(wsb + w.sp_off);
@@ -862,8 +874,13 @@ int d3tom::importance_run(const void* q, const void* k, int dt,
 #undef D3TOM_IMP_STATS
 #undef D3TOM_IMP_STREAM
         if (keep) {
-            const dim3 g2k(ceil_div(max_N, 16), B);
-            D3TOM_IMP_FROM_LOGITS(false, part);
+#define D3TOM_IMP_FROM_LOGITS(ROWS)                                                                                                       \
+    D3TOM_LAUNCH(IMP_SCORES, st, (imp_scores_from_logits<ROWS><<<dim3(ceil_div(max_N, 16), B), IMP_FL_THREADS, (size_t)rows * sizeof(float), st>>>(   \
+        H, seq_off, dec_off, vis_start, vis_count, score_off, max_D, max_V, w.DPAD, w.NCH, w.KC, w.NKB, part, logits, scores)))
+            if (rows <= IMP_FL_GROUPS) D3TOM_IMP_FROM_LOGITS(1);
+            else if (rows <= 4 * IMP_FL_GROUPS) D3TOM_IMP_FROM_LOGITS(4);
+            else D3TOM_IMP_FROM_LOGITS(16);
+#undef D3TOM_IMP_FROM_LOGITS
             return D3TOM_OK;
         }
 #define D3TOM_IMP_SCORES(DHV)                                                                                 \
@@ -876,18 +893,21 @@ int d3tom::importance_run(const void* q, const void* k, int dt,
         return D3TOM_OK;
     }
     float* cws = (float*)(wsb + w.c_off);
-    const bool keep = imp_keeps_logits(H, max_D);
-    float* logits = keep ? (float*)(wsb + w.logit_off) : nullptr;
-    const dim3 g1(max_D, H, B), g2(ceil_div(max_V, IMG_KEYS), B), g2k(ceil_div(max_N, 16), B);
-    if (dt == D3TOM_F32) {
-        D3TOM_LAUNCH(IMP_STATS, st, imp_stats_generic<float><<<g1, 256, 0, st>>>(
-            (const float*)q, (const float*)k, H, dh, scale2, seq_off, dec_idx, dec_off, max_D, w.NKB, logits, cws));
-    } else {
-        D3TOM_LAUNCH(IMP_STATS, st, imp_stats_generic<uint16_t><<<g1, 256, 0, st>>>(
-            (const uint16_t*)q, (const uint16_t*)k, H, dh, scale2, seq_off, dec_idx, dec_off, max_D, w.NKB, logits, cws));
-    }
+    const bool keep = max_D <= IMP_KEEP_MAXD;
+    float* probs = keep ? (float*)(wsb + w.logit_off) : nullptr;
+    const ScoreSums sums = {probs, rows, w.NKB * 16, H, vis_start};
+    const dim3 g1(max_D, H, B), g2(ceil_div(max_V, IMG_KEYS), B);
+#define D3TOM_IMP_GENERIC_OF(T, THREADS)                                                                     \
+    D3TOM_LAUNCH(IMP_STATS, st, (imp_stats_generic<T, THREADS><<<g1, THREADS, 0, st>>>(                          \
+        (const T*)q, (const T*)k, H, dh, scale2, seq_off, dec_idx, dec_off, max_D, sums.NK, probs, cws)))
+#define D3TOM_IMP_GENERIC(T)                                                                                  \
+    do { if (max_N <= 256) D3TOM_IMP_GENERIC_OF(T, 256); else if (max_N <= 512) D3TOM_IMP_GENERIC_OF(T, 512); else D3TOM_IMP_GENERIC_OF(T, 1024); } while (0)
+    if (dt == D3TOM_F32) D3TOM_IMP_GENERIC(float); else D3TOM_IMP_GENERIC(uint16_t);
+#undef D3TOM_IMP_GENERIC
+#undef D3TOM_IMP_GENERIC_OF
     if (keep) {
-        D3TOM_IMP_FROM_LOGITS(true, (const float2*)cws);
+        if (left && topk_takes_sums(rows, max_V)) *left = sums;
+        else D3TOM_LAUNCH(IMP_SCORES, st, imp_sum_generic<<<dim3(ceil_div(max_V, 64), B), 256, 0, st>>>(sums, seq_off, vis_count, score_off, max_V, scores));
     } else if (dt == D3TOM_F32) {
         D3TOM_LAUNCH(IMP_SCORES, st, imp_scores_generic<float><<<g2, 256, 0, st>>>(
             (const float*)q, (const float*)k, H, dh, scale2, seq_off, dec_idx, dec_off, vis_start, vis_count, score_off,
@@ -897,8 +917,6 @@ int d3tom::importance_run(const void* q, const void* k, int dt,
             (const uint16_t*)q, (const uint16_t*)k, H, dh, scale2, seq_off, dec_idx, dec_off, vis_start, vis_count,
             score_off, max_D, max_V, cws, scores));
     }
-#undef D3TOM_IMP_FROM_LOGITS
-#undef D3TOM_IMP_FROM_LOGITS_ROWS
     return D3TOM_OK;
 }
 

@@ -12,10 +12,40 @@ int importance_check(const void* q, const void* k, int dt, int B, const int32_t*
                      const int32_t* dec_idx, const int32_t* dec_off, int min_D, int max_D,
                      const int32_t* vis_start, const int32_t* vis_count, const int32_t* score_off,
                      int max_N, int max_V, const float* scores);
+// Probabilities of the generic path's small decider sets in the importance workspace, [B][rows][NK]: a visual token's score is the
+// sum of its column over the (head, decider) rows, divided by the heads.  In SUM_PARTS parts of consecutive rows, wherever it is formed.
+struct ScoreSums {
+    const float* probs = nullptr;            // none: there is nothing to sum
+    int rows = 0, NK = 0, H = 0;
+    const int32_t* vis_start = nullptr;
+};
+constexpr int SUM_PARTS = 4;
+template <int R>                             // rows requested at once
+__device__ __forceinline__ float score_sum_part(const ScoreSums& s, int b, int token, int part) {
+    const int per = (s.rows + SUM_PARTS - 1) / SUM_PARTS, r1 = min(s.rows, (part + 1) * per);
+    const float* p = s.probs + (size_t)b * s.rows * s.NK + min(token, s.NK - 1);
+    float acc = 0.f;
+    for (int r = part * per; r < r1; r += R) {
+        float a[R];
+#pragma unroll
+        for (int u = 0; u < R; ++u) a[u] = p[(size_t)min(r + u, r1 - 1) * s.NK];
+#pragma unroll
+        for (int u = 0; u < R; ++u) acc += r + u < r1 ? a[u] : 0.f;
+    }
+    return acc;
+}
+__device__ __forceinline__ float score_of_parts(float p0, float p1, float p2, float p3, int H) { return ((p0 + p1) + (p2 + p3)) / (float)H; }
+// Whether the selection of the one-call merge layer forms such scores itself, up to 32 rows of a key to a thread: a launch less, which counts
+// on the host too (float32 layers of 48 .. 205 visual tokens, 4 heads, 5 .. 26 deciders 24.0 .. 25.5 us with a launch for the scores, 21.6 .. 24.7 so;
+// with 375 visual tokens, in two turns, 26.1 and 27.5).
+constexpr int SUM_MAX_V = 256, SUM_MAX_ROWS = 128;
+inline bool topk_takes_sums(int rows, int max_V) { return rows <= SUM_MAX_ROWS && max_V <= SUM_MAX_V; }
+
+// left, if given: sums that the selection is to form (their probabilities, or none: the scores are written)
 int importance_run(const void* q, const void* k, int dt, int B, const int32_t* seq_off, int H, int dh, float scale,
                    const int32_t* dec_idx, const int32_t* dec_off, int max_D,
                    const int32_t* vis_start, const int32_t* vis_count, const int32_t* score_off,
-                   int max_N, int max_V, float* scores, void* ws, void* stream);
+                   int max_N, int max_V, float* scores, void* ws, void* stream, ScoreSums* left = nullptr);
 size_t importance_ws_bytes(int B, int max_N, int max_V, int H, int dh, int max_D);
 
 // Sum of squares of one row of d elements (bf16 or float32, 16-byte aligned, d a multiple of the elements per 16
@@ -122,10 +152,11 @@ __device__ __forceinline__ void stream_row_norms(const MergePrep& prep, int max_
 
 // d3tom_select_topk; with a usable prep the launch prepares the merge and *prepared says so; with keep_ratio != nullptr the kept counts are computed on the device from the ratios and
 // written, with their prefix sums and the output row offsets, to keep_k / kept_off / out_off
-int topk_run(const float* scores, int B, const int32_t* score_off, const int32_t* keep_k, const int32_t* kept_off, int max_V,
+// sums: scores that are left to form; they are written to `scores` on the way
+int topk_run(float* scores, int B, const int32_t* score_off, const int32_t* keep_k, const int32_t* kept_off, int max_V,
              int32_t* kept_idx, int32_t* slot_of, const double* keep_ratio, const int32_t* seq_off, int32_t* keep_k_out,
              int32_t* kept_off_out, int32_t* out_off_out, void* stream, const MergePrep* prep = nullptr,
-             bool* prepared = nullptr);
+             bool* prepared = nullptr, const ScoreSums& sums = ScoreSums());
 
 // d3tom_merge / d3tom_merge_kv; prepared: the selection launch has filled the workspace as MergePrep describes;
 // out_rows_hint: output rows per sample to expect when max_out is only a loose bound (a sample may have more)

@@ -45,8 +45,9 @@ extern "C" int d3tom_merge_layer(const void* q, const void* k, const void* x, co
     const LayerWs w = layer_ws_layout(B, max_N, max_V, H, dh, max_D);
     if (ws_bytes < w.total || (((uintptr_t)ws) & 255u)) return D3TOM_ERR_WORKSPACE_TOO_SMALL;
     char* base = (char*)ws;
+    ScoreSums sums;
     rc = importance_run(q, k, dt, B, seq_off, H, dh, scale, dec_idx, dec_off, max_D, vis_start, vis_count, vis_off, max_N,
-                        max_V, scores, base + w.imp, stream);
+                        max_V, scores, base + w.imp, stream, &sums);
     if (rc != D3TOM_OK) return rc;
     // The selection leaves most of the chip idle: its launch carries workgroups that stream the visual rows of the
     // similarity features and leave their norms, so that the rows are in the memory-side cache when the cosine kernel
@@ -62,7 +63,7 @@ extern "C" int d3tom_merge_layer(const void* q, const void* k, const void* x, co
     merge_prep_targets(base + w.merge, B, max_V, &prep);
     bool prepared = false;
     rc = topk_run(scores, B, vis_off, nullptr, nullptr, max_V, kept_idx, (int32_t*)(base + w.slot), keep_ratio, seq_off, keep_k,
-                  kept_off, out_off, stream, &prep, &prepared);
+                  kept_off, out_off, stream, &prep, &prepared, sums);
     if (rc != D3TOM_OK) return rc;
     // launch sizes from the host-known bounds on the kept counts; workgroups beyond a sample's real sizes exit at once
     return merge_run(x, y, nullptr, nullptr, sim, d, d_sim, dt, B, seq_off, vis_start, vis_count, vis_off, kept_idx, kept_off,

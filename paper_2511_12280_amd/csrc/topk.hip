@@ -69,12 +69,12 @@ __device__ __forceinline__ uint32_t wave_min_u(uint32_t v) {
 }
 #endif
 
-template <int TOPK_PER>                          // keys per thread at most
+template <int TOPK_PER, bool SUMS>               // TOPK_PER: keys per thread at most.  SUMS: the scores are formed here
 __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
-    const float* __restrict__ scores, const int32_t* __restrict__ score_off, const int32_t* __restrict__ keep_k,
+    float* __restrict__ scores, const int32_t* __restrict__ score_off, const int32_t* __restrict__ keep_k,
     const int32_t* __restrict__ kept_off, int max_V, int32_t* __restrict__ kept_idx, int32_t* __restrict__ slot_of,
     const double* __restrict__ keep_ratio, const int32_t* __restrict__ seq_off, int32_t* __restrict__ keep_k_out,
-    int32_t* __restrict__ kept_off_out, int32_t* __restrict__ out_off_out, MergePrep prep) {
+    int32_t* __restrict__ kept_off_out, int32_t* __restrict__ out_off_out, MergePrep prep, ScoreSums sums) {
 #if defined(__HIP_DEVICE_COMPILE__)
     if (blockIdx.y > 0) {
         // streaming workgroups: norms of the sample's visual rows
@@ -98,12 +98,19 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
     // thread t holds keys t, t + 1024, ...
     uint32_t key[TOPK_PER];
     uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-    const __amdgpu_buffer_rsrc_t mine = make_uniform_rsrc(scores + s0, (uint32_t)max(V, 0) * 4u);       // beyond the sample: 0, not fetched
+    static_assert(!SUMS || TOPK_PER == 1, "");
+    __shared__ float part[SUMS ? SUM_PARTS : 1][SUMS ? SUM_MAX_V : 1];
+    if constexpr (SUMS) {
+        const int vs = max(sums.vis_start[b], 0);
+        for (int j = tid & 255; j < V; j += 256) part[wave >> 2][j] = score_sum_part<16>(sums, b, vs + j, wave >> 2);
+    } else {
+        const __amdgpu_buffer_rsrc_t mine = make_uniform_rsrc(scores + s0, (uint32_t)max(V, 0) * 4u);       // beyond the sample: 0, not fetched
 #pragma unroll
-    for (int c = 0; c < TOPK_PER && c < 4; ++c) key[c] = __builtin_amdgcn_raw_buffer_load_b32(mine, (c * TOPK_THREADS + tid) * 4, 0, 0);
-    if (V > 4 * TOPK_THREADS) {                   // requests beyond the sample take their turn in the load path too
+        for (int c = 0; c < TOPK_PER && c < 4; ++c) key[c] = __builtin_amdgcn_raw_buffer_load_b32(mine, (c * TOPK_THREADS + tid) * 4, 0, 0);
+        if (V > 4 * TOPK_THREADS) {                   // requests beyond the sample take their turn in the load path too
 #pragma unroll
-        for (int c = 4; c < TOPK_PER; ++c) key[c] = __builtin_amdgcn_raw_buffer_load_b32(mine, (c * TOPK_THREADS + tid) * 4, 0, 0);
+            for (int c = 4; c < TOPK_PER; ++c) key[c] = __builtin_amdgcn_raw_buffer_load_b32(mine, (c * TOPK_THREADS + tid) * 4, 0, 0);
+        }
     }
     if (keep_ratio && wave == 15) {
         // kept counts from the ratios, on the device: this sample's count, and the prefix sums over the samples
@@ -130,6 +137,14 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
     }
     for (int t = tid; t < TOPK_BINS; t += TOPK_THREADS) hist[t] = 0;
     if (tid == 0) sel[3] = 0;
+    if constexpr (SUMS) {
+        __syncthreads();
+        if (tid < V) {
+            const float v = score_of_parts(part[0][tid], part[1][tid], part[2][tid], part[3][tid], sums.H);
+            scores[s0 + tid] = v;
+            key[0] = __float_as_uint(v);
+        }
+    }
 #pragma unroll
     for (int c = 0; c < TOPK_PER; ++c) {
         if (c * TOPK_THREADS >= V) break;
@@ -293,10 +308,10 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
 
 using namespace d3tom;
 
-int d3tom::topk_run(const float* scores, int B, const int32_t* score_off, const int32_t* keep_k, const int32_t* kept_off,
+int d3tom::topk_run(float* scores, int B, const int32_t* score_off, const int32_t* keep_k, const int32_t* kept_off,
                     int max_V, int32_t* kept_idx, int32_t* slot_of, const double* keep_ratio, const int32_t* seq_off,
                     int32_t* keep_k_out, int32_t* kept_off_out, int32_t* out_off_out, void* stream, const MergePrep* prep_in,
-                    bool* prepared) {
+                    bool* prepared, const ScoreSums& sums) {
     if (prepared) *prepared = false;
     if (!scores || !score_off || !kept_idx || !slot_of) return D3TOM_ERR_INVALID_ARG;
     if (keep_ratio ? (!seq_off || !keep_k_out || !kept_off_out || !out_off_out) : (!keep_k || !kept_off)) return D3TOM_ERR_INVALID_ARG;
@@ -306,12 +321,13 @@ int d3tom::topk_run(const float* scores, int B, const int32_t* score_off, const 
     const bool streaming = merge_prep_usable(prep_in, B, max_V, seq_off);
     const MergePrep prep = streaming ? *prep_in : MergePrep();
     const int extra = streaming ? (B >= TOPK_STREAM_WGS ? 1 : TOPK_STREAM_WGS / B) : 0;
-#define D3TOM_SELECT(PER)                                                                                       \
-    D3TOM_LAUNCH(TOPK_SELECT, st, (topk_select_kernel<PER><<<dim3(B, 1 + extra), TOPK_THREADS, 0, st>>>(           \
-        scores, score_off, keep_k, kept_off, max_V, kept_idx, slot_of, keep_ratio, seq_off, keep_k_out, kept_off_out, out_off_out, prep)))
-    if (max_V <= TOPK_THREADS) D3TOM_SELECT(1);
-    else if (max_V <= 4 * TOPK_THREADS) D3TOM_SELECT(4);
-    else D3TOM_SELECT(D3TOM_MAX_VISUAL / TOPK_THREADS);
+#define D3TOM_SELECT(PER, SUMS)                                                                                 \
+    D3TOM_LAUNCH(TOPK_SELECT, st, (topk_select_kernel<PER, SUMS><<<dim3(B, 1 + extra), TOPK_THREADS, 0, st>>>(           \
+        scores, score_off, keep_k, kept_off, max_V, kept_idx, slot_of, keep_ratio, seq_off, keep_k_out, kept_off_out, out_off_out, prep, sums)))
+    if (sums.probs) D3TOM_SELECT(1, true);
+    else if (max_V <= TOPK_THREADS) D3TOM_SELECT(1, false);
+    else if (max_V <= 4 * TOPK_THREADS) D3TOM_SELECT(4, false);
+    else D3TOM_SELECT(D3TOM_MAX_VISUAL / TOPK_THREADS, false);
 #undef D3TOM_SELECT
     if (prepared) *prepared = streaming;
     return D3TOM_OK;
@@ -322,6 +338,6 @@ extern "C" int d3tom_select_topk(const float* scores, int B, const int32_t* scor
                                  int32_t* kept_idx, int32_t* slot_of,
                                  void* ws, size_t ws_bytes, void* stream) {
     (void)ws; (void)ws_bytes;
-    return topk_run(scores, B, score_off, keep_k, kept_off, max_V, kept_idx, slot_of, nullptr, nullptr, nullptr, nullptr,
+    return topk_run(const_cast<float*>(scores), B, score_off, keep_k, kept_off, max_V, kept_idx, slot_of, nullptr, nullptr, nullptr, nullptr,
                     nullptr, stream);
 }

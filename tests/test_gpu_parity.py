@@ -640,6 +640,26 @@ def test_merge_slices_of_the_contraction(d, shapes):
         check_merge({key: out[key][b] for key in out}, s["x"], s["vis_start"], s["V"], kept[b], "bf16")
 
 
+@pytest.mark.parametrize("dtype,H,dh,V,D", [
+    ("f32", 4, 32, 255, 32), ("f32", 4, 64, 256, 16), ("f32", 4, 32, 257, 16), ("f32", 1, 64, 1, 1), ("f32", 3, 36, 200, 30), ("f32", 43, 4, 100, 3),
+    ("f32", 3, 32, 90, 33), ("f32", 1, 64, 1030, 3), ("f32", 2, 32, 520, 20), ("bf16", 5, 40, 130, 24), ("bf16", 2, 136, 700, 9),
+])
+def test_importance_generic_scores_from_probabilities(dtype, H, dh, V, D):
+    """Generic kernels: (head, decider) rows around 16, 64 and 128, decider counts around 32, visual tokens around 64 and the 256 whose scores the
+    one call's selection forms, tokens around the 256, 512 and 1024 of a workgroup.  A second sample has fewer deciders and tokens.  Against
+    the oracle, and the one call against the separate calls bit for bit."""
+    samples = [W.random_case(850 + V, V + D + 3, H * dh, H, 1, V, D, dtype=dtype, centres=max(2, V // 8)),
+               W.random_case(851, 12, H * dh, H, 3, 6, 2 if D > 1 else 1, dtype=dtype)]
+    keeps = [oracle.keep_count(s["V"], 0.3) for s in samples]
+    step, S, kept, mout, _ = _chain(samples, keeps, dtype)
+    S1, kept1, m1 = step.merge_layer([0.3, 0.3])
+    for b in range(2):
+        np.testing.assert_array_equal(S1[b], S[b])
+        np.testing.assert_array_equal(kept1[b], kept[b])
+        for key in m1:
+            np.testing.assert_array_equal(m1[key][b], mout[key][b])
+
+
 @pytest.mark.parametrize("dtype,d,H", [("bf16", 512, 4), ("bf16", 4096, 32), ("f32", 96, 2), ("f32", 2048, 16)])
 def test_merge_layer_one_call_with_more_rows_than_expected(dtype, d, H):
     """Samples with more output rows than the longest one without the longest visual part has: their workgroups take several rows (a merged one,
