@@ -12,7 +12,10 @@
 // histogram per wave and keys in LDS took about 25: 8.0 us instead of 5.7 at 729 keys, 13.1 instead of 9.9 at 16 x 2304.)  Between them
 // exchanges and sums stay in the vector ALU, and the members are ranked sixteen lanes to each (729 keys 5.4 -> 4.4 us, 16 x 2304 8.6 -> 7.8).
 // A kernel of a few us also pays for the code that it fetches: unrolled for 1, 4 or 16 keys a thread it is 7, 12 or 32 KB (the last one for
-// all sizes against these: 144 keys 4.8 -> 4.2 us, 729 4.6 -> 3.9, 1024 beside streamed rows 6.0 -> 5.0, 3645 8.4 -> 7.5).
+// all sizes against these: 144 keys 4.8 -> 4.2 us, 729 4.6 -> 3.9, 1024 beside streamed rows 6.0 -> 5.0, 3645 8.4 -> 7.5).  And with 16 waves
+// on four SIMDs every instruction that all of them execute costs 20 clocks: what the waves have to tell each other is combined by the lanes of
+// a row, waves without members skip the ranking, bins are found with one comparison (144 keys 3.7 -> 3.4, 1024 4.1 -> 3.6, 3645 6.4 -> 5.3; with 4 or 8
+// waves that have four or two keys a thread 1024 keys 5.4 and 4.4).
 //
 // The selection is a chain of short dependent passes on one compute unit per sample.  Called from the one-call
 // merge layer, the launch carries further workgroups (blockIdx.y > 0) that do not select anything: one wave per
@@ -56,12 +59,16 @@ __device__ __forceinline__ int row16_sum_i(int v) {
     return v;
 }
 __device__ __forceinline__ int wave_total(int v) { return __builtin_amdgcn_readlane(wave_incl_scan(v), 63); }
-__device__ __forceinline__ uint32_t wave_min_u(uint32_t v) {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t row16_min_u(uint32_t v) {
     v = min(v, (uint32_t)dpp_move_i<0xB1>((int)v));
     v = min(v, (uint32_t)dpp_move_i<0x4E>((int)v));
     v = min(v, (uint32_t)dpp_move_i<0x141>((int)v));
     v = min(v, (uint32_t)dpp_move_i<0x140>((int)v));
+    return v;
+}
+__device__ __forceinline__ uint32_t wave_min_u(uint32_t v) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    v = row16_min_u(v);
     u2 r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
     v = min(r[0], r[1]);
     r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
@@ -158,28 +165,28 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
     if (lane == 0) { wrange[wave] = kmin; wrange[16 + wave] = kmax; }
     __syncthreads();
     if (V <= 0) return;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) { kmin = min(kmin, wrange[w]); kmax = max(kmax, wrange[16 + w]); }
+    kmin = row16_min_u(wrange[lane & 15]);        // (16 waves' values by the lanes of a row: a loop over them is 32 instructions in every wave)
+    kmax = ~row16_min_u(~wrange[16 + (lane & 15)]);
     int remaining = keep_ratio ? plan[0] : min(max(keep_k[b], 1), V);      // rank of the threshold among the keys in [lo, hi]
-    const int k0 = keep_ratio ? plan[1] : kept_off[b];
+    const int k0 = keep_ratio ? plan[1] : kept_off[b], kept_count = remaining;
 
     uint32_t lo = kmin, hi = kmax;
     int members = V;
+    uint32_t range;
     for (;;) {                                    // one turn, unless a bin holds more than TOPK_CAND members
-        const uint32_t range = hi - lo;
+        range = hi - lo;
         const int shift = (range < TOPK_BINS) ? 0 : 21 - __clz(range);        // range >> shift < 2048
 #pragma unroll
         for (int c = 0; c < TOPK_PER; ++c) {
             if (c * TOPK_THREADS >= V) break;
-            const bool match = (c * TOPK_THREADS + tid < V) && key[c] >= lo && key[c] <= hi;
-            const int bin = match ? (int)((key[c] - lo) >> shift) : 0;
-            const unsigned long long mm = __builtin_amdgcn_ballot_w64(match);
-            if (mm) {
+            const uint32_t above = key[c] - lo;                               // beyond the range if it is below lo, too
+            if (c * TOPK_THREADS + tid < V && above <= range) {
                 // a whole wave in one bin would serialise on one LDS address: add it once instead
-                const int first = __ffsll((long long)mm) - 1;
-                const int bin0 = __builtin_amdgcn_readlane(bin, first);
-                if (__builtin_amdgcn_ballot_w64(match && bin == bin0) == mm) { if (lane == first) atomicAdd(&hist[bin0], __popcll(mm)); }
-                else if (match) atomicAdd(&hist[bin], 1);
+                const int bin = (int)(above >> shift);
+                const uint64_t here = __builtin_amdgcn_ballot_w64(true);
+                if (__builtin_amdgcn_ballot_w64(bin == __builtin_amdgcn_readfirstlane(bin)) == here) {
+                    if (lane == __builtin_ctzll(here)) atomicAdd(&hist[bin], __popcll(here));
+                } else atomicAdd(&hist[bin], 1);
             }
         }
         __syncthreads();
@@ -188,9 +195,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
         const int inc = wave_incl_scan(h0 + h1);
         if (lane == 63) wsum[wave] = inc;
         __syncthreads();
-        int before = inc - h0 - h1;
-#pragma unroll
-        for (int w = 0; w < 16; ++w) before += (w < wave) ? wsum[w] : 0;
+        const int before = inc - h0 - h1 + row16_sum_i((lane & 15) < wave ? wsum[lane & 15] : 0);
         if (before < remaining && remaining <= before + h0) {
             sel[0] = TOPK_BINS - 1 - 2 * tid; sel[1] = remaining - before; sel[2] = h0;
         } else if (before + h0 < remaining && remaining <= before + h0 + h1) {
@@ -199,6 +204,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
         __syncthreads();
         lo += (uint32_t)sel[0] << shift;
         hi = min(hi, lo + (uint32_t)((1u << shift) - 1u));
+        range = hi - lo;
         remaining = sel[1];
         members = sel[2];
         if (TOPK_PER == 1 || members <= TOPK_CAND || shift == 0) break;       // (at most 1024 keys)
@@ -211,21 +217,22 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
         for (int c = 0; c < TOPK_PER; ++c) {
             if (c * TOPK_THREADS >= V) break;
             const int j = c * TOPK_THREADS + tid;
-            if (j < V && key[c] >= lo && key[c] <= hi) cand[atomicAdd(&sel[3], 1)] = make_uint2(key[c], (uint32_t)j);
+            if (j < V && key[c] - lo <= range) cand[atomicAdd(&sel[3], 1)] = make_uint2(key[c], (uint32_t)j);
         }
         __syncthreads();
         if (members <= TOPK_THREADS / 16) {
-            // sixteen lanes to a member (one to a member: a chain of that many trips to LDS)
-            const int c = tid >> 4;
-            const uint2 me = cand[min(c, members - 1)];
-            int rank = 0;
-#pragma unroll
-            for (int u = 0; u < TOPK_THREADS / 256; ++u) {
-                const int t = u * 16 + (tid & 15);
-                const uint2 o = cand[min(t, members - 1)];
-                rank += (t < members) && ((o.x > me.x) || (o.x == me.x && o.y < me.y));
+            // sixteen lanes to a member (one to a member: a chain of that many trips to LDS); a wave has four members, most waves none
+            if (wave * 4 < members) {
+                const int c = tid >> 4;
+                const uint2 me = cand[min(c, members - 1)];
+                int rank = 0;
+                for (int t0 = 0; t0 < members; t0 += 16) {
+                    const int t = t0 + (tid & 15);
+                    const uint2 o = cand[min(t, members - 1)];
+                    rank += (t < members) && ((o.x > me.x) || (o.x == me.x && o.y < me.y));
+                }
+                if (row16_sum_i(rank) == remaining - 1 && c < members) { thr_s[0] = me.x; thr_s[1] = me.y; }
             }
-            if (row16_sum_i(rank) == remaining - 1 && c < members) { thr_s[0] = me.x; thr_s[1] = me.y; }
         } else if (tid < members) {
             const uint2 me = cand[tid];
             int rank = 0;
@@ -273,6 +280,17 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
         if (lane == 0) wcnt[c * 16 + wave] = __popcll(m);
     }
     __syncthreads();
+    // Where a thread has several keys the stores go through buffers, those that a key does not take part in and those of keys beyond the sample
+    // to nowhere: fewer instructions a key, which are what several keys cost (3645 keys 6.2 -> 5.8 us; with one key a thread 4.0 -> 4.2).
+    constexpr bool BUFFERS = TOPK_PER > 1;
+    constexpr uint32_t NOWHERE = 0x80000000u;
+    __amdgpu_buffer_rsrc_t slots, list, entries, others;
+    if constexpr (BUFFERS) {
+        slots = make_uniform_rsrc(slot_of + s0, (uint32_t)V * 4u);
+        list = make_uniform_rsrc(kept_idx + k0, (uint32_t)kept_count * 4u);
+        entries = make_uniform_rsrc(prep.table + (size_t)b * prep.VP, prep.table ? (uint32_t)V * 8u : 0u);
+        others = make_uniform_rsrc(prep.pruned + (size_t)b * max_V, prep.table ? (uint32_t)V * 4u : 0u);
+    }
     // kept keys in front of each run of 64: four chunks (64 runs, one per lane) at a time
     int base = 0;
 #pragma unroll
@@ -285,14 +303,23 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_select_kernel(
         for (int u = 0; u < 4; ++u) {
             const int c = c4 + u;
             if (c >= TOPK_PER || c * TOPK_THREADS >= V) break;
+            const int j = c * TOPK_THREADS + tid;
             const bool keep = kept(c);
             const unsigned long long m = __builtin_amdgcn_ballot_w64(keep);
             const int slot = base + __builtin_amdgcn_readlane(exc, u * 16 + wave) + __popcll(m & ((1ull << lane) - 1ull));
-            const int j = c * TOPK_THREADS + tid;
-            if (j < V) {
+            // slot = kept tokens in front of j: a pruned token sits at position j - slot of the ascending pruned list
+            if constexpr (BUFFERS) {
+                __builtin_amdgcn_raw_buffer_store_b32((uint32_t)(keep ? slot : -1), slots, j * 4, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b32((uint32_t)j, list, keep ? (uint32_t)slot * 4u : NOWHERE, 0, 0);
+                if (prep.table) {
+                    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+                    const u2 entry = {keep ? 0xFFFFFFFFu - (uint32_t)slot : 0u, keep ? 0xFFFFFFFFu : 0u};    // table_entry_kept(slot) or nothing yet
+                    __builtin_amdgcn_raw_buffer_store_b64(entry, entries, j * 8, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b32((uint32_t)j, others, keep || j >= V ? NOWHERE : (uint32_t)(j - slot) * 4u, 0, 0);
+                }
+            } else if (j < V) {
                 slot_of[s0 + j] = keep ? slot : -1;
                 if (prep.table) {
-                    // slot = kept tokens in front of j: a pruned token sits at position j - slot of the ascending pruned list
                     prep.table[(size_t)b * prep.VP + j] = keep ? table_entry_kept(slot) : (table_t)0;
                     if (!keep) prep.pruned[(size_t)b * max_V + (j - slot)] = j;
                 }
