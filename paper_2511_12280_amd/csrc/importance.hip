@@ -176,17 +176,25 @@ __device__ __forceinline__ void imp_for_blocks(const char* lds, int nblk, int r,
 }
 
 // log2-sum-exp2 of a decider row from the statistics of its nch chunks of keys (of which `first` has up to eight), summed around the
-// common maximum of eight chunks at a time, in ascending order
+// common maximum of eight chunks at a time, in ascending order.  LEAVE: a branch at every chunk instead of a selection (for 16 waves that have
+// nothing else to do; with keys under way it costs 0.4 us).
+template <bool LEAVE>
 __device__ __forceinline__ float imp_lse(float2 (&first)[8], const float2* p, int nch, int NCH, int DPAD) {
     float m = -INFINITY, z = 0.f;
     for (int c0 = 0;;) {
         float mn = m;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) mn = fmaxf(mn, c0 + u < nch ? first[u].x : -INFINITY);
+        for (int u = 0; u < 8; ++u) {
+            if (LEAVE && c0 + u >= nch) break;               // uniform
+            mn = fmaxf(mn, c0 + u < nch ? first[u].x : -INFINITY);
+        }
         const float ref = (mn == -INFINITY) ? 0.f : mn;      // nothing but empty chunks so far
         z *= __builtin_amdgcn_exp2f(m - ref);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) z += c0 + u < nch ? first[u].y * __builtin_amdgcn_exp2f(first[u].x - ref) : 0.f;
+        for (int u = 0; u < 8; ++u) {
+            if (LEAVE && c0 + u >= nch) break;
+            z += c0 + u < nch ? first[u].y * __builtin_amdgcn_exp2f(first[u].x - ref) : 0.f;
+        }
         m = mn;
         c0 += 8;
         if (c0 >= nch) break;
@@ -333,7 +341,7 @@ __global__ __launch_bounds__(256, 4) void imp_scores_bf16(
     if (wave * 64 < nblk * 16) {
         // log2-sum-exp2 of every decider row of this head, key chunks combined in ascending order
         const int nch = (N + KC - 1) / KC;
-        const float c = imp_lse(a, p, nch, NCH, DPAD);
+        const float c = imp_lse<false>(a, p, nch, NCH, DPAD);
         if (tid < nblk * 16) c_lds[tid] = tid < D ? c : INFINITY;       // padded rows contribute exp2(-inf) = 0
     }
 #pragma unroll
@@ -583,7 +591,8 @@ __global__ __launch_bounds__(256, 2) void imp_stream_bf16(
 // third launch, K fetched once).
 // Bound by the chain request -> statistics -> exponentials -> reduction, so it has 16 waves: every thread holds one or two
 // (head, decider) rows of the statistics and at most 16 logits at 32 heads x 32 deciders, all requested at once.  (Statistics behind the
-// logits and offsets, each chunk rescaling the sum before it: 1024 rows of 1152 keys 5.6 us, now 5.0; 208 of 817 3.7, 3.3.  Blocks of 8 keys on
+// logits and offsets, each chunk rescaling the sum before it: 1024 rows of 1152 keys 5.6 us, then 5.0, and 4.6 without conditions for rows
+// that every sample has; 208 of 817 3.7, 3.3, 3.2.  Blocks of 8 keys on
 // twice as many compute units 5.2.)
 // Unrolled for 1, 4 or 16 (head, decider) rows a thread: rows that a block does not have cost their instructions all the same, in four
 // waves per SIMD (16 for all against these: 64 rows of 208 keys 4.2 -> 2.7 us (float32), of 3773 4.8 -> 3.4, 208 rows of 817 4.6 -> 3.7).
@@ -604,7 +613,9 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     const int vs = min(max(vs0, 0), N);
     const int V = min(min(vc, max_V), N - vs);
     const int key0 = kb * 16;
-    extern __shared__ float c_lds[];                    // [H][max_D] log2-sum-exp2, +inf for rows past the sample's deciders
+    constexpr int PASS = IMP_FL_ROWS * IMP_FL_GROUPS;   // rows of a pass
+    // log2-sum-exp2, +inf for rows past the sample's deciders and the block's rows; the rows of a thread side by side
+    extern __shared__ __attribute__((aligned(16))) float c_lds[];
     __shared__ float red[IMP_FL_THREADS / 64][16];
     // thread (key = t % 16, group = t / 16) takes rows group, group + 64, ... of the block's H x max_D logit rows: 64
     // consecutive rows are 4 KB in one piece.  They, the statistics and the sample's offsets are requested together (they come from another
@@ -616,7 +627,7 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     auto request = [&](int r0) {
 #pragma unroll
         for (int u = 0; u < IMP_FL_ROWS; ++u)
-            l[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(lb, (uint32_t)((r0 + grp + u * IMP_FL_GROUPS) * 16 + key) * 4u, 0, 0));
+            l[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(lb, threadIdx.x * 4u, (uint32_t)(r0 + u * IMP_FL_GROUPS) * 64u, 0));
     };
     request(0);
     // the statistics of row t: head t / max_D (exact: (t + 1/2) / max_D is 1/64 or more away from the integers, t below 12288), decider the rest
@@ -635,29 +646,39 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     if (wave0 < rows) statistics(min((int)threadIdx.x, rows - 1));
     if (D <= 0 || key0 >= vs + V || key0 + 16 <= vs || key0 >= N) return;
     const int nch = min((N + KC - 1) / KC, NCH);
-    for (int t0 = wave0; t0 < rows;) {
+    const int padded = (rows + PASS - 1) / PASS * PASS;
+    for (int t0 = wave0; t0 < padded;) {
         const int t = t0 + ((int)threadIdx.x & 63);
-        const float c = imp_lse(a, p, nch, NCH, DPAD);
-        if (t < rows) c_lds[t] = i < D ? c : INFINITY;
+        float c = INFINITY;
+        if (t0 < rows) {
+            const float lse = imp_lse<true>(a, p, nch, NCH, DPAD);
+            c = t < rows && i < D ? lse : INFINITY;
+        }
+        c_lds[t / PASS * PASS + (t % IMP_FL_GROUPS) * IMP_FL_ROWS + t % PASS / IMP_FL_GROUPS] = c;
         t0 += IMP_FL_THREADS;
         if (t0 < rows) statistics(min(t0 + ((int)threadIdx.x & 63), rows - 1));
     }
     __syncthreads();
     float acc = 0.f;
-    auto add_row = [&](int row, float v) {
-        // a row past the sample's deciders was never written: whatever it holds must not reach the sum
-        const float c = (row < rows) ? c_lds[row] : INFINITY;
-        acc += (c < INFINITY) ? __builtin_amdgcn_exp2f(v - c) : 0.f;
+    // (16 waves on four SIMDs: an instruction for every row of every thread is 20 clocks x 16.  Most samples have all of the launch's rows.)
+    const bool whole = D == max_D && rows == padded;
+    auto add_rows = [&](int r0) {
+        const float* c = c_lds + r0 + grp * IMP_FL_ROWS;
+        if (whole) {
+#pragma unroll
+            for (int u = 0; u < IMP_FL_ROWS; ++u) acc += __builtin_amdgcn_exp2f(l[u] - c[u]);
+        } else {
+            // a row past the sample's deciders was never written: whatever it holds must not reach the sum
+#pragma unroll
+            for (int u = 0; u < IMP_FL_ROWS; ++u) acc += (c[u] < INFINITY) ? __builtin_amdgcn_exp2f(l[u] - c[u]) : 0.f;
+        }
     };
-#pragma unroll
-    for (int u = 0; u < IMP_FL_ROWS; ++u) add_row(grp + u * IMP_FL_GROUPS, l[u]);
-    for (int r0 = IMP_FL_ROWS * IMP_FL_GROUPS; IMP_FL_ROWS == 16 && r0 < rows; r0 += IMP_FL_ROWS * IMP_FL_GROUPS) {     // more than 1024 rows
+    add_rows(0);
+    for (int r0 = PASS; IMP_FL_ROWS == 16 && r0 < rows; r0 += PASS) {     // more than 1024 rows
         request(r0);
-#pragma unroll
-        for (int u = 0; u < IMP_FL_ROWS; ++u) add_row(r0 + grp + u * IMP_FL_GROUPS, l[u]);
+        add_rows(r0);
     }
-    acc += __shfl_xor(acc, 16, WAVE);
-    acc += __shfl_xor(acc, 32, WAVE);
+    acc = quad_combine(acc, [](float x, float y) { return x + y; });
     if ((threadIdx.x & 63) < 16) red[threadIdx.x >> 6][key] = acc;
     __syncthreads();
     const int j = key0 + (int)threadIdx.x - vs;          // visual index of key threadIdx.x of this block
@@ -875,7 +896,7 @@ int d3tom::importance_run(const void* q, const void* k, int dt,
 #undef D3TOM_IMP_STREAM
         if (keep) {
 #define D3TOM_IMP_FROM_LOGITS(ROWS)                                                                                                       \
-    D3TOM_LAUNCH(IMP_SCORES, st, (imp_scores_from_logits<ROWS><<<dim3(ceil_div(max_N, 16), B), IMP_FL_THREADS, (size_t)rows * sizeof(float), st>>>(   \
+    D3TOM_LAUNCH(IMP_SCORES, st, (imp_scores_from_logits<ROWS><<<dim3(ceil_div(max_N, 16), B), IMP_FL_THREADS, (size_t)ceil_div(rows, ROWS * IMP_FL_GROUPS) * ROWS * IMP_FL_GROUPS * sizeof(float), st>>>(   \
         H, seq_off, dec_off, vis_start, vis_count, score_off, max_D, max_V, w.DPAD, w.NCH, w.KC, w.NKB, part, logits, scores)))
             if (rows <= IMP_FL_GROUPS) D3TOM_IMP_FROM_LOGITS(1);
             else if (rows <= 4 * IMP_FL_GROUPS) D3TOM_IMP_FROM_LOGITS(4);
