@@ -48,6 +48,7 @@
 // online softmax in plain float arithmetic.
 #include "common.hpp"
 #include "direct_load.hpp"
+#include "internal.hpp"
 #include <type_traits>
 
 namespace d3tom {
@@ -926,7 +927,7 @@ __global__ __launch_bounds__(256) void attend_generic_kernel(
 using namespace d3tom;
 
 static int attend_any(const void* q, const void* k, const void* v, int dt, int B, const int32_t* cu_seqlens, int max_seqlen, int H, int dh,
-                      float scale, const int32_t* counts, const int32_t* kept_off, const int32_t* vis_start, void* o, void* stream) {
+                      float scale, const int32_t* counts, const int32_t* kept_off, const int32_t* vis_start, void* o, void* stream, bool whole = false) {
     if (!q || !k || !v || !o || !cu_seqlens) return D3TOM_ERR_INVALID_ARG;
     if (B < 1 || max_seqlen < 1 || H < 1 || dh < 1) return D3TOM_ERR_INVALID_ARG;
     if (!(scale > 0.f) || !(scale < 3.0e38f)) return D3TOM_ERR_INVALID_ARG;      // the running max is taken on raw logits
@@ -946,7 +947,11 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
     // Short samples without weights whose 32-query workgroups have a compute unit each: keys split across the waves.  (Against the 64-query
     // tiles below: 231 keys, 32 heads of 128 6.3 us and 6.5, 493 keys, 8 heads of 128 7.5 and 8.2, 493 keys, 16 heads of 64 5.6 and 6.2; up to
     // 128 keys 5.2 and 4.7; two workgroups to a unit 493 keys, 32 heads of 128 11.5 and 8.9.)
-    if (mfma && !wgt && max_seqlen > 128 && max_seqlen <= ATS_MAX_KEYS && ceil_div(max_seqlen, 32) * heads <= 256) {
+    // whole: the blocks of a stack in front of its merge, up to two workgroups a unit, and no 64-query tiles: which of two near-equal cosines
+    // takes a token goes by the last bits of these sums, and they are not to move with the number of samples.  (Of 26 drawn merged stacks
+    // of 200 to 2000 visual tokens, 4 had tokens that went to another row of 1e-5 to 5e-5 less or more cosine when these blocks took 64-query tiles.)
+    if (mfma && !wgt && max_seqlen <= ATS_MAX_KEYS &&
+        (whole ? ceil_div(max_seqlen, 128) * heads <= 512 : max_seqlen > 128 && ceil_div(max_seqlen, 32) * heads <= 256)) {
         const int nqt = ceil_div(max_seqlen, 32);
         const dim3 g((unsigned)(8 * ceil_div(H * B, 8) * nqt));
         const size_t lds = (size_t)4 * 2 * ATS_BK * dh * 2;
@@ -969,7 +974,7 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
         // against this, by the number of 64-query tiles: heads of 128, up to 256 tiles 1.13 (samples of up to 128 keys) to 1.46 (more than 1024), 257
         // to 384 0.68 to 1.02; heads of 64, up to 256 tiles 1.12 to 1.37, 257 to 512 0.99 to 1.15 (up to 128 keys 0.92), 513 to 640 1.12 to 1.28,
         // 641 to 768 0.95 to 1.07.  (A sample of one tile of keys has nothing to share.)
-        const bool split = max_seqlen > ATT_BK && ceil_div(max_seqlen, 64) * heads <= (dh == 64 && max_seqlen > 128 ? 640 : 256);
+        const bool split = !whole && max_seqlen > ATT_BK && ceil_div(max_seqlen, 64) * heads <= (dh == 64 && max_seqlen > 128 ? 640 : 256);
         // Rounds of workgroups over the 256 compute units.  A round of 128-query tiles costs 0.61 to 0.70 of one of 256-query tiles
         // (every fragment read from LDS feeds one MFMA instead of two; 32 heads, narrow against wide: 1024 keys 21.9 us against 30.9,
         // one round each; 1198 keys 44.7 against 35.7, two to one; 3773 keys 255 against 210, four to two; 2100 keys 106 against
@@ -1023,6 +1028,11 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
                 (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, cu_seqlens, H, dh, scale2, (uint16_t*)o, kw));
     }
     return D3TOM_OK;
+}
+
+int d3tom::attend_whole_run(const void* q, const void* k, const void* v, int B, const int32_t* cu_seqlens, int max_seqlen, int H, int dh, float scale,
+                            void* o, void* stream) {
+    return attend_any(q, k, v, D3TOM_BF16, B, cu_seqlens, max_seqlen, H, dh, scale, nullptr, nullptr, nullptr, o, stream, true);
 }
 
 extern "C" int d3tom_attend(const void* q, const void* k, const void* v, int dt,

@@ -158,6 +158,10 @@ int topk_run(float* scores, int B, const int32_t* score_off, const int32_t* keep
              int32_t* kept_off_out, int32_t* out_off_out, void* stream, const MergePrep* prep = nullptr,
              bool* prepared = nullptr, const ScoreSums& sums = ScoreSums());
 
+// d3tom_attend on samples that no merge has shortened, where a merge may follow (bf16): sums that do not depend on the number of samples
+int attend_whole_run(const void* q, const void* k, const void* v, int B, const int32_t* cu_seqlens, int max_seqlen, int H, int dh, float scale,
+                     void* o, void* stream);
+
 // d3tom_merge / d3tom_merge_kv; prepared: the selection launch has filled the workspace as MergePrep describes;
 // out_rows_hint: output rows per sample to expect when max_out is only a loose bound (a sample may have more)
 int merge_run(const void* x0, void* y0, const void* x1, void* y1, const void* sim, int d, int d_sim, int dt,

@@ -207,7 +207,9 @@ extern "C" int d3tom_stack_step_batch(const void* x, int B, const int32_t* N_h, 
         void* vv = (char*)qkv + (size_t)2 * n * d * 2;
         // the rotation of q and k happens in the projection's epilogue
         D3TOM_TRY(linear_run(nrm, b.w_qkv, n, 3 * d, d, LIN_PLAIN, nullptr, qkv, d, 0, st, rope_cs, dh));
-        D3TOM_TRY(d3tom_attend(qq, kk, vv, D3TOM_BF16, B, cu, longest, H, dh, scale, att, nullptr, 0, st));
+        // (a merge that keeps every token shortens nothing: its model is the unmerged one, bit for bit)
+        if (n == sum_N) D3TOM_TRY(attend_whole_run(qq, kk, vv, B, cu, longest, H, dh, scale, att, st));
+        else D3TOM_TRY(d3tom_attend(qq, kk, vv, D3TOM_BF16, B, cu, longest, H, dh, scale, att, nullptr, 0, st));
         // post-attention hidden state = residual + attention output projection; in place, except that the
         // caller's input is never written
         void* post = (cur == x) ? h : const_cast<void*>(cur);
