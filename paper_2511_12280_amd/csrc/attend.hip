@@ -624,8 +624,8 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 // waits for the wave's own loads: K of the next tile is requested as soon as the K fragments are in
 // registers, V of the next tile as soon as the V fragments are).  At the end the four partial results
 // (running max, sum, O^T) meet in LDS and wave t combines and stores the 32 output dims t*32 ..
-// Four times the K/V traffic per query of the kernel above, which is why it is only used while every workgroup has a compute unit to
-// itself.
+// Four times the K/V traffic per query of the kernel above, which is why it is only taken while every workgroup has a compute unit to
+// itself (in front of a stack's merge: two of them).
 constexpr int ATS_BK = 32;      // keys per wave tile
 constexpr int ATS_MAX_KEYS = 512;
 

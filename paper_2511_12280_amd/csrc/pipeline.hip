@@ -2,7 +2,8 @@
 // by "l = l* and the decider set is not empty": importance map, TopK at the step's keep ratio, cosine
 // assignment, aggregation and removal), with the kept counts computed on the device from per-sample keep
 // ratios, so that no host integer sits between the importance map and the merge.  Host-side sequencing of
-// the same kernels the four separate entry points launch, sharing one workspace.
+// the same kernels the four separate entry points launch, sharing one workspace (the selection also streams the rows for the merge and, on the
+// generic path, forms the scores of few tokens, to the same bits).
 #include "internal.hpp"
 
 namespace d3tom {
