@@ -834,31 +834,36 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
 #endif
 }
 
-// generic: one workgroup per (query, head), keys in chunks of 256, plain float online softmax.  A wave forms the logits of 64 keys, 16 lanes
+// generic: one workgroup per (Q queries, head), keys in chunks of 256, plain float online softmax.  A wave forms the logits of 64 keys, 16 lanes
 // to a key; for the output a thread takes one 16-byte chunk of the channels and every G-th key (G = 256 / chunks), and the
 // G partial rows meet in LDS at the end.  The first values are requested with the keys.  (A single row of dh threads walking all keys is one
 // chain of n dependent loads: 8.1 us at 100 keys, launch included; split over the groups, a key to a thread 5.8 us; now 5.0.)
-template <typename T>
+template <typename T, int Q>                   // Q: queries of a workgroup
 __global__ __launch_bounds__(256) void attend_generic_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restrict__ cu,
     int H, int dh, float scale2, T* __restrict__ o, KeyWeights kw) {
     constexpr int EPC = 16 / sizeof(T);
-    const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int i0 = blockIdx.x * Q, h = blockIdx.y, b = blockIdx.z;
     const int tok0 = cu[b];
     const int n = cu[b + 1] - tok0;
-    if (i >= n) return;
-    __shared__ float ps[256];
-    __shared__ float red[8];
+    if (i0 >= n) return;
+    __shared__ float ps[Q][256];
+    __shared__ float red[Q][8];
     __shared__ float part[256][EPC + 1];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const size_t rs = (size_t)H * dh;
-    const T* qr = q + (size_t)(tok0 + i) * rs + (size_t)h * dh;
+    const T* qr[Q];
+#pragma unroll
+    for (int x = 0; x < Q; ++x) qr[x] = q + (size_t)(tok0 + min(i0 + x, n - 1)) * rs + (size_t)h * dh;
     const int nch = dh / EPC, G = 256 / nch;
     const int grp = tid / nch, ch = tid - grp * nch;           // threads beyond G * nch take no keys
-    float m_run = -INFINITY, l_run = 0.f;
-    float acc[EPC];
+    float m_run[Q], l_run[Q], acc[Q][EPC];
 #pragma unroll
-    for (int e = 0; e < EPC; ++e) acc[e] = 0.f;
+    for (int x = 0; x < Q; ++x) {
+        m_run[x] = -INFINITY; l_run[x] = 0.f;
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) acc[x][e] = 0.f;
+    }
     for (int j0 = 0; j0 < n; j0 += 256) {
         const int cnt = (grp < G) ? min(256, n - j0) : 0;
         const T* vr = v + (size_t)(tok0 + j0) * rs + (size_t)h * dh + ch * EPC;
@@ -869,42 +874,59 @@ __global__ __launch_bounds__(256) void attend_generic_kernel(
         };
         values(grp);                               // before the logits, whose keys arrive with them
         const int first = j0 + wave * 64, j = first + wave_dots_row(lane);
-        float s2 = -INFINITY;
+        float s2[Q];
+#pragma unroll
+        for (int x = 0; x < Q; ++x) s2[x] = -INFINITY;
         if (first < n) {
-            const float dot = wave_row_dots<T>(qr, k + (size_t)(tok0 + first) * rs + (size_t)h * dh, rs, n - first, dh, lane);
+            float dot[Q];
+            wave_row_dots<T, Q>(qr, k + (size_t)(tok0 + first) * rs + (size_t)h * dh, rs, n - first, dh, lane, dot);
             if (j < n) {
-                s2 = dot * scale2;
-                if (kw.counts) s2 += key_log2_weight(kw, b, j);
+                const float weight = kw.counts ? key_log2_weight(kw, b, j) : 0.f;
+#pragma unroll
+                for (int x = 0; x < Q; ++x) s2[x] = kw.counts ? dot[x] * scale2 + weight : dot[x] * scale2;
             }
         }
-        float wm = wave_max(s2);
-        if (lane == 0) red[wave] = wm;
-        __syncthreads();
-        const float cmax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-        const float m_new = fmaxf(m_run, cmax);
-        const float alpha = exp2f(m_run - m_new);
-        const float p = (j < n) ? exp2f(s2 - m_new) : 0.f;
-        ps[wave * 64 + wave_dots_row(lane)] = p;
-        float wsum = wave_sum(p);
-        if (lane == 0) red[4 + wave] = wsum;
-        __syncthreads();
-        l_run = l_run * alpha + (red[4] + red[5] + red[6] + red[7]);
-        m_run = m_new;
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) acc[e] *= alpha;
+        for (int x = 0; x < Q; ++x) {
+            const float wm = wave_max(s2[x]);
+            if (lane == 0) red[x][wave] = wm;
+        }
+        __syncthreads();
+        float alpha[Q];
+#pragma unroll
+        for (int x = 0; x < Q; ++x) {
+            const float cmax = fmaxf(fmaxf(red[x][0], red[x][1]), fmaxf(red[x][2], red[x][3]));
+            const float m_new = fmaxf(m_run[x], cmax);
+            alpha[x] = exp2f(m_run[x] - m_new);
+            const float p = (j < n) ? exp2f(s2[x] - m_new) : 0.f;
+            ps[x][wave * 64 + wave_dots_row(lane)] = p;
+            const float wsum = wave_sum(p);
+            if (lane == 0) red[x][4 + wave] = wsum;
+            m_run[x] = m_new;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int x = 0; x < Q; ++x) {
+            l_run[x] = l_run[x] * alpha[x] + (red[x][4] + red[x][5] + red[x][6] + red[x][7]);
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) acc[x][e] *= alpha[x];
+        }
         for (int t0 = grp; t0 < cnt; t0 += 8 * G) {
             if (t0 != grp) values(t0);
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 if (t0 + u * G >= cnt) break;
-                const float pt = ps[t0 + u * G];
                 const uint32_t ww[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if constexpr (sizeof(T) == 2) {
-                        acc[2 * e] += pt * bf16_lo(ww[e]); acc[2 * e + 1] += pt * bf16_hi(ww[e]);
-                    } else {
-                        acc[e] += pt * __uint_as_float(ww[e]);
+                for (int x = 0; x < Q; ++x) {
+                    const float pt = ps[x][t0 + u * G];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if constexpr (sizeof(T) == 2) {
+                            acc[x][2 * e] += pt * bf16_lo(ww[e]); acc[x][2 * e + 1] += pt * bf16_hi(ww[e]);
+                        } else {
+                            acc[x][e] += pt * __uint_as_float(ww[e]);
+                        }
                     }
                 }
             }
@@ -912,13 +934,17 @@ __global__ __launch_bounds__(256) void attend_generic_kernel(
         __syncthreads();
     }
 #pragma unroll
-    for (int e = 0; e < EPC; ++e) part[tid][e] = acc[e];
-    __syncthreads();
-    if (tid < dh) {
-        const int c0 = tid / EPC, e = tid - c0 * EPC;
-        float sum = 0.f;
-        for (int g = 0; g < G; ++g) sum += part[g * nch + c0][e];      // groups in ascending order
-        Elem<T>::store(o + (size_t)(tok0 + i) * rs + (size_t)h * dh + tid, sum / l_run);
+    for (int x = 0; x < Q; ++x) {
+        if (x) __syncthreads();
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) part[tid][e] = acc[x][e];
+        __syncthreads();
+        if (tid < dh && i0 + x < n) {
+            const int c0 = tid / EPC, e = tid - c0 * EPC;
+            float sum = 0.f;
+            for (int g = 0; g < G; ++g) sum += part[g * nch + c0][e];      // groups in ascending order
+            Elem<T>::store(o + (size_t)(tok0 + i0 + x) * rs + (size_t)h * dh + tid, sum / l_run[x]);
+        }
     }
 }
 
@@ -1019,13 +1045,17 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
 #undef D3TOM_ATT8
 #undef D3TOM_ATT
     } else {
-        const dim3 g(max_seqlen, H, B);
-        if (dt == D3TOM_F32)
-            D3TOM_LAUNCH(ATTEND, st, attend_generic_kernel<float><<<g, 256, 0, st>>>(
-                (const float*)q, (const float*)k, (const float*)v, cu_seqlens, H, dh, scale2, (float*)o, kw));
-        else
-            D3TOM_LAUNCH(ATTEND, st, attend_generic_kernel<uint16_t><<<g, 256, 0, st>>>(
-                (const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, cu_seqlens, H, dh, scale2, (uint16_t*)o, kw));
+#define D3TOM_ATT_GENERIC(T, Q)                                                                                             \
+    D3TOM_LAUNCH(ATTEND, st, (attend_generic_kernel<T, Q><<<dim3(ceil_div(max_seqlen, Q), H, B), 256, 0, st>>>(             \
+        (const T*)q, (const T*)k, (const T*)v, cu_seqlens, H, dh, scale2, (T*)o, kw)))
+        // float32 is bound by reading each query its keys and values.  With two queries to a workgroup a round of workgroups reads half of that, but two
+        // fit on a unit for three, and the round takes up to 1.3 times as long: taken where it saves enough rounds.  (One query and two; 4 heads of 64:
+        // 160 rows 6.1 and 6.5 us, 200 rows 8.6 and 6.8, 300 rows 13.4 and 15.6, 400 rows 21.2 and 19.3, 700 rows 46.9 and 42.1; 16 heads of 64, 100 rows
+        // 9.6 and 9.6, 300 rows 42.7 and 40.8; 8 heads of 36, 200 rows 11.2 and 11.6; 4 heads of 256, 200 rows 20.9 and 13.8.)
+        const long one = (max_seqlen * heads + 767) / 768, two = (ceil_div(max_seqlen, 2) * heads + 511) / 512;
+        if (dt == D3TOM_F32) { if (13 * two < 10 * one) D3TOM_ATT_GENERIC(float, 2); else D3TOM_ATT_GENERIC(float, 1); }
+        else D3TOM_ATT_GENERIC(uint16_t, 1);
+#undef D3TOM_ATT_GENERIC
     }
     return D3TOM_OK;
 }

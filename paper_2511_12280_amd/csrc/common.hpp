@@ -167,33 +167,41 @@ __device__ __forceinline__ float wave_max(float v) { return quad_combine(row16_m
 // them the row `a`, whose place may be the last thing to be known.  (A row to a lane: every load touches 64 lines.)
 // 64 rows span less than 4 GB (65535 heads of 256 float32 channels at most).
 __device__ __forceinline__ int wave_dots_row(int lane) { return (lane & 15) * 4 + (lane >> 4); }
-template <typename T>
-__device__ __forceinline__ float wave_row_dots(const T* __restrict__ a, const T* __restrict__ rows, size_t stride, int count, int n, int lane) {
+// Q rows `a`: the same rows with each of them.
+template <typename T, int Q>
+__device__ __forceinline__ void wave_row_dots(const T* const (&a)[Q], const T* __restrict__ rows, size_t stride, int count, int n, int lane, float (&r)[Q]) {
     const int l = lane & 15, g = lane >> 4, nch = n / (int)(16 / sizeof(T));
     const uint32_t step = (uint32_t)(stride * sizeof(T));
     const char* base = reinterpret_cast<const char*>(rows);
-    float d[16];
+    float d[Q][16];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) d[u] = 0.f;
+    for (int u = 0; u < 16; ++u)
+#pragma unroll
+        for (int q = 0; q < Q; ++q) d[q][u] = 0.f;
     for (int c0 = 0; c0 < nch; c0 += 16) {
         const uint32_t at = (uint32_t)min(c0 + l, nch - 1) * 16u;
-        uint4 y[16];
+        uint4 y[16], x[Q];
 #pragma unroll
         for (int u = 0; u < 16; ++u) y[u] = *reinterpret_cast<const uint4*>(base + ((uint32_t)min(u * 4 + g, count - 1) * step + at));
-        const uint4 x = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a) + at);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) x[q] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a[q]) + at);
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const float v = chunk_dot<T>(x[q], y[u], d[q][u]);
+                d[q][u] = c0 + l < nch ? v : d[q][u];
+            }
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        r[q] = 0.f;
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
-            const float v = chunk_dot<T>(x, y[u], d[u]);
-            d[u] = c0 + l < nch ? v : d[u];
+            const float v = row16_sum(d[q][u]);
+            r[q] = l == u ? v : r[q];
         }
     }
-    float r = 0.f;
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-        const float v = row16_sum(d[u]);
-        r = l == u ? v : r;
-    }
-    return r;
 }
 
 #if defined(__HIP_DEVICE_COMPILE__)

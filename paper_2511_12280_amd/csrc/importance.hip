@@ -750,7 +750,9 @@ __global__ __launch_bounds__(THREADS) void imp_stats_generic(
     float m = -INFINITY, z = 0.f, first = 0.f;             // first: the logit of this thread's first key (the others wait in `row`)
     for (int j0 = wave * 64; j0 < N; j0 += THREADS) {
         const int j = j0 + wave_dots_row(lane);
-        const float s = wave_row_dots<T>(qr, k + ((size_t)(tok0 + j0) * H + h) * dh, (size_t)H * dh, N - j0, dh, lane) * scale2;
+        float dot[1];
+        wave_row_dots<T, 1>({qr}, k + ((size_t)(tok0 + j0) * H + h) * dh, (size_t)H * dh, N - j0, dh, lane, dot);
+        const float s = dot[0] * scale2;
         if (j < N) {
             if (j0 < THREADS) first = s;
             else if (probs && j < kept) row[j] = s;

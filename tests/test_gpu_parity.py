@@ -514,6 +514,23 @@ def test_attend_weighted_varlen(H, dh, dtype, lens):
 TOL_SAME = {"bf16": 2.0 ** -7, "f32": 1e-5}
 
 
+@pytest.mark.parametrize("H,dh,lens", [
+    (4, 64, [192]),                 # one query a workgroup: the last size of a single round
+    (4, 64, [193]),                 # two: the last workgroup holds one query
+    (4, 64, [256]), (4, 64, [257]),             # two, one; one and two chunks of keys
+    (4, 64, [511, 1, 300]),         # two: ragged, a sample of one query
+    (2, 36, [601, 90]), (3, 256, [300]),        # two: chunks of the channels that do not divide the threads, the widest head
+])
+def test_generic_queries_per_workgroup(H, dh, lens):
+    rng = np.random.default_rng(sum(lens) + dh)
+    qkv = [W.random_qkv(70 + n, n, H, dh, "f32") for n in lens]
+    counts = [rng.integers(1, 40, size=n // 2).astype(np.int32) for n in lens]
+    vis = [n // 4 for n in lens]
+    for (q, k, v), o, w, vs, c, n in zip(qkv, gpu_attend(qkv, "f32"), gpu_attend_weighted(qkv, counts, vis, "f32"), vis, counts, lens):
+        check_attend(o, q, k, v, "f32")
+        check_attend(w, q, k, v, "f32", key_weight=key_weights(n, vs, c))
+
+
 def test_merge_counts_feed_weighted_attention():
     """The counts d3tom_merge writes are what d3tom_attend_weighted reads: merge a sample, project the merged rows
     (host, not on the path), attend with the counts as key weights, compare with the oracle given the same weights."""
