@@ -745,7 +745,7 @@ template <typename T, int CPT>     // CPT: 16-byte chunks per thread per pass
 __global__ __launch_bounds__(256, CPT == 2 ? 7 : 5) void merge_scatter_kernel(
     const T* __restrict__ x0, const T* __restrict__ x1, int d, const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_start,
     const int32_t* __restrict__ vis_count, const int32_t* __restrict__ kept_idx, const int32_t* __restrict__ kept_off,
-    int max_V, int max_keep, int mode, const int32_t* __restrict__ out_off, const table_t* __restrict__ table, int VP,
+    int max_V, int max_keep, int max_out, int mode, const int32_t* __restrict__ out_off, const table_t* __restrict__ table, int VP,
     const int32_t* __restrict__ vis_off, T* __restrict__ y0, T* __restrict__ y1, int32_t* __restrict__ assign_out,
     int32_t* __restrict__ counts_out, int32_t* __restrict__ src_pos_out) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -765,7 +765,7 @@ __global__ __launch_bounds__(256, CPT == 2 ? 7 : 5) void merge_scatter_kernel(
     int vo0 = vis_off[b], oo0 = out_off[b];
     const SampleGeom s = sample_geom(b, seq_off, vis_start, vis_count, kept_off, max_V, max_keep, vo0, oo0);
     int32_t* assign = (blockIdx.z || slice || !assign_out) ? nullptr : assign_out + vo0;
-    const int N_m = s.N - s.M;
+    const int N_m = min(s.N - s.M, max_out);               // the caller's bound on the rows of y, whatever the sample's sizes say
     if (o >= N_m) return;
     __shared__ int list[SCAT_LIST];
     __shared__ int stage[4][SCAT_WAVE];
@@ -1116,8 +1116,8 @@ int d3tom::merge_run(const void* x0, void* y0, const void* x1, void* y1, const v
     const dim3 gs(rows_expected * nslice, B, x1 ? 2 : 1);    // output rows (x slices) per sample x payloads
 #define D3TOM_SCATTER(TYPE, CPT)                                                                                        \
     D3TOM_LAUNCH(MERGE_SCATTER, st, merge_scatter_kernel<TYPE, CPT><<<gs, 256, 0, st>>>(                                \
-        (const TYPE*)x0, (const TYPE*)x1, d, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep, mode,   \
-        out_off, table, w.VP, vis_off, (TYPE*)y0, (TYPE*)y1, assign, counts, src_pos))
+        (const TYPE*)x0, (const TYPE*)x1, d, seq_off, vis_start, vis_count, kept_idx, kept_off, max_V, max_keep,         \
+        max_out, mode, out_off, table, w.VP, vis_off, (TYPE*)y0, (TYPE*)y1, assign, counts, src_pos))
     if (dt == D3TOM_BF16) { if (nslice == 2) D3TOM_SCATTER(uint16_t, 1); else D3TOM_SCATTER(uint16_t, 2); }
     else                  { if (nslice == 2) D3TOM_SCATTER(float, 1); else D3TOM_SCATTER(float, 2); }
 #undef D3TOM_SCATTER

@@ -693,6 +693,33 @@ def test_merge_layer_one_call_with_more_rows_than_expected(dtype, d, H):
             np.testing.assert_array_equal(m1[key][b], mout[key][b])
 
 
+@pytest.mark.parametrize("kv", [False, True])
+@pytest.mark.parametrize("d", [256, 4096])               # one workgroup a row, two half rows
+def test_merge_writes_no_more_rows_than_max_out(d, kv):
+    """A sample whose visual count on the device exceeds the stated max_V is clamped: its other visual tokens are then not
+    merged away and would be rows of the output, but the outputs have max_out rows.  The rows behind those are as they were (the
+    buffers of this test have room for every token, so that nothing outside them is ever at stake)."""
+    P, V, O, D = 9, 400, 7, 2
+    c = W.random_case(905, P + V + O, d, d // 64, P, V, D, dtype="bf16")
+    lay = B.Layout([c["N"]], [P], [V], [c["dec_idx"]], [40])
+    max_V, max_out = 100, P + 40 + O
+    kept = torch.arange(40, dtype=torch.int32, device="cuda")
+    x = B.to_device(c["x"], "bf16")
+    full = lambda *shape, dtype=torch.int32: torch.full(shape, -7, dtype=dtype, device="cuda")
+    y, v_out = (full(c["N"], d, dtype=torch.bfloat16) for _ in range(2))
+    assign, counts, src = full(V), full(40), full(c["N"])
+    lay.max_V, lay.max_pruned, lay.max_Nm = max_V, max_V - 40, max_out
+    ws = B.workspace(B.d3tom_workspace_bytes(B.D3TOM_OP_MERGE, 1, lay.max_N, max_V, 1, d, D))
+    if kv:
+        B.d3tom_merge_kv(x, x.flip(0), lay, kept, B.D3TOM_MERGE_MEAN, y, v_out, assign, counts, src, ws)
+    else:
+        B.d3tom_merge(x, None, lay, kept, B.D3TOM_MERGE_MEAN, y, assign, counts, src, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(y[:P], x[:P])
+    assert bool((y[max_out:] == -7).all()) and bool((v_out[max_out:] == -7).all()) and bool((src[max_out:] == -7).all())
+    assert bool((assign[max_V:] == -7).all())
+
+
 @pytest.mark.parametrize("dtype,d,H,V,k", [
     ("bf16", 4096, 32, 300, 100),         # contraction cut in 16
     ("bf16", 2048, 16, 700, 513),         # cut in 2, five column tiles
