@@ -162,6 +162,7 @@ extern "C" int d3tom_stack_step_batch(const void* x, int B, const int32_t* N_h, 
     }
     const StackWs w = stack_ws_layout(B, sum_N, max_N, d, H, F, merging ? sum_V : 0, merging ? max_V : 0, merging ? max_D : 0);
     if (ws_bytes < w.total || (((uintptr_t)ws) & 255u)) return D3TOM_ERR_WORKSPACE_TOO_SMALL;
+    if (!(theta > 1.f) || !(theta < 3.0e38f)) return D3TOM_ERR_INVALID_ARG;      // as d3tom_rope
     char* base = (char*)ws;
     int32_t* meta = (int32_t*)(base + w.meta);
     int32_t* pos = (int32_t*)(base + w.pos);

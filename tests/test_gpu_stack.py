@@ -527,6 +527,15 @@ def test_stack_step_rejects(B):
     with pytest.raises(B.D3tomError) as e:
         B.d3tom_stack_step(x, 4, 512, arr, 1, 1, dec, 2, 4, 40, 10, mode=0, eps=1e-5, theta=10000.0, y=y, ws=ws[:1024])
     assert e.value.status == B.D3TOM_ERR_WORKSPACE_TOO_SMALL
+    for theta in (1.0, 0.5, 0.0, -1.0, float("nan"), float("inf"), 3.2e38):
+        bad = dict(args, theta=theta)
+        for D in (2, 0):
+            with pytest.raises(B.D3tomError) as e:
+                B.d3tom_stack_step(x, 4, 512, arr, 1, 1, dec, D, 4, 40, 10, **bad)
+            assert e.value.status == B.D3TOM_ERR_INVALID_ARG
+            with pytest.raises(B.D3tomError) as e:
+                B.d3tom_stack_step_batch(x, [case["N"]], 4, 512, arr, 1, 1, dec, [D], [4], [40], [10], **bad)
+            assert e.value.status == B.D3TOM_ERR_INVALID_ARG
 
 
 # ---- full-size shapes (hidden 4096, 32 x 128 heads, SwiGLU 11008, 3645 + 64 + 64 tokens) --------------------

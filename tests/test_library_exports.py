@@ -79,6 +79,23 @@ def test_device_entry_points_reject_bad_arguments_without_a_gpu(lib):
     assert lib.d3tom_stack_workspace_bytes(i(0), i(256), i(4), i(512), i(144), i(16)) == 0
 
 
+def test_stack_step_refuses_a_rotary_base_without_a_gpu(lib):
+    # everything else is in order (the addresses are never read on the host, and a refused call enqueues nothing), so a call that
+    # is not refused would come back as D3TOM_ERR_DEVICE here
+    from paper_2511_12280_amd import binding as B
+    i, f, p = ctypes.c_int, ctypes.c_float, ctypes.c_void_p(1 << 20)
+    blocks = (ctypes.c_void_p * 6)(*[1 << 20] * 6)
+    one = lambda v: (ctypes.c_int32 * 1)(v)
+    nbytes = ctypes.c_size_t(B.d3tom_stack_workspace_bytes(48, 256, 4, 512, 40, 2))
+    lib.d3tom_stack_step.restype = lib.d3tom_stack_step_batch.restype = ctypes.c_int
+    for theta in (1.0, 0.5, 0.0, -1.0, float("nan"), float("inf"), 3.2e38):
+        for D in (0, 2):
+            assert lib.d3tom_stack_step(p, i(48), i(256), i(4), i(512), i(1), blocks, i(1), p, i(D), i(4), i(40), i(10), i(0), f(1e-5),
+                                        f(theta), p, None, None, None, None, None, p, nbytes, None) == 1
+            assert lib.d3tom_stack_step_batch(p, i(1), one(48), i(256), i(4), i(512), i(1), blocks, i(1), p, one(D), one(4), one(40), one(10),
+                                              i(0), f(1e-5), f(theta), p, None, None, None, None, None, p, nbytes, None) == 1
+
+
 def test_schedule_variants_share_their_mean(lib):
     from paper_2511_12280_amd import binding as B
     # low -> high (D3ToM-t) and its reverse (D3ToM-t dagger) through the one direction-neutral helper:
