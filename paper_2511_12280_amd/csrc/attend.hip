@@ -116,8 +116,7 @@ constexpr int ATT_WKEYS = 3584;     // longest sample of the weighted tiled kern
 // SPLIT: the groups share their queries (64 of them) and take the tiles of keys in turn, each in its own half of the ring; at the end
 // each hands half of the channels of its O^T to the other through LDS.  A launch that leaves compute units idle is one chain of
 // phases per unit, and this is half as long a chain on twice as many units: 8 heads of 128, 775 keys 15.8 -> 11.3 us, 2000 keys 33.4 -> 23.1,
-// 16 heads of 64, 1024 keys 13.9 -> 9.4; 32 heads of 128, 493 keys 11.9 (the short-sample kernel) -> 9.0, each unit taking in
-// the keys of its head once instead of twice.  No part of a phase bounds it (without loads, exponentials, rescaling or reads of V it is 3 to 8 %
+// 16 heads of 64, 1024 keys 13.9 -> 9.4.  No part of a phase bounds it (without loads, exponentials, rescaling or reads of V it is 3 to 8 %
 // faster each).
 template <int DH, bool WGT, int NQ, bool TURNS, bool SKIP, bool SPLIT>
 __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
@@ -624,15 +623,14 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 // waits for the wave's own loads: K of the next tile is requested as soon as the K fragments are in
 // registers, V of the next tile as soon as the V fragments are).  At the end the four partial results
 // (running max, sum, O^T) meet in LDS and wave t combines and stores the 32 output dims t*32 ..
-// Four times the K/V traffic per query of the kernel above, which is why it is only taken while every workgroup has a compute unit to
-// itself (in front of a stack's merge: two of them).
+// Four times the K/V traffic per query of the kernel above, which is why it is only taken while the whole sample is short.
 constexpr int ATS_BK = 32;      // keys per wave tile
 constexpr int ATS_MAX_KEYS = 512;
 
-template <int DH>
+template <int DH, bool WGT>
 __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-    const int32_t* __restrict__ cu, int H, int nB, int nqt, float scale2, uint16_t* __restrict__ o) {
+    const int32_t* __restrict__ cu, int H, int nB, int nqt, float scale2, uint16_t* __restrict__ o, KeyWeights kw) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int KS = DH / 16;
     constexpr int DT = DH / 32;
@@ -645,6 +643,7 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
     static_assert(WREG == DT * 16 * 64 * 4, "a wave's region also holds its partial O^T");
     extern __shared__ __attribute__((aligned(16))) char ring[];
     __shared__ float part_m[4][32], part_l[4][32];
+    __shared__ __attribute__((aligned(16))) float lw_s[WGT ? ATS_MAX_KEYS : 4];
 
     const int xcd = blockIdx.x & 7, li = blockIdx.x >> 3;
     const int hb = (li / nqt) * 8 + xcd, qt = li % nqt;
@@ -655,6 +654,10 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
     if (qt * 32 >= n) return;
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    if constexpr (WGT) {
+        for (int j = tid; j < ATS_MAX_KEYS; j += 256) lw_s[j] = (j < n) ? key_log2_weight(kw, b, j) : 0.f;
+        __syncthreads();
+    }
     const int c = lane & 31, g = lane >> 5;
     const size_t rs = (size_t)H * DH;
     const uint16_t* kb = k + (size_t)tok0 * rs + (size_t)h * DH;
@@ -732,36 +735,72 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
         // the K fragments are in registers (the MFMAs above consumed them): the K tile is free
         if (more) issue_k(key0 + 4 * ATS_BK);
         __builtin_amdgcn_sched_barrier(0);
-        if (key0 + ATS_BK > n) {
+        if constexpr (WGT) {
+            // weighted: maximum and exponent on scale2 * logit + log2 w (m_run lives in that scaled domain)
+#pragma unroll
+            for (int e4 = 0; e4 < 4; ++e4) {
+                const f32x4 w4 = *reinterpret_cast<const f32x4*>(&lw_s[min(key0 + e4 * 8 + g * 4, ATS_MAX_KEYS - 4)]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int key = key0 + e4 * 8 + g * 4 + e;
+                    const float t = __builtin_fmaf(st[e4 * 4 + e], scale2, w4[e]);
+                    st[e4 * 4 + e] = (key < n) ? t : -INFINITY;
+                }
+            }
+            float tmax = st[0];
+#pragma unroll
+            for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, st[e]);
+            tmax = att_pair_max(tmax);
+            const float m_new = fmaxf(m_run, tmax);
+            float psum = 0.f;
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const int key = key0 + (e >> 2) * 8 + g * 4 + (e & 3);
-                if (key >= n) st[e] = -INFINITY;
+                const float p = __builtin_amdgcn_exp2f(st[e] - m_new);
+                st[e] = p;
+                psum += p;
             }
+            if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+                l_run *= alpha;
+#pragma unroll
+                for (int t = 0; t < DT; ++t)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) ot[t][e] *= alpha;
+            }
+            l_run += psum;
+            m_run = m_new;
+        } else {
+            if (key0 + ATS_BK > n) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int key = key0 + (e >> 2) * 8 + g * 4 + (e & 3);
+                    if (key >= n) st[e] = -INFINITY;
+                }
+            }
+            float tmax = st[0];
+#pragma unroll
+            for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, st[e]);
+            tmax = att_pair_max(tmax);
+            const float m_new = fmaxf(m_run, tmax);                // finite: every tile holds >= 1 valid key
+            const float ms = m_new * scale2;
+            float psum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(st[e], scale2, -ms));
+                st[e] = p;
+                psum += p;
+            }
+            if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+                const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale2);
+                l_run *= alpha;
+#pragma unroll
+                for (int t = 0; t < DT; ++t)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) ot[t][e] *= alpha;
+            }
+            l_run += psum;
+            m_run = m_new;
         }
-        float tmax = st[0];
-#pragma unroll
-        for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, st[e]);
-        tmax = att_pair_max(tmax);
-        const float m_new = fmaxf(m_run, tmax);                // finite: every tile holds >= 1 valid key
-        const float ms = m_new * scale2;
-        float psum = 0.f;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(st[e], scale2, -ms));
-            st[e] = p;
-            psum += p;
-        }
-        if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-            const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale2);
-            l_run *= alpha;
-#pragma unroll
-            for (int t = 0; t < DT; ++t)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) ot[t][e] *= alpha;
-        }
-        l_run += psum;
-        m_run = m_new;
         __builtin_amdgcn_sched_barrier(0);
         // V of this tile: everything older than the K loads just issued has landed
         if (more) wait_loads<LD>(); else wait_loads<0>();
@@ -810,7 +849,7 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
 #pragma unroll
     for (int w2 = 0; w2 < 4; ++w2) {
         const float mw = part_m[w2][c];
-        f[w2] = (mw == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((mw - m) * scale2);
+        f[w2] = (mw == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((mw - m) * (WGT ? 1.0f : scale2));
         l += part_l[w2][c] * f[w2];
     }
     const float inv = 1.0f / l;
@@ -970,37 +1009,40 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
     // the weighted MFMA kernels keep a sample's weights in LDS
     if (wgt && mfma && max_seqlen > ATT_WKEYS) return D3TOM_ERR_UNSUPPORTED;
     const long heads = (long)H * B;
-    // Short samples without weights whose 32-query workgroups have a compute unit each: keys split across the waves.  (Against the 64-query
-    // tiles below: 231 keys, 32 heads of 128 6.3 us and 6.5, 493 keys, 8 heads of 128 7.5 and 8.2, 493 keys, 16 heads of 64 5.6 and 6.2; up to
-    // 128 keys 5.2 and 4.7; two workgroups to a unit 493 keys, 32 heads of 128 11.5 and 8.9.)
-    // whole: the blocks of a stack in front of its merge, up to two workgroups a unit, and no 64-query tiles: which of two near-equal cosines
-    // takes a token goes by the last bits of these sums, and they are not to move with the number of samples.  (Of 26 drawn merged stacks
-    // of 200 to 2000 visual tokens, 4 had tokens that went to another row of 1e-5 to 5e-5 less or more cosine when these blocks took 64-query tiles.)
-    if (mfma && !wgt && max_seqlen <= ATS_MAX_KEYS &&
-        (whole ? ceil_div(max_seqlen, 128) * heads <= 512 : max_seqlen > 128 && ceil_div(max_seqlen, 32) * heads <= 256)) {
+    // Short samples, up to two rounds of 128-query tiles: keys split across the waves.  The tiles below are faster for some of them (493 keys, 32 heads of
+    // 128 11.5 us here, 8.9 with 64-query tiles; 100 keys 5.2 and 4.7; batches of 129 .. 512 keys up to 1.8 times as fast, others up to 1.75 times as
+    // slow), but this kernel has four running maxima a row, over tiles of 32 keys, relative to which the probabilities are rounded.  Error against
+    // float64 (2-norm, relative, output rounded to bf16) at logit spreads of 1 and 2, 493 keys: 2.10e-3, 1.77e-3 here; 2.16e-3, 1.82e-3 with 64-query
+    // tiles; 2.19e-3, 1.86e-3 with wider ones.  66 to 512 keys, weighted or not, heads of 64 and 128: 2.2 to 4.9 % more with any of the tiles.
+    if (mfma && max_seqlen <= ATS_MAX_KEYS && ceil_div(max_seqlen, 128) * heads <= 512) {
         const int nqt = ceil_div(max_seqlen, 32);
         const dim3 g((unsigned)(8 * ceil_div(H * B, 8) * nqt));
         const size_t lds = (size_t)4 * 2 * ATS_BK * dh * 2;
         const int threads = 256;
         static PerDeviceOnce lds_setup_s;
         if (!lds_setup_s.run([] {
-                return raise_dynamic_lds(attend_bf16_short_kernel<128>, 4 * 2 * ATS_BK * 128 * 2) &&
-                       raise_dynamic_lds(attend_bf16_short_kernel<64>, 4 * 2 * ATS_BK * 64 * 2);
+                return raise_dynamic_lds(attend_bf16_short_kernel<128, false>, 4 * 2 * ATS_BK * 128 * 2) &&
+                       raise_dynamic_lds(attend_bf16_short_kernel<64, false>, 4 * 2 * ATS_BK * 64 * 2) &&
+                       raise_dynamic_lds(attend_bf16_short_kernel<128, true>, 4 * 2 * ATS_BK * 128 * 2) &&
+                       raise_dynamic_lds(attend_bf16_short_kernel<64, true>, 4 * 2 * ATS_BK * 64 * 2);
             }))
             return D3TOM_ERR_DEVICE;
-#define D3TOM_ATT_SHORT(DHV)                                                                                                   \
-    D3TOM_LAUNCH(ATTEND, st, (attend_bf16_short_kernel<DHV><<<g, threads, lds, st>>>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, \
-                                                           cu_seqlens, H, B, nqt, scale2, (uint16_t*)o)))
-        if (dh == 128) D3TOM_ATT_SHORT(128); else D3TOM_ATT_SHORT(64);
+#define D3TOM_ATT_SHORT(DHV, WGTV)                                                                                              \
+    D3TOM_LAUNCH(ATTEND, st, (attend_bf16_short_kernel<DHV, WGTV><<<g, threads, lds, st>>>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, \
+                                                           cu_seqlens, H, B, nqt, scale2, (uint16_t*)o, kw)))
+        if (dh == 128) { if (wgt) D3TOM_ATT_SHORT(128, true); else D3TOM_ATT_SHORT(128, false); }
+        else           { if (wgt) D3TOM_ATT_SHORT(64, true);  else D3TOM_ATT_SHORT(64, false); }
 #undef D3TOM_ATT_SHORT
     } else if (mfma) {
         // 64-query tiles whose groups share the keys, where they fill one round of compute units at most: half as long a chain as 128-query
-        // tiles on twice as many units.  Two workgroups of heads of 64 fit on a unit, and of ragged batches fewer tiles are real than the longest
+        // tiles on twice as many units, and two running maxima a row instead of one (error against float64 0.98 of theirs).  Two workgroups of heads of
+        // 64 fit on a unit, and of ragged batches fewer tiles are real than the longest
         // sample lets the host expect.  Means over 897 drawn batches (1 to 16 samples of 33 to 2400 keys), the better of 128 and 256 queries
         // against this, by the number of 64-query tiles: heads of 128, up to 256 tiles 1.13 (samples of up to 128 keys) to 1.46 (more than 1024), 257
-        // to 384 0.68 to 1.02; heads of 64, up to 256 tiles 1.12 to 1.37, 257 to 512 0.99 to 1.15 (up to 128 keys 0.92), 513 to 640 1.12 to 1.28,
-        // 641 to 768 0.95 to 1.07.  (A sample of one tile of keys has nothing to share.)
-        const bool split = !whole && max_seqlen > ATT_BK && ceil_div(max_seqlen, 64) * heads <= (dh == 64 && max_seqlen > 128 ? 640 : 256);
+        // to 384 0.68 to 1.02; heads of 64, up to 256 tiles 1.12 to 1.37, 257 to 512 0.99 to 1.15, 513 to 640 1.12 to 1.28,
+        // 641 to 768 0.95 to 1.07.  (Samples of up to 512 keys that are not for the short-sample kernel have more tiles than that.)
+        // whole: the blocks of a stack in front of its merge do without these tiles, see attend_whole_run.
+        const bool split = !whole && max_seqlen > ATS_MAX_KEYS && ceil_div(max_seqlen, 64) * heads <= (dh == 64 ? 640 : 256);
         // Rounds of workgroups over the 256 compute units.  A round of 128-query tiles costs 0.61 to 0.70 of one of 256-query tiles
         // (every fragment read from LDS feeds one MFMA instead of two; 32 heads, narrow against wide: 1024 keys 21.9 us against 30.9,
         // one round each; 1198 keys 44.7 against 35.7, two to one; 3773 keys 255 against 210, four to two; 2100 keys 106 against
