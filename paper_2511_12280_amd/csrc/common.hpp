@@ -50,7 +50,7 @@ template <> struct Elem<uint16_t> {   // bf16 storage
 };
 
 // Dot product of two rows of n elements (16-byte aligned, n a multiple of the elements per 16 bytes):
-// 16-byte loads, eight chunks requested before the first is used, float32 accumulation in that order.  For the
+// 16-byte loads, eight chunks requested before the first is used, float32 accumulation.  For the
 // generic kernels, whose time is load latency: one scalar load per multiply made them 10-50 times slower.
 template <typename T>
 __device__ __forceinline__ float chunk_dot(const uint4& a, const uint4& b, float acc) {
@@ -66,24 +66,36 @@ __device__ __forceinline__ float chunk_dot(const uint4& a, const uint4& b, float
     }
     return acc;
 }
+// The products are added as wave_row_dots adds them: sixteen chains over chunks u, u + 16, ..., then neighbours, pairs, quads and eights.
 template <typename T>
 __device__ __forceinline__ float row_dot(const T* __restrict__ a, const T* __restrict__ b, int n) {
     const uint4* pa = reinterpret_cast<const uint4*>(a);
     const uint4* pb = reinterpret_cast<const uint4*>(b);
     const int nch = n / (int)(16 / sizeof(T));
-    float acc = 0.f;
-    for (int c = 0; c < nch; c += 8) {
-        uint4 x[8], y[8];
+    float acc[16];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const bool ok = c + u < nch;
-            x[u] = ok ? pa[c + u] : make_uint4(0, 0, 0, 0);
-            y[u] = ok ? pb[c + u] : make_uint4(0, 0, 0, 0);
+    for (int u = 0; u < 16; ++u) acc[u] = 0.f;
+    for (int c0 = 0; c0 < nch; c0 += 16) {
+#pragma unroll
+        for (int half = 0; half < 16; half += 8) {
+            const int c = c0 + half;
+            if (c >= nch) break;
+            uint4 x[8], y[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const bool ok = c + u < nch;
+                x[u] = ok ? pa[c + u] : make_uint4(0, 0, 0, 0);
+                y[u] = ok ? pb[c + u] : make_uint4(0, 0, 0, 0);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc[half + u] = chunk_dot<T>(x[u], y[u], acc[half + u]);
         }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc = chunk_dot<T>(x[u], y[u], acc);
     }
-    return acc;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1)
+#pragma unroll
+        for (int u = 0; u < 16; u += 2 * o) acc[u] += acc[u + o];
+    return acc[0];
 }
 
 // Makes a kernel hold all of these wave-uniform values at one point, so that they are read together.  A sample's offsets written one

@@ -218,6 +218,25 @@ def test_importance_generic_kept_logits(dtype, H, dh):
             check_scores(S[i], oracle.importance(s["q"], s["k"], s["dec_idx"], s["vis_start"], s["V"]))
 
 
+@pytest.mark.parametrize("D", [3, 32, 33, 100])
+@pytest.mark.parametrize("dtype,H,dh", [("f32", 4, 64), ("f32", 2, 256), ("f32", 3, 36), ("f32", 2, 132), ("bf16", 3, 96)])
+def test_importance_generic_one_key_has_the_row(dtype, H, dh, D):
+    """Every decider row goes to one key, whose logit of some thousands is next to the others' infinity: its probability is 1, however the
+    logit was rounded, if the sum of exponentials holds the same logit.  (A logit formed in another order there is off by up to
+    2^-11, and so is then the probability.)"""
+    V, P = 140, 5
+    s = W.random_case(880 + D, P + V + D, H * dh, H, P, V, D, dtype=dtype)
+    s["dec_idx"] = np.arange(P + V, P + V + D, dtype=np.int32); s["D"] = D
+    target = np.random.default_rng(D).permutation(V)[:D]
+    s["q"] = W.round_to(s["q"] * np.float32(30), dtype)
+    s["k"] = W.round_to(s["k"] * np.float32(10), dtype)
+    s["k"][P + target] = s["q"][s["dec_idx"]]
+    ref = np.zeros(V); ref[target] = 1.0
+    np.testing.assert_allclose(oracle.importance(s["q"], s["k"], s["dec_idx"], P, V), ref, atol=1e-12)
+    S = GpuStep([s], [4], dtype).importance()[0]
+    np.testing.assert_allclose(S, ref, rtol=0, atol=2e-6)
+
+
 @pytest.mark.parametrize("dtype,H,dh,D", [("bf16", 8, 64, 8), ("bf16", 5, 128, 13), ("bf16", 16, 64, 16), ("bf16", 257, 64, 1), ("bf16", 64, 64, 16),
                                           ("bf16", 35, 64, 31), ("f32", 4, 64, 16), ("f32", 5, 36, 13), ("f32", 8, 32, 32), ("f32", 9, 32, 29)])
 def test_importance_rows_per_thread(dtype, H, dh, D):
