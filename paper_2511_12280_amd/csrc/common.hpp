@@ -79,16 +79,14 @@ __device__ __forceinline__ float row_dot(const T* __restrict__ a, const T* __res
 #pragma unroll
         for (int half = 0; half < 16; half += 8) {
             const int c = c0 + half;
-            if (c >= nch) break;
             uint4 x[8], y[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const bool ok = c + u < nch;
-                x[u] = ok ? pa[c + u] : make_uint4(0, 0, 0, 0);
-                y[u] = ok ? pb[c + u] : make_uint4(0, 0, 0, 0);
-            }
+            for (int u = 0; u < 8; ++u) { x[u] = pa[min(c + u, nch - 1)]; y[u] = pb[min(c + u, nch - 1)]; }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc[half + u] = chunk_dot<T>(x[u], y[u], acc[half + u]);
+            for (int u = 0; u < 8; ++u) {
+                const float v = chunk_dot<T>(x[u], y[u], acc[half + u]);
+                acc[half + u] = c + u < nch ? v : acc[half + u];
+            }
         }
     }
 #pragma unroll
