@@ -417,7 +417,8 @@ size_t d3tom_stack_workspace_bytes(int N, int d, int H, int F, int V, int max_D)
  *              always enough)
  *   src_pos    int32[n_out] out or NULL: original position of every output row
  *   scores_out float[V], kept_idx_out int32[keep_k], assign_out int32[V]: the merge layer's intermediate
- *              results, out or NULL (written only when merging)
+ *              results, out or NULL (written only when merging).  These and src_pos are never read: arrays that overlap each
+ *              other spoil their own contents and nothing else
  *   n_out      HOST int out or NULL
  * dh must be 64 or 128, d and F multiples of 64, d at most 8192, every activation and weight matrix below
  * 2 GiB (otherwise D3TOM_ERR_UNSUPPORTED, before anything is enqueued).  theta > 1 and finite, as for

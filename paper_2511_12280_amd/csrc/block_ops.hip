@@ -9,11 +9,11 @@ constexpr int NORM_MAX_CHUNKS = 4;     // 16-byte chunks per thread held in regi
 
 // y = x / sqrt(mean(x^2) + eps) * gain
 // ANGLES: each row's workgroup also leaves the row's dh/2 rotary angles in the table (behind the merge, where the positions of the rows
-// have changed; a launch of its own takes 5 us, this one 0.3 longer)
+// have changed; a launch of its own takes 5 us, this one 0.3 longer) and, if the caller wants them, a copy of the positions
 template <bool ANGLES>
 __global__ __launch_bounds__(256) void rmsnorm_bf16_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ gain,
                                                            int d, float eps, uint16_t* __restrict__ y, const int32_t* __restrict__ pos,
-                                                           int dh, double log2_theta, float2* __restrict__ table) {
+                                                           int dh, double log2_theta, float2* __restrict__ table, int32_t* pos_out) {
     __shared__ float wsum[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const size_t row = (size_t)blockIdx.x * d;
@@ -35,7 +35,9 @@ __global__ __launch_bounds__(256) void rmsnorm_bf16_kernel(const uint16_t* __res
     if (lane == 0) wsum[wave] = ss;
     if constexpr (ANGLES) {
         const int half = dh >> 1;
-        if (tid < half) table[(size_t)blockIdx.x * half + tid] = rope_cos_sin(pos[blockIdx.x], tid, dh, log2_theta);
+        const int p = pos[blockIdx.x];
+        if (tid < half) table[(size_t)blockIdx.x * half + tid] = rope_cos_sin(p, tid, dh, log2_theta);
+        if (pos_out && tid == 0) pos_out[blockIdx.x] = p;
     }
     __syncthreads();
     const float total = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
@@ -152,9 +154,9 @@ __global__ __launch_bounds__(256) void rope_bf16_kernel(uint16_t* __restrict__ q
     }
 }
 
-// table != nullptr: the rotary angles of the rows at positions pos as well
+// table != nullptr: the rotary angles of the rows at positions pos as well (and a copy of those positions to pos_out, if that is given)
 int rmsnorm_run(const void* x, const void* gain, int rows, int d, float eps, void* y, hipStream_t st, const int32_t* pos, int dh,
-                double log2_theta, float2* table) {
+                double log2_theta, float2* table, int32_t* pos_out) {
     if (!x || !gain || !y || rows < 1 || d < 1) return D3TOM_ERR_INVALID_ARG;
     if (!aligned16(x) || !aligned16(gain) || !aligned16(y)) return D3TOM_ERR_INVALID_ARG;
     if (!(eps >= 0.f)) return D3TOM_ERR_INVALID_ARG;
@@ -162,7 +164,7 @@ int rmsnorm_run(const void* x, const void* gain, int rows, int d, float eps, voi
     if (table && (!pos || dh < 2 || dh > 512)) return D3TOM_ERR_INVALID_ARG;
 #define D3TOM_RMSNORM(ANGLES)                                                                                             \
     D3TOM_LAUNCH(RMSNORM, st, (rmsnorm_bf16_kernel<ANGLES><<<rows, 256, 0, st>>>((const uint16_t*)x, (const uint16_t*)gain, d, eps, \
-                                                                                 (uint16_t*)y, pos, dh, log2_theta, table)))
+                                                                                 (uint16_t*)y, pos, dh, log2_theta, table, pos_out)))
     if (table) D3TOM_RMSNORM(true); else D3TOM_RMSNORM(false);
 #undef D3TOM_RMSNORM
     return D3TOM_OK;
@@ -190,7 +192,7 @@ int rope_run(void* q, void* k, const int32_t* pos, int rows, int H, int dh, floa
 }  // namespace d3tom
 
 extern "C" int d3tom_rmsnorm(const void* x, const void* gain, int rows, int d, float eps, void* y, void* stream) {
-    return d3tom::rmsnorm_run(x, gain, rows, d, eps, y, (hipStream_t)stream, nullptr, 0, 0.0, nullptr);
+    return d3tom::rmsnorm_run(x, gain, rows, d, eps, y, (hipStream_t)stream, nullptr, 0, 0.0, nullptr, nullptr);
 }
 
 extern "C" int d3tom_rope(void* q, void* k, const int32_t* pos, int rows, int H, int dh, float theta, void* stream) {

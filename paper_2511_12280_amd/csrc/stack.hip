@@ -8,7 +8,7 @@ namespace d3tom {
 int linear_run(const void* a, const void* w, int M, int N, int K, int epilogue, const void* residual, void* out,
                int out_chunk, int tile, hipStream_t st, const float2* rope_cs = nullptr, int rope_dh = 0);
 int rmsnorm_run(const void* x, const void* gain, int rows, int d, float eps, void* y, hipStream_t st, const int32_t* pos = nullptr, int dh = 0,
-                double log2_theta = 0.0, float2* table = nullptr);
+                double log2_theta = 0.0, float2* table = nullptr, int32_t* pos_out = nullptr);
 int rope_run(void* q, void* k, const int32_t* pos, int rows, int H, int dh, float theta, hipStream_t st);
 int linear_split_plan(int M, int N, int K, size_t max_floats, int* cfg);
 int linear_partial_run(const void* a, const void* w, int M, int N, int K, int ksplit, int cfg, float* partial, hipStream_t st);
@@ -33,15 +33,19 @@ enum MetaSlot { META_SEQ_OFF = 0, META_VIS_START, META_VIS_COUNT, META_VIS_OFF, 
 constexpr int META_STRIDE = STACK_MAX_BATCH + 1;
 constexpr int META_INTS = META_ARRAYS * META_STRIDE;
 
-// prefix sums of the per-sample sizes (one thread: at most 64 samples), the position of every token inside its sample and the (cos, sin) of
-// the token's dh/2 rotary angles there, which the projection epilogue that applies the rotation reads (a thread has one of them)
-__global__ __launch_bounds__(256) void stack_meta_kernel(int32_t* meta, int32_t* pos, BatchSizes sz, int sum_N, int dh, double log2_theta,
-                                                         float2* __restrict__ table) {
+// prefix sums of the per-sample sizes (one thread: at most 64 samples), the position of every token inside its sample (for the caller as well
+// where no merge follows) and the (cos, sin) of the token's dh/2 rotary angles there, which the projection epilogue that applies the
+// rotation reads (a thread has one of them)
+__global__ __launch_bounds__(256) void stack_meta_kernel(int32_t* meta, int32_t* pos, int32_t* pos_out, BatchSizes sz, int sum_N, int dh,
+                                                         double log2_theta, float2* __restrict__ table) {
     const int t = blockIdx.x * 256 + threadIdx.x, half = dh >> 1, row = t / half, c = t - row * half;
     if (row < sum_N) {
         int off = 0, b = 0;
         while (b < sz.B - 1 && row >= off + sz.N[b]) { off += sz.N[b]; ++b; }
-        if (c == 0) pos[row] = row - off;
+        if (c == 0) {
+            pos[row] = row - off;
+            if (pos_out) pos_out[row] = row - off;
+        }
         table[t] = rope_cos_sin(row - off, c, dh, log2_theta);
     }
     if (t == 0) {
@@ -63,6 +67,16 @@ __global__ __launch_bounds__(256) void stack_meta_kernel(int32_t* meta, int32_t*
         meta[META_OUT_OFF * META_STRIDE + sz.B] = oo;
         meta[META_DEC_OFF * META_STRIDE + sz.B] = dof;
     }
+}
+
+// what the caller wants of the merge: nothing is read back from the caller's arrays, so that it does not matter where those lie
+__global__ __launch_bounds__(256) void stack_outputs_kernel(const float* __restrict__ scores, const int32_t* __restrict__ kept,
+                                                            const int32_t* __restrict__ assign, int n_vis, int n_kept, float* scores_out,
+                                                            int32_t* kept_out, int32_t* assign_out) {
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (scores_out && t < n_vis) scores_out[t] = scores[t];
+    if (kept_out && t < n_kept) kept_out[t] = kept[t];
+    if (assign_out && t < n_vis) assign_out[t] = assign[t];
 }
 
 struct StackWs {
@@ -170,13 +184,10 @@ extern "C" int d3tom_stack_step_batch(const void* x, int B, const int32_t* N_h, 
     void *h = base + w.h, *hm = base + w.hm, *nrm = base + w.nrm, *qkv = base + w.qkv;
     void *att = base + w.att, *act = base + w.act;
     float* part = (float*)(base + w.part);
-    // what the caller wants of the merge goes to the caller's arrays at once
-    float* scores = scores_out ? scores_out : (float*)(base + w.scores);
-    int32_t* kept = kept_idx_out ? kept_idx_out : (int32_t*)(base + w.kept);
+    float* scores = (float*)(base + w.scores);
+    int32_t* kept = (int32_t*)(base + w.kept);
     int32_t* slot = (int32_t*)(base + w.slot);
-    int32_t* asg = assign_out ? assign_out : (int32_t*)(base + w.assign);
-    int32_t* pos_out = src_pos ? src_pos : pos;      // positions of the output rows
-    if (!merging) pos = pos_out;
+    int32_t* asg = (int32_t*)(base + w.assign);
     void* sub = base + w.sub;
     const float scale = 1.0f / sqrtf((float)dh);
     if (n_out)
@@ -185,7 +196,7 @@ extern "C" int d3tom_stack_step_batch(const void* x, int B, const int32_t* N_h, 
 
     const double log2_theta = log2((double)theta);
     // (rotary angles: renewed behind the merge, where the positions of the rows change)
-    D3TOM_LAUNCH(STACK_META, st, (stack_meta_kernel<<<(unsigned)(((size_t)sum_N * (dh / 2) + 255) / 256), 256, 0, st>>>(meta, pos, sz, sum_N, dh, log2_theta, rope_cs)));
+    D3TOM_LAUNCH(STACK_META, st, (stack_meta_kernel<<<(unsigned)(((size_t)sum_N * (dh / 2) + 255) / 256), 256, 0, st>>>(meta, pos, merging ? nullptr : src_pos, sz, sum_N, dh, log2_theta, rope_cs)));
 
     const void* cur = x;          // hidden state entering the block (the input itself is never written)
     int n = sum_N;                // its row count
@@ -244,15 +255,18 @@ extern "C" int d3tom_stack_step_batch(const void* x, int B, const int32_t* N_h, 
             void* merged = (post == h) ? hm : h;
             D3TOM_TRY(merge_run(post, merged, nullptr, nullptr, nullptr, d, d, D3TOM_BF16, B, M(META_SEQ_OFF), M(META_VIS_START),
                                 M(META_VIS_COUNT), M(META_VIS_OFF), kept, M(META_KEPT_OFF), max_N, max_V, max_keep,
-                                max_pruned, max_out, mode, M(META_OUT_OFF), asg, nullptr, pos_out, sub, w.sub_bytes, st, prepared));
-            // from here on every stage sees the shortened sequences; pos_out holds the original positions
+                                max_pruned, max_out, mode, M(META_OUT_OFF), asg, nullptr, pos, sub, w.sub_bytes, st, prepared));
+            if (scores_out || kept_idx_out || assign_out)
+                D3TOM_LAUNCH(STACK_META, st, (stack_outputs_kernel<<<ceil_div(sum_V, 256), 256, 0, st>>>(
+                    scores, kept, asg, sum_V, sum_out - (sum_N - sum_V), scores_out, kept_idx_out, assign_out)));
+            // from here on every stage sees the shortened sequences; pos holds the original positions
             ht = merged;
             n = sum_out;
             longest = max_out;
             cu = M(META_OUT_OFF);
         }
         if (!ffn_nrm_ready)
-            D3TOM_TRY(rmsnorm_run(ht, b.ffn_norm, n, d, eps, nrm, st, pos_out, dh, log2_theta, merge_here ? rope_cs : nullptr));
+            D3TOM_TRY(rmsnorm_run(ht, b.ffn_norm, n, d, eps, nrm, st, pos, dh, log2_theta, merge_here ? rope_cs : nullptr, merge_here ? src_pos : nullptr));
         D3TOM_TRY(linear_run(nrm, b.w_gate_up, n, 2 * F, d, LIN_SWIGLU, nullptr, act, 0, 0, st));
         void* outp = last ? y : ht;                  // in place, except that the last block writes the caller's y
         const int ks_d = linear_split_plan(n, d, F, STACK_PARTIAL_BYTES / sizeof(float), &cfg_d);

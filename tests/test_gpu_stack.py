@@ -538,6 +538,25 @@ def test_stack_step_rejects(B):
             assert e.value.status == B.D3TOM_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("merging", [True, False])
+@pytest.mark.parametrize("merge_layer", [1, 2, 3])
+def test_stack_step_optional_outputs_are_only_written(B, merge_layer, merging):
+    """A caller who has no use for the optional outputs may pass one array for all of them: they spoil each other and nothing else."""
+    case = W.stack_case(83, L=3, d=256, H=4, F=512, P=6, V=300, O=9, D=4, std=1.0 / 16, gain_jitter=0.1)
+    gb = _gpu_blocks(case)
+    x, arr = _dev(case["x"]), B.block_weights(gb)
+    dec = torch.from_numpy(case["dec_idx"]).cuda() if merging else None
+    ws = B.workspace(B.d3tom_stack_workspace_bytes(case["N"], 256, 4, 512, 300, 4))
+    dummy = torch.zeros(case["N"], dtype=torch.int32, device="cuda")
+    ys = []
+    for extra in (dict(), dict(src_pos=dummy, scores=dummy.view(torch.float32), kept_idx=dummy, assign=dummy)):
+        y = torch.zeros_like(x)
+        n = B.d3tom_stack_step(x, 4, 512, arr, 3, merge_layer, dec, 4 if merging else 0, 6, 300, 120, 0, 1e-5, 10000.0, y, ws, **extra)
+        torch.cuda.synchronize()
+        ys.append(y[:n].clone())
+    assert torch.equal(*ys)
+
+
 # ---- full-size shapes (hidden 4096, 32 x 128 heads, SwiGLU 11008, 3645 + 64 + 64 tokens) --------------------
 def _full_size(B, L):
     cfg = dict(W.STACK_3645, L=L)
