@@ -617,6 +617,7 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     // log2-sum-exp2, +inf for rows past the sample's deciders and the block's rows; the rows of a thread side by side
     extern __shared__ __attribute__((aligned(16))) float c_lds[];
     __shared__ float red[IMP_FL_THREADS / 64][16];
+    __shared__ int odd[IMP_FL_THREADS / 64];            // a wave met a row of the sample whose sum of exponentials is not finite
     // thread (key = t % 16, group = t / 16) takes rows group, group + 64, ... of the block's H x max_D logit rows: 64
     // consecutive rows are 4 KB in one piece.  They, the statistics and the sample's offsets are requested together (they come from another
     // XCD's writes, i.e. from memory): no request depends on an offset, what a sample does not have is left out when it is there.
@@ -647,28 +648,32 @@ __global__ __launch_bounds__(IMP_FL_THREADS) void imp_scores_from_logits(
     if (D <= 0 || key0 >= vs + V || key0 + 16 <= vs || key0 >= N) return;
     const int nch = min((N + KC - 1) / KC, NCH);
     const int padded = (rows + PASS - 1) / PASS * PASS;
+    bool bad = false;
     for (int t0 = wave0; t0 < padded;) {
         const int t = t0 + ((int)threadIdx.x & 63);
         float c = INFINITY;
         if (t0 < rows) {
             const float lse = imp_lse<true>(a, p, nch, NCH, DPAD);
             c = t < rows && i < D ? lse : INFINITY;
+            bad |= t < rows && i < D && !(lse < INFINITY);
         }
         c_lds[t / PASS * PASS + (t % IMP_FL_GROUPS) * IMP_FL_ROWS + t % PASS / IMP_FL_GROUPS] = c;
         t0 += IMP_FL_THREADS;
         if (t0 < rows) statistics(min(t0 + ((int)threadIdx.x & 63), rows - 1));
     }
+    odd[threadIdx.x >> 6] = __builtin_amdgcn_ballot_w64(bad) != 0;
     __syncthreads();
     float acc = 0.f;
     // (16 waves on four SIMDs: an instruction for every row of every thread is 20 clocks x 16.  Most samples have all of the launch's rows.)
-    const bool whole = D == max_D && rows == padded;
+    const bool whole = D == max_D && rows == padded && __builtin_amdgcn_ballot_w64(odd[threadIdx.x & 15] != 0) == 0;
     auto add_rows = [&](int r0) {
         const float* c = c_lds + r0 + grp * IMP_FL_ROWS;
         if (whole) {
 #pragma unroll
             for (int u = 0; u < IMP_FL_ROWS; ++u) acc += __builtin_amdgcn_exp2f(l[u] - c[u]);
         } else {
-            // a row past the sample's deciders was never written: whatever it holds must not reach the sum
+            // a row past the sample's deciders was never written: whatever it holds must not reach the sum (nor does a row whose logits went
+            // beyond float32)
 #pragma unroll
             for (int u = 0; u < IMP_FL_ROWS; ++u) acc += (c[u] < INFINITY) ? __builtin_amdgcn_exp2f(l[u] - c[u]) : 0.f;
         }
@@ -772,7 +777,7 @@ __global__ __launch_bounds__(THREADS) void imp_stats_generic(
     }
     for (int j0 = wave * 64; j0 < kept; j0 += THREADS) {
         const int j = j0 + wave_dots_row(lane);
-        if (j < kept) row[j] = exp2f((j0 < THREADS ? first : row[j]) - c);
+        if (j < kept) row[j] = c < INFINITY ? exp2f((j0 < THREADS ? first : row[j]) - c) : 0.f;      // (a row whose logits went beyond float32 adds nothing)
     }
 }
 

@@ -203,6 +203,28 @@ def test_importance_chunk_of_infinite_logits(dtype, H, dh, D, N, copies):
         np.testing.assert_array_equal(S[i], S[len(batch) - len(samples) + i])
 
 
+@pytest.mark.parametrize("dtype,H,dh,D", [("bf16", 8, 64, 8), ("bf16", 4, 128, 16), ("bf16", 16, 128, 16), ("bf16", 32, 64, 32), ("bf16", 5, 128, 7),
+                                          ("f32", 4, 64, 16), ("f32", 5, 36, 13), ("bf16", 3, 40, 9)])
+def test_importance_rows_beyond_float32_add_nothing(dtype, H, dh, D):
+    """Small decider sets: a (head, decider) row whose logits overflow leaves no mark on the scores, whether the sample has all of the rows
+    that the launch is unrolled for or not (two samples, the second with fewer deciders)."""
+    samples = []
+    for N, n in ((90, D), (70, max(1, D - 3))):
+        s = W.random_case(695 + N, N, H * dh, H, 2, N - 2 - n, n, dtype=dtype)
+        s["q"][s["dec_idx"][n // 2], H - 1] = np.float32(2.0 ** 127)
+        samples.append(s)
+    for batch in (samples, samples[:1]):
+        S = GpuStep(batch, [4] * len(batch), dtype).importance()
+        for got, s in zip(S, batch):
+            dec = s["dec_idx"]
+            z = np.einsum("ihc,jhc->hij", s["q"][dec].astype(np.float64), s["k"].astype(np.float64)) / np.sqrt(dh)
+            z[H - 1, len(dec) // 2] = 0.0
+            e = np.exp(z - z.max(-1, keepdims=True))
+            prob = e / e.sum(-1, keepdims=True)
+            prob[H - 1, len(dec) // 2] = 0.0
+            check_scores(got, prob.sum((0, 1))[s["vis_start"]:s["vis_start"] + s["V"]] / H)
+
+
 @pytest.mark.parametrize("dtype,H,dh", [("f32", 4, 64), ("f32", 3, 36), ("bf16", 2, 40), ("f32", 400, 8)])
 def test_importance_generic_kept_logits(dtype, H, dh):
     """Generic kernels: decider counts around the largest set that keeps its logits, key counts around blocks of 16 and 256; with
