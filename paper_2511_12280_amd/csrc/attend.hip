@@ -1047,11 +1047,14 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
         // (every fragment read from LDS feeds one MFMA instead of two; 32 heads, narrow against wide: 1024 keys 21.9 us against 30.9,
         // one round each; 1198 keys 44.7 against 35.7, two to one; 3773 keys 255 against 210, four to two; 2100 keys 106 against
         // 111, 3 x 1000 keys 60.9 against 64.9, three to two); with heads of 64 two workgroups of 128 queries share a CU, and it costs
-        // 0.52 (16 heads, 3500 keys: 69.2 against 65.9, two to one; 8 x 560 keys: 22.1 against 28.9, one to one).  In a batch, whose samples may all
-        // but one be shorter than the bound, two rounds against one go to the narrow tiles there (the 116 of those batches that it changes: 1.08 x on
-        // average, 0.86 to 1.43).
+        // 0.52 (16 heads, 3500 keys: 69.2 against 65.9, two to one; 8 x 560 keys: 22.1 against 28.9, one to one).  That holds for one sample.  A batch
+        // with heads of 64 takes 128-query tiles always: its samples may all but one be shorter than the bound, and neither the rounds nor the bound say
+        // by how much.  6028 drawn batches (2 to 48 samples, the longest of 170 to 8000 keys, the others as long, or from a half, a third or an
+        // eighth of it on, 8 to 32 heads): 0.993 of the better width's speed, 0.75 at the least; by rounds, as for one sample, 0.955 and 0.58.  Where
+        // the rounds speak for 256 queries, wide against narrow in the mean: samples of one length 0.95 to 1.01, ragged ones 0.71 to 1.02 (above
+        // 1.00 from 13 rounds on).
         const long wide = (ceil_div(max_seqlen, 256) * heads + 255) / 256, narrow = (ceil_div(max_seqlen, 128) * heads + 255) / 256;
-        const int nq = split || (dh == 128 ? 66 : B > 1 ? 49 : 55) * narrow < 100 * wide ? 1 : 2;
+        const int nq = split || (dh == 64 && B > 1) || (dh == 128 ? 66 : 55) * narrow < 100 * wide ? 1 : 2;
         const int nqt = ceil_div(max_seqlen, split ? 64 : nq * 128);
         // Several rounds of workgroups that have a compute unit to themselves: one per unit, which takes its tiles in turn, samples by
         // falling length (one tile per workgroup / in turn: 16 x 700 .. 1505 keys 440 / 422 us, 4 x 575 .. 1951 141 / 133, 12 x 270 .. 800
