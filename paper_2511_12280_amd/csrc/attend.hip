@@ -19,8 +19,8 @@
 // shape lets another wave's vector instructions through: per tile 1058 clocks of MFMAs and 756 of softmax arithmetic (an fma,
 // an exp2 and half a conversion per logit) of the other wave take 1250 clocks together, whereas beside MFMA 32x32x16 the exponentials do not issue at all (1029 + 756 -> 1780).
 // Measured at 32 heads of 128 (four independent waves on the larger shape before): 3773 keys 240 -> 210 us, 1951 keys
-// 71 -> 62 us, 4096 keys 270 -> 235 us = 1170 TFLOP/s; 16 heads of 64, 4 x 2000 keys: 83 us either way, half as many MFMAs beside
-// the same softmax arithmetic.
+// 71 -> 62 us, 4096 keys 270 -> 235 us = 1170 TFLOP/s; 16 heads of 64, 4 x 2000 keys on 256-query tiles: 83 us either way, half as many
+// MFMAs beside the same softmax arithmetic.
 //
 // K and V tiles go HBM/L2 -> LDS with direct loads (buffer_load ... lds, no register staging; rows past the end of the sample
 // load as zeros through the buffer bounds check) into a ring; rows are unpadded and their 16-byte chunks XOR-swizzled by the
@@ -29,7 +29,7 @@
 //
 // The softmax arithmetic paces the loop (every MFMA of the other wave takes 8 clocks of the vector issue port as well), so its
 // wave has the higher priority (3773 keys 207.8 -> 205.4 us against priority for the MFMAs, 4 x 2000 keys with heads of 64
-// 84.9 -> 82.1), and it is cut to what the results need: per logit one fma, one exp2, one addition and the packing to bf16, and
+// 84.9 -> 82.1, 256-query tiles), and it is cut to what the results need: per logit one fma, one exp2, one addition and the packing to bf16, and
 //   - the weights and the tail mask of the weighted form enter as the C operand of S^T (log2 w / scale2, -inf);
 //   - the running maximum costs one max3 per two logits: a lane compares its own logits with the column's maximum, and only where one
 //     of them exceeds it do the four lanes meet and the accumulators of that block of 16 queries get their new scale.
@@ -44,7 +44,7 @@
 // their probabilities, so that the two kernels give a merge other near-ties: in stack steps of 1000 to 3700 tokens several
 // tokens then go to another near-duplicate.
 //
-// The generic path (float32 or any head size) is one workgroup per (query, head) with a chunked
+// The generic path (float32 or any head size) is one workgroup per query, or in float32 per two queries, and head, with a chunked
 // online softmax in plain float arithmetic.
 #include "common.hpp"
 #include "direct_load.hpp"

@@ -160,8 +160,9 @@ __global__ __launch_bounds__(512, 2) void linear_bf16_kernel(
         w_addr[kk] = NA * C::A_BYTES + (wcol * 16 * TN + q) * 128 + (((kk * 4 + g) ^ (((q >> 1) & 1) | ((r >> 2) << 1))) << 4);
     }
     // The columns of a fragment row are taken there and those of the next one back, so that every MFMA has an operand in common with the one
-    // before it: less switching, and the card is power bound (256 x 256 tiles at 3773 rows 278.7 -> 276.3 us, 160 x 256 at 2100 rows
-    // and 11008 channels 166.3 -> 164.3, 256 x 128 with loading waves at 3773 rows 310.6 -> 308.9; short launches 0 to 0.5 %).
+    // before it: less switching, and the card is power bound (3773 rows, 256 x 256 tiles, 12288 columns of 4096 279.6 -> 276.1 us, 4096
+    // of 11008 242.2 -> 238.5, with 256 x 128 tiles and loading waves 268.6 -> 265.7; 160 x 256 at 2100 rows 166.1 -> 165.6, as much as two runs
+    // differ; short launches -0.4 to 0.9 %).
     auto there_and_back = [](int i, int j) { return (i & 1) ? TN - 1 - j : j; };
     bf16x8 af[2][TM], wf[2][TN];
     if constexpr (WC == 4) {

@@ -159,7 +159,7 @@ __device__ __forceinline__ int band_height(int RB, int per_b, int per, int nrt_b
 // the kernel derives the pruned tokens from the kept list itself and writes the pruned list and the kept tokens' table entries
 // for the kernels behind it: no norms launch (4 of the 21 us that a merge of 356 tokens takes).  The norms are summed here whether
 // or not the selection launch has left others: near-ties of two cosines go by their last bits, and the one call and the
-// separate calls have to agree.
+// separate calls agree on them where their bounds on the kept and pruned counts give the same number of slices (tight bounds do).
 template <int TM, int CBK, bool SPLIT>     // CBK: 16-column blocks of a wave
 __global__ __launch_bounds__(512) void cos_argmax_bf16(
     const uint16_t* __restrict__ f, int d, const int32_t* __restrict__ seq_off, const int32_t* __restrict__ vis_start,

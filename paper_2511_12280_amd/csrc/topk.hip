@@ -11,7 +11,7 @@
 // Bound by its chain of barriers on one compute unit: this takes 9 of them.  (A digit-by-digit radix selection with one
 // histogram per wave and keys in LDS took about 25: 8.0 us instead of 5.7 at 729 keys, 13.1 instead of 9.9 at 16 x 2304.)  Between them
 // exchanges and sums stay in the vector ALU, and the members are ranked sixteen lanes to each (729 keys 5.4 -> 4.4 us, 16 x 2304 8.6 -> 7.8).
-// A kernel of a few us also pays for the code that it fetches: unrolled for 1, 4 or 16 keys a thread it is 7, 12 or 32 KB (the last one for
+// A kernel of a few us also pays for the code that it fetches: unrolled for 1, 4 or 16 keys a thread it is 7, 11 or 27 KB (32 KB for
 // all sizes against these: 144 keys 4.8 -> 4.2 us, 729 4.6 -> 3.9, 1024 beside streamed rows 6.0 -> 5.0, 3645 8.4 -> 7.5).  And with 16 waves
 // on four SIMDs every instruction that all of them execute costs 20 clocks: what the waves have to tell each other is combined by the lanes of
 // a row, waves without members skip the ranking, bins are found with one comparison (144 keys 3.7 -> 3.4, 1024 4.1 -> 3.6, 3645 6.4 -> 5.3; with 4 or 8

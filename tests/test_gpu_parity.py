@@ -227,8 +227,8 @@ def test_importance_rows_beyond_float32_add_nothing(dtype, H, dh, D):
 
 @pytest.mark.parametrize("dtype,H,dh", [("f32", 4, 64), ("f32", 3, 36), ("bf16", 2, 40), ("f32", 400, 8)])
 def test_importance_generic_kept_logits(dtype, H, dh):
-    """Generic kernels: decider counts around the largest set that keeps its logits, key counts around blocks of 16 and 256; with
-    400 heads the statistics of 32 deciders no longer fit beside them."""
+    """Generic kernels: decider counts around the largest set whose first sweep leaves its probabilities (larger ones form their logits
+    again), key counts around blocks of 16 and 256; with 400 heads more rows than the kept logits of the MFMA path may have."""
     shapes = [(40, 16, 1), (257, 239, 32), (256, 17, 5)]                   # tokens, visual, deciders
     for extra in (0, 1):
         samples = [W.random_case(640 + i, N, H * dh, H, 3, V, D + extra, dtype=dtype) for i, (N, V, D) in enumerate(shapes)]
@@ -260,9 +260,12 @@ def test_importance_generic_one_key_has_the_row(dtype, H, dh, D):
 
 
 @pytest.mark.parametrize("dtype,H,dh,D", [("bf16", 8, 64, 8), ("bf16", 5, 128, 13), ("bf16", 16, 64, 16), ("bf16", 257, 64, 1), ("bf16", 64, 64, 16),
-                                          ("bf16", 35, 64, 31), ("f32", 4, 64, 16), ("f32", 5, 36, 13), ("f32", 8, 32, 32), ("f32", 9, 32, 29)])
+                                          ("bf16", 35, 64, 31), ("bf16", 384, 64, 32), ("bf16", 385, 64, 32), ("bf16", 97, 128, 32),
+                                          ("f32", 4, 64, 16), ("f32", 5, 36, 13), ("f32", 8, 32, 32), ("f32", 9, 32, 29)])
 def test_importance_rows_per_thread(dtype, H, dh, D):
-    """(head, decider) rows around what one, four and sixteen a thread take: 64, 65, 256, 257, 1024 and 1085 of them."""
+    """(head, decider) rows around what one, four and sixteen a thread take: 64, 65, 256, 257, 1024 and 1085 of them; 3104 and 12288 in several
+    passes, the latter the most whose statistics fit into LDS, and 12320, which take a second sweep over the keys.  In float32 as many
+    rows of probabilities for the generic path's sums."""
     samples = [W.random_case(690 + N, N, H * dh, H, 2, N - 2 - n, n, dtype=dtype) for N, n in ((70, D), (49, 1))]
     S = GpuStep(samples, [4, 4], dtype).importance()
     for i, s in enumerate(samples):
@@ -731,6 +734,21 @@ def test_merge_slices_of_the_contraction(d, shapes):
     for b, s in enumerate(samples):
         check_assign(out["assign"][b], s["x"], s["vis_start"], s["V"], kept[b])
         check_merge({key: out[key][b] for key in out}, s["x"], s["vis_start"], s["V"], kept[b], "bf16")
+
+
+def test_merge_bounds_that_split_the_contraction_differently():
+    """A ragged batch whose tight bounds on kept and pruned counts (separate calls) cut the contraction into slices while the looser ones of the one
+    call do not: the sums' last bits may differ then, and both are held to the oracle's rule for near-ties."""
+    shapes = [(4, 1000, 6, 3, 0.9), (9, 300, 5, 2, 0.1)]
+    samples = [W.random_case(860 + i, P + V + O, 2048, 16, P, V, D, dtype="bf16", centres=V // 6) for i, (P, V, O, D, _) in enumerate(shapes)]
+    ratios = [r for *_, r in shapes]
+    ref = GpuStep(samples, [oracle.keep_count(s["V"], r) for s, r in zip(samples, ratios)], "bf16")
+    assert ref.lay.max_pruned == 270 and ref.lay.max_V - min(ref.lay.keep) == 970
+    S = ref.importance(); kept, slot = ref.select_topk(); mout = ref.merge()
+    S1, kept1, m1 = ref.merge_layer(ratios)
+    for b in range(len(samples)):
+        check_full_sample(ref, b, S, kept, slot, mout)
+        check_full_sample(ref, b, S1, kept1, slot, m1)
 
 
 @pytest.mark.parametrize("dtype,H,dh,V,D", [

@@ -406,7 +406,8 @@ def _merge_block_inputs(B, case, l_star, eps=1e-5, theta=10000.0):
     """What the merge layer of block l_star sees on the GPU: the block's rotated q, k and its post-attention
     hidden state, rebuilt from the same entry points in the same order (the kernels are deterministic, so
     these are the very values inside d3tom_stack_step, up to the order of the float32 sums of an output projection
-    that the step cuts along its contraction)."""
+    that the step cuts along its contraction, and of the attention above 512 tokens, where the step does without the 64-query tiles that
+    d3tom_attend takes for few heads)."""
     N, d, H, F, V = case["N"], case["d"], case["H"], case["F"], case["V"]
     dh = d // H
     x = _dev(case["x"])
@@ -496,6 +497,28 @@ def test_spellings_of_the_unmerged_model_agree(B, V):
     plain = _run_stack(B, case, 10, 0, D=0)
     for got in (_run_stack(B, case, 10, 2, D=0), _run_stack(B, case, 10, 1, D=0), _run_stack(B, case, 10, 0), _run_stack(B, case, V, 1)):
         np.testing.assert_array_equal(got["y"], plain["y"])
+
+
+@pytest.mark.parametrize("n,others", [(600, [520, 777, 600] * 5), (530, [1500]), (700, [3, 40, 513])])
+def test_rows_of_a_sample_do_not_depend_on_its_companions(B, n, others):
+    """Above 512 tokens the unmerged blocks of a stack give a sample the same bits alone (few tiles of queries) and in a batch (more and wider
+    ones): what a merge decides near-ties by does not move with the number of samples."""
+    d, H, F = 256, 4, 320
+    case = W.stack_case(84, L=2, d=d, H=H, F=F, P=8, V=n - 20, O=12, D=3, std=1.0 / 16, gain_jitter=0.1)
+    gb = _gpu_blocks(case)
+    arr = B.block_weights(gb)
+    x = _dev(case["x"])
+    outs = []
+    for rest in ([], others):
+        N = rest + [n]
+        rows = torch.cat([torch.randn(sum(rest), d, device="cuda").to(torch.bfloat16), x])
+        y = torch.zeros_like(rows)
+        ws = B.workspace(B.d3tom_stack_batch_workspace_bytes(len(N), sum(N), max(N), d, H, F, 0, 0, 1))
+        z = [0] * len(N)
+        B.d3tom_stack_step_batch(rows, N, H, F, arr, 2, 0, None, z, z, z, z, 0, 1e-5, 10000.0, y, ws)
+        torch.cuda.synchronize()
+        outs.append(y[-n:].clone())
+    assert torch.equal(*outs)
 
 
 def test_stack_step_sum_mode(B):
