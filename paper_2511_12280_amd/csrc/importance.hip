@@ -291,10 +291,13 @@ __global__ __launch_bounds__(256, 2) void imp_stats_bf16(
         float m = a[0].x, z = 0.f;
 #pragma unroll
         for (int w = 1; w < 16; ++w) m = fmaxf(m, a[w].x);
-        const float ref = (m == -INFINITY) ? 0.f : m;                   // every logit of the chunk is -inf: it counts as empty, (-inf, 0)
+        // Every logit of the chunk is -inf or NaN: it counts as empty, (-inf, 0), so that a row of NaN alone has no sum, -inf for its logarithm and
+        // NaN for its probabilities.
+        const bool empty = !(m > -INFINITY);
+        const float ref = empty ? 0.f : m;
 #pragma unroll
         for (int w = 0; w < 16; ++w) z += a[w].y * __builtin_amdgcn_exp2f(a[w].x - ref);
-        part[((size_t)(b * H + h) * NCH + chunk) * DPAD + b0 * 16 + t] = make_float2(m, z);
+        part[((size_t)(b * H + h) * NCH + chunk) * DPAD + b0 * 16 + t] = empty ? make_float2(-INFINITY, 0.f) : make_float2(m, z);
     }
     }
 }

@@ -225,6 +225,24 @@ def test_importance_rows_beyond_float32_add_nothing(dtype, H, dh, D):
             check_scores(got, prob.sum((0, 1))[s["vis_start"]:s["vis_start"] + s["V"]] / H)
 
 
+@pytest.mark.parametrize("fill", [np.nan, np.inf])
+@pytest.mark.parametrize("dtype,H,dh,D", [("bf16", 8, 64, 8), ("bf16", 16, 128, 16), ("bf16", 5, 128, 7), ("bf16", 3, 64, 40), ("f32", 4, 64, 16),
+                                          ("bf16", 3, 40, 9), ("f32", 3, 36, 40)])
+def test_importance_row_of_nan_reaches_the_scores(dtype, H, dh, D, fill):
+    """A decider whose logits in one head are all NaN (NaN in its query, or infinities that cancel) makes its sample's scores NaN and no other's,
+    whether the sample has all rows that the launch is unrolled for or not, with one chunk of keys and with several."""
+    samples = []
+    for N, n in ((90, D), (70, max(1, D - 3)), (1300, D)):
+        s = W.random_case(697 + N, N, H * dh, H, 2, N - 2 - n, n, dtype=dtype)
+        s["q"][s["dec_idx"][n // 2], H - 1] = fill
+        samples.append(s)
+    samples.append(W.random_case(698, 60, H * dh, H, 2, 58 - D, D, dtype=dtype))
+    for batch in (samples, samples[:1], samples[2:3]):
+        S = GpuStep(batch, [4] * len(batch), dtype).importance()
+        for got, s in zip(S, batch):
+            assert np.isnan(got).all() if s is not samples[-1] else np.isfinite(got).all()
+
+
 @pytest.mark.parametrize("dtype,H,dh", [("f32", 4, 64), ("f32", 3, 36), ("bf16", 2, 40), ("f32", 400, 8)])
 def test_importance_generic_kept_logits(dtype, H, dh):
     """Generic kernels: decider counts around the largest set whose first sweep leaves its probabilities (larger ones form their logits
