@@ -19,17 +19,35 @@
 // shape lets another wave's vector instructions through: per tile 1058 clocks of MFMAs and 756 of softmax arithmetic (an fma,
 // an exp2 and half a conversion per logit) of the other wave take 1250 clocks together, whereas beside MFMA 32x32x16 the exponentials do not issue at all (1029 + 756 -> 1780).
 // Measured at 32 heads of 128 (four independent waves on the larger shape before): 3773 keys 240 -> 210 us, 1951 keys
-// 71 -> 62 us, 4096 keys 270 -> 235 us = 1170 TFLOP/s; 16 heads of 64, 4 x 2000 keys on 256-query tiles: 83 us either way, half as many
+// 71 -> 62 us; 16 heads of 64, 4 x 2000 keys on 256-query tiles: 83 us either way, half as many
 // MFMAs beside the same softmax arithmetic.
+//
+// What both waves of a SIMD share is the port of the vector instructions.  An MFMA of 17.4 clocks keeps the other wave's from it for 9.6, the
+// softmax arithmetic of a tile takes 740 (an exp2 or a conversion of a pair 8 clocks, others 4) and 190 more for each block of 16 queries whose
+// maximum moves.  What costs more than its share is an instruction of that kind in an MFMA phase: it waits behind the exponentials of the
+// other wave, and the MFMAs behind it wait as well (with the eight additions of a tile's V addresses the first product took 870 or 1270
+// clocks, the latter where the other wave had no accumulators to rescale first).  And a barrier makes four SIMDs wait for the one with the most to rescale.  So
+//   - the fragments' addresses move on in the softmax phase, and are few: K and V tiles lie in LDS in parts of 64 dims, whose k-steps and blocks differ
+//     by constants that go into the instructions, so that six addresses serve a stage instead of twelve;
+//   - the loads' addresses are constants, the way from tile to tile is in the buffer descriptors and done by the scalar unit in the MFMA phase;
+//   - the exponentials are held inside the phase (the compiler put them behind its end, out of its priority and behind a wait for loads);
+//   - both blocks' maxima are there before the first branch on one, and those of four lanes are plain v_max (fmaxf also quiets each operand);
+//   - a tile has one barrier, in front of group 0's softmax phase and group 1's MFMA phase, not two: inside a tile the waves of a SIMD find
+//     their turns by themselves (groups that share their queries have a ring each and need both).
+// 32 heads of 128: 3773 keys 210 -> 203 us, 4 x 493 .. 1951 weighted 130 -> 124, 16 x 600 .. 1500 369 -> 356, 1951 60.7 -> 57.9, 1000 21.9 -> 21.0; 8 heads,
+// 900 keys 11.95 -> 10.95; 16 heads of 64, 900 keys 9.35 -> 8.55, 4 x 2000 85.4 -> 83.0.  (The one barrier alone 1.02 to 1.04.  Without effect or worse: twelve
+// addresses moved in the softmax phase, 1.00 and in short chains of phases 1.03; descriptors made up in front of the loads, short chains 0.96; stages unrolled
+// in pairs, which spills; O not transposed, so that only the rows of queries whose maximum moved are rescaled, 0.95 to 0.99 and 0.83 in short chains; loads behind
+// the MFMAs or behind the maxima, 0.98 to 1.00.)
 //
 // K and V tiles go HBM/L2 -> LDS with direct loads (buffer_load ... lds, no register staging; rows past the end of the sample
 // load as zeros through the buffer bounds check) into a ring; rows are unpadded and their 16-byte chunks XOR-swizzled by the
 // row index instead.  Loads are issued in the softmax phase, and the first K fragments of a tile are read there, so that the
 // MFMA phase starts at once.
 //
-// The softmax arithmetic paces the loop (every MFMA of the other wave takes 8 clocks of the vector issue port as well), so its
-// wave has the higher priority (3773 keys 207.8 -> 205.4 us against priority for the MFMAs, 4 x 2000 keys with heads of 64
-// 84.9 -> 82.1, 256-query tiles), and it is cut to what the results need: per logit one fma, one exp2, one addition and the packing to bf16, and
+// The softmax arithmetic paces the loop, so its wave has the higher priority (against none, and the MFMAs before it: 8 heads, 900 keys 11.0, 12.0, 12.9 us; 16
+// heads of 64, 900 keys 8.5, 9.5, 10.1; 32 heads, 1000 keys 20.9, 21.1, 21.5; several rounds the same), and it is cut to what the results need: per logit one
+// fma, one exp2, one addition and the packing to bf16, and
 //   - the weights and the tail mask of the weighted form enter as the C operand of S^T (log2 w / scale2, -inf);
 //   - the running maximum costs one max3 per two logits: a lane compares its own logits with the column's maximum, and only where one
 //     of them exceeds it do the four lanes meet and the accumulators of that block of 16 queries get their new scale.
@@ -62,18 +80,25 @@ typedef __attribute__((__vector_size__(4 * sizeof(short)))) short att_short4;
 // 4 keys x 16 dims of a row-major LDS tile, transposed on the way to the registers: within each group
 // of 16 lanes, lanes 4j..4j+3 point at 4 x 4 consecutive elements of row j, and lane i receives
 // column i of that 4 x 16 block (ds_read_b64_tr_b16).
-__device__ __forceinline__ att_short4 lds_read_tr16(const char* p) {
+template <typename P>           // a generic pointer into LDS or one of its address space
+__device__ __forceinline__ att_short4 lds_read_tr16(P p) {
     typedef __attribute__((address_space(3))) att_short4* lp;
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)p);
 }
 
 #if defined(__HIP_DEVICE_COMPILE__)
+// the larger of two values that are no signalling NaN (fmaxf: two instructions more, which quiet its operands)
+__device__ __forceinline__ float att_max(uint32_t a, uint32_t b) {
+    float m;
+    asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));
+    return m;
+}
 // the two lanes (l, l ^ 32) that share a query column combine their values: after the swap of the upper
 // half of one copy with the lower half of the other, the two results hold {own, partner} in some order
 __device__ __forceinline__ float att_pair_max(float x) {
     typedef unsigned att_u2 __attribute__((ext_vector_type(2)));
     const att_u2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    return att_max(r[0], r[1]);
 }
 __device__ __forceinline__ float att_pair_sum(float x) {
     typedef unsigned att_u2 __attribute__((ext_vector_type(2)));
@@ -84,7 +109,7 @@ __device__ __forceinline__ float att_pair_sum(float x) {
 __device__ __forceinline__ float att_quad_max(float x) {
     typedef unsigned att_u2 __attribute__((ext_vector_type(2)));
     const att_u2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return att_pair_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+    return att_pair_max(att_max(r[0], r[1]));
 }
 __device__ __forceinline__ float att_quad_sum(float x) {
     typedef unsigned att_u2 __attribute__((ext_vector_type(2)));
@@ -125,10 +150,13 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int KS = DH / 32;                 // k-steps of the first product
     constexpr int DB = DH / 16;                 // 16-dim blocks of O^T
-    constexpr int ROWB = DH * 2;                // bytes per K / V row in LDS (unpadded, chunks swizzled)
+    constexpr int ROWB = DH * 2;                // bytes per row of q, k, v and o
     constexpr int NCHK = DH / 8;                // 16-byte chunks per row
-    constexpr int RPI = 64 / NCHK;              // rows covered by one wave-wide direct load (1 KB)
-    constexpr int LD = ATT_BK / ((SPLIT ? 4 : 8) * RPI);        // direct loads per wave and operand tile
+    constexpr int RPI = 64 / NCHK;              // rows of q or o covered by one wave-wide access (1 KB)
+    constexpr int HALVES = DH / 64, PARTB = 128;        // K and V tiles lie in LDS in parts of 64 dims: 64 rows of 128 bytes, unpadded, chunks swizzled
+    constexpr int PART = ATT_BK * PARTB;
+    constexpr int LROWS = SPLIT ? 2 : 1;        // groups of 8 rows that a wave loads of each part, one direct load (1 KB) each
+    constexpr int LD = LROWS * HALVES;          // direct loads per wave and operand tile
     constexpr int TILE = ATT_BK * ROWB;         // bytes of one K (or V) tile
     constexpr int STAGE = 2 * TILE;             // stage j: K of tile j, V of tile j - 1
     constexpr int NS = ATT_SLOTS;
@@ -230,7 +258,12 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     auto rows_of = [&](const uint16_t* p) {
         return make_uniform_rsrc(p + (size_t)tok0 * rs + (size_t)h * DH, (uint32_t)(((size_t)(n - 1) * rs + DH) * 2));
     };
-    __amdgpu_buffer_rsrc_t rk = rows_of(k), rv = rows_of(v), rq = rows_of(q);
+    __amdgpu_buffer_rsrc_t rq = rows_of(q);
+    // this head's first byte in q, k, v and o, and the bytes from there to its end in the sample's last row
+    size_t head_at;
+    uint32_t head_bytes;
+    auto place_head = [&] { head_at = ((size_t)tok0 * rs + (size_t)h * DH) * 2; head_bytes = (uint32_t)(((size_t)(n - 1) * rs + DH) * 2); };
+    place_head();
 
     int q0 = qt * BQ + wq * NQ * 16;            // this wave's first query
     bf16x8 qf[NQ][KS];
@@ -249,49 +282,85 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 
     // direct loads: lane -> (row, chunk position).  The chunk fetched into position p of row x is p ^ f(x): K fragments are 16
     // consecutive rows of one chunk, transposing reads of V four consecutive rows (per 16 lanes) of one 32-byte piece.
-    int k_off[LD], v_off[LD];                   // byte offsets inside the head's K / V for key0 = 0
+    int k_off[LROWS], v_off[LROWS];             // byte offsets inside the head's K / V for key0 = 0; the second part of a row lies 128 bytes on
 #pragma unroll
-    for (int i = 0; i < LD; ++i) {
-        const int x = (wq * LD + i) * RPI + lane / NCHK, pos = lane % NCHK;
-        k_off[i] = x * row_bytes + ((pos ^ (DH == 128 ? (x & 15) : ((x >> 1) & 7))) << 4);
-        v_off[i] = x * row_bytes + ((pos ^ (DH == 128 ? (x & 7) << 1 : ((x >> 1) & 3) << 1)) << 4);
+    for (int i = 0; i < LROWS; ++i) {
+        const int x = (wq * LROWS + i) * 8 + (lane >> 3), pos = lane & 7;
+        k_off[i] = x * row_bytes + ((pos ^ ((x >> 1) & 7)) << 4);
+        v_off[i] = x * row_bytes + ((pos ^ (((x >> 1) & 3) << 1)) << 4);
     }
     const uint32_t ring0 = (uint32_t)(size_t)(lds_ptr_t)ring;
-    const uint32_t wave_lds = ring0 + wq * LD * 1024;
+    const uint32_t wave_lds = ring0 + wq * LROWS * 1024;
+    // The tiles of the next stage to be requested, as buffers that begin with them and end with the sample's rows (stage 0 has no V tile).
+    __amdgpu_buffer_rsrc_t rk, rv;
+    int tile_at;                                // of that stage's K tile: bytes behind the head's first one
+    const int tile_step = (SPLIT ? 2 : 1) * ATT_BK * row_bytes;
+    auto first_tile = [&] {
+        tile_at = (SPLIT ? grp : 0) * ATT_BK * row_bytes;
+        rk = make_uniform_rsrc((const char*)k + head_at + tile_at, (uint32_t)max((int)head_bytes - tile_at, 0));
+        rv = make_uniform_rsrc((const char*)v + head_at, 0);
+    };
+    auto next_tile = [&] {
+        rv = make_uniform_rsrc((const char*)v + head_at + tile_at, (uint32_t)max((int)head_bytes - tile_at, 0));
+        tile_at += tile_step;
+        rk = make_uniform_rsrc((const char*)k + head_at + tile_at, (uint32_t)max((int)head_bytes - tile_at, 0));
+    };
+    first_tile();
     auto issue_one = [&](int j, int i) {        // one of the 2 LD loads of stage j
-        const uint32_t dst = wave_lds + slot_of(j) * STAGE + (i >> 1) * 1024;
-        // (stage 0 has no V tile: its offsets lie outside the buffer)
-        if (i & 1) direct_load_16(rv, v_off[i >> 1] + tile_of(j - 1) * ATT_BK * row_bytes, dst + TILE);
-        else direct_load_16(rk, k_off[i >> 1] + tile_of(j) * ATT_BK * row_bytes, dst);
+        const int u = i >> 1, row = u / HALVES, half = u % HALVES;
+        const uint32_t dst = wave_lds + slot_of(j) * STAGE + half * PART + row * 1024 + (i & 1) * TILE;
+        if (half) direct_load_16<128>((i & 1) ? rv : rk, ((i & 1) ? v_off : k_off)[row], dst);
+        else direct_load_16((i & 1) ? rv : rk, ((i & 1) ? v_off : k_off)[row], dst);
     };
     auto issue = [&](int j) {
 #pragma unroll
         for (int i = 0; i < 2 * LD; ++i) issue_one(j, i);
+        next_tile();
     };
-    // addresses inside a stage; what varies from fragment to fragment goes in by exclusive or
-    const int k_addr = r * ROWB + ((g ^ (DH == 128 ? r : (r >> 1) & 7)) << 4);      // K fragment of rows 0..15, chunk 4 ks + g
-    // transposing read: row 4 g + tj, 4-dim quad tq of a 16-dim block; the block number goes in by exclusive or (32-byte pieces)
-    const int tj = (lane & 15) >> 2, tq = lane & 3, tx = 4 * g + tj;
-    const int v_addr = TILE + tx * ROWB + (((tq >> 1) ^ (DH == 128 ? (tx & 7) << 1 : ((tx >> 1) & 3) << 1)) << 4) + (tq & 1) * 8;
+    // LDS addresses of the fragments in the stage that the next MFMA phase reads: two k-steps of K, four blocks of V; the others lie in the next part
+    // of the tile.  V's move on in the softmax phase, K's, which are wanted at its start, at the end of the MFMA phase.
+    constexpr int KA = 2, VA = 4;
+    uint32_t ka[KA], va[VA];
+    auto first_addresses = [&] {
+        // the lane's number anew, so that nothing of this is kept in a register from one item to the next
+        int l = threadIdx.x;
+        asm volatile("" : "+v"(l));
+        l &= 63;
+        const int lr = l & 15, lg = l >> 4;
+        const int k0 = lr * PARTB + ((lg ^ ((lr >> 1) & 7)) << 4);               // rows 0..15, chunk 4 ks + g
+        // transposing read: row 4 g + tj, 4-dim quad tq of a 16-dim block; the block number goes in by exclusive or (32-byte pieces)
+        const int tj = lr >> 2, tq = l & 3, tx = 4 * lg + tj;
+        const int v0 = TILE + tx * PARTB + (((tq >> 1) ^ (((tx >> 1) & 3) << 1)) << 4) + (tq & 1) * 8;
+        const uint32_t base = ring0 + slot_of(0) * STAGE;
+#pragma unroll
+        for (int i = 0; i < KA; ++i) ka[i] = base + (k0 ^ (i << 6));
+#pragma unroll
+        for (int i = 0; i < VA; ++i) va[i] = base + (v0 ^ (i << 5));
+    };
+    auto step_to = [&](int j) { return (uint32_t)__builtin_amdgcn_readfirstlane((slot_of(j) - slot_of(j - 1)) * STAGE); };     // from stage j - 1 to j
+    auto move = [](uint32_t& a, uint32_t step) { asm volatile("v_add_u32 %0, %1, %0" : "+v"(a) : "s"(step)); };
+    typedef __attribute__((address_space(3))) const char* lds_bytes_t;
+    auto k_fragment = [&](int ks, int kb) {
+        typedef __attribute__((address_space(3))) const bf16x8* lp;
+        return *(lp)((lds_bytes_t)(size_t)ka[ks % KA] + ks / KA * PART + kb * 16 * PARTB);
+    };
 
     bf16x8 kf[KPRE];                            // the first 32 keys' fragments of the next tile
-    auto read_first = [&](const char* sb, int f) {
-        kf[f] = *reinterpret_cast<const bf16x8*>(sb + (k_addr ^ ((f / 2) << 6)) + (f % 2) * 16 * ROWB);
-    };
+    auto read_first = [&](int f) { kf[f] = k_fragment(f / 2, f % 2); };
     f32x4 st[4][NQ];                            // S^T: [16-key block][query block]
     bf16x8 pf[2][NQ];                           // P^T: [32-key half][query block]
     // S of tile j (QK) and O += V P of tile j - 1 (PV).  A wave that issues LDS reads back to back waits for the CU's one LDS at each
     // of them while the matrix core idles; every fragment of what comes next is therefore read right behind the MFMAs that used
     // up the registers it goes into (a bunch of reads in front of each part: 1710 clocks per phase; dealt: 1350).
     static_assert(KPRE == DB, "a V fragment follows every K fragment");
+    uint32_t step = 0;                          // from the stage of the last MFMA phase to the next one
     auto mfma_phase = [&](int j, auto qk_c, auto pv_c) {
         constexpr bool QK = decltype(qk_c)::value, PV = decltype(pv_c)::value;
         typedef __attribute__((__vector_size__(8 * sizeof(short)))) short att_short8;
-        const char* sb = ring + slot_of(j) * STAGE;
         att_short8 vf[DB];                      // V^T of 32 keys, 16 dims each
         auto read_v = [&](int kt, int t) {
-            const char* p = sb + (v_addr ^ (t << 5)) + kt * 32 * ROWB;
-            vf[t] = __builtin_shufflevector(lds_read_tr16(p), lds_read_tr16(p + 16 * ROWB), 0, 1, 2, 3, 4, 5, 6, 7);
+            const lds_bytes_t p = (lds_bytes_t)(size_t)va[t % VA] + t / VA * PART + kt * 32 * PARTB;
+            vf[t] = __builtin_shufflevector(lds_read_tr16(p), lds_read_tr16(p + 16 * PARTB), 0, 1, 2, 3, 4, 5, 6, 7);
         };
         auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
         fence();
@@ -309,7 +378,9 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
                 for (int qb = 0; qb < NQ; ++qb)
                     st[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[f], qf[qb][ks], ks ? st[kb][qb] : c0[kb], 0, 0, 0);
                 fence();
-                if (i < KPRE) kf[f] = *reinterpret_cast<const bf16x8*>(sb + (k_addr ^ (ks << 6)) + (kb + 2) * 16 * ROWB);
+                if (PV && i == KPRE) next_tile();
+                if (i == KPRE) step = step_to(j + 1);
+                if (i < KPRE) kf[f] = k_fragment(ks, kb + 2);
                 else if constexpr (PV) read_v(0, f);
                 fence();
             }
@@ -330,6 +401,10 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
             }
         }
         fence();
+        if constexpr (QK) {
+#pragma unroll
+            for (int i = 0; i < KA; ++i) move(ka[i], step);
+        }
     };
     auto softmax_phase = [&](int j, auto last_c) {
         constexpr bool LAST = decltype(last_c)::value;
@@ -350,23 +425,31 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
 #pragma unroll
-                for (int f = i * KPRE / 8; f < (i + 1) * KPRE / 8; ++f) read_first(ring + slot_of(j + 1) * STAGE, f);
+                for (int f = i * KPRE / 8; f < (i + 1) * KPRE / 8; ++f) read_first(f);
 #pragma unroll
                 for (int f = i * (2 * LD - LATER) / 8; f < (i + 1) * (2 * LD - LATER) / 8; ++f) issue_one(j + AHEAD, f);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+#pragma unroll
+        for (int i = 0; i < VA; ++i) move(va[i], step);
         // The running maximum.  A lane sees its own 16 of a column's 64 logits; only if one of them exceeds the column's maximum do
         // the four lanes meet and the accumulators get their new scale.
+        float peak[NQ];
+        uint64_t above[NQ];
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) {
-            float t = m_run[qb];
+            peak[qb] = m_run[qb];
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) t = fmaxf(t, st[kb][qb][e]);
-            if (__builtin_amdgcn_ballot_w64(t > m_run[qb]) != 0) {
-                const float m_new = att_quad_max(t);        // finite: every tile holds at least one key of the sample
+                for (int e = 0; e < 4; ++e) peak[qb] = fmaxf(peak[qb], st[kb][qb][e]);
+            above[qb] = __builtin_amdgcn_ballot_w64(peak[qb] > m_run[qb]);
+        }
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) {
+            if (above[qb] != 0) {
+                const float m_new = att_quad_max(peak[qb]);    // finite: every tile holds at least one key of the sample
                 const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_new) * scale2);
                 ms[qb] = m_new * scale2;
                 m_run[qb] = m_new;
@@ -394,6 +477,9 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
                     pf[kb >> 1][qb][(kb & 1) * 4 + e] = (__bf16)p;
                     l_run[qb] += p;
                 }
+        // (all of it here, not behind what ends the phase)
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) asm volatile("" : "+v"(pf[0][qb]), "+v"(pf[1][qb]), "+v"(l_run[qb]));
     };
 
     int ntile = (n + KROUND - 1) / KROUND;      // tiles of a group (SPLIT: the last one may lie past the end in part or, of group 1, in full)
@@ -413,6 +499,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
         }
 #pragma unroll
         for (int i = 0; i < 2 * LD; i += 2) issue_one(0, i);
+        next_tile();
         issue(1);
         wait_loads<2 * LD>();
         if constexpr (WGT) __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): the weights are written
@@ -439,7 +526,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb)
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const bf16x8*>(ring + q_lds + (k_addr ^ (ks << 6)) + qb * 16 * ROWB);
+            for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const bf16x8*>(ring + q_lds + (qb * 16 + r) * ROWB + (((ks * 4 + g) ^ row_swizzle(r)) << 4));
         __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0): the queries are there (and the weights written)
         phase_barrier();
     }
@@ -456,12 +543,13 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
         constexpr bool LIVE = decltype(live_c)::value;
         if constexpr (!SPLIT) issue(2);
         if constexpr (LIVE) {
+            first_addresses();
 #pragma unroll
-            for (int f = 0; f < KPRE; ++f) read_first(ring + slot_of(0) * STAGE, f);
+            for (int f = 0; f < KPRE; ++f) read_first(f);
         }
-        // Stage j + 1 has to have landed when the softmax phase of tile j begins (its first fragments are read there).  Groups that
-        // share the ring: both wait for their loads before the barrier that ends group 0's MFMA phase of tile j.  Stages behind
-        // j + 1 stay in flight.  SPLIT: a group has a ring of two slots of its own, and stage j + 1, requested in the softmax phase of tile j - 1,
+        // Stage j + 1 has to have landed when the softmax phase of tile j begins (its first fragments are read there), and stage j - 1, whose slot the
+        // loads of that phase fill, has to have been read.  Groups that share the ring: both wait for their loads before the one barrier of tile j, which ends
+        // group 0's MFMA phase of tile j and group 1's softmax phase of tile j - 1.  Stages behind j + 1 stay in flight.  SPLIT: a group has a ring of two slots of its own, and stage j + 1, requested in the softmax phase of tile j - 1,
         // is all that is on its way; the group waits for it before the barrier that ends its own MFMA phase of tile j.
         if (grp == 1) { if (!SPLIT && first) wait_loads<KEEP>(); phase_barrier(); }
         bool wait0 = SPLIT || (grp == 0 && first);         // (behind another item the first two stages have landed, and its stores may still be on their way)
@@ -475,7 +563,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
         for (int j = 0; COUNTED ? j < last : j + 1 < ntile; ++j) {
             if (wait0) wait_loads<KEEP>();
             wait0 = SPLIT || grp == 0;
-            phase_barrier();
+            if (SPLIT || grp == 0) phase_barrier();
             if constexpr (LIVE) {
                 __builtin_amdgcn_s_setprio(2);
                 softmax_phase(j, no());
@@ -486,14 +574,13 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
                 issue(j + AHEAD);
             }
             if (!SPLIT && grp == 1) wait_loads<KEEP>();
-            phase_barrier();
+            if (SPLIT || grp == 1) phase_barrier();
             if constexpr (LIVE) mfma_phase(j + 1, yes(), yes());
         }
-        if (SPLIT || grp == 0) wait_loads<0>();
-        phase_barrier();
+        if (SPLIT || grp == 0) { wait_loads<0>(); phase_barrier(); }
         if constexpr (LIVE) softmax_phase(ntile - 1, yes());
         if (grp == 1) wait_loads<0>();
-        phase_barrier();
+        if (SPLIT || grp == 1) phase_barrier();
         if constexpr (LIVE) mfma_phase(ntile, no(), yes());
     };
     // SPLIT: the two parts of the keys meet.  A wave gives the channels that it does not finish to the wave with the same queries (group 0
@@ -571,7 +658,9 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
             more = item(pass);
             if (more) {
                 phase_barrier();                // everybody is done with the ring and the weights
-                rk = rows_of(k); rv = rows_of(v); rq = rows_of(q);
+                rq = rows_of(q);
+                place_head();
+                first_tile();
                 q0 = qt * BQ + wave * NQ * 16;
                 ntile = (n + ATT_BK - 1) / ATT_BK;
                 issue(0);

@@ -20,9 +20,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_uniform_rsrc(const void* 
 // (zeros when that is past the end of the buffer) into LDS byte lds_base + 16 i.  Issued from inline
 // assembly on purpose: the waits for these loads are placed by hand (wait_loads), and the
 // compiler, when it sees such a load, makes every later transposing LDS read wait for all of them.
+// OFFSET more bytes into the buffer go into the instruction, which adds them to the LDS address as well.
+template <int OFFSET = 0>
 __device__ __forceinline__ void direct_load_16(__amdgpu_buffer_rsrc_t rsrc, int voff, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :: "s"(lds_base), "v"(voff), "s"(rsrc) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen offset:%3 lds"
+                 :: "s"(lds_base - OFFSET), "v"(voff), "s"(rsrc), "n"(OFFSET) : "memory", "m0");
 }
 #endif
 
