@@ -704,34 +704,45 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     }
 #endif
 }
-// ---- short sequences: the keys are split across the four waves -------------------------------------
+// ---- short sequences: the keys are split across four waves -------------------------------------
 // With a few hundred keys the kernel above is one short serial chain per workgroup (8 stages at 493 keys)
-// on half of the CUs.  Here a workgroup owns 32 queries of one head and its four waves take the 32-key
-// tiles w, w + 4, w + 8, ... with the same transposed products as above; each wave has a private K and V
-// tile in LDS, filled by its own direct loads, so the waves never meet inside the loop (no s_barrier, only
-// waits for the wave's own loads: K of the next tile is requested as soon as the K fragments are in
-// registers, V of the next tile as soon as the V fragments are).  At the end the four partial results
-// (running max, sum, O^T) meet in LDS and wave t combines and stores the 32 output dims t*32 ..
-// Four times the K/V traffic per query of the kernel above, which is why it is only taken while the whole sample is short.
+// on half of the CUs.  Here a workgroup owns 32 or 64 queries (QH halves of 32) of one head.  The waves of a half take the 32-key
+// tiles w, w + 4, w + 8, ... with the same transposed products as above, and at the end the four partial results
+// (running max, sum, O^T) of a half meet in LDS, rows of queries, from where eight threads to a row store whole lines.  A step is four tiles, one for
+// each wave of a half; the waves of two halves share their tile, load half of it each and meet at one barrier a step.  K and V of a
+// step go to LDS by direct loads one step ahead, the queries in front of them take the same way.
+// Bound by the chain of trips to memory where workgroups are few (the sample's offsets; queries and tiles: 1080 and some 2500 clocks), and by what a
+// compute unit takes in where they are many, four times the K and V per query of the kernel above with 32 queries, twice with 64.  Against 32 queries
+// always, queries in fragments of 32 bytes a row that were waited for before the first tile was requested, and a tile's K and V requested when the one before
+// had been read (the same bits): 32 heads of 128, 100 rows 4.9 -> 4.15 us, 231 5.85 -> 5.4, 300 9.0 -> 7.4, 493 12.5 -> 10.1, weighted 14.5 -> 11.0; 8 heads, 493 rows
+// 7.13 -> 7.19; 4 x 300 rows 23.8 -> 22.5, 4 x 100 .. 128 7.6 -> 6.0, 8 x 120 .. 250 27.1 -> 24.4; 16 heads of 64, 331 rows 4.8 -> 4.3, 8 x 120 .. 250 8.1 -> 6.7.
+// (64 queries: the next step requested in front of the first product 10.3, behind it 10.1.  32 queries: K waited for apart from V, and the loads two steps
+// ahead: no gain.)
 constexpr int ATS_BK = 32;      // keys per wave tile
 constexpr int ATS_MAX_KEYS = 512;
 
-template <int DH, bool WGT>
-__global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
+template <int DH, int QH> struct AtsLds {
+    static constexpr int ROWB = DH * 2, TILE = ATS_BK * ROWB, REGION = 2 * TILE, BUF = 4 * REGION;     // a wave's K and V tile; four of them a step
+    static constexpr int PITCH = DH + 4;                                                                // floats of a row of a partial O
+    static constexpr int STEPS = 2 * BUF + QH * 32 * ROWB, PARTS = 4 * QH * 32 * PITCH * 4;
+    static constexpr int BYTES = STEPS > PARTS ? STEPS : PARTS;
+};
+template <int DH, bool WGT, int QH>
+__global__ __launch_bounds__(256 * QH, 2) void attend_bf16_short_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ cu, int H, int nB, int nqt, float scale2, uint16_t* __restrict__ o, KeyWeights kw) {
 #if defined(__HIP_DEVICE_COMPILE__)
+    using C = AtsLds<DH, QH>;
     constexpr int KS = DH / 16;
     constexpr int DT = DH / 32;
-    constexpr int ROWB = DH * 2;
+    constexpr int ROWB = C::ROWB, TILE = C::TILE;
     constexpr int NCHK = DH / 8;
     constexpr int RPI = 64 / NCHK;              // rows per wave-wide direct load
-    constexpr int LD = ATS_BK / RPI;            // direct loads per operand tile
-    constexpr int TILE = ATS_BK * ROWB;         // bytes of one K (or V) tile
-    constexpr int WREG = 2 * TILE;              // bytes of a wave's private region (K tile, V tile)
-    static_assert(WREG == DT * 16 * 64 * 4, "a wave's region also holds its partial O^T");
+    constexpr int LD = ATS_BK / RPI / QH;       // direct loads per wave and operand tile
+    constexpr int QLD = 32 / RPI / 4;           // of the queries
+    constexpr bool ALONE = QH == 1;             // nobody else reads or loads a wave's tiles
     extern __shared__ __attribute__((aligned(16))) char ring[];
-    __shared__ float part_m[4][32], part_l[4][32];
+    __shared__ float part_m[4 * QH][32], part_l[4 * QH][32];
     __shared__ __attribute__((aligned(16))) float lw_s[WGT ? ATS_MAX_KEYS : 4];
 
     const int xcd = blockIdx.x & 7, li = blockIdx.x >> 3;
@@ -740,56 +751,48 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
     const int h = hb % H, b = hb / H;
     const int tok0 = cu[b];
     const int n = min(cu[b + 1] - tok0, ATS_MAX_KEYS);
-    if (qt * 32 >= n) return;
+    const int q0 = qt * 32 * QH;
+    if (q0 >= n) return;
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    if constexpr (WGT) {
-        for (int j = tid; j < ATS_MAX_KEYS; j += 256) lw_s[j] = (j < n) ? key_log2_weight(kw, b, j) : 0.f;
-        __syncthreads();
-    }
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int kg = wave & 3, qh = wave >> 2;               // which tiles of keys, which half of the queries
     const int c = lane & 31, g = lane >> 5;
     const size_t rs = (size_t)H * DH;
-    const uint16_t* kb = k + (size_t)tok0 * rs + (size_t)h * DH;
-    const uint16_t* vb = v + (size_t)tok0 * rs + (size_t)h * DH;
-    const uint32_t span = (uint32_t)(((size_t)(n - 1) * rs + DH) * 2);      // rows past the end load as zeros
-    const __amdgpu_buffer_rsrc_t rk = make_uniform_rsrc(kb, span), rv = make_uniform_rsrc(vb, span);
     const int row_bytes = (int)(rs * 2);
+    const size_t head = (size_t)tok0 * rs + (size_t)h * DH;
+    const uint32_t span = (uint32_t)(((size_t)(n - 1) * rs + DH) * 2);      // rows past the end load as zeros
+    const __amdgpu_buffer_rsrc_t rq = make_uniform_rsrc(q + head, span), rk = make_uniform_rsrc(k + head, span), rv = make_uniform_rsrc(v + head, span);
 
-    const int qrow = qt * 32 + c;
-    const bool qvalid = qrow < n;
-    bf16x8 qf[KS];
-    // rows past the end load as zeros here too (under a condition 32 heads of 128, 150 rows 5.9 us, now 5.7; 231 rows 6.44, 6.40; K or V in front 6.6)
-    const __amdgpu_buffer_rsrc_t rq = make_uniform_rsrc(q + (size_t)tok0 * rs + (size_t)h * DH, span);
+    // direct loads: same chunk swizzles as in the kernel above
+    const int ld_pos = lane % NCHK, ld_row = lane / NCHK;
+    const uint32_t ring0 = (uint32_t)(size_t)(lds_ptr_t)ring;
+    constexpr int Q_LDS = 2 * C::BUF;
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rq, qrow * row_bytes + g * 16, kk * 32, 0));
-    f32x16 ot[DT];
-#pragma unroll
-    for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) ot[t][e] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;
-
-    // direct loads of a 32-key tile: same chunk swizzles as in the kernel above
-    const int ld_pos = lane % NCHK;
+    for (int i = 0; i < QLD; ++i) {
+        const int x = wave * QLD * RPI + i * RPI + ld_row;
+        direct_load_16(rq, (q0 + x) * row_bytes + (((ld_pos ^ (x & 15)) & (NCHK - 1)) << 4), ring0 + Q_LDS + (wave * QLD + i) * 1024);
+    }
     int k_off[LD], v_off[LD];
 #pragma unroll
     for (int i = 0; i < LD; ++i) {
-        const int r = lane / NCHK + i * RPI;
-        k_off[i] = r * row_bytes + (((ld_pos ^ (r & 15)) & (NCHK - 1)) << 4);
-        v_off[i] = r * row_bytes + (((ld_pos ^ ((r & 3) * 4)) & (NCHK - 1)) << 4);
+        const int r = (qh * LD + i) * RPI + ld_row;
+        k_off[i] = (kg * ATS_BK + r) * row_bytes + (((ld_pos ^ (r & 15)) & (NCHK - 1)) << 4);
+        v_off[i] = (kg * ATS_BK + r) * row_bytes + (((ld_pos ^ ((r & 3) * 4)) & (NCHK - 1)) << 4);
     }
-    char* wreg = ring + wave * WREG;
-    const uint32_t wave_lds = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lds_ptr_t)ring + wave * WREG);
-    auto issue_k = [&](int key0) {
-        const int kofs = key0 * row_bytes;
+    auto issue = [&](int step) {
+        const int at = step * 4 * ATS_BK * row_bytes;
+        const uint32_t dst = ring0 + (step & 1) * C::BUF + kg * C::REGION + qh * LD * 1024;
 #pragma unroll
-        for (int i = 0; i < LD; ++i) direct_load_16(rk, k_off[i] + kofs, wave_lds + i * RPI * ROWB);
-    };
-    auto issue_v = [&](int key0) {
-        const int kofs = key0 * row_bytes;
+        for (int i = 0; i < LD; ++i) direct_load_16(rk, k_off[i] + at, dst + i * 1024);
 #pragma unroll
-        for (int i = 0; i < LD; ++i) direct_load_16(rv, v_off[i] + kofs, wave_lds + TILE + i * RPI * ROWB);
+        for (int i = 0; i < LD; ++i) direct_load_16(rv, v_off[i] + at, dst + TILE + i * 1024);
     };
+    const int ntile = (n + ATS_BK - 1) / ATS_BK, nstep = (ntile + 3) / 4;
+    issue(0);
+    if (ALONE && nstep > 1) issue(1);
+    if constexpr (WGT)
+        for (int j = tid; j < ATS_MAX_KEYS; j += 256 * QH) lw_s[j] = (j < n) ? key_log2_weight(kw, b, j) : 0.f;
+
     int k_addr[KS];
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) k_addr[kk] = c * ROWB + ((((kk * 2 + g) ^ (c & 15)) & (NCHK - 1)) << 4);
@@ -800,15 +803,31 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
         const int chunk = t * 4 + tr_half * 2 + (tr_t >> 1);
         v_addr[t] = TILE + (g * 4 + tr_j) * ROWB + (tr_t % 2) * 8 + (((chunk ^ (tr_j * 4)) & (NCHK - 1)) << 4);
     }
-
-    const int ntile = (n + ATS_BK - 1) / ATS_BK;
+    f32x16 ot[DT];
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) asm volatile("" :: "v"(qf[kk]));      // Q has arrived before the first direct load
-    if (wave < ntile) { issue_k(wave * ATS_BK); issue_v(wave * ATS_BK); }
-    for (int it = wave; it < ntile; it += 4) {
-        const int key0 = it * ATS_BK;
-        const bool more = it + 4 < ntile;
-        wait_loads<LD>();                                  // K of this tile has landed (V may still be on its way)
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) ot[t][e] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+    bf16x8 qf[KS];
+    const bool live = q0 + qh * 32 < n;         // uniform
+    for (int step = 0; step < nstep; ++step) {
+        // This step's tiles (and the queries, the weights) are there.  ALONE: behind the first step a wave waits for nobody; otherwise
+        // everybody is done with the step before, whose place the next one's tiles take.
+        if (ALONE && step > 0) wait_loads<0>();
+        else if (ALONE && nstep > 1 && !WGT) wait_loads_and_barrier<2 * LD>();
+        else wait_loads_and_barrier<0>();
+        if (ALONE && step > 0 && step + 1 < nstep) issue(step + 1);
+        if (step == 0) {
+#pragma unroll
+            for (int kk = 0; kk < KS; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(ring + Q_LDS + qh * TILE + k_addr[kk]);
+        }
+        if (step * 4 + kg >= ntile || !live) {
+            if (!ALONE && step + 1 < nstep) issue(step + 1);
+            continue;
+        }
+        const int key0 = (step * 4 + kg) * ATS_BK;
+        const char* wreg = ring + (step & 1) * C::BUF + kg * C::REGION;
         bf16x8 kf[KS];
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(wreg + k_addr[kk]);
@@ -816,13 +835,20 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
         f32x16 st;
 #pragma unroll
         for (int e = 0; e < 16; ++e) st[e] = 0.f;
-        __builtin_amdgcn_s_setprio(3);
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], st, 0, 0, 0);
-        __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
-        // the K fragments are in registers (the MFMAs above consumed them): the K tile is free
-        if (more) issue_k(key0 + 4 * ATS_BK);
+        if (!ALONE && step + 1 < nstep) issue(step + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        att_short4 vf[2][DT][2];
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+            for (int t = 0; t < DT; ++t) {
+                const char* pa = wreg + v_addr[t] + hh * 16 * ROWB;
+                vf[hh][t][0] = lds_read_tr16(pa);
+                vf[hh][t][1] = lds_read_tr16(pa + 8 * ROWB);
+            }
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (WGT) {
             // weighted: maximum and exponent on scale2 * logit + log2 w (m_run lives in that scaled domain)
@@ -836,74 +862,37 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
                     st[e4 * 4 + e] = (key < n) ? t : -INFINITY;
                 }
             }
-            float tmax = st[0];
-#pragma unroll
-            for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, st[e]);
-            tmax = att_pair_max(tmax);
-            const float m_new = fmaxf(m_run, tmax);
-            float psum = 0.f;
+        } else if (key0 + ATS_BK > n) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
-                const float p = __builtin_amdgcn_exp2f(st[e] - m_new);
-                st[e] = p;
-                psum += p;
+                const int key = key0 + (e >> 2) * 8 + g * 4 + (e & 3);
+                if (key >= n) st[e] = -INFINITY;
             }
-            if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-                l_run *= alpha;
-#pragma unroll
-                for (int t = 0; t < DT; ++t)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) ot[t][e] *= alpha;
-            }
-            l_run += psum;
-            m_run = m_new;
-        } else {
-            if (key0 + ATS_BK > n) {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int key = key0 + (e >> 2) * 8 + g * 4 + (e & 3);
-                    if (key >= n) st[e] = -INFINITY;
-                }
-            }
-            float tmax = st[0];
-#pragma unroll
-            for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, st[e]);
-            tmax = att_pair_max(tmax);
-            const float m_new = fmaxf(m_run, tmax);                // finite: every tile holds >= 1 valid key
-            const float ms = m_new * scale2;
-            float psum = 0.f;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(st[e], scale2, -ms));
-                st[e] = p;
-                psum += p;
-            }
-            if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-                const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale2);
-                l_run *= alpha;
-#pragma unroll
-                for (int t = 0; t < DT; ++t)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) ot[t][e] *= alpha;
-            }
-            l_run += psum;
-            m_run = m_new;
         }
-        __builtin_amdgcn_sched_barrier(0);
-        // V of this tile: everything older than the K loads just issued has landed
-        if (more) wait_loads<LD>(); else wait_loads<0>();
-        att_short4 vf[2][DT][2];
+        float tmax = st[0];
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
+        for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, st[e]);
+        tmax = att_pair_max(tmax);
+        const float m_new = fmaxf(m_run, tmax);                // finite: every tile holds >= 1 valid key
+        const float ms = m_new * scale2;
+        float psum = 0.f;
 #pragma unroll
-            for (int t = 0; t < DT; ++t) {
-                const char* pa = wreg + v_addr[t] + hh * 16 * ROWB;
-                vf[hh][t][0] = lds_read_tr16(pa);
-                vf[hh][t][1] = lds_read_tr16(pa + 8 * ROWB);
-            }
+        for (int e = 0; e < 16; ++e) {
+            const float p = __builtin_amdgcn_exp2f(WGT ? st[e] - m_new : __builtin_fmaf(st[e], scale2, -ms));
+            st[e] = p;
+            psum += p;
+        }
+        if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+            const float alpha = __builtin_amdgcn_exp2f(WGT ? m_run - m_new : (m_run - m_new) * scale2);
+            l_run *= alpha;
+#pragma unroll
+            for (int t = 0; t < DT; ++t)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) ot[t][e] *= alpha;
+        }
+        l_run += psum;
+        m_run = m_new;
         __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(3);
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
             bf16x8 pf;
@@ -916,48 +905,56 @@ __global__ __launch_bounds__(256, 2) void attend_bf16_short_kernel(
                 ot[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v8), pf, ot[t], 0, 0, 0);
             }
         }
-        __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
-        // the V fragments are in registers: the V tile is free
-        if (more) issue_v(key0 + 4 * ATS_BK);
     }
-    // the four partial results meet in LDS (every wave's own region is free: it has no load in flight)
-    l_run = att_pair_sum(l_run);
-    float* po = reinterpret_cast<float*>(wreg);
+    // the four partial results of a half meet in LDS, rows of queries
+    __syncthreads();                            // everybody is done with the tiles
+    float* part = reinterpret_cast<float*>(ring);
+    if (live) {
+        l_run = att_pair_sum(l_run);
+        float* mine = part + (wave * 32 + c) * C::PITCH + g * 4;
 #pragma unroll
-    for (int t = 0; t < DT; ++t)
+        for (int t = 0; t < DT; ++t)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) po[(t * 16 + e) * 64 + lane] = ot[t][e];
-    if (g == 0) { part_m[wave][c] = m_run; part_l[wave][c] = l_run; }
+            for (int e4 = 0; e4 < 4; ++e4)
+                *reinterpret_cast<f32x4*>(mine + t * 32 + e4 * 8) = f32x4{ot[t][e4 * 4], ot[t][e4 * 4 + 1], ot[t][e4 * 4 + 2], ot[t][e4 * 4 + 3]};
+        if (g == 0) { part_m[wave][c] = m_run; part_l[wave][c] = l_run; }
+    }
     __syncthreads();
-    if (wave >= DT || !qvalid) return;
-    float m = part_m[0][c];
+    // eight threads to a row, an eighth of its channels each
+    constexpr int CH = DH / 8;
+    const int row = tid >> 3, w0 = (row >> 5) * 4, x = row & 31, ch = (tid & 7) * CH;
+    if (q0 + row >= n) return;
+    float m = part_m[w0][x];
 #pragma unroll
-    for (int w2 = 1; w2 < 4; ++w2) m = fmaxf(m, part_m[w2][c]);
+    for (int w2 = 1; w2 < 4; ++w2) m = fmaxf(m, part_m[w0 + w2][x]);
     float f[4], l = 0.f;
 #pragma unroll
     for (int w2 = 0; w2 < 4; ++w2) {
-        const float mw = part_m[w2][c];
+        const float mw = part_m[w0 + w2][x];
         f[w2] = (mw == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f((mw - m) * (WGT ? 1.0f : scale2));
-        l += part_l[w2][c] * f[w2];
+        l += part_l[w0 + w2][x] * f[w2];
     }
     const float inv = 1.0f / l;
-    float acc[16];
+    uint16_t* op = o + (size_t)(tok0 + q0 + row) * rs + (size_t)h * DH + ch;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        float a2 = 0.f;
+    for (int e8 = 0; e8 < CH; e8 += 8) {
+        float acc[8];
 #pragma unroll
-        for (int w2 = 0; w2 < 4; ++w2)
-            a2 += reinterpret_cast<const float*>(ring + w2 * WREG)[(wave * 16 + e) * 64 + lane] * f[w2];
-        acc[e] = a2 * inv;
-    }
-    uint16_t* op = o + (size_t)(tok0 + qrow) * rs + (size_t)h * DH + wave * 32;
+        for (int e = 0; e < 8; ++e) acc[e] = 0.f;
 #pragma unroll
-    for (int e4 = 0; e4 < 4; ++e4) {
-        uint2 w2;
-        w2.x = pack_bf16x2(acc[e4 * 4 + 0], acc[e4 * 4 + 1]);
-        w2.y = pack_bf16x2(acc[e4 * 4 + 2], acc[e4 * 4 + 3]);
-        *reinterpret_cast<uint2*>(op + e4 * 8 + g * 4) = w2;
+        for (int w2 = 0; w2 < 4; ++w2) {
+            const f32x4* p = reinterpret_cast<const f32x4*>(part + ((w0 + w2) * 32 + x) * C::PITCH + ch + e8);
+            const f32x4 lo = p[0], hi = p[1];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { acc[e] += lo[e] * f[w2]; acc[4 + e] += hi[e] * f[w2]; }
+        }
+        uint4 w;
+        w.x = pack_bf16x2(acc[0] * inv, acc[1] * inv);
+        w.y = pack_bf16x2(acc[2] * inv, acc[3] * inv);
+        w.z = pack_bf16x2(acc[4] * inv, acc[5] * inv);
+        w.w = pack_bf16x2(acc[6] * inv, acc[7] * inv);
+        *reinterpret_cast<uint4*>(op + e8) = w;
     }
 #endif
 }
@@ -1099,28 +1096,27 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
     if (wgt && mfma && max_seqlen > ATT_WKEYS) return D3TOM_ERR_UNSUPPORTED;
     const long heads = (long)H * B;
     // Short samples, up to two rounds of 128-query tiles: keys split across the waves.  The tiles below are faster for some of them (493 keys, 32 heads of
-    // 128 11.5 us here, 8.9 with 64-query tiles; 100 keys 5.2 and 4.7; batches of 129 .. 512 keys up to 1.8 times as fast, others up to 1.75 times as
-    // slow), but this kernel has four running maxima a row, over tiles of 32 keys, relative to which the probabilities are rounded.  Error against
+    // 128 10.1 us here, 8.5 with 64-query tiles), but this kernel has four running maxima a row, over tiles of 32 keys, relative to which the probabilities are rounded.  Error against
     // float64 (2-norm, relative, output rounded to bf16) at logit spreads of 1 and 2, 493 keys: 2.10e-3, 1.77e-3 here; 2.16e-3, 1.82e-3 with 64-query
     // tiles; 2.19e-3, 1.86e-3 with wider ones.  66 to 512 keys, weighted or not, heads of 64 and 128: 2.2 to 4.9 % more with any of the tiles.
     if (mfma && max_seqlen <= ATS_MAX_KEYS && ceil_div(max_seqlen, 128) * heads <= 512) {
-        const int nqt = ceil_div(max_seqlen, 32);
+        // 32 queries to a workgroup while its tiles fill one round of compute units (two workgroups with heads of 64 fit on one), 64 above.  (32 and
+        // 64; 32 heads of 128, 231 rows 5.4 and 6.2 us, 300 11.2 and 7.4, 493 14.9 and 10.1; 8 heads, 3 x 100 .. 300 rows 6.2 and 7.1, 8 x 40 .. 250 9.3 and
+        // 6.4; 16 heads of 64, 2 x 200 .. 400 5.3 and 6.2, 5 x 150 .. 250 7.0 and 6.3.)
+        const int qh = ceil_div(max_seqlen, 32) * heads <= (dh == 64 ? 512 : 256) ? 1 : 2;
+        const int nqt = ceil_div(max_seqlen, 32 * qh);
         const dim3 g((unsigned)(8 * ceil_div(H * B, 8) * nqt));
-        const size_t lds = (size_t)4 * 2 * ATS_BK * dh * 2;
-        const int threads = 256;
-        static PerDeviceOnce lds_setup_s;
-        if (!lds_setup_s.run([] {
-                return raise_dynamic_lds(attend_bf16_short_kernel<128, false>, 4 * 2 * ATS_BK * 128 * 2) &&
-                       raise_dynamic_lds(attend_bf16_short_kernel<64, false>, 4 * 2 * ATS_BK * 64 * 2) &&
-                       raise_dynamic_lds(attend_bf16_short_kernel<128, true>, 4 * 2 * ATS_BK * 128 * 2) &&
-                       raise_dynamic_lds(attend_bf16_short_kernel<64, true>, 4 * 2 * ATS_BK * 64 * 2);
-            }))
-            return D3TOM_ERR_DEVICE;
-#define D3TOM_ATT_SHORT(DHV, WGTV)                                                                                              \
-    D3TOM_LAUNCH(ATTEND, st, (attend_bf16_short_kernel<DHV, WGTV><<<g, threads, lds, st>>>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, \
-                                                           cu_seqlens, H, B, nqt, scale2, (uint16_t*)o, kw)))
-        if (dh == 128) { if (wgt) D3TOM_ATT_SHORT(128, true); else D3TOM_ATT_SHORT(128, false); }
-        else           { if (wgt) D3TOM_ATT_SHORT(64, true);  else D3TOM_ATT_SHORT(64, false); }
+#define D3TOM_ATT_SHORT(DHV, WGTV, QHV)                                                                                         \
+    do {                                                                                                                        \
+        static PerDeviceOnce lds_setup;                                                                                         \
+        if (!lds_setup.run([] { return raise_dynamic_lds(attend_bf16_short_kernel<DHV, WGTV, QHV>, AtsLds<DHV, QHV>::BYTES); })) return D3TOM_ERR_DEVICE; \
+        D3TOM_LAUNCH(ATTEND, st, (attend_bf16_short_kernel<DHV, WGTV, QHV><<<g, 256 * QHV, AtsLds<DHV, QHV>::BYTES, st>>>((const uint16_t*)q, (const uint16_t*)k, \
+                                                               (const uint16_t*)v, cu_seqlens, H, B, nqt, scale2, (uint16_t*)o, kw))); \
+    } while (0)
+#define D3TOM_ATT_SHORT2(DHV, WGTV) do { if (qh == 1) D3TOM_ATT_SHORT(DHV, WGTV, 1); else D3TOM_ATT_SHORT(DHV, WGTV, 2); } while (0)
+        if (dh == 128) { if (wgt) D3TOM_ATT_SHORT2(128, true); else D3TOM_ATT_SHORT2(128, false); }
+        else           { if (wgt) D3TOM_ATT_SHORT2(64, true);  else D3TOM_ATT_SHORT2(64, false); }
+#undef D3TOM_ATT_SHORT2
 #undef D3TOM_ATT_SHORT
     } else if (mfma) {
         // 64-query tiles whose groups share the keys, where they fill one round of compute units at most: half as long a chain as 128-query

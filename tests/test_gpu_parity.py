@@ -478,6 +478,24 @@ def test_attend_error_of_short_samples(H, dh, n, weighted, copies, spread):
     assert got <= 1.01 * bound
 
 
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("H,dh,lens", [
+    (32, 128, [256]), (32, 128, [257]),                     # 256 tiles of 32 queries, and more: 64 queries to a workgroup from there on
+    (16, 64, [512]), (16, 64, [512, 300]), (17, 64, [512, 40]),             # 512 with heads of 64
+    (5, 128, [2]), (5, 128, [33]), (5, 64, [129]), (5, 128, [385]),         # one to four steps of four tiles, the last one with a single tile
+    (9, 128, [1, 31, 32, 33, 63, 64, 65, 97, 127, 128, 129, 255, 384, 511]), (40, 64, [64, 1, 95, 96, 97, 130, 257, 512]),     # halves without queries, steps without tiles
+])
+def test_attend_short_samples_by_halves_of_64_queries(H, dh, lens, weighted):
+    """The short-sample kernel with 32 and with 64 queries to a workgroup, at the edges of tiles, halves and steps."""
+    qkv = [W.random_qkv(1010 + n, n, H, dh, "bf16") for n in lens]
+    vis, counts = [n // 5 for n in lens], [(1 + np.arange(n // 2) % 37).astype(np.int32) for n in lens]
+    outs = gpu_attend_weighted(qkv, counts, vis, "bf16") if weighted else gpu_attend(qkv, "bf16")
+    for (q, k, v), o, vs, c in zip(qkv, outs, vis, counts):
+        n = len(q)
+        rows = np.union1d(np.arange(0, n, 1 if n < 66 else 13), np.arange(max(n - 9, 0), n))
+        check_attend(o, q, k, v, "bf16", rows=rows, key_weight=key_weights(n, vs, c) if weighted else None)
+
+
 @pytest.mark.parametrize("H,dh,longest,batch,weighted", [
     (5, 128, 300, 40, False),            # several rounds of 128-query tiles, heads that do not divide among the XCDs
     (5, 128, 600, 32, True),             # ... of 256-query tiles
