@@ -319,53 +319,84 @@ __global__ __launch_bounds__(512, 2) void linear_bf16_kernel(
     // epilogue, in registers: lane (r, g) holds row r of every 16-row fragment and, over the TN fragments, 4 TN consecutive
     // values of its part: plain columns, or (PAIR) 2 TN consecutive outputs with their partners in elements 2 and 3
     const int u0 = unit0 + wcol * (UNITS / WC) + g * (UNITS / (4 * WC));
+    // values per store (plain columns: never across an out_chunk, a multiple of 8), and where they go from the start of a row of the output's first
+    // section: worked out once for all rows
+    constexpr int V = !PAIR ? ((TN % 2 == 0) ? 8 : 4) : (TN % 4 == 0) ? 8 : (TN % 2 == 0) ? 4 : 2, NV = (PAIR ? 2 : 4) * TN / V;
+    const int row_width = EPI == LIN_PARTIAL ? N : out_chunk;
+    size_t at[NV];
+    int c[EPI == LIN_ROPE ? NV : 1];                    // ROPE: the first channel's place in its half of the head
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        const int m = rt * BM + grp * (BM / 2) + i * 16 + r;
-        if (m >= M) continue;
-        if constexpr (EPI == LIN_PARTIAL) {
-            float* po = reinterpret_cast<float*>(out) + ((size_t)blockIdx.y * M + m) * N + u0;
+    for (int x = 0; x < NV; ++x) {
+        int col = min(u0 + x * V, unit_end - V);        // past the end: loaded from there, not stored
+        if constexpr (EPI == LIN_ROPE) { const int h = col / half; c[x] = col - h * half; col = h * rope_dh + c[x]; }
+        const int section = col / row_width;
+        at[x] = (size_t)section * M * row_width + (col - section * row_width);
+    }
+    auto row_of = [&](int i) { return rt * BM + grp * (BM / 2) + i * 16 + r; };
+    if constexpr (EPI == LIN_PARTIAL) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            if (row_of(i) >= M) continue;
+            float* po = reinterpret_cast<float*>(out) + ((size_t)blockIdx.y * M + row_of(i)) * N + u0;
 #pragma unroll
             for (int j = 0; j < TN; ++j)
                 if (u0 + j * 4 < unit_end) *reinterpret_cast<f32x4*>(po + j * 4) = acc[i][j];
-        } else if constexpr (!PAIR) {
-            constexpr int V = (TN % 2 == 0) ? 8 : 4;        // columns per store (never across an out_chunk: a multiple of 8)
+        }
+    } else if constexpr (!PAIR) {
+        // all of the residual is requested before the first of it is used (it may be the output: nobody else writes these elements)
+        uint32_t rr[EPI == LIN_RESIDUAL ? TM : 1][NV][V / 2];
+        if constexpr (EPI == LIN_RESIDUAL) {
 #pragma unroll
-            for (int v0 = 0; v0 < 4 * TN; v0 += V) {
-                const int col = u0 + v0;
-                if (col >= unit_end) continue;
-                const size_t o = (size_t)(col / out_chunk) * M * out_chunk + (size_t)m * out_chunk + col % out_chunk;
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int x = 0; x < NV; ++x)
+                    __builtin_memcpy(rr[i][x], __builtin_assume_aligned(residual + at[x] + (size_t)min(row_of(i), M - 1) * row_width, V * 2), V * 2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int x = 0; x < NV; ++x) {
                 float v[V];
 #pragma unroll
-                for (int e = 0; e < V; ++e) v[e] = acc[i][(v0 + e) >> 2][e & 3];
+                for (int e = 0; e < V; ++e) v[e] = acc[i][(x * V + e) >> 2][e & 3];
                 if constexpr (EPI == LIN_RESIDUAL) {
-                    uint32_t rr[V / 2];
-                    __builtin_memcpy(rr, __builtin_assume_aligned(residual + o, V * 2), V * 2);
 #pragma unroll
-                    for (int e = 0; e < V / 2; ++e) { v[2 * e] += bf16_lo(rr[e]); v[2 * e + 1] += bf16_hi(rr[e]); }
+                    for (int e = 0; e < V / 2; ++e) { v[2 * e] += bf16_lo(rr[i][x][e]); v[2 * e + 1] += bf16_hi(rr[i][x][e]); }
                 }
-                store_bf16<V>(out + o, v);
+                if (row_of(i) < M && u0 + x * V < unit_end) store_bf16<V>(out + at[x] + (size_t)row_of(i) * row_width, v);
             }
-        } else {
-            constexpr int V = (TN % 4 == 0) ? 8 : (TN % 2 == 0) ? 4 : 2;      // outputs per store
+    } else {
+        // ROPE: (cos, sin) of channels 2 e and 2 e + 1 of the next row are requested in front of a row's arithmetic
+        float4 cs[2][EPI == LIN_ROPE ? NV : 1][V / 2];
+        auto request = [&](int i) {
 #pragma unroll
-            for (int v0 = 0; v0 < 2 * TN; v0 += V) {
-                const int u = u0 + v0;
-                if (u >= unit_end) continue;
+            for (int n = 0; n < NV; ++n)
+#pragma unroll
+                for (int e = 0; e < V / 2; ++e)
+                    cs[i & 1][n][e] = reinterpret_cast<const float4*>(rope_cs + (size_t)min(row_of(i), M - 1) * half + c[n])[e];
+        };
+        if constexpr (EPI == LIN_ROPE) request(0);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            if constexpr (EPI == LIN_ROPE) if (i + 1 < TM) request(i + 1);
+#pragma unroll
+            for (int n = 0; n < NV; ++n) {
                 float x[V], y[V];
 #pragma unroll
-                for (int e = 0; e < V; ++e) { x[e] = acc[i][(v0 + e) >> 1][e & 1]; y[e] = acc[i][(v0 + e) >> 1][2 + (e & 1)]; }
+                for (int e = 0; e < V; ++e) { x[e] = acc[i][(n * V + e) >> 1][e & 1]; y[e] = acc[i][(n * V + e) >> 1][2 + (e & 1)]; }
+                uint16_t* o = out + at[n] + (size_t)row_of(i) * row_width;
+                const bool in = row_of(i) < M && u0 + n * V < unit_end;
                 if constexpr (EPI == LIN_SWIGLU) {
 #pragma unroll
                     for (int e = 0; e < V; ++e) x[e] = x[e] / (1.f + expf(-x[e])) * y[e];
-                    store_bf16<V>(out + (size_t)m * n_out + u, x);
+                    if (in) store_bf16<V>(o, x);
                 } else {
-                    const int h = u / half, c = u - h * half, col = h * rope_dh + c;
-                    if (col < 2 * out_chunk) {                         // q and k sections; v passes through
-                        const float4* cs = reinterpret_cast<const float4*>(rope_cs + (size_t)m * half + c);
+                    const int h = (u0 + n * V) / half;
+                    if (h * rope_dh + c[n] < 2 * out_chunk) {          // q and k sections; v passes through
 #pragma unroll
                         for (int e = 0; e < V / 2; ++e) {
-                            const float4 t = cs[e];                    // (cos, sin) of channels 2e and 2e + 1
+                            const float4 t = cs[i & 1][n][e];
                             // both channels as the stored bf16 projection, then the rotation in float32
 #pragma unroll
                             for (int f = 0; f < 2; ++f) {
@@ -374,9 +405,7 @@ __global__ __launch_bounds__(512, 2) void linear_bf16_kernel(
                             }
                         }
                     }
-                    const size_t o = (size_t)(col / out_chunk) * M * out_chunk + (size_t)m * out_chunk + col % out_chunk;
-                    store_bf16<V>(out + o, x);
-                    store_bf16<V>(out + o + half, y);
+                    if (in) { store_bf16<V>(o, x); store_bf16<V>(o + half, y); }
                 }
             }
         }
