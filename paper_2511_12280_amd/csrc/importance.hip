@@ -704,14 +704,19 @@ __global__ __launch_bounds__(256) void imp_finish_kernel(
     const float* __restrict__ sp, int H, int VPAD, const int32_t* __restrict__ seq_off,
     const int32_t* __restrict__ vis_start, const int32_t* __restrict__ vis_count, const int32_t* __restrict__ score_off,
     int max_V, float* __restrict__ scores) {
+#if defined(__HIP_DEVICE_COMPILE__)
     const int b = blockIdx.y, j = blockIdx.x * 256 + threadIdx.x;
     int tok0 = seq_off[b], tok1 = seq_off[b + 1], vs0 = vis_start[b], vc = vis_count[b], s0 = score_off[b];
     float a[32];                                           // 32 independent loads in flight, added in head order
-    auto request = [&](int h0) {
+    auto request = [&](int h0) {                           // heads behind the last read as 0
+        const __amdgpu_buffer_rsrc_t rows = make_uniform_rsrc(sp + (size_t)(b * H + h0) * VPAD, (uint32_t)(min(H - h0, 32) * VPAD) * 4u);
 #pragma unroll
-        for (int u = 0; u < 32; ++u) a[u] = sp[(size_t)(b * H + min(h0 + u, H - 1)) * VPAD + min(j, VPAD - 1)];
+        for (int u = 0; u < 32; ++u) a[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, (uint32_t)(u * VPAD + j) * 4u, 0, 0));
     };
-    request(0);                                            // with the offsets (3645 scores of 32 heads 5.0 us behind them, now 4.9)
+    request(0);                                            // with the offsets, not behind them: without the next line the compiler puts them there
+#pragma unroll
+    for (int u = 0; u < 32; u += 8)
+        asm volatile("" : "+v"(a[u]), "+v"(a[u + 1]), "+v"(a[u + 2]), "+v"(a[u + 3]), "+v"(a[u + 4]), "+v"(a[u + 5]), "+v"(a[u + 6]), "+v"(a[u + 7]));
     request_together(tok0, tok1, vs0, vc, s0);
     const int N = tok1 - tok0;
     const int vs = min(max(vs0, 0), N);
@@ -720,12 +725,13 @@ __global__ __launch_bounds__(256) void imp_finish_kernel(
     float s = 0.f;
     for (int h0 = 0;;) {
 #pragma unroll
-        for (int u = 0; u < 32; ++u) s += (h0 + u < H) ? a[u] : 0.f;
+        for (int u = 0; u < 32; ++u) s += a[u];
         h0 += 32;
         if (h0 >= H) break;
         request(h0);
     }
     scores[s0 + j] = s / (float)H;
+#endif
 }
 
 // ---------------------------------------------------------------------------------------------
