@@ -119,26 +119,28 @@ constexpr int IMP_QROWS = 128, IMP_QBLK = IMP_QROWS / 16;
 template <int DH>
 struct ImpQueries {
     static constexpr int ROWB = DH * 2, NCHK = DH / 8, RPI = 64 / NCHK, MAXL = IMP_QROWS / RPI / 4;
-    int pos[MAXL];
+    int pos[MAXL];                          // as they were loaded
     __device__ __forceinline__ static int swizzle(int x) { return DH == 128 ? (x & 15) : ((x >> 1) & 7); }
     // rows i0 .. i0 + 16 * nblk - 1
-    __device__ __forceinline__ void positions(const int32_t* dec, int i0, int D, int N, int nblk) {
+    __device__ __forceinline__ void positions(const int32_t* dec, int i0, int D) {
         const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
-        for (int u = 0; u < MAXL; ++u) {
-            const int l = wave + 4 * u;
-            pos[u] = (l * RPI < nblk * 16) ? min(max(dec[min(i0 + l * RPI + lane / NCHK, D - 1)], 0), N - 1) : 0;
-        }
+        for (int u = 0; u < MAXL; ++u) pos[u] = dec[min(i0 + (wave + 4 * u) * RPI + lane / NCHK, D - 1)];
     }
-    __device__ __forceinline__ void rows(const uint16_t* q, int tok0, int H, int h, int nblk, char* lds) const {
+    __device__ __forceinline__ void rows(const uint16_t* q, int tok0, int N, int H, int h, int nblk, char* lds) {
 #if defined(__HIP_DEVICE_COMPILE__)
+        // All positions were requested, wanted or not, and are waited for here: loads under the condition below were each waited for in it, one trip
+        // to memory behind the other and the keys behind them all (first sweep over 3773 tokens, 64 deciders 11.6 -> 11.0 us, 1152 tokens, 32 deciders
+        // 6.5 -> 6.0, second sweep 9.2 -> 8.6 with the statistics in front).
+#pragma unroll
+        for (int u = 0; u < MAXL; ++u) asm volatile("" : "+v"(pos[u]));
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
 #pragma unroll
         for (int u = 0; u < MAXL; ++u) {
             const int l = wave + 4 * u;
             if (l * RPI < nblk * 16) {
                 const int x = l * RPI + lane / NCHK;
-                const uint16_t* p = q + ((size_t)(tok0 + pos[u]) * H + h) * DH + (((lane % NCHK) ^ swizzle(x)) << 3);
+                const uint16_t* p = q + ((size_t)(tok0 + min(max(pos[u], 0), N - 1)) * H + h) * DH + (((lane % NCHK) ^ swizzle(x)) << 3);
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p,
                                                  (lds_ptr_t)(lds + l * 1024), 16, 0, 0);
             }
@@ -230,17 +232,17 @@ __global__ __launch_bounds__(256, 2) void imp_stats_bf16(
     const int wrows = min(DPAD, IMP_QROWS);
 
     ImpQueries<DH> queries;
-    queries.positions(dec, 0, D, N, min(nblk, IMP_QBLK));
+    queries.positions(dec, 0, D);
     bf16x8 kf[IMP_SUB_STATS][KS];
     const int wave_key = key_base + wave * IMP_SUB_STATS * 16;
     load_keys<DH, IMP_SUB_STATS>(k + ((size_t)(tok0 + key_base) * H + h) * DH, min(N - key_base, KC), H, wave * IMP_SUB_STATS * 16, r, g, kf);
-    queries.rows(q, tok0, H, h, min(nblk, IMP_QBLK), qs);
+    queries.rows(q, tok0, N, H, h, min(nblk, IMP_QBLK), qs);
     const bool ragged = wave_key + IMP_SUB_STATS * 16 > N;              // uniform: some of the wave's keys lie past the end
     for (int b0 = 0; b0 < nblk; b0 += IMP_QBLK) {
     const int nb = min(nblk - b0, IMP_QBLK);
-    if (b0 > 0) queries.rows(q, tok0, H, h, nb, qs);
+    if (b0 > 0) queries.rows(q, tok0, N, H, h, nb, qs);
     __syncthreads();
-    if (b0 + IMP_QBLK < nblk) queries.positions(dec, (b0 + IMP_QBLK) * 16, D, N, min(nblk - b0 - IMP_QBLK, IMP_QBLK));
+    if (b0 + IMP_QBLK < nblk) queries.positions(dec, (b0 + IMP_QBLK) * 16, D);
     imp_for_blocks<DH, true>(qs, nb, r, g, [&](int blk, const bf16x8 (&qf)[KS]) {
         // acc[s][e]: logit of decider (b0 + blk) * 16 + r and key 4 g + e of sub-tile s
         f32x4 acc[IMP_SUB_STATS];
@@ -314,12 +316,14 @@ __global__ __launch_bounds__(256, 4) void imp_scores_bf16(
     const int h = blockIdx.x, chunk = blockIdx.y, b = blockIdx.z;
     int tok0 = seq_off[b], tok1 = seq_off[b + 1], d0 = dec_off[b], d1 = dec_off[b + 1], vs0 = vis_start[b], vc = vis_count[b];
     // The statistics (a decider to a thread) are requested with the offsets, the keys with the deciders' positions, and the
-    // statistics are put together while those are under way (64 deciders of 3773 tokens x 32 heads, the keys behind them 9.7 us, now 9.4).
+    // statistics are put together while those are under way.
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
     const float2* p = part + ((size_t)(b * H + h) * NCH) * DPAD + min(tid, DPAD - 1);
     float2 a[8];                                                        // chunks of keys requested at once
 #pragma unroll
     for (int u = 0; u < 8; ++u) a[u] = p[(size_t)min(u, NCH - 1) * DPAD];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) asm volatile("" : "+v"(a[u]));          // or the compiler requests them behind the keys
     request_together(tok0, tok1, d0, d1, vs0, vc);
     const int N = min(tok1 - tok0, NCH * KC);
     const int D = min(d1 - d0, max_D);
@@ -335,7 +339,7 @@ __global__ __launch_bounds__(256, 4) void imp_scores_bf16(
     float* c_lds = reinterpret_cast<float*>(smem + min(DPAD, IMP_QROWS) * DH * 2);     // [DPAD] log2-sum-exp2
 
     ImpQueries<DH> queries;
-    queries.positions(dec, 0, D, N, min(nblk, IMP_QBLK));
+    queries.positions(dec, 0, D);
     bf16x8 kf[IMP_SUB_SCORES][KS];
     float acc_s[IMP_SUB_SCORES];
     load_keys<DH, IMP_SUB_SCORES>(k + ((size_t)(tok0 + vs + key_base) * H + h) * DH, min(V - key_base, KCS), H,
@@ -349,15 +353,15 @@ __global__ __launch_bounds__(256, 4) void imp_scores_bf16(
     }
 #pragma unroll
     for (int s = 0; s < IMP_SUB_SCORES; ++s) acc_s[s] = 0.f;
-    queries.rows(q, tok0, H, h, min(nblk, IMP_QBLK), qs);
+    queries.rows(q, tok0, N, H, h, min(nblk, IMP_QBLK), qs);
     for (int b0 = 0; b0 < nblk; b0 += IMP_QBLK) {
     const int nb = min(nblk - b0, IMP_QBLK);
     if (b0 > 0) {
         __syncthreads();
-        queries.rows(q, tok0, H, h, nb, qs);
+        queries.rows(q, tok0, N, H, h, nb, qs);
     }
     __syncthreads();
-    if (b0 + IMP_QBLK < nblk) queries.positions(dec, (b0 + IMP_QBLK) * 16, D, N, min(nblk - b0 - IMP_QBLK, IMP_QBLK));
+    if (b0 + IMP_QBLK < nblk) queries.positions(dec, (b0 + IMP_QBLK) * 16, D);
     imp_for_blocks<DH, false>(qs, nb, r, g, [&](int blk, const bf16x8 (&qf)[KS]) {
         const f32x4 cc = *reinterpret_cast<const f32x4*>(c_lds + (b0 + blk) * 16 + 4 * g);
         f32x4 acc[IMP_SUB_SCORES];
