@@ -920,10 +920,18 @@ __global__ __launch_bounds__(256, CPT == 2 ? 7 : 5) void merge_scatter_kernel(
             if (c < c_hi) {
                 uint4 w;
                 if constexpr (sizeof(T) == 2) {
-                    w.x = pack_bf16x2(acc[u][0] / inv, acc[u][1] / inv);
-                    w.y = pack_bf16x2(acc[u][2] / inv, acc[u][3] / inv);
-                    w.z = pack_bf16x2(acc[u][4] / inv, acc[u][5] / inv);
-                    w.w = pack_bf16x2(acc[u][6] / inv, acc[u][7] / inv);
+                    // The quotients one by one: seen as pairs by the compiler, because the conversion takes two, all sums above became
+                    // pairs of registers, with a wait at every row's addition (16 samples 86 -> 105 us, two payloads 18.3 -> 21.6).
+                    float q[EPC];
+#pragma unroll
+                    for (int e = 0; e < EPC; ++e) {
+                        q[e] = acc[u][e] / inv;
+                        asm volatile("" : "+v"(q[e]));
+                    }
+                    w.x = pack_bf16x2(q[0], q[1]);
+                    w.y = pack_bf16x2(q[2], q[3]);
+                    w.z = pack_bf16x2(q[4], q[5]);
+                    w.w = pack_bf16x2(q[6], q[7]);
                 } else {
                     w.x = __float_as_uint(acc[u][0] / inv); w.y = __float_as_uint(acc[u][1] / inv);
                     w.z = __float_as_uint(acc[u][2] / inv); w.w = __float_as_uint(acc[u][3] / inv);
