@@ -1200,6 +1200,35 @@ def test_update_deciders_batch_and_chain_into_importance():
     np.testing.assert_array_equal(step.importance()[0], S_ref)
 
 
+@pytest.mark.parametrize("nb", [1, 2, 17, 64, 65, 130])            # one sample a workgroup up to 64 samples, runs of two and three above
+@pytest.mark.parametrize("share", [0.01, 0.5, 1.0])                # of the positions that were decided last
+def test_update_deciders_sizes(nb, share):
+    rng = np.random.default_rng(1000 * nb + int(100 * share))
+    edge = [4097, 1, 1024, 0, 64, 65, 1025, 4096, 63, 8193, 1023, 2688, 4095]
+    lens = [edge[b % len(edge)] if b < 2 * len(edge) else int(rng.integers(0, 300)) for b in range(nb)]
+    M, max_D, total = 126336, 200, sum(lens)
+    prev, cur = rng.integers(0, 32000, total).astype(np.int32), rng.integers(0, 32000, total).astype(np.int32)
+    prev[rng.random(total) < 0.5] = M
+    cur[(prev == M) & (rng.random(total) >= share)] = M
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    idx = torch.full((nb * max_D + 1,), -7, dtype=torch.int32, device="cuda")
+    off, cnt = torch.full((nb + 1,), -7, dtype=torch.int32, device="cuda"), torch.full((nb,), -7, dtype=torch.int32, device="cuda")
+    pad = torch.full((3,), M, dtype=torch.int32)               # ids that lie on 4 bytes only, and a decider on either side of them
+    p = torch.cat([pad, torch.from_numpy(prev), pad]).cuda()[3:3 + total]
+    c = torch.cat([pad * 0, torch.from_numpy(cur), pad * 0]).cuda()[3:3 + total]
+    B.d3tom_update_deciders(p, c, M, torch.from_numpy(offs).cuda(), max_D, idx, off, cnt)
+    want, ends, counts = [], [0], []
+    for b in range(nb):
+        ref = oracle.deciders(prev[offs[b]:offs[b + 1]], cur[offs[b]:offs[b + 1]], M)
+        want += list(ref[:max_D])
+        ends.append(len(want))
+        counts.append(len(ref))
+    np.testing.assert_array_equal(off.cpu().numpy(), ends)
+    np.testing.assert_array_equal(cnt.cpu().numpy(), counts)
+    np.testing.assert_array_equal(idx.cpu().numpy()[:len(want)], want)
+    assert (idx.cpu().numpy()[len(want):] == -7).all()
+
+
 def test_bitwise_determinism():
     c = W.random_case(41, 900, 4 * 128, 4, 30, 800, 12, dtype="bf16", centres=60)
     k = oracle.keep_count(800, 0.2)
