@@ -13,7 +13,7 @@
 // the rescale of O^T is a per-lane scalar.  The contraction index of the second product (keys) is
 // fed in the order the accumulator holds it; V^T is read from LDS in that same order.
 //
-// A workgroup has eight waves of 32 (or 16) queries in two groups of four; wave i and wave i + 4 share a SIMD.  The groups
+// A workgroup has eight waves of 32 or 16 queries in two groups of four; wave i and wave i + 4 share a SIMD.  The groups
 // alternate (ping-pong): while one issues the MFMAs of a 64-key tile (S of tile i + 1, O += V P of tile i: 64 of them, 1024
 // clocks), the other does the softmax arithmetic of its tile; a barrier ends the phase.  That pays because the smaller MFMA
 // shape lets another wave's vector instructions through: per tile 1058 clocks of MFMAs and 756 of softmax arithmetic (an fma,
@@ -143,7 +143,11 @@ constexpr int ATT_WKEYS = 3584;     // longest sample of the weighted tiled kern
 // phases per unit, and this is half as long a chain on twice as many units: 8 heads of 128, 775 keys 15.8 -> 11.3 us, 2000 keys 33.4 -> 23.1,
 // 16 heads of 64, 1024 keys 13.9 -> 9.4.  No part of a phase bounds it (without loads, exponentials, rescaling or reads of V it is 3 to 8 %
 // faster each).
-template <int DH, bool WGT, int NQ, bool TURNS, bool SKIP, bool SPLIT>
+//
+// UNEVEN: 192 queries, 32 to a wave of group 0 and 16 to one of group 1.  Where 256 queries fill three quarters of a round of compute units or less, or 128 need
+// another round.  A tile of keys takes 0.86 to 0.94 of the time that 256 queries take, not 0.75: group 1's fragments feed one MFMA each, and four waves
+// that read 32 KB of them keep the LDS busy as long as group 0's MFMAs take.  The sums of a row are those of the other two, bit by bit.
+template <int DH, bool WGT, int NQ, bool TURNS, bool SKIP, bool SPLIT, bool UNEVEN>
 __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ cu, int H, int nB, int nqt, float scale2, uint16_t* __restrict__ o, KeyWeights kw) {
@@ -161,7 +165,8 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     constexpr int STAGE = 2 * TILE;             // stage j: K of tile j, V of tile j - 1
     constexpr int NS = ATT_SLOTS;
     constexpr int AHEAD = SPLIT ? 2 : NS - 1;   // the softmax phase of tile j fetches stage j + AHEAD
-    constexpr int BQ = NQ * (SPLIT ? 64 : 128); // queries of the workgroup: NQ blocks of 16 per wave
+    constexpr int BQ = UNEVEN ? 192 : NQ * (SPLIT ? 64 : 128);          // queries of the workgroup: NQ blocks of 16 per wave
+    static_assert(!UNEVEN || (NQ == 2 && !SPLIT), "group 1 has half of group 0's queries");
     constexpr int KPRE = 2 * KS;                // K fragments read ahead: the first 32 keys
     typedef unsigned att_u4 __attribute__((ext_vector_type(4)));
     extern __shared__ __attribute__((aligned(16))) char ring[];
@@ -210,7 +215,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
             const int c0 = cu[min(smp, nB - 1)], c1 = cu[min(smp + 1, nB)];
             const int len = smp < nB ? max(min(c1 - c0, WGT ? ATT_WKEYS : 0x7FFFFFFF), 0) : 0;
             const int left = len % BQ, all = (len + BQ - 1) / BQ;
-            int lone = two && left > 0 && left <= BQ / 2;
+            int lone = !UNEVEN && two && left > 0 && left <= BQ / 2;
             {
                 // passes over the XCD's units with the last tiles among the others, and with them behind all others
                 const int sum = is_last ? 0 : all, sum_lone = is_last ? 0 : lone;
@@ -265,7 +270,8 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     auto place_head = [&] { head_at = ((size_t)tok0 * rs + (size_t)h * DH) * 2; head_bytes = (uint32_t)(((size_t)(n - 1) * rs + DH) * 2); };
     place_head();
 
-    int q0 = qt * BQ + wq * NQ * 16;            // this wave's first query
+    auto first_query = [&] { return qt * BQ + (UNEVEN && grp ? 64 + wq * 16 : wq * NQ * 16); };
+    int q0 = first_query();                     // this wave's first query
     bf16x8 qf[NQ][KS];
     f32x4 ot[DB][NQ];
     // m_run: running maximum of the RAW logits; ms: what the exponents subtract; l_run: this lane's part of the column's sum
@@ -354,7 +360,8 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     // up the registers it goes into (a bunch of reads in front of each part: 1710 clocks per phase; dealt: 1350).
     static_assert(KPRE == DB, "a V fragment follows every K fragment");
     uint32_t step = 0;                          // from the stage of the last MFMA phase to the next one
-    auto mfma_phase = [&](int j, auto qk_c, auto pv_c) {
+    auto mfma_phase = [&](int j, auto qk_c, auto pv_c, auto blocks) {
+        constexpr int NB = decltype(blocks)::value;         // query blocks of this wave: NQ, or (UNEVEN, group 1) one
         constexpr bool QK = decltype(qk_c)::value, PV = decltype(pv_c)::value;
         typedef __attribute__((__vector_size__(8 * sizeof(short)))) short att_short8;
         att_short8 vf[DB];                      // V^T of 32 keys, 16 dims each
@@ -375,7 +382,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
             for (int i = 0; i < 2 * KPRE; ++i) {
                 const int f = i % KPRE, ks = f / 2, kb = (i / KPRE) * 2 + f % 2;
 #pragma unroll
-                for (int qb = 0; qb < NQ; ++qb)
+                for (int qb = 0; qb < NB; ++qb)
                     st[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[f], qf[qb][ks], ks ? st[kb][qb] : c0[kb], 0, 0, 0);
                 fence();
                 if (PV && i == KPRE) next_tile();
@@ -393,7 +400,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
             for (int i = 0; i < 2 * DB; ++i) {
                 const int kt = i / DB, t = i % DB;
 #pragma unroll
-                for (int qb = 0; qb < NQ; ++qb)
+                for (int qb = 0; qb < NB; ++qb)
                     ot[t][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf[t]), pf[kt][qb], ot[t][qb], 0, 0, 0);
                 fence();
                 if (kt == 0) read_v(1, t);
@@ -406,13 +413,14 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
             for (int i = 0; i < KA; ++i) move(ka[i], step);
         }
     };
-    auto softmax_phase = [&](int j, auto last_c) {
+    auto softmax_phase = [&](int j, auto last_c, auto blocks) {
+        constexpr int NB = decltype(blocks)::value;
         constexpr bool LAST = decltype(last_c)::value;
         if (LAST && !WGT && (tile_of(j) + 1) * ATT_BK > n) {
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-                for (int qb = 0; qb < NQ; ++qb)
+                for (int qb = 0; qb < NB; ++qb)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         if (tile_of(j) * ATT_BK + kb * 16 + g * 4 + e >= n) st[kb][qb][e] = -INFINITY;
@@ -435,10 +443,10 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
         for (int i = 0; i < VA; ++i) move(va[i], step);
         // The running maximum.  A lane sees its own 16 of a column's 64 logits; only if one of them exceeds the column's maximum do
         // the four lanes meet and the accumulators get their new scale.
-        float peak[NQ];
-        uint64_t above[NQ];
+        float peak[NB];
+        uint64_t above[NB];
 #pragma unroll
-        for (int qb = 0; qb < NQ; ++qb) {
+        for (int qb = 0; qb < NB; ++qb) {
             peak[qb] = m_run[qb];
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb)
@@ -447,7 +455,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
             above[qb] = __builtin_amdgcn_ballot_w64(peak[qb] > m_run[qb]);
         }
 #pragma unroll
-        for (int qb = 0; qb < NQ; ++qb) {
+        for (int qb = 0; qb < NB; ++qb) {
             if (above[qb] != 0) {
                 const float m_new = att_quad_max(peak[qb]);    // finite: every tile holds at least one key of the sample
                 const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_new) * scale2);
@@ -469,7 +477,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-            for (int qb = 0; qb < NQ; ++qb)
+            for (int qb = 0; qb < NB; ++qb)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                 {
@@ -479,7 +487,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
                 }
         // (all of it here, not behind what ends the phase)
 #pragma unroll
-        for (int qb = 0; qb < NQ; ++qb) asm volatile("" : "+v"(pf[0][qb]), "+v"(pf[1][qb]), "+v"(l_run[qb]));
+        for (int qb = 0; qb < NB; ++qb) asm volatile("" : "+v"(pf[0][qb]), "+v"(pf[1][qb]), "+v"(l_run[qb]));
     };
 
     int ntile = (n + KROUND - 1) / KROUND;      // tiles of a group (SPLIT: the last one may lie past the end in part or, of group 1, in full)
@@ -539,7 +547,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     // tiles and keeps step: in a last tile of at most 128 queries a SIMD has one wave to serve instead of two, in others the card has
     // less to do.  (Last tiles computed in full before: 16 samples of 614 .. 1536 keys 346 -> 332 us, 64 of 300 .. 1000 at 8
     // heads 166 -> 155, 12 of 270 .. 800 84.6 -> 82.3, one of 1951 61.4 -> 60.5, of 3700 203 -> 201; 8 of 1000, 232 queries in the last, 133.)
-    auto sweep = [&](auto live_c) {
+    auto sweep = [&](auto live_c, auto blocks) {
         constexpr bool LIVE = decltype(live_c)::value;
         if constexpr (!SPLIT) issue(2);
         if constexpr (LIVE) {
@@ -553,7 +561,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
         // is all that is on its way; the group waits for it before the barrier that ends its own MFMA phase of tile j.
         if (grp == 1) { if (!SPLIT && first) wait_loads<KEEP>(); phase_barrier(); }
         bool wait0 = SPLIT || (grp == 0 && first);         // (behind another item the first two stages have landed, and its stores may still be on their way)
-        if constexpr (LIVE) mfma_phase(0, yes(), no());
+        if constexpr (LIVE) mfma_phase(0, yes(), no(), blocks);
         // The last tile is peeled off: a loop left in its middle keeps both the accumulators before and after the MFMA phase alive.
         // (The weighted form with heads of 128 gets its trip count in a scalar register by force: the compiler counted in a vector register and
         // branched on vcc, 0.5 % of single rounds of 128-query tiles.  The others are 0.2 to 0.5 % faster as they are.)
@@ -566,7 +574,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
             if (SPLIT || grp == 0) phase_barrier();
             if constexpr (LIVE) {
                 __builtin_amdgcn_s_setprio(2);
-                softmax_phase(j, no());
+                softmax_phase(j, no(), blocks);
                 __builtin_amdgcn_s_setprio(0);
                 __builtin_amdgcn_sched_barrier(0);
                 __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): the fragments are there (a wait the compiler knows of)
@@ -575,13 +583,13 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
             }
             if (!SPLIT && grp == 1) wait_loads<KEEP>();
             if (SPLIT || grp == 1) phase_barrier();
-            if constexpr (LIVE) mfma_phase(j + 1, yes(), yes());
+            if constexpr (LIVE) mfma_phase(j + 1, yes(), yes(), blocks);
         }
         if (SPLIT || grp == 0) { wait_loads<0>(); phase_barrier(); }
-        if constexpr (LIVE) softmax_phase(ntile - 1, yes());
+        if constexpr (LIVE) softmax_phase(ntile - 1, yes(), blocks);
         if (grp == 1) wait_loads<0>();
         if (SPLIT || grp == 1) phase_barrier();
-        if constexpr (LIVE) mfma_phase(ntile, no(), yes());
+        if constexpr (LIVE) mfma_phase(ntile, no(), yes(), blocks);
     };
     // SPLIT: the two parts of the keys meet.  A wave gives the channels that it does not finish to the wave with the same queries (group 0
     // finishes the first half of them), takes that wave's part of its own, and stores its half rows through LDS.
@@ -627,11 +635,11 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
         }
     };
     for (int pass = 1;; ++pass) {
-        if constexpr (SKIP) {
-            if (q0 < n) sweep(yes()); else sweep(no());
-        } else {
-            sweep(yes());
-        }
+        using all = std::integral_constant<int, NQ>;
+        using one = std::integral_constant<int, 1>;
+        if (SKIP && q0 >= n) sweep(no(), all());
+        else if (UNEVEN && grp == 1) sweep(yes(), one());
+        else sweep(yes(), all());
         wait_loads<0>();                        // nothing may be in flight into LDS when the workgroup ends
         if (grp == 0) phase_barrier();
         if constexpr (SPLIT) {
@@ -661,7 +669,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
                 rq = rows_of(q);
                 place_head();
                 first_tile();
-                q0 = qt * BQ + wave * NQ * 16;
+                q0 = first_query();
                 ntile = (n + ATT_BK - 1) / ATT_BK;
                 issue(0);
                 issue(1);
@@ -676,8 +684,10 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
         }
         char* ow = ring + slot * STAGE + (wave & 3) * QROWS * ROWB;
         static_assert(4 * QROWS * ROWB <= STAGE, "a group's rows fit into a slot");
+        const int blocks = UNEVEN && grp == 1 ? 1 : NQ;
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) {
+            if (qb >= blocks) break;
             const float inv = 1.0f / att_quad_sum(l_run[qb]);
 #pragma unroll
             for (int t = 0; t < DB; ++t) {
@@ -690,6 +700,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
         wait_lds();
 #pragma unroll
         for (int i = 0; i < QLD; ++i) {
+            if (i * RPI >= blocks * 16) break;
             const int x = i * RPI + el / NCHK;
             const uint4 w = *reinterpret_cast<const uint4*>(ow + x * ROWB + (((el % NCHK) ^ row_swizzle(x)) << 4));
             // rows past the end of the sample lie outside the buffer and are not written
@@ -698,7 +709,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
         if (!more) break;
         clear();
         first = false;
-        wait_loads<QLD>();                      // all loads have landed; the stores may be on their way
+        wait_loads<UNEVEN ? QLD / 2 : QLD>();   // all loads have landed; the stores (UNEVEN: of group 1, half as many) may be on their way
         __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): the rows are out of the slots, the weights are written
         phase_barrier();
     }
@@ -1140,7 +1151,13 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
         // 1.00 from 13 rounds on).
         const long wide = (ceil_div(max_seqlen, 256) * heads + 255) / 256, narrow = (ceil_div(max_seqlen, 128) * heads + 255) / 256;
         const int nq = split || (dh == 64 && B > 1) || (dh == 128 ? 66 : 55) * narrow < 100 * wide ? 1 : 2;
-        const int nqt = ceil_div(max_seqlen, split ? 64 : nq * 128);
+        // 192 queries, by rounds again.  Of one round whatever the other samples' lengths are (all tiles run side by side, the longest sample's decide), of
+        // several only for one sample, whose tiles the host knows.  (128, 192 and 256 queries; 32 heads: 1100 keys 41.2, 28.5 and 31.6 us, 1500 52.3, 39.5 and
+        // 41.9, 2060 94.4, 93.1 and 94.3, 2400 117, 106 and 123, 3000 155, 141 and 152, 4500 361, 311 and 340; 2 x 700 28.5, 22.1 and 23.4; 16 heads,
+        // 2200 71.2, 48.1 and 53.4; weighted, 1100 43.9, 30.0 and 32.5.  Where 192 take a round more: 1600 keys 54.4, 72.3 and 43.4, 3773 250, 243 and 201.)
+        const long mid = (ceil_div(max_seqlen, 192) * heads + 255) / 256;
+        const bool uneven = dh == 128 && !split && (mid == 1 || B == 1) && 90 * mid < (nq == 1 ? 66 * narrow : 100 * wide);
+        const int nqt = ceil_div(max_seqlen, split ? 64 : uneven ? 192 : nq * 128);
         // Several rounds of workgroups that have a compute unit to themselves: one per unit, which takes its tiles in turn, samples by
         // falling length (one tile per workgroup / in turn: 16 x 700 .. 1505 keys 440 / 422 us, 4 x 575 .. 1951 141 / 133, 12 x 270 .. 800
         // 114 / 82, 8 x 1000 149 / 145, one sample of 3773 211 / 211; 8 heads, 16 x 1000 .. 3000 303 / 262).
@@ -1152,24 +1169,26 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
 #define D3TOM_ATT(KERNEL)                                                                                            \
     D3TOM_LAUNCH(ATTEND, st, (KERNEL<<<g, threads, lds, st>>>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, \
                                                            cu_seqlens, H, B, nqt, scale2, (uint16_t*)o, kw)))
-#define D3TOM_ATT8(DHV, WGTV, NQV, TURNSV, SKIPV, SPLITV)                                                                   \
+#define D3TOM_ATT8(DHV, WGTV, NQV, TURNSV, SKIPV, SPLITV, UNEVENV)                                                           \
     do {                                                                                                                    \
         static PerDeviceOnce lds_setup;                                                                                     \
-        if (!lds_setup.run([] { return raise_dynamic_lds(attend_bf16_kernel<DHV, WGTV, NQV, TURNSV, SKIPV, SPLITV>, ATT_SLOTS * 2 * ATT_BK * DHV * 2); })) \
+        if (!lds_setup.run([] { return raise_dynamic_lds(attend_bf16_kernel<DHV, WGTV, NQV, TURNSV, SKIPV, SPLITV, UNEVENV>, ATT_SLOTS * 2 * ATT_BK * DHV * 2); })) \
             return D3TOM_ERR_DEVICE;                                                                                        \
-        D3TOM_ATT((attend_bf16_kernel<DHV, WGTV, NQV, TURNSV, SKIPV, SPLITV>));                                                     \
+        D3TOM_ATT((attend_bf16_kernel<DHV, WGTV, NQV, TURNSV, SKIPV, SPLITV, UNEVENV>));                                                     \
     } while (0)
-#define D3TOM_ATT8_2(DHV, WGTV) do { if (turns) D3TOM_ATT8(DHV, WGTV, 2, true, true, false); else D3TOM_ATT8(DHV, WGTV, 2, false, true, false); } while (0)
-#define D3TOM_ATT8_1(DHV, WGTV) do { if (skip) D3TOM_ATT8(DHV, WGTV, 1, false, true, false); else D3TOM_ATT8(DHV, WGTV, 1, false, false, false); } while (0)
-#define D3TOM_ATT8_128(WGTV) do { if (nq == 2) D3TOM_ATT8_2(128, WGTV); else if (turns) D3TOM_ATT8(128, WGTV, 1, true, true, false); else D3TOM_ATT8_1(128, WGTV); } while (0)
+#define D3TOM_ATT8_2(DHV, WGTV) do { if (turns) D3TOM_ATT8(DHV, WGTV, 2, true, true, false, false); else D3TOM_ATT8(DHV, WGTV, 2, false, true, false, false); } while (0)
+#define D3TOM_ATT8_1(DHV, WGTV) do { if (skip) D3TOM_ATT8(DHV, WGTV, 1, false, true, false, false); else D3TOM_ATT8(DHV, WGTV, 1, false, false, false, false); } while (0)
+#define D3TOM_ATT8_U(WGTV) do { if (turns) D3TOM_ATT8(128, WGTV, 2, true, true, false, true); else D3TOM_ATT8(128, WGTV, 2, false, false, false, true); } while (0)
+#define D3TOM_ATT8_128(WGTV) do { if (uneven) D3TOM_ATT8_U(WGTV); else if (nq == 2) D3TOM_ATT8_2(128, WGTV); else if (turns) D3TOM_ATT8(128, WGTV, 1, true, true, false, false); else D3TOM_ATT8_1(128, WGTV); } while (0)
 #define D3TOM_ATT8_64(WGTV) do { if (nq == 2) D3TOM_ATT8_2(64, WGTV); else D3TOM_ATT8_1(64, WGTV); } while (0)
         if (split) {
-            if (dh == 128) { if (wgt) D3TOM_ATT8(128, true, 1, false, false, true); else D3TOM_ATT8(128, false, 1, false, false, true); }
-            else           { if (wgt) D3TOM_ATT8(64, true, 1, false, false, true);  else D3TOM_ATT8(64, false, 1, false, false, true); }
+            if (dh == 128) { if (wgt) D3TOM_ATT8(128, true, 1, false, false, true, false); else D3TOM_ATT8(128, false, 1, false, false, true, false); }
+            else           { if (wgt) D3TOM_ATT8(64, true, 1, false, false, true, false);  else D3TOM_ATT8(64, false, 1, false, false, true, false); }
         } else if (dh == 128) { if (wgt) D3TOM_ATT8_128(true); else D3TOM_ATT8_128(false); }
         else           { if (wgt) D3TOM_ATT8_64(true);  else D3TOM_ATT8_64(false); }
 #undef D3TOM_ATT8_64
 #undef D3TOM_ATT8_128
+#undef D3TOM_ATT8_U
 #undef D3TOM_ATT8_1
 #undef D3TOM_ATT8_2
 #undef D3TOM_ATT8

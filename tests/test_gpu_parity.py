@@ -587,6 +587,26 @@ def test_attend_groups_that_share_queries(H, dh, lens, rise, weighted):
         check_attend(o, q, k, v, "bf16", rows=rows, key_weight=key_weights(n, vs, c) if weighted else None)
 
 
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("H,dh,lens", [
+    (32, 128, [1025]), (32, 128, [1152]), (32, 128, [1153]), (32, 128, [1281]), (32, 128, [1536]),      # last tiles of 65 to 192 queries, one round
+    (32, 128, [700, 1, 128, 129]), (32, 128, [768, 192, 193, 64]), (64, 128, [513, 144]), (40, 128, [1040]),      # ragged, samples of one tile
+    (32, 128, [2049]), (32, 128, [2060]), (32, 128, [2113]), (33, 128, [3072]), (64, 128, [1409]),      # tiles in turn
+    (60, 128, [769]), (60, 128, [850]), (60, 128, [1000]), (32, 128, [1537]),      # 256 queries beside them, one round
+])
+def test_attend_tiles_of_192_queries(H, dh, lens, weighted):
+    """Two query blocks to a wave of one group of waves, one to a wave of the other: every row around the borders between waves, groups and tiles."""
+    base = W.random_qkv(960 + H, max(lens), H, dh, "bf16")
+    qkv = [tuple(np.roll(t, i, axis=0)[:n] for t in base) for i, n in enumerate(lens)]
+    vis, counts = [n // 5 for n in lens], [(1 + np.arange(n // 2) % 37).astype(np.int32) for n in lens]
+    outs = gpu_attend_weighted(qkv, counts, vis, "bf16") if weighted else gpu_attend(qkv, "bf16")
+    for (q, k, v), o, vs, c in zip(qkv, outs, vis, counts):
+        n = len(q)
+        edges = [r for t in range(0, n, 192) for r in (t, t + 31, t + 32, t + 127, t + 128, t + 143, t + 144, t + 191)]
+        rows = np.array(sorted({r for r in edges if r < n} | set(range(max(n - 9, 0), n))))
+        check_attend(o, q, k, v, "bf16", rows=rows, key_weight=key_weights(n, vs, c) if weighted else None)
+
+
 def test_attend_special_cases_bf16():
     q, k, v = W.random_qkv(5, 150, 2, 128, "bf16", spread=2.0)
     v1 = np.broadcast_to(v[:1], v.shape).copy()
