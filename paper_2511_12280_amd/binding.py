@@ -77,6 +77,8 @@ _lib.d3tom_linear_tile_name.restype = ctypes.c_char_p
 _lib.d3tom_linear_tile_name.argtypes = [_i]
 _lib.d3tom_linear_plan.restype = _i
 _lib.d3tom_linear_plan.argtypes = [_i, _i, _i, _sz, _i32p]
+_lib.d3tom_attend_plan.restype = _i
+_lib.d3tom_attend_plan.argtypes = [_i] * 6 + [_i32p]
 _lib.d3tom_linear_pinned.restype = _i
 _lib.d3tom_linear_pinned.argtypes = [_vp, _vp, _i, _i, _i, _i, _vp, _vp, _i, _i, _i, _i, _vp]
 
@@ -319,6 +321,13 @@ def d3tom_attend_weighted(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, cu_
                                          float(scale), counts, kept_off, vis_start, o, None, 0,
                                          _stream(stream)), "d3tom_attend_weighted")
     return o
+
+
+def d3tom_attend_plan(dt: int, B: int, max_seqlen: int, H: int, dh: int, whole: bool = False):
+    """(kernel: 0 generic, 1 short samples, 2 tiles; queries of a workgroup; whether it takes several tiles in turn; dynamic LDS bytes); host only."""
+    plan = (ctypes.c_int32 * 4)()
+    _check(_lib.d3tom_attend_plan(dt, B, max_seqlen, H, dh, int(whole), plan), "d3tom_attend_plan")
+    return tuple(plan)
 
 
 def d3tom_update_deciders(prev_ids: torch.Tensor, cur_ids: torch.Tensor, mask_id: int, seq_off: torch.Tensor, max_D: int,

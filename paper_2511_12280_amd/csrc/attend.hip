@@ -720,22 +720,23 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
 // on half of the CUs.  Here a workgroup owns 32 or 64 queries (QH halves of 32) of one head.  The waves of a half take the 32-key
 // tiles w, w + 4, w + 8, ... with the same transposed products as above, and at the end the four partial results
 // (running max, sum, O^T) of a half meet in LDS, rows of queries, from where eight threads to a row store whole lines.  A step is four tiles, one for
-// each wave of a half; the waves of two halves share their tile, load half of it each and meet at one barrier a step.  K and V of a
-// step go to LDS by direct loads one step ahead, the queries in front of them take the same way.
+// each wave of a half.  K and V go to LDS by direct loads, the queries in front of them take the same way.  With one half nobody else reads a
+// wave's tiles, and each has one place: K of the next step is requested behind the first product, V in front of the second one, and two workgroups of heads of 128 (four
+// of 64) fit on a unit, which hide each other's waits.  The waves of two halves share their tile, load half of it each and meet at one barrier a step, with a second place for
+// the step ahead.
 // Bound by the chain of trips to memory where workgroups are few (the sample's offsets; queries and tiles: 1080 and some 2500 clocks), and by what a
-// compute unit takes in where they are many, four times the K and V per query of the kernel above with 32 queries, twice with 64.  Against 32 queries
-// always, queries in fragments of 32 bytes a row that were waited for before the first tile was requested, and a tile's K and V requested when the one before
-// had been read (the same bits): 32 heads of 128, 100 rows 4.9 -> 4.15 us, 231 5.85 -> 5.4, 300 9.0 -> 7.4, 493 12.5 -> 10.1, weighted 14.5 -> 11.0; 8 heads, 493 rows
-// 7.13 -> 7.19; 4 x 300 rows 23.8 -> 22.5, 4 x 100 .. 128 7.6 -> 6.0, 8 x 120 .. 250 27.1 -> 24.4; 16 heads of 64, 331 rows 4.8 -> 4.3, 8 x 120 .. 250 8.1 -> 6.7.
-// (64 queries: the next step requested in front of the first product 10.3, behind it 10.1.  32 queries: K waited for apart from V, and the loads two steps
-// ahead: no gain.)
+// compute unit takes in where they are many, four times the K and V per query of the kernel above with 32 queries, twice with 64.
+// With 32 queries, against two places for a wave's tiles, one workgroup to a unit with heads of 128, and 64 queries wherever 32 need more than a round (the same
+// bits): 32 heads of 128, 16 x 8 rows 7.1 -> 4.6 us, 8 x 65 9.4 -> 7.8, 9 x 100 13.0 -> 11.0, one sample of 100 rows 4.2 -> 4.1, of 200 5.4 -> 5.2, of 300 7.6 -> 7.4; 8 heads of 128, one of 512
+// 7.15 -> 6.3, 9 x 200 11.7 -> 6.8; 32 heads of 64, 16 x 21 .. 65 8.3 -> 5.5; 887 calls of up to 512 tiles of 128 queries 1.066 in the mean.
 constexpr int ATS_BK = 32;      // keys per wave tile
 constexpr int ATS_MAX_KEYS = 512;
 
 template <int DH, int QH> struct AtsLds {
     static constexpr int ROWB = DH * 2, TILE = ATS_BK * ROWB, REGION = 2 * TILE, BUF = 4 * REGION;     // a wave's K and V tile; four of them a step
     static constexpr int PITCH = DH + 4;                                                                // floats of a row of a partial O
-    static constexpr int STEPS = 2 * BUF + QH * 32 * ROWB, PARTS = 4 * QH * 32 * PITCH * 4;
+    static constexpr int BUFS = QH == 1 ? 1 : 2;                                                        // steps with a place of their own
+    static constexpr int STEPS = BUFS * BUF + QH * 32 * ROWB, PARTS = 4 * QH * 32 * PITCH * 4;
     static constexpr int BYTES = STEPS > PARTS ? STEPS : PARTS;
 };
 template <int DH, bool WGT, int QH>
@@ -777,7 +778,7 @@ __global__ __launch_bounds__(256 * QH, 2) void attend_bf16_short_kernel(
     // direct loads: same chunk swizzles as in the kernel above
     const int ld_pos = lane % NCHK, ld_row = lane / NCHK;
     const uint32_t ring0 = (uint32_t)(size_t)(lds_ptr_t)ring;
-    constexpr int Q_LDS = 2 * C::BUF;
+    constexpr int Q_LDS = C::BUFS * C::BUF;
 #pragma unroll
     for (int i = 0; i < QLD; ++i) {
         const int x = wave * QLD * RPI + i * RPI + ld_row;
@@ -790,17 +791,18 @@ __global__ __launch_bounds__(256 * QH, 2) void attend_bf16_short_kernel(
         k_off[i] = (kg * ATS_BK + r) * row_bytes + (((ld_pos ^ (r & 15)) & (NCHK - 1)) << 4);
         v_off[i] = (kg * ATS_BK + r) * row_bytes + (((ld_pos ^ ((r & 3) * 4)) & (NCHK - 1)) << 4);
     }
-    auto issue = [&](int step) {
-        const int at = step * 4 * ATS_BK * row_bytes;
-        const uint32_t dst = ring0 + (step & 1) * C::BUF + kg * C::REGION + qh * LD * 1024;
+    auto place = [&](int step) { return (C::BUFS == 2 ? (step & 1) * C::BUF : 0) + kg * C::REGION; };
+    auto issue_k = [&](int step) {
 #pragma unroll
-        for (int i = 0; i < LD; ++i) direct_load_16(rk, k_off[i] + at, dst + i * 1024);
-#pragma unroll
-        for (int i = 0; i < LD; ++i) direct_load_16(rv, v_off[i] + at, dst + TILE + i * 1024);
+        for (int i = 0; i < LD; ++i) direct_load_16(rk, k_off[i] + step * 4 * ATS_BK * row_bytes, ring0 + place(step) + (qh * LD + i) * 1024);
     };
+    auto issue_v = [&](int step) {
+#pragma unroll
+        for (int i = 0; i < LD; ++i) direct_load_16(rv, v_off[i] + step * 4 * ATS_BK * row_bytes, ring0 + place(step) + TILE + (qh * LD + i) * 1024);
+    };
+    auto issue = [&](int step) { issue_k(step); issue_v(step); };
     const int ntile = (n + ATS_BK - 1) / ATS_BK, nstep = (ntile + 3) / 4;
     issue(0);
-    if (ALONE && nstep > 1) issue(1);
     if constexpr (WGT)
         for (int j = tid; j < ATS_MAX_KEYS; j += 256 * QH) lw_s[j] = (j < n) ? key_log2_weight(kw, b, j) : 0.f;
 
@@ -826,19 +828,18 @@ __global__ __launch_bounds__(256 * QH, 2) void attend_bf16_short_kernel(
         // This step's tiles (and the queries, the weights) are there.  ALONE: behind the first step a wave waits for nobody; otherwise
         // everybody is done with the step before, whose place the next one's tiles take.
         if (ALONE && step > 0) wait_loads<0>();
-        else if (ALONE && nstep > 1 && !WGT) wait_loads_and_barrier<2 * LD>();
         else wait_loads_and_barrier<0>();
-        if (ALONE && step > 0 && step + 1 < nstep) issue(step + 1);
+        const bool more = step + 1 < nstep;
         if (step == 0) {
 #pragma unroll
             for (int kk = 0; kk < KS; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(ring + Q_LDS + qh * TILE + k_addr[kk]);
         }
         if (step * 4 + kg >= ntile || !live) {
-            if (!ALONE && step + 1 < nstep) issue(step + 1);
+            if (!ALONE && more) issue(step + 1);            // (ALONE: no tile, no later one)
             continue;
         }
         const int key0 = (step * 4 + kg) * ATS_BK;
-        const char* wreg = ring + (step & 1) * C::BUF + kg * C::REGION;
+        const char* wreg = ring + place(step);
         bf16x8 kf[KS];
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(wreg + k_addr[kk]);
@@ -849,7 +850,7 @@ __global__ __launch_bounds__(256 * QH, 2) void attend_bf16_short_kernel(
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], st, 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        if (!ALONE && step + 1 < nstep) issue(step + 1);
+        if (more) { if (ALONE) issue_k(step + 1); else issue(step + 1); }        // (ALONE: the products above have taken the K fragments)
         __builtin_amdgcn_sched_barrier(0);
         att_short4 vf[2][DT][2];
 #pragma unroll
@@ -903,6 +904,11 @@ __global__ __launch_bounds__(256 * QH, 2) void attend_bf16_short_kernel(
         }
         l_run += psum;
         m_run = m_new;
+        __builtin_amdgcn_sched_barrier(0);
+        if (ALONE && more) {
+            __builtin_amdgcn_s_waitcnt(0xC07F);             // lgkmcnt(0): the V fragments are in registers
+            issue_v(step + 1);
+        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
@@ -1088,6 +1094,88 @@ __global__ __launch_bounds__(256) void attend_generic_kernel(
 
 using namespace d3tom;
 
+// Which kernel takes a call, and how many queries a workgroup of it has.
+namespace {
+enum { ATT_GENERIC = 0, ATT_SHORT = 1, ATT_TILES = 2 };
+struct AttendPlan {
+    int kernel, queries;                // of a workgroup
+    int nqt;                            // such tiles of the longest sample
+    bool turns, skip;                   // ATT_TILES: a workgroup takes several tiles in turn; waves without queries skip their products
+    size_t lds;                         // dynamic
+};
+// whole: without the 64-query tiles (the blocks of a stack in front of its merge), see attend_whole_run
+AttendPlan attend_plan(int dt, int B, int max_seqlen, int H, int dh, bool whole) {
+    AttendPlan p{ATT_GENERIC, 1, max_seqlen, false, false, 0};
+    // the tiled kernel addresses one sample's K / V rows with 32-bit byte offsets
+    const bool fits32 = ((size_t)max_seqlen + 8 * ATT_BK) * (size_t)H * (size_t)dh * 2 < ((size_t)1 << 31);
+    const long heads = (long)H * B;
+    if (dt != D3TOM_BF16 || (dh != 128 && dh != 64) || !fits32) {
+        // float32 is bound by reading each query its keys and values.  With two queries to a workgroup a round of workgroups reads half of that, but two
+        // fit on a unit for three, and the round takes up to 1.3 times as long: taken where it saves enough rounds.  (One query and two; 4 heads of 64:
+        // 160 rows 6.1 and 6.5 us, 200 rows 8.6 and 6.8, 300 rows 13.4 and 15.6, 400 rows 21.2 and 19.3, 700 rows 46.9 and 42.1; 16 heads of 64, 100 rows
+        // 9.6 and 9.6, 300 rows 42.7 and 40.8; 8 heads of 36, 200 rows 11.2 and 11.6; 4 heads of 256, 200 rows 20.9 and 13.8.)
+        const long one = (max_seqlen * heads + 767) / 768, two = (ceil_div(max_seqlen, 2) * heads + 511) / 512;
+        if (dt == D3TOM_F32 && 13 * two < 10 * one) { p.queries = 2; p.nqt = ceil_div(max_seqlen, 2); }
+        return p;
+    }
+    // Short samples, up to two rounds of 128-query tiles: keys split across the waves.  The tiles below are faster for some of them (493 keys, 32 heads of
+    // 128 10.1 us here, 8.5 with 64-query tiles), but this kernel has four running maxima a row, over tiles of 32 keys, relative to which the probabilities are rounded.  Error against
+    // float64 (2-norm, relative, output rounded to bf16) at logit spreads of 1 and 2, 493 keys: 2.10e-3, 1.77e-3 here; 2.16e-3, 1.82e-3 with 64-query
+    // tiles; 2.19e-3, 1.86e-3 with wider ones.  66 to 512 keys, weighted or not, heads of 64 and 128: 2.2 to 4.9 % more with any of the tiles.
+    if (max_seqlen <= ATS_MAX_KEYS && ceil_div(max_seqlen, 128) * heads <= 512) {
+        // 32 queries to a workgroup, of which two with heads of 128 and four with heads of 64 fit on a unit, and 64 only for one sample of more than 256 keys whose
+        // tiles fill the rounds of an XCD's units, one or two workgroups to each, by nine tenths: there they read half of the K and V that 32 queries read.
+        // (32 and 64; one sample at 32 heads of 128, 200 rows 5.2 and 6.3 us, 300 7.4 and 7.6, 512 9.9 and 9.4; 8 heads of 128, 9 x 200 rows 6.8 and 11.7, 9 x 75 .. 200 6.5
+        // and 8.8; 32 heads of 128, 16 x 8 rows 4.6 and 7.1, 8 x 30 .. 65 5.6 and 8.9; 32 heads of 64, 16 x 21 .. 65 5.5 and 8.4.  Over 880 single samples the choice is
+        // 0.997 of the better one's speed.  Batches, of which the host knows the longest sample only, lose most where they are of one length that fills the rounds,
+        // 8 x 512 rows at 8 heads of 128 17.7 and 17.5, weighted 20.1 and 19.1, 32 heads of 64, 4 x 256 7.1 and 6.8; 4 x 106 .. 256 6.3 and 6.7.)
+        const int tiles = ceil_div(H, 8) * ceil_div(max_seqlen, 64), round = dh == 64 ? 64 : 32;
+        p.queries = B == 1 && max_seqlen > 256 && 10 * tiles >= 9 * round * ceil_div(tiles, round) ? 64 : 32;
+        p.kernel = ATT_SHORT;
+        p.nqt = ceil_div(max_seqlen, p.queries);
+        p.lds = dh == 128 ? (p.queries == 64 ? AtsLds<128, 2>::BYTES : AtsLds<128, 1>::BYTES) : (p.queries == 64 ? AtsLds<64, 2>::BYTES : AtsLds<64, 1>::BYTES);
+        return p;
+    }
+    // 64-query tiles whose groups share the keys, where they fill one round of compute units at most: half as long a chain as 128-query
+    // tiles on twice as many units, and two running maxima a row instead of one (error against float64 0.98 of theirs).  Two workgroups of heads of
+    // 64 fit on a unit, and of ragged batches fewer tiles are real than the longest
+    // sample lets the host expect.  Means over 897 drawn batches (1 to 16 samples of 33 to 2400 keys), the better of 128 and 256 queries
+    // against this, by the number of 64-query tiles: heads of 128, up to 256 tiles 1.13 (samples of up to 128 keys) to 1.46 (more than 1024), 257
+    // to 384 0.68 to 1.02; heads of 64, up to 256 tiles 1.12 to 1.37, 257 to 512 0.99 to 1.15, 513 to 640 1.12 to 1.28,
+    // 641 to 768 0.95 to 1.07.  (Samples of up to 512 keys that are not for the short-sample kernel have more tiles than that.)
+    // whole: the blocks of a stack in front of its merge do without these tiles, see attend_whole_run.
+    const bool split = !whole && max_seqlen > ATS_MAX_KEYS && ceil_div(max_seqlen, 64) * heads <= (dh == 64 ? 640 : 256);
+    // Rounds of workgroups over the 256 compute units.  A round of 128-query tiles costs 0.61 to 0.70 of one of 256-query tiles
+    // (every fragment read from LDS feeds one MFMA instead of two; 32 heads, narrow against wide: 1024 keys 21.9 us against 30.9,
+    // one round each; 1198 keys 44.7 against 35.7, two to one; 3773 keys 255 against 210, four to two; 2100 keys 106 against
+    // 111, 3 x 1000 keys 60.9 against 64.9, three to two); with heads of 64 two workgroups of 128 queries share a CU, and it costs
+    // 0.52 (16 heads, 3500 keys: 69.2 against 65.9, two to one; 8 x 560 keys: 22.1 against 28.9, one to one).  That holds for one sample.  A batch
+    // with heads of 64 takes 128-query tiles always: its samples may all but one be shorter than the bound, and neither the rounds nor the bound say
+    // by how much.  6028 drawn batches (2 to 48 samples, the longest of 170 to 8000 keys, the others as long, or from a half, a third or an
+    // eighth of it on, 8 to 32 heads): 0.993 of the better width's speed, 0.75 at the least; by rounds, as for one sample, 0.955 and 0.58.  Where
+    // the rounds speak for 256 queries, wide against narrow in the mean: samples of one length 0.95 to 1.01, ragged ones 0.71 to 1.02 (above
+    // 1.00 from 13 rounds on).
+    const long wide = (ceil_div(max_seqlen, 256) * heads + 255) / 256, narrow = (ceil_div(max_seqlen, 128) * heads + 255) / 256;
+    const bool small = (dh == 64 && B > 1) || (dh == 128 ? 66 : 55) * narrow < 100 * wide;
+    // 192 queries, by rounds again.  Of one round whatever the other samples' lengths are (all tiles run side by side, the longest sample's decide), of
+    // several only for one sample, whose tiles the host knows.  (128, 192 and 256 queries; 32 heads: 1100 keys 41.2, 28.5 and 31.6 us, 1500 52.3, 39.5 and
+    // 41.9, 2060 94.4, 93.1 and 94.3, 2400 117, 106 and 123, 3000 155, 141 and 152, 4500 361, 311 and 340; 2 x 700 28.5, 22.1 and 23.4; 16 heads,
+    // 2200 71.2, 48.1 and 53.4; weighted, 1100 43.9, 30.0 and 32.5.  Where 192 take a round more: 1600 keys 54.4, 72.3 and 43.4, 3773 250, 243 and 201.)
+    const long mid = (ceil_div(max_seqlen, 192) * heads + 255) / 256;
+    const bool uneven = dh == 128 && (mid == 1 || B == 1) && 90 * mid < (small ? 66 * narrow : 100 * wide);
+    p.kernel = ATT_TILES;
+    p.queries = split ? 64 : uneven ? 192 : small ? 128 : 256;
+    p.nqt = ceil_div(max_seqlen, p.queries);
+    p.lds = (size_t)ATT_SLOTS * 2 * ATT_BK * dh * 2;
+    // Several rounds of workgroups that have a compute unit to themselves: one per unit, which takes its tiles in turn, samples by
+    // falling length (one tile per workgroup / in turn: 16 x 700 .. 1505 keys 440 / 422 us, 4 x 575 .. 1951 141 / 133, 12 x 270 .. 800
+    // 114 / 82, 8 x 1000 149 / 145, one sample of 3773 211 / 211; 8 heads, 16 x 1000 .. 3000 303 / 262).
+    p.turns = !split && p.nqt * heads > 256 && !(dh == 64 && p.queries == 128) && B <= WAVE;
+    p.skip = p.nqt * heads > (dh == 64 ? 512 : 256);                   // more than one round (two workgroups of 128 queries with heads of 64 to a unit)
+    return p;
+}
+}  // namespace
+
 static int attend_any(const void* q, const void* k, const void* v, int dt, int B, const int32_t* cu_seqlens, int max_seqlen, int H, int dh,
                       float scale, const int32_t* counts, const int32_t* kept_off, const int32_t* vis_start, void* o, void* stream, bool whole = false) {
     if (!q || !k || !v || !o || !cu_seqlens) return D3TOM_ERR_INVALID_ARG;
@@ -1100,74 +1188,27 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
     const KeyWeights kw{counts, kept_off, vis_start};
     hipStream_t st = (hipStream_t)stream;
     const float scale2 = scale * LOG2E;
-    // the tiled kernel addresses one sample's K / V rows with 32-bit byte offsets
-    const bool fits32 = ((size_t)max_seqlen + 8 * ATT_BK) * (size_t)H * (size_t)dh * 2 < ((size_t)1 << 31);
-    const bool mfma = dt == D3TOM_BF16 && (dh == 128 || dh == 64) && fits32;
+    const AttendPlan p = attend_plan(dt, B, max_seqlen, H, dh, whole);
     // the weighted MFMA kernels keep a sample's weights in LDS
-    if (wgt && mfma && max_seqlen > ATT_WKEYS) return D3TOM_ERR_UNSUPPORTED;
-    const long heads = (long)H * B;
-    // Short samples, up to two rounds of 128-query tiles: keys split across the waves.  The tiles below are faster for some of them (493 keys, 32 heads of
-    // 128 10.1 us here, 8.5 with 64-query tiles), but this kernel has four running maxima a row, over tiles of 32 keys, relative to which the probabilities are rounded.  Error against
-    // float64 (2-norm, relative, output rounded to bf16) at logit spreads of 1 and 2, 493 keys: 2.10e-3, 1.77e-3 here; 2.16e-3, 1.82e-3 with 64-query
-    // tiles; 2.19e-3, 1.86e-3 with wider ones.  66 to 512 keys, weighted or not, heads of 64 and 128: 2.2 to 4.9 % more with any of the tiles.
-    if (mfma && max_seqlen <= ATS_MAX_KEYS && ceil_div(max_seqlen, 128) * heads <= 512) {
-        // 32 queries to a workgroup while its tiles fill one round of compute units (two workgroups with heads of 64 fit on one), 64 above.  (32 and
-        // 64; 32 heads of 128, 231 rows 5.4 and 6.2 us, 300 11.2 and 7.4, 493 14.9 and 10.1; 8 heads, 3 x 100 .. 300 rows 6.2 and 7.1, 8 x 40 .. 250 9.3 and
-        // 6.4; 16 heads of 64, 2 x 200 .. 400 5.3 and 6.2, 5 x 150 .. 250 7.0 and 6.3.)
-        const int qh = ceil_div(max_seqlen, 32) * heads <= (dh == 64 ? 512 : 256) ? 1 : 2;
-        const int nqt = ceil_div(max_seqlen, 32 * qh);
-        const dim3 g((unsigned)(8 * ceil_div(H * B, 8) * nqt));
+    if (wgt && p.kernel != ATT_GENERIC && max_seqlen > ATT_WKEYS) return D3TOM_ERR_UNSUPPORTED;
+    const int nqt = p.nqt;
+    const dim3 g(p.turns ? 8u * ATT_TURNS_WGS : 8u * (unsigned)ceil_div(H * B, 8) * (unsigned)nqt);
+    if (p.kernel == ATT_SHORT) {
 #define D3TOM_ATT_SHORT(DHV, WGTV, QHV)                                                                                         \
     do {                                                                                                                        \
         static PerDeviceOnce lds_setup;                                                                                         \
         if (!lds_setup.run([] { return raise_dynamic_lds(attend_bf16_short_kernel<DHV, WGTV, QHV>, AtsLds<DHV, QHV>::BYTES); })) return D3TOM_ERR_DEVICE; \
-        D3TOM_LAUNCH(ATTEND, st, (attend_bf16_short_kernel<DHV, WGTV, QHV><<<g, 256 * QHV, AtsLds<DHV, QHV>::BYTES, st>>>((const uint16_t*)q, (const uint16_t*)k, \
+        D3TOM_LAUNCH(ATTEND, st, (attend_bf16_short_kernel<DHV, WGTV, QHV><<<g, 256 * QHV, p.lds, st>>>((const uint16_t*)q, (const uint16_t*)k, \
                                                                (const uint16_t*)v, cu_seqlens, H, B, nqt, scale2, (uint16_t*)o, kw))); \
     } while (0)
-#define D3TOM_ATT_SHORT2(DHV, WGTV) do { if (qh == 1) D3TOM_ATT_SHORT(DHV, WGTV, 1); else D3TOM_ATT_SHORT(DHV, WGTV, 2); } while (0)
+#define D3TOM_ATT_SHORT2(DHV, WGTV) do { if (p.queries == 32) D3TOM_ATT_SHORT(DHV, WGTV, 1); else D3TOM_ATT_SHORT(DHV, WGTV, 2); } while (0)
         if (dh == 128) { if (wgt) D3TOM_ATT_SHORT2(128, true); else D3TOM_ATT_SHORT2(128, false); }
         else           { if (wgt) D3TOM_ATT_SHORT2(64, true);  else D3TOM_ATT_SHORT2(64, false); }
 #undef D3TOM_ATT_SHORT2
 #undef D3TOM_ATT_SHORT
-    } else if (mfma) {
-        // 64-query tiles whose groups share the keys, where they fill one round of compute units at most: half as long a chain as 128-query
-        // tiles on twice as many units, and two running maxima a row instead of one (error against float64 0.98 of theirs).  Two workgroups of heads of
-        // 64 fit on a unit, and of ragged batches fewer tiles are real than the longest
-        // sample lets the host expect.  Means over 897 drawn batches (1 to 16 samples of 33 to 2400 keys), the better of 128 and 256 queries
-        // against this, by the number of 64-query tiles: heads of 128, up to 256 tiles 1.13 (samples of up to 128 keys) to 1.46 (more than 1024), 257
-        // to 384 0.68 to 1.02; heads of 64, up to 256 tiles 1.12 to 1.37, 257 to 512 0.99 to 1.15, 513 to 640 1.12 to 1.28,
-        // 641 to 768 0.95 to 1.07.  (Samples of up to 512 keys that are not for the short-sample kernel have more tiles than that.)
-        // whole: the blocks of a stack in front of its merge do without these tiles, see attend_whole_run.
-        const bool split = !whole && max_seqlen > ATS_MAX_KEYS && ceil_div(max_seqlen, 64) * heads <= (dh == 64 ? 640 : 256);
-        // Rounds of workgroups over the 256 compute units.  A round of 128-query tiles costs 0.61 to 0.70 of one of 256-query tiles
-        // (every fragment read from LDS feeds one MFMA instead of two; 32 heads, narrow against wide: 1024 keys 21.9 us against 30.9,
-        // one round each; 1198 keys 44.7 against 35.7, two to one; 3773 keys 255 against 210, four to two; 2100 keys 106 against
-        // 111, 3 x 1000 keys 60.9 against 64.9, three to two); with heads of 64 two workgroups of 128 queries share a CU, and it costs
-        // 0.52 (16 heads, 3500 keys: 69.2 against 65.9, two to one; 8 x 560 keys: 22.1 against 28.9, one to one).  That holds for one sample.  A batch
-        // with heads of 64 takes 128-query tiles always: its samples may all but one be shorter than the bound, and neither the rounds nor the bound say
-        // by how much.  6028 drawn batches (2 to 48 samples, the longest of 170 to 8000 keys, the others as long, or from a half, a third or an
-        // eighth of it on, 8 to 32 heads): 0.993 of the better width's speed, 0.75 at the least; by rounds, as for one sample, 0.955 and 0.58.  Where
-        // the rounds speak for 256 queries, wide against narrow in the mean: samples of one length 0.95 to 1.01, ragged ones 0.71 to 1.02 (above
-        // 1.00 from 13 rounds on).
-        const long wide = (ceil_div(max_seqlen, 256) * heads + 255) / 256, narrow = (ceil_div(max_seqlen, 128) * heads + 255) / 256;
-        const int nq = split || (dh == 64 && B > 1) || (dh == 128 ? 66 : 55) * narrow < 100 * wide ? 1 : 2;
-        // 192 queries, by rounds again.  Of one round whatever the other samples' lengths are (all tiles run side by side, the longest sample's decide), of
-        // several only for one sample, whose tiles the host knows.  (128, 192 and 256 queries; 32 heads: 1100 keys 41.2, 28.5 and 31.6 us, 1500 52.3, 39.5 and
-        // 41.9, 2060 94.4, 93.1 and 94.3, 2400 117, 106 and 123, 3000 155, 141 and 152, 4500 361, 311 and 340; 2 x 700 28.5, 22.1 and 23.4; 16 heads,
-        // 2200 71.2, 48.1 and 53.4; weighted, 1100 43.9, 30.0 and 32.5.  Where 192 take a round more: 1600 keys 54.4, 72.3 and 43.4, 3773 250, 243 and 201.)
-        const long mid = (ceil_div(max_seqlen, 192) * heads + 255) / 256;
-        const bool uneven = dh == 128 && !split && (mid == 1 || B == 1) && 90 * mid < (nq == 1 ? 66 * narrow : 100 * wide);
-        const int nqt = ceil_div(max_seqlen, split ? 64 : uneven ? 192 : nq * 128);
-        // Several rounds of workgroups that have a compute unit to themselves: one per unit, which takes its tiles in turn, samples by
-        // falling length (one tile per workgroup / in turn: 16 x 700 .. 1505 keys 440 / 422 us, 4 x 575 .. 1951 141 / 133, 12 x 270 .. 800
-        // 114 / 82, 8 x 1000 149 / 145, one sample of 3773 211 / 211; 8 heads, 16 x 1000 .. 3000 303 / 262).
-        const bool turns = !split && nqt * heads > 256 && !(dh == 64 && nq == 1) && B <= WAVE;
-        const dim3 g(turns ? 8u * ATT_TURNS_WGS : (unsigned)(8 * ceil_div(H * B, 8) * nqt));
-        const size_t lds = (size_t)ATT_SLOTS * 2 * ATT_BK * dh * 2;
-        const int threads = 512;
-        const bool skip = nqt * heads > (dh == 64 ? 512 : 256);            // more than one round (two workgroups of 128 queries with heads of 64 to a unit)
+    } else if (p.kernel == ATT_TILES) {
 #define D3TOM_ATT(KERNEL)                                                                                            \
-    D3TOM_LAUNCH(ATTEND, st, (KERNEL<<<g, threads, lds, st>>>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, \
+    D3TOM_LAUNCH(ATTEND, st, (KERNEL<<<g, 512, p.lds, st>>>((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, \
                                                            cu_seqlens, H, B, nqt, scale2, (uint16_t*)o, kw)))
 #define D3TOM_ATT8(DHV, WGTV, NQV, TURNSV, SKIPV, SPLITV, UNEVENV)                                                           \
     do {                                                                                                                    \
@@ -1176,12 +1217,12 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
             return D3TOM_ERR_DEVICE;                                                                                        \
         D3TOM_ATT((attend_bf16_kernel<DHV, WGTV, NQV, TURNSV, SKIPV, SPLITV, UNEVENV>));                                                     \
     } while (0)
-#define D3TOM_ATT8_2(DHV, WGTV) do { if (turns) D3TOM_ATT8(DHV, WGTV, 2, true, true, false, false); else D3TOM_ATT8(DHV, WGTV, 2, false, true, false, false); } while (0)
-#define D3TOM_ATT8_1(DHV, WGTV) do { if (skip) D3TOM_ATT8(DHV, WGTV, 1, false, true, false, false); else D3TOM_ATT8(DHV, WGTV, 1, false, false, false, false); } while (0)
-#define D3TOM_ATT8_U(WGTV) do { if (turns) D3TOM_ATT8(128, WGTV, 2, true, true, false, true); else D3TOM_ATT8(128, WGTV, 2, false, false, false, true); } while (0)
-#define D3TOM_ATT8_128(WGTV) do { if (uneven) D3TOM_ATT8_U(WGTV); else if (nq == 2) D3TOM_ATT8_2(128, WGTV); else if (turns) D3TOM_ATT8(128, WGTV, 1, true, true, false, false); else D3TOM_ATT8_1(128, WGTV); } while (0)
-#define D3TOM_ATT8_64(WGTV) do { if (nq == 2) D3TOM_ATT8_2(64, WGTV); else D3TOM_ATT8_1(64, WGTV); } while (0)
-        if (split) {
+#define D3TOM_ATT8_2(DHV, WGTV) do { if (p.turns) D3TOM_ATT8(DHV, WGTV, 2, true, true, false, false); else D3TOM_ATT8(DHV, WGTV, 2, false, true, false, false); } while (0)
+#define D3TOM_ATT8_1(DHV, WGTV) do { if (p.skip) D3TOM_ATT8(DHV, WGTV, 1, false, true, false, false); else D3TOM_ATT8(DHV, WGTV, 1, false, false, false, false); } while (0)
+#define D3TOM_ATT8_U(WGTV) do { if (p.turns) D3TOM_ATT8(128, WGTV, 2, true, true, false, true); else D3TOM_ATT8(128, WGTV, 2, false, false, false, true); } while (0)
+#define D3TOM_ATT8_128(WGTV) do { if (p.queries == 192) D3TOM_ATT8_U(WGTV); else if (p.queries == 256) D3TOM_ATT8_2(128, WGTV); else if (p.turns) D3TOM_ATT8(128, WGTV, 1, true, true, false, false); else D3TOM_ATT8_1(128, WGTV); } while (0)
+#define D3TOM_ATT8_64(WGTV) do { if (p.queries == 256) D3TOM_ATT8_2(64, WGTV); else D3TOM_ATT8_1(64, WGTV); } while (0)
+        if (p.queries == 64) {
             if (dh == 128) { if (wgt) D3TOM_ATT8(128, true, 1, false, false, true, false); else D3TOM_ATT8(128, false, 1, false, false, true, false); }
             else           { if (wgt) D3TOM_ATT8(64, true, 1, false, false, true, false);  else D3TOM_ATT8(64, false, 1, false, false, true, false); }
         } else if (dh == 128) { if (wgt) D3TOM_ATT8_128(true); else D3TOM_ATT8_128(false); }
@@ -1195,14 +1236,9 @@ static int attend_any(const void* q, const void* k, const void* v, int dt, int B
 #undef D3TOM_ATT
     } else {
 #define D3TOM_ATT_GENERIC(T, Q)                                                                                             \
-    D3TOM_LAUNCH(ATTEND, st, (attend_generic_kernel<T, Q><<<dim3(ceil_div(max_seqlen, Q), H, B), 256, 0, st>>>(             \
+    D3TOM_LAUNCH(ATTEND, st, (attend_generic_kernel<T, Q><<<dim3(nqt, H, B), 256, 0, st>>>(             \
         (const T*)q, (const T*)k, (const T*)v, cu_seqlens, H, dh, scale2, (T*)o, kw)))
-        // float32 is bound by reading each query its keys and values.  With two queries to a workgroup a round of workgroups reads half of that, but two
-        // fit on a unit for three, and the round takes up to 1.3 times as long: taken where it saves enough rounds.  (One query and two; 4 heads of 64:
-        // 160 rows 6.1 and 6.5 us, 200 rows 8.6 and 6.8, 300 rows 13.4 and 15.6, 400 rows 21.2 and 19.3, 700 rows 46.9 and 42.1; 16 heads of 64, 100 rows
-        // 9.6 and 9.6, 300 rows 42.7 and 40.8; 8 heads of 36, 200 rows 11.2 and 11.6; 4 heads of 256, 200 rows 20.9 and 13.8.)
-        const long one = (max_seqlen * heads + 767) / 768, two = (ceil_div(max_seqlen, 2) * heads + 511) / 512;
-        if (dt == D3TOM_F32) { if (13 * two < 10 * one) D3TOM_ATT_GENERIC(float, 2); else D3TOM_ATT_GENERIC(float, 1); }
+        if (dt == D3TOM_F32) { if (p.queries == 2) D3TOM_ATT_GENERIC(float, 2); else D3TOM_ATT_GENERIC(float, 1); }
         else D3TOM_ATT_GENERIC(uint16_t, 1);
 #undef D3TOM_ATT_GENERIC
     }
@@ -1228,4 +1264,16 @@ extern "C" int d3tom_attend_weighted(const void* q, const void* k, const void* v
     (void)ws; (void)ws_bytes;
     if (!counts || !kept_off || !vis_start) return D3TOM_ERR_INVALID_ARG;
     return attend_any(q, k, v, dt, B, cu_seqlens, max_seqlen, H, dh, scale, counts, kept_off, vis_start, o, stream);
+}
+
+// ---- for tuning and tests: which kernel takes a call: {generic, short samples, tiles}, queries of a workgroup, whether a workgroup takes
+// several tiles in turn, dynamic LDS bytes; whole: as the blocks of a stack in front of its merge call it
+extern "C" int d3tom_attend_plan(int dt, int B, int max_seqlen, int H, int dh, int whole, int32_t* plan) {
+    if (!plan || B < 1 || max_seqlen < 1 || H < 1 || dh < 1) return D3TOM_ERR_INVALID_ARG;
+    const AttendPlan p = attend_plan(dt, B, max_seqlen, H, dh, whole != 0);
+    plan[0] = p.kernel;
+    plan[1] = p.queries;
+    plan[2] = p.turns;
+    plan[3] = (int32_t)p.lds;
+    return D3TOM_OK;
 }

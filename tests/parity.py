@@ -238,3 +238,10 @@ def check_full_sample(step: GpuStep, b: int, S_gpu, kept_gpu, slot_gpu, mout, as
     na = check_assign(out["assign"], s["x"], s["vis_start"], s["V"], kept_gpu[b], only=assign_rows)
     err = check_merge(out, s["x"], s["vis_start"], s["V"], kept_gpu[b], step.dtype, mode)
     return dict(score_rel=rel, kept_excused=nk, assign_excused=na, y_err=err)
+
+
+def attend_form(H, lens, dh, whole=False):
+    """Which kernel takes a bf16 attention call, as d3tom_attend_plan says it: "short 32", "short 64", "tiles 64" .. "tiles 256", with " in turn"
+    where a workgroup takes several tiles."""
+    kernel, queries, turns, _ = B.d3tom_attend_plan(B.D3TOM_BF16, len(lens), max(lens), H, dh, whole)
+    return f"{('generic', 'short', 'tiles')[kernel]} {queries}" + (" in turn" if turns else "")

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 if torch.cuda.is_available():
     from paper_2511_12280_amd import binding as B
     from parity import (GpuStep, check_assign, check_attend, check_full_sample, check_kept, check_merge,
-                        check_scores, gpu_attend, gpu_attend_weighted, key_weights)
+                        check_scores, attend_form, gpu_attend, gpu_attend_weighted, key_weights)
 
 
 def _chain(samples, keeps, dtype, mode="mean", assign_rows=None, check=None):
@@ -479,14 +479,16 @@ def test_attend_error_of_short_samples(H, dh, n, weighted, copies, spread):
 
 
 @pytest.mark.parametrize("weighted", [False, True])
-@pytest.mark.parametrize("H,dh,lens", [
-    (32, 128, [256]), (32, 128, [257]),                     # 256 tiles of 32 queries, and more: 64 queries to a workgroup from there on
-    (16, 64, [512]), (16, 64, [512, 300]), (17, 64, [512, 40]),             # 512 with heads of 64
-    (5, 128, [2]), (5, 128, [33]), (5, 64, [129]), (5, 128, [385]),         # one to four steps of four tiles, the last one with a single tile
-    (9, 128, [1, 31, 32, 33, 63, 64, 65, 97, 127, 128, 129, 255, 384, 511]), (40, 64, [64, 1, 95, 96, 97, 130, 257, 512]),     # halves without queries, steps without tiles
+@pytest.mark.parametrize("H,dh,lens,queries", [
+    (32, 128, [256], 32), (32, 128, [257], 32),                             # 256 tiles of 32 queries, and more
+    (32, 128, [450], 64), (32, 128, [480], 64), (40, 128, [350], 64), (48, 128, [300], 64), (64, 128, [500], 64), (96, 64, [300], 64), (64, 64, [449], 64),
+    (16, 64, [512], 32), (16, 64, [512, 300], 32), (17, 64, [512, 40], 32),                         # 512 tiles with heads of 64, and more
+    (5, 128, [2], 32), (5, 128, [33], 32), (5, 64, [129], 32), (5, 128, [385], 32),         # one to four steps of four tiles, the last one with a single tile
+    (9, 128, [1, 31, 32, 33, 63, 64, 65, 97, 127, 128, 129, 255, 384, 511], 32), (40, 64, [64, 1, 95, 96, 97, 130, 257, 512], None),     # steps without tiles
 ])
-def test_attend_short_samples_by_halves_of_64_queries(H, dh, lens, weighted):
+def test_attend_short_samples_by_halves_of_64_queries(H, dh, lens, queries, weighted):
     """The short-sample kernel with 32 and with 64 queries to a workgroup, at the edges of tiles, halves and steps."""
+    assert queries is None or attend_form(H, lens, dh) == f"short {queries}"
     qkv = [W.random_qkv(1010 + n, n, H, dh, "bf16") for n in lens]
     vis, counts = [n // 5 for n in lens], [(1 + np.arange(n // 2) % 37).astype(np.int32) for n in lens]
     outs = gpu_attend_weighted(qkv, counts, vis, "bf16") if weighted else gpu_attend(qkv, "bf16")

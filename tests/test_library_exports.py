@@ -179,3 +179,16 @@ def test_projection_tiles_are_all_taken(lib):
     assert sliced == {"64x64 loaders", "64x96 loaders", "64x128 loaders", "96x128 loaders", "128x128", "160x128 loaders", "192x128 loaders", "256x128"}
     assert whole == {"64x64 loaders", "64x96 loaders", "64x128 loaders", "96x128 loaders", "128x128", "128x192 loaders", "128x256",
                      "160x128 loaders", "160x256", "192x128 loaders", "192x256", "224x256", "256x128 loaders", "256x192", "256x256"}
+
+
+@pytest.mark.parametrize("H,dh,longest,batch", [(32, 128, 8, 9), (32, 128, 32, 16), (8, 128, 200, 9), (32, 128, 65, 8), (32, 64, 65, 16), (16, 64, 200, 9), (32, 64, 32, 1),
+                                                (32, 128, 493, 1), (32, 128, 231, 1)])
+def test_short_samples_share_the_units(lib, H, dh, longest, batch):
+    """Workgroups of 32 queries of the short-sample kernel: two with heads of 128 and four with heads of 64 fit into a unit's 160 KB of LDS, and a batch, of which
+    the host knows the longest sample only, takes them always; one long sample whose 64-query tiles fill the units takes those."""
+    pytest.importorskip("msgpack")
+    from paper_2511_12280_amd import binding as B
+    kernel, queries, turns, lds = B.d3tom_attend_plan(B.D3TOM_BF16, batch, longest, H, dh)
+    assert (kernel, queries, turns) == (1, 64 if longest == 493 else 32, 0)
+    fixed = max(k[".group_segment_fixed_size"] for k in _kernels(LIB) if re.search(rf"attend_bf16_short_kernelILi{dh}ELb[01]ELi{queries // 32}E", k[".name"]))
+    assert 1024 <= fixed and (queries == 64 or (lds + fixed) * (2 if dh == 128 else 4) <= 160 * 1024)
