@@ -1145,24 +1145,36 @@ AttendPlan attend_plan(int dt, int B, int max_seqlen, int H, int dh, bool whole)
     // 641 to 768 0.95 to 1.07.  (Samples of up to 512 keys that are not for the short-sample kernel have more tiles than that.)
     // whole: the blocks of a stack in front of its merge do without these tiles, see attend_whole_run.
     const bool split = !whole && max_seqlen > ATS_MAX_KEYS && ceil_div(max_seqlen, 64) * heads <= (dh == 64 ? 640 : 256);
-    // Rounds of workgroups over the 256 compute units.  A round of 128-query tiles costs 0.61 to 0.70 of one of 256-query tiles
-    // (every fragment read from LDS feeds one MFMA instead of two; 32 heads, narrow against wide: 1024 keys 21.9 us against 30.9,
-    // one round each; 1198 keys 44.7 against 35.7, two to one; 3773 keys 255 against 210, four to two; 2100 keys 106 against
-    // 111, 3 x 1000 keys 60.9 against 64.9, three to two); with heads of 64 two workgroups of 128 queries share a CU, and it costs
-    // 0.52 (16 heads, 3500 keys: 69.2 against 65.9, two to one; 8 x 560 keys: 22.1 against 28.9, one to one).  That holds for one sample.  A batch
-    // with heads of 64 takes 128-query tiles always: its samples may all but one be shorter than the bound, and neither the rounds nor the bound say
+    // Rounds: an XCD has the tiles of an eighth of the heads and 32 compute units.  (Counted over the whole card, one sample at 12 heads of 128, 3227 keys, took 17 tiles of
+    // 192 queries for each head, of which four XCDs have two heads: 145 us, with 256 queries 91; 28 heads, 1710 keys 77 and 51; 20 heads of 64, 2687 keys 83 with
+    // 256, 54 with 128.)
+    // With heads of 128 a round of 128-query tiles costs 0.63 to 0.72 of one of 256-query tiles (every fragment read from LDS feeds one MFMA instead of two), one of
+    // 192 queries 0.87 to 0.94; with heads of 64 two workgroups of 128 queries share a CU, and a round of half of them costs 0.52.  (128, 192 and 256 queries; 32 heads of 128:
+    // 1024 keys 19.8, 24.1 and 27.6 us, 1100 39.7, 27.1 and 31.1, 1500 52.0, 39.7 and 42.5, 1600 54.0, 72.2 and 43.5, 2060 94.5, 93.8 and 94.9, 2400 117.6, 107.1 and 123.7, 3000 153.5,
+    // 139.2 and 154.2, 3773 240, 240 and 200, 4500 354, 298 and 338; weighted, 1100 42.8, 29.7 and 32.8; 16 heads, 2200 70.6, 48.0 and 53.2.)  Last 128-query tiles that
+    // leave half of the waves without a query are items of their own behind the others (see the kernel) and count for less where the others leave room for most of them: 40 heads, 1538 keys 65.1,
+    // 71.9 and 71.2, 1566 69.3, 71.9 and 74.2, 48 heads, 1282 57.0, 63.0 and 61.3; with no or little room 24 heads, 2690 117, 115 and 130, 56 heads, 1182 59.7, 56.9 and 67.1.
+    // That holds for one sample (of 541 at 4 to 64 heads of 128 and 379 of 64 the choice is 0.9995 and 0.9998 of the best one's speed; counted over the card 0.964 and 0.986).  Of a batch the host
+    // knows the longest sample only.  192 queries are for what is one round of them whatever the others' lengths are (all tiles run side by side, the longest sample's
+    // decide; 2 x 700 28.3, 21.6 and 22.5).  A batch with heads of 64 takes 128-query tiles always: its samples may all but one be shorter than the bound, and neither the rounds nor the bound say
     // by how much.  6028 drawn batches (2 to 48 samples, the longest of 170 to 8000 keys, the others as long, or from a half, a third or an
     // eighth of it on, 8 to 32 heads): 0.993 of the better width's speed, 0.75 at the least; by rounds, as for one sample, 0.955 and 0.58.  Where
     // the rounds speak for 256 queries, wide against narrow in the mean: samples of one length 0.95 to 1.01, ragged ones 0.71 to 1.02 (above
     // 1.00 from 13 rounds on).
-    const long wide = (ceil_div(max_seqlen, 256) * heads + 255) / 256, narrow = (ceil_div(max_seqlen, 128) * heads + 255) / 256;
-    const bool small = (dh == 64 && B > 1) || (dh == 128 ? 66 : 55) * narrow < 100 * wide;
-    // 192 queries, by rounds again.  Of one round whatever the other samples' lengths are (all tiles run side by side, the longest sample's decide), of
-    // several only for one sample, whose tiles the host knows.  (128, 192 and 256 queries; 32 heads: 1100 keys 41.2, 28.5 and 31.6 us, 1500 52.3, 39.5 and
-    // 41.9, 2060 94.4, 93.1 and 94.3, 2400 117, 106 and 123, 3000 155, 141 and 152, 4500 361, 311 and 340; 2 x 700 28.5, 22.1 and 23.4; 16 heads,
-    // 2200 71.2, 48.1 and 53.4; weighted, 1100 43.9, 30.0 and 32.5.  Where 192 take a round more: 1600 keys 54.4, 72.3 and 43.4, 3773 250, 243 and 201.)
-    const long mid = (ceil_div(max_seqlen, 192) * heads + 255) / 256;
-    const bool uneven = dh == 128 && (mid == 1 || B == 1) && 90 * mid < (small ? 66 * narrow : 100 * wide);
+    const int per_xcd = ceil_div(H * B, 8);
+    auto rounds_of = [](long tiles) { return (tiles + 31) / 32; };
+    auto rounds = [&](int queries) { return rounds_of((long)per_xcd * ceil_div(max_seqlen, queries)); };
+    // in hundredths of a round of 256-query tiles
+    const long wide = 100 * rounds(256), mid = 90 * rounds(192);
+    long narrow = (dh == 128 ? 66 : 55) * rounds(128);
+    const int left = max_seqlen % 128;
+    if (dh == 128 && B == 1 && left > 0 && left <= 64) {
+        // last tiles that find no place in the rounds of the others
+        const long full = (long)per_xcd * (max_seqlen / 128), r = rounds_of(full), behind = max(per_xcd - (r * 32 - full), 0L);
+        if (2 * behind <= per_xcd) narrow = 66 * r + 47 * rounds_of(behind);
+    }
+    const bool small = (dh == 64 && B > 1) || narrow < wide;
+    const bool uneven = dh == 128 && (B == 1 || rounds(192) == 1) && mid < (small ? narrow : wide);
     p.kernel = ATT_TILES;
     p.queries = split ? 64 : uneven ? 192 : small ? 128 : 256;
     p.nqt = ceil_div(max_seqlen, p.queries);

@@ -192,3 +192,17 @@ def test_short_samples_share_the_units(lib, H, dh, longest, batch):
     assert (kernel, queries, turns) == (1, 64 if longest == 493 else 32, 0)
     fixed = max(k[".group_segment_fixed_size"] for k in _kernels(LIB) if re.search(rf"attend_bf16_short_kernelILi{dh}ELb[01]ELi{queries // 32}E", k[".name"]))
     assert 1024 <= fixed and (queries == 64 or (lds + fixed) * (2 if dh == 128 else 4) <= 160 * 1024)
+
+
+@pytest.mark.parametrize("H,lens,dh,form", [
+    # tiles of 192 queries (256 with heads of 64) that fill one round of the card's 256 units, and of some XCD's 32 more than one
+    (12, [3227], 128, "tiles 256"), (20, [2135], 128, "tiles 256"), (28, [1710], 128, "tiles 256"), (36, [1236], 128, "tiles 256"), (4, [3089] * 3, 128, "tiles 256"),
+    (36, [3870], 128, "tiles 256 in turn"), (20, [2687], 64, "tiles 128"),
+    (16, [2200], 128, "tiles 192"), (24, [1900], 128, "tiles 192"), (32, [1100], 128, "tiles 192"), (32, [700, 700], 128, "tiles 192"),
+    (40, [1538], 128, "tiles 128 in turn"), (48, [1282], 128, "tiles 128 in turn"), (24, [2690], 128, "tiles 192 in turn"),      # last tiles that fit beside the others, or not
+    (32, [1024], 128, "tiles 128"), (32, [1600], 128, "tiles 256"), (32, [3773], 128, "tiles 256 in turn"), (16, [3500], 64, "tiles 256"),
+])
+def test_attention_counts_rounds_of_an_xcd(lib, H, lens, dh, form):
+    """The width of the query tiles goes by rounds over the 32 units of the XCD with the most heads."""
+    from parity import attend_form
+    assert attend_form(H, lens, dh) == form
