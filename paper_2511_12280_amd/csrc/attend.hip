@@ -1155,8 +1155,10 @@ AttendPlan attend_plan(int dt, int B, int max_seqlen, int H, int dh, bool whole)
     // leave half of the waves without a query are items of their own behind the others (see the kernel) and count for less where the others leave room for most of them: 40 heads, 1538 keys 65.1,
     // 71.9 and 71.2, 1566 69.3, 71.9 and 74.2, 48 heads, 1282 57.0, 63.0 and 61.3; with no or little room 24 heads, 2690 117, 115 and 130, 56 heads, 1182 59.7, 56.9 and 67.1.
     // That holds for one sample (of 541 at 4 to 64 heads of 128 and 379 of 64 the choice is 0.9995 and 0.9998 of the best one's speed; counted over the card 0.964 and 0.986).  Of a batch the host
-    // knows the longest sample only.  192 queries are for what is one round of them whatever the others' lengths are (all tiles run side by side, the longest sample's
-    // decide; 2 x 700 28.3, 21.6 and 22.5).  A batch with heads of 64 takes 128-query tiles always: its samples may all but one be shorter than the bound, and neither the rounds nor the bound say
+    // knows the longest sample only.  192 queries are for what is one round of them on every XCD whatever the others' lengths are (all tiles run side by side, the longest sample's
+    // decide; 2 x 700 28.3, 21.6 and 22.5); for 128 or 256 its rounds are those of the card: where the longest sample's length makes a round of 128 overfull on some XCDs, the others' often
+    // does not (12 heads, 834, 738 and 350 keys 15.9, 21.3 and 23.5; over 800 drawn batches by XCD 1.096 times as fast as with 128 and 256 by card alone, but 0.81 at
+    // the least, so 1.093 and 0.98).  A batch with heads of 64 takes 128-query tiles always: its samples may all but one be shorter than the bound, and neither the rounds nor the bound say
     // by how much.  6028 drawn batches (2 to 48 samples, the longest of 170 to 8000 keys, the others as long, or from a half, a third or an
     // eighth of it on, 8 to 32 heads): 0.993 of the better width's speed, 0.75 at the least; by rounds, as for one sample, 0.955 and 0.58.  Where
     // the rounds speak for 256 queries, wide against narrow in the mean: samples of one length 0.95 to 1.01, ragged ones 0.71 to 1.02 (above
@@ -1164,9 +1166,10 @@ AttendPlan attend_plan(int dt, int B, int max_seqlen, int H, int dh, bool whole)
     const int per_xcd = ceil_div(H * B, 8);
     auto rounds_of = [](long tiles) { return (tiles + 31) / 32; };
     auto rounds = [&](int queries) { return rounds_of((long)per_xcd * ceil_div(max_seqlen, queries)); };
+    auto rounds_for = [&](int queries) { return B == 1 ? rounds(queries) : (ceil_div(max_seqlen, queries) * heads + 255) / 256; };
     // in hundredths of a round of 256-query tiles
-    const long wide = 100 * rounds(256), mid = 90 * rounds(192);
-    long narrow = (dh == 128 ? 66 : 55) * rounds(128);
+    const long wide = 100 * rounds_for(256), mid = 90 * rounds(192);
+    long narrow = (dh == 128 ? 66 : 55) * rounds_for(128);
     const int left = max_seqlen % 128;
     if (dh == 128 && B == 1 && left > 0 && left <= 64) {
         // last tiles that find no place in the rounds of the others

@@ -200,9 +200,10 @@ def test_short_samples_share_the_units(lib, H, dh, longest, batch):
     (36, [3870], 128, "tiles 256 in turn"), (20, [2687], 64, "tiles 128"),
     (16, [2200], 128, "tiles 192"), (24, [1900], 128, "tiles 192"), (32, [1100], 128, "tiles 192"), (32, [700, 700], 128, "tiles 192"),
     (40, [1538], 128, "tiles 128 in turn"), (48, [1282], 128, "tiles 128 in turn"), (24, [2690], 128, "tiles 192 in turn"),      # last tiles that fit beside the others, or not
+    (12, [834, 738, 350], 128, "tiles 128"), (6, [1689, 1200, 900], 128, "tiles 128"),      # batches of which not every sample need have as many tiles as the longest
     (32, [1024], 128, "tiles 128"), (32, [1600], 128, "tiles 256"), (32, [3773], 128, "tiles 256 in turn"), (16, [3500], 64, "tiles 256"),
 ])
 def test_attention_counts_rounds_of_an_xcd(lib, H, lens, dh, form):
-    """The width of the query tiles goes by rounds over the 32 units of the XCD with the most heads."""
+    """The width of one sample's query tiles, and whether a batch has tiles of 192, goes by rounds over the 32 units of the XCD with the most heads."""
     from parity import attend_form
     assert attend_form(H, lens, dh) == form
