@@ -160,7 +160,7 @@ int topk_run(float* scores, int B, const int32_t* score_off, const int32_t* keep
 
 // d3tom_attend without its 64-query tiles (bf16): the blocks of a stack on samples that no merge has shortened, where a merge may follow.  Which of
 // two near-equal cosines takes a token goes by the last bits of these sums.  Above 512 tokens the groups of those tiles add the keys in another
-// order than the wider ones do, and whether they are taken goes by the number of samples; tiles of 128 and 256 queries add alike.  (Of 26 drawn
+// order than the wider ones do, and whether they are taken goes by the number of samples; tiles of 128, 192 and 256 queries add alike.  (Of 26 drawn
 // merged stacks of 200 to 2000 visual tokens, 4 had tokens that went to another row of 1e-5 to 5e-5 less or more cosine with them.)  What still moves
 // the sums of a sample of up to 512 tokens is whether the batch is for the short-sample kernel: its longest sample, and its 128-query tiles.
 int attend_whole_run(const void* q, const void* k, const void* v, int B, const int32_t* cu_seqlens, int max_seqlen, int H, int dh, float scale,

@@ -438,12 +438,14 @@ def _attend_rounded_probabilities(q, k, v, weight, tile=64, parts=1):
 
 
 @pytest.mark.parametrize("spread", [1.0, 2.0, 4.0])
-@pytest.mark.parametrize("H,dh,n,weighted", [(2, 128, 1300, False), (2, 64, 1300, False), (2, 128, 1300, True), (13, 128, 1300, False), (32, 128, 1198, False), (32, 64, 1300, True)])
-def test_attend_error_is_that_of_rounded_probabilities(H, dh, n, weighted, spread):
+@pytest.mark.parametrize("H,dh,n,weighted,form", [(2, 128, 1300, False, "tiles 64"), (2, 64, 1300, False, "tiles 64"), (2, 128, 1300, True, "tiles 64"), (13, 128, 1300, False, "tiles 128"),
+                                                  (32, 128, 1198, False, "tiles 192"), (32, 128, 1600, False, "tiles 256"), (32, 64, 1300, True, "tiles 256")])
+def test_attend_error_is_that_of_rounded_probabilities(H, dh, n, weighted, form, spread):
     """The tiled kernel against float64, in 2-norm: no further off than the rounding of the probabilities against the running
-    maximum makes it, with query tiles of 64 (two groups with a maximum each: the first three), 128 and 256.  Both sides round almost the same probabilities, so the two errors agree to a fraction of a percent (the
+    maximum makes it, with query tiles of 64 (two groups with a maximum each: the first three), 128, 192 and 256.  Both sides round almost the same probabilities, so the two errors agree to a fraction of a percent (the
     bound of 2 % leaves room for ties of the rounding); any fixed reference of the exponents is 4 % off at unit logit spread and
     8 to 15 % at 2 and 4.  `spread` is the standard deviation of the logits."""
+    assert attend_form(H, [n], dh) == form
     q, k, v = W.random_qkv(870 + n + dh, n, H, dh, "bf16")
     q, k = (W.round_to(t * np.float32(np.sqrt(spread)), "bf16") for t in (q, k))
     vis, counts = n // 5, (1 + np.arange(n // 2) % 6).astype(np.int32)
@@ -484,11 +486,11 @@ def test_attend_error_of_short_samples(H, dh, n, weighted, copies, spread):
     (32, 128, [450], 64), (32, 128, [480], 64), (40, 128, [350], 64), (48, 128, [300], 64), (64, 128, [500], 64), (96, 64, [300], 64), (64, 64, [449], 64),
     (16, 64, [512], 32), (16, 64, [512, 300], 32), (17, 64, [512, 40], 32),                         # 512 tiles with heads of 64, and more
     (5, 128, [2], 32), (5, 128, [33], 32), (5, 64, [129], 32), (5, 128, [385], 32),         # one to four steps of four tiles, the last one with a single tile
-    (9, 128, [1, 31, 32, 33, 63, 64, 65, 97, 127, 128, 129, 255, 384, 511], 32), (40, 64, [64, 1, 95, 96, 97, 130, 257, 512], None),     # steps without tiles
+    (9, 128, [1, 31, 32, 33, 63, 64, 65, 97, 127, 128, 129, 255, 384, 511], 32), (12, 64, [64, 1, 95, 96, 97, 130, 257, 512], 32),     # steps without tiles
 ])
 def test_attend_short_samples_by_halves_of_64_queries(H, dh, lens, queries, weighted):
     """The short-sample kernel with 32 and with 64 queries to a workgroup, at the edges of tiles, halves and steps."""
-    assert queries is None or attend_form(H, lens, dh) == f"short {queries}"
+    assert attend_form(H, lens, dh) == f"short {queries}"
     qkv = [W.random_qkv(1010 + n, n, H, dh, "bf16") for n in lens]
     vis, counts = [n // 5 for n in lens], [(1 + np.arange(n // 2) % 37).astype(np.int32) for n in lens]
     outs = gpu_attend_weighted(qkv, counts, vis, "bf16") if weighted else gpu_attend(qkv, "bf16")
@@ -502,7 +504,8 @@ def test_attend_short_samples_by_halves_of_64_queries(H, dh, lens, queries, weig
     (5, 128, 300, 40, False),            # several rounds of 128-query tiles, heads that do not divide among the XCDs
     (5, 128, 600, 32, True),             # ... of 256-query tiles
     (9, 128, 1030, 16, False), (9, 128, 1030, 16, True),
-    (44, 64, 2813, 1, False), (44, 64, 2813, 1, True),          # heads of 64: only one sample has 256-query tiles
+    (44, 64, 2550, 1, False), (44, 64, 2550, 1, True),          # heads of 64: only one sample has 256-query tiles
+    (44, 64, 2813, 1, True),                                    # ... where they save rounds
     (9, 64, 1030, 16, False), (9, 64, 1030, 16, True),          # ... and a batch one workgroup per 128-query tile
     (12, 128, 520, 64, False), (12, 128, 520, 65, False),       # as many samples as a wave has lanes, one more
     (12, 128, 100, 65, False), (12, 128, 100, 66, True),        # one workgroup per 128-query tile, several rounds
@@ -530,14 +533,26 @@ def _drawn_lengths(seed, choices=(1, 64, 65, 128, 129, 192, 193, 256, 257, 320, 
     return [r.choice(choices) for _ in range(32)]
 
 
-@pytest.mark.parametrize("H,dh,lens,weighted", [
-    (32, 128, [2060], False), (32, 128, [2060], True), (32, 128, [650] * 3, False), (20, 128, [1025, 1030, 260, 300, 513], True),
-    (9, 128, _drawn_lengths(9), True), (13, 128, _drawn_lengths(393), False), (12, 128, _drawn_lengths(352), False),     # as many samples as have two places
-    (20, 64, [1025, 1030, 260, 300, 513], True), (12, 64, _drawn_lengths(352), False),      # (heads of 64 in a batch: every tile for itself)
+def _last_tiles_apart(H, lens, width):
+    """The kernel's estimate: whether last tiles with at most half of their queries are items of their own behind all others."""
+    P = sum(-(-n // width) for n in lens) * H // 8
+    S = sum(0 < n % width <= width // 2 for n in lens) * H // 8
+    among, full = -(-P // 32), -(-(P - S) // 32)
+    free = full * 32 - (P - S)
+    return len(lens) <= 32 and S > 0 and full + 0.72 * (-(-(S - free) // 32) if S > free else 0) <= 0.99 * among * (P - 0.28 * S) / P
+
+
+@pytest.mark.parametrize("H,dh,lens,weighted,form", [
+    (40, 128, [1540], False, "tiles 128 in turn"), (40, 128, [1566], True, "tiles 128 in turn"), (32, 128, [650] * 3, False, "tiles 128 in turn"),
+    (64, 128, [4098], False, "tiles 256 in turn"), (128, 128, [2050], True, "tiles 256 in turn"),
+    (20, 128, [1025, 1030, 260, 300, 513], True, "tiles 256 in turn"),
+    (9, 128, _drawn_lengths(9), True, "tiles 256 in turn"), (13, 128, _drawn_lengths(393), False, "tiles 256 in turn"), (12, 128, _drawn_lengths(352), False, "tiles 256 in turn"),     # as many samples as have two places
+    (20, 64, [1025, 1030, 260, 300, 513], True, "tiles 128"), (12, 64, _drawn_lengths(352), False, "tiles 128"),      # (heads of 64 in a batch: every tile for itself)
 ])
-def test_attend_short_last_tiles_behind_the_others(H, dh, lens, weighted):
+def test_attend_short_last_tiles_behind_the_others(H, dh, lens, weighted, form):
     """Lengths at which the last tiles with at most half of their queries are items of their own behind all others (the estimate of the
     passes over an XCD's 32 units says so), heads that do not divide among the XCDs too: every row has to be there."""
+    assert attend_form(H, lens, dh) == form and ("turn" not in form or _last_tiles_apart(H, lens, int(form.split()[1])))
     base = W.random_qkv(930 + H, max(lens), H, dh, "bf16")
     qkv = [tuple(np.roll(t, i, axis=0)[:n] for t in base) for i, n in enumerate(lens)]
     vis, counts = [n // 5 for n in lens], [(1 + np.arange(n // 2) % 37).astype(np.int32) for n in lens]
@@ -548,11 +563,15 @@ def test_attend_short_last_tiles_behind_the_others(H, dh, lens, weighted):
         check_attend(o, q, k, v, "bf16", rows=rows, key_weight=key_weights(n, vs, c) if weighted else None)
 
 
-@pytest.mark.parametrize("H,dh,n,weighted", [(60, 128, 520, False), (60, 128, 640, True), (60, 128, 641, False), (60, 64, 705, True), (60, 64, 737, False),
-                                             (2, 128, 513, False), (2, 128, 560, True), (2, 64, 656, False)])
-def test_attend_last_tile_with_few_queries(H, dh, n, weighted):
-    """One round of 256-query tiles (60 heads) or 128-query tiles (2) whose last tile leaves one to seven of its eight waves without
-    a query: with 256 queries those only load and keep step, with 128 they compute with rows that are zero and store nothing."""
+@pytest.mark.parametrize("H,dh,n,weighted,form", [
+    (60, 128, 770, False, "tiles 256"), (60, 128, 896, True, "tiles 256"), (60, 128, 897, False, "tiles 256"), (60, 64, 705, True, "tiles 256"), (60, 64, 737, False, "tiles 256"),
+    (60, 128, 520, False, "tiles 192"), (60, 128, 640, True, "tiles 192"), (60, 128, 641, False, "tiles 192"),
+    (32, 128, 520, False, "tiles 128"), (32, 128, 560, True, "tiles 128"),
+    (2, 128, 513, False, "tiles 64"), (2, 128, 560, True, "tiles 64"), (2, 64, 656, False, "tiles 64")])
+def test_attend_last_tile_with_few_queries(H, dh, n, weighted, form):
+    """One round of tiles whose last one leaves waves without a query: with 256 queries those only load and keep step, with fewer they compute
+    with rows that are zero and store nothing."""
+    assert attend_form(H, [n], dh) == form
     q, k, v = W.random_qkv(910 + n, n, H, dh, "bf16")
     vs, c = n // 5, (1 + np.arange(n // 2) % 37).astype(np.int32)
     o = (gpu_attend_weighted([(q, k, v)], [c], [vs], "bf16") if weighted else gpu_attend([(q, k, v)], "bf16"))[0]
@@ -590,16 +609,22 @@ def test_attend_groups_that_share_queries(H, dh, lens, rise, weighted):
 
 
 @pytest.mark.parametrize("weighted", [False, True])
-@pytest.mark.parametrize("H,dh,lens", [
-    (32, 128, [1025]), (32, 128, [1152]), (32, 128, [1153]), (32, 128, [1281]), (32, 128, [1536]),      # last tiles of 65 to 192 queries, one round
-    (32, 128, [700, 1, 128, 129]), (32, 128, [768, 192, 193, 64]), (64, 128, [513, 144]), (40, 128, [1040]),      # ragged, samples of one tile
-    (32, 128, [2049]), (32, 128, [2060]), (32, 128, [2113]), (33, 128, [3072]), (64, 128, [1409]),      # tiles in turn
-    (60, 128, [769]), (60, 128, [850]), (60, 128, [1000]), (32, 128, [1537]),      # 256 queries beside them, one round
+@pytest.mark.parametrize("rise", [0.0, 9.0])
+@pytest.mark.parametrize("H,lens,form", [
+    (32, [1025], "tiles 192"), (32, [1152], "tiles 192"), (32, [1153], "tiles 192"), (32, [1281], "tiles 192"), (32, [1536], "tiles 192"), (40, [1040], "tiles 192"),   # last tiles of 65 to 192 queries, one round
+    (32, [700, 129], "tiles 192"), (32, [1, 700], "tiles 192"), (16, [768, 193, 64, 1], "tiles 192"), (16, [129, 700, 1, 128], "tiles 192"), (3, [700, 193] * 8, "tiles 192"),      # ragged, samples of one tile
+    (32, [2049], "tiles 192 in turn"), (32, [2113], "tiles 192 in turn"), (36, [1631], "tiles 192 in turn"), (64, [1409], "tiles 192 in turn"),
+    (32, [700, 1, 128, 129], "tiles 128 in turn"), (64, [513, 144], "tiles 128 in turn"),       # beside them: a batch of more than one round,
+    (60, [769], "tiles 256"), (32, [1537], "tiles 256"), (33, [3072], "tiles 256 in turn"),     # one sample that takes a round more
 ])
-def test_attend_tiles_of_192_queries(H, dh, lens, weighted):
-    """Two query blocks to a wave of one group of waves, one to a wave of the other: every row around the borders between waves, groups and tiles."""
+def test_attend_tiles_of_192_queries(H, lens, form, rise, weighted):
+    """Two query blocks to a wave of one group of waves, one to a wave of the other: every row around the borders between waves, groups and tiles.  With `rise` later
+    keys exceed earlier ones by far, and the running maximum of every block moves with almost every tile."""
+    dh = 128
+    assert attend_form(H, lens, dh) == form
     base = W.random_qkv(960 + H, max(lens), H, dh, "bf16")
     qkv = [tuple(np.roll(t, i, axis=0)[:n] for t in base) for i, n in enumerate(lens)]
+    qkv = [(q, W.round_to(k * (1 + rise * np.arange(len(k), dtype=np.float32) / len(k))[:, None, None], "bf16"), v) for q, k, v in qkv]
     vis, counts = [n // 5 for n in lens], [(1 + np.arange(n // 2) % 37).astype(np.int32) for n in lens]
     outs = gpu_attend_weighted(qkv, counts, vis, "bf16") if weighted else gpu_attend(qkv, "bf16")
     for (q, k, v), o, vs, c in zip(qkv, outs, vis, counts):
@@ -607,6 +632,27 @@ def test_attend_tiles_of_192_queries(H, dh, lens, weighted):
         edges = [r for t in range(0, n, 192) for r in (t, t + 31, t + 32, t + 127, t + 128, t + 143, t + 144, t + 191)]
         rows = np.array(sorted({r for r in edges if r < n} | set(range(max(n - 9, 0), n))))
         check_attend(o, q, k, v, "bf16", rows=rows, key_weight=key_weights(n, vs, c) if weighted else None)
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("rise", [0.0, 9.0])
+@pytest.mark.parametrize("H,dh,n,batches", [
+    (32, 128, 1100, [(1, "tiles 192"), (2, "tiles 128 in turn"), (3, "tiles 256 in turn")]),
+    (20, 128, 1300, [(1, "tiles 192"), (2, "tiles 256"), (3, "tiles 128 in turn"), (4, "tiles 256 in turn")]),
+    (60, 64, 705, [(1, "tiles 256"), (2, "tiles 128")]),
+])
+def test_attend_bits_do_not_depend_on_the_width_of_the_tiles(H, dh, n, batches, rise, weighted):
+    """Tiles of 128, 192 and 256 queries add a row's products alike: a sample has the same bits alone and beside others.  (A stack relies on it in front of its merge.)"""
+    q, k, v = W.random_qkv(1100 + n, n, H, dh, "bf16")
+    k = W.round_to(k * (1 + rise * np.arange(n, dtype=np.float32) / n)[:, None, None], "bf16")
+    vis, counts = n // 5, (1 + np.arange(n // 2) % 37).astype(np.int32)
+    outs = []
+    for copies, form in batches:
+        assert attend_form(H, [n] * copies, dh) == form
+        qkv = [(q, k, v)] * copies
+        outs += gpu_attend_weighted(qkv, [counts] * copies, [vis] * copies, "bf16") if weighted else gpu_attend(qkv, "bf16")
+    for o in outs[1:]:
+        np.testing.assert_array_equal(o, outs[0])
 
 
 def test_attend_special_cases_bf16():
