@@ -6,17 +6,19 @@
 // reads it (dec_idx + prefix-sum offsets) without a host round trip, so a workgroup needs the counts of all samples in front of
 // its own: it takes them itself, a wave per sample, 16 positions a lane in flight.  Of its own samples it tests 4096 positions at a time, four
 // a thread, and compacts the flags in ascending position order (ballots, then a prefix over the 64 pieces of 64 positions).
-// Bound by trips to memory: the offsets, then a trip per 1024 positions of the longest sample in front, the own sample's beside
-// them.  DEC_GROUPS bounds what the counting reads again: half of DEC_GROUPS times all ids.
-// (One workgroup for all samples, 1024 positions at a time: 16 samples of 2688 ids 34.2 us, now 6.4; 64 of 1152 82 -> 12.6; 200 of 1000
-// 217 -> 24.5; 4 of 3773 12.1 -> 5.6; one of 9000 7.2 -> 4.5; one of 208 .. 3773 4.1 .. 4.3 -> 3.7.)
+// Bound by trips to memory: the offsets, then the own sample's first ids and the ids in front, for a wave every 16th sample, 1024 positions a trip; behind the barrier a
+// trip per further 4096 positions.  Few positions are bound by the instructions of 16 waves on one unit: waves skip what lies past the end, and the list's part if they found
+// nothing.  DEC_GROUPS bounds what the counting reads again: half of DEC_GROUPS times all ids.
+// (One workgroup for all samples, 1024 positions at a time; own ids requested behind the count and its barrier, every wave all of a turn; now.  Calls in a graph: one sample of 64 ids 2.03,
+// 2.50 and 2.2 us, of 1000 2.15, 2.7 and 2.4, of 4097 4.6, 3.6 and 3.3; two of 64 2.55, 3.3 and 2.4; 16 of 64 10.8, 4.3 and 3.1, of 500 .. 4000 32, 7.1 and 6.5; 64 of 1025 82, 12.7 and 9.2; 200 of
+// 1000 157, 21.9 and 19.9.)
 #include "internal.hpp"
 
 namespace d3tom {
 
 constexpr int DEC_THREADS = 1024, DEC_WAVES = DEC_THREADS / 64;
 constexpr int DEC_PER = 4;                       // positions of a thread per turn
-constexpr int DEC_COUNT = 16;                    // positions of a lane per turn of the count
+constexpr int DEC_COUNT = 16, DEC_FEW = 4;       // positions of a lane per turn of the count, and where no more are left
 constexpr int DEC_GROUPS = 64;
 
 __global__ __launch_bounds__(DEC_THREADS) void update_deciders_kernel(
@@ -24,66 +26,96 @@ __global__ __launch_bounds__(DEC_THREADS) void update_deciders_kernel(
     const int32_t* __restrict__ seq_off, int max_D, int32_t* __restrict__ dec_idx, int32_t* __restrict__ dec_off,
     int32_t* __restrict__ dec_count) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    __shared__ int wtot[DEC_PER * DEC_WAVES];    // deciders in each 64 positions of a turn
+    __shared__ int wtot[2][DEC_PER * DEC_WAVES]; // deciders in each 64 positions of a turn; turns alternate
     __shared__ int wsum[DEC_WAVES];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b0 = (int)blockIdx.x * run, b1 = min(b0 + run, B);
-    // which of U pieces of 64 positions each hold deciders: positions i0 + 64 * (first + stride * u) + lane of the sample
-    auto test = [&](int tok0, int N, int i0, int first, int stride, auto pieces, uint64_t* m) {
-        constexpr int U = decltype(pieces)::value;
-        const int left = min(N - i0, DEC_PER * DEC_THREADS);                    // beyond the sample: outside the buffer, not fetched
-        const __amdgpu_buffer_rsrc_t cur = make_uniform_rsrc(cur_ids + (size_t)tok0 + i0, (uint32_t)left * 4u);
-        const __amdgpu_buffer_rsrc_t prev = make_uniform_rsrc(prev_ids + (size_t)tok0 + i0, (uint32_t)left * 4u);
-        int c[U], p[U];
+    // the `left` ids of a sample from position i0 on (beyond them: outside the buffer, not fetched), and which of 64 positions hold deciders
+    auto buffer = [&](const int32_t* ids, int tok0, int i0, int left) { return make_uniform_rsrc(ids + (size_t)tok0 + i0, (uint32_t)max(left, 0) * 4u); };
+    auto test = [&](int left, int at, int c, int p) { return __builtin_amdgcn_ballot_w64(at + lane < left && c != mask_id && p == mask_id); };
+    // a turn of the own samples: this wave's pieces, of those past the end not even the instructions
+    int c[DEC_PER], p[DEC_PER];
+    auto request = [&](int tok0, int i0, int left) {
+        const __amdgpu_buffer_rsrc_t cur = buffer(cur_ids, tok0, i0, left), prev = buffer(prev_ids, tok0, i0, left);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int at = (64 * (first + stride * u) + lane) * 4;
-            c[u] = __builtin_amdgcn_raw_buffer_load_b32(cur, at, 0, 0);
-            p[u] = __builtin_amdgcn_raw_buffer_load_b32(prev, at, 0, 0);
+        for (int u = 0; u < DEC_PER; ++u) {
+            const int at = DEC_THREADS * u + wave * 64;
+            if (at >= left) break;
+            c[u] = __builtin_amdgcn_raw_buffer_load_b32(cur, (at + lane) * 4, 0, 0);
+            p[u] = __builtin_amdgcn_raw_buffer_load_b32(prev, (at + lane) * 4, 0, 0);
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            m[u] = __builtin_amdgcn_ballot_w64(64 * (first + stride * u) + lane < left && c[u] != mask_id && p[u] == mask_id);
     };
-    // entries written for the samples in front of this workgroup's
-    int mine = 0;
-    for (int b = wave; b < b0; b += DEC_WAVES) {
-        const int tok0 = __builtin_amdgcn_readfirstlane(seq_off[b]), N = __builtin_amdgcn_readfirstlane(seq_off[b + 1]) - tok0;
-        int found = 0;
-        for (int i0 = 0; i0 < N; i0 += 64 * DEC_COUNT) {
-            uint64_t m[DEC_COUNT];
-            test(tok0, N, i0, 0, 1, std::integral_constant<int, DEC_COUNT>{}, m);
+    // the first turn of the own sample is on its way while those in front are counted
+    int tok0 = seq_off[b0], N = seq_off[b0 + 1] - tok0;
+    request(tok0, 0, N);
+    if (b0 > 0) {
+        // entries written for the samples in front of this workgroup's
+        int mine = 0;
+        for (int b = wave; b < b0; b += DEC_WAVES) {
+            const int t = __builtin_amdgcn_readfirstlane(seq_off[b]), n = __builtin_amdgcn_readfirstlane(seq_off[b + 1]) - t;
+            int found = 0;
+            auto count = [&](int i0, auto pieces) {
+                constexpr int U = decltype(pieces)::value;
+                const __amdgpu_buffer_rsrc_t cur = buffer(cur_ids, t, i0, n - i0), prev = buffer(prev_ids, t, i0, n - i0);
+                int cc[U], pp[U];
 #pragma unroll
-            for (int u = 0; u < DEC_COUNT; ++u) found += __popcll(m[u]);
+                for (int u = 0; u < U; ++u) {
+                    cc[u] = __builtin_amdgcn_raw_buffer_load_b32(cur, (64 * u + lane) * 4, 0, 0);
+                    pp[u] = __builtin_amdgcn_raw_buffer_load_b32(prev, (64 * u + lane) * 4, 0, 0);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) found += __popcll(test(n - i0, 64 * u, cc[u], pp[u]));
+            };
+            for (int i0 = 0; i0 < n; i0 += 64 * DEC_COUNT) {
+                if (n - i0 > 64 * DEC_FEW) count(i0, std::integral_constant<int, DEC_COUNT>());
+                else count(i0, std::integral_constant<int, DEC_FEW>());
+            }
+            mine += min(found, max_D);
         }
-        mine += min(found, max_D);
+        if (lane == 0) wsum[wave] = mine;
+    } else if (tid == 0) {
+        dec_off[0] = 0;
     }
-    if (lane == 0) wsum[wave] = mine;
-    __syncthreads();
-    int base = 0;
-#pragma unroll
-    for (int w = 0; w < DEC_WAVES; ++w) base += wsum[w];
-    if (b0 == 0 && tid == 0) dec_off[0] = 0;
+    int base = 0, turns = 0;
     for (int b = b0; b < b1; ++b) {
-        const int tok0 = seq_off[b], N = seq_off[b + 1] - tok0;
+        if (b > b0) {
+            tok0 = seq_off[b]; N = seq_off[b + 1] - tok0;
+            request(tok0, 0, N);
+        }
         int found = 0;                                     // deciders of this sample seen so far (all of them)
-        for (int i0 = 0; i0 < N; i0 += DEC_PER * DEC_THREADS) {                 // uniform trip count
-            uint64_t m[DEC_PER];
-            test(tok0, N, i0, wave, DEC_WAVES, std::integral_constant<int, DEC_PER>{}, m);
-            __syncthreads();                               // wtot of the turn before has been read
-            if (lane == 0)
-#pragma unroll
-                for (int u = 0; u < DEC_PER; ++u) wtot[u * DEC_WAVES + wave] = __popcll(m[u]);
-            __syncthreads();
-            static_assert(DEC_PER * DEC_WAVES == 64, "a piece per lane");
-            const int upto = wave_incl_scan(wtot[lane]);
+        for (int i0 = 0;;) {                               // uniform trip count, one turn for a sample without positions
+            const int left = N - i0;
+            const bool more = left > DEC_PER * DEC_THREADS;
+            uint64_t m[DEC_PER], any = 0;
+            int* const w = wtot[turns & 1];
 #pragma unroll
             for (int u = 0; u < DEC_PER; ++u) {
-                const int piece = u * DEC_WAVES + wave;
-                const int ord = found + (piece ? __builtin_amdgcn_readlane(upto, piece - 1) : 0) + __popcll(m[u] & ((1ull << lane) - 1ull));
-                if (((m[u] >> lane) & 1) && ord < max_D) dec_idx[base + ord] = i0 + 64 * piece + lane;     // beyond max_D: counted, not listed
+                const int at = DEC_THREADS * u + wave * 64;
+                m[u] = at < left ? test(left, at, c[u], p[u]) : 0;
+                any |= m[u];
+                if (at < left && lane == 0) w[u * DEC_WAVES + wave] = __popcll(m[u]);
             }
-            found += __builtin_amdgcn_readlane(upto, 63);
+            __syncthreads();                               // (the turn after this one writes the other half, the one after that is behind another barrier)
+            if (turns++ == 0 && b0 > 0) {
+#pragma unroll
+                for (int v = 0; v < DEC_WAVES; ++v) base += wsum[v];
+            }
+            if (any || wave == 0 || more || b + 1 < b1) {  // (the others are done)
+                static_assert(DEC_PER * DEC_WAVES == 64, "a piece per lane");
+                const int upto = wave_incl_scan(lane * 64 < left ? w[lane] : 0);
+#pragma unroll
+                for (int u = 0; u < DEC_PER; ++u) {
+                    if (m[u] == 0) continue;
+                    const int piece = u * DEC_WAVES + wave;
+                    const int ord = found + (piece ? __builtin_amdgcn_readlane(upto, piece - 1) : 0) +
+                                    __builtin_amdgcn_mbcnt_hi((uint32_t)(m[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[u], 0));
+                    if (((m[u] >> lane) & 1) && ord < max_D) dec_idx[base + ord] = i0 + 64 * piece + lane;     // beyond max_D: counted, not listed
+                }
+                found += __builtin_amdgcn_readlane(upto, 63);
+            }
+            if (!more) break;
+            i0 += DEC_PER * DEC_THREADS;
+            request(tok0, i0, N - i0);
         }
         const int kept = min(found, max_D);
         if (tid == 0) {

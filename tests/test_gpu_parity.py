@@ -1274,6 +1274,11 @@ def test_update_deciders_sizes(nb, share):
     rng = np.random.default_rng(1000 * nb + int(100 * share))
     edge = [4097, 1, 1024, 0, 64, 65, 1025, 4096, 63, 8193, 1023, 2688, 4095]
     lens = [edge[b % len(edge)] if b < 2 * len(edge) else int(rng.integers(0, 300)) for b in range(nb)]
+    _check_update_deciders(lens, share, rng)
+
+
+def _check_update_deciders(lens, share, rng):
+    nb = len(lens)
     M, max_D, total = 126336, 200, sum(lens)
     prev, cur = rng.integers(0, 32000, total).astype(np.int32), rng.integers(0, 32000, total).astype(np.int32)
     prev[rng.random(total) < 0.5] = M
@@ -1295,6 +1300,17 @@ def test_update_deciders_sizes(nb, share):
     np.testing.assert_array_equal(cnt.cpu().numpy(), counts)
     np.testing.assert_array_equal(idx.cpu().numpy()[:len(want)], want)
     assert (idx.cpu().numpy()[len(want):] == -7).all()
+
+
+@pytest.mark.parametrize("share", [0.02, 1.0])
+@pytest.mark.parametrize("n", [0, 1, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 1280, 1281, 2049, 4096, 4097, 5120, 8193])
+def test_update_deciders_of_one_sample_and_behind_it(n, share):
+    """A sample alone, and as the one that the next samples' workgroups count: at the edges of a wave's 64 positions, of the count's turns of 256 and 1024, of
+    the own turns of 1024 positions a part and 4096 together."""
+    rng = np.random.default_rng(10 * n + int(share))
+    for lens in ([n], [n, 70], [70, n, 1], [n] * 18):
+        if sum(lens):
+            _check_update_deciders(lens, share, rng)
 
 
 def test_bitwise_determinism():
