@@ -15,52 +15,41 @@
 //
 // A workgroup has eight waves of 32 or 16 queries in two groups of four; wave i and wave i + 4 share a SIMD.  The groups
 // alternate (ping-pong): while one issues the MFMAs of a 64-key tile (S of tile i + 1, O += V P of tile i: 64 of them, 1024
-// clocks), the other does the softmax arithmetic of its tile; a barrier ends the phase.  That pays because the smaller MFMA
-// shape lets another wave's vector instructions through: per tile 1058 clocks of MFMAs and 756 of softmax arithmetic (an fma,
-// an exp2 and half a conversion per logit) of the other wave take 1250 clocks together, whereas beside MFMA 32x32x16 the exponentials do not issue at all (1029 + 756 -> 1780).
-// Measured at 32 heads of 128 (four independent waves on the larger shape before): 3773 keys 240 -> 210 us, 1951 keys
-// 71 -> 62 us; 16 heads of 64, 4 x 2000 keys on 256-query tiles: 83 us either way, half as many
-// MFMAs beside the same softmax arithmetic.
+// clocks), the other does the softmax arithmetic of its tile.  That pays because the smaller MFMA shape lets another wave's vector
+// instructions through: per tile 1058 clocks of MFMAs and 756 of softmax arithmetic (an fma, an exp2 and half a conversion per logit) of
+// the other wave take 1250 clocks together, whereas beside MFMA 32x32x16 the exponentials do not issue at all (1029 + 756 -> 1780).
 //
-// What both waves of a SIMD share is the port of the vector instructions.  An MFMA of 17.4 clocks keeps the other wave's from it for 9.6, the
+// Bound by the port of the vector instructions, which both waves of a SIMD share.  An MFMA of 17.4 clocks keeps the other wave's from it for 9.6, the
 // softmax arithmetic of a tile takes 740 (an exp2 or a conversion of a pair 8 clocks, others 4) and 190 more for each block of 16 queries whose
 // maximum moves.  What costs more than its share is an instruction of that kind in an MFMA phase: it waits behind the exponentials of the
-// other wave, and the MFMAs behind it wait as well (with the eight additions of a tile's V addresses the first product took 870 or 1270
-// clocks, the latter where the other wave had no accumulators to rescale first).  And a barrier makes four SIMDs wait for the one with the most to rescale.  So
+// other wave, and the MFMAs behind it wait as well.  And a barrier makes four SIMDs wait for the one with the most to rescale.  So
 //   - the fragments' addresses move on in the softmax phase, and are few: K and V tiles lie in LDS in parts of 64 dims, whose k-steps and blocks differ
-//     by constants that go into the instructions, so that six addresses serve a stage instead of twelve;
+//     by constants that go into the instructions, so that six addresses serve a stage;
 //   - the loads' addresses are constants, the way from tile to tile is in the buffer descriptors and done by the scalar unit in the MFMA phase;
 //   - the exponentials are held inside the phase (the compiler put them behind its end, out of its priority and behind a wait for loads);
 //   - both blocks' maxima are there before the first branch on one, and those of four lanes are plain v_max (fmaxf also quiets each operand);
-//   - a tile has one barrier, in front of group 0's softmax phase and group 1's MFMA phase, not two: inside a tile the waves of a SIMD find
-//     their turns by themselves (groups that share their queries have a ring each and need both).
-// 32 heads of 128: 3773 keys 210 -> 203 us, 4 x 493 .. 1951 weighted 130 -> 124, 16 x 600 .. 1500 369 -> 356, 1951 60.7 -> 57.9, 1000 21.9 -> 21.0; 8 heads,
-// 900 keys 11.95 -> 10.95; 16 heads of 64, 900 keys 9.35 -> 8.55, 4 x 2000 85.4 -> 83.0.  (The one barrier alone 1.02 to 1.04.  Without effect or worse: twelve
-// addresses moved in the softmax phase, 1.00 and in short chains of phases 1.03; descriptors made up in front of the loads, short chains 0.96; stages unrolled
-// in pairs, which spills; O not transposed, so that only the rows of queries whose maximum moved are rescaled, 0.95 to 0.99 and 0.83 in short chains; loads behind
-// the MFMAs or behind the maxima, 0.98 to 1.00.)
+//   - a tile has one barrier, in front of group 0's softmax phase and group 1's MFMA phase: inside a tile the waves of a SIMD find
+//     their turns by themselves (groups that share their queries have a ring each and need a barrier in front of either).
+// 32 heads of 128 (four independent waves on the larger shape; two barriers a tile and addresses moved among the MFMAs; now): 3773 keys 240, 208 and 200 us = 1.17
+// PFLOP/s, 1951 keys 71, 61.8 and 58.7.
 //
 // K and V tiles go HBM/L2 -> LDS with direct loads (buffer_load ... lds, no register staging; rows past the end of the sample
 // load as zeros through the buffer bounds check) into a ring; rows are unpadded and their 16-byte chunks XOR-swizzled by the
 // row index instead.  Loads are issued in the softmax phase, and the first K fragments of a tile are read there, so that the
 // MFMA phase starts at once.
 //
-// The softmax arithmetic paces the loop, so its wave has the higher priority (against none, and the MFMAs before it: 8 heads, 900 keys 11.0, 12.0, 12.9 us; 16
-// heads of 64, 900 keys 8.5, 9.5, 10.1; 32 heads, 1000 keys 20.9, 21.1, 21.5; several rounds the same), and it is cut to what the results need: per logit one
-// fma, one exp2, one addition and the packing to bf16, and
+// The softmax arithmetic paces the loop, so its wave has the higher priority (against none, and the MFMAs before it: 8 heads, 900 keys 11.0, 12.0, 12.9 us;
+// several rounds the same), and it is cut to what the results need: per logit one fma, one exp2, one addition and the packing to bf16, and
 //   - the weights and the tail mask of the weighted form enter as the C operand of S^T (log2 w / scale2, -inf);
 //   - the running maximum costs one max3 per two logits: a lane compares its own logits with the column's maximum, and only where one
 //     of them exceeds it do the four lanes meet and the accumulators of that block of 16 queries get their new scale.
 // What the exponents refer to is a matter of precision.  The probabilities are rounded to bf16, the largest ones carry most of
 // that rounding, and relative to the running maximum the largest is exactly 1 and not rounded at all.  With the first tile's
-// maximum as a fixed reference (and the sums of the rounded probabilities from the matrix core) the kernel takes 189 us at 3773
-// keys, but its error against float64 (2-norm, relative, before the output is rounded) is 1.06 to 1.11 times as large at a
-// logit spread of 1 (600 .. 3773 keys), 1.5 to 1.6 at 2 and 1.8 to 1.9 at 4.  Rounded output, measured at 3773 keys, spreads 1,
-// 2, 4: 2.266e-3, 1.919e-3, 1.735e-3; with the fixed reference 2.332e-3, 2.226e-3, 1.916e-3.
+// maximum as a fixed reference the kernel is a tenth faster, but its error against float64 (2-norm, relative) is 2.33e-3, 2.23e-3 and 1.92e-3 at 3773 keys and logit
+// spreads of 1, 2 and 4 instead of 2.27e-3, 1.92e-3 and 1.74e-3.
 // The row sums are float32 sums of the unrounded probabilities, as in the short-sample kernel.  The sums of the rounded ones
-// (a fragment of ones times P^T: 207.5 instead of 211.8 us) are as near to float64, but they move whole rows by the rounding of
-// their probabilities, so that the two kernels give a merge other near-ties: in stack steps of 1000 to 3700 tokens several
-// tokens then go to another near-duplicate.
+// (a fragment of ones times P^T, 2 % faster) are as near to float64, but they move whole rows by the rounding of
+// their probabilities, so that the two kernels give a merge other near-ties.
 //
 // The generic path (float32 or any head size) is one workgroup per query, or in float32 per two queries, and head, with a chunked
 // online softmax in plain float arithmetic.
@@ -144,9 +133,9 @@ constexpr int ATT_WKEYS = 3584;     // longest sample of the weighted tiled kern
 // 16 heads of 64, 1024 keys 13.9 -> 9.4.  No part of a phase bounds it (without loads, exponentials, rescaling or reads of V it is 3 to 8 %
 // faster each).
 //
-// UNEVEN: 192 queries, 32 to a wave of group 0 and 16 to one of group 1.  Where 256 queries fill three quarters of a round of compute units or less, or 128 need
-// another round.  A tile of keys takes 0.86 to 0.94 of the time that 256 queries take, not 0.75: group 1's fragments feed one MFMA each, and four waves
-// that read 32 KB of them keep the LDS busy as long as group 0's MFMAs take.  The sums of a row are those of the other two, bit by bit.
+// UNEVEN: 192 queries, 32 to a wave of group 0 and 16 to one of group 1.  Where 256 queries fill three quarters of a round of an XCD's compute units or less, or 128 need
+// another round.  A round takes 0.87 to 0.94 of the time that one of 256 queries takes, not 0.75 (32 heads, 1100 and 1500 keys 27.1 and 31.1 us, 39.7 and 42.5): group 1's fragments feed one
+// MFMA each, and four waves that read 32 KB of them keep the LDS busy as long as group 0's MFMAs take.  The sums of a row are those of the other two, bit by bit.
 template <int DH, bool WGT, int NQ, bool TURNS, bool SKIP, bool SPLIT, bool UNEVEN>
 __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -185,9 +174,9 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
     // tiles of a head one after the other.  One item per workgroup (places = samples as they come), or (TURNS) workgroup li of the W of
     // an XCD takes its items li, 2 W - 1 - li, 2 W + li, ..., in order of falling time.  Up to 32 samples may have two places, one for the last
     // tile if that leaves half of the waves without a query (0.72 of the others' time) and one for the other tiles: where the tiles fill
-    // the rounds better with the short ones behind all others (2060 .. 2100 keys 106 -> 98 us, 3 x 650 41 -> 38, 8 x 200 .. 700 41.5 -> 39.7,
-    // 24 x 600 .. 1500 at 16 heads of 64 195 -> 186).  Apart from its head's other tiles a short one does not find K and V in the XCD's L2: always
-    // behind the others, 6 x 800 keys take 82 instead of 76.
+    // the rounds better with the short ones behind all others (48 heads, 1290 keys 71 -> 63 us, 40 heads, 1540 78 -> 75, 64 heads, 4098 527 -> 513; 3 x 650 at 32 heads 40.9 -> 39.8; some ragged
+    // batches lose, 32 drawn samples of 1 .. 520 at 13 heads 30.6 -> 32.9: the estimate counts passes as equal, whatever the lengths of the samples in them).
+    // Apart from its head's other tiles a short one does not find K and V in the XCD's L2: always behind the others, 6 x 800 keys take 87 instead of 78.
     const int xcd = blockIdx.x & 7, li = blockIdx.x >> 3;
     constexpr int W = ATT_TURNS_WGS;
     __shared__ int4 tab[TURNS ? WAVE : 1];                 // by place: first token, tokens, sample (its complement: the last tile only), tiles
@@ -217,7 +206,7 @@ __global__ __launch_bounds__(512, 2) void attend_bf16_kernel(
             const int left = len % BQ, all = (len + BQ - 1) / BQ;
             int lone = !UNEVEN && two && left > 0 && left <= BQ / 2;
             {
-                // passes over the XCD's units with the last tiles among the others, and with them behind all others
+                // passes over the XCD's units with the last tiles among the others, and with them behind all others, as if all samples were of one length
                 const int sum = is_last ? 0 : all, sum_lone = is_last ? 0 : lone;
                 const int P = __builtin_amdgcn_readlane(wave_incl_scan(sum), 63) * H / 8, S = __builtin_amdgcn_readlane(wave_incl_scan(sum_lone), 63) * H / 8;
                 const int among = (P + W - 1) / W, full = (P - S + W - 1) / W, free = full * W - (P - S);
@@ -1139,10 +1128,9 @@ AttendPlan attend_plan(int dt, int B, int max_seqlen, int H, int dh, bool whole)
     // 64-query tiles whose groups share the keys, where they fill one round of compute units at most: half as long a chain as 128-query
     // tiles on twice as many units, and two running maxima a row instead of one (error against float64 0.98 of theirs).  Two workgroups of heads of
     // 64 fit on a unit, and of ragged batches fewer tiles are real than the longest
-    // sample lets the host expect.  Means over 897 drawn batches (1 to 16 samples of 33 to 2400 keys), the better of 128 and 256 queries
-    // against this, by the number of 64-query tiles: heads of 128, up to 256 tiles 1.13 (samples of up to 128 keys) to 1.46 (more than 1024), 257
-    // to 384 0.68 to 1.02; heads of 64, up to 256 tiles 1.12 to 1.37, 257 to 512 0.99 to 1.15, 513 to 640 1.12 to 1.28,
-    // 641 to 768 0.95 to 1.07.  (Samples of up to 512 keys that are not for the short-sample kernel have more tiles than that.)
+    // sample lets the host expect.  Means over 697 drawn calls (1 to 16 samples of 513 to 2400 keys), the other widths' choice against this, by the
+    // number of 64-query tiles: heads of 128, up to 128 tiles 1.37, 129 to 256 1.25 (0.81 where an XCD has more than 32 of them), 257 to 384 0.82; heads of 64, up to 256 tiles
+    // 1.32, 257 to 512 0.98, 513 to 640 1.05, 641 to 768 0.97.
     // whole: the blocks of a stack in front of its merge do without these tiles, see attend_whole_run.
     const bool split = !whole && max_seqlen > ATS_MAX_KEYS && ceil_div(max_seqlen, 64) * heads <= (dh == 64 ? 640 : 256);
     // Rounds: an XCD has the tiles of an eighth of the heads and 32 compute units.  (Counted over the whole card, one sample at 12 heads of 128, 3227 keys, took 17 tiles of
@@ -1183,8 +1171,8 @@ AttendPlan attend_plan(int dt, int B, int max_seqlen, int H, int dh, bool whole)
     p.nqt = ceil_div(max_seqlen, p.queries);
     p.lds = (size_t)ATT_SLOTS * 2 * ATT_BK * dh * 2;
     // Several rounds of workgroups that have a compute unit to themselves: one per unit, which takes its tiles in turn, samples by
-    // falling length (one tile per workgroup / in turn: 16 x 700 .. 1505 keys 440 / 422 us, 4 x 575 .. 1951 141 / 133, 12 x 270 .. 800
-    // 114 / 82, 8 x 1000 149 / 145, one sample of 3773 211 / 211; 8 heads, 16 x 1000 .. 3000 303 / 262).
+    // falling length (one tile per workgroup / in turn, 32 heads of 128: 16 x 700 .. 1505 keys 386 / 375 us, 4 x 575 .. 1951 126 / 119, 12 x 270 .. 800
+    // 103 / 82, 8 x 1000 140.5 / 138.7, one sample of 3773 206 / 206; 8 heads, 64 x 300 .. 1000 179 / 156; one sample in tiles of 192 queries 0.98, 2400 keys 108.6 / 110.7).
     p.turns = !split && p.nqt * heads > 256 && !(dh == 64 && p.queries == 128) && B <= WAVE;
     p.skip = p.nqt * heads > (dh == 64 ? 512 : 256);                   // more than one round (two workgroups of 128 queries with heads of 64 to a unit)
     return p;

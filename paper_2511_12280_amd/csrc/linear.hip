@@ -367,7 +367,8 @@ __global__ __launch_bounds__(512, 2) void linear_bf16_kernel(
                 if (row_of(i) < M && u0 + x * V < unit_end) store_bf16<V>(out + at[x] + (size_t)row_of(i) * row_width, v);
             }
     } else {
-        // ROPE: (cos, sin) of channels 2 e and 2 e + 1 of the next row are requested in front of a row's arithmetic
+        // ROPE: (cos, sin) of channels 2 e and 2 e + 1 of the next row are requested in front of a row's arithmetic, also by tiles of the v section, which use
+        // none (under a condition, 55 shapes of 16 to 3773 rows 0.994 in the mean, 3773 rows of 512 channels 12.2 -> 13.4 us)
         float4 cs[2][EPI == LIN_ROPE ? NV : 1][V / 2];
         auto request = [&](int i) {
 #pragma unroll
