@@ -640,9 +640,11 @@ def test_attend_tiles_of_192_queries(H, lens, form, rise, weighted):
     (32, 128, 1100, [(1, "tiles 192"), (2, "tiles 128 in turn"), (3, "tiles 256 in turn")]),
     (20, 128, 1300, [(1, "tiles 192"), (2, "tiles 256"), (3, "tiles 128 in turn"), (4, "tiles 256 in turn")]),
     (60, 64, 705, [(1, "tiles 256"), (2, "tiles 128")]),
+    (32, 128, 493, [(1, "short 64"), (2, "short 32")]), (64, 64, 500, [(1, "short 64"), (2, "short 32")]),
 ])
 def test_attend_bits_do_not_depend_on_the_width_of_the_tiles(H, dh, n, batches, rise, weighted):
-    """Tiles of 128, 192 and 256 queries add a row's products alike: a sample has the same bits alone and beside others.  (A stack relies on it in front of its merge.)"""
+    """Tiles of 128, 192 and 256 queries add a row's products alike, and so do the short-sample kernel's of 32 and 64: a sample has the same bits alone and beside others.
+    (A stack relies on it in front of its merge.)"""
     q, k, v = W.random_qkv(1100 + n, n, H, dh, "bf16")
     k = W.round_to(k * (1 + rise * np.arange(n, dtype=np.float32) / n)[:, None, None], "bf16")
     vis, counts = n // 5, (1 + np.arange(n // 2) % 37).astype(np.int32)
